@@ -2,7 +2,8 @@
 
 Argument marshalling only: every step of the computation runs inside the HIP library.  PyTorch
 is used to own device memory and to name the stream.  If the library is not built the import
-fails loudly - there is no fallback path.
+fails loudly - there is no fallback path.  The calls that a training or search loop makes go through csrc/marshal.cpp
+(_marshal.so), which does the same marshalling natively: in Python it was most of a small call's latency.
 """
 import ctypes
 import os
@@ -98,6 +99,11 @@ def _load():
 
 
 lib = _load()
+try:
+    from . import _marshal
+except ImportError as e:
+    raise ImportError("_marshal.so is not built (%s); run `python -m paper_1805_05225_amd.build`" % e) from e
+_marshal.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS})
 
 
 def strerror(status):
@@ -118,6 +124,13 @@ def _check(status):
         raise LstmError(status)
 
 
+def _checked(r):
+    """Results of a _marshal call, whose first element is the status."""
+    if r[0] != 0:
+        raise LstmError(r[0])
+    return r
+
+
 def make_desc(T, B, n_in, n, dtype, direction=1, flags=0):
     return LstmDesc(T, B, n_in, n, direction, dtype, flags, 0, 0, 0)
 
@@ -129,7 +142,7 @@ def query(desc, bidirectional):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_of(x):
@@ -141,30 +154,10 @@ def forward(x, W_x, W_h, b=None, h0=None, c0=None, seq_lens=None, *, bidirection
     """Allocates the outputs and calls lstm_fwd / blstm_fwd.  Returns a dict with y, c, hT, cT,
     reserve, workspace and the descriptor (everything the backward call needs).  poison: fill reserve and workspace
     with 0xFF bytes first."""
+    _, y, c, hT, cT, reserve, workspace, rb = _checked(_marshal.forward(
+        x, W_x, W_h, b, h0, c0, seq_lens, bidirectional, direction, flags, workspace, want_c, want_state, poison, _stream()))
     T, B, n_in = x.shape
-    n = W_h.shape[-2]
-    D = 2 if bidirectional else 1
-    dev = x.device
-    desc = make_desc(T, B, n_in, n, _dtype_of(x), direction, flags)
-    rb, wb = query(desc, bidirectional)
-    infer = bool(flags & FLAG_INFERENCE)
-    reserve = None if infer else torch.empty(rb, dtype=torch.uint8, device=dev)
-    if workspace is None or workspace.numel() < wb:
-        workspace = torch.empty(wb, dtype=torch.uint8, device=dev)
-    if poison:          # tests: every byte the library has not written reads as NaN
-        workspace.fill_(0xFF)
-        if reserve is not None:
-            reserve.fill_(0xFF)
-    desc.reserve_bytes = 0 if infer else rb
-    desc.workspace_bytes = workspace.numel()
-    y = torch.empty(T, B, D * n, dtype=x.dtype, device=dev)
-    shp = (D, B, n) if bidirectional else (B, n)
-    c = torch.empty((D, T, B, n) if bidirectional else (T, B, n), dtype=torch.float32, device=dev) if (want_c or not infer) else None
-    hT = torch.empty(shp, dtype=torch.float32, device=dev) if want_state else None
-    cT = torch.empty(shp, dtype=torch.float32, device=dev) if want_state else None
-    fn = lib.blstm_fwd if bidirectional else lib.lstm_fwd
-    _check(fn(ctypes.byref(desc), _ptr(x), _ptr(W_x), _ptr(W_h), _ptr(b), _ptr(h0), _ptr(c0), _ptr(seq_lens),
-              _ptr(y), _ptr(c), _ptr(hT), _ptr(cT), _ptr(reserve), _ptr(workspace), _stream()))
+    desc = LstmDesc(T, B, n_in, W_h.shape[-2], direction, _dtype_of(x), flags, 0, rb, workspace.numel())
     return dict(y=y, c=c, hT=hT, cT=cT, reserve=reserve, workspace=workspace, desc=desc, bidirectional=bidirectional)
 
 
@@ -172,62 +165,33 @@ def backward(fwd, x, W_x, W_h, h0, c0, seq_lens, dy, dhT=None, dcT=None, *, want
              accumulate_into=None):
     """Allocates the gradients and calls lstm_bwd / blstm_bwd with the buffers of `forward`'s result."""
     desc = fwd["desc"]
-    bidirectional = fwd["bidirectional"]
-    T, B, n_in = x.shape
-    n = W_h.shape[-2]
-    dev = x.device
+    dW_x = dW_h = db = None
     if accumulate_into is not None:
         dW_x, dW_h, db = accumulate_into
         desc = LstmDesc(desc.T, desc.B, desc.n_in, desc.n, desc.direction, desc.dtype, desc.flags | FLAG_ACCUMULATE, 0,
                         desc.reserve_bytes, desc.workspace_bytes)
-    else:
-        dW_x = torch.empty(W_x.shape, dtype=torch.float32, device=dev)
-        dW_h = torch.empty(W_h.shape, dtype=torch.float32, device=dev)
-        db = torch.empty(W_x.shape[:-2] + (4 * n,), dtype=torch.float32, device=dev)
-    dx = torch.empty_like(x) if want_dx else None
-    shp = (2, B, n) if bidirectional else (B, n)
-    dh0 = torch.empty(shp, dtype=torch.float32, device=dev) if want_dstate else None
-    dc0 = torch.empty(shp, dtype=torch.float32, device=dev) if want_dstate else None
-    fn = lib.blstm_bwd if bidirectional else lib.lstm_bwd
-    _check(fn(ctypes.byref(desc), _ptr(x), _ptr(W_x), _ptr(W_h), _ptr(h0), _ptr(c0), _ptr(seq_lens),
-              _ptr(fwd["y"]), _ptr(fwd["c"]), _ptr(fwd["reserve"]), _ptr(dy), _ptr(dhT), _ptr(dcT),
-              _ptr(dx), _ptr(dW_x), _ptr(dW_h), _ptr(db), _ptr(dh0), _ptr(dc0), _ptr(fwd["workspace"]), _stream()))
+    _, dx, dW_x, dW_h, db, dh0, dc0 = _checked(_marshal.backward(
+        ctypes.addressof(desc), fwd["bidirectional"], x, W_x, W_h, h0, c0, seq_lens, fwd["y"], fwd["c"], fwd["reserve"], dy, dhT, dcT,
+        dW_x, dW_h, db, want_dx, want_dstate, fwd["workspace"], _stream()))
     return dict(dx=dx, dW_x=dW_x, dW_h=dW_h, db=db, dh0=dh0, dc0=dc0)
 
 
 def gemm(A, B, *, a_kcontig, b_kcontig, M, N, K, out_dtype=torch.float32, bias=None, C=None, accumulate=False,
          lens=None, Bt=1, T=0):
     """C[M,N] (+)= A B + bias through lstm_gemm; A and B are 2-D tensors in the stated storage order."""
-    in_bf16 = A.dtype == torch.bfloat16
-    if C is None:
-        C = torch.empty(M, N, dtype=out_dtype, device=A.device)
-    _check(lib.lstm_gemm(int(in_bf16), int(C.dtype == torch.bfloat16), int(a_kcontig), int(b_kcontig), M, N, K,
-                         _ptr(A), A.stride(0), _ptr(B), B.stride(0), _ptr(C), C.stride(0), _ptr(bias), int(accumulate),
-                         _ptr(lens), Bt, T, _stream()))
-    return C
+    return _checked(_marshal.gemm(A, B, C, bias, lens, a_kcontig, b_kcontig, M, N, K, accumulate, Bt, T, out_dtype == torch.bfloat16, _stream()))[1]
 
 
 def time_pool_fwd(y, seq_lens, pool, *, want_arg=True):
     """Max-pooling in time of y [T, B, F] (float or bfloat16) with windows of `pool` frames inside every sequence.
     -> dict(out [T', B, F], lens [B] int32, arg [T', B, F] uint8 or None)."""
-    T, B, F = y.shape
-    assert y.stride(2) == 1 and y.stride(0) == B * y.stride(1)
-    Tp = -(-T // pool)
-    out = torch.empty(Tp, B, F, dtype=y.dtype, device=y.device)
-    arg = torch.empty(Tp, B, F, dtype=torch.uint8, device=y.device) if want_arg else None
-    lens_out = torch.empty(B, dtype=torch.int32, device=y.device)
-    _check(lib.lstm_time_pool_fwd(_dtype_of(y), T, B, F, pool, y.data_ptr(), y.stride(1), _ptr(seq_lens), _ptr(out), F, _ptr(arg),
-                                  _ptr(lens_out), _stream()))
-    return dict(out=out, lens=lens_out, arg=arg)
+    _, out, lens, arg = _checked(_marshal.time_pool_fwd(y, seq_lens, pool, want_arg, _stream()))
+    return dict(out=out, lens=lens, arg=arg)
 
 
 def time_pool_bwd(dout, arg, seq_lens, pool, T):
     """Gradient of time_pool_fwd: dy [T, B, F] from dout [T', B, F]."""
-    Tp, B, F = dout.shape
-    assert dout.is_contiguous()
-    dy = torch.empty(T, B, F, dtype=dout.dtype, device=dout.device)
-    _check(lib.lstm_time_pool_bwd(_dtype_of(dout), T, B, F, pool, _ptr(dout), F, _ptr(arg), _ptr(seq_lens), _ptr(dy), F, _stream()))
-    return dy
+    return _checked(_marshal.time_pool_bwd(dout, arg, seq_lens, pool, T, _stream()))[1]
 
 
 def attention_query(S, Q, beam, A, E, n):
@@ -242,57 +206,22 @@ def attention_step(enc, enc_ctx, src_lens, beam, s, W_s, b_s, w_fb, b_fb, v, b_e
     """One attention step through lstm_attention_step.  enc [S,Q,E], enc_ctx [S,Q,A], s [B,n] (a view with a row stride is
     fine), W_s [A,n] bfloat16; b_s, w_fb, b_fb, v float [A]; accum float [B,S]; att: optional bfloat16 [B,>=E] view to write into.
     -> dict(a, accum, att, workspace)."""
-    S, Q, E = enc.shape
-    A = enc_ctx.shape[2]
-    B, n = s.shape
-    d = attention_query(S, Q, beam, A, E, n)
-    if workspace is None or workspace.numel() < d.workspace_bytes:
-        workspace = torch.empty(d.workspace_bytes, dtype=torch.uint8, device=enc.device)
-    d.workspace_bytes = workspace.numel()
-    if att is None:
-        att = torch.empty(B, E, dtype=torch.bfloat16, device=enc.device)
-    a = torch.empty(B, S, dtype=torch.float32, device=enc.device) if want_a else None
-    accum_out = torch.empty(B, S, dtype=torch.float32, device=enc.device)
-    assert enc.is_contiguous() and enc_ctx.is_contiguous() and accum.is_contiguous() and s.stride(1) == 1 and att.stride(1) == 1
-    _check(lib.lstm_attention_step(ctypes.byref(d), _ptr(enc), _ptr(enc_ctx), _ptr(src_lens), s.data_ptr(), s.stride(0), _ptr(W_s), _ptr(b_s),
-                                   _ptr(w_fb), _ptr(b_fb), _ptr(v), float(b_e), _ptr(accum), _ptr(accum_out), _ptr(a), att.data_ptr(),
-                                   att.stride(0), _ptr(workspace), _stream()))
+    _, a, accum_out, att, workspace = _checked(_marshal.attention_step(
+        enc, enc_ctx, src_lens, beam, s, W_s, b_s, w_fb, b_fb, v, b_e, accum, att, workspace, want_a, _stream()))
     return dict(a=a, accum=accum_out, att=att, workspace=workspace)
 
 
 def readout(s, trg, att, W_r, b_r, *, out=None, workspace=None, flags=0):
     """out = relu([s | trg | att] W_r^T + b_r) through lstm_readout; s [B,n], trg [B,n_trg], att [B,E] bfloat16 (views with a
     row stride are fine), W_r [R, n+n_trg+E] bfloat16, b_r float [R]."""
-    B, n = s.shape
-    nt, E, R = trg.shape[1], att.shape[1], W_r.shape[0]
-    need = ctypes.c_uint64(0)
-    _check(lib.lstm_readout_query(B, R, n, nt, E, ctypes.byref(need)))
-    if workspace is None or workspace.numel() < need.value:
-        workspace = torch.empty(need.value, dtype=torch.uint8, device=s.device)
-    if out is None:
-        out = torch.empty(B, R, dtype=torch.bfloat16, device=s.device)
-    assert s.stride(1) == 1 and trg.stride(1) == 1 and att.stride(1) == 1 and W_r.is_contiguous() and out.stride(1) == 1
-    _check(lib.lstm_readout(flags, B, R, s.data_ptr(), s.stride(0), n, trg.data_ptr(), trg.stride(0), nt, att.data_ptr(), att.stride(0), E,
-                            _ptr(W_r), _ptr(b_r), out.data_ptr(), out.stride(0), _ptr(workspace), workspace.numel(), _stream()))
-    return out
+    return _checked(_marshal.readout(s, trg, att, W_r, b_r, out, workspace, flags, _stream()))[1]
 
 
 def beam_step(logits, score, *, workspace=None):
     """One beam-search step through lstm_beam_step.  logits float [Q*beam, V] (row stride allowed), score float [Q, beam]
     -> dict(score [Q,beam] float, src [Q,beam] int32, label [Q,beam] int32, workspace)."""
-    Q, beam = score.shape
-    V = logits.shape[1]
-    need = ctypes.c_uint64(0)
-    _check(lib.lstm_beam_query(Q, beam, V, ctypes.byref(need)))
-    if workspace is None or workspace.numel() < need.value:
-        workspace = torch.empty(need.value, dtype=torch.uint8, device=logits.device)
-    out = torch.empty(Q, beam, dtype=torch.float32, device=logits.device)
-    src = torch.empty(Q, beam, dtype=torch.int32, device=logits.device)
-    label = torch.empty(Q, beam, dtype=torch.int32, device=logits.device)
-    assert logits.stride(1) == 1 and logits.dtype == torch.float32 and score.dtype == torch.float32
-    _check(lib.lstm_beam_step(Q, beam, V, logits.data_ptr(), logits.stride(0), _ptr(score), _ptr(out), _ptr(src), _ptr(label),
-                              _ptr(workspace), workspace.numel(), _stream()))
-    return dict(score=out, src=src, label=label, workspace=workspace)
+    _, score, src, label, workspace = _checked(_marshal.beam_step(logits, score, workspace, _stream()))
+    return dict(score=score, src=src, label=label, workspace=workspace)
 
 
 def beam_step_static(logits, score):
@@ -330,22 +259,15 @@ def gather_items(pairs):
 
 def beam_gather_many(states, src, outs=None):
     """beam_gather for up to 8 state arrays in one launch (lstm_beam_gather_many); `outs` may be views with a larger row stride."""
-    Q, beam = src.shape
     if outs is None:
         outs = [torch.empty_like(a) for a in states]
-    arr = gather_items(list(zip(states, outs)))
-    _check(lib.lstm_beam_gather_many(Q, beam, len(arr), arr, _ptr(src), _stream()))
+    _check(_marshal.gather_many(states, outs, src, _stream()))
     return outs
 
 
 def embed(label, W_trg, b_trg=None, *, out=None):
     """trg = W_trg[label] + b_trg through lstm_embed; label int32 (any shape), W_trg [V, n] bfloat16 -> [label.numel(), n] bfloat16."""
-    V, n = W_trg.shape
-    B = label.numel()
-    if out is None:
-        out = torch.empty(B, n, dtype=torch.bfloat16, device=W_trg.device)
-    _check(lib.lstm_embed(B, n, V, _ptr(label), _ptr(W_trg), _ptr(b_trg), out.data_ptr(), out.stride(0), _stream()))
-    return out
+    return _checked(_marshal.embed(label, W_trg, b_trg, out, _stream()))[1]
 
 
 PHASES = ("prep", "gemm_zx", "loop_fwd", "loop_bwd", "gemm_dx", "gemm_dwx", "gemm_dwh", "db")

@@ -1,16 +1,19 @@
 """Builds the HIP library in-tree:  python -m paper_1805_05225_amd.build
 
 Each translation unit is compiled for gfx950 with hipcc (objects are built in parallel), then
-linked into paper_1805_05225_amd/libmi355x_lstm.so.  No GPU is needed to build.
+linked into paper_1805_05225_amd/libmi355x_lstm.so; the host side of the Python binding (no device code) is compiled
+with g++ into paper_1805_05225_amd/_marshal.so.  No GPU is needed to build.
 """
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmi355x_lstm.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["gemm.hip", "gemm_nt.hip", "gemm_skinny.hip", "gemm_float.hip", "recurrent.hip", "persistent.hip", "single_step.hip", "time_pool.hip", "attention.hip", "beam.hip", "lstm_abi.hip"]
 # packed-FP32 instructions are switched off: some of their forms have produced wrong results on the test machines
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -26,14 +29,28 @@ def _compile(src):
     return obj
 
 
+def _marshal():
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    inc = ["-I" + d for d in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"])]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), *inc,
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for marshal.cpp:\n%s\n%s" % (r.stdout, r.stderr))
+
+
 def build(verbose=True):
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        marshal = ex.submit(_marshal)
         objs = list(ex.map(_compile, SOURCES))
+        marshal.result()
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
     if verbose:
-        print("built", LIB)
+        print("built", LIB, "and", MARSHAL)
     return LIB
 
 
