@@ -14,6 +14,7 @@
 
 #include "../../include/lstm_abi.h"
 #include "common.h"
+#include "gemm_skinny.h"
 #include "recurrent_dev.h"
 #include <type_traits>
 
@@ -115,6 +116,66 @@ __global__ __launch_bounds__(256) void att_energy_kernel(const uint16_t* __restr
   }
 }
 
+// The same for few sentences, where the form above would put a handful of work-groups on the device (one sentence of 27 positions: 14,
+// each with four dependent rounds of loads for twelve hypotheses: 11 us): one position and four hypotheses per work-group,
+// all loads of 1024 features in flight at once.  At the benchmark's 64 sentences it is the slower one (every ctx row is read
+// once per four hypotheses).
+constexpr int kFewHyp = 4;
+__global__ __launch_bounds__(256) void att_energy_few_kernel(const uint16_t* __restrict__ ctx, const float* __restrict__ s_tr,
+                                                              const float* __restrict__ accum, const float* __restrict__ w_fb,
+                                                              const float* __restrict__ b_fb, const float* __restrict__ v, float b_e,
+                                                              const int* __restrict__ lens, float* __restrict__ e, int S, int Q, int beam,
+                                                              int A) {
+  __shared__ float part[4][kFewHyp];
+  const int q = blockIdx.y, j = blockIdx.x, r0 = blockIdx.z * kFewHyp, tid = threadIdx.x;
+  const float* ap = accum + ((long)q * beam) * S + j;
+  const uint16_t* cp = ctx + ((long)j * Q + q) * A;
+  const float* sp = s_tr + (long)q * beam * A;
+  constexpr float kScale = 2.8853900817779268f;                // 2 log2(e)
+  constexpr int kU = 4;                                        // features per lane in a round
+  if (j >= src_len(lens, q, S)) return;
+  float ac[kFewHyp], sum[kFewHyp];
+  int row[kFewHyp];
+#pragma unroll
+  for (int r = 0; r < kFewHyp; ++r) {
+    row[r] = min(r0 + r, beam - 1);
+    ac[r] = ap[(long)row[r] * S];
+    sum[r] = 0.f;
+  }
+  float vsum = 0.f;
+  for (int k0 = tid; k0 < A; k0 += 256 * kU) {
+    float c[kU], st[kU][kFewHyp], bf[kU], wf[kU], vk[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int k = min(k0 + 256 * u, A - 1);
+      c[u] = bf_bits2f(cp[k]);
+#pragma unroll
+      for (int r = 0; r < kFewHyp; ++r) st[u][r] = sp[(long)row[r] * A + k];
+      bf[u] = b_fb[k]; wf[u] = w_fb[k]; vk[u] = v[k];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const float vu = k0 + 256 * u < A ? vk[u] : 0.f, cu = kScale * (c[u] + bf[u]), wu = kScale * wf[u];
+      vsum += vu;
+#pragma unroll
+      for (int r = 0; r < kFewHyp; ++r) {
+        const float x2 = __builtin_fmaf(ac[r], wu, cu) + kScale * st[u][r];
+        sum[r] = __builtin_fmaf(__builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(x2) + 1.f), -2.f * vu, sum[r]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kFewHyp; ++r) {
+    float t = sum[r] + vsum;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+    if ((tid & 63) == 0) part[tid >> 6][r] = t;
+  }
+  __syncthreads();
+  if (tid < kFewHyp && r0 + tid < beam)
+    e[((long)q * beam + r0 + tid) * S + j] = part[0][tid] + part[1][tid] + part[2][tid] + part[3][tid] + b_e;
+}
+
 // a[r, :] = softmax of e[r, :] over the valid positions, accum' = accum + a, and att[r] = sum_j a[r][j] H[j][q], for
 // the hypotheses of sentence q = blockIdx.y and the 128 features from blockIdx.x * 128.  Every work-group of a sentence
 // works the softmax out for itself (beam x S exponentials from one round of loads: cheaper than a launch of its own and
@@ -132,6 +193,17 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
   const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int L = src_len(lens, q, S);
   const int nb4 = (beam + 3) >> 2;                              // groups of four hypotheses
+  const int f = (blockIdx.x * 64 + lane) * 2;
+  const bool live = f < E;
+  const uint16_t* Hq = H + (long)q * E + (live ? f : 0);        // E even, rows 4-byte aligned
+  const long jstride = (long)Q * E;
+  constexpr int kU = 8;
+  // the first kU positions of this wavefront are asked for before the weights are worked out
+  unsigned hh[kU];
+  if (L > 0) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) hh[u] = *(const unsigned*)(Hq + min(wave + 4 * u, L - 1) * jstride);
+  }
   {
     const int r = tid >> 4, l = tid & 15;                       // beam <= 16: one group of 16 lanes per hypothesis
     const long row = (long)q * beam + r;
@@ -169,18 +241,14 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
     }
   }
   __syncthreads();
-  const int f = (blockIdx.x * 64 + lane) * 2;
-  const bool live = f < E;
   float acc[kMaxBeam][2];
 #pragma unroll
   for (int r = 0; r < kMaxBeam; ++r) acc[r][0] = acc[r][1] = 0.f;
-  const uint16_t* Hq = H + (long)q * E + (live ? f : 0);        // E even, rows 4-byte aligned
-  const long jstride = (long)Q * E;
-  constexpr int kU = 8;
   for (int j = wave; j < L; j += 4 * kU) {
-    unsigned hh[kU];
+    if (j != wave) {
 #pragma unroll
-    for (int u = 0; u < kU; ++u) hh[u] = *(const unsigned*)(Hq + min(j + 4 * u, L - 1) * jstride);
+      for (int u = 0; u < kU; ++u) hh[u] = *(const unsigned*)(Hq + min(j + 4 * u, L - 1) * jstride);
+    }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
       if (j + 4 * u >= L) break;                                // uniform within the wavefront
@@ -321,7 +389,11 @@ int lstm_attention_step(const lstm_att_desc* d, const void* enc, const void* enc
   float* parts = (float*)(ws + up256((size_t)B * d->A * 4) + up256((size_t)B * d->S * 4));
   const int ks = ranges_for(B, d->A, d->n);
   if (linear_rows(s, ld_s, W_s, d->n, b_s, s_tr, B, d->A, d->n, parts, ks, st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
-  hipLaunchKernelGGL(att_energy_kernel, dim3((d->S + kJB - 1) / kJB, d->Q), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr, accum_in, w_fb,
+  if ((long)d->Q * d->S < 512)          // fewer work-groups than the device has compute units in the form for many sentences
+    hipLaunchKernelGGL(att_energy_few_kernel, dim3(d->S, d->Q, (d->beam + kFewHyp - 1) / kFewHyp), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr,
+                       accum_in, w_fb, b_fb, v, b_e, src_lens, e, d->S, d->Q, d->beam, d->A);
+  else
+    hipLaunchKernelGGL(att_energy_kernel, dim3((d->S + kJB - 1) / kJB, d->Q), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr, accum_in, w_fb,
                      b_fb, v, b_e, src_lens, e, d->S, d->Q, d->beam, d->A);
   static std::atomic<unsigned long long> attr_set{0};            // S = 1024 needs 64 KiB of dynamic LDS beside the static arrays
   if (once_per_device(attr_set, [] {
@@ -350,8 +422,8 @@ int lstm_readout_query(int B, int R, int n, int n_trg, int E, uint64_t* workspac
   if (rc) return rc;
   const long Kp = readout_kpad(n, n_trg, E);
   const int ks = ranges_for(B, R, (int)Kp);
-  *workspace_bytes = 256 + up256((size_t)R * Kp * 2) + up256((size_t)B * Kp * 2) + up256((size_t)B * R * 4) +
-                     (ks > 1 ? up256((size_t)ks * B * R * 4) : 0);
+  *workspace_bytes = 256 + up256((size_t)R * Kp * 2) + up256(frag_bytes(R, Kp)) + up256(std::max((size_t)B * Kp * 2, frag_bytes(B, Kp))) +
+                     up256((size_t)B * R * 4) + (ks > 1 ? up256((size_t)ks * B * R * 4) : 0);
   return LSTM_OK;
 }
 
@@ -373,13 +445,24 @@ int lstm_readout(int flags, int B, int R, const void* s, int64_t ld_s, int n, co
   const int K = n + n_trg + E;
   const long Kp = readout_kpad(n, n_trg, E);
   char* ws = (char*)(((uintptr_t)workspace + 255) / 256 * 256);
-  // workspace: W_r with its rows padded with zeros to whole 16-byte chunks (kept between calls under
-  // LSTM_FLAG_WEIGHTS_PACKED), the concatenated inputs padded the same way, the float product, the K ranges' parts
+  // workspace: W_r with its rows padded with zeros to whole 16-byte chunks and in fragment order (both kept between calls under
+  // LSTM_FLAG_WEIGHTS_PACKED, which says nothing about B), the concatenated inputs, the float product, the K ranges' parts
   uint16_t* Wp = (uint16_t*)ws;
-  uint16_t* cat = (uint16_t*)(ws + up256((size_t)R * Kp * 2));
-  float* z = (float*)((char*)cat + up256((size_t)B * Kp * 2));
+  char* Wf = ws + up256((size_t)R * Kp * 2);
+  uint16_t* cat = (uint16_t*)(Wf + up256(frag_bytes(R, Kp)));
+  float* z = (float*)((char*)cat + up256(std::max((size_t)B * Kp * 2, frag_bytes(B, Kp))));
   float* parts = (float*)((char*)z + up256((size_t)B * R * 4));
-  if (!(flags & LSTM_FLAG_WEIGHTS_PACKED) && launch_pad_rows(W_r, Wp, R, K, (int)Kp, st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
+  if (!(flags & LSTM_FLAG_WEIGHTS_PACKED) && (launch_pad_rows(W_r, Wp, R, K, (int)Kp, st) != hipSuccess || launch_pack_rows_frag(W_r, Wf, R, K, st) != hipSuccess)) {
+    (void)hipGetLastError();
+    return LSTM_ERR_HIP;
+  }
+  if (B <= kFewReadoutRows) {
+    if (launch_few_readout(s, (long)ld_s, n, trg, (long)ld_trg, n_trg, att, (long)ld_att, E, cat, Wf, b_r, out, (long)ld_out, B, R, st) != hipSuccess) {
+      (void)hipGetLastError();
+      return LSTM_ERR_HIP;
+    }
+    return LSTM_OK;
+  }
   if (launch_concat3((const uint16_t*)s, (long)ld_s, n, (const uint16_t*)trg, (long)ld_trg, n_trg, (const uint16_t*)att, (long)ld_att, E, cat,
                      Kp, B, st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
   {                                  // few rows: bias, max(0, .) and the rounding happen in the product's epilogue

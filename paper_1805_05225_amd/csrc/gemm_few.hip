@@ -1,0 +1,453 @@
+// Products with a handful of rows: the decoder step of one sentence (beam 12: 12 rows) or of a few.
+//
+//     C[M,N] = A[M,K] B[N,K]^T (+ bias, max(0, .)), or the LSTM cell of the stepped decoder in the epilogue
+//
+// With M up to a few dozen the product is a read of B: 29 MB of packed cell weights at n_in = 2620, n = 1000 against
+// 0.3 GFLOP at 12 rows, i.e. 6 us at the rate a large copy reaches.  The tiles of gemm_skinny.hip (96 rows x 128 columns)
+// put such a product on 32 compute units, each of which pulls its 0.9 MB through a pipeline of 64-wide stages: 31 us.
+// Here a work-group owns `ct` <= 16 columns (for the cell: the four gates of four units) and up to sixteen wavefronts share its K,
+// so that N = 4000 gives 250 work-groups and N = 1000 still does (ct = 4; the MFMA's other columns repeat them, the matrix
+// cores have nothing else to do).  Operands go from memory straight into MFMA fragments - nothing is shared between
+// wavefronts, so there is nothing to stage - with everything a wavefront needs of a small K in flight at once; the
+// wavefronts' sums meet in LDS.  Rows come in blocks of 16 MT (grid y): B is read once per block.
+//
+// FRAG: both operands lie in memory in fragment order, [tile of 16 rows / columns][chunk of 32 k][lane] x 16 bytes (packed that
+// way once per search for the weights, by the concatenation for A): a wavefront's load is 1 KiB in a row.  Otherwise they are
+// row-major and k-contiguous, rows 16-byte aligned; neighbouring lanes then sit in different rows, each group of four
+// touches four cache lines, and the load path takes four times as long - which is why the decoder's two large products
+// are packed.  Both bfloat16, K a multiple of 8.
+#include "recurrent_dev.h"
+#include "gemm_skinny.h"
+
+namespace lstm {
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+constexpr int kBufFlags = 0x00020000;   // raw buffer descriptor word 3 for gfx9-family devices
+constexpr unsigned kParked = 0x7ffffff0u;
+
+__device__ __forceinline__ f32x4 mma16(u32x4 a, u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Pieces of up to three matrices side by side, [x0 | x1 | x2]: piece i covers columns k_i .. k_i + len_i - 1 of the result, whatever
+// lies between is zero; x2 may be float (rounded where it is read) and NULL (zeros).
+struct ConcatArgs {
+  const uint16_t* x0; const uint16_t* x1; const void* x2;
+  long ld0, ld1, ld2;
+  int k0, len0, k1, len1, k2, len2;
+  int B, nkc; long s2;                   // rows; chunks of 32 columns; elements between the directions' x2
+  int cut[4];                            // groups of eight columns in which a piece begins or ends (-1: none)
+  void find_cuts() {
+    int have = 0;
+    for (int e : {k0 + len0, k1 + len1, k2, k2 + len2}) {
+      bool known = e % 8 == 0;
+      for (int i = 0; i < have; ++i) known |= cut[i] == e / 8;
+      if (!known) cut[have++] = e / 8;
+    }
+    while (have < 4) cut[have++] = -1;
+  }
+};
+typedef uint4 __attribute__((aligned(2))) uint4_u;
+typedef float4 __attribute__((aligned(4))) float4_u;
+__device__ __forceinline__ uint4 frag_pack(const uint16_t (&v)[8]) {
+  return make_uint4(v[0] | ((unsigned)v[1] << 16), v[2] | ((unsigned)v[3] << 16), v[4] | ((unsigned)v[5] << 16), v[6] | ((unsigned)v[7] << 16));
+}
+// eight floats rounded to bfloat16 (to nearest even)
+__device__ __forceinline__ uint4 frag_pack(const float4& lo, const float4& hi) {
+  typedef __attribute__((ext_vector_type(8))) float f32x8;
+  return __builtin_bit_cast(uint4, __builtin_convertvector((f32x8){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}, bf16x8));
+}
+// columns k .. k + 7 of a row, one by one: where a piece begins or ends inside them
+template <bool F32>
+__device__ __forceinline__ uint4 concat_slow(const ConcatArgs& a, int z, int row, int k) {
+  uint16_t v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int c = k + e;
+    v[e] = 0;
+    if (c >= a.k0 && c < a.k0 + a.len0) v[e] = a.x0[row * a.ld0 + c - a.k0];
+    else if (c >= a.k1 && c < a.k1 + a.len1) v[e] = a.x1[row * a.ld1 + c - a.k1];
+    else if (a.x2 && c >= a.k2 && c < a.k2 + a.len2)
+      v[e] = F32 ? f2bf_bits(((const float*)a.x2)[a.s2 * z + row * a.ld2 + c - a.k2]) : ((const uint16_t*)a.x2)[row * a.ld2 + c - a.k2];
+  }
+  return frag_pack(v);
+}
+
+// Sums of the wavefronts' shares, red[wavefront][row tile][row][column], and what is done with them.
+template <int MT, int NW, bool CELL>
+__device__ __forceinline__ void few_epilogue(const SkinnyArgs& g, int ct, const float (&red)[NW][MT][16][17]) {
+  const int tid = threadIdx.x, z = blockIdx.z, m0 = blockIdx.y * (16 * MT), n0 = blockIdx.x * ct;
+  if constexpr (CELL) {
+    // thread -> (row, unit of four)
+    for (int idx = tid; idx < MT * 64; idx += 64 * NW) {
+      const int u = idx & 3, row = idx >> 2, b = m0 + row, j = blockIdx.x * 4 + u, n = g.n;
+      if (b >= g.M || j >= n) continue;
+      const long si = ((long)z * g.M + b) * n + j;
+      const bool valid = clamp_len(g.lens, b, 1) > 0;
+      float c = g.c_in ? g.c_in[si] : 0.f, h = 0.f;
+      if (valid) {
+        float zh[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float s = g.bias ? g.bias[(long)z * 4 * n + q * n + j] : 0.f;
+#pragma unroll
+          for (int w = 0; w < NW; ++w) s += red[w][row >> 4][row & 15][4 * q + u];
+          zh[q] = s;
+        }
+        const float zx[4] = {0.f, 0.f, 0.f, 0.f};
+        const CellOut o = lstm_cell(zh, zx, c);
+        c = o.c; h = o.h;
+      }
+      g.y[(long)b * g.ldy + (long)z * n + j] = f2bf_bits(h);
+      if (g.cs) g.cs[si] = c;
+      if (g.c_out) g.c_out[si] = c;
+      if (g.h_out) g.h_out[si] = valid ? h : (g.h_in ? g.h_in[si] : 0.f);
+    }
+  } else {
+    for (int idx = tid; idx < MT * 256; idx += 64 * NW) {
+      const int cc = idx & 15, row = idx >> 4, m = m0 + row, c = n0 + cc;
+      if (cc >= ct || m >= g.M || c >= g.N) continue;
+      float s = g.bias ? g.bias[g.sbiasz * z + c] : 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s += red[w][row >> 4][row & 15][cc];
+      if (g.relu) s = s > 0.f ? s : 0.f;
+      const long off = g.sCz * z + (long)m * g.ldc + c;
+      if (g.out_bf16) ((uint16_t*)g.C)[off] = f2bf_bits(s);
+      else ((float*)g.C)[off] = s;
+    }
+  }
+}
+
+// MT row tiles of 16 per work-group, NW wavefronts, U k-chunks (of 32) per wavefront in a batch; with DB the next batch's loads
+// are in flight while a batch is multiplied.
+template <int MT, int NW, int U, bool DB, bool FRAG, bool CELL>
+__global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
+  static_assert(U % 2 == 0, "chunks come in pairs: 128 bytes of a row");
+  __shared__ float red[NW][MT][16][17];                        // [wavefront][row tile][row][column]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, gk = lane >> 4;
+  const int z = blockIdx.z, m0 = blockIdx.y * (16 * MT), n0 = blockIdx.x * ct;
+  const int K = g.K, npair = (K + 63) / 64;                    // pairs of chunks: 64 k
+
+  // Columns past ct repeat others: quads of lanes stay on the same lines.  Rows past M: the last one again (row-major), or whatever
+  // the packed rows hold there; both end in output rows that are not stored.
+  const int col = r16 & (ct - 1);
+  const int nkc = (K + 31) / 32;
+  const long a_bytes = FRAG ? (long)((g.M + 15) / 16) * nkc * 1024 : (long)g.M * g.lda * 2;
+  const long b_bytes = FRAG ? (long)((CELL ? (g.n + 3) / 4 : (g.N + 15) / 16)) * nkc * 1024 : (long)g.N * g.ldb * 2;
+  const auto rec = [](long bytes) { return (int)(bytes > 0x7fffff00L ? 0x7fffff00L : bytes); };
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)(g.A + g.sAz * z * 2), 0, rec(a_bytes), kBufFlags);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)(g.B + g.sBz * z * 2), 0, rec(b_bytes), kBufFlags);
+  constexpr unsigned kChunk = FRAG ? 1024u : 64u;              // bytes from one chunk of a lane's row to the next
+  unsigned ao[MT], bo;
+  if constexpr (FRAG) {
+    bo = (unsigned)((long)(CELL ? (int)blockIdx.x : n0 >> 4) * nkc * 1024) + (unsigned)(gk * 16 + (n0 & 15) + col) * 16u;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) ao[i] = (unsigned)((long)min((m0 >> 4) + i, (g.M - 1) >> 4) * nkc * 1024) + (unsigned)lane * 16u;
+  } else {
+    bo = (unsigned)((long)min(n0 + col, g.N - 1) * g.ldb * 2) + gk * 16u;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) ao[i] = (unsigned)((long)min(m0 + 16 * i + r16, g.M - 1) * g.lda * 2) + gk * 16u;
+  }
+
+  f32x4 acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // every work-group reads all of A: those of an XCD start at different places, so that they do not ask its L2 for the same
+  // lines at the same time
+  const int rot = (int)(((long)((blockIdx.x >> 3) & 31) * npair) >> 5);
+  struct Batch { u32x4 a[U][MT], b[U]; };
+  // Chunk j of a batch that starts at pair p: pair p + NW (j / 2), half j % 2.  A chunk past K arrives as zeros (both operands:
+  // the other one may hold anything there).
+  auto load = [&](Batch& x, int p) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int q = p + NW * (j >> 1), kp = q + rot;
+      const int kc = q < npair ? 2 * (kp < npair ? kp : kp - npair) + (j & 1) : 0x1000000;
+      const bool in = kc * 32 + gk * 8 < K;
+      x.b[j] = __builtin_amdgcn_raw_buffer_load_b128(rb, in ? bo + (unsigned)kc * kChunk : kParked, 0, 0);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) x.a[j][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, in ? ao[i] + (unsigned)kc * kChunk : kParked, 0, 0);
+    }
+  };
+  auto multiply = [&](const Batch& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[i] = mma16(x.a[j][i], x.b[j], acc[i]);
+  };
+  constexpr int kAdvance = NW * U / 2;                         // pairs per batch of all wavefronts
+  if constexpr (DB) {
+    Batch x, y;
+    int p = wave;
+    if (p < npair) {
+      load(x, p);
+      for (;;) {
+        if (p + kAdvance >= npair) { multiply(x); break; }
+        load(y, p + kAdvance);
+        multiply(x);
+        p += kAdvance;
+        if (p + kAdvance >= npair) { multiply(y); break; }
+        load(x, p + kAdvance);
+        multiply(y);
+        p += kAdvance;
+      }
+    }
+  } else {
+    Batch x;
+    for (int p = wave; p < npair; p += kAdvance) {
+      load(x, p);
+      __builtin_amdgcn_sched_barrier(0);                       // (all of them first: left alone the compiler keeps half in flight)
+      multiply(x);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][i][4 * gk + v][r16] = acc[i][v];
+  __syncthreads();
+
+  few_epilogue<MT, NW, CELL>(g, ct, red);
+}
+
+// The same for at most 16 rows with A taken from where its pieces lie, [x0 | x1 | x2]: no concatenation pass, whose launch
+// costs as much as half of this kernel (12 rows, K = 3624: concatenation 4.1 us + product 8.0).  A wavefront reads a chunk with four
+// neighbouring lanes per row (64 bytes in a row), turns it into fragment order through 1 KiB of LDS of its own - LDS
+// operations of a wavefront happen in order, so nothing has to be waited for - and the weights, asked for first, arrive
+// behind all of that.  B in fragment order, at most 16 * U * 32 values of k.
+template <int U, bool F32, bool CELL>
+__global__ __launch_bounds__(1024) void few_gather_kernel(SkinnyArgs g, ConcatArgs ca, int ct) {
+  constexpr int NW = 16, kHalf = U / 2;
+  __shared__ float red[NW][1][16][17];
+  __shared__ uint4 turn[NW][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, gk = lane >> 4, z = blockIdx.z, n0 = blockIdx.x * ct;
+  const int nkc = ca.nkc, npair = (nkc + 1) / 2;
+  const long b_bytes = (long)(CELL ? (g.n + 3) / 4 : (g.N + 15) / 16) * nkc * 1024;
+  const __amdgpu_buffer_rsrc_t rb =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(g.B + g.sBz * z * 2), 0, (int)(b_bytes > 0x7fffff00L ? 0x7fffff00L : b_bytes), kBufFlags);
+  const unsigned bo = (unsigned)((long)(CELL ? (int)blockIdx.x : n0 >> 4) * nkc * 1024) + (unsigned)(gk * 16 + (n0 & 15) + (r16 & (ct - 1))) * 16u;
+  const int rot = (int)(((long)((blockIdx.x >> 3) & 31) * npair) >> 5);      // (see few_kernel)
+  auto chunk = [&](int j) __attribute__((always_inline)) {     // chunk j of this wavefront; nkc or more: none
+    const int q = wave + NW * (j >> 1), kp = q + rot;
+    return q < npair ? 2 * (kp < npair ? kp : kp - npair) + (j & 1) : 0x1000000;
+  };
+  // Every lane loads twice 16 bytes: the two halves of eight floats, or the same eight bfloat16, or (nothing to read there, or a piece
+  // begins or ends inside the eight) the weights' first bytes, to be replaced by zeros.  A goes out in front of the weights:
+  // loads return in order, and A, out of L2, is turned while the weights are on their way.
+  const int row = lane >> 2, arow = min(row, g.M - 1);         // rows past M: the last one again
+  uint4 lo[U], hi[U];
+  unsigned as_float = 0u, as_zero = 0u;                        // a bit per chunk
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const int k = chunk(j) * 32 + (lane & 3) * 8;
+    const bool in0 = k >= ca.k0 && k + 8 <= ca.k0 + ca.len0, in1 = k >= ca.k1 && k + 8 <= ca.k1 + ca.len1;
+    const bool in2 = ca.x2 && k >= ca.k2 && k + 8 <= ca.k2 + ca.len2;
+    const char* p0 = (const char*)(ca.x0 + arow * ca.ld0 + (k - ca.k0));
+    const char* p1 = (const char*)(ca.x1 + arow * ca.ld1 + (k - ca.k1));
+    const char* p2 = F32 ? (const char*)((const float*)ca.x2 + ca.s2 * z + arow * ca.ld2 + (k - ca.k2))
+                         : (const char*)((const uint16_t*)ca.x2 + arow * ca.ld2 + (k - ca.k2));
+    const char* p = in0 ? p0 : in1 ? p1 : in2 ? p2 : (const char*)g.B;
+    lo[j] = *(const uint4_u*)p;
+    if (F32) hi[j] = *(const uint4_u*)(p + (in2 ? 16 : 0));
+    as_float |= (F32 && in2 ? 1u : 0u) << j;
+    as_zero |= (in0 || in1 || in2 ? 0u : 1u) << j;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  u32x4 b[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) b[j] = __builtin_amdgcn_raw_buffer_load_b128(rb, chunk(j) < nkc ? bo + (unsigned)chunk(j) * 1024u : kParked, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4 acc[1] = {(f32x4){0.f, 0.f, 0.f, 0.f}};
+  u32x4 a[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    uint4 v = lo[j];
+    if (F32 && ((as_float >> j) & 1u)) v = frag_pack(__builtin_bit_cast(float4, lo[j]), __builtin_bit_cast(float4, hi[j]));
+    if ((as_zero >> j) & 1u) v = make_uint4(0, 0, 0, 0);
+    turn[wave][(lane & 3) * 16 + row] = v;
+    asm volatile("" ::: "memory");
+    a[j] = __builtin_bit_cast(u32x4, turn[wave][lane]);
+    asm volatile("" ::: "memory");
+  }
+#pragma unroll
+  for (int j = 0; j < U; ++j) acc[0] = mma16(a[j], b[j], acc[0]);
+  // groups of eight k in which a piece begins or ends: a product of their own, the rest of the chunk zero
+  if (wave < 4 && ca.cut[wave] >= 0) {
+    const int g8 = ca.cut[wave];
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (gk == (g8 & 3)) v = concat_slow<F32>(ca, z, min(r16, g.M - 1), g8 * 8);
+    const u32x4 bx = __builtin_amdgcn_raw_buffer_load_b128(rb, bo + (unsigned)(g8 >> 2) * 1024u, 0, 0);
+    acc[0] = mma16(__builtin_bit_cast(u32x4, v), bx, acc[0]);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][0][4 * gk + v][r16] = acc[0][v];
+  __syncthreads();
+  few_epilogue<1, NW, CELL>(g, ct, red);
+}
+
+template <int MT, int NW, int U, bool DB, bool FRAG, bool CELL>
+hipError_t launch_as(const SkinnyArgs& a, int ct, int tiles_n, hipStream_t s) {
+  hipLaunchKernelGGL((few_kernel<MT, NW, U, DB, FRAG, CELL>), dim3(tiles_n, cdiv(a.M, 16 * MT), a.nz), dim3(64 * NW), 0, s, a, ct);
+  return hipGetLastError();
+}
+// Four wavefronts, eight chunks each, hold K = 1024 in one batch; a longer K takes sixteen.
+template <bool FRAG, bool CELL>
+hipError_t launch_rows(const SkinnyArgs& a, int ct, int tiles_n, hipStream_t s) {
+  const bool longk = a.K > 1024;
+  if (a.M <= 16) return longk ? launch_as<1, 16, 8, false, FRAG, CELL>(a, ct, tiles_n, s) : launch_as<1, 4, 8, false, FRAG, CELL>(a, ct, tiles_n, s);
+  if (a.M <= 32) return longk ? launch_as<2, 16, 4, true, FRAG, CELL>(a, ct, tiles_n, s) : launch_as<2, 4, 8, false, FRAG, CELL>(a, ct, tiles_n, s);
+  return longk ? launch_as<4, 16, 2, true, FRAG, CELL>(a, ct, tiles_n, s) : launch_as<4, 4, 8, false, FRAG, CELL>(a, ct, tiles_n, s);
+}
+
+// Weights of the stepped cell: tile t holds the gates of units 4 t .. 4 t + 3 (column 4 q + u), k runs over [x | 0 | h | 0].
+// A work-group turns 64 k x 64 units through LDS, so that W is read along its columns.
+__global__ __launch_bounds__(256) void pack_cell_frag_kernel(const uint16_t* Wx, const uint16_t* Wh, uint4* out, int n_in, int n_in_pad, int n, int nkc,
+                                                             int ntile) {
+  __shared__ uint16_t tile[64][66];                            // [k][unit]
+  const int d = blockIdx.z >> 2, q = blockIdx.z & 3, k0 = blockIdx.x * 64, u0 = blockIdx.y * 64, N4 = 4 * n;
+  Wx += (long)d * n_in * N4;
+  Wh += (long)d * n * N4;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6, j = u0 + tx;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int k = k0 + ty + 4 * i;
+    uint16_t v = 0;
+    if (j < n) {
+      if (k < n_in) v = Wx[(long)k * N4 + q * n + j];
+      else if (k >= n_in_pad && k < n_in_pad + n) v = Wh[(long)(k - n_in_pad) * N4 + q * n + j];
+    }
+    tile[ty + 4 * i][tx] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int rep = 0; rep < 2; ++rep) {                          // 64 units x 8 groups of eight k
+    const int idx = threadIdx.x + 256 * rep, u = idx & 63, g8 = idx >> 6, kc = k0 / 32 + (g8 >> 2), unit = u0 + u, t = unit >> 2;
+    if (t >= ntile || kc >= nkc) continue;
+    uint16_t v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = tile[g8 * 8 + e][u];
+    out[(((long)d * ntile + t) * nkc + kc) * 64 + (g8 & 3) * 16 + q * 4 + (unit & 3)] = frag_pack(v);
+  }
+}
+
+// rows of W[R][K] -> fragment order
+__global__ void pack_rows_frag_kernel(const uint16_t* W, uint4* out, int R, int K, int nkc, long total) {
+  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= total) return;
+  const int lane = (int)(idx & 63), kc = (int)((idx >> 6) % nkc);
+  const long row = ((idx >> 6) / nkc) * 16 + (lane & 15);
+  uint16_t v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int k = kc * 32 + (lane >> 4) * 8 + e;
+    v[e] = row < R && k < K ? W[row * K + k] : (uint16_t)0;
+  }
+  out[idx] = frag_pack(v);
+}
+
+// [x0 | x1 | x2] in fragment order (grid y: direction); the rows that fill up the last tile are zero
+template <bool F32>
+__global__ void concat_frag_kernel(ConcatArgs a, uint4* out, long total) {
+  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= total) return;
+  // (a row's threads are neighbours: reads run along the rows)
+  const int kk = (int)(idx % (a.nkc * 4)), row = (int)(idx / (a.nkc * 4)), k = kk * 8, z = blockIdx.y;
+  const auto inside = [&](int b, int len) { return k >= b && k + 8 <= b + len; };
+  uint4 o = make_uint4(0, 0, 0, 0);
+  if (row < a.B) {
+    if (inside(a.k0, a.len0)) o = *(const uint4_u*)(a.x0 + row * a.ld0 + (k - a.k0));
+    else if (inside(a.k1, a.len1)) o = *(const uint4_u*)(a.x1 + row * a.ld1 + (k - a.k1));
+    else if (inside(a.k2, a.len2) && a.x2) {
+      if constexpr (F32) {
+        const float* p = (const float*)a.x2 + a.s2 * z + row * a.ld2 + (k - a.k2);
+        o = frag_pack(*(const float4_u*)p, *(const float4_u*)(p + 4));
+      } else {
+        o = *(const uint4_u*)((const uint16_t*)a.x2 + row * a.ld2 + (k - a.k2));
+      }
+    } else {
+      o = concat_slow<F32>(a, z, row, k);
+    }
+  }
+  const long tiles = (a.B + 15) / 16;
+  out[((tiles * z + (row >> 4)) * a.nkc + (kk >> 2)) * 64 + (kk & 3) * 16 + (row & 15)] = o;
+}
+
+constexpr int kGatherU = 8;              // chunks per wavefront: K up to 4096
+// columns per work-group: as many as still give most compute units one
+int few_columns(int M, int N) {
+  const long blocks = M <= 64 ? 1 : cdiv(M, 64);
+  return blocks * cdiv(N, 16) >= 192 ? 16 : blocks * cdiv(N, 8) >= 192 ? 8 : 4;
+}
+
+}  // namespace
+
+hipError_t launch_few(const SkinnyArgs& a, hipStream_t s) {
+  const int ct = few_columns(a.M, a.N);
+  return a.frag ? launch_rows<true, false>(a, ct, cdiv(a.N, ct), s) : launch_rows<false, false>(a, ct, cdiv(a.N, ct), s);
+}
+
+hipError_t launch_pack_cell_frag(const void* W_x, const void* W_h, void* out, int n_in, int n_in_pad, int n, int K, int ndir, hipStream_t s) {
+  const int nkc = cdiv(K, 32), ntile = cdiv(n, 4);
+  hipLaunchKernelGGL(pack_cell_frag_kernel, dim3(cdiv(nkc, 2), cdiv(4L * ntile, 64), 4 * ndir), dim3(256), 0, s, (const uint16_t*)W_x,
+                     (const uint16_t*)W_h, (uint4*)out, n_in, n_in_pad, n, nkc, ntile);
+  return hipGetLastError();
+}
+hipError_t launch_pack_rows_frag(const void* W, void* out, int R, int K, hipStream_t s) {
+  const long total = (long)cdiv(R, 16) * cdiv(K, 32) * 64;
+  hipLaunchKernelGGL(pack_rows_frag_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const uint16_t*)W, (uint4*)out, R, K, cdiv(K, 32), total);
+  return hipGetLastError();
+}
+
+hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void* Wfrag, const float* bias, const float* c_in, float* h_out,
+                           float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n_in, int n_in_pad, int n, int ndir, hipStream_t s) {
+  const int K = n_in_pad + n, nkc = cdiv(K, 32);
+  ConcatArgs c = {};
+  c.x0 = (const uint16_t*)x; c.ld0 = n_in; c.k0 = 0; c.len0 = n_in;
+  c.k1 = c.len1 = 0;
+  c.x2 = h_in; c.ld2 = n; c.k2 = n_in_pad; c.len2 = n; c.s2 = (long)B * n;
+  c.B = B; c.nkc = nkc;
+  c.find_cuts();
+  SkinnyArgs a = {};
+  a.A = (const char*)A; a.B = (const char*)Wfrag; a.bias = bias; a.M = B; a.N = 4 * n; a.K = K; a.frag = 1;
+  a.sAz = (long)cdiv(B, 16) * nkc * 512; a.sBz = (long)cdiv(n, 4) * nkc * 512; a.nz = ndir;
+  a.n = n; a.h_in = h_in; a.c_in = c_in; a.h_out = h_out; a.c_out = c_out; a.y = (uint16_t*)y; a.ldy = ldy; a.cs = cs; a.lens = lens;
+  if (B <= 16 && nkc <= 16 * kGatherU) {
+    hipLaunchKernelGGL((few_gather_kernel<kGatherU, true, true>), dim3(cdiv(n, 4), 1, ndir), dim3(1024), 0, s, a, c, 16);
+    return hipGetLastError();
+  }
+  const long total = (long)cdiv(B, 16) * 16 * nkc * 4;
+  hipLaunchKernelGGL(concat_frag_kernel<true>, dim3(cdiv(total, 256), ndir), dim3(256), 0, s, c, (uint4*)A, total);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_rows<true, true>(a, 16, cdiv(n, 4), s);
+}
+
+hipError_t launch_few_readout(const void* x0, long ld0, int k0, const void* x1, long ld1, int k1, const void* x2, long ld2, int k2, void* A,
+                              const void* Wfrag, const float* bias, void* out, long ldo, int B, int R, hipStream_t s) {
+  ConcatArgs c = {};
+  c.x0 = (const uint16_t*)x0; c.ld0 = ld0; c.k0 = 0; c.len0 = k0;
+  c.x1 = (const uint16_t*)x1; c.ld1 = ld1; c.k1 = k0; c.len1 = k1;
+  c.x2 = x2; c.ld2 = ld2; c.k2 = k0 + k1; c.len2 = k2;
+  const int K = k0 + k1 + k2;
+  c.B = B; c.nkc = cdiv(K, 32);
+  c.find_cuts();
+  SkinnyArgs a = {};
+  a.A = (const char*)A; a.B = (const char*)Wfrag; a.C = out; a.bias = bias; a.M = B; a.N = R; a.K = c.nkc * 32; a.ldc = ldo; a.nz = 1;
+  a.out_bf16 = 1; a.relu = 1; a.frag = 1;
+  if (B <= 16 && c.nkc <= 16 * kGatherU) {
+    const int ct = few_columns(B, R);
+    hipLaunchKernelGGL((few_gather_kernel<kGatherU, false, false>), dim3(cdiv(R, ct)), dim3(1024), 0, s, a, c, ct);
+    return hipGetLastError();
+  }
+  const long total = (long)cdiv(B, 16) * 16 * c.nkc * 4;
+  hipLaunchKernelGGL(concat_frag_kernel<false>, dim3(cdiv(total, 256)), dim3(256), 0, s, c, (uint4*)A, total);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_few(a, s);
+}
+
+}  // namespace lstm

@@ -22,6 +22,7 @@
 // against 192): what bounds the kernel is the rate at which ONE compute unit pulls operands from L2, so more, smaller
 // tiles finish sooner although they move more bytes in total.
 #include "recurrent_dev.h"
+#include "gemm_skinny.h"
 
 namespace lstm {
 namespace {
@@ -43,17 +44,6 @@ struct Geo {
   static_assert(kTM * kEpStride * 4 <= kDummy, "the epilogue's staging must fit into the stage buffers");
 };
 constexpr unsigned kParked = 0x7ffffff0u;
-
-struct SkinnyArgs {
-  const char* A; const char* B; void* C; const float* bias;
-  int M, N, K;
-  long lda, ldb, ldc;                    // elements
-  long sAz, sBz, sCz, sbiasz; int nz;    // blockIdx.z batches independent problems (the two directions)
-  int out_bf16, relu;
-  // cell epilogue (cell != 0): N = 128 * ceil(n / 32), column 128 * tile + 32 * gate + unit; bias is [4n] gate-major
-  int cell, n;
-  const float* h_in; const float* c_in; float* h_out; float* c_out; uint16_t* y; long ldy; float* cs; const int* lens;
-};
 
 __device__ __forceinline__ void load_to_lds_b128(const u32x4& rsrc, unsigned lds_addr, unsigned voff, unsigned soff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
@@ -354,6 +344,7 @@ hipError_t launch_as(const SkinnyArgs& a, hipStream_t s) {
 hipError_t launch(const SkinnyArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.nz <= 0) return hipSuccess;
   if (a.cell) return launch_as<3, 2, true>(a, s);
+  if (a.M <= kFewRows) return launch_few(a, s);
   // fewer 96 x 128 tiles than half the device has compute units: 64 x 64 tiles
   if ((long)cdiv(a.M, 96) * cdiv(a.N, 128) * a.nz < 128) return launch_as<2, 1, false>(a, s);
   return launch_as<3, 2, false>(a, s);

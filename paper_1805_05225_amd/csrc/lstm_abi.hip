@@ -3,6 +3,7 @@
 // can be produced on a machine without a GPU.
 #include "../../include/lstm_abi.h"
 #include "common.h"
+#include "gemm_skinny.h"
 
 #include <string.h>
 #include <stdlib.h>
@@ -28,7 +29,7 @@ struct Plan {
   size_t ws_Wf, ws_Wb, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
       ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_XT, ws_DZT, ws_HT, ws_cidx, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, workspace_bytes;
   int ks_dwx, ks_dwh, ks_dx;                // K ranges of the weight-gradient products and of dX (few output tiles: the whole device works on them)
-  bool single_step, step_fused; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
+  bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool fast_gemm; int n_in_pad; long TBp;   // bf16 products through the k-contiguous kernel (operands transposed once)
   size_t hfrag_bytes, dzfrag_bytes, DZ_dir_elems, Zx_dir_elems, Wf_bytes;
 };
@@ -94,6 +95,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   // epilogue (B <= kSkinnyMaxRows); larger batches go through the throughput kernel, K cut into ranges whose partial
   // products lie side by side for the cell kernel to add.
   p->step_fused = p->single_step && d->B <= kSkinnyMaxRows;
+  p->step_few = p->step_fused && d->B <= kFewCellRows;
   {
     const long tiles = (long)cdiv(B > 0 ? B : 1, 256) * cdiv(4L * d->n, 256) * p->D;
     const long stages = cdiv((long)p->n_in_pad + d->n, 64);
@@ -117,7 +119,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_fidx = take(fm ? (size_t)p->TBp * 4 : 0);
   p->ws_count = take(fm ? 256 : 0);
   p->ws_Wcat = take(p->single_step ? D * std::max((size_t)4 * n, wcell_rows(d->n)) * p->Kc * 2 : 0);
-  p->ws_Acat = take(p->single_step ? D * B * p->Kc * 2 : 0);
+  p->ws_Acat = take(p->single_step ? D * std::max((size_t)B * p->Kc * 2, frag_bytes(d->B, p->Kc)) : 0);
   // weight-gradient products with few output tiles cut K into ranges whose partial results are summed afterwards
   const auto ksplit_for = [&](long M, long N) {
     const long tiles = (long)cdiv(M, 256) * cdiv(N, 256) * p->D;
@@ -219,6 +221,16 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     char* Wcat = ws + p.ws_Wcat;
     char* Acat = ws + p.ws_Acat;
     float* z = (float*)(ws + p.ws_Zx);
+    if (p.step_few) {                  // a handful of rows: operands in fragment order
+      if (!(desc->flags & LSTM_FLAG_WEIGHTS_PACKED)) {
+        Phase ph(LSTM_PHASE_PREP, 1, s);
+        HIPCHK(launch_pack_cell_frag(W_x, W_h, Wcat, p.n_in, p.n_in_pad, p.n, p.n_in_pad + p.n, p.D, s));
+      }
+      Phase ph(LSTM_PHASE_LOOP_FWD, 2, s);
+      HIPCHK(launch_few_cell(x, (const float*)h0, Acat, Wcat, (const float*)b, (const float*)c0, (float*)hT, (float*)cT, y, (long)(D * n), (float*)c,
+                             seq_lens, p.B, p.n_in, p.n_in_pad, p.n, p.D, s));
+      return LSTM_OK;
+    }
     {
       Phase ph(LSTM_PHASE_PREP, 2, s);
       if (!(desc->flags & LSTM_FLAG_WEIGHTS_PACKED)) {

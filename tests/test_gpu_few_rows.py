@@ -1,0 +1,62 @@
+"""The kernels for a handful of rows (stepped cell, readout, plain product) at the row counts where the dispatch changes kernel and
+at column counts and pieces that end inside a tile or a chunk, against float64 products of the same bfloat16 values."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from oracle import decoder_oracle as D
+from oracle import lstm_oracle as O
+from tests.gpu_util import check, dev
+
+TOL = 2e-2
+
+
+def _bf(rng, *shape, w=1.0):
+    return torch.from_numpy(rng.uniform(-w, w, shape)).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("B,n_in,n", [(1, 37, 50), (16, 300, 104), (17, 300, 104), (32, 1100, 36), (33, 40, 1000), (64, 2620, 130),
+                                      (65, 77, 34), (192, 1200, 66), (193, 1200, 66), (12, 4100, 24)])
+def test_stepped_cell(B, n_in, n):
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(B + n_in)
+    Wx, Wh = _bf(rng, n_in, 4 * n, w=0.1), _bf(rng, n, 4 * n, w=0.1)
+    b, h, c = rng.uniform(-.1, .1, 4 * n), rng.uniform(-1, 1, (B, n)), rng.standard_normal((B, n))
+    x = _bf(rng, 1, B, n_in)
+    f64 = lambda t: t.float().numpy().astype(np.float64)
+    ws = None
+    for flags in (Bn.FLAG_INFERENCE, Bn.FLAG_INFERENCE | Bn.FLAG_WEIGHTS_PACKED):
+        s = Bn.forward(x.cuda(), Wx.cuda(), Wh.cuda(), dev(b), dev(h), dev(c), None, bidirectional=False, flags=flags, workspace=ws)
+        ws = s["workspace"]
+        y, _, ho, co = O.lstm_fwd(f64(x), f64(Wx), f64(Wh), b, h, c, None, 1)
+        torch.cuda.synchronize()
+        check("y", s["y"], y, TOL)
+        check("hT", s["hT"], ho, TOL)
+        check("cT", s["cT"], co, TOL)
+
+
+@pytest.mark.parametrize("n,nt,E,R", [(104, 62, 130, 20), (1000, 620, 2000, 1000), (5, 3, 8, 33)])
+def test_readout_packed_once_for_any_row_count(n, nt, E, R):
+    """FLAG_WEIGHTS_PACKED speaks of the weights and the workspace, not of the number of rows."""
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(n)
+    W, br = _bf(rng, R, n + nt + E, w=0.1), rng.uniform(-.1, .1, R)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    for k, B in enumerate((300, 1, 16, 17, 64, 192, 193)):
+        s, t, a = _bf(rng, B, n), _bf(rng, B, nt), _bf(rng, B, E)
+        out = Bn.readout(s.cuda(), t.cuda(), a.cuda(), W.cuda(), dev(br), workspace=ws, flags=Bn.FLAG_WEIGHTS_PACKED if k else 0)
+        f64 = lambda v: v.float().numpy().astype(np.float64)
+        torch.cuda.synchronize()
+        check("readout B=%d" % B, out, D.readout(f64(s), f64(t), f64(a), f64(W).T, br), 5e-3)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 20001, 1000), (16, 4097, 72), (17, 33, 2048), (32, 1000, 1000), (33, 1000, 1000)])
+def test_product(M, N, K):
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(M + N)
+    A, B, bias = _bf(rng, M, K), _bf(rng, N, K), rng.uniform(-1, 1, N)
+    C = Bn.gemm(A.cuda(), B.cuda(), a_kcontig=True, b_kcontig=True, M=M, N=N, K=K, bias=dev(bias))
+    torch.cuda.synchronize()
+    check("C", C, A.double().numpy() @ B.double().numpy().T + bias, 1e-4)
