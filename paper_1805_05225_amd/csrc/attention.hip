@@ -34,13 +34,18 @@ __device__ __forceinline__ int src_len(const int* lens, int q, int S) {
 
 // e[r][j] for the rows of sentence q = blockIdx.y and the kJB positions from blockIdx.x * kJB.  A lane owns the
 // attention features k = lane, lane + 256, ...: it loads ctx[j][q][k] once and uses it for every hypothesis of the
-// sentence.  The beam x kJB partial sums of the 256 lanes are added through LDS.
+// sentence.  The beam x kJB partial sums of the 256 lanes are added through LDS.  NB: hypotheses rounded up to a multiple of 4
+// (registers and loads for 16 where a beam of 12 has 12 cost a quarter of the time).
+// What bounds it is the vector ALU: an element is five full-rate operations and two transcendental ones at a quarter of the rate,
+// 10 us for 64 sentences x 40 positions x 12 hypotheses x 1000 features (measured: 22.6 us with NB = 16, DESIGN table).
+template <int NB>
 __global__ __launch_bounds__(256) void att_energy_kernel(const uint16_t* __restrict__ ctx, const float* __restrict__ s_tr,
                                                           const float* __restrict__ accum, const float* __restrict__ w_fb,
                                                           const float* __restrict__ b_fb, const float* __restrict__ v, float b_e,
                                                           const int* __restrict__ lens, float* __restrict__ e, int S, int Q, int beam,
                                                           int A) {
-  __shared__ float part[32 * kPartStride];                     // 32 (hypothesis, position) pairs at a time
+  constexpr int kVals = NB * kJB;                              // (hypothesis, position) pairs
+  __shared__ __attribute__((aligned(16))) float part[kVals * kPartStride];
   const int q = blockIdx.y, j0 = blockIdx.x * kJB, tid = threadIdx.x;
   const int L = src_len(lens, q, S);
   if (j0 >= L) return;
@@ -48,33 +53,33 @@ __global__ __launch_bounds__(256) void att_energy_kernel(const uint16_t* __restr
   // tanh(x) = 1 - 2 / (1 + 2^(x * 2 log2 e)): with every addend of x scaled by 2 log2 e beforehand an element costs
   // multiply-add, add, exp2, add, reciprocal, multiply-add; the "1" of every term is added once per lane (vsum).
   constexpr float kScale = 2.8853900817779268f;                // 2 log2(e)
-  float sum[kMaxBeam][kJB];
+  float sum[NB][kJB];
 #pragma unroll
-  for (int r = 0; r < kMaxBeam; ++r)
+  for (int r = 0; r < NB; ++r)
 #pragma unroll
     for (int j = 0; j < kJB; ++j) sum[r][j] = 0.f;
   float vsum = 0.f;
   // the accumulated weights of the beam x kJB (row, position) pairs: the same for every lane and every k
-  float ac[kMaxBeam][kJB];
+  float ac[NB][kJB];
 #pragma unroll
-  for (int r = 0; r < kMaxBeam; ++r)
+  for (int r = 0; r < NB; ++r)
 #pragma unroll
-    for (int j = 0; j < kJB; ++j) ac[r][j] = (r < beam && j < nj) ? accum[((long)q * beam + r) * S + j0 + j] : 0.f;
+    for (int j = 0; j < kJB; ++j) ac[r][j] = accum[((long)q * beam + min(r, beam - 1)) * S + j0 + min(j, nj - 1)];
   for (int k = tid; k < A; k += 256) {
     // every load of this k goes out before the first use: inside the uniform branches below each would be waited for
     // on its own, one L2 latency per hypothesis (measured: 47 -> 30 us).  Fetching the next k's operands ahead of
     // this k's arithmetic as well measured no faster.
-    float c[kJB], st[kMaxBeam];
+    float c[kJB], st[NB];
 #pragma unroll
     for (int j = 0; j < kJB; ++j) c[j] = bf_bits2f(ctx[((long)(j0 + min(j, nj - 1)) * Q + q) * A + k]);
 #pragma unroll
-    for (int r = 0; r < kMaxBeam; ++r) st[r] = s_tr[((long)q * beam + min(r, beam - 1)) * A + k];
+    for (int r = 0; r < NB; ++r) st[r] = s_tr[((long)q * beam + min(r, beam - 1)) * A + k];
     const float bf = b_fb[k], wf = kScale * w_fb[k], vk = v[k], m2v = -2.f * vk;
 #pragma unroll
     for (int j = 0; j < kJB; ++j) c[j] = kScale * (c[j] + bf);
     vsum += vk;
 #pragma unroll
-    for (int r = 0; r < kMaxBeam; ++r) {
+    for (int r = 0; r < NB; ++r) {
       if (r < beam) {                                          // uniform: a scalar branch
         const float s2 = kScale * st[r];
 #pragma unroll
@@ -86,34 +91,24 @@ __global__ __launch_bounds__(256) void att_energy_kernel(const uint16_t* __restr
     }
   }
 #pragma unroll
-  for (int r = 0; r < kMaxBeam; ++r)
+  for (int r = 0; r < NB; ++r)
 #pragma unroll
-    for (int j = 0; j < kJB; ++j) sum[r][j] += vsum;
-  // the partial sums of 32 (hypothesis, position) pairs at a time: kRows hypotheses x kJB positions
-  constexpr int kRows = 32 / kJB < kMaxBeam ? 32 / kJB : kMaxBeam;
+    for (int j = 0; j < kJB; ++j) part[(r * kJB + j) * kPartStride + tid] = sum[r][j] + vsum;
+  __syncthreads();
+  // pair `vid` is added up by eight lanes, each taking eight times four of the 256 partial sums
+  const int vid = tid >> 3, sub = tid & 7, r = vid / kJB, j = vid % kJB;
+  float t = 0.f;
+  if (vid < kVals) {
 #pragma unroll
-  for (int grp = 0; grp < kMaxBeam / kRows; ++grp) {
-    if (grp * kRows >= beam) break;
-    if (grp) __syncthreads();                                   // the previous group has been read
-#pragma unroll
-    for (int rr = 0; rr < kRows; ++rr)
-      if (grp * kRows + rr < beam) {
-#pragma unroll
-        for (int j = 0; j < kJB; ++j) part[(rr * kJB + j) * kPartStride + tid] = sum[grp * kRows + rr][j];
-      }
-    __syncthreads();
-    // value `vid` (= rr * kJB + j) is added up by four lanes, each taking every fourth of the 256 partial sums
-    const int vid = tid >> 2, sub = tid & 3;
-    const int r = grp * kRows + vid / kJB, j = vid % kJB;
-    const bool live = vid < kRows * kJB && r < beam;
-    float t = 0.f;
-    if (live) {
-      for (int i = 0; i < 64; ++i) t += part[vid * kPartStride + 4 * i + sub];
+    for (int i = 0; i < 8; ++i) {
+      const float4 p = *(const float4*)&part[vid * kPartStride + 32 * i + 4 * sub];
+      t += (p.x + p.y) + (p.z + p.w);
     }
-    t += __shfl_xor(t, 1);
-    t += __shfl_xor(t, 2);
-    if (sub == 0 && live && j < nj) e[((long)q * beam + r) * S + j0 + j] = t + b_e;
   }
+  t += __shfl_xor(t, 1);
+  t += __shfl_xor(t, 2);
+  t += __shfl_xor(t, 4);
+  if (sub == 0 && vid < kVals && r < beam && j < nj) e[((long)q * beam + r) * S + j0 + j] = t + b_e;
 }
 
 // The same for few sentences, where the form above would put a handful of work-groups on the device (one sentence of 27 positions: 14,
@@ -179,7 +174,7 @@ __global__ __launch_bounds__(256) void att_energy_few_kernel(const uint16_t* __r
 // a[r, :] = softmax of e[r, :] over the valid positions, accum' = accum + a, and att[r] = sum_j a[r][j] H[j][q], for
 // the hypotheses of sentence q = blockIdx.y and the 128 features from blockIdx.x * 128.  Every work-group of a sentence
 // works the softmax out for itself (beam x S exponentials from one round of loads: cheaper than a launch of its own and
-// a pass through memory); the one with blockIdx.x == 0 writes a and accum'.  Softmax: 16 lanes per hypothesis, e staged
+// a pass through memory); the last one writes a and accum'.  Softmax: 16 lanes per hypothesis, e staged
 // in LDS.  Context: lane l of every wavefront owns features 2l, 2l + 1 of the slice, the four wavefronts share the
 // source positions (wavefront w takes j = w, w + 4, ...), kU loads in flight per lane, and their partial sums meet in
 // LDS.  H is read once for all hypotheses of the sentence.  Dynamic LDS: S * kMaxBeam floats, w[j][r] (rows r >= beam
@@ -204,41 +199,40 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
 #pragma unroll
     for (int u = 0; u < kU; ++u) hh[u] = *(const unsigned*)(Hq + min(wave + 4 * u, L - 1) * jstride);
   }
-  {
-    const int r = tid >> 4, l = tid & 15;                       // beam <= 16: one group of 16 lanes per hypothesis
-    const long row = (long)q * beam + r;
-    float m = -3.0e38f;
-    if (r < beam) {
-      for (int j = l; j < L; j += 16) {
-        const float ev = e[row * S + j];
-        w[j * kMaxBeam + r] = ev;
-        m = fmaxf(m, ev);
-      }
-    } else if (r < nb4 * 4) {
-      for (int j = l; j < L; j += 16) w[j * kMaxBeam + r] = 0.f;
-    }
-    // a lane reads back only what it wrote itself until the weights are complete
+  __shared__ float inv_z[kMaxBeam];
+  const int r_own = tid >> 4, l_own = tid & 15;                 // beam <= 16: one group of 16 lanes per hypothesis
+  const long row_own = (long)q * beam + r_own;
+  // (loads of four positions per lane go out together: one after the other, as the loop was first written, they were most of
+  // this kernel's time)
+  constexpr int kP = 4;
+  float m = -3.0e38f, z = 0.f;
+  if (r_own < beam) {
+    for (int j0 = l_own; j0 < L; j0 += 16 * kP) {
+      float ev[kP];
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (r < beam) {
-      float z = 0.f;
-      for (int j = l; j < L; j += 16) {
-        const float p = __expf(w[j * kMaxBeam + r] - m);
-        w[j * kMaxBeam + r] = p;
-        z += p;
-      }
+      for (int u = 0; u < kP; ++u) ev[u] = e[row_own * S + min(j0 + 16 * u, L - 1)];
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) z += __shfl_xor(z, o);
-      const float inv = L > 0 ? 1.f / z : 0.f;
-      for (int j = l; j < L; j += 16) w[j * kMaxBeam + r] *= inv;
-      if (blockIdx.x == 0) {
-        for (int j = l; j < S; j += 16) {
-          const float p = j < L ? w[j * kMaxBeam + r] : 0.f;
-          if (a_out) a_out[row * S + j] = p;
-          accum_out[row * S + j] = j < L ? accum_in[row * S + j] + p : 0.f;
+      for (int u = 0; u < kP; ++u)
+        if (j0 + 16 * u < L) {
+          w[(j0 + 16 * u) * kMaxBeam + r_own] = ev[u];
+          m = fmaxf(m, ev[u]);
         }
-      }
     }
+  } else if (r_own < nb4 * 4) {
+    for (int j = l_own; j < L; j += 16) w[j * kMaxBeam + r_own] = 0.f;
+  }
+  // a lane reads back only what it wrote itself until the weights are complete
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  if (r_own < beam) {
+    for (int j = l_own; j < L; j += 16) {
+      const float p = __expf(w[j * kMaxBeam + r_own] - m);
+      w[j * kMaxBeam + r_own] = p;
+      z += p;
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) z += __shfl_xor(z, o);
+    if (l_own == 0) inv_z[r_own] = L > 0 ? 1.f / z : 0.f;       // (applied to the sums below)
   }
   __syncthreads();
   float acc[kMaxBeam][2];
@@ -271,12 +265,29 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
       if (r < beam) { red[wave - 1][2 * r][lane] = acc[r][0]; red[wave - 1][2 * r + 1][lane] = acc[r][1]; }
   }
   __syncthreads();
+  if (blockIdx.x == gridDim.x - 1 && r_own < beam) {            // one work-group of the sentence writes the weights
+    const float inv = inv_z[r_own];
+    for (int j0 = l_own; j0 < S; j0 += 16 * kP) {
+      float before[kP];
+#pragma unroll
+      for (int u = 0; u < kP; ++u) before[u] = accum_in[row_own * S + min(j0 + 16 * u, max(L - 1, 0))];     // (nothing past L is read)
+#pragma unroll
+      for (int u = 0; u < kP; ++u) {
+        const int j = j0 + 16 * u;
+        if (j >= S) break;
+        const float p = j < L ? w[j * kMaxBeam + r_own] * inv : 0.f;
+        if (a_out) a_out[row_own * S + j] = p;
+        accum_out[row_own * S + j] = j < L ? before[u] + p : 0.f;
+      }
+    }
+  }
   if (wave > 0 || !live) return;
 #pragma unroll
   for (int r = 0; r < kMaxBeam; ++r)
     if (r < beam) {
-      const float s0 = acc[r][0] + red[0][2 * r][lane] + red[1][2 * r][lane] + red[2][2 * r][lane];
-      const float s1 = acc[r][1] + red[0][2 * r + 1][lane] + red[1][2 * r + 1][lane] + red[2][2 * r + 1][lane];
+      const float inv = inv_z[r];
+      const float s0 = (acc[r][0] + red[0][2 * r][lane] + red[1][2 * r][lane] + red[2][2 * r][lane]) * inv;
+      const float s1 = (acc[r][1] + red[0][2 * r + 1][lane] + red[1][2 * r + 1][lane] + red[2][2 * r + 1][lane]) * inv;
       const unsigned o = (unsigned)f2bf_bits(s0) | ((unsigned)f2bf_bits(s1) << 16);
       *(unsigned*)(att + ((long)q * beam + r) * ldatt + f) = o;
     }
@@ -393,8 +404,9 @@ int lstm_attention_step(const lstm_att_desc* d, const void* enc, const void* enc
     hipLaunchKernelGGL(att_energy_few_kernel, dim3(d->S, d->Q, (d->beam + kFewHyp - 1) / kFewHyp), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr,
                        accum_in, w_fb, b_fb, v, b_e, src_lens, e, d->S, d->Q, d->beam, d->A);
   else
-    hipLaunchKernelGGL(att_energy_kernel, dim3((d->S + kJB - 1) / kJB, d->Q), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr, accum_in, w_fb,
-                     b_fb, v, b_e, src_lens, e, d->S, d->Q, d->beam, d->A);
+    hipLaunchKernelGGL(d->beam <= 4 ? att_energy_kernel<4> : d->beam <= 8 ? att_energy_kernel<8> : d->beam <= 12 ? att_energy_kernel<12> : att_energy_kernel<16>,
+                       dim3((d->S + kJB - 1) / kJB, d->Q), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr, accum_in, w_fb, b_fb, v, b_e, src_lens, e,
+                       d->S, d->Q, d->beam, d->A);
   static std::atomic<unsigned long long> attr_set{0};            // S = 1024 needs 64 KiB of dynamic LDS beside the static arrays
   if (once_per_device(attr_set, [] {
         return hipFuncSetAttribute((const void*)att_context_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxS * kMaxBeam * 4);

@@ -41,7 +41,7 @@ struct Geo {
   static constexpr int kDummy = kDepth * kStage;      // 4 KiB that the surplus loads of a stage write zeros to (see the kernel)
   static constexpr int kEpStride = kTN + 4;           // floats per staged row
   static constexpr int kLds = kDummy + 4096;          // <3,2>: 118784 bytes; the epilogue's staging reuses the stages
-  static_assert(kTM * kEpStride * 4 <= kDummy, "the epilogue's staging must fit into the stage buffers");
+  static_assert(2 * kTM * kEpStride * 4 <= kDummy, "the epilogue's staging must fit into the stage buffers");
 };
 constexpr unsigned kParked = 0x7ffffff0u;
 
@@ -238,20 +238,22 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
   }
   __syncthreads();                                 // the stage buffers are free for the epilogue
 
-  // Epilogue.  The four k-steps' shares meet in LDS (the stage buffers are free), one after the other:
-  // acc[i][j][v] is row i*32 + 8 (v / 4) + 4 gq + v % 4, column wc*32*BJ + j*32 + r.
+  // Epilogue.  The four k-steps' shares meet in LDS (the stage buffers are free): k-steps 2 and 3 store theirs side by side, 0 and 1
+  // add to them, and whoever reads adds the two.  (One after the other into one array, four rounds of it, took 8 us of the 768-row
+  // cell's 39.)  acc[i][j][v] is row i*32 + 8 (v / 4) + 4 gq + v % 4, column wc*32*BJ + j*32 + r.
   float* ep = (float*)lds;
+  constexpr int kEpHalf = kTM * kEpStride;
 #pragma unroll
-  for (int round = 3; round >= 0; --round) {
-    if (kq == round) {
+  for (int round = 1; round >= 0; --round) {
+    if ((kq >> 1) == round) {
 #pragma unroll
       for (int i = 0; i < BI; ++i)
 #pragma unroll
         for (int j = 0; j < BJ; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            float* e = &ep[(i * 32 + 8 * (v >> 2) + 4 * gq + (v & 3)) * kEpStride + wc * 32 * BJ + j * 32 + r];
-            *e = round == 3 ? acc[i][j][v] : *e + acc[i][j][v];
+            float* e = &ep[(kq & 1) * kEpHalf + (i * 32 + 8 * (v >> 2) + 4 * gq + (v & 3)) * kEpStride + wc * 32 * BJ + j * 32 + r];
+            *e = round == 1 ? acc[i][j][v] : *e + acc[i][j][v];
           }
     }
     __syncthreads();
@@ -270,8 +272,8 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
     for (int rr = tid / kTpr; rr < kTM; rr += 512 / kTpr) {
       const int row = m0 + rr;
       if (row >= g.M || col >= g.N) continue;
-      const float4 val = *(const float4*)&ep[rr * kEpStride + c4];
-      float e[4] = {val.x + bv[0], val.y + bv[1], val.z + bv[2], val.w + bv[3]};
+      const float4 val = *(const float4*)&ep[rr * kEpStride + c4], val2 = *(const float4*)&ep[kEpHalf + rr * kEpStride + c4];
+      float e[4] = {val.x + val2.x + bv[0], val.y + val2.y + bv[1], val.z + val2.z + bv[2], val.w + val2.w + bv[3]};
       if (g.relu) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) e[k] = e[k] > 0.f ? e[k] : 0.f;
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
         if (valid) {
           float zh[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) zh[q] = ep[rr * kEpStride + q * 32 + uu] + bv[q];
+          for (int q = 0; q < 4; ++q) zh[q] = ep[rr * kEpStride + q * 32 + uu] + ep[kEpHalf + rr * kEpStride + q * 32 + uu] + bv[q];
           const float zx[4] = {0.f, 0.f, 0.f, 0.f};
           const CellOut o = lstm_cell(zh, zx, c);
           c = o.c; h = o.h;
