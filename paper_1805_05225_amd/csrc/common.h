@@ -163,6 +163,10 @@ inline int ll_nkc(int n, int slots) { return (int)((((long)(n + 15) / 16) * slot
 // zero-filled slot never looks written.
 __host__ __device__ inline unsigned ll_fwd_tag(unsigned tau) { return ((tau >> 1) & 1u) ^ 1u; }
 
+// How a launch of the bfloat16 kernels maps its work-groups (set by the launcher, explained at wg_coord): unit tiles, row groups
+// (of 8 or 16 rows) in the launch, groups per XCD.
+struct GridMap { int ntile, nrow, gpx; };
+
 struct PFwdDir {
   const uint4* Wf;    // [unit tile][gate][nkc][64] chunks
   const uint4* Wzero; // one chunk (64 x 16 bytes) of zeros
@@ -181,6 +185,7 @@ struct PFwdArgs {
   unsigned* sync; unsigned spin_limit;
   unsigned* xcc;      // NULL or one zeroed word per work-group (see PBwdArgs)
   int rt0;            // set by the launcher: first 16-row tile of the batch that this launch handles
+  GridMap map;
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
 };
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s);
@@ -207,6 +212,7 @@ struct PBwdArgs {
   unsigned* sync; unsigned spin_limit;
   unsigned* xcc;      // NULL or one zeroed word per work-group: lets an exchange group find out whether it shares an XCD
   int rt0;            // set by the launcher: first 16-row tile of the batch that this launch handles
+  GridMap map;
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
 };
 // Does the single-launch backward kernel (partial sums of Dh exchanged; W_h via launch_prep_bwd_ll, ring of
@@ -223,7 +229,9 @@ inline size_t bwd_f32_ring_bytes(int B, int n) {
   const size_t tiles = (size_t)((n + 15) / 16), rts = 2 * (size_t)(((B > 0 ? B : 1) + 31) / 32);
   return rts * tiles * tiles * 1024;
 }
-inline size_t bwdp_wh_bytes(int n) { return (size_t)((n + 31) / 32) * 262144; }                  // per direction
+// output column tiles (of 16) per wavefront of the bfloat16 backward kernel: four wavefronts cover n
+inline int bwdp_nct(int n) { return n <= 256 ? 4 : n <= 512 ? 8 : 16; }
+inline size_t bwdp_wh_bytes(int n) { return (size_t)((n + 31) / 32) * 16384 * bwdp_nct(n); }                // per direction
 inline size_t bwdp_ring_bytes(int B, int n) {                                                      // per direction and slot
   const size_t groups = 2 * (size_t)(((B > 0 ? B : 1) + 15) / 16), tiles = (size_t)((n + 31) / 32);
   return groups * tiles * tiles * 512;

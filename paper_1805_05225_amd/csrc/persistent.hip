@@ -283,13 +283,18 @@ __device__ __forceinline__ void mfma_settle(f32x4& a0, f32x4& a1, f32x4& a2, f32
 // from `group_base`) and reads the group's words; anything but "all equal to mine" - a word still unset after the
 // poll limit included - means "not local", and the caller then uses agent-scope stores as before.  The verdict
 // needs no agreement: a work-group that says "local" has seen every member on its own XCD.
-__device__ __forceinline__ bool group_is_xcd_local(unsigned* tab, int group_base, int members, int me, unsigned limit) {
+// The words are published before W_h is loaded and looked at behind it, a lane per member (one thread reading 32 words
+// one after the other held every launch up by 10 us).
+__device__ __forceinline__ unsigned my_xcd() { return (__builtin_amdgcn_s_getreg(((4 - 1) << 11) | 20) & 15u) + 1u; }   // XCC_ID, bits 3:0
+__device__ __forceinline__ void publish_xcd(unsigned* tab, int group_base, int me) {
+  if (tab && threadIdx.x == 0) st_relaxed(&tab[group_base + me], my_xcd());
+}
+__device__ __forceinline__ int group_is_xcd_local(unsigned* tab, int group_base, int members, unsigned limit) {
   __shared__ int verdict;
-  if (threadIdx.x == 0) {
-    const unsigned mine = (__builtin_amdgcn_s_getreg(((4 - 1) << 11) | 20) & 15u) + 1u;     // XCC_ID, bits 3:0
-    st_relaxed(&tab[group_base + me], mine);
-    bool same = true;
-    for (int p = 0; p < members && same; ++p) {
+  if (threadIdx.x < 64) {
+    const unsigned mine = my_xcd();
+    bool same = tab != nullptr;
+    for (int p = threadIdx.x; p < members && same; p += 64) {
       unsigned v = 0u;
       for (unsigned poll = 0; poll < limit; ++poll) {
         v = ld_relaxed(&tab[group_base + p]);
@@ -297,29 +302,38 @@ __device__ __forceinline__ bool group_is_xcd_local(unsigned* tab, int group_base
       }
       same = v == mine;
     }
-    verdict = same ? 1 : 0;
+    const bool all = __builtin_amdgcn_ballot_w64(!same) == 0ull;
+    if (threadIdx.x == 0) verdict = all ? 1 : 0;
   }
   __syncthreads();
-  return verdict != 0;
+  return __builtin_amdgcn_readfirstlane(verdict);
 }
 
-// Work-group -> (unit tile, row tile, direction).  Work-groups are dealt to the 8 XCDs round-robin in launch
-// order, and every work-group of one (direction, row tile) group reads the same ring tile each step.  When the
-// shape allows it the groups are laid out so that each XCD serves a single group: its L2 then fetches one
-// ring tile per step instead of all of them.  Any bijection is correct; this one is only faster.
-struct WgCoord { int tile, rt, dir; };
-__device__ __forceinline__ WgCoord wg_coord() {
-  const int ntiles = gridDim.x, nrt = gridDim.y, ndir = gridDim.z;
-  const int groups = nrt * ndir, total = ntiles * groups;
-  const int lin = blockIdx.x + ntiles * (blockIdx.y + nrt * blockIdx.z);
-  WgCoord c = {(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z};
-  if (groups <= 8 && 8 % groups == 0 && total % 8 == 0) {
+// Work-group -> (unit tile, row group, direction).  Work-groups are dealt to the 8 XCDs round-robin in launch order, and
+// the work-groups of one (direction, row group) exchange data every step.  map.gpx > 0: XCD x runs the groups x, x + 8, ...
+// (gpx of them at most; the grid is sized for 8 gpx groups and the surplus leaves at once), so that every exchange stays inside one
+// XCD - also with fewer groups than XCDs, where spreading a group over two of them to use them all made a step 2.7 us instead
+// of 1.6 (one sentence, both directions, n = 1000).  gpx = 0 (more work-groups per XCD than it has compute units): where the shape
+// allows it each XCD serves a single group.  Any bijection is correct; these are only faster.
+struct WgCoord { int tile, rt, dir, base; bool live; };      // base: place of the group's first word in the XCD table
+__device__ __forceinline__ WgCoord wg_coord(const GridMap& m, int ndir) {
+  const int groups = m.nrow * ndir, total = m.ntile * groups, lin = blockIdx.x;
+  int tile = lin % m.ntile, group = lin / m.ntile;
+  if (m.gpx > 0) {
+    const int slot = lin >> 3;
+    group = (lin & 7) + 8 * (slot / m.ntile);
+    tile = slot % m.ntile;
+  } else if (groups <= 8 && 8 % groups == 0 && total % 8 == 0) {
     const int xcd = lin & 7, slot = lin >> 3, per_group = 8 / groups;     // XCDs per group
-    const int group = xcd % groups;
-    c.tile = xcd / groups + per_group * slot;
-    c.rt = group % nrt;
-    c.dir = group / nrt;
+    group = xcd % groups;
+    tile = xcd / groups + per_group * slot;
   }
+  // (told to be wave-uniform: divisions leave them in vector registers, and a buffer descriptor formed from those is applied
+  // lane by lane in a loop)
+  tile = __builtin_amdgcn_readfirstlane(tile);
+  group = __builtin_amdgcn_readfirstlane(group);
+  const int dir = __builtin_amdgcn_readfirstlane(group / m.nrow);
+  WgCoord c = {tile, group - dir * m.nrow, dir, group * m.ntile, group < groups};
   return c;
 }
 
@@ -330,7 +344,9 @@ __device__ __forceinline__ WgCoord wg_coord() {
 template <int NIT>
 __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   __shared__ float red[2][4][8][129];                    // two copies, used by even and odd steps: one barrier per step
-  const WgCoord wg = wg_coord();
+  const WgCoord wg = wg_coord(a.map, a.ndir);
+  if (!wg.live) return;
+  publish_xcd(a.xcc, wg.base, wg.tile);
   const PFwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
   const int tile2 = wg.tile, rt = a.rt0 + (wg.rt >> 1), half = wg.rt & 1;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -380,8 +396,7 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   const int cch = t16p * 2 + (m >> 1);
   const long unit_index = (((long)rt * nkc + (cch >> 2)) * 64 + (cch & 3) * 16 + half * 8 + r8) * 2 + (m & 1);
   const bool publishes = (u & 3) == 0 && t16p < ntiles16;
-  const bool local = a.xcc != nullptr &&
-                     group_is_xcd_local(a.xcc, (wg.dir * (int)gridDim.y + wg.rt) * (int)gridDim.x, gridDim.x, tile2, a.spin_limit);
+  const bool local = group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit);
   // Has this row had a frame yet?  Until then it publishes zeros, not the initial state it carries: that state's product
   // with W_h has been added to the pre-activations of the row's first frame by the host side, and what travels
   // through the ring must keep |h| <= 1 (the tag bit).
@@ -632,7 +647,9 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   // back exactly what it asked for, so no barrier is involved - only the loads' completion.
   __shared__ float zxs[2][4][8][64];
   __shared__ u32x4 rbuf[4][NIT][64];                     // the ring loads of a step: [wavefront][load][lane], written by the memory unit
-  const WgCoord wg = wg_coord();
+  const WgCoord wg = wg_coord(a.map, a.ndir);
+  if (!wg.live) return;
+  publish_xcd(a.xcc, wg.base, wg.tile);
   const PFwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
   const int tile2 = wg.tile, rt = a.rt0 + wg.rt;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -684,8 +701,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   const int cch = t16p * 2 + (m >> 1);
   const bool publishes = (u & 3) == 0 && t16p < ntiles16;
   bool started[2] = {false, false};                      // (see the 32 x 8 kernel)
-  const bool local = a.xcc != nullptr &&
-                     group_is_xcd_local(a.xcc, (wg.dir * (int)gridDim.y + wg.rt) * (int)gridDim.x, gridDim.x, tile2, a.spin_limit);
+  const bool local = group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit);
 
   constexpr unsigned kParked = 0x7ff00000u;
   const unsigned g_bytes = (unsigned)B * 4u * n * 4u, y_bytes = (unsigned)B * d.ldy * 2u, s_bytes = (unsigned)B * n * 4u;
@@ -994,23 +1010,25 @@ constexpr float kPartScale = 1.f / 4294967296.f;          // 2^-32
 // (sigma - 1) & 1; alternates between consecutive uses of a slot and is 1 at the first, so zero-filled slots look unwritten
 __device__ __forceinline__ unsigned part_tag(int sigma) { return ((((unsigned)sigma - 1u) >> 1) & 1u) ^ 1u; }
 
-template <int NPW>                                        // producers per wavefront at most: n <= 128 * NPW
+template <int NPW, int NCT>                               // n <= 128 * NPW (producers per wavefront) and n <= 64 * NCT (its output column tiles)
 __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   __shared__ float red[8][8][33];                        // [wavefront, producer of the pair][row][output]
   __shared__ __attribute__((aligned(16))) unsigned short zb[8][136];
-  const WgCoord wg = wg_coord();
+  const WgCoord wg = wg_coord(a.map, a.ndir);
+  if (!wg.live) return;
+  publish_xcd(a.xcc, wg.base, wg.tile);
   const PBwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
-  const int J = wg.tile, R = 2 * a.rt0 + wg.rt, ntile2 = gridDim.x;     // R: row group of 8 rows, counted over the whole batch
+  const int J = wg.tile, R = 2 * a.rt0 + wg.rt, ntile2 = a.map.ntile;     // R: row group of 8 rows, counted over the whole batch
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int n = a.n, B = a.B, T = a.T;
   unsigned* err = a.sync;
   bool dead = false;
 
-  u32x4 w[4][16];                                        // all 256 accumulation registers
+  u32x4 w[4][NCT];                                       // all 256 accumulation registers at NCT = 16
 #pragma unroll
   for (int kc = 0; kc < 4; ++kc)
 #pragma unroll
-    for (int c = 0; c < 16; ++c) w[kc][c] = load_to_agpr(&d.Wb[((((long)J * 4 + wave) * 4 + kc) * 16 + c) * 64 + lane]);
+    for (int c = 0; c < NCT; ++c) w[kc][c] = load_to_agpr(&d.Wb[((((long)J * 4 + wave) * 4 + kc) * NCT + c) * 64 + lane]);
   agpr_loads_done();
 
   const int r8 = tid >> 5, u = tid & 31;                 // pointwise pair of this thread
@@ -1077,20 +1095,18 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   // consumer side: a load covers two producers' blocks; lane reads output lane%32, all eight rows, of producer lane/32
   const int ccol = lane & 31, chalf = lane >> 5;
   const int nitv = (ntile2 + 7) / 8, rot = J % nitv;
-  const long ring_tile = ((long)R * ntile2 + J) * ntile2 * (kPartBytes / 16);     // uint4 index of [R][J][0]
+  // (row group's part of the ring in bytes, below 2^31; wave-uniform by decree, see wg_coord)
+  const unsigned ring_group = __builtin_amdgcn_readfirstlane((unsigned)R * ntile2 * ntile2 * kPartBytes), ring_tile = __builtin_amdgcn_readfirstlane(ring_group + (unsigned)(J * ntile2 * kPartBytes));
   // producer side: lanes 0..31 hold rows 4*(lane/16) .. +3 of output column lane%16 of each accumulator tile
   const int pg = (lane >> 4) & 1, pcol = lane & 15;
-  // (the verdict comes out of shared memory; the compiler has to be told that it is the same in every lane, or the
-  // two copies of the publishing code below become one divergent region)
-  const bool local = __builtin_amdgcn_readfirstlane((int)(a.xcc != nullptr &&
-                     group_is_xcd_local(a.xcc, (wg.dir * (int)gridDim.y + wg.rt) * ntile2, ntile2, J, a.spin_limit))) != 0;
+  const int local = group_is_xcd_local(a.xcc, wg.base, ntile2, a.spin_limit);
   // byte offset, from row group R's part of the ring, of what this lane stores for accumulator tile c: destination tile
   // wave*8 + c/2 (one past the last falls outside the buffer), this producer's block, output column, row half.  Lanes
   // 32..63 hold copies of the same rows; their offset is parked outside the buffer and the store is dropped.
-  unsigned pub_off[16];
+  unsigned pub_off[NCT];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int Jd = wave * 8 + (c >> 1);
+  for (int c = 0; c < NCT; ++c) {
+    const int Jd = wave * (NCT / 2) + (c >> 1);
     pub_off[c] = lane < 32 ? (unsigned)(((Jd * ntile2 + J) * 32 + (c & 1) * 16 + pcol) * 2 + pg) * 8u : 0xfff00000u;
   }
 
@@ -1127,7 +1143,7 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
     };
     if constexpr (decltype(ring_c)::value) {
       RingReader rd;
-      rd.rs = __builtin_amdgcn_make_buffer_rsrc((void*)((((sigma - 1) & 1) ? d.ring1 : d.ring0) + ring_tile), 0, ntile2 * kPartBytes,
+      rd.rs = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)(((sigma - 1) & 1) ? d.ring1 : d.ring0) + ring_tile), 0, __builtin_amdgcn_readfirstlane(ntile2 * kPartBytes),
                                                 kBufFlags);
       // load `it` of this wavefront covers producers 2 * (wave + 4 * it) and the one after it (1 KiB)
       rd.voff = (unsigned)(wave * 2 * kPartBytes + lane * 16);
@@ -1249,13 +1265,13 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
       // consecutive bytes.  Each 8-byte half carries its own tag in its upper dword, so the only thing relied on
       // beyond the 64-bit units of the other kernels is that an aligned 16-byte lane store is not split below 8 bytes.
       const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(((sigma & 1) ? d.ring1 : d.ring0) + (long)R * ntile2 * ntile2 * (kPartBytes / 16)), 0, ntile2 * ntile2 * kPartBytes, kBufFlags);
+          (void*)((const char*)((sigma & 1) ? d.ring1 : d.ring0) + ring_group), 0, __builtin_amdgcn_readfirstlane(ntile2 * ntile2 * kPartBytes), kBufFlags);
       const unsigned tag_hi = part_tag(sigma + 1) << 30;
       u32x4 av[4];
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) av[kc] = *(const u32x4*)&zb[lane & 7][kc * 32 + (lane >> 4) * 8];
-      f32x4 acc[16];
-      // Sixteen column tiles, the k loop inside.  An MFMA of this shape issues every 16 cycles, of which the wavefront's
+      f32x4 acc[NCT];
+      // NCT column tiles, the k loop inside.  An MFMA of this shape issues every 16 cycles, of which the wavefront's
       // issue slot is taken for 4 (see the forward kernel for the measurements).  What publishes a tile (two conversions,
       // three moves and one store) is cut into single instructions that follow the MFMAs of the tile two behind it:
       // by then its last result has been written (more than the 20 wait states mfma_settle would spend), the
@@ -1276,7 +1292,7 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
         };
         operands_settle(av[0], av[1], av[2], av[3]);
 #pragma unroll
-        for (int c = 0; c < 16; ++c)
+        for (int c = 0; c < NCT; ++c)
 #pragma unroll
           for (int kc = 0; kc < 4; ++kc) {
             if (kc == 0) mfma_b_agpr_first(acc[c], av[kc], w[kc][c]);
@@ -1287,13 +1303,16 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
               __builtin_amdgcn_sched_barrier(0);
             }
           }
-        mfma_settle(acc[12], acc[13], acc[14], acc[15]);
+        mfma_settle(acc[NCT - 4], acc[NCT - 3], acc[NCT - 2], acc[NCT - 1]);
 #pragma unroll
-        for (int c = 16 - kPubLag; c < 16; ++c)
+        for (int c = NCT - kPubLag; c < NCT; ++c)
 #pragma unroll
           for (int k = 0; k < kPubSteps; ++k) pub_step(c, k);
       };
-      if (local) mma_publish(std::true_type{});
+      // (opaque in every step: the compiler would make two copies of the whole time loop otherwise)
+      int local_ = local;
+      asm volatile("" : "+s"(local_));
+      if (local_) mma_publish(std::true_type{});
       else mma_publish(std::false_type{});
       PROF_MARK(1)
       if (active) {
@@ -1344,24 +1363,26 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
 // doing real work (the 8-row form computes every row twice); a (producer, destination tile) block is 1 KiB -
 // [32 outputs][4 row quarters] x 8 bytes -, a consumer's load covers one producer (lane = output lane/2, row half lane%2),
 // so a wavefront reads eight loads per step instead of four, and the pointwise part runs twice.
-template <int NPW>                                        // producers per wavefront at most: n <= 128 * NPW
+template <int NPW, int NCT>                               // n <= 128 * NPW (producers per wavefront) and n <= 64 * NCT (its output column tiles)
 __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   __shared__ float red[4][16][33];                       // [wavefront][row][output]
   __shared__ __attribute__((aligned(16))) unsigned short zb[16][136];
   constexpr int kBlock = 2 * kPartBytes;                 // one (producer, destination tile)
-  const WgCoord wg = wg_coord();
+  const WgCoord wg = wg_coord(a.map, a.ndir);
+  if (!wg.live) return;
+  publish_xcd(a.xcc, wg.base, wg.tile);
   const PBwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
-  const int J = wg.tile, R = a.rt0 + wg.rt, ntile2 = gridDim.x;         // R: row group of 16 rows, counted over the whole batch
+  const int J = wg.tile, R = a.rt0 + wg.rt, ntile2 = a.map.ntile;         // R: row group of 16 rows, counted over the whole batch
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int n = a.n, B = a.B, T = a.T;
   unsigned* err = a.sync;
   bool dead = false;
 
-  u32x4 w[4][16];                                        // all 256 accumulation registers
+  u32x4 w[4][NCT];                                       // all 256 accumulation registers at NCT = 16
 #pragma unroll
   for (int kc = 0; kc < 4; ++kc)
 #pragma unroll
-    for (int c = 0; c < 16; ++c) w[kc][c] = load_to_agpr(&d.Wb[((((long)J * 4 + wave) * 4 + kc) * 16 + c) * 64 + lane]);
+    for (int c = 0; c < NCT; ++c) w[kc][c] = load_to_agpr(&d.Wb[((((long)J * 4 + wave) * 4 + kc) * NCT + c) * 64 + lane]);
   agpr_loads_done();
 
   const int r8 = tid >> 5, u = tid & 31;                 // pointwise pairs of this thread: rows r8 and r8 + 8, unit u
@@ -1441,19 +1462,17 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   // consumer side: a load covers one producer's block; lane reads output lane/2, rows 8 * (lane%2) .. + 7
   const int ccol = lane >> 1, chalf = lane & 1;
   const int nitv = (ntile2 + 3) / 4, rot = J % nitv;
-  const long ring_tile = ((long)R * ntile2 + J) * ntile2 * (kBlock / 16);         // uint4 index of [R][J][0]
+  // (row group's part of the ring in bytes, below 2^31; wave-uniform by decree, see wg_coord)
+  const unsigned ring_group = __builtin_amdgcn_readfirstlane((unsigned)R * ntile2 * ntile2 * kBlock), ring_tile = __builtin_amdgcn_readfirstlane(ring_group + (unsigned)(J * ntile2 * kBlock));
   // producer side: lane holds rows 4*(lane/16) .. +3 of output column lane%16 of each accumulator tile
   const int pq = lane >> 4, pcol = lane & 15;
-  // (the verdict comes out of shared memory; the compiler has to be told that it is the same in every lane, or the
-  // two copies of the publishing code below become one divergent region)
-  const bool local = __builtin_amdgcn_readfirstlane((int)(a.xcc != nullptr &&
-                     group_is_xcd_local(a.xcc, (wg.dir * (int)gridDim.y + wg.rt) * ntile2, ntile2, J, a.spin_limit))) != 0;
+  const int local = group_is_xcd_local(a.xcc, wg.base, ntile2, a.spin_limit);
   // byte offset, from row group R's part of the ring, of what this lane stores for accumulator tile c: destination tile
   // wave*8 + c/2 (one past the last falls outside the buffer), this producer's block, output column, row quarter
-  unsigned pub_off[16];
+  unsigned pub_off[NCT];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const int Jd = wave * 8 + (c >> 1);
+  for (int c = 0; c < NCT; ++c) {
+    const int Jd = wave * (NCT / 2) + (c >> 1);
     pub_off[c] = (unsigned)(((Jd * ntile2 + J) * 32 + (c & 1) * 16 + pcol) * 4 + pq) * 8u;
   }
 
@@ -1503,7 +1522,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
     };
     if constexpr (decltype(ring_c)::value) {
       RingReader rd;
-      rd.rs = __builtin_amdgcn_make_buffer_rsrc((void*)((((sigma - 1) & 1) ? d.ring1 : d.ring0) + ring_tile), 0, ntile2 * kBlock,
+      rd.rs = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)(((sigma - 1) & 1) ? d.ring1 : d.ring0) + ring_tile), 0, __builtin_amdgcn_readfirstlane(ntile2 * kBlock),
                                                 kBufFlags);
       // load `it` of this wavefront covers producer wave + 4 * it (1 KiB)
       rd.voff = (unsigned)(wave * kBlock + lane * 16);
@@ -1631,13 +1650,13 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
       // consecutive bytes.  Each 8-byte half carries its own tag in its upper dword, so the only thing relied on
       // beyond the 64-bit units of the other kernels is that an aligned 16-byte lane store is not split below 8 bytes.
       const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
-          (void*)(((sigma & 1) ? d.ring1 : d.ring0) + (long)R * ntile2 * ntile2 * (kBlock / 16)), 0, ntile2 * ntile2 * kBlock, kBufFlags);
+          (void*)((const char*)((sigma & 1) ? d.ring1 : d.ring0) + ring_group), 0, __builtin_amdgcn_readfirstlane(ntile2 * ntile2 * kBlock), kBufFlags);
       const unsigned tag_hi = part_tag(sigma + 1) << 30;
       u32x4 av[4];
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) av[kc] = *(const u32x4*)&zb[lane & 15][kc * 32 + (lane >> 4) * 8];
-      f32x4 acc[16];
-      // Sixteen column tiles, the k loop inside.  An MFMA of this shape issues every 16 cycles, of which the wavefront's
+      f32x4 acc[NCT];
+      // NCT column tiles, the k loop inside.  An MFMA of this shape issues every 16 cycles, of which the wavefront's
       // issue slot is taken for 4 (see the forward kernel for the measurements).  What publishes a tile (two conversions,
       // three moves and one store) is cut into single instructions that follow the MFMAs of the tile two behind it:
       // by then its last result has been written (more than the 20 wait states mfma_settle would spend), the
@@ -1658,7 +1677,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
         };
         operands_settle(av[0], av[1], av[2], av[3]);
 #pragma unroll
-        for (int c = 0; c < 16; ++c)
+        for (int c = 0; c < NCT; ++c)
 #pragma unroll
           for (int kc = 0; kc < 4; ++kc) {
             if (kc == 0) mfma_b_agpr_first(acc[c], av[kc], w[kc][c]);
@@ -1669,13 +1688,16 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
               __builtin_amdgcn_sched_barrier(0);
             }
           }
-        mfma_settle(acc[12], acc[13], acc[14], acc[15]);
+        mfma_settle(acc[NCT - 4], acc[NCT - 3], acc[NCT - 2], acc[NCT - 1]);
 #pragma unroll
-        for (int c = 16 - kPubLag; c < 16; ++c)
+        for (int c = NCT - kPubLag; c < NCT; ++c)
 #pragma unroll
           for (int k = 0; k < kPubSteps; ++k) pub_step(c, k);
       };
-      if (local) mma_publish(std::true_type{});
+      // (opaque in every step: the compiler would make two copies of the whole time loop otherwise)
+      int local_ = local;
+      asm volatile("" : "+s"(local_));
+      if (local_) mma_publish(std::true_type{});
       else mma_publish(std::false_type{});
       PROF_MARK(1)
 #pragma unroll
@@ -2178,14 +2200,17 @@ __device__ __forceinline__ void pack_wh_fwd_ll_body(long idx, const bf16_t* W, u
   }
   out[idx] = *(uint4*)v;
 }
-// partial-sum backward kernel: chunk index = ((((dir*ntile2 + J)*4 + wave)*4 + kc)*16 + c)*64 + lane ; B fragment of
-// gate kc, K = the 32 units of tile J, columns = outputs (wave*16 + c)*16 .. +15
-__device__ __forceinline__ void pack_wh_bwdp_body(long idx, const bf16_t* W, uint4* out, int n, int ntile2, long total) {
+// partial-sum backward kernel: chunk index = ((((dir*ntile2 + J)*4 + wave)*4 + kc)*nct + c)*64 + lane ; B fragment of
+// gate kc, K = the 32 units of tile J, columns = outputs (wave*nct + c)*16 .. +15
+__device__ __forceinline__ void pack_wh_bwdp_body(long idx, const bf16_t* W, uint4* out, int n, int ntile2, int nct, long total) {
   if (idx >= total) return;
-  const int lane = idx & 63, c = (idx >> 6) & 15, kc = (idx >> 10) & 3, wave = (idx >> 12) & 3;
-  const long rest = idx >> 14;
+  const int lane = idx & 63;
+  long rest = idx >> 6;
+  const int c = rest % nct; rest /= nct;
+  const int kc = rest & 3, wave = (rest >> 2) & 3;
+  rest >>= 4;
   const int J = rest % ntile2, dir = rest / ntile2;
-  const int jout = (wave * 16 + c) * 16 + (lane & 15), g = lane >> 4;
+  const int jout = (wave * nct + c) * 16 + (lane & 15), g = lane >> 4;
   const bf16_t* Wd = W + (long)dir * n * 4 * n;
   bf16_t v[8];
 #pragma unroll
@@ -2209,7 +2234,7 @@ __device__ __forceinline__ void pack_state_ll_body(long idx, uint4* ring0, uint4
 // (frame_map_body) when the products that follow go over real frames only.
 struct PrepArgs {
   ZeroRegions z;
-  const bf16_t* W; uint4* Wout; int n, nk; long w_total;   // nk: nkc (forward) / ntile2 (backward)
+  const bf16_t* W; uint4* Wout; int n, nk, nct; long w_total;   // nk: nkc (forward) / ntile2 (backward)
   uint4* ring0; uint4* ring1; long ring_total;
   const int* lens; int T, B; int* cidx; int* fidx; int* count;     // frame map (cidx == NULL: none)
   int first_pack, first_ring, first_map, backward;
@@ -2227,7 +2252,7 @@ __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
     for (size_t i = (size_t)(bid - a.z.first_block[k]) * 256 + threadIdx.x; i < nwords; i += nb * 256) p[i] = 0u;
   } else if (bid < a.first_ring) {
     const long idx = (long)(bid - a.first_pack) * 256 + threadIdx.x;
-    if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.w_total);
+    if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, a.w_total);
     else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, a.w_total);
   } else if (bid < a.first_map) {
     pack_state_ll_body((long)(bid - a.first_ring) * 256 + threadIdx.x, a.ring0, a.ring1, a.ring_total);
@@ -2255,7 +2280,7 @@ __global__ __launch_bounds__(256) void h0_term_kernel(const float* h0, const TW*
 std::mutex g_capacity_mu;
 std::map<std::pair<int, const void*>, int> g_capacity;    // (device, kernel) -> work-groups of the kernel that device holds at once
 
-// How many work-groups of `kernel` the current device holds at once (0 if that cannot be found out).
+// How many work-groups of `kernel` the current device holds at once, one per compute unit (0 if that cannot be found out).
 template <typename K>
 int capacity(K kernel) {
   int dev = 0;
@@ -2271,16 +2296,13 @@ int capacity(K kernel) {
       (void)hipGetLastError();
       return 0;
     }
-    it = g_capacity.emplace(key, per_cu * prop.multiProcessorCount).first;
+    it = g_capacity.emplace(key, std::min(per_cu, 1) * prop.multiProcessorCount).first;
   }
   return it->second;
 }
-// Can `grid` be resident all at once (the condition of a cooperative launch)?
-template <typename K>
-bool fits_device(K kernel, dim3 grid) { return (long)grid.x * grid.y * grid.z <= capacity(kernel); }
 
-// Cooperative launches over the batch in slabs of whole 16-row tiles.  A work-group owns `rows_per_y` rows (16 or 8),
-// so one row tile takes grid.x * (16 / rows_per_y) * ndir work-groups; as many row tiles as the device can hold at
+// Cooperative launches over the batch in slabs of whole 16-row tiles (or of all rows).  A work-group owns `rows_per_group` rows
+// (16 or 8), so a row group takes ntile * ndir work-groups; as many row groups as the device can hold at
 // once go into one launch (the kernels need every work-group of a launch resident together), the rest follow in
 // further launches on the same stream: batch rows never interact, each launch walks all T steps of its rows.
 // Between launches the table in which exchange groups record their XCD is cleared again.  Returns
@@ -2289,18 +2311,22 @@ bool fits_device(K kernel, dim3 grid) { return (long)grid.x * grid.y * grid.z <=
 // kernel form or the per-step path on the untouched state); any other error = a later slab failed after earlier
 // slabs had already advanced the state of their rows, so the call as a whole has failed and nothing may be re-run.
 template <typename K, typename A>
-hipError_t coop_slabs(K kernel, int grid_x, int rows_per_y, const A& a, hipStream_t s) {
-  const int per_rt = 16 / rows_per_y, nrt = cdiv(a.B, 16);
+hipError_t coop_slabs(K kernel, int ntile, int rows_per_group, const A& a, hipStream_t s) {
+  const int per_rt = 16 / rows_per_group, nrow = cdiv(a.B, rows_per_group);
   const long cap = capacity(kernel);
-  const long slab = cap / ((long)grid_x * per_rt * a.ndir);            // row tiles per launch
+  const long most = cap / ((long)ntile * a.ndir);                      // row groups per launch
+  const int slab = most >= nrow ? nrow : (int)(most / per_rt * per_rt);
   if (slab < 1) return hipErrorCooperativeLaunchTooLarge;
-  for (int rt0 = 0; rt0 < nrt; rt0 += (int)slab) {
+  for (int row0 = 0; row0 < nrow; row0 += slab) {
     A copy = a;
-    copy.rt0 = rt0;
-    const int here = (int)std::min<long>(slab, nrt - rt0);
-    const dim3 grid(grid_x, per_rt * here, a.ndir);
-    if (rt0 > 0 && a.xcc) {
-      const hipError_t e = launch_fill_zero(a.xcc, (size_t)grid_x * per_rt * slab * a.ndir * 4, s);
+    copy.rt0 = row0 / per_rt;
+    copy.map.ntile = ntile;
+    copy.map.nrow = std::min(slab, nrow - row0);
+    const int groups = copy.map.nrow * a.ndir, gpx = cdiv(groups, 8);
+    copy.map.gpx = (long)gpx * ntile <= cap / 8 ? gpx : 0;
+    const dim3 grid(copy.map.gpx ? 8 * gpx * ntile : groups * ntile);
+    if (row0 > 0 && a.xcc) {
+      const hipError_t e = launch_fill_zero(a.xcc, (size_t)ntile * slab * a.ndir * 4, s);
       if (e != hipSuccess) return e == hipErrorCooperativeLaunchTooLarge ? hipErrorLaunchFailure : e;
     }
     void* args[] = {&copy};
@@ -2310,7 +2336,7 @@ hipError_t coop_slabs(K kernel, int grid_x, int rows_per_y, const A& a, hipStrea
                                         : hipLaunchCooperativeKernel((const void*)kernel, grid, dim3(256), args, 0, s);
     if (e != hipSuccess) {
       (void)hipGetLastError();
-      if (rt0 == 0) return hipErrorCooperativeLaunchTooLarge;          // the first launch was refused: nothing has run
+      if (row0 == 0) return hipErrorCooperativeLaunchTooLarge;         // the first launch was refused: nothing has run
       return e == hipErrorCooperativeLaunchTooLarge ? hipErrorLaunchFailure : e;
     }
   }
@@ -2323,49 +2349,52 @@ inline bool offsets_fit(long B, long n, long ld_out, long ring_bytes) {
   return B * 4 * n * 4 < lim && B * ld_out * 2 < lim && ring_bytes < lim;
 }
 template <typename K>
-bool slab_fits(K kernel, int grid_x, int rows_per_y, int ndir) {
-  return capacity(kernel) >= (long)grid_x * (16 / rows_per_y) * ndir;
+bool slab_fits(K kernel, int ntile, int rows_per_group, int nrow, int ndir) {
+  return capacity(kernel) >= (long)ntile * std::min(16 / rows_per_group, nrow) * ndir;
 }
+// The form of a kernel for n units: half (a quarter) of the registers' worth of weights, MFMAs and ring loads per step
+// for n <= 512 (256).
+typedef void (*FwdKernel)(PFwdArgs);
+typedef void (*BwdKernel)(PBwdArgs);
+FwdKernel fwd8_for(int n) { return n <= 512 ? persist_fwd8_kernel<4> : persist_fwd8_kernel<8>; }
+FwdKernel fwd16_for(int n) { return n <= 512 ? persist_fwd16r_kernel<4> : persist_fwd16r_kernel<8>; }
+BwdKernel bwd8_for(int n) { return n <= 256 ? persist_bwdp_kernel<4, 4> : n <= 512 ? persist_bwdp_kernel<4, 8> : persist_bwdp_kernel<8, 16>; }
+BwdKernel bwd16_for(int n) { return n <= 256 ? persist_bwdp16_kernel<4, 4> : n <= 512 ? persist_bwdp16_kernel<4, 8> : persist_bwdp16_kernel<8, 16>; }
 
 }  // namespace
 
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s) {
-  if (a.nkc > kLLMaxNkcFwd) return hipErrorCooperativeLaunchTooLarge;
-  if (!offsets_fit(a.B, a.n, std::max(a.d[0].ldy, a.d[a.ndir - 1].ldy), (long)cdiv(a.B, 16) * a.nkc * 1024)) return hipErrorCooperativeLaunchTooLarge;
-  const int t32 = cdiv(cdiv(a.n, 16), 2), nrt = cdiv(a.B, 16);
+  if (!persist_fwd_fits(a)) return hipErrorCooperativeLaunchTooLarge;
+  const int t32 = cdiv(a.n, 32);
   // more rows than the 32 x 8 form holds in one launch: 32 units x 16 rows, if that takes a single launch
-  if ((long)t32 * 2 * nrt * a.ndir > capacity(persist_fwd8_kernel<kLLMaxNkcFwd / 4>) &&
-      (long)t32 * nrt * a.ndir <= capacity(persist_fwd16r_kernel<kLLMaxNkcFwd / 4>)) {
-    const hipError_t e16 = coop_slabs(persist_fwd16r_kernel<kLLMaxNkcFwd / 4>, t32, 16, a, s);
+  if ((long)t32 * cdiv(a.B, 8) * a.ndir > capacity(fwd8_for(a.n)) && (long)t32 * cdiv(a.B, 16) * a.ndir <= capacity(fwd16_for(a.n))) {
+    const hipError_t e16 = coop_slabs(fwd16_for(a.n), t32, 16, a, s);
     if (e16 != hipErrorCooperativeLaunchTooLarge) return e16;
     (void)hipGetLastError();
   }
   // 32 units x 8 rows per work-group
-  return coop_slabs(persist_fwd8_kernel<kLLMaxNkcFwd / 4>, t32, 8, a, s);
+  return coop_slabs(fwd8_for(a.n), t32, 8, a, s);
 }
 // Would launch_persist_fwd launch anything?  (Asked before the initial state's term is added to the pre-activations,
 // which only the single-launch kernels expect there.)
 bool persist_fwd_fits(const PFwdArgs& a) {
   if (a.nkc > kLLMaxNkcFwd) return false;
   if (!offsets_fit(a.B, a.n, std::max(a.d[0].ldy, a.d[a.ndir - 1].ldy), (long)cdiv(a.B, 16) * a.nkc * 1024)) return false;
-  const int t32 = cdiv(cdiv(a.n, 16), 2);
-  return slab_fits(persist_fwd8_kernel<kLLMaxNkcFwd / 4>, t32, 8, a.ndir);
+  return slab_fits(fwd8_for(a.n), cdiv(a.n, 32), 8, cdiv(a.B, 8), a.ndir);
 }
 bool persist_bwd_fits(const PBwdArgs& a) {
-  const int t32 = cdiv(cdiv(a.n, 16), 2);
   if (!offsets_fit(a.B, a.n, std::max(a.d[0].lddy, a.d[a.ndir - 1].lddy), (long)bwdp_ring_bytes(a.B, a.n))) return false;
-  return a.n <= 1024 && slab_fits(persist_bwdp_kernel<8>, t32, 8, a.ndir);
+  return a.n <= 1024 && slab_fits(bwd8_for(a.n), cdiv(a.n, 32), 8, cdiv(a.B, 8), a.ndir);
 }
 hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s) {
-  const int t32 = cdiv(cdiv(a.n, 16), 2);
+  const int t32 = cdiv(a.n, 32);
   // more rows than the 8-row form holds in one launch: 16 rows per work-group, if that takes a single launch
-  const int nrt = cdiv(a.B, 16);
-  if ((long)t32 * 2 * nrt * a.ndir > capacity(persist_bwdp_kernel<8>) && (long)t32 * nrt * a.ndir <= capacity(persist_bwdp16_kernel<8>)) {
-    const hipError_t e16 = coop_slabs(persist_bwdp16_kernel<8>, t32, 16, a, s);
+  if ((long)t32 * cdiv(a.B, 8) * a.ndir > capacity(bwd8_for(a.n)) && (long)t32 * cdiv(a.B, 16) * a.ndir <= capacity(bwd16_for(a.n))) {
+    const hipError_t e16 = coop_slabs(bwd16_for(a.n), t32, 16, a, s);
     if (e16 != hipErrorCooperativeLaunchTooLarge) return e16;
     (void)hipGetLastError();
   }
-  return coop_slabs(persist_bwdp_kernel<8>, t32, 8, a, s);
+  return coop_slabs(bwd8_for(a.n), t32, 8, a, s);
 }
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, uint4* ring0, uint4* ring1,
                               int nrt, const FrameMapArgs& fm, hipStream_t s) {
@@ -2384,7 +2413,7 @@ hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, in
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
-  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.w_total = (long)ndir * a.nk * 4 * 4 * 16 * 64;
+  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.nct = bwdp_nct(n); a.w_total = (long)ndir * a.nk * 4 * 4 * a.nct * 64;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.first_map = a.first_ring;
