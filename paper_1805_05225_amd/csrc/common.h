@@ -60,10 +60,12 @@ struct GemmArgs {
   int a_phys_rows;                        // rows of A in memory when a_rows is given
   const int* m_dev; const int* k_dev;     // M / K read from device memory (capped by M / K above, which size the grid)
   const int* k_rows; int k_phys_rows;     // both operands k-major: k -> row of A and of B in memory; rows each holds in memory
+                                          // (A k-contiguous, B k-major: k_phys_rows > 0 = rows of B, where A's rows are padded up to K)
   int ksplit;                             // > 1: K cut into that many ranges whose parts are ADDED to C atomically
                                           // (float C, nseg == 1; C must hold zeros or the value to add to) ...
   float* parts;                           // ... or, if not NULL (nz * ksplit * M * ldc floats, no c_rows): every range stores
                                           // its part there and a second kernel writes C (+)= their sum (`accumulate` honoured)
+  size_t parts_bytes;                     // what `parts` holds (gemm_tile.hip, which plans its own ranges)
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for problems with both operands k-contiguous, 16-byte aligned rows and K % 8 == 0
@@ -74,6 +76,13 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s);
 // float C.  Row k of both operands is row k_rows[k] in memory if k_rows is given (launch_gemm routes to it by itself).
 bool gemm_tn_ok(const GemmArgs& g);
 hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s);
+// bfloat16 products with few 256 x 256 tiles, and A k-contiguous x B k-major at any size (gemm_tile.hip; launch_gemm routes to it by itself).
+// It cuts K into ranges of its own if `parts` holds gemm_tile_parts_bytes.
+bool gemm_tile_ok(const GemmArgs& g);
+bool gemm_tile_small(long M, long N, int nz);
+int gemm_tile_ranges(long M, long N, long K, int nz, int nseg);
+size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg);
+hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s);
 // Float storage (gemm_float.hip): operands as they lie in memory, rows 16-byte aligned, extents along 16-byte chunks
 // multiples of 4 (K for a k-contiguous operand, M / N for a k-major one); row maps, device-resident M / K, segments
 // and atomic K ranges as above (launch_gemm routes to it by itself; what it does not take goes to the generic kernel).
@@ -113,7 +122,7 @@ struct FwdDir {
   float* cstate;
   void* y; long ldy;  // row b of this frame's output at y + b*ldy (storage type)
   float* cs;          // frame slab [B][n] or NULL
-  void* hprev;        // frame slab [B][n] (storage type) or NULL
+  void* hprev; long ldh;   // frame slab [B][ldh >= n] (storage type) or NULL
   int t;              // frame index of this step
 };
 struct FwdArgs {
@@ -175,7 +184,7 @@ struct PFwdDir {
   float* hstate; float* cstate;
   void* y; long ldy;  // y + column offset of this direction; frame stride B*ldy
   float* cs;          // [T][B][n] or NULL
-  void* hprev;        // [T][B][n] or NULL
+  void* hprev; long ldh;   // [T][B][ldh >= n] or NULL (float storage: ldh = n)
   int rev;            // 0: t = tau, 1: t = T-1-tau
 };
 struct PFwdArgs {

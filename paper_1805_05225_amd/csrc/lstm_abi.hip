@@ -23,13 +23,16 @@ struct Plan {
   size_t esz;
   int nkc_f, nkc_b, nrt, ntile_f, ntile_b;
   int nkc_ll_f, ntile16;                    // ring layout of the single-launch forward kernels
-  // reserve: per direction [gates float T*B*4n][hprev storage T*B*n]
+  // reserve: per direction [gates float T*B*4n][hprev storage T*B*ldh], ldh = n, in bfloat16 rounded up to rows of whole 16-byte chunks
+  long ldh;
   size_t res_gates, res_hprev, res_dir_stride, reserve_bytes;
   // workspace
   size_t ws_Wf, ws_Wb, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
-      ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_XT, ws_DZT, ws_HT, ws_cidx, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, workspace_bytes;
+      ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_cidx, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
   int ks_dwx, ks_dwh, ks_dx;                // K ranges of the weight-gradient products and of dX (few output tiles: the whole device works on them)
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
+  bool zx_nn;                               // few 256 x 256 tiles: Zx from W_x as it lies in memory (gemm_tile.hip)
+  int n_in8;                                // n_in up to whole 16-byte chunks: row length of the padded copy of x there and for dW_x
   bool fast_gemm; int n_in_pad; long TBp;   // bf16 products through the k-contiguous kernel (operands transposed once)
   size_t hfrag_bytes, dzfrag_bytes, DZ_dir_elems, Zx_dir_elems, Wf_bytes;
 };
@@ -57,7 +60,8 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   const bool infer = d->flags & LSTM_FLAG_INFERENCE;
   p->res_gates = 0;
   p->res_hprev = up(TB * 4 * n * 4);
-  p->res_dir_stride = p->res_hprev + up(TB * n * p->esz);
+  p->ldh = p->bf16 ? (d->n + 7) / 8 * 8 : d->n;
+  p->res_dir_stride = p->res_hprev + up(TB * p->ldh * p->esz);
   p->reserve_bytes = D * p->res_dir_stride + kAlign;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up(bytes); return at; };
@@ -108,11 +112,10 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->fast_gemm = p->bf16 && d->n % 2 == 0;
   p->TBp = (TB + 63) / 64 * 64;
   const bool fg = p->fast_gemm;
-  p->ws_WxT = take(fg ? D * 4 * n * p->n_in_pad * 2 : 0);
-  p->ws_xpad = take(fg && p->n_in_pad != d->n_in ? TB * p->n_in_pad * 2 : 0);
-  p->ws_XT = take(fg && !infer ? (size_t)d->n_in * p->TBp * 2 : 0);
-  p->ws_DZT = take(fg && !infer ? D * 4 * n * p->TBp * 2 : 0);
-  p->ws_HT = take(fg && !infer ? D * n * p->TBp * 2 : 0);
+  p->n_in8 = (d->n_in + 7) / 8 * 8;
+  p->zx_nn = fg && gemm_tile_small(TB, 4L * d->n, p->D);
+  p->ws_WxT = take(fg && !p->zx_nn ? D * 4 * n * p->n_in_pad * 2 : 0);
+  p->ws_xpad = take(fg ? TB * std::max(!p->zx_nn && p->n_in_pad != d->n_in ? p->n_in_pad : 0, p->n_in8 != d->n_in ? p->n_in8 : 0) * 2 : 0);
   // frame map of the batch (which frames are real), used to leave padded frames out of the products
   const bool fm = fg || !p->bf16;             // (float storage: its product kernels take the same row maps)
   p->ws_cidx = take(fm ? (size_t)TB * 4 : 0);
@@ -140,8 +143,14 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   }
   p->ks_dwx = fg && !infer ? ksplit_for(d->n_in, 4L * d->n) : 1;
   p->ks_dwh = fg && !infer ? ksplit_for(d->n, 4L * d->n) : 1;
-  p->ws_parts = take(std::max({p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
-                               p->ks_dx > 1 ? (size_t)p->ks_dx * TB * d->n_in * 4 : 0}));
+  // (the same products where gemm_tile.hip takes them: its own ranges)
+  const auto tile_parts = [&](long M, long N, long K, int nz, int nseg) { return fg && gemm_tile_small(M, N, nz) ? gemm_tile_parts_bytes(M, N, K, nz, nseg) : (size_t)0; };
+  size_t tp = TB > 0 && p->zx_nn && !p->single_step ? tile_parts(TB, 4L * d->n, p->n_in8, p->D, 1) : 0;
+  if (!infer && TB > 0)
+    tp = std::max({tp, tile_parts(TB, d->n_in, 4L * d->n, 1, p->D), tile_parts(d->n_in, 4L * d->n, TB, p->D, 1), tile_parts(d->n, 4L * d->n, TB, p->D, 1)});
+  p->parts_bytes = std::max({tp, p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
+                               p->ks_dx > 1 ? (size_t)p->ks_dx * TB * d->n_in * 4 : 0});
+  p->ws_parts = take(p->parts_bytes);
   p->workspace_bytes = o + kAlign;
   return LSTM_OK;
 }
@@ -311,16 +320,23 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
     {
       Phase ph(LSTM_PHASE_GEMM_ZX, 1, s);
-      if (p.fast_gemm) {                 // W_x is transposed once so that both operands are k-contiguous
-        HIPCHK(launch_transpose(W_x, ws + p.ws_WxT, p.n_in, 4 * p.n, 4 * n, p.n_in_pad, p.D, (long)p.n_in * 4 * n,
-                                (long)(4 * n) * p.n_in_pad, nullptr, 1, 0, s));
-        if (p.n_in_pad != p.n_in) {      // rows of x are not 16-byte aligned, or narrow: zero-padded copy
-          HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), p.n_in, p.n_in_pad, s));
+      if (p.fast_gemm) {
+        const int ldx = p.zx_nn ? p.n_in8 : p.n_in_pad;
+        if (ldx != p.n_in) {             // rows of x are not 16-byte aligned, or narrow: zero-padded copy
+          HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), p.n_in, ldx, s));
           g.A = ws + p.ws_xpad;
         }
-        g.B = ws + p.ws_WxT; g.K = p.n_in_pad; g.lda = p.n_in_pad; g.ldb = p.n_in_pad;
-        g.sBz = (long)(4 * n) * p.n_in_pad; g.b_kcontig = true;
-        if (seq_lens && gemm_nt_ok(g)) {
+        g.K = ldx; g.lda = ldx;
+        if (p.zx_nn) {                   // few tiles: W_x as it lies in memory
+          g.k_phys_rows = p.n_in;
+          g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
+          if (!gemm_tile_ok(g)) { g.K = p.n_in; g.k_phys_rows = 0; g.parts = nullptr; }   // (operands past 2 GB: the generic kernel, which knows no padding)
+        } else {                         // W_x is transposed once so that both operands are k-contiguous
+          HIPCHK(launch_transpose(W_x, ws + p.ws_WxT, p.n_in, 4 * p.n, 4 * n, p.n_in_pad, p.D, (long)p.n_in * 4 * n,
+                                  (long)(4 * n) * p.n_in_pad, nullptr, 1, 0, s));
+          g.B = ws + p.ws_WxT; g.ldb = p.n_in_pad; g.sBz = (long)(4 * n) * p.n_in_pad; g.b_kcontig = true;
+        }
+        if (seq_lens && (p.zx_nn ? gemm_tile_ok(g) : gemm_nt_ok(g))) {
           // only real frames are projected: row r of the product is frame fidx[r]; the pre-activations of padded
           // frames stay unwritten and are never read
           int* fidx = (int*)(ws + p.ws_fidx);
@@ -358,6 +374,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         fd.ldy = (long)(D * n);
         fd.cs = c ? (float*)c + d * T * B * n : nullptr;
         fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev;
+        fd.ldh = p.ldh;
         fd.rev = bidir ? d == 1 : desc->direction == -1;
       }
       hipError_t e = hipErrorCooperativeLaunchTooLarge;
@@ -401,6 +418,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         fd.ldy = (long)(D * n);
         fd.cs = c ? (float*)c + d * T * B * n : nullptr;
         fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev;
+        fd.ldh = p.ldh;
         fd.rev = bidir ? d == 1 : desc->direction == -1;
       }
       hipError_t e = hipErrorCooperativeLaunchTooLarge;
@@ -441,7 +459,8 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         fd.y = (char*)y + (t * B * D * n + d * n) * p.esz;
         fd.ldy = (long)(D * n);
         fd.cs = c ? (float*)c + (d * T + t) * B * n : nullptr;
-        fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev + t * B * n * p.esz;
+        fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev + t * B * p.ldh * p.esz;
+        fd.ldh = p.ldh;
         fd.t = (int)t;
       }
       HIPCHK(launch_step_fwd(a, p.bf16, s));
@@ -611,8 +630,6 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   int* cidx = (int*)(ws + p.ws_cidx);
   int* fidx = (int*)(ws + p.ws_fidx);
   int* count = (int*)(ws + p.ws_count);
-  const auto fits = [](long rows, long ld) { return rows * ld * 2 <= 0x7fffff00L; };
-  const bool compact_w = compact && fits(p.n_in, p.TBp) && fits(4L * p.n, p.TBp) && fits(p.n, p.TBp);
   if (compact && !use_ll) {          // (the bfloat16 single-launch path numbered the frames in its set-up launch)
     Phase ph(LSTM_PHASE_PREP, 1, s);
     HIPCHK(launch_frame_map(seq_lens, p.T, p.B, cidx, fidx, count, s));
@@ -631,7 +648,9 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       if (!dx_cleared) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
       g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = TB; g.m_dev = count;
     }
-    if (p.ks_dx > 1 && gemm_nt_ok(g)) { g.ksplit = p.ks_dx; g.parts = (float*)(ws + p.ws_parts); }
+    g.parts_bytes = 0;
+    if (p.bf16 && gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+    else if (p.ks_dx > 1 && gemm_nt_ok(g)) { g.ksplit = p.ks_dx; g.parts = (float*)(ws + p.ws_parts); }
     if (!p.bf16 && p.ks_dx == 8) {
       g.ksplit = 8; g.parts = (float*)(ws + p.ws_parts);
       if (!gemm_float_ok(g)) { g.ksplit = 0; g.parts = nullptr; }
@@ -658,51 +677,23 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
     g.vecA = 16; g.vecB = 16;
     if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
-    if (ks > 1) { g.ksplit = ks; g.parts = (float*)(ws + p.ws_parts); }
+    if (gemm_tile_small(M, 4L * p.n, p.D)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+    else if (ks > 1) { g.ksplit = ks; g.parts = (float*)(ws + p.ws_parts); }
     return g;
   };
-  const GemmArgs gx = frame_major(x, n_in, 0, p.n_in, dW_x, p.ks_dwx);
-  const GemmArgs gh = frame_major(rs + p.res_hprev, n, (long)(p.res_dir_stride / 2), p.n, dW_h, p.ks_dwh);
-  if (p.fast_gemm && (!seq_lens || compact) && gemm_tn_ok(gx) && gemm_tn_ok(gh)) {
+  const bool pad_x = p.n_in8 != p.n_in;                          // rows of x are not 16-byte aligned: padded copy
+  const GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x, p.ks_dwx);
+  const GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h, p.ks_dwh);
+  const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
+  if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
     {
       Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+      if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
       HIPCHK(launch_gemm(gx, s));
     }
     {
       Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
       HIPCHK(launch_gemm(gh, s));
-    }
-  } else if (p.fast_gemm) {        // operands transposed once: everything k-contiguous
-    const long TBp = p.TBp;
-    {
-      Phase ph(LSTM_PHASE_GEMM_DWX, 3, s);
-      const int* cmap = compact_w ? cidx : nullptr;
-      HIPCHK(launch_transpose(DZ, ws + p.ws_DZT, TB, 4 * p.n, 4 * n, TBp, p.D, (long)p.DZ_dir_elems, (long)(4 * n) * TBp,
-                              nullptr, 1, 0, s, cmap, fidx, count));
-      HIPCHK(launch_transpose(x, ws + p.ws_XT, TB, p.n_in, n_in, TBp, 1, 0, 0, seq_lens, p.B, p.T, s, cmap, fidx, count));
-      GemmArgs g = {};
-      g.A = ws + p.ws_XT; g.B = ws + p.ws_DZT; g.C = dW_x;
-      g.M = p.n_in; g.N = 4 * p.n; g.K = (int)TBp; g.lda = TBp; g.ldb = TBp; g.ldc = 4 * n;
-      g.sAz = 0; g.sBz = (long)(4 * n) * TBp; g.sCz = (long)(n_in * 4 * n); g.nz = p.D; g.nseg = 1;
-      g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
-      g.vecA = 16; g.vecB = 16;
-      if (compact_w) g.k_dev = count + 1;
-      if (gemm_nt_ok(g) && p.ks_dwx > 1) { g.ksplit = p.ks_dwx; g.parts = (float*)(ws + p.ws_parts); }
-      HIPCHK(launch_gemm(g, s));
-    }
-    {
-      Phase ph(LSTM_PHASE_GEMM_DWH, 2, s);
-      HIPCHK(launch_transpose(rs + p.res_hprev, ws + p.ws_HT, TB, p.n, n, TBp, p.D, (long)(p.res_dir_stride / 2), (long)n * TBp,
-                              nullptr, 1, 0, s, compact_w ? cidx : nullptr, fidx, count));
-      GemmArgs g = {};
-      g.A = ws + p.ws_HT; g.B = ws + p.ws_DZT; g.C = dW_h;
-      g.M = p.n; g.N = 4 * p.n; g.K = (int)TBp; g.lda = TBp; g.ldb = TBp; g.ldc = 4 * n;
-      g.sAz = (long)n * TBp; g.sBz = (long)(4 * n) * TBp; g.sCz = (long)(n * 4 * n); g.nz = p.D; g.nseg = 1;
-      g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
-      g.vecA = 16; g.vecB = 16;
-      if (compact_w) g.k_dev = count + 1;
-      if (gemm_nt_ok(g) && p.ks_dwh > 1) { g.ksplit = p.ks_dwh; g.parts = (float*)(ws + p.ws_parts); }
-      HIPCHK(launch_gemm(g, s));
     }
   } else {                         // dW_x = X^T DZ, padded frames of X masked out
     GemmArgs g = {};
@@ -720,7 +711,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       HIPCHK(launch_gemm(g, s));
     }
     // dW_h = Hprev^T DZ
-    g.A = rs + p.res_hprev; g.C = dW_h; g.M = p.n; g.lda = n;
+    g.A = rs + p.res_hprev; g.C = dW_h; g.M = p.n; g.lda = p.ldh;
     g.sAz = (long)(p.res_dir_stride / p.esz); g.sCz = (long)(n * 4 * n);
     g.lens = nullptr;
     g.vecA = widest(g.lda, g.sAz, 0, p.esz, 4);

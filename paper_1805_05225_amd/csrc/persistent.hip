@@ -409,12 +409,13 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   // compiler has to assume the fewest when it places the waits.
   // The outputs go the same way: one descriptor per array and frame (zero-sized if the array is absent), offsets
   // that never change, parked where a lane has nothing to store; and so does the ring store, whose descriptor ends
-  // below the parking offset.  Frame sizes in bytes: gates [B,4n] float, y [B,ldy] bf16, cs [B,n] float, hprev [B,n] bf16.
+  // below the parking offset.  Frame sizes in bytes: gates [B,4n] float, y [B,ldy] bf16, cs [B,n] float, hprev [B,ldh] bf16.
   constexpr unsigned kParked = 0x7ff00000u;
   const unsigned g_bytes = (unsigned)B * 4u * n * 4u, y_bytes = (unsigned)B * d.ldy * 2u, s_bytes = (unsigned)B * n * 4u;
   const unsigned g_off = active ? ((unsigned)b * 4u * n + j) * 4u : kParked;
   const unsigned y_off = active ? ((unsigned)b * d.ldy + j) * 2u : kParked;
-  const unsigned s_off = active ? ((unsigned)b * n + j) * 4u : kParked;        // (half of it in the bf16 array; still parked)
+  const unsigned s_off = active ? ((unsigned)b * n + j) * 4u : kParked;
+  const unsigned h_bytes = (unsigned)B * (unsigned)d.ldh * 2u, h_off = active ? ((unsigned)b * (unsigned)d.ldh + j) * 2u : kParked;
   const unsigned pub_off = publishes ? (unsigned)unit_index * 8u : kParked;
   auto frame_of = [&](const void* base, int t, unsigned bytes, bool present = true) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)t * bytes), 0, present && base != nullptr ? bytes : 0u, kBufFlags);
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
     {                                 // layer outputs and what the backward pass needs (2: non-temporal)
       __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(valid ? h_bits : 0u), frame_of(d.y, t, y_bytes), y_off, 0, 2);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c), frame_of(d.cs, t, s_bytes), s_off, 0, 2);
-      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)h_prev_bits, frame_of(d.hprev, t, s_bytes >> 1), s_off >> 1, 0, 2);
+      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)h_prev_bits, frame_of(d.hprev, t, h_bytes), h_off, 0, 2);
       const __amdgpu_buffer_rsrc_t rw = frame_of(d.gates, t, g_bytes, a.write_gates != 0);
       const unsigned gw = valid ? g_off : kParked;
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.gi), rw, gw, 0u, 2);
@@ -711,10 +712,12 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   const unsigned g_off0 = active[0] ? (b0 * 4u * n + j) * 4u : kParked;
   const unsigned y_off0 = active[0] ? (b0 * d.ldy + j) * 2u : kParked;
   const unsigned s_off0 = active[0] ? (b0 * n + j) * 4u : kParked;
+  const unsigned h_bytes = (unsigned)B * (unsigned)d.ldh * 2u, h_off0 = active[0] ? (b0 * (unsigned)d.ldh + j) * 2u : kParked;
   const unsigned pub_off0 = publishes ? (unsigned)((((long)rt * nkc + (cch >> 2)) * 64 + (cch & 3) * 16 + r8) * 2 + (m & 1)) * 8u : kParked;
   auto g_off = [&](int k) { return k == 0 ? g_off0 : (active[1] ? g_off0 + 8u * 4u * n * 4u : kParked); };
   auto y_off = [&](int k) { return k == 0 ? y_off0 : (active[1] ? y_off0 + 8u * (unsigned)d.ldy * 2u : kParked); };
   auto s_off = [&](int k) { return k == 0 ? s_off0 : (active[1] ? s_off0 + 8u * n * 4u : kParked); };
+  auto h_off = [&](int k) { return k == 0 ? h_off0 : (active[1] ? h_off0 + 8u * (unsigned)d.ldh * 2u : kParked); };
   auto pub_off = [&](int k) { return k == 0 ? pub_off0 : (publishes ? pub_off0 + 8u * 16u : kParked); };
   auto frame_of = [&](const void* base, int t, unsigned bytes, bool present = true) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)t * bytes), 0, present && base != nullptr ? bytes : 0u, kBufFlags);
@@ -919,7 +922,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
     asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     __syncthreads();
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((tau & 1) ? d.ring0 : d.ring1), 0, kParked, kBufFlags);
-    const __amdgpu_buffer_rsrc_t ry = frame_of(d.y, t, y_bytes), rc = frame_of(d.cs, t, s_bytes), rh = frame_of(d.hprev, t, s_bytes >> 1);
+    const __amdgpu_buffer_rsrc_t ry = frame_of(d.y, t, y_bytes), rc = frame_of(d.cs, t, s_bytes), rh = frame_of(d.hprev, t, h_bytes);
     const __amdgpu_buffer_rsrc_t rw = frame_of(d.gates, t, g_bytes, a.write_gates != 0);
     // both cells first, then both ring stores (the recurrence's critical stores, close together so that the two halves
     // of a row tile turn their tags at about the same time), then the outputs
@@ -958,7 +961,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
     for (int k = 0; k < 2; ++k) {          // layer outputs and what the backward pass needs (2: non-temporal)
       __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(valid[k] ? h_bits[k] : 0u), ry, y_off(k), 0, 2);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c[k]), rc, s_off(k), 0, 2);
-      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)h_prev_bits[k], rh, s_off(k) >> 1, 0, 2);
+      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)h_prev_bits[k], rh, h_off(k), 0, 2);
       const unsigned gw = valid[k] ? g_off(k) : kParked;
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[k].gi), rw, gw, 0u, 2);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[k].gf), rw, gw, 4u * n, 2);

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(FwdArgs a) {
   Store<T>::store(d.hout, frag_offset<T>(b, j, nkc), h_new);
   Store<T>::store(d.y, (long)b * d.ldy + j, yv);
   if (d.cs) d.cs[(long)b * n + j] = c_new;
-  if (d.hprev) Store<T>::store(d.hprev, (long)b * n + j, h_prev);
+  if (d.hprev) Store<T>::store(d.hprev, (long)b * d.ldh + j, h_prev);
 }
 
 // ------------------------------------------------------------------------------------------------
