@@ -9,7 +9,8 @@
 // a walk over 32 stages of K at the latency of a load (1.6 us): 51 us for 0.9 GFLOP and 32 MB of weights, behind a transpose
 // of those weights (17 us).  Here: tiles of 128 x 128, four wavefronts of 64 x 64 (2 x 2 MFMA blocks of 32 x 32 x 16), two work-groups per
 // compute unit, and K cut into as many ranges as give the device 512 of them; the ranges' parts are added by a second kernel,
-// which also applies bias, row map and rounding.
+// which also applies bias, row map and rounding.  (More stages in flight - three or four of them and one work-group per compute unit - were
+// slower: 37 -> 49 us for 1600 x 4000 x 1000; a second work-group hides more than a deeper pipeline.)
 //
 // Operands go from global memory straight into LDS (16 bytes per lane), K in stages of 64, two stages; the order within a stage
 // and the reasons are those of gemm_nt.hip.  A k-contiguous operand sits there as rows of 128 bytes whose 16-byte slot p holds
@@ -341,12 +342,24 @@ __global__ __launch_bounds__(256) void sum_tile_parts_kernel(TileArgs g) {
   for (int ks = 0; ks < g.ksplit; ++ks) v += __builtin_nontemporal_load((const f4*)(g.parts + ((long)(z * g.ksplit + ks) * g.M + m) * g.ldp + n));
   const float* bias = g.bias ? g.bias + g.sbiasz * z : nullptr;
   const long off = g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
+  float e[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) e[k] = v[k] + (bias && n + k < g.N ? bias[n + k] : 0.f);
+  if (n + 3 < g.N && (off & 3) == 0 && ((uintptr_t)g.C & 15u) == 0) {
+    if constexpr (sizeof(TC) == 4) {
+      float* p = (float*)g.C + off;
+      if (g.accumulate) { const float4 o = *(const float4*)p; e[0] += o.x; e[1] += o.y; e[2] += o.z; e[3] += o.w; }
+      *(float4*)p = make_float4(e[0], e[1], e[2], e[3]);
+    } else {
+      *(uint2*)((uint16_t*)g.C + off) = make_uint2(f2bf_bits(e[0]) | ((unsigned)f2bf_bits(e[1]) << 16), f2bf_bits(e[2]) | ((unsigned)f2bf_bits(e[3]) << 16));
+    }
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     if (n + k >= g.N) break;
-    const float e = v[k] + (bias ? bias[n + k] : 0.f);
-    if constexpr (sizeof(TC) == 4) { float* p = (float*)g.C + off + k; *p = g.accumulate ? *p + e : e; }
-    else ((uint16_t*)g.C)[off + k] = f2bf_bits(e);
+    if constexpr (sizeof(TC) == 4) { float* p = (float*)g.C + off + k; *p = g.accumulate ? *p + e[k] : e[k]; }
+    else ((uint16_t*)g.C)[off + k] = f2bf_bits(e[k]);
   }
 }
 
