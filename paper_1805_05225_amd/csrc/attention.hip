@@ -37,7 +37,7 @@ __device__ __forceinline__ int src_len(const int* lens, int q, int S) {
 // sentence.  The beam x kJB partial sums of the 256 lanes are added through LDS.  NB: hypotheses rounded up to a multiple of 4
 // (registers and loads for 16 where a beam of 12 has 12 cost a quarter of the time).
 // What bounds it is the vector ALU: an element is five full-rate operations and two transcendental ones at a quarter of the rate,
-// 10 us for 64 sentences x 40 positions x 12 hypotheses x 1000 features (measured: 22.6 us with NB = 16, DESIGN table).
+// 10 us for 64 sentences x 40 positions x 12 hypotheses x 1000 features (measured: 22.6 us with NB = 16).
 template <int NB>
 __global__ __launch_bounds__(256) void att_energy_kernel(const uint16_t* __restrict__ ctx, const float* __restrict__ s_tr,
                                                           const float* __restrict__ accum, const float* __restrict__ w_fb,

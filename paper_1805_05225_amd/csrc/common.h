@@ -252,6 +252,55 @@ inline size_t bwdp_ring_bytes(int B, int n) {                                   
 hipError_t launch_h0_term(const float* h0, const void* W_h, bool bf16, float* gates, long gates_stride, const int* lens, int T, int B, int n,
                           int ndir, int rev0, int rev1, hipStream_t s);
 
+// Narrow layers, all of W_h on one compute unit (loop_small.hip): W_h as it lies in memory, states straight from and to the caller's arrays.
+struct SmallFwdDir {
+  const void* W; float* gates; const float* h0; const float* c0; float* hT; float* cT;     // h0, c0 [B][n] or NULL (zeros); hT, cT or NULL
+  void* y; long ldy; float* cs; void* hprev; long ldh;                                    // as in PFwdDir
+  int rev;
+};
+struct SmallFwdArgs {
+  SmallFwdDir d[2];
+  const int* lens;
+  int B, n, T, ndir, write_gates;
+  unsigned* sync;                         // cleared
+};
+struct SmallBwdDir {
+  const void* W; const float* gates; const float* cs; const float* c0; const void* dy; long lddy; void* DZ;
+  const float* dhT; const float* dcT; float* dh0; float* dc0;                             // each [B][n] or NULL
+  float* db; float* dbpart;               // [4n] or NULL; [ceil(B / 4)][4n], a slice per work-group (B <= 4: straight into db)
+  int rev;
+};
+struct SmallBwdArgs {
+  SmallBwdDir d[2];
+  const int* lens;
+  int B, n, T, ndir, accumulate;
+  unsigned* sync;                         // cleared
+  unsigned* counters; int ncounters;      // cleared for the products behind the loop
+};
+bool loop_small_ok(int n);
+hipError_t launch_small_fwd(const SmallFwdArgs& a, bool bf16, hipStream_t s);
+hipError_t launch_small_bwd(const SmallBwdArgs& a, bool bf16, hipStream_t s);
+
+// A few small products in one launch (gemm_tiny.hip), float or bfloat16 operands in either layout each, any alignment.
+struct TinyProduct {
+  const void* A; const void* B; void* C; const float* bias;
+  int M, N, K;
+  long lda, ldb, ldc, sAz, sBz, sCz, sbiasz; int nz;
+  int nseg; long sAseg, sBseg;            // sums over segments of K each
+  int a_kcontig, b_kcontig, out_bf16, accumulate;
+  const int* lens; int Bt, T;             // lens != NULL: k is frame (k / Bt, k % Bt) and A is read as zero unless it is a real one
+  int ksplit, tile0;                      // set by the launcher
+};
+struct TinyGroup { TinyProduct p[3]; int count; };
+// Above these multiply-adds the kernels with tiles in LDS are faster.  Measured: Zx of n_in = n = 64, 2560 frames (84 M) 36 / 34 us, of 128 and 2560
+// (336 M) 57 / 50; the three products of a backward pass, bfloat16, 1.0 G 124 / 135 us with the loop, 2.0 G 194 / 195, 4.0 G 178 / 155.
+constexpr long kTinyZxMacs = 1L << 28, kTinyBwdMacs = 1L << 31;
+long tiny_macs(const TinyProduct& p);
+// counters: zeroed, tiny_counters() of them; parts: scratch of tiny_parts_bytes()
+int tiny_counters(const TinyGroup& g);
+size_t tiny_parts_bytes(const TinyGroup& g);
+hipError_t launch_gemm_tiny(const TinyGroup& g, bool in_bf16, unsigned* counters, float* parts, hipStream_t s);
+
 // Weight / state packing and small helpers (all enqueue-only).
 hipError_t launch_pack_wh_fwd(const void* W_h, uint4* Wf, int n, int nkc, int ndir, bool bf16, hipStream_t s);
 hipError_t launch_pack_wh_bwd(const void* W_h, uint4* Wb, int n, int nkc, int ndir, bool bf16, hipStream_t s);

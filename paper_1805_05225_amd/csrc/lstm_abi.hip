@@ -31,11 +31,45 @@ struct Plan {
       ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_cidx, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
   int ks_dwx, ks_dwh, ks_dx;                // K ranges of the weight-gradient products and of dX (few output tiles: the whole device works on them)
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
+  bool small;                               // narrow layer: loop_small.hip
+  bool zx_tiny, dw_tiny;                    // its products by gemm_tiny.hip
+  size_t ws_tiny_cnt, ws_tiny_parts;
   bool zx_nn;                               // few 256 x 256 tiles: Zx from W_x as it lies in memory (gemm_tile.hip)
   int n_in8;                                // n_in up to whole 16-byte chunks: row length of the padded copy of x there and for dW_x
   bool fast_gemm; int n_in_pad; long TBp;   // bf16 products through the k-contiguous kernel (operands transposed once)
   size_t hfrag_bytes, dzfrag_bytes, DZ_dir_elems, Zx_dir_elems, Wf_bytes;
 };
+
+// The products of a narrow layer (gemm_tiny.hip); sizes come from the plan alone, pointers from the call.
+TinyProduct tiny_zx(const Plan& p, const void* x, const void* W_x, const void* b, float* gates, long gates_stride) {
+  TinyProduct t = {};
+  const long n4 = 4L * p.n;
+  t.A = x; t.B = W_x; t.C = gates; t.bias = (const float*)b;
+  t.M = p.T * p.B; t.N = (int)n4; t.K = p.n_in; t.lda = p.n_in; t.ldb = n4; t.ldc = n4;
+  t.sBz = p.n_in * n4; t.sCz = gates_stride; t.sbiasz = n4; t.nz = p.D; t.nseg = 1; t.a_kcontig = 1;
+  return t;
+}
+TinyGroup tiny_bwd(const Plan& p, const void* x, const void* W_x, const void* hprev, const void* DZ, const int32_t* lens, void* dx, void* dW_x,
+                   void* dW_h, int acc) {
+  TinyGroup g = {};
+  const long n4 = 4L * p.n, hp_stride = (long)(p.res_dir_stride / p.esz);
+  auto wgrad = [&](const void* A, long lda, long sAz, int M, void* C, const int32_t* mask) {
+    TinyProduct t = {};
+    t.A = A; t.B = DZ; t.C = C; t.M = M; t.N = (int)n4; t.K = p.T * p.B; t.lda = lda; t.ldb = n4; t.ldc = n4;
+    t.sAz = sAz; t.sBz = (long)p.DZ_dir_elems; t.sCz = M * n4; t.nz = p.D; t.nseg = 1; t.accumulate = acc;
+    t.lens = mask; t.Bt = p.B; t.T = p.T;
+    return t;
+  };
+  g.p[g.count++] = wgrad(x, p.n_in, 0, p.n_in, dW_x, lens);     // (x may hold anything at padded frames; hprev and DZ are numbers there, DZ zeros)
+  g.p[g.count++] = wgrad(hprev, p.ldh, hp_stride, p.n, dW_h, nullptr);
+  if (dx) {
+    TinyProduct t = {};
+    t.A = DZ; t.B = W_x; t.C = dx; t.M = p.T * p.B; t.N = p.n_in; t.K = (int)n4; t.lda = n4; t.ldb = n4; t.ldc = p.n_in;
+    t.nz = 1; t.nseg = p.D; t.sAseg = (long)p.DZ_dir_elems; t.sBseg = p.n_in * n4; t.a_kcontig = t.b_kcontig = 1; t.out_bf16 = p.bf16;
+    g.p[g.count++] = t;
+  }
+  return g;
+}
 
 int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   if (!d) return LSTM_ERR_NULL;
@@ -151,6 +185,22 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->parts_bytes = std::max({tp, p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
                                p->ks_dx > 1 ? (size_t)p->ks_dx * TB * d->n_in * 4 : 0});
   p->ws_parts = take(p->parts_bytes);
+  // (one step runs as one step of LSTM_FLAG_PER_STEP does, bit for bit)
+  p->small = loop_small_ok(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
+  p->zx_tiny = p->small && tiny_macs(tiny_zx(*p, nullptr, nullptr, nullptr, nullptr, 0)) <= kTinyZxMacs;
+  p->dw_tiny = false;
+  p->ws_tiny_cnt = p->ws_tiny_parts = o;
+  if (p->small && !infer) {
+    char any;
+    const TinyGroup g = tiny_bwd(*p, nullptr, nullptr, nullptr, nullptr, nullptr, &any, nullptr, nullptr, 0);
+    long macs = 0;
+    for (int i = 0; i < g.count; ++i) macs += tiny_macs(g.p[i]);
+    p->dw_tiny = macs <= kTinyBwdMacs;
+    if (p->dw_tiny) {
+      p->ws_tiny_cnt = take((size_t)tiny_counters(g) * 4);
+      p->ws_tiny_parts = take(tiny_parts_bytes(g));
+    }
+  }
   p->workspace_bytes = o + kAlign;
   return LSTM_OK;
 }
@@ -274,42 +324,11 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     }
     return LSTM_OK;
   }
+  // hoisted input projection for all frames and both directions: Zx = X W_x + b
+  float* gates = infer ? (float*)(ws + p.ws_Zx) : (float*)(rs + p.res_gates);
+  const long gates_stride = infer ? (long)p.Zx_dir_elems : (long)(p.res_dir_stride / 4);
   bool frames_mapped = false;            // the frame map was written by the set-up launch
-  {
-    Phase ph(LSTM_PHASE_PREP, 5, s);
-    ZeroRegions z;
-    z.add(ws + p.ws_sync, p.sync_bytes);
-    if (h0) HIPCHK(launch_copy(hstate, h0, state_bytes, s)); else z.add(hstate, state_bytes);
-    if (c0) HIPCHK(launch_copy(cstate, c0, state_bytes, s)); else z.add(cstate, state_bytes);
-    if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd)
-      z.add(ws + p.ws_Wf + p.Wf_bytes, 1024);              // the chunk of zeros behind the packed W_h (single-launch path)
-    // (on the single-launch path the fills, the packed W_h and the initial ring are one launch)
-    if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd) {
-      FrameMapArgs fm = {};
-      if (p.fast_gemm && seq_lens) {   // the input projection below goes over the real frames
-        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
-        frames_mapped = true;
-      }
-      HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
-                                p.nrt, fm, s));
-    } else HIPCHK(launch_fill_zero_many(z, s));
-  }
-  // single-launch path: bf16 storage, at least two steps, register budget of the kernel
-  bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd;
-  auto pack_fwd = [&]() -> int {            // the per-step kernels' order (also what a single-launch path that does not start falls back to)
-    Phase ph(LSTM_PHASE_PREP, 2, s);
-    HIPCHK(launch_pack_wh_fwd(W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_f, p.D, p.bf16, s));
-    HIPCHK(launch_pack_state(hstate, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1), p.B, p.n, p.nkc_f, p.nrt,
-                             p.D, p.bf16, s));
-    return LSTM_OK;
-  };
-  if (T > 0 && !use_ll) {
-    if ((rc = pack_fwd())) return rc;
-  }
-  if (T > 0) {
-    // hoisted input projection for all frames and both directions: Zx = X W_x + b
-    float* gates = infer ? (float*)(ws + p.ws_Zx) : (float*)(rs + p.res_gates);
-    const long gates_stride = infer ? (long)p.Zx_dir_elems : (long)(p.res_dir_stride / 4);
+  auto project = [&]() -> int {
     GemmArgs g = {};
     g.A = x; g.B = W_x; g.C = gates; g.bias = (const float*)b;
     g.M = (int)(T * B); g.N = 4 * p.n; g.K = p.n_in;
@@ -352,6 +371,65 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       }
       HIPCHK(launch_gemm(g, s));
     }
+    return LSTM_OK;
+  };
+  if (p.small) {                         // a narrow layer: projection and loop, nothing to set up
+    if (p.zx_tiny) {
+      Phase ph(LSTM_PHASE_GEMM_ZX, 1, s);
+      TinyGroup g = {};
+      g.p[g.count++] = tiny_zx(p, x, W_x, b, gates, gates_stride);
+      HIPCHK(launch_gemm_tiny(g, p.bf16, nullptr, nullptr, s));
+    } else if ((rc = project())) return rc;
+    SmallFwdArgs a = {};
+    a.lens = seq_lens; a.B = p.B; a.n = p.n; a.T = p.T; a.ndir = p.D; a.write_gates = infer ? 0 : 1; a.sync = (unsigned*)(ws + p.ws_sync);
+    for (size_t d = 0; d < D; ++d) {
+      SmallFwdDir& fd = a.d[d];
+      fd.W = (const char*)W_h + d * n * 4 * n * p.esz;
+      fd.gates = gates + d * gates_stride;
+      fd.h0 = h0 ? (const float*)h0 + d * B * n : nullptr; fd.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;
+      fd.hT = hT ? (float*)hT + d * B * n : nullptr; fd.cT = cT ? (float*)cT + d * B * n : nullptr;
+      fd.y = (char*)y + d * n * p.esz; fd.ldy = (long)(D * n);
+      fd.cs = c ? (float*)c + d * T * B * n : nullptr;
+      fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev; fd.ldh = p.ldh;
+      fd.rev = bidir ? d == 1 : desc->direction == -1;
+    }
+    Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
+    HIPCHK(launch_small_fwd(a, p.bf16, s));
+    return LSTM_OK;
+  }
+  {
+    Phase ph(LSTM_PHASE_PREP, 5, s);
+    ZeroRegions z;
+    z.add(ws + p.ws_sync, p.sync_bytes);
+    if (h0) HIPCHK(launch_copy(hstate, h0, state_bytes, s)); else z.add(hstate, state_bytes);
+    if (c0) HIPCHK(launch_copy(cstate, c0, state_bytes, s)); else z.add(cstate, state_bytes);
+    if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd)
+      z.add(ws + p.ws_Wf + p.Wf_bytes, 1024);              // the chunk of zeros behind the packed W_h (single-launch path)
+    // (on the single-launch path the fills, the packed W_h and the initial ring are one launch)
+    if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd) {
+      FrameMapArgs fm = {};
+      if (p.fast_gemm && seq_lens) {   // the input projection below goes over the real frames
+        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
+        frames_mapped = true;
+      }
+      HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
+                                p.nrt, fm, s));
+    } else HIPCHK(launch_fill_zero_many(z, s));
+  }
+  // single-launch path: bf16 storage, at least two steps, register budget of the kernel
+  bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd;
+  auto pack_fwd = [&]() -> int {            // the per-step kernels' order (also what a single-launch path that does not start falls back to)
+    Phase ph(LSTM_PHASE_PREP, 2, s);
+    HIPCHK(launch_pack_wh_fwd(W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_f, p.D, p.bf16, s));
+    HIPCHK(launch_pack_state(hstate, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1), p.B, p.n, p.nkc_f, p.nrt,
+                             p.D, p.bf16, s));
+    return LSTM_OK;
+  };
+  if (T > 0 && !use_ll) {
+    if ((rc = pack_fwd())) return rc;
+  }
+  if (T > 0) {
+    if ((rc = project())) return rc;
 
     bool done = false;
     if (use_ll) {
@@ -514,213 +592,262 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   // that numbering and the transposed operands of the weight gradients are packed by it.
   const int TB = (int)(T * B);
   const bool compact = (p.fast_gemm || !p.bf16) && seq_lens && TB > 0;
-  // single-launch path: bf16 storage, at least two steps, and the kernel fits the device
-  PBwdArgs pa = {};
-  pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.T = p.T; pa.ndir = p.D;
-  pa.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
-  pa.sync = (unsigned*)(ws + p.ws_sync); pa.spin_limit = kSpinLimit;
-  pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
-  for (size_t d = 0; d < D; ++d) pa.d[d].lddy = (long)(D * n);       // (the check looks at the frame sizes)
-  const bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_bwd_fits(pa);
-  const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n % 8 == 0 && p.n <= 1024 && p.B <= 256 &&
-                        persist_bwd_f32_fits(pa);
-  bool dx_cleared = false;
-  {
-    Phase ph(LSTM_PHASE_PREP, 5, s);
-    ZeroRegions z;
-    z.add(ws + p.ws_sync, p.sync_bytes);
-    if (dhT) HIPCHK(launch_copy(Dh, dhT, state_bytes, s)); else z.add(Dh, state_bytes);
-    if (dcT) HIPCHK(launch_copy(Dc, dcT, state_bytes, s)); else z.add(Dc, state_bytes);
-    z.add(ws + p.ws_dzfrag0, p.dzfrag_bytes);
-    z.add(ws + p.ws_dzfrag1, p.dzfrag_bytes);
-    if (2 * p.nrt <= kColsumSlices) z.add(ws + p.ws_colsum, D * kColsumSlices * 4 * n * 4);   // bias-gradient slices of row groups the grid lacks
-    // (the bfloat16 single-launch path clears and packs W_h^T in one launch)
-    if (use_ll) {
-      FrameMapArgs fm = {};
-      if (compact) fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
-      if (compact && dx && ((size_t)TB * n_in * p.esz) % 4 == 0) {   // dX is scattered to the real frames' rows: the padded frames' rows are cleared here
-        z.add(dx, (size_t)TB * n_in * p.esz);
-        dx_cleared = true;
-      }
-      HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, fm, s));
-    } else HIPCHK(launch_fill_zero_many(z, s));
-  }
-  if (!use_ll) {
-    Phase ph(LSTM_PHASE_PREP, 1, s);
-    if (use_ll32) HIPCHK(launch_pack_wh_bwd_f32p(W_h, ws + p.ws_Wb, p.n, p.D, s));
-    else HIPCHK(launch_pack_wh_bwd(W_h, (uint4*)(ws + p.ws_Wb), p.n, p.nkc_b, p.D, p.bf16, s));
-  }
-
-  const size_t frag_dir = (size_t)p.nrt * p.nkc_b * 1024;
   char* DZ = ws + p.ws_DZ;
-  bool done = false;
-  const bool db_in_loop = (use_ll || use_ll32) && 2 * p.nrt <= kColsumSlices;   // the single-launch kernels also sum the bias gradient
-  if (use_ll || use_ll32) {
-    const size_t ring_dir = use_ll ? bwdp_ring_bytes(p.B, p.n) : bwd_f32_ring_bytes(p.B, p.n);
-    const size_t wb_dir = use_ll ? bwdp_wh_bytes(p.n) : bwd_f32_wh_bytes(p.n);
+  bool dx_cleared = false, frames_mapped = false;      // done by a set-up launch of the loop
+  int db_slices = 0;                                   // slices of the bias gradient that the loop leaves in ws_colsum (0: none)
+  TinyGroup tiny = {};
+  if (p.dw_tiny) tiny = tiny_bwd(p, x, W_x, rs + p.res_hprev, DZ, seq_lens, dx, dW_x, dW_h, acc);
+  bool db_done = false;
+
+  auto narrow_loop = [&]() -> int {
+    SmallBwdArgs a = {};
+    const int slices = cdiv((long)B, 4);
+    a.lens = seq_lens; a.B = p.B; a.n = p.n; a.T = p.T; a.ndir = p.D; a.accumulate = acc; a.sync = (unsigned*)(ws + p.ws_sync);
+    if (p.dw_tiny) { a.counters = (unsigned*)(ws + p.ws_tiny_cnt); a.ncounters = tiny_counters(tiny); }
     for (size_t d = 0; d < D; ++d) {
-      PBwdDir& bd = pa.d[d];
-      bd.Wb = (const uint4*)(ws + p.ws_Wb + d * wb_dir);
-      bd.ring0 = (uint4*)(ws + p.ws_dzfrag0 + d * ring_dir);
-      bd.ring1 = (uint4*)(ws + p.ws_dzfrag1 + d * ring_dir);
+      SmallBwdDir& bd = a.d[d];
+      bd.W = (const char*)W_h + d * n * 4 * n * p.esz;
       bd.gates = (const float*)(rs + d * p.res_dir_stride + p.res_gates);
       bd.cs = (const float*)c + d * T * B * n;
       bd.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;
-      bd.dy = (const char*)dy + d * n * p.esz;
-      bd.lddy = (long)(D * n);
+      bd.dy = (const char*)dy + d * n * p.esz; bd.lddy = (long)(D * n);
       bd.DZ = DZ + d * p.DZ_dir_elems * p.esz;
-      bd.Dh = Dh + d * B * n;
-      bd.Dc = Dc + d * B * n;
-      bd.dbpart = db_in_loop ? (float*)(ws + p.ws_colsum) + d * kColsumSlices * 4 * n : nullptr;
+      bd.dhT = dhT ? (const float*)dhT + d * B * n : nullptr; bd.dcT = dcT ? (const float*)dcT + d * B * n : nullptr;
+      bd.dh0 = dh0 ? (float*)dh0 + d * B * n : nullptr; bd.dc0 = dc0 ? (float*)dc0 + d * B * n : nullptr;
+      bd.db = slices <= kColsumSlices ? (float*)db + d * 4 * n : nullptr;
+      bd.dbpart = (float*)(ws + p.ws_colsum) + d * kColsumSlices * 4 * n;
       bd.rev = bidir ? d == 1 : desc->direction == -1;
     }
-    hipError_t e;
+    db_done = slices == 1;
+    db_slices = slices <= kColsumSlices ? slices : 0;
+    Phase ph(LSTM_PHASE_LOOP_BWD, 1, s);
+    HIPCHK(launch_small_bwd(a, p.bf16, s));
+    return LSTM_OK;
+  };
+
+  auto wide_loop = [&]() -> int {
+    // single-launch path: bf16 storage, at least two steps, and the kernel fits the device
+    PBwdArgs pa = {};
+    pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.T = p.T; pa.ndir = p.D;
+    pa.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
+    pa.sync = (unsigned*)(ws + p.ws_sync); pa.spin_limit = kSpinLimit;
+    pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
+    for (size_t d = 0; d < D; ++d) pa.d[d].lddy = (long)(D * n);       // (the check looks at the frame sizes)
+    const bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_bwd_fits(pa);
+    const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n % 8 == 0 && p.n <= 1024 && p.B <= 256 &&
+                          persist_bwd_f32_fits(pa);
     {
-      Phase ph(LSTM_PHASE_LOOP_BWD, 1, s);
-      e = use_ll ? launch_persist_bwd(pa, s) : launch_persist_bwd_f32(pa, s);
+      Phase ph(LSTM_PHASE_PREP, 5, s);
+      ZeroRegions z;
+      z.add(ws + p.ws_sync, p.sync_bytes);
+      if (dhT) HIPCHK(launch_copy(Dh, dhT, state_bytes, s)); else z.add(Dh, state_bytes);
+      if (dcT) HIPCHK(launch_copy(Dc, dcT, state_bytes, s)); else z.add(Dc, state_bytes);
+      z.add(ws + p.ws_dzfrag0, p.dzfrag_bytes);
+      z.add(ws + p.ws_dzfrag1, p.dzfrag_bytes);
+      if (2 * p.nrt <= kColsumSlices) z.add(ws + p.ws_colsum, D * kColsumSlices * 4 * n * 4);   // bias-gradient slices of row groups the grid lacks
+      // (the bfloat16 single-launch path clears and packs W_h^T in one launch)
+      if (use_ll) {
+        FrameMapArgs fm = {};
+        if (compact) {
+          fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
+          frames_mapped = true;
+        }
+        if (compact && dx && ((size_t)TB * n_in * p.esz) % 4 == 0) {   // dX is scattered to the real frames' rows: the padded frames' rows are cleared here
+          z.add(dx, (size_t)TB * n_in * p.esz);
+          dx_cleared = true;
+        }
+        HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, fm, s));
+      } else HIPCHK(launch_fill_zero_many(z, s));
     }
-    if (e == hipSuccess) done = true;
-    else if (e != hipErrorCooperativeLaunchTooLarge) {   // a later batch slab failed after earlier ones ran
-      (void)hipGetLastError();
-      return LSTM_ERR_HIP;
-    } else {
-      (void)hipGetLastError();
+    if (!use_ll) {
       Phase ph(LSTM_PHASE_PREP, 1, s);
-      HIPCHK(launch_pack_wh_bwd(W_h, (uint4*)(ws + p.ws_Wb), p.n, p.nkc_b, p.D, p.bf16, s));
+      if (use_ll32) HIPCHK(launch_pack_wh_bwd_f32p(W_h, ws + p.ws_Wb, p.n, p.D, s));
+      else HIPCHK(launch_pack_wh_bwd(W_h, (uint4*)(ws + p.ws_Wb), p.n, p.nkc_b, p.D, p.bf16, s));
     }
-  }
-  BwdArgs a = {};
-  a.lens = seq_lens; a.B = p.B; a.n = p.n; a.nkc = p.nkc_b; a.T = p.T; a.ndir = p.D;
-  if (!done) {
-  Phase ph(LSTM_PHASE_LOOP_BWD, (long)T + 1, s);
-  for (long tau = (long)T - 1; tau >= -1; --tau) {
-    a.do_matmul = tau < (long)T - 1;
-    a.do_pointwise = tau >= 0;
-    for (size_t d = 0; d < D; ++d) {
-      const bool rev = bidir ? d == 1 : desc->direction == -1;
-      const long t = rev ? (long)T - 1 - tau : tau;            // frame of this step (out of range when tau == -1)
-      const long t_next = rev ? t - 1 : t + 1;                 // frame of the previous backward step
-      BwdDir& bd = a.d[d];
-      bd.Wb = (const uint4*)(ws + p.ws_Wb + d * (size_t)p.ntile_b * p.nkc_b * 1024);
-      bd.dzin = (const uint4*)(ws + (((tau + 1) & 1) ? p.ws_dzfrag1 : p.ws_dzfrag0) + d * frag_dir);
-      bd.dzout = ws + ((tau & 1) ? p.ws_dzfrag1 : p.ws_dzfrag0) + d * frag_dir;
-      bd.Dh = Dh + d * B * n;
-      bd.Dc = Dc + d * B * n;
-      bd.t = (int)t; bd.t_next = (int)t_next;
-      if (tau >= 0) {
-        const float* cs = (const float*)c + d * T * B * n;
-        const long tp = rev ? t + 1 : t - 1;                   // frame processed just before t in the forward pass
-        bd.gates = (const float*)(rs + d * p.res_dir_stride + p.res_gates) + t * B * 4 * n;
-        bd.cs = cs + t * B * n;
-        bd.cprev = (tp >= 0 && tp < (long)T) ? cs + tp * B * n : (c0 ? (const float*)c0 + d * B * n : nullptr);
-        bd.dy = (const char*)dy + (t * B * D * n + d * n) * p.esz;
+
+    const size_t frag_dir = (size_t)p.nrt * p.nkc_b * 1024;
+    bool done = false;
+    const bool db_in_loop = (use_ll || use_ll32) && 2 * p.nrt <= kColsumSlices;   // the single-launch kernels also sum the bias gradient
+    if (use_ll || use_ll32) {
+      const size_t ring_dir = use_ll ? bwdp_ring_bytes(p.B, p.n) : bwd_f32_ring_bytes(p.B, p.n);
+      const size_t wb_dir = use_ll ? bwdp_wh_bytes(p.n) : bwd_f32_wh_bytes(p.n);
+      for (size_t d = 0; d < D; ++d) {
+        PBwdDir& bd = pa.d[d];
+        bd.Wb = (const uint4*)(ws + p.ws_Wb + d * wb_dir);
+        bd.ring0 = (uint4*)(ws + p.ws_dzfrag0 + d * ring_dir);
+        bd.ring1 = (uint4*)(ws + p.ws_dzfrag1 + d * ring_dir);
+        bd.gates = (const float*)(rs + d * p.res_dir_stride + p.res_gates);
+        bd.cs = (const float*)c + d * T * B * n;
+        bd.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;
+        bd.dy = (const char*)dy + d * n * p.esz;
         bd.lddy = (long)(D * n);
-        bd.DZ = DZ + (d * p.DZ_dir_elems + t * B * 4 * n) * p.esz;
+        bd.DZ = DZ + d * p.DZ_dir_elems * p.esz;
+        bd.Dh = Dh + d * B * n;
+        bd.Dc = Dc + d * B * n;
+        bd.dbpart = db_in_loop ? (float*)(ws + p.ws_colsum) + d * kColsumSlices * 4 * n : nullptr;
+        bd.rev = bidir ? d == 1 : desc->direction == -1;
+      }
+      hipError_t e;
+      {
+        Phase ph(LSTM_PHASE_LOOP_BWD, 1, s);
+        e = use_ll ? launch_persist_bwd(pa, s) : launch_persist_bwd_f32(pa, s);
+      }
+      if (e == hipSuccess) {
+        done = true;
+        if (db_in_loop) db_slices = 2 * p.nrt;
+      }
+      else if (e != hipErrorCooperativeLaunchTooLarge) {   // a later batch slab failed after earlier ones ran
+        (void)hipGetLastError();
+        return LSTM_ERR_HIP;
+      } else {
+        (void)hipGetLastError();
+        Phase ph(LSTM_PHASE_PREP, 1, s);
+        HIPCHK(launch_pack_wh_bwd(W_h, (uint4*)(ws + p.ws_Wb), p.n, p.nkc_b, p.D, p.bf16, s));
       }
     }
-    HIPCHK(launch_step_bwd(a, p.bf16, s));
-  }
-  }
-  {
-    Phase ph(LSTM_PHASE_PREP, 2, s);
-    if (dh0) HIPCHK(launch_copy(dh0, Dh, state_bytes, s));
-    if (dc0) HIPCHK(launch_copy(dc0, Dc, state_bytes, s));
-  }
+    BwdArgs a = {};
+    a.lens = seq_lens; a.B = p.B; a.n = p.n; a.nkc = p.nkc_b; a.T = p.T; a.ndir = p.D;
+    if (!done) {
+    Phase ph(LSTM_PHASE_LOOP_BWD, (long)T + 1, s);
+    for (long tau = (long)T - 1; tau >= -1; --tau) {
+      a.do_matmul = tau < (long)T - 1;
+      a.do_pointwise = tau >= 0;
+      for (size_t d = 0; d < D; ++d) {
+        const bool rev = bidir ? d == 1 : desc->direction == -1;
+        const long t = rev ? (long)T - 1 - tau : tau;            // frame of this step (out of range when tau == -1)
+        const long t_next = rev ? t - 1 : t + 1;                 // frame of the previous backward step
+        BwdDir& bd = a.d[d];
+        bd.Wb = (const uint4*)(ws + p.ws_Wb + d * (size_t)p.ntile_b * p.nkc_b * 1024);
+        bd.dzin = (const uint4*)(ws + (((tau + 1) & 1) ? p.ws_dzfrag1 : p.ws_dzfrag0) + d * frag_dir);
+        bd.dzout = ws + ((tau & 1) ? p.ws_dzfrag1 : p.ws_dzfrag0) + d * frag_dir;
+        bd.Dh = Dh + d * B * n;
+        bd.Dc = Dc + d * B * n;
+        bd.t = (int)t; bd.t_next = (int)t_next;
+        if (tau >= 0) {
+          const float* cs = (const float*)c + d * T * B * n;
+          const long tp = rev ? t + 1 : t - 1;                   // frame processed just before t in the forward pass
+          bd.gates = (const float*)(rs + d * p.res_dir_stride + p.res_gates) + t * B * 4 * n;
+          bd.cs = cs + t * B * n;
+          bd.cprev = (tp >= 0 && tp < (long)T) ? cs + tp * B * n : (c0 ? (const float*)c0 + d * B * n : nullptr);
+          bd.dy = (const char*)dy + (t * B * D * n + d * n) * p.esz;
+          bd.lddy = (long)(D * n);
+          bd.DZ = DZ + (d * p.DZ_dir_elems + t * B * 4 * n) * p.esz;
+        }
+      }
+      HIPCHK(launch_step_bwd(a, p.bf16, s));
+    }
+    }
+    {
+      Phase ph(LSTM_PHASE_PREP, 2, s);
+      if (dh0) HIPCHK(launch_copy(dh0, Dh, state_bytes, s));
+      if (dc0) HIPCHK(launch_copy(dc0, Dc, state_bytes, s));
+    }
+    return LSTM_OK;
+  };
+  if ((rc = p.small ? narrow_loop() : wide_loop())) return rc;
 
   int* cidx = (int*)(ws + p.ws_cidx);
   int* fidx = (int*)(ws + p.ws_fidx);
   int* count = (int*)(ws + p.ws_count);
-  if (compact && !use_ll) {          // (the bfloat16 single-launch path numbered the frames in its set-up launch)
+  if (compact && !frames_mapped && !p.dw_tiny) {
     Phase ph(LSTM_PHASE_PREP, 1, s);
     HIPCHK(launch_frame_map(seq_lens, p.T, p.B, cidx, fidx, count, s));
   }
-  if (dx) {                        // dX = sum over directions of DZ W_x^T
-    GemmArgs g = {};
-    g.A = DZ; g.B = W_x; g.C = dx;
-    g.M = TB; g.N = p.n_in; g.K = 4 * p.n;
-    g.lda = 4 * n; g.ldb = 4 * n; g.ldc = n_in; g.nz = 1;
-    g.nseg = p.D; g.sAseg = (long)p.DZ_dir_elems; g.sBseg = (long)(n_in * 4 * n);
-    g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = p.bf16; g.out_bf16 = p.bf16;
-    g.vecA = widest(g.lda, g.sAseg, 0, p.esz, 16);
-    g.vecB = widest(g.ldb, g.sBseg, 0, p.esz, 16);
-    Phase ph(LSTM_PHASE_GEMM_DX, 1, s);
-    if (compact && (gemm_nt_ok(g) || !p.bf16)) {      // rows of padded frames: zero, and left out of the product
-      if (!dx_cleared) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
-      g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = TB; g.m_dev = count;
-    }
-    g.parts_bytes = 0;
-    if (p.bf16 && gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
-    else if (p.ks_dx > 1 && gemm_nt_ok(g)) { g.ksplit = p.ks_dx; g.parts = (float*)(ws + p.ws_parts); }
-    if (!p.bf16 && p.ks_dx == 8) {
-      g.ksplit = 8; g.parts = (float*)(ws + p.ws_parts);
-      if (!gemm_float_ok(g)) { g.ksplit = 0; g.parts = nullptr; }
-    }
-    if (!p.bf16 && !g.parts) {
-      // float storage, shapes the eight-range form above does not take: rows = frames and n_in columns give few 128 x 128 tiles (config 2: 85 with real
-      // frames), so K = 4n per direction is cut into ranges that add their parts to the zero-filled dx atomically
-      const long tiles = (long)cdiv(TB, 128) * cdiv(p.n_in, 128), stages = (long)p.D * cdiv(4L * p.n, 32);
-      const int ks = (int)std::max(1L, std::min(std::min(384 / std::max(tiles, 1L), stages / 16), 8L));
-      if (ks > 1) {
-        if (!compact) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
-        g.ksplit = ks;
+  auto products = [&]() -> int {
+    if (dx) {                        // dX = sum over directions of DZ W_x^T
+      GemmArgs g = {};
+      g.A = DZ; g.B = W_x; g.C = dx;
+      g.M = TB; g.N = p.n_in; g.K = 4 * p.n;
+      g.lda = 4 * n; g.ldb = 4 * n; g.ldc = n_in; g.nz = 1;
+      g.nseg = p.D; g.sAseg = (long)p.DZ_dir_elems; g.sBseg = (long)(n_in * 4 * n);
+      g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = p.bf16; g.out_bf16 = p.bf16;
+      g.vecA = widest(g.lda, g.sAseg, 0, p.esz, 16);
+      g.vecB = widest(g.ldb, g.sBseg, 0, p.esz, 16);
+      Phase ph(LSTM_PHASE_GEMM_DX, 1, s);
+      if (compact && (gemm_nt_ok(g) || !p.bf16)) {      // rows of padded frames: zero, and left out of the product
+        if (!dx_cleared) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
+        g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = TB; g.m_dev = count;
       }
-    }
-    HIPCHK(launch_gemm(g, s));
-  }
-  // Weight gradients straight from the frame-major tensors (a row per frame in X, Hprev and DZ: both operands of
-  // X^T DZ are k-major), over the packed list of real frames when lengths are given.
-  auto frame_major = [&](const void* A, long lda, long sAz, int M, void* C, int ks) {
-    GemmArgs g = {};
-    g.A = A; g.B = DZ; g.C = C;
-    g.M = M; g.N = 4 * p.n; g.K = (int)TB; g.lda = lda; g.ldb = 4 * n; g.ldc = 4 * n;
-    g.sAz = sAz; g.sBz = (long)p.DZ_dir_elems; g.sCz = (long)M * 4 * n; g.nz = p.D; g.nseg = 1;
-    g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
-    g.vecA = 16; g.vecB = 16;
-    if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
-    if (gemm_tile_small(M, 4L * p.n, p.D)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
-    else if (ks > 1) { g.ksplit = ks; g.parts = (float*)(ws + p.ws_parts); }
-    return g;
-  };
-  const bool pad_x = p.n_in8 != p.n_in;                          // rows of x are not 16-byte aligned: padded copy
-  const GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x, p.ks_dwx);
-  const GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h, p.ks_dwh);
-  const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
-  if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
-    {
-      Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
-      if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
-      HIPCHK(launch_gemm(gx, s));
-    }
-    {
-      Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
-      HIPCHK(launch_gemm(gh, s));
-    }
-  } else {                         // dW_x = X^T DZ, padded frames of X masked out
-    GemmArgs g = {};
-    g.A = x; g.B = DZ; g.C = dW_x;
-    g.M = p.n_in; g.N = 4 * p.n; g.K = TB;
-    g.lda = n_in; g.ldb = 4 * n; g.ldc = 4 * n;
-    g.sAz = 0; g.sBz = (long)p.DZ_dir_elems; g.sCz = (long)(n_in * 4 * n); g.nz = p.D; g.nseg = 1;
-    g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = p.bf16; g.out_bf16 = false; g.accumulate = acc;
-    if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }   // the real frames only
-    else { g.lens = seq_lens; g.Bt = p.B; g.T = p.T; }                              // (or every frame, padded ones read as zero)
-    g.vecA = widest(g.lda, 0, 0, p.esz, 4);
-    g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
-    {
-      Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+      g.parts_bytes = 0;
+      if (p.bf16 && gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+      else if (p.ks_dx > 1 && gemm_nt_ok(g)) { g.ksplit = p.ks_dx; g.parts = (float*)(ws + p.ws_parts); }
+      if (!p.bf16 && p.ks_dx == 8) {
+        g.ksplit = 8; g.parts = (float*)(ws + p.ws_parts);
+        if (!gemm_float_ok(g)) { g.ksplit = 0; g.parts = nullptr; }
+      }
+      if (!p.bf16 && !g.parts) {
+        // float storage, shapes the eight-range form above does not take: rows = frames and n_in columns give few 128 x 128 tiles (config 2: 85 with real
+        // frames), so K = 4n per direction is cut into ranges that add their parts to the zero-filled dx atomically
+        const long tiles = (long)cdiv(TB, 128) * cdiv(p.n_in, 128), stages = (long)p.D * cdiv(4L * p.n, 32);
+        const int ks = (int)std::max(1L, std::min(std::min(384 / std::max(tiles, 1L), stages / 16), 8L));
+        if (ks > 1) {
+          if (!compact) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
+          g.ksplit = ks;
+        }
+      }
       HIPCHK(launch_gemm(g, s));
     }
-    // dW_h = Hprev^T DZ
-    g.A = rs + p.res_hprev; g.C = dW_h; g.M = p.n; g.lda = p.ldh;
-    g.sAz = (long)(p.res_dir_stride / p.esz); g.sCz = (long)(n * 4 * n);
-    g.lens = nullptr;
-    g.vecA = widest(g.lda, g.sAz, 0, p.esz, 4);
-    Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
-    HIPCHK(launch_gemm(g, s));
-  }
+    // Weight gradients straight from the frame-major tensors (a row per frame in X, Hprev and DZ: both operands of
+    // X^T DZ are k-major), over the packed list of real frames when lengths are given.
+    auto frame_major = [&](const void* A, long lda, long sAz, int M, void* C, int ks) {
+      GemmArgs g = {};
+      g.A = A; g.B = DZ; g.C = C;
+      g.M = M; g.N = 4 * p.n; g.K = (int)TB; g.lda = lda; g.ldb = 4 * n; g.ldc = 4 * n;
+      g.sAz = sAz; g.sBz = (long)p.DZ_dir_elems; g.sCz = (long)M * 4 * n; g.nz = p.D; g.nseg = 1;
+      g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
+      g.vecA = 16; g.vecB = 16;
+      if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
+      if (gemm_tile_small(M, 4L * p.n, p.D)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+      else if (ks > 1) { g.ksplit = ks; g.parts = (float*)(ws + p.ws_parts); }
+      return g;
+    };
+    const bool pad_x = p.n_in8 != p.n_in;                          // rows of x are not 16-byte aligned: padded copy
+    const GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x, p.ks_dwx);
+    const GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h, p.ks_dwh);
+    const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
+    if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
+      {
+        Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+        if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
+        HIPCHK(launch_gemm(gx, s));
+      }
+      {
+        Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
+        HIPCHK(launch_gemm(gh, s));
+      }
+    } else {                         // dW_x = X^T DZ, padded frames of X masked out
+      GemmArgs g = {};
+      g.A = x; g.B = DZ; g.C = dW_x;
+      g.M = p.n_in; g.N = 4 * p.n; g.K = TB;
+      g.lda = n_in; g.ldb = 4 * n; g.ldc = 4 * n;
+      g.sAz = 0; g.sBz = (long)p.DZ_dir_elems; g.sCz = (long)(n_in * 4 * n); g.nz = p.D; g.nseg = 1;
+      g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = p.bf16; g.out_bf16 = false; g.accumulate = acc;
+      if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }   // the real frames only
+      else { g.lens = seq_lens; g.Bt = p.B; g.T = p.T; }                              // (or every frame, padded ones read as zero)
+      g.vecA = widest(g.lda, 0, 0, p.esz, 4);
+      g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
+      {
+        Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+        HIPCHK(launch_gemm(g, s));
+      }
+      // dW_h = Hprev^T DZ
+      g.A = rs + p.res_hprev; g.C = dW_h; g.M = p.n; g.lda = p.ldh;
+      g.sAz = (long)(p.res_dir_stride / p.esz); g.sCz = (long)(n * 4 * n);
+      g.lens = nullptr;
+      g.vecA = widest(g.lda, g.sAz, 0, p.esz, 4);
+      Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
+      HIPCHK(launch_gemm(g, s));
+    }
+    return LSTM_OK;
+  };
+  if (p.dw_tiny) {
+    Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+    HIPCHK(launch_gemm_tiny(tiny, p.bf16, (unsigned*)(ws + p.ws_tiny_cnt), (float*)(ws + p.ws_tiny_parts), s));
+  } else if ((rc = products())) return rc;
+  if (db_done) return LSTM_OK;
   Phase ph(LSTM_PHASE_DB, 2, s);
-  if (done && db_in_loop) {
-    HIPCHK(launch_colsum_final((const float*)(ws + p.ws_colsum), (float*)db, 4 * p.n, p.D, 2 * p.nrt, acc, s));
+  if (db_slices) {
+    HIPCHK(launch_colsum_final((const float*)(ws + p.ws_colsum), (float*)db, 4 * p.n, p.D, db_slices, acc, s));
     return LSTM_OK;
   }
   HIPCHK(launch_colsum(DZ, (float*)db, (float*)(ws + p.ws_colsum), TB, 4 * p.n, p.D, (long)p.DZ_dir_elems, p.bf16, acc, s));

@@ -1,0 +1,51 @@
+"""Layers at the sizes where the recurrent loop or its products change form: one compute unit per four rows up to 128 units, the
+widths where the bfloat16 loops change their split, products with tile edges and K ranges.  Every optional input, NaN in padded
+frames and in untouched workspace, against the oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from tests import test_gpu_parity as P
+from tests.gpu_util import TOL
+
+
+def _lens(rng, T, B):
+    lens = rng.integers(0, T + 1, B)
+    lens[0], lens[-1] = T, min(1, T)
+    return lens
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("T,B,n_in,n,bidir", [
+    (2, 1, 1, 5, False), (2, 4, 33, 64, True), (9, 5, 40, 65, False), (6, 3, 7, 63, True), (5, 8, 130, 128, True), (7, 2, 31, 127, False),
+    (3, 260, 12, 20, True),                                                 # bias gradient: more slices than the workspace keeps
+    (65, 64, 128, 128, False),                                              # products too large for the tiny ones
+    (40, 2, 64, 64, False), (21, 17, 100, 96, True),
+])
+def test_narrow_layer(T, B, n_in, n, bidir, dt):
+    _layer(T, B, n_in, n, bidir, dt)
+
+
+@pytest.mark.parametrize("T,B,n_in,n,bidir", [
+    (4, 1, 200, 256, True), (4, 9, 64, 257, True), (5, 17, 250, 512, True), (4, 3, 500, 513, True), (3, 33, 130, 136, False),
+    (60, 7, 333, 264, True),
+])
+def test_wider_layer(T, B, n_in, n, bidir):
+    _layer(T, B, n_in, n, bidir, "bf16")
+
+
+def _layer(T, B, n_in, n, bidir, dt):
+    from paper_1805_05225_amd import binding
+    P.Bn = binding
+    rng = np.random.default_rng(T * 1000 + B + n)
+    for lens in (None, _lens(rng, T, B)):
+        c = P.rnd_case(rng, T, B, n_in, n, 2 if bidir else 1, lens, dt, scale=2.0 / np.sqrt(n + n_in))
+        x, dy = c["x"].copy(), c["dy"].copy()
+        if lens is not None:
+            for b in range(B):
+                x[lens[b]:, b], dy[lens[b]:, b] = np.nan, np.nan
+        print("  layer", dt, T, B, n_in, n, bidir, lens is not None, flush=True)
+        for direction in ((1,) if bidir else (1, -1)):
+            f, g = P.run_gpu(c, dt, bidir, direction, x_override=x, dy_override=dy, poison=True)
+            P.compare(f, g, *P.run_oracle(c, bidir, direction), TOL[dt])
