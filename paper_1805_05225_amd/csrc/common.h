@@ -61,11 +61,10 @@ struct GemmArgs {
   const int* m_dev; const int* k_dev;     // M / K read from device memory (capped by M / K above, which size the grid)
   const int* k_rows; int k_phys_rows;     // both operands k-major: k -> row of A and of B in memory; rows each holds in memory
                                           // (A k-contiguous, B k-major: k_phys_rows > 0 = rows of B, where A's rows are padded up to K)
-  int ksplit;                             // > 1: K cut into that many ranges whose parts are ADDED to C atomically
-                                          // (float C, nseg == 1; C must hold zeros or the value to add to) ...
-  float* parts;                           // ... or, if not NULL (nz * ksplit * M * ldc floats, no c_rows): every range stores
-                                          // its part there and a second kernel writes C (+)= their sum (`accumulate` honoured)
-  size_t parts_bytes;                     // what `parts` holds (gemm_tile.hip, which plans its own ranges)
+  int ksplit;                             // > 1 (gemm_nt.hip's kernels): K cut into that many ranges ...
+  float* parts;                           // ... every range stores its part there (nz * ksplit * M * ldc floats, no c_rows) and a
+                                          // second kernel writes C (+)= their sum (`accumulate` honoured)
+  size_t parts_bytes;                     // what `parts` holds (gemm_tile.hip and gemm_float.hip, which plan their own ranges)
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for problems with both operands k-contiguous, 16-byte aligned rows and K % 8 == 0
@@ -83,9 +82,11 @@ bool gemm_tile_small(long M, long N, int nz);
 int gemm_tile_ranges(long M, long N, long K, int nz, int nseg);
 size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg);
 hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s);
-// Float storage (gemm_float.hip): operands as they lie in memory, rows 16-byte aligned, extents along 16-byte chunks
-// multiples of 4 (K for a k-contiguous operand, M / N for a k-major one); row maps, device-resident M / K, segments
-// and atomic K ranges as above (launch_gemm routes to it by itself; what it does not take goes to the generic kernel).
+// Float storage (gemm_float.hip): operands as they lie in memory, rows 16-byte aligned, K a multiple of 4 for a k-contiguous
+// operand; row maps, device-resident M / K and segments as above; K ranges of its own if `parts` holds gemm_float_parts_bytes
+// (launch_gemm routes to it by itself; what it does not take goes to the generic kernel).
+int gemm_float_ranges(long M, long N, long K, int nz, int nseg, bool frames);      // frames: M counts frames, padded ones included
+size_t gemm_float_parts_bytes(long M, long N, long K, int nz, int nseg, bool frames);
 bool gemm_float_ok(const GemmArgs& g);
 hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s);
 // Products with few rows (gemm_skinny.hip): both operands k-contiguous bfloat16 with 16-byte aligned rows, K % 8 == 0,

@@ -224,10 +224,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
   const int rel = bid - band * 8 * tiles_m;
   const int tn = band * 8 + rel % width, tm = rel / width;
   const int m0 = tm * kBM, n0 = tn * kBN;
-  // blockIdx.y = problem z and, with ksplit > 1 (float C holding zeros or the value to add to), the range of the K axis
-  // that this work-group multiplies; the ranges' parts meet in C by atomic adds
-  const int ks = g.ksplit > 1 ? g.ksplit : 1;
-  const int z = blockIdx.y / ks, range = blockIdx.y - z * ks;
+  const int z = blockIdx.y;
   // Row maps and device-side extents (the frames that are real, numbered on the device): logical row r of a k-contiguous A
   // and of C is row a_rows[r] / c_rows[r] in memory, M is cut down to *m_dev; with both operands m-contiguous, row k of
   // the K axis is row k_rows[k] of A and of B, K cut down to *k_dev.
@@ -261,16 +258,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
     S::fetchA(sa, g, A, M, K, m0, kt * S::EPT, tid, arow);
     S::fetchB(sb, g, B, K, n0, kt * S::EPT, tid, brow);
   };
-  const int it_begin = (int)((long)total * range / ks), it_end = (int)((long)total * (range + 1) / ks);
-  if (it_end > it_begin) {
-    fetch(it_begin);
+  if (total > 0) {
+    fetch(0);
     S::commitA(sa, lds, tid);
     S::commitB(sb, lds + kTileBytes, tid);
   }
   __syncthreads();
-  for (int it = it_begin; it < it_end; ++it) {
-    const int cur = (it - it_begin) & 1;
-    if (it + 1 < it_end) fetch(it + 1);
+  for (int it = 0; it < total; ++it) {
+    const int cur = it & 1;
+    if (it + 1 < total) fetch(it + 1);
     const char* As = lds + cur * 2 * kTileBytes + (wm * 64 + r) * kLdsStride + gq * 16;
     const char* Bs = lds + cur * 2 * kTileBytes + kTileBytes + (wn * 64 + r) * kLdsStride + gq * 16;
 #pragma unroll
@@ -282,7 +278,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
       acc[1][0] = Mma<T>::run(a1, b0, acc[1][0]);
       acc[1][1] = Mma<T>::run(a1, b1, acc[1][1]);
     }
-    if (it + 1 < it_end) {
+    if (it + 1 < total) {
       S::commitA(sa, lds + (cur ^ 1) * 2 * kTileBytes, tid);
       S::commitB(sb, lds + (cur ^ 1) * 2 * kTileBytes + kTileBytes, tid);
     }
@@ -296,7 +292,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
   for (int j = 0; j < 2; ++j) {
     const int col = n0 + wn * 64 + j * 32 + r;
     if (col >= g.N) continue;
-    const float bv = (bias && range == 0) ? bias[col] : 0.f;
+    const float bv = bias ? bias[col] : 0.f;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -306,11 +302,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
           float val = acc[i][j][v] + bv;
           long off = (long)(g.c_rows ? g.c_rows[row] : row) * g.ldc + col;
           if constexpr (sizeof(TC) == 4) {
-            if (ks > 1) unsafeAtomicAdd((float*)C + off, val);
-            else {
-              if (g.accumulate) val += ((float*)C)[off];
-              ((float*)C)[off] = val;
-            }
+            if (g.accumulate) val += ((float*)C)[off];
+            ((float*)C)[off] = val;
           } else {
             ((uint16_t*)C)[off] = f2bf_bits(val);
           }
@@ -322,8 +315,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
 template <typename T, typename TC>
 hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
-  if (g.ksplit > 1 && (sizeof(TC) != 4 || g.parts)) return hipErrorInvalidValue;   // ranges of K: float C, added atomically
-  dim3 grid(tiles_m * tiles_n, g.nz * (g.ksplit > 1 ? g.ksplit : 1)), block(kThreads);
+  if (g.ksplit > 1) return hipErrorInvalidValue;
+  dim3 grid(tiles_m * tiles_n, g.nz), block(kThreads);
   if (g.a_kcontig && !g.b_kcontig) hipLaunchKernelGGL((gemm_kernel<T, TC, true, false, false>), grid, block, 0, s, g);
   else if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL((gemm_kernel<T, TC, true, true, false>), grid, block, 0, s, g);
   else if (!g.a_kcontig && !g.b_kcontig && g.lens) hipLaunchKernelGGL((gemm_kernel<T, TC, false, false, true>), grid, block, 0, s, g);

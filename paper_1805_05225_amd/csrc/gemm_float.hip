@@ -49,9 +49,8 @@ struct FArgs {
   int accumulate;
   const int* a_rows; const int* c_rows; int a_phys_rows; const int* m_dev;
   const int* k_rows; int k_phys_rows; const int* k_dev;
-  int ksplit;                                    // > 1: every K range adds its part to C atomically ...
-  float* parts; long sPart;                      // ... or (ksplit == 8 only) stores it at parts + (z * 8 + range) * sPart, rows
-                                                 // packed, and range r is worked on by XCD r alone
+  int ksplit;                                    // > 1: K range r stores its part at parts + (z * ksplit + r) * M * ldp, rows packed
+  float* parts; long ldp;                        // (of eight ranges, range r is worked on by XCD r alone)
   int tiles_m, tiles_n, per_xcd;
   unsigned a_bytes, b_bytes;                     // extent of one segment of A / B in memory
 };
@@ -82,24 +81,24 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
 
   // Work-groups are dealt to the eight XCDs round-robin: an XCD takes a run of consecutive tiles, column-major, i.e.
   // all row tiles of a few tile columns - the A panels and those few B panels are what its L2 has to hold.
-  // With `parts` (few tiles, long K: dX) every XCD takes ALL tiles for one eighth of K instead: its L2 then holds that
+  // With eight K ranges every XCD takes ALL tiles for one eighth of K instead: its L2 then holds that
   // eighth of B for good and streams that eighth of A once, and no operand byte is fetched by two XCDs.  The tiles
   // of one row panel (same rows of A) are neighbours in launch order, so they run side by side.
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const bool by_range = g.parts != nullptr;
+  const bool to_parts = g.ksplit > 1, by_range = g.ksplit == 8;
   const int t = by_range ? slot : xcd * g.per_xcd + slot;
   if ((!by_range && slot >= g.per_xcd) || t >= g.tiles_m * g.tiles_n) return;
   const int m0 = (by_range ? t / g.tiles_n : t % g.tiles_m) * kTile, n0 = (by_range ? t % g.tiles_n : t / g.tiles_m) * kTile;
   const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M;              // the grid is sized for g.M; surplus tiles leave at once
   if (m0 >= M) return;
-  const int ksplit = g.ksplit > 1 ? g.ksplit : 1;
+  const int ksplit = g.ksplit;
   const int z = by_range ? blockIdx.y : blockIdx.y / ksplit, ks = by_range ? xcd : blockIdx.y - z * ksplit;
   const int K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
   const int sps = max((K + kKS - 1) / kKS, 1);                   // stages per segment; what lies past K arrives as zeros
   const int nstage = K > 0 ? sps * g.nseg : 0;
   const int it0 = (int)((long)nstage * ks / ksplit);
   const int total = (int)((long)nstage * (ks + 1) / ksplit) - it0;
-  if (total <= 0 && !by_range && (ksplit > 1 || g.accumulate)) return;        // nothing to add
+  if (total <= 0 && !to_parts && g.accumulate) return;           // nothing to add
 
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)lds;
   // ---- loads ----
@@ -107,7 +106,7 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
   // of the stage, the upper 32 k-row p + 16; lane l fetches columns 4 (l % 32) .. + 3 of the tile.
   const int half = lane >> 5, chunk32 = lane & 31;
   const int k_lane = 16 * half + 4 * wave;                       // k of wavefront-load 0 inside a stage; load i adds i
-  const long krows_mem = g.k_rows ? g.k_phys_rows : K;
+  const long krows_mem = g.k_phys_rows > 0 ? g.k_phys_rows : K;  // rows that a k-major operand has in memory
   const bool am_col_ok = m0 + chunk32 * 4 < g.M, bm_col_ok = n0 + chunk32 * 4 < g.N;
   const unsigned am_col = (unsigned)(m0 + chunk32 * 4) * 4u, bm_col = (unsigned)(n0 + chunk32 * 4) * 4u;
   // k-contiguous operand: wavefront-load i writes tile rows 32 wave + 8 i .. + 7; lane l fills slot l % 8 of row l / 8
@@ -248,32 +247,29 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
   }
 
   // Epilogue: lane l holds C[m = block_m * 16 + l % 16][n = block_n * 16 + 4 (l / 16) .. + 3].
-  float* C = by_range ? g.parts + ((long)z * 8 + ks) * g.sPart : g.C + g.sCz * z;
-  const float* bias = (g.bias && ks == 0) ? g.bias + g.sbiasz * z : nullptr;
-  const bool vec_ok = (g.ldc % 4 == 0) && (((uintptr_t)C & 15u) == 0);
+  float* C = to_parts ? g.parts + ((long)z * ksplit + ks) * g.M * g.ldp : g.C + g.sCz * z;
+  const long ldc = to_parts ? g.ldp : g.ldc;
+  const float* bias = (g.bias && !to_parts) ? g.bias + g.sbiasz * z : nullptr;
+  const bool vec_ok = (ldc % 4 == 0) && (((uintptr_t)C & 15u) == 0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = m0 + wm * 64 + i * 16 + i16;
     if (row >= M) continue;
-    const long prow = (g.c_rows && !by_range) ? g.c_rows[row] : row;
+    const long prow = (g.c_rows && !to_parts) ? g.c_rows[row] : row;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int col = n0 + wn * 64 + j * 16 + 4 * q;
       if (col >= g.N) continue;
-      float* p = C + prow * g.ldc + col;
+      float* p = C + prow * ldc + col;
       float e[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
       if (bias) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           if (col + v < g.N) e[v] += bias[col + v];
       }
-      if (ksplit > 1 && !by_range) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (col + v < g.N) unsafeAtomicAdd(p + v, e[v]);
-      } else if (vec_ok && col + 3 < g.N) {
+      if (vec_ok && col + 3 < g.N) {
         float4 o = make_float4(e[0], e[1], e[2], e[3]);
-        if (g.accumulate && !by_range) {
+        if (g.accumulate && !to_parts) {
           const float4 old = *(const float4*)p;
           o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w;
         }
@@ -281,40 +277,31 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (col + v < g.N) p[v] = (g.accumulate && !by_range) ? p[v] + e[v] : e[v];
+          if (col + v < g.N) p[v] = (g.accumulate && !to_parts) ? p[v] + e[v] : e[v];
       }
     }
   }
 }
 
-// C[z][rows[m]][n] (+)= sum over the eight K ranges of parts[z][range][m][n], m below *m_dev when given; four columns per lane.
-__global__ void sum_ranges_kernel(const float* parts, float* C, int M, int N, long ldc, long sCz, long sPart, const int* c_rows,
-                                  const int* m_dev, int accumulate) {
-  const int nq = (N + 3) / 4;
+// C[z][rows[m]][n] (+)= sum over the K ranges of parts[z][range][m][n] (+ bias[n]), m below *m_dev when given; four columns per lane.
+__global__ void sum_ranges_kernel(FArgs g) {
+  const int nq = (g.N + 3) / 4;
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int m = (int)(idx / nq), n = (int)(idx % nq) * 4, z = blockIdx.y;
-  if (m >= (m_dev ? min(M, *m_dev) : M)) return;
-  const long src = (long)m * ldc + n;
-  float* dst = C + sCz * z + (long)(c_rows ? c_rows[m] : m) * ldc + n;
-  float v[4] = {0.f, 0.f, 0.f, 0.f};
-  const bool whole = n + 3 < N && ldc % 4 == 0 && (((uintptr_t)(C + sCz * z) & 15u) == 0);
-  if (accumulate)
-    for (int k = 0; k < 4; ++k)
-      if (n + k < N) v[k] = dst[k];
-  for (int r = 0; r < 8; ++r) {
-    const float* p = parts + ((long)z * 8 + r) * sPart + src;
-    if (whole) {
-      const f32x4 q4 = __builtin_nontemporal_load((const f32x4*)p);
-      v[0] += q4[0]; v[1] += q4[1]; v[2] += q4[2]; v[3] += q4[3];
-    } else {
-      for (int k = 0; k < 4; ++k)
-        if (n + k < N) v[k] += p[k];
-    }
-  }
-  if (whole) *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+  if (m >= (g.m_dev ? min(g.M, *g.m_dev) : g.M)) return;
+  const float* p = g.parts + (long)z * g.ksplit * g.M * g.ldp + (long)m * g.ldp + n;      // (ldp is a multiple of 4: whole quads)
+  float* dst = g.C + g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int r = 0; r < g.ksplit; ++r) v += __builtin_nontemporal_load((const f32x4*)(p + (long)r * g.M * g.ldp));
+  const float* bias = g.bias ? g.bias + g.sbiasz * z + n : nullptr;
+  const int cols = min(4, g.N - n);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (k < cols) v[k] += (bias ? bias[k] : 0.f) + (g.accumulate ? dst[k] : 0.f);
+  if (cols == 4 && ((uintptr_t)dst & 15u) == 0) *(f32x4*)dst = v;
   else
-    for (int k = 0; k < 4; ++k)
-      if (n + k < N) dst[k] = v[k];
+    for (int k = 0; k < cols; ++k) dst[k] = v[k];
 }
 
 __global__ __launch_bounds__(256, 2) void gemm_float_nn_kernel(FArgs g) { gemm_float_body<true, false>(g); }
@@ -323,12 +310,43 @@ __global__ __launch_bounds__(256, 2) void gemm_float_tn_kernel(FArgs g) { gemm_f
 
 }  // namespace
 
+// K ranges for a product with few 128 x 128 tiles.  A tile's stage of 32 k is 1.75 us of a compute unit's matrix cores (2.6 when the
+// unit has a single work-group and nothing hides its waits), work-groups come in whole rounds of 256 units, and the parts are
+// written and read once.  (Config 2, dW_x: 320 tiles leave 3 of 8 units idle in the second round; dW of 64 units over 10240 frames
+// was 4 tiles on 4 units, 1.4 ms, and is now 0.04.)
+// `frames`: rows are frames, padded ones included: judged with 0.6 of the rows real as well as with all.
+int gemm_float_ranges(long M, long N, long K, int nz, int nseg, bool frames) {
+  const long tiles = (long)cdiv(M, kTile) * cdiv(N, kTile) * nz, fewer = frames ? (long)cdiv(M * 3 / 5, kTile) * cdiv(N, kTile) * nz : tiles;
+  const long stages = nseg * (long)cdiv(K, kKS);
+  const auto loop_us = [&](long t, int r) {
+    const long rounds = cdiv(std::max(t, 1L) * r, 256L);
+    return (rounds == 1 ? 2.6 : 1.75 * rounds) * cdiv(stages, (long)r);
+  };
+  int best = 1;
+  double best_us = 1e30;
+  for (int r = 1; r <= 64 && (r == 1 || stages / r >= 4); ++r) {
+    double us = 0.5 * (loop_us(tiles, r) + loop_us(fewer, r)) + (r > 1 ? 6.0 + (double)r * M * N * nz * 8 / 4.5e6 : 0.0);
+    if (frames && r == 8) us *= 0.65;    // a range per XCD, operands from its own L2: dX of config 2 218 us, with six ranges 327
+    if (us < 0.95 * best_us) { best = r; best_us = us; }
+  }
+  return best;
+}
+size_t gemm_float_parts_bytes(long M, long N, long K, int nz, int nseg, bool frames) {
+  const int r = gemm_float_ranges(M, N, K, nz, nseg, frames);
+  return r > 1 ? (size_t)nz * r * M * ((N + 3) / 4 * 4) * 4 : 0;
+}
+
+static long rows_in_memory(const GemmArgs& g, bool a) {
+  if (a && g.a_kcontig) return g.a_rows ? g.a_phys_rows : g.M;
+  if (!a && g.b_kcontig) return g.N;
+  return g.k_phys_rows > 0 ? g.k_phys_rows : g.K;
+}
 bool gemm_float_ok(const GemmArgs& g) {
   const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
   const auto m4 = [](long v) { return v % 4 == 0; };
   const long lim = 0x7fffff00L;                                  // operands are addressed with 32-bit byte offsets
   if (g.in_bf16 || g.out_bf16 || g.lens || g.nseg < 1 || (!g.a_kcontig && g.b_kcontig)) return false;
-  if (g.parts && (g.ksplit != 8 || g.bias || !m4(g.ldc) || !a16(g.parts))) return false;   // parts: eight ranges, one per XCD
+  if (g.parts && !a16(g.parts)) return false;
   if (!a16(g.A) || !a16(g.B) || !m4(g.lda) || !m4(g.ldb) || !m4(g.sAz) || !m4(g.sBz) || !m4(g.sAseg) || !m4(g.sBseg)) return false;
   const bool tn = !g.a_kcontig && !g.b_kcontig;
   if (g.k_rows && (!tn || !a16(g.k_rows))) return false;
@@ -336,10 +354,8 @@ bool gemm_float_ok(const GemmArgs& g) {
   if (g.c_rows && !g.a_kcontig) return false;
   if (tn && g.nseg != 1) return false;
   if ((g.a_kcontig || g.b_kcontig) && !m4(g.K)) return false;    // 16-byte chunks along k must not straddle K
-  if (!g.a_kcontig && !m4(g.M)) return false;                    // ... nor along the columns of a k-major operand
-  if (!g.b_kcontig && !m4(g.N)) return false;
-  const long a_rows_mem = g.a_kcontig ? (g.a_rows ? g.a_phys_rows : g.M) : (g.k_rows ? g.k_phys_rows : g.K);
-  const long b_rows_mem = g.b_kcontig ? g.N : (g.k_rows ? g.k_phys_rows : g.K);
+                                                                 // (columns past M / N of a k-major operand reach no stored element)
+  const long a_rows_mem = rows_in_memory(g, true), b_rows_mem = rows_in_memory(g, false);
   return a_rows_mem * g.lda * 4 <= lim && b_rows_mem * g.ldb * 4 <= lim;
 }
 
@@ -352,12 +368,12 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s) {
   a.accumulate = g.accumulate;
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.a_phys_rows = g.a_phys_rows; a.m_dev = g.m_dev;
   a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows; a.k_dev = g.k_dev;
-  a.ksplit = g.ksplit > 1 ? g.ksplit : 1;
-  a.parts = g.parts; a.sPart = (long)g.M * g.ldc;
+  a.ksplit = g.parts ? gemm_float_ranges(g.M, g.N, g.K, g.nz, g.nseg, g.a_kcontig) : 1;
+  if (a.ksplit > 1 && gemm_float_parts_bytes(g.M, g.N, g.K, g.nz, g.nseg, g.a_kcontig) > g.parts_bytes) a.ksplit = 1;
+  a.parts = g.parts; a.ldp = (g.N + 3) / 4 * 4;
   a.tiles_m = cdiv(g.M, kTile); a.tiles_n = cdiv(g.N, kTile);
   a.per_xcd = cdiv(a.tiles_m * a.tiles_n, 8);
-  const long a_rows_mem = g.a_kcontig ? (g.a_rows ? g.a_phys_rows : g.M) : (g.k_rows ? g.k_phys_rows : g.K);
-  const long b_rows_mem = g.b_kcontig ? g.N : (g.k_rows ? g.k_phys_rows : g.K);
+  const long a_rows_mem = rows_in_memory(g, true), b_rows_mem = rows_in_memory(g, false);
   a.a_bytes = (unsigned)(a_rows_mem * g.lda * 4); a.b_bytes = (unsigned)(b_rows_mem * g.ldb * 4);
   static std::atomic<unsigned long long> attr_set{0};
   const hipError_t ea = once_per_device(attr_set, [] {
@@ -368,14 +384,13 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s) {
     return hipSuccess;
   });
   if (ea != hipSuccess) return ea;
-  const dim3 grid = a.parts ? dim3(a.tiles_m * a.tiles_n * 8, g.nz) : dim3(a.per_xcd * 8, g.nz * a.ksplit), block(256);
+  const dim3 grid = a.ksplit == 8 ? dim3(a.tiles_m * a.tiles_n * 8, g.nz) : dim3(a.per_xcd * 8, g.nz * a.ksplit), block(256);
   if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL(gemm_float_nt_kernel, grid, block, kLds, s, a);
   else if (g.a_kcontig) hipLaunchKernelGGL(gemm_float_nn_kernel, grid, block, kLds, s, a);
   else hipLaunchKernelGGL(gemm_float_tn_kernel, grid, block, kLds, s, a);
-  if (a.parts) {
+  if (a.ksplit > 1) {
     const long lanes = (long)g.M * ((g.N + 3) / 4);
-    hipLaunchKernelGGL(sum_ranges_kernel, dim3((unsigned)cdiv(lanes, 256L), g.nz), dim3(256), 0, s, a.parts, a.C, g.M, g.N, g.ldc, g.sCz, a.sPart,
-                       g.c_rows, g.m_dev, g.accumulate);
+    hipLaunchKernelGGL(sum_ranges_kernel, dim3((unsigned)cdiv(lanes, 256L), g.nz), dim3(256), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -146,10 +146,10 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->fast_gemm = p->bf16 && d->n % 2 == 0;
   p->TBp = (TB + 63) / 64 * 64;
   const bool fg = p->fast_gemm;
-  p->n_in8 = (d->n_in + 7) / 8 * 8;
+  p->n_in8 = p->bf16 ? (d->n_in + 7) / 8 * 8 : (d->n_in + 3) / 4 * 4;
   p->zx_nn = fg && gemm_tile_small(TB, 4L * d->n, p->D);
   p->ws_WxT = take(fg && !p->zx_nn ? D * 4 * n * p->n_in_pad * 2 : 0);
-  p->ws_xpad = take(fg ? TB * std::max(!p->zx_nn && p->n_in_pad != d->n_in ? p->n_in_pad : 0, p->n_in8 != d->n_in ? p->n_in8 : 0) * 2 : 0);
+  p->ws_xpad = take(fg || !p->bf16 ? TB * std::max(fg && !p->zx_nn && p->n_in_pad != d->n_in ? p->n_in_pad : 0, p->n_in8 != d->n_in ? p->n_in8 : 0) * p->esz : 0);
   // frame map of the batch (which frames are real), used to leave padded frames out of the products
   const bool fm = fg || !p->bf16;             // (float storage: its product kernels take the same row maps)
   p->ws_cidx = take(fm ? (size_t)TB * 4 : 0);
@@ -171,17 +171,17 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
     // rows' tiles do any work: 384 instead of 256 work-groups are aimed at.  Config 3: 160 tiles, 96 of them real, two
     // ranges instead of one: dX 1.44 -> 0.89 ms per step.)
     p->ks_dx = fg && !infer && p->bf16 && tiles > 0 ? (int)std::max(1L, std::min(std::min(384 / tiles, stages / 16), 8L)) : 1;
-    // float storage: 128 x 128 tiles; with fewer than 512 of them each XCD takes an eighth of K for all tiles (gemm_float.hip)
-    const long tiles_f = (long)cdiv(TB, 128) * cdiv(d->n_in, 128), stages_f = (long)p->D * cdiv(4L * d->n, 32);
-    if (!p->bf16 && !infer && tiles_f > 0 && tiles_f < 512 && stages_f >= 64) p->ks_dx = 8;
   }
   p->ks_dwx = fg && !infer ? ksplit_for(d->n_in, 4L * d->n) : 1;
   p->ks_dwh = fg && !infer ? ksplit_for(d->n, 4L * d->n) : 1;
-  // (the same products where gemm_tile.hip takes them: its own ranges)
-  const auto tile_parts = [&](long M, long N, long K, int nz, int nseg) { return fg && gemm_tile_small(M, N, nz) ? gemm_tile_parts_bytes(M, N, K, nz, nseg) : (size_t)0; };
-  size_t tp = TB > 0 && p->zx_nn && !p->single_step ? tile_parts(TB, 4L * d->n, p->n_in8, p->D, 1) : 0;
+  // (the same products where gemm_tile.hip or gemm_float.hip take them: their own ranges)
+  const auto tile_parts = [&](long M, long N, long K, int nz, int nseg, bool frames) {
+    if (!p->bf16) return gemm_float_parts_bytes(M, N, K, nz, nseg, frames);
+    return fg && gemm_tile_small(M, N, nz) ? gemm_tile_parts_bytes(M, N, K, nz, nseg) : (size_t)0;
+  };
+  size_t tp = TB > 0 && (p->zx_nn || !p->bf16) && !p->single_step ? tile_parts(TB, 4L * d->n, p->n_in8, p->D, 1, true) : 0;
   if (!infer && TB > 0)
-    tp = std::max({tp, tile_parts(TB, d->n_in, 4L * d->n, 1, p->D), tile_parts(d->n_in, 4L * d->n, TB, p->D, 1), tile_parts(d->n, 4L * d->n, TB, p->D, 1)});
+    tp = std::max({tp, tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true), tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false), tile_parts(d->n, 4L * d->n, TB, p->D, 1, false)});
   p->parts_bytes = std::max({tp, p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
                                p->ks_dx > 1 ? (size_t)p->ks_dx * TB * d->n_in * 4 : 0});
   p->ws_parts = take(p->parts_bytes);
@@ -363,11 +363,22 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           if (!frames_mapped) HIPCHK(launch_frame_map(seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), fidx, count, s));
           g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = g.M; g.m_dev = count;
         }
-      } else if (!p.bf16 && seq_lens) {  // float storage: the same selection of real frames
-        int* fidx = (int*)(ws + p.ws_fidx);
-        int* count = (int*)(ws + p.ws_count);
-        HIPCHK(launch_frame_map(seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), fidx, count, s));
-        g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = g.M; g.m_dev = count;
+      } else if (!p.bf16) {              // float storage: the same padding, the same selection of real frames
+        g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
+        if (p.n_in8 != p.n_in) {
+          GemmArgs gp = g;
+          gp.A = ws + p.ws_xpad; gp.K = p.n_in8; gp.lda = p.n_in8; gp.k_phys_rows = p.n_in;
+          if (gemm_float_ok(gp)) {
+            HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), 2 * p.n_in, 2 * p.n_in8, s));
+            g = gp;
+          }
+        }
+        if (seq_lens) {
+          int* fidx = (int*)(ws + p.ws_fidx);
+          int* count = (int*)(ws + p.ws_count);
+          HIPCHK(launch_frame_map(seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), fidx, count, s));
+          g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = g.M; g.m_dev = count;
+        }
       }
       HIPCHK(launch_gemm(g, s));
     }
@@ -771,20 +782,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.parts_bytes = 0;
       if (p.bf16 && gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
       else if (p.ks_dx > 1 && gemm_nt_ok(g)) { g.ksplit = p.ks_dx; g.parts = (float*)(ws + p.ws_parts); }
-      if (!p.bf16 && p.ks_dx == 8) {
-        g.ksplit = 8; g.parts = (float*)(ws + p.ws_parts);
-        if (!gemm_float_ok(g)) { g.ksplit = 0; g.parts = nullptr; }
-      }
-      if (!p.bf16 && !g.parts) {
-        // float storage, shapes the eight-range form above does not take: rows = frames and n_in columns give few 128 x 128 tiles (config 2: 85 with real
-        // frames), so K = 4n per direction is cut into ranges that add their parts to the zero-filled dx atomically
-        const long tiles = (long)cdiv(TB, 128) * cdiv(p.n_in, 128), stages = (long)p.D * cdiv(4L * p.n, 32);
-        const int ks = (int)std::max(1L, std::min(std::min(384 / std::max(tiles, 1L), stages / 16), 8L));
-        if (ks > 1) {
-          if (!compact) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
-          g.ksplit = ks;
-        }
-      }
+      if (!p.bf16) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
       HIPCHK(launch_gemm(g, s));
     }
     // Weight gradients straight from the frame-major tensors (a row per frame in X, Hprev and DZ: both operands of
@@ -826,6 +824,17 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       else { g.lens = seq_lens; g.Bt = p.B; g.T = p.T; }                              // (or every frame, padded ones read as zero)
       g.vecA = widest(g.lda, 0, 0, p.esz, 4);
       g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
+      if (!p.bf16) {
+        g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
+        if (pad_x) {
+          GemmArgs gp = g;
+          gp.A = ws + p.ws_xpad; gp.lda = p.n_in8;
+          if (gemm_float_ok(gp)) {
+            HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, 2 * p.n_in, 2 * p.n_in8, s));
+            g = gp;
+          }
+        }
+      }
       {
         Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
         HIPCHK(launch_gemm(g, s));
