@@ -195,6 +195,7 @@ struct PFwdArgs {
   unsigned* sync; unsigned spin_limit;
   unsigned* xcc;      // NULL or one zeroed word per work-group (see PBwdArgs)
   int rt0;            // set by the launcher: first 16-row tile of the batch that this launch handles
+  int slab0, slab_tiles;   // likewise (float kernels): first slab of this launch, row tiles per slab
   GridMap map;
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
 };
@@ -222,6 +223,7 @@ struct PBwdArgs {
   unsigned* sync; unsigned spin_limit;
   unsigned* xcc;      // NULL or one zeroed word per work-group: lets an exchange group find out whether it shares an XCD
   int rt0;            // set by the launcher: first 16-row tile of the batch that this launch handles
+  int slab0, slab_tiles;   // likewise (float kernels): first slab of this launch, row tiles per slab
   GridMap map;
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
 };
@@ -234,7 +236,8 @@ hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s);
 bool persist_bwd_f32_fits(const PBwdArgs& a);
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s);
 hipError_t launch_pack_wh_bwd_f32p(const void* W_h, void* Wb, int n, int ndir, hipStream_t s);
-inline size_t bwd_f32_wh_bytes(int n) { return (size_t)((n + 15) / 16) * 4 * 16 * 16 * 64 * 4; }
+inline int bwd_f32_nct(int n) { return n <= 256 ? 4 : n <= 512 ? 8 : 16; }      // output column tiles (of 16) per wavefront
+inline size_t bwd_f32_wh_bytes(int n) { return (size_t)((n + 15) / 16) * 4 * bwd_f32_nct(n) * 16 * 64 * 4; }
 inline size_t bwd_f32_ring_bytes(int B, int n) {
   const size_t tiles = (size_t)((n + 15) / 16), rts = 2 * (size_t)(((B > 0 ? B : 1) + 31) / 32);
   return rts * tiles * tiles * 1024;

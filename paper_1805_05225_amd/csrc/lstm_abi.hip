@@ -23,7 +23,7 @@ struct Plan {
   size_t esz;
   int nkc_f, nkc_b, nrt, ntile_f, ntile_b;
   int nkc_ll_f, ntile16;                    // ring layout of the single-launch forward kernels
-  // reserve: per direction [gates float T*B*4n][hprev storage T*B*ldh], ldh = n, in bfloat16 rounded up to rows of whole 16-byte chunks
+  // reserve: per direction [gates float T*B*4n][hprev storage T*B*ldh], ldh = n rounded up to rows of whole 16-byte chunks
   long ldh;
   size_t res_gates, res_hprev, res_dir_stride, reserve_bytes;
   // workspace
@@ -94,7 +94,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   const bool infer = d->flags & LSTM_FLAG_INFERENCE;
   p->res_gates = 0;
   p->res_hprev = up(TB * 4 * n * 4);
-  p->ldh = p->bf16 ? (d->n + 7) / 8 * 8 : d->n;
+  p->ldh = p->bf16 ? (d->n + 7) / 8 * 8 : (d->n + 3) / 4 * 4;
   p->res_dir_stride = p->res_hprev + up(TB * p->ldh * p->esz);
   p->reserve_bytes = D * p->res_dir_stride + kAlign;
   size_t o = 0;
@@ -106,7 +106,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_Wf = take(p->Wf_bytes + 1024);            // packed W_h, then one chunk of zeros
   const bool part = p->bf16 && d->n <= 1024;          // the partial-sum backward kernel may be chosen
   // float storage: the single-launch backward kernel (batches of up to 256 rows: its rings grow with B n^2 / 16)
-  const bool part32 = !p->bf16 && d->n % 8 == 0 && d->n <= 1024 && d->B <= 256;
+  const bool part32 = !p->bf16 && d->n <= 1024 && d->B <= 256;
   p->ws_Wb = take(infer ? 0 : D * std::max({(size_t)p->ntile_b * p->nkc_b * 1024, part ? bwdp_wh_bytes(d->n) : (size_t)0,
                                             part32 ? bwd_f32_wh_bytes(d->n) : (size_t)0}));
   p->hfrag_bytes = D * p->nrt * (size_t)std::max(p->nkc_f, p->nkc_ll_f) * 1024;
@@ -489,11 +489,12 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     }
     // float storage: one launch for the whole time loop as well (the kernel works on the per-step path's packed W_h and
     // h buffers)
-    if (!done && !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n % 8 == 0) {
+    if (!done && !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2) {
       PFwdArgs pa = {};
       pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.nkc = p.nkc_f; pa.T = p.T; pa.ndir = p.D; pa.write_gates = infer ? 0 : 1;
       pa.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
       pa.sync = (unsigned*)(ws + p.ws_sync); pa.spin_limit = kSpinLimit;
+      pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
       const size_t frag_dir = (size_t)p.nrt * p.nkc_f * 1024;
       for (size_t d = 0; d < D; ++d) {
         PFwdDir& fd = pa.d[d];
@@ -645,7 +646,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
     for (size_t d = 0; d < D; ++d) pa.d[d].lddy = (long)(D * n);       // (the check looks at the frame sizes)
     const bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_bwd_fits(pa);
-    const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n % 8 == 0 && p.n <= 1024 && p.B <= 256 &&
+    const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n <= 1024 && p.B <= 256 &&
                           persist_bwd_f32_fits(pa);
     {
       Phase ph(LSTM_PHASE_PREP, 5, s);

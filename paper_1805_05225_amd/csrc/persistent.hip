@@ -1769,16 +1769,57 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
 // x 16 bytes, a lane's 16 bytes being two such units, so the reader of the other kernels applies unchanged.  An initial
 // hidden state never enters the ring (it is not bounded by 1): rows publish zeros until their first frame is done, and
 // launch_h0_term has added h0 W_h to that frame's pre-activations.
+// Rows are dealt to row tiles by falling length, and a slab is a long tile together with a short one: a row tile leaves its
+// loop (reversed: enters it) at its longest row's last frame - every work-group of the exchange group knows it from the lengths - and its
+// half of every step beyond that costs nothing but the stores of padding.  (Config 2, rows of 10 - 50 frames in any order: the four tiles
+// work 50, 40, 30 and 20 of 50 steps: forward 594 -> 470 us, backward 703 -> 538.)  Rows beyond 256 stay where they are.  With a single row tile per slab (whenever the device
+// holds the launch that way) a step has no other half to wait for.
+// order[slot] = row; called by all 256 threads
+__device__ __forceinline__ void rows_by_length(int* order, int* len, const int* lens, int B, int T) {
+  const int b = threadIdx.x;
+  if (b < B) len[b] = clamp_len(lens, b, T);
+  __syncthreads();
+  if (b < B) {
+    int rank = 0;
+    for (int o = 0; o < B; ++o) rank += len[o] > len[b] || (len[o] == len[b] && o < b);
+    order[rank] = b;
+  }
+  __syncthreads();
+}
+// What a work-group of the float kernels works on: row tiles (of rows in falling length), the rows of this thread's cells (pointwise row r16), and
+// the steps that a tile takes part in, as positions in processing order [first, first + count).
+struct F32Rows {
+  int count_tiles, tile[2], row[2], first[2], count[2];      // row: -1 = none
+};
+__device__ __forceinline__ F32Rows f32_rows(const int* lens, int B, int T, bool rev, int slab, int slab_tiles, int r16) {
+  __shared__ int order[256], len[256];
+  const bool sorted = lens != nullptr && B <= 256;
+  if (sorted) rows_by_length(order, len, lens, B, T);
+  F32Rows f;
+  const int nrt = (B + 15) / 16;
+  f.tile[0] = slab; f.tile[1] = nrt - 1 - slab;
+  f.count_tiles = slab_tiles == 2 && f.tile[1] > f.tile[0] ? 2 : 1;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int slot = f.tile[k] * 16 + r16;
+    f.row[k] = k < f.count_tiles && slot < B ? (sorted ? order[slot] : slot) : -1;
+    f.count[k] = __builtin_amdgcn_readfirstlane(sorted && k < f.count_tiles ? len[order[f.tile[k] * 16]] : T);    // (the tile's first row is its longest)
+    f.first[k] = rev ? T - f.count[k] : 0;
+  }
+  return f;
+}
+
 template <int NCH>                                         // chunks per wavefront at most: n <= 64 * NCH
 __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
   __shared__ float red[4][16][65];
-  const int tile = blockIdx.x, dir = blockIdx.z;           // tile: 16 units
-  const PFwdDir d = a.d[dir];          // a copy: fields read through a reference are fetched again in every time step
+  const WgCoord wg = wg_coord(a.map, a.ndir);
+  if (!wg.live) return;
+  publish_xcd(a.xcc, wg.base, wg.tile);
+  const int tile = wg.tile;                                // 16 units
+  const PFwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nkc = a.nkc, n = a.n, B = a.B, T = a.T;
-  const int rt_base = a.rt0 + 2 * (int)blockIdx.y;         // first 16-row tile of this work-group's slab
-  const int nrt_here = min(2, (B + 15) / 16 - rt_base);
   const int ntile8 = (n + 7) / 8;
   unsigned* err = a.sync;
   bool dead = false;
@@ -1799,10 +1840,13 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
     }
   }
   agpr_loads_done();
+  const int local = NCH <= 8 ? group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit) : 0;      // (more than 32 members never are)
 
   // pointwise: row r16 of each row tile, unit u of the tile's 16
   const int r16 = tid >> 4, u = tid & 15;
   const int j = tile * 16 + u;
+  const F32Rows rows = f32_rows(a.lens, B, T, d.rev, a.slab0 + wg.rt, a.slab_tiles, r16);
+  const int nrt_here = rows.count_tiles;
   float c[2] = {0.f, 0.f}, h[2] = {0.f, 0.f};
   int L[2] = {0, 0};
   bool active[2];
@@ -1811,8 +1855,8 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
   bool started[2] = {false, false};
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    const int b = (rt_base + k) * 16 + r16;
-    active[k] = k < nrt_here && b < B && j < n;
+    const int b = rows.row[k];
+    active[k] = b >= 0 && j < n;
     if (active[k]) {
       c[k] = d.cstate[(long)b * n + j];
       h[k] = d.hstate[(long)b * n + j];
@@ -1821,7 +1865,7 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
   }
   // The even unit of a pair publishes both: chunk j / 16, lane group (j % 16) / 4, half ((j % 4) / 2) of that lane's 16 bytes
   constexpr unsigned kParked = 0x7ff00000u;
-  const bool publishes = (u & 1) == 0 && j < n;            // (n is a multiple of 8: the odd partner exists as well)
+  const bool publishes = (u & 1) == 0 && (j & ~3) < n;     // (readers look at whole quads of units: those past n are published as zeros)
   const unsigned pub_in_tile = (unsigned)((((long)(j >> 4) * 64 + ((j & 15) >> 2) * 16 + r16) * 2 + ((j >> 1) & 1)) * 8);
   const unsigned ring_bytes = (unsigned)((B + 15) / 16) * nkc * 1024u;
   const long fg = (long)B * 4 * n, fy = (long)B * d.ldy, fs = (long)B * n;     // elements per frame
@@ -1836,25 +1880,35 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 #endif
   constexpr int kEarly = LSTM_FWD_F32_EARLY;
   u32x4 x[NCH];
-  auto reader = [&](int tau, int k) __attribute__((always_inline)) {
-    return make_reader(((tau & 1) ? d.ring1 : d.ring0) + (long)(rt_base + k) * nkc * 64, nkc, (n + 3) / 4, wave, lane,
-                       ll_fwd_tag((unsigned)tau) << 14, err, a.spin_limit, 0);
+  auto in_loop = [&](int tau, int k) { return k < nrt_here && tau >= rows.first[k] && tau < rows.first[k] + rows.count[k]; };
+  auto reader = [&](int step, int k) __attribute__((always_inline)) {       // step: of the row tile's own steps
+    return make_reader(((step & 1) ? d.ring1 : d.ring0) + (long)rows.tile[k] * nkc * 64, nkc, (n + 3) / 4, wave, lane,
+                       ll_fwd_tag((unsigned)step) << 14, err, a.spin_limit, 0);
   };
   auto issue_loads = [&](int tau, int k) __attribute__((always_inline)) {
-    const RingReader rn = reader(tau, k);
+    const RingReader rn = reader(tau - rows.first[k], k);
 #pragma unroll
     for (int it = 0; it < kEarly; ++it) x[it] = rn.load_it(it);
   };
-  if (T > 0) issue_loads(0, 0);
+  // (a row tile takes part in no step before the longer one of its slab, and in none after it)
+  if (rows.count[0] > 0) issue_loads(rows.first[0], 0);
 
   for (int tau = 0; tau < T; ++tau) {
     const int t = d.rev ? T - 1 - tau : tau;
-    const unsigned tag = ll_fwd_tag((unsigned)tau) << 14, tagw = tag << 16;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {                          // the slab's two row tiles, half a step apart
-      if (k >= nrt_here) break;                            // (the same in every work-group of the launch)
+      if (k >= nrt_here) break;                            // (the same in every work-group of the exchange group)
       PROF_MARK(4)
-      const int b = (rt_base + k) * 16 + r16;
+      const int b = rows.row[k], step = tau - rows.first[k];
+      if (!in_loop(tau, k)) {                              // every row of the tile is padding here
+        if (active[k]) {
+          ((float*)d.y)[t * fy + (long)b * d.ldy + j] = 0.f;
+          if (d.cs) d.cs[t * fs + (long)b * n + j] = c[k];
+          if (d.hprev) ((float*)d.hprev)[(t * (long)B + b) * d.ldh + j] = h[k];
+        }
+        continue;
+      }
+      const unsigned tagw = ll_fwd_tag((unsigned)step) << 30;
       const bool valid = active[k] && t < L[k];
       // this frame's x W_x + b: in flight while the products run
       float zx[4];
@@ -1864,7 +1918,7 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) acc[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
       operands_settle(acc[0], acc[1], acc[2], acc[3]);     // (the MFMAs are assembly text: wait states by hand)
-      const RingReader rd = reader(tau, k);
+      const RingReader rd = reader(step, k);
       auto use = [&](int it, const u32x4& x) __attribute__((always_inline)) {
         u32x4 av = {x[0], x[1] & ~kLLFwdTagBit, x[2], x[3] & ~kLLFwdTagBit};
         asm volatile("s_nop 4" : "+v"(av));                // masked just now by the vector ALU
@@ -1884,8 +1938,8 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
         else { redo |= 1ull << it; PROF_REDO(1) }
       }
       if (redo) rd.template fix_up_batch<NCH>(redo, dead, use);
-      if (k + 1 < nrt_here) issue_loads(tau, k + 1);
-      else if (tau + 1 < T) issue_loads(tau + 1, 0);
+      if (k == 0 && in_loop(tau, 1)) issue_loads(tau, 1);
+      else if (in_loop(tau + 1, 0)) issue_loads(tau + 1, 0);
       mfma_settle(acc[0], acc[1], acc[2], acc[3]);         // (behind the loads: their issue covers part of the wait)
       PROF_MARK(0)
       // accumulator rows 4 * (lane / 16) + v of the row tile, column lane % 16 of the column tile
@@ -1913,14 +1967,16 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
       {                               // the recurrence's critical store goes out first (16: agent scope, written through)
         const unsigned h_pub = started[k] ? __float_as_uint(h[k]) : 0u;
         const unsigned h_odd = (unsigned)__builtin_amdgcn_mov_dpp((int)h_pub, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]: the neighbour's h
-        const u32x2 unit = {h_pub, h_odd | (ll_fwd_tag((unsigned)tau + 1u) << 30)};
-        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((tau & 1) ? d.ring0 : d.ring1), 0, ring_bytes, kBufFlags);
-        __builtin_amdgcn_raw_buffer_store_b64(unit, ro, publishes ? (unsigned)(rt_base + k) * (unsigned)nkc * 1024u + pub_in_tile : kParked, 0, 16);
+        const u32x2 unit = {h_pub, h_odd | (ll_fwd_tag((unsigned)step + 1u) << 30)};
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((step & 1) ? d.ring0 : d.ring1), 0, ring_bytes, kBufFlags);
+        const unsigned off = publishes ? (unsigned)rows.tile[k] * (unsigned)nkc * 1024u + pub_in_tile : kParked;
+        if (local) __builtin_amdgcn_raw_buffer_store_b64(unit, ro, off, 0, 1);
+        else __builtin_amdgcn_raw_buffer_store_b64(unit, ro, off, 0, 16);
       }
       if (active[k]) {                // layer outputs and what the backward pass needs
         ((float*)d.y)[t * fy + (long)b * d.ldy + j] = valid ? h[k] : 0.f;
         if (d.cs) d.cs[t * fs + (long)b * n + j] = c[k];
-        if (d.hprev) ((float*)d.hprev)[t * fs + (long)b * n + j] = hprev;
+        if (d.hprev) ((float*)d.hprev)[(t * (long)B + b) * d.ldh + j] = hprev;
         if (valid && a.write_gates) {
           float* gp = d.gates + t * fg + (long)b * 4 * n + j;
           gp[0] = o.gi; gp[n] = o.gf; gp[2 * n] = o.gg; gp[3 * n] = o.go;
@@ -1933,7 +1989,7 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 #pragma unroll
   for (int k = 0; k < 2; ++k)
     if (active[k]) {
-      const int b = (rt_base + k) * 16 + r16;
+      const int b = rows.row[k];
       d.cstate[(long)b * n + j] = c[k];
       d.hstate[(long)b * n + j] = h[k];
     }
@@ -1957,14 +2013,15 @@ template <int NCT>                                         // column tiles per w
 __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   __shared__ float red[4][16][17];                         // [wavefront][row][output]
   __shared__ __attribute__((aligned(16))) float zb[16][68];// dz of the row tile in hand: [row][gate column kappa]
-  const int J = blockIdx.x, dir = blockIdx.z;              // J: tile of 16 units
-  const PBwdDir d = a.d[dir];          // a copy: fields read through a reference are fetched again in every time step
+  const WgCoord wg = wg_coord(a.map, a.ndir);
+  if (!wg.live) return;
+  publish_xcd(a.xcc, wg.base, wg.tile);
+  const int J = wg.tile;                                   // tile of 16 units
+  const PBwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = a.n, B = a.B, T = a.T;
   const int ntile = (n + 15) / 16;
-  const int rt_base = a.rt0 + 2 * (int)blockIdx.y;         // first 16-row tile of this work-group's slab
-  const int nrt_here = min(2, (B + 15) / 16 - rt_base);
   unsigned* err = a.sync;
   bool dead = false;
 
@@ -1978,18 +2035,21 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) w[ci][s4] = load_to_agpr((const uint4*)d.Wb + ((((long)J * 4 + wave) * NCT + ci) * 4 + s4) * 64 + lane);
   agpr_loads_done();
+  const int local = NCT <= 8 ? group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit) : 0;      // (more than 32 members never are)
 
   // pointwise: row r16 of each row tile, unit u of the tile's 16
   const int r16 = tid >> 4, u = tid & 15;
   const int j = J * 16 + u;
+  const F32Rows rows = f32_rows(a.lens, B, T, d.rev, a.slab0 + wg.rt, a.slab_tiles, r16);
+  const int nrt_here = rows.count_tiles;
   float Dh[2] = {0.f, 0.f}, Dc[2] = {0.f, 0.f};
   float dbsum[4] = {0.f, 0.f, 0.f, 0.f};                    // bias gradient of this thread's unit over its two rows and all frames
   int L[2] = {0, 0};
   bool active[2];
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    const int b = (rt_base + k) * 16 + r16;
-    active[k] = k < nrt_here && b < B && j < n;
+    const int b = rows.row[k];
+    active[k] = b >= 0 && j < n;
     if (active[k]) {
       Dh[k] = d.Dh[(long)b * n + j];
       Dc[k] = d.Dc[(long)b * n + j];
@@ -2004,23 +2064,24 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   // earlier, the loads run kWin ahead of the additions, one load and one addition behind each column tile's MFMAs, and
   // the matrix cores do not wait for the exchange.  `ps_c` / `redo_c` carry the sums (or, if a tag was stale, the order to fetch
   // everything again) into the next half step.
-#ifndef LSTM_BWD_F32_WIN
-#define LSTM_BWD_F32_WIN 6
-#endif
-  constexpr int kWin = LSTM_BWD_F32_WIN;
+  constexpr int kWin = NCT < 6 ? NCT : 6;
   static_assert(kWin >= 1 && kWin <= 16 && kWin <= NCT, "wait_loads_but covers up to 15 younger loads");
   u32x4 x[NCT];
   float ps_c[4] = {0.f, 0.f, 0.f, 0.f};
   unsigned long long redo_c = 0ull;
   bool have_c = false;
-  auto reader = [&](int sigma, int k) __attribute__((always_inline)) {
+  // A row tile's own steps: step s of `count` works on position first + count - 1 - s in processing order; step `count` only
+  // collects the Dh that leaves the tile's first frame.  In a shorter tile they begin later (reversed: end earlier).
+  auto step_of = [&](int sigma, int k) { return sigma - (T - rows.first[k] - rows.count[k]); };
+  auto in_loop = [&](int sigma, int k) { const int st = step_of(sigma, k); return k < nrt_here && st >= 0 && st <= rows.count[k] && rows.count[k] > 0; };
+  auto reader = [&](int st, int k) __attribute__((always_inline)) {
     RingReader rd;
-    const long tile_base = (((long)(rt_base + k) * ntile + J) * ntile) * 64;                   // uint4 index of [row tile][J][0]
-    rd.rs = __builtin_amdgcn_make_buffer_rsrc((void*)((((sigma - 1) & 1) ? d.ring1 : d.ring0) + tile_base), 0, ntile * 1024, kBufFlags);
+    const long tile_base = (((long)rows.tile[k] * ntile + J) * ntile) * 64;                    // uint4 index of [row tile][J][0]
+    rd.rs = __builtin_amdgcn_make_buffer_rsrc((void*)((((st - 1) & 1) ? d.ring1 : d.ring0) + tile_base), 0, ntile * 1024, kBufFlags);
     rd.voff = (unsigned)(wave * 1024 + lane * 16);       // load `it` of this wavefront covers producer wave + 4 it
     rd.it_bytes = 4096u;
     rd.lim = ntile - wave; rd.lim_step = 4;
-    rd.tag = part_tag(sigma) << 14; rd.err = err; rd.limit = a.spin_limit;
+    rd.tag = part_tag(st) << 14; rd.err = err; rd.limit = a.spin_limit;
     rd.nitv = (ntile + 3) / 4; rd.rot = 0;
     return rd;
   };
@@ -2035,12 +2096,20 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
     const int tau = T - 1 - sigma;                         // position in processing order; -1 in the collecting step
     const int t = d.rev ? T - 1 - tau : tau;               // this step's frame (outside [0, T) in the collecting step)
     const int t_next = d.rev ? t - 1 : t + 1;              // the frame of the step before: where the partial sums come from
-    const bool pointwise = sigma < T;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {                          // the slab's two row tiles, half a step apart
-      if (k >= nrt_here) break;                            // (the same in every work-group of the launch)
+      if (k >= nrt_here) break;                            // (the same in every work-group of the exchange group)
       PROF_MARK(4)
-      const int b = (rt_base + k) * 16 + r16;
+      const int b = rows.row[k], st = step_of(sigma, k);
+      if (!in_loop(sigma, k) || (st == rows.count[k] && tau >= 0)) {
+        // every row of the tile is padding here; the tile's collecting step falls on such a frame if the tile is reversed and shorter
+        if (active[k] && tau >= 0) {
+          float* zp = (float*)d.DZ + t * fg + (long)b * 4 * n + j;
+          zp[0] = 0.f; zp[n] = 0.f; zp[2 * n] = 0.f; zp[3 * n] = 0.f;
+        }
+        if (!in_loop(sigma, k)) continue;
+      }
+      const bool pointwise = st < rows.count[k];
       const bool valid = pointwise && active[k] && t < L[k];
       // what the gate gradients of the frame need: in flight while the partial sums are collected
       float gi = 0.f, gf = 0.f, gg = 0.f, go = 0.f, c_new = 0.f, c_prev = 0.f, dy = 0.f;
@@ -2052,8 +2121,8 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
         c_prev = (tp >= 0 && tp < T) ? d.cs[tp * fs + (long)b * n + j] : (d.c0 ? d.c0[(long)b * n + j] : 0.f);
         dy = ((const float*)d.dy)[t * fy + (long)b * d.lddy + j];
       }
-      if (sigma > 0) {                                     // the partial sums of Dh that the step before published
-        const RingReader rd = reader(sigma, k);
+      if (st > 0) {                                        // the partial sums of Dh that the step before published
+        const RingReader rd = reader(st, k);
         const unsigned tagw = rd.tag << 16;
         float ps[4] = {ps_c[0], ps_c[1], ps_c[2], ps_c[3]};
         unsigned long long redo = redo_c;
@@ -2079,7 +2148,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       }
       PROF_MARK(0)
       __syncthreads();
-      if (sigma > 0 && active[k] && t_next >= 0 && t_next < L[k])
+      if (st > 0 && active[k] && t_next >= 0 && t_next < L[k])
         Dh[k] = (red[0][r16][u] + red[1][r16][u] + red[2][r16][u] + red[3][r16][u]) * (1.f / kPartScale);
       float dz[4] = {0.f, 0.f, 0.f, 0.f};
       if (valid) lstm_cell_grad(gi, gf, gg, go, c_new, c_prev, dy + Dh[k], Dc[k], dz);
@@ -2098,9 +2167,10 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       have_c = false;
       if (pointwise) {
         // what the next half step consumes (the other row tile's partial sums, published half a step ago) is collected here
-        const int k_n = k ^ 1, sigma_n = k == 0 ? sigma : sigma + 1;
-        const bool collect = nrt_here == 2 && sigma_n >= 1 && sigma_n <= T;
-        const RingReader rn = reader(sigma_n, k_n);
+        const int k_n = k ^ 1, sigma_n = k == 0 ? sigma : sigma + 1, st_n = step_of(sigma_n, k_n);
+        // (the next half step must be the other tile's, and not its first, which consumes nothing)
+        const bool collect = in_loop(sigma_n, k_n) && st_n >= 1;
+        const RingReader rn = reader(st_n, k_n);
         const unsigned tagw_n = rn.tag << 16;
         float psn[4] = {0.f, 0.f, 0.f, 0.f};
         unsigned stale_n = 0u;
@@ -2115,16 +2185,17 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           const float4 v = *(const float4*)&zb[lane & 15][(lane >> 4) * 16 + 4 * s4];
           av[4 * s4] = v.x; av[4 * s4 + 1] = v.y; av[4 * s4 + 2] = v.z; av[4 * s4 + 3] = v.w;
         }
-        const unsigned tag_hi = part_tag(sigma + 1) << 30;
-        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((sigma & 1) ? d.ring1 : d.ring0), 0, ring_bytes, kBufFlags);
+        const unsigned tag_hi = part_tag(st + 1) << 30;
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((st & 1) ? d.ring1 : d.ring0), 0, ring_bytes, kBufFlags);
         // destination tile wave + 4 ci (one past the last: parked), this producer's block
-        const unsigned pub0 = (unsigned)((((rt_base + k) * ntile + wave) * ntile + J) * 1024 + lane * 16);
+        const unsigned pub0 = (unsigned)(((rows.tile[k] * ntile + wave) * ntile + J) * 1024 + lane * 16);
         // The accumulator of column tile ci is published behind the MFMAs of column tile ci + 1: by then its last MFMA has long
         // finished (the compiler does not see the MFMAs in the assembly text and inserts no wait states for their results).
         auto publish = [&](int ci, const f32x4& acc) __attribute__((always_inline)) {
           const u32x4 unit = {__float_as_uint(acc[0]), __float_as_uint(acc[1]) | tag_hi, __float_as_uint(acc[2]), __float_as_uint(acc[3]) | tag_hi};
           const unsigned off = wave + 4 * ci < ntile ? pub0 + (unsigned)(4 * ci) * (unsigned)ntile * 1024u : 0x7ff00000u;
-          __builtin_amdgcn_raw_buffer_store_b128(unit, ro, off, 0, 16);    // 16: agent scope, written through
+          if (local) __builtin_amdgcn_raw_buffer_store_b128(unit, ro, off, 0, 1);
+          else __builtin_amdgcn_raw_buffer_store_b128(unit, ro, off, 0, 16);    // 16: agent scope, written through
         };
         f32x4 acc2[2];
 #pragma unroll
@@ -2163,11 +2234,11 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 #pragma unroll
   for (int k = 0; k < 2; ++k)
     if (active[k]) {
-      const int b = (rt_base + k) * 16 + r16;
+      const int b = rows.row[k];
       d.Dh[(long)b * n + j] = Dh[k];
       d.Dc[(long)b * n + j] = Dc[k];
     }
-  if (d.dbpart) {                       // bias gradient: this work-group's 32 rows summed into the first of the slab's four slices (the others stay zero)
+  if (d.dbpart) {                       // bias gradient: this work-group's rows summed into the first slice of its first row tile (the others stay zero)
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 4; ++q) zb[r16][q * 16 + u] = dbsum[q];
@@ -2177,7 +2248,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       float sum = 0.f;
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) sum += zb[rr][q * 16 + uu];
-      if (jj < n) d.dbpart[(long)2 * rt_base * 4 * n + q * n + jj] = sum;
+      if (jj < n) d.dbpart[(long)2 * rows.tile[0] * 4 * n + q * n + jj] = sum;
     }
   }
 }
@@ -2315,7 +2386,7 @@ int capacity(K kernel) {
 // slabs had already advanced the state of their rows, so the call as a whole has failed and nothing may be re-run.
 template <typename K, typename A>
 hipError_t coop_slabs(K kernel, int ntile, int rows_per_group, const A& a, hipStream_t s) {
-  const int per_rt = 16 / rows_per_group, nrow = cdiv(a.B, rows_per_group);
+  const int per_rt = rows_per_group > 16 ? 1 : 16 / rows_per_group, nrow = cdiv(a.B, rows_per_group);
   const long cap = capacity(kernel);
   const long most = cap / ((long)ntile * a.ndir);                      // row groups per launch
   const int slab = most >= nrow ? nrow : (int)(most / per_rt * per_rt);
@@ -2323,6 +2394,7 @@ hipError_t coop_slabs(K kernel, int ntile, int rows_per_group, const A& a, hipSt
   for (int row0 = 0; row0 < nrow; row0 += slab) {
     A copy = a;
     copy.rt0 = row0 / per_rt;
+    copy.slab0 = row0; copy.slab_tiles = rows_per_group / 16;          // (the float kernels)
     copy.map.ntile = ntile;
     copy.map.nrow = std::min(slab, nrow - row0);
     const int groups = copy.map.nrow * a.ndir, gpx = cdiv(groups, 8);
@@ -2433,97 +2505,74 @@ __global__ void init_ring_f32_kernel(uint4* ring0, uint4* ring1, long total) {
   ring0[idx] = make_uint4(0u, t, 0u, t);
   ring1[idx] = make_uint4(0u, 0u, 0u, 0u);
 }
+// The float kernels' form for n units, as above (50 steps, both directions: n = 500, 64 rows, forward 519 -> 239 us, backward 767 -> 253; n = 256,
+// 16 rows, 332 -> 155 and 329 -> 149, with the exchange inside an XCD).
+FwdKernel fwd_f32_for(int n) { return n <= 256 ? persist_fwd_f32_kernel<4> : n <= 512 ? persist_fwd_f32_kernel<8> : persist_fwd_f32_kernel<16>; }
+BwdKernel bwd_f32_for(int n) { return bwd_f32_nct(n) == 4 ? persist_bwd_f32_kernel<4> : bwd_f32_nct(n) == 8 ? persist_bwd_f32_kernel<8> : persist_bwd_f32_kernel<16>; }
+// A work-group is one row tile where the device holds all of them so, else two.
+template <typename K>
+int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntile * cdiv(B, 16) * ndir <= capacity(kernel) ? 16 : 32; }
+
 bool persist_fwd_f32_fits(const PFwdArgs& a) {
-  constexpr int kNch = 16;
-  if (a.n % 8 != 0 || a.nkc > 4 * kNch || a.T < 2) return false;
+  if (a.n > 1024 || a.T < 2) return false;
   const long ring_bytes = (long)cdiv(a.B, 16) * a.nkc * 1024;
-  if (ring_bytes >= 0x7ff00000L) return false;
-  for (int d = 0; d < a.ndir; ++d) {
-    const PFwdDir& f = a.d[d];
-    if ((((uintptr_t)f.y | (uintptr_t)f.cs | (uintptr_t)f.hprev | (uintptr_t)f.gates | (uintptr_t)f.hstate | (uintptr_t)f.cstate) & 7) || (f.ldy & 1))
-      return false;
-  }
-  return (long)cdiv(a.n, 16) * a.ndir <= capacity(persist_fwd_f32_kernel<kNch>);
+  return ring_bytes < 0x7ff00000L && (long)cdiv(a.n, 16) * a.ndir <= capacity(fwd_f32_for(a.n));
 }
-// As many slabs of 32 rows per launch as the device holds at once (each launch walks all T steps of its rows; batch
-// rows never interact).
 hipError_t launch_persist_fwd_f32(const PFwdArgs& a, hipStream_t s) {
-  constexpr int kNch = 16;
   if (!persist_fwd_f32_fits(a)) return hipErrorCooperativeLaunchTooLarge;
-  const int nrt = cdiv(a.B, 16), nslab = cdiv(nrt, 2), grid_x = cdiv(a.n, 16);
-  const int per_launch = (int)std::min<long>(nslab, capacity(persist_fwd_f32_kernel<kNch>) / ((long)grid_x * a.ndir));
-  {
-    const long total = (long)nrt * a.nkc * 64;
-    for (int d = 0; d < a.ndir; ++d)
-      hipLaunchKernelGGL(init_ring_f32_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, a.d[d].ring0, a.d[d].ring1, total);
-    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  }
-  for (int slab0 = 0; slab0 < nslab; slab0 += per_launch) {
-    PFwdArgs copy = a;
-    copy.rt0 = 2 * slab0;
-    const dim3 grid(grid_x, std::min(per_launch, nslab - slab0), a.ndir);
-    void* args[] = {&copy};
-    const hipError_t e = a.plain_launch ? hipLaunchKernel((const void*)persist_fwd_f32_kernel<kNch>, grid, dim3(256), args, 0, s)
-                                        : hipLaunchCooperativeKernel((const void*)persist_fwd_f32_kernel<kNch>, grid, dim3(256), args, 0, s);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      if (slab0 == 0) return hipErrorCooperativeLaunchTooLarge;        // the first launch was refused: nothing has run
-      return e == hipErrorCooperativeLaunchTooLarge ? hipErrorLaunchFailure : e;
-    }
-  }
-  return hipSuccess;
+  const long total = (long)cdiv(a.B, 16) * a.nkc * 64;
+  for (int d = 0; d < a.ndir; ++d)
+    hipLaunchKernelGGL(init_ring_f32_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, a.d[d].ring0, a.d[d].ring1, total);
+  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+  const auto kernel = fwd_f32_for(a.n);
+  return coop_slabs(kernel, cdiv(a.n, 16), f32_rows_per_group(kernel, cdiv(a.n, 16), a.B, a.ndir), a, s);
 }
 // W_h^T for the float partial-sum backward kernel, scaled by 2^-32: float index
 // ((((dir*ntile + J)*4 + wave)*NCT + ci)*16 + s)*64 + lane holds W_h[unit (wave + 4 ci)*16 + lane%16][gate column
 // (kappa/16)*n + J*16 + kappa%16], kappa = 16 (lane/16) + s; stored so that a lane's k-steps 4 s4 .. 4 s4 + 3 are one float4:
 // float4 index ((((dir*ntile + J)*4 + wave)*NCT + ci)*4 + s4)*64 + lane.
-__global__ void pack_wh_bwd_f32p_kernel(const float* W, float* out, int n, int ntile, int nct, long total) {
+// A wavefront packs one (J, wave, ci): four lanes read the 64 consecutive bytes of a row and gate, and store 256 consecutive bytes with
+// the lanes of the other rows (one value per thread and 64 rows per load: 32 us for config 2's two directions).
+__global__ void pack_wh_bwd_f32p_kernel(const float* W, float4* out, int n, int ntile, int nct, long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= total) return;
-  const int e = idx & 3;
-  long rest = idx >> 2;
-  const int lane = rest & 63; rest >>= 6;
-  const int s4 = rest & 3; rest >>= 2;
+  const int r = (idx & 63) >> 2, s4 = idx & 3;
+  long rest = idx >> 6;
   const int ci = rest % nct; rest /= nct;
   const int wave = rest & 3; rest >>= 2;
   const int J = rest % ntile, dir = rest / ntile;
-  const int s = 4 * s4 + e, kappa = 16 * (lane >> 4) + s;
-  const int unit_in = (wave + 4 * ci) * 16 + (lane & 15), unit_out = J * 16 + (kappa & 15), q = kappa >> 4;
-  const float* Wd = W + (long)dir * n * 4 * n;
-  out[idx] = (unit_in < n && unit_out < n) ? Wd[(long)unit_in * 4 * n + q * n + unit_out] * kPartScale : 0.f;
+  const int unit_in = (wave + 4 * ci) * 16 + r, unit_out = J * 16 + 4 * s4;    // kappa = 16 q + s: gate q of unit J * 16 + s
+  const float* row = W + ((long)dir * n + min(unit_in, n - 1)) * 4 * n;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (unit_in < n && n % 4 == 0 && unit_out < n) {
+      const float4 x = *(const float4*)(row + q * n + unit_out);
+      v[0] = x.x * kPartScale; v[1] = x.y * kPartScale; v[2] = x.z * kPartScale; v[3] = x.w * kPartScale;
+    } else if (unit_in < n) {
+      for (int e = 0; e < 4; ++e)
+        if (unit_out + e < n) v[e] = row[q * n + unit_out + e] * kPartScale;
+    }
+    out[((idx >> 6) * 4 + s4) * 64 + q * 16 + r] = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
-constexpr int kBwdF32Nct = 16;
 bool persist_bwd_f32_fits(const PBwdArgs& a) {
-  if (a.n % 8 != 0 || a.n > 64 * kBwdF32Nct || a.T < 2) return false;
+  if (a.n > 1024 || a.T < 2) return false;
   const long ntile = cdiv(a.n, 16);
   if ((long)cdiv(a.B, 16) * ntile * ntile * 1024 >= 0x7ff00000L) return false;
-  return ntile * a.ndir <= capacity(persist_bwd_f32_kernel<kBwdF32Nct>);
+  return ntile * a.ndir <= capacity(bwd_f32_for(a.n));
 }
 hipError_t launch_pack_wh_bwd_f32p(const void* W, void* Wb, int n, int ndir, hipStream_t s) {
-  const int ntile = cdiv(n, 16);
-  const long total = (long)ndir * ntile * 4 * kBwdF32Nct * 16 * 64;
-  hipLaunchKernelGGL(pack_wh_bwd_f32p_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const float*)W, (float*)Wb, n, ntile, kBwdF32Nct, total);
+  const int ntile = cdiv(n, 16), nct = bwd_f32_nct(n);
+  const long total = (long)ndir * ntile * 4 * nct * 64;
+  hipLaunchKernelGGL(pack_wh_bwd_f32p_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const float*)W, (float4*)Wb, n, ntile, nct, total);
   return hipGetLastError();
 }
-// As many slabs of 32 rows per launch as the device holds at once; the rings must hold zeros.
+// (the rings must hold zeros)
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s) {
   if (!persist_bwd_f32_fits(a)) return hipErrorCooperativeLaunchTooLarge;
-  const int nrt = cdiv(a.B, 16), nslab = cdiv(nrt, 2), grid_x = cdiv(a.n, 16);
-  const int per_launch = (int)std::min<long>(nslab, capacity(persist_bwd_f32_kernel<kBwdF32Nct>) / ((long)grid_x * a.ndir));
-  for (int slab0 = 0; slab0 < nslab; slab0 += per_launch) {
-    PBwdArgs copy = a;
-    copy.rt0 = 2 * slab0;
-    const dim3 grid(grid_x, std::min(per_launch, nslab - slab0), a.ndir);
-    void* args[] = {&copy};
-    const hipError_t e = a.plain_launch ? hipLaunchKernel((const void*)persist_bwd_f32_kernel<kBwdF32Nct>, grid, dim3(256), args, 0, s)
-                                        : hipLaunchCooperativeKernel((const void*)persist_bwd_f32_kernel<kBwdF32Nct>, grid, dim3(256), args, 0, s);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      if (slab0 == 0) return hipErrorCooperativeLaunchTooLarge;        // the first launch was refused: nothing has run
-      return e == hipErrorCooperativeLaunchTooLarge ? hipErrorLaunchFailure : e;
-    }
-  }
-  return hipSuccess;
+  const auto kernel = bwd_f32_for(a.n);
+  return coop_slabs(kernel, cdiv(a.n, 16), f32_rows_per_group(kernel, cdiv(a.n, 16), a.B, a.ndir), a, s);
 }
 hipError_t launch_h0_term(const float* h0, const void* W_h, bool bf16, float* gates, long gates_stride, const int* lens, int T, int B, int n,
                           int ndir, int rev0, int rev1, hipStream_t s) {

@@ -35,6 +35,15 @@ def test_wider_layer(T, B, n_in, n, bidir):
     _layer(T, B, n_in, n, bidir, "bf16")
 
 
+@pytest.mark.parametrize("T,B,n_in,n,bidir", [
+    (5, 1, 37, 132, False), (6, 17, 30, 256, True), (4, 40, 101, 257, True), (7, 70, 33, 131, True), (3, 300, 8, 130, False),
+    (5, 33, 64, 513, True), (4, 64, 41, 1001, True), (90, 12, 30, 140, False),
+])
+def test_wider_float_layer(T, B, n_in, n, bidir):
+    """Rows in any order of length over several row tiles, widths that are no multiple of a tile or a chunk."""
+    _layer(T, B, n_in, n, bidir, "f32")
+
+
 def _layer(T, B, n_in, n, bidir, dt):
     from paper_1805_05225_amd import binding
     P.Bn = binding
