@@ -256,6 +256,44 @@ inline size_t bwdp_ring_bytes(int B, int n) {                                   
 hipError_t launch_h0_term(const float* h0, const void* W_h, bool bf16, float* gates, long gates_stride, const int* lens, int T, int B, int n,
                           int ndir, int rev0, int rev1, hipStream_t s);
 
+// Wide layers, bfloat16 (loop_block.hip): 1024 < n <= 2048, W_h in blocks over the device; one direction per launch.  h0 / c0 / hT / cT / cs / hprev,
+// dhT / dcT / dh0 / dc0 may be NULL.  ring: loop_block_ring_bytes (_bwd) bytes; xcc: a word per block; both cleared by the launch, as is *sync.
+struct BlockFwdArgs {
+  const void* W;                          // launch_pack_blocks
+  float* gates;                           // [T][B][4n]
+  const float* h0; const float* c0; float* hT; float* cT;
+  void* y; long ldy; float* cs; void* hprev; long ldh;
+  int rev;
+  const int* lens;
+  int B, n, T, write_gates;
+  char* ring; size_t ring_bytes;
+  unsigned* sync; unsigned* xcc; unsigned spin_limit;
+  bool plain_launch;
+  int row0, ni;                           // set by the launcher: first row; K ranges
+};
+struct BlockBwdArgs {
+  const void* W;                          // W_h as it lies in memory
+  const float* gates; const float* cs; const float* c0; const float* dhT; const float* dcT; float* dh0; float* dc0;
+  const void* dy; long lddy; void* DZ;
+  float* dbpart;                          // [4 ceil(B / 16)][4n] or NULL
+  int rev;
+  const int* lens;
+  int B, n, T;
+  char* ring; size_t ring_bytes;
+  unsigned* sync; unsigned* xcc; unsigned spin_limit;
+  bool plain_launch;
+  int row0;
+};
+bool loop_block_width(int n);
+bool loop_block_fits(int B, int n, long ld_out);      // does the current device hold the launch?
+size_t loop_block_ring_bytes(int n);
+size_t loop_block_ring_bytes_bwd(int n);
+size_t loop_block_wh_bytes(int n);
+hipError_t launch_pack_blocks(const void* W_h, void* out, int n, hipStream_t s);
+hipError_t launch_block_fwd(const BlockFwdArgs& a, hipStream_t s);
+hipError_t launch_block_bwd(const BlockBwdArgs& a, hipStream_t s);
+int device_capacity(const void* kernel);  // work-groups of 256 threads that the device holds at once, one per compute unit at most
+
 // Narrow layers, all of W_h on one compute unit (loop_small.hip): W_h as it lies in memory, states straight from and to the caller's arrays.
 struct SmallFwdDir {
   const void* W; float* gates; const float* h0; const float* c0; float* hT; float* cT;     // h0, c0 [B][n] or NULL (zeros); hT, cT or NULL

@@ -32,6 +32,8 @@ struct Plan {
   int ks_dwx, ks_dwh, ks_dx;                // K ranges of the weight-gradient products and of dX (few output tiles: the whole device works on them)
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool small;                               // narrow layer: loop_small.hip
+  bool blocks;                              // wide bfloat16 layer: loop_block.hip, if the device holds it
+  size_t ws_blocks;
   bool zx_tiny, dw_tiny;                    // its products by gemm_tiny.hip
   size_t ws_tiny_cnt, ws_tiny_parts;
   bool zx_nn;                               // few 256 x 256 tiles: Zx from W_x as it lies in memory (gemm_tile.hip)
@@ -100,7 +102,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up(bytes); return at; };
   // error word, per-row-tile words, then one word per work-group of a single-launch kernel (its XCD)
-  p->sync_bytes = up((64 + 2 * (size_t)p->nrt) * 4 + D * 2 * (size_t)p->nrt * cdiv(d->n, 32) * 4);
+  p->sync_bytes = up((64 + 2 * (size_t)p->nrt) * 4 + std::max(D * 2 * (size_t)p->nrt * cdiv(d->n, 32), (size_t)256) * 4);
   p->ws_sync = take(p->sync_bytes);              // first, so that lstm_sync_status() finds it without a plan
   p->Wf_bytes = D * std::max((size_t)p->ntile_f * 2 * p->nkc_f, (size_t)p->ntile16 * 4 * p->nkc_ll_f) * 1024;
   p->ws_Wf = take(p->Wf_bytes + 1024);            // packed W_h, then one chunk of zeros
@@ -185,6 +187,8 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->parts_bytes = std::max({tp, p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
                                p->ks_dx > 1 ? (size_t)p->ks_dx * TB * d->n_in * 4 : 0});
   p->ws_parts = take(p->parts_bytes);
+  p->blocks = p->bf16 && loop_block_width(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
+  p->ws_blocks = take(p->blocks ? loop_block_wh_bytes(d->n) + std::max(loop_block_ring_bytes(d->n), loop_block_ring_bytes_bwd(d->n)) : 0);
   // (one step runs as one step of LSTM_FLAG_PER_STEP does, bit for bit)
   p->small = loop_small_ok(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
   p->zx_tiny = p->small && tiny_macs(tiny_zx(*p, nullptr, nullptr, nullptr, nullptr, 0)) <= kTinyZxMacs;
@@ -407,6 +411,33 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
     HIPCHK(launch_small_fwd(a, p.bf16, s));
     return LSTM_OK;
+  }
+  if (p.blocks && loop_block_fits(p.B, p.n, (long)(D * n))) {    // a wide layer: projection, then a launch per direction and 32 rows
+    if ((rc = project())) return rc;
+    hipError_t e = hipSuccess;
+    for (size_t d = 0; d < D && e == hipSuccess; ++d) {
+      BlockFwdArgs a = {};
+      a.W = ws + p.ws_blocks; a.gates = gates + d * gates_stride;
+      a.h0 = h0 ? (const float*)h0 + d * B * n : nullptr; a.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;
+      a.hT = hT ? (float*)hT + d * B * n : nullptr; a.cT = cT ? (float*)cT + d * B * n : nullptr;
+      a.y = (char*)y + d * n * p.esz; a.ldy = (long)(D * n);
+      a.cs = c ? (float*)c + d * T * B * n : nullptr;
+      a.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev; a.ldh = p.ldh;
+      a.rev = bidir ? d == 1 : desc->direction == -1;
+      a.lens = seq_lens; a.B = p.B; a.n = p.n; a.T = p.T; a.write_gates = infer ? 0 : 1;
+      a.ring = ws + p.ws_blocks + loop_block_wh_bytes(p.n); a.ring_bytes = loop_block_ring_bytes(p.n);
+      a.sync = (unsigned*)(ws + p.ws_sync); a.xcc = a.sync + 64; a.spin_limit = kSpinLimit;
+      a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
+      {
+        Phase ph(LSTM_PHASE_PREP, 1, s);
+        HIPCHK(launch_pack_blocks((const char*)W_h + d * n * 4 * n * p.esz, ws + p.ws_blocks, p.n, s));
+      }
+      Phase ph(LSTM_PHASE_LOOP_FWD, 2, s);
+      e = launch_block_fwd(a, s);
+      if (e != hipSuccess && (d > 0 || e != hipErrorCooperativeLaunchTooLarge)) return LSTM_ERR_HIP;
+    }
+    if (e == hipSuccess) return LSTM_OK;
+    (void)hipGetLastError();               // refused before anything ran: the per-step path
   }
   {
     Phase ph(LSTM_PHASE_PREP, 5, s);
@@ -637,7 +668,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     return LSTM_OK;
   };
 
-  auto wide_loop = [&]() -> int {
+  auto split_loop = [&]() -> int {
     // single-launch path: bf16 storage, at least two steps, and the kernel fits the device
     PBwdArgs pa = {};
     pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.T = p.T; pa.ndir = p.D;
@@ -756,7 +787,37 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     }
     return LSTM_OK;
   };
-  if ((rc = p.small ? narrow_loop() : wide_loop())) return rc;
+  auto block_loop = [&]() -> int {
+    const int slices = 4 * cdiv((long)B, 16);
+    for (size_t d = 0; d < D; ++d) {
+      BlockBwdArgs a = {};
+      a.W = (const char*)W_h + d * n * 4 * n * p.esz;
+      a.gates = (const float*)(rs + d * p.res_dir_stride + p.res_gates);
+      a.cs = (const float*)c + d * T * B * n;
+      a.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;
+      a.dhT = dhT ? (const float*)dhT + d * B * n : nullptr; a.dcT = dcT ? (const float*)dcT + d * B * n : nullptr;
+      a.dh0 = dh0 ? (float*)dh0 + d * B * n : nullptr; a.dc0 = dc0 ? (float*)dc0 + d * B * n : nullptr;
+      a.dy = (const char*)dy + d * n * p.esz; a.lddy = (long)(D * n);
+      a.DZ = DZ + d * p.DZ_dir_elems * p.esz;
+      a.dbpart = slices <= kColsumSlices ? (float*)(ws + p.ws_colsum) + d * kColsumSlices * 4 * n : nullptr;
+      a.rev = bidir ? d == 1 : desc->direction == -1;
+      a.lens = seq_lens; a.B = p.B; a.n = p.n; a.T = p.T;
+      a.ring = ws + p.ws_blocks + loop_block_wh_bytes(p.n); a.ring_bytes = loop_block_ring_bytes_bwd(p.n);
+      a.sync = (unsigned*)(ws + p.ws_sync); a.xcc = a.sync + 64; a.spin_limit = kSpinLimit;
+      a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
+      Phase ph(LSTM_PHASE_LOOP_BWD, 2, s);
+      const hipError_t e = launch_block_bwd(a, s);
+      if (e == hipErrorCooperativeLaunchTooLarge && d == 0) {      // refused before anything ran
+        (void)hipGetLastError();
+        return split_loop();
+      }
+      HIPCHK(e);
+    }
+    db_slices = slices <= kColsumSlices ? slices : 0;
+    return LSTM_OK;
+  };
+
+  if ((rc = p.small ? narrow_loop() : p.blocks && loop_block_fits(p.B, p.n, (long)(D * n)) ? block_loop() : split_loop())) return rc;
 
   int* cidx = (int*)(ws + p.ws_cidx);
   int* fidx = (int*)(ws + p.ws_fidx);

@@ -30,6 +30,7 @@ def test_narrow_layer(T, B, n_in, n, bidir, dt):
 @pytest.mark.parametrize("T,B,n_in,n,bidir", [
     (4, 1, 200, 256, True), (4, 9, 64, 257, True), (5, 17, 250, 512, True), (4, 3, 500, 513, True), (3, 33, 130, 136, False),
     (60, 7, 333, 264, True),
+    (3, 1, 40, 1025, False), (5, 17, 72, 1160, False), (4, 33, 33, 1027, True), (5, 32, 64, 2048, False), (6, 20, 40, 1900, False),
 ])
 def test_wider_layer(T, B, n_in, n, bidir):
     _layer(T, B, n_in, n, bidir, "bf16")
