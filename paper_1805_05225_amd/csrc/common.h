@@ -182,10 +182,10 @@ struct PFwdDir {
   const uint4* Wzero; // one chunk (64 x 16 bytes) of zeros
   uint4* ring0; uint4* ring1;   // [row tile][nkc][64] chunks each
   float* gates;       // [T][B][4n]
-  float* hstate; float* cstate;
+  const float* h0; const float* c0; float* hT; float* cT;   // [B][n] each or NULL (zeros; not wanted)
   void* y; long ldy;  // y + column offset of this direction; frame stride B*ldy
   float* cs;          // [T][B][n] or NULL
-  void* hprev; long ldh;   // [T][B][ldh >= n] or NULL (float storage: ldh = n)
+  void* hprev; long ldh;   // [T][B][ldh >= n] or NULL
   int rev;            // 0: t = tau, 1: t = T-1-tau
 };
 struct PFwdArgs {
@@ -201,7 +201,7 @@ struct PFwdArgs {
 };
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s);
 bool persist_fwd_fits(const PFwdArgs& a);     // would launch_persist_fwd launch anything on this device?
-// Float storage (an initial hidden state goes through launch_h0_term, as for bfloat16): Wf is the per-step kernel's packed W_h (launch_pack_wh_fwd), ring0 / ring1 its
+// Float storage (an initial hidden state goes into the pre-activations, as for bfloat16): Wf is the per-step kernel's packed W_h (launch_pack_wh_fwd), ring0 / ring1 its
 // fragment-ordered h buffers (initialised here), y / hprev float; nkc = chunks of 16 k.
 hipError_t launch_persist_fwd_f32(const PFwdArgs& a, hipStream_t s);
 bool persist_fwd_f32_fits(const PFwdArgs& a);
@@ -212,7 +212,7 @@ struct PBwdDir {
   const float* gates; const float* cs; const float* c0;
   const void* dy; long lddy;
   void* DZ;           // [T][B][4n]
-  float* Dh; float* Dc;
+  const float* dhT; const float* dcT; float* dh0; float* dc0;   // [B][n] each or NULL (zeros; not wanted)
   float* dbpart;      // NULL or [2 * row tiles][4n]: slice g receives the bias gradient summed over row group g (8 rows)
   int rev;
 };
@@ -250,11 +250,10 @@ inline size_t bwdp_ring_bytes(int B, int n) {                                   
   return groups * tiles * tiles * 512;
 }
 // (launch_prep_fwd_ll: W_h in ring order; ring slot 0 = zeros carrying the tag of step 0, ring slot 1 cleared.  The initial state does
-// not travel through the ring: launch_h0_term adds its product with W_h to the pre-activations of every row's first frame instead.)
-// gates[first frame of row b][b][:] += bf16(h0[b]) . W_h for every row with a frame (forward: t = 0; reverse: t = len - 1),
-// per direction; gates [T][B][4n] float with `gates_stride` elements between directions.
-hipError_t launch_h0_term(const float* h0, const void* W_h, bool bf16, float* gates, long gates_stride, const int* lens, int T, int B, int n,
-                          int ndir, int rev0, int rev1, hipStream_t s);
+// not travel through the ring: its product with W_h is added to the pre-activations of every row's first frame instead, over operands from here.)
+// out[dir][b][0..ld) = h0[dir][b][0..n) in the storage type, then zeros; rows[dir][b] = t0 * B + b, t0 the row's first frame (reverse: len - 1).
+hipError_t launch_h0_rows(const float* h0, bool bf16, void* out, int ld, int* rows, const int* lens, int T, int B, int n, int ndir, int rev0, int rev1,
+                          hipStream_t s);
 
 // Wide layers, bfloat16 (loop_block.hip): 1024 < n <= 2048, W_h in blocks over the device; one direction per launch.  h0 / c0 / hT / cT / cs / hprev,
 // dhT / dcT / dh0 / dc0 may be NULL.  ring: loop_block_ring_bytes (_bwd) bytes; xcc: a word per block; both cleared by the launch, as is *sync.

@@ -33,7 +33,7 @@ struct Plan {
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool small;                               // narrow layer: loop_small.hip
   bool blocks;                              // wide bfloat16 layer: loop_block.hip, if the device holds it
-  size_t ws_blocks;
+  size_t ws_blocks, ws_h0, ws_h0rows;
   bool zx_tiny, dw_tiny;                    // its products by gemm_tiny.hip
   size_t ws_tiny_cnt, ws_tiny_parts;
   bool zx_nn;                               // few 256 x 256 tiles: Zx from W_x as it lies in memory (gemm_tile.hip)
@@ -182,6 +182,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
     return fg && gemm_tile_small(M, N, nz) ? gemm_tile_parts_bytes(M, N, K, nz, nseg) : (size_t)0;
   };
   size_t tp = TB > 0 && (p->zx_nn || !p->bf16) && !p->single_step ? tile_parts(TB, 4L * d->n, p->n_in8, p->D, 1, true) : 0;
+  if (TB > 0) tp = std::max(tp, tile_parts(d->B, 4L * d->n, p->ldh, 1, 1, false));      // (h0 W_h)
   if (!infer && TB > 0)
     tp = std::max({tp, tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true), tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false), tile_parts(d->n, 4L * d->n, TB, p->D, 1, false)});
   p->parts_bytes = std::max({tp, p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
@@ -189,6 +190,8 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_parts = take(p->parts_bytes);
   p->blocks = p->bf16 && loop_block_width(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
   p->ws_blocks = take(p->blocks ? loop_block_wh_bytes(d->n) + std::max(loop_block_ring_bytes(d->n), loop_block_ring_bytes_bwd(d->n)) : 0);
+  p->ws_h0 = take(D * B * p->ldh * p->esz);
+  p->ws_h0rows = take(D * B * 4);
   // (one step runs as one step of LSTM_FLAG_PER_STEP does, bit for bit)
   p->small = loop_small_ok(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
   p->zx_tiny = p->small && tiny_macs(tiny_zx(*p, nullptr, nullptr, nullptr, nullptr, 0)) <= kTinyZxMacs;
@@ -443,8 +446,6 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     Phase ph(LSTM_PHASE_PREP, 5, s);
     ZeroRegions z;
     z.add(ws + p.ws_sync, p.sync_bytes);
-    if (h0) HIPCHK(launch_copy(hstate, h0, state_bytes, s)); else z.add(hstate, state_bytes);
-    if (c0) HIPCHK(launch_copy(cstate, c0, state_bytes, s)); else z.add(cstate, state_bytes);
     if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd)
       z.add(ws + p.ws_Wf + p.Wf_bytes, 1024);              // the chunk of zeros behind the packed W_h (single-launch path)
     // (on the single-launch path the fills, the packed W_h and the initial ring are one launch)
@@ -460,103 +461,91 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   }
   // single-launch path: bf16 storage, at least two steps, register budget of the kernel
   bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd;
-  auto pack_fwd = [&]() -> int {            // the per-step kernels' order (also what a single-launch path that does not start falls back to)
-    Phase ph(LSTM_PHASE_PREP, 2, s);
+  // what the per-step kernels work on (also what a single-launch path that does not start falls back to)
+  auto pack_w = [&]() -> int {
+    Phase ph(LSTM_PHASE_PREP, 1, s);
     HIPCHK(launch_pack_wh_fwd(W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_f, p.D, p.bf16, s));
-    HIPCHK(launch_pack_state(hstate, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1), p.B, p.n, p.nkc_f, p.nrt,
-                             p.D, p.bf16, s));
     return LSTM_OK;
   };
-  if (T > 0 && !use_ll) {
-    if ((rc = pack_fwd())) return rc;
+  auto state_in = [&]() -> int {
+    Phase ph(LSTM_PHASE_PREP, 3, s);
+    if (h0) HIPCHK(launch_copy(hstate, h0, state_bytes, s)); else HIPCHK(launch_fill_zero(hstate, state_bytes, s));
+    if (c0) HIPCHK(launch_copy(cstate, c0, state_bytes, s)); else HIPCHK(launch_fill_zero(cstate, state_bytes, s));
+    if (T > 0)
+      HIPCHK(launch_pack_state(hstate, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1), p.B, p.n, p.nkc_f, p.nrt, p.D, p.bf16, s));
+    return LSTM_OK;
+  };
+  // The initial state does not travel through the exchange rings (what does must keep |h| <= 1): its product with W_h goes into the
+  // pre-activations of every row's first frame, and the kernels start from zeros in the ring.  (B rows, but W_h is read once
+  // for all of them: a kernel with a thread per column and row took 270 us for 32 rows of 1024 units.)
+  auto h0_term = [&](const PFwdArgs& pa) -> int {
+    Phase ph(LSTM_PHASE_PREP, 1 + p.D, s);
+    int* rows = (int*)(ws + p.ws_h0rows);
+    HIPCHK(launch_h0_rows((const float*)h0, p.bf16, ws + p.ws_h0, (int)p.ldh, rows, seq_lens, p.T, p.B, p.n, p.D, pa.d[0].rev, pa.d[D - 1].rev, s));
+    for (size_t d = 0; d < D; ++d) {
+      GemmArgs g = {};
+      g.A = ws + p.ws_h0 + d * B * p.ldh * p.esz; g.B = (const char*)W_h + d * n * 4 * n * p.esz; g.C = gates + d * gates_stride;
+      g.M = p.B; g.N = 4 * p.n; g.K = (int)p.ldh; g.lda = p.ldh; g.ldb = 4 * n; g.ldc = 4 * n; g.nz = 1; g.nseg = 1;
+      g.a_kcontig = true; g.in_bf16 = p.bf16; g.accumulate = 1; g.c_rows = rows + d * B; g.k_phys_rows = p.n;
+      g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
+      if (!(p.bf16 ? gemm_tile_ok(g) : gemm_float_ok(g))) { g.K = p.n; g.k_phys_rows = 0; g.parts = nullptr; }
+      g.vecA = widest(g.lda, 0, 0, p.esz, 16);
+      g.vecB = widest(g.ldb, 0, 0, p.esz, 4);
+      HIPCHK(launch_gemm(g, s));
+    }
+    return LSTM_OK;
+  };
+  bool done = false;
+  auto set_dirs = [&](PFwdArgs& pa, const char* Wf, size_t wf_dir, size_t frag_dir) {
+    pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.T = p.T; pa.ndir = p.D; pa.write_gates = infer ? 0 : 1;
+    pa.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
+    pa.sync = (unsigned*)(ws + p.ws_sync); pa.spin_limit = kSpinLimit;
+    pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
+    for (size_t d = 0; d < D; ++d) {
+      PFwdDir& fd = pa.d[d];
+      fd.Wf = (const uint4*)(Wf + d * wf_dir);
+      fd.Wzero = (const uint4*)(ws + p.ws_Wf + p.Wf_bytes);
+      fd.ring0 = (uint4*)(ws + p.ws_hfrag0 + d * frag_dir);
+      fd.ring1 = (uint4*)(ws + p.ws_hfrag1 + d * frag_dir);
+      fd.gates = gates + d * gates_stride;
+      fd.h0 = h0 ? (const float*)h0 + d * B * n : nullptr; fd.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;
+      fd.hT = hT ? (float*)hT + d * B * n : nullptr; fd.cT = cT ? (float*)cT + d * B * n : nullptr;
+      fd.y = (char*)y + d * n * p.esz;
+      fd.ldy = (long)(D * n);
+      fd.cs = c ? (float*)c + d * T * B * n : nullptr;
+      fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev;
+      fd.ldh = p.ldh;
+      fd.rev = bidir ? d == 1 : desc->direction == -1;
+    }
+  };
+  PFwdArgs pa = {};                      // the single-launch kernels' arguments, if one of them takes this problem
+  if (use_ll) {
+    pa.nkc = p.nkc_ll_f;
+    set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile16 * 4 * p.nkc_ll_f * 1024, (size_t)p.nrt * p.nkc_ll_f * 1024);
+  } else {
+    pa.nkc = p.nkc_f;                    // (float storage: the per-step kernels' packed W_h and h buffers)
+    set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile_f * 2 * p.nkc_f * 1024, (size_t)p.nrt * p.nkc_f * 1024);
   }
+  const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_fwd_f32_fits(pa);
+  const bool single = use_ll ? persist_fwd_fits(pa) : use_ll32;
+  if (T > 0 && (!use_ll || !single) && (rc = pack_w())) return rc;
+  if (!single && (rc = state_in())) return rc;
   if (T > 0) {
     if ((rc = project())) return rc;
-
-    bool done = false;
-    if (use_ll) {
-      PFwdArgs pa = {};
-      pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.nkc = p.nkc_ll_f; pa.T = p.T; pa.ndir = p.D; pa.write_gates = infer ? 0 : 1;
-      pa.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
-      pa.sync = (unsigned*)(ws + p.ws_sync); pa.spin_limit = kSpinLimit;
-      pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
-      const size_t frag_dir = (size_t)p.nrt * p.nkc_ll_f * 1024;
-      for (size_t d = 0; d < D; ++d) {
-        PFwdDir& fd = pa.d[d];
-        fd.Wf = (const uint4*)(ws + p.ws_Wf + d * (size_t)p.ntile16 * 4 * p.nkc_ll_f * 1024);
-        fd.Wzero = (const uint4*)(ws + p.ws_Wf + p.Wf_bytes);
-        fd.ring0 = (uint4*)(ws + p.ws_hfrag0 + d * frag_dir);
-        fd.ring1 = (uint4*)(ws + p.ws_hfrag1 + d * frag_dir);
-        fd.gates = gates + d * gates_stride;
-        fd.hstate = hstate + d * B * n;
-        fd.cstate = cstate + d * B * n;
-        fd.y = (char*)y + d * n * p.esz;
-        fd.ldy = (long)(D * n);
-        fd.cs = c ? (float*)c + d * T * B * n : nullptr;
-        fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev;
-        fd.ldh = p.ldh;
-        fd.rev = bidir ? d == 1 : desc->direction == -1;
-      }
-      hipError_t e = hipErrorCooperativeLaunchTooLarge;
-      if (persist_fwd_fits(pa)) {
-        // The initial state does not travel through the exchange ring (what does must keep |h| <= 1): its product with W_h
-        // goes into the pre-activations of every row's first frame, and the kernels start from zeros in the ring.
-        if (h0) {
-          Phase ph(LSTM_PHASE_PREP, 1, s);
-          HIPCHK(launch_h0_term((const float*)h0, W_h, true, gates, gates_stride, seq_lens, p.T, p.B, p.n, p.D, pa.d[0].rev, pa.d[D - 1].rev, s));
-        }
+    if (single) {
+      if (h0 && (rc = h0_term(pa))) return rc;
+      hipError_t e;
+      {
         Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
-        e = launch_persist_fwd(pa, s);
-        if (e == hipErrorCooperativeLaunchTooLarge && h0) e = hipErrorLaunchFailure;   // the pre-activations are no longer what the per-step path expects
+        e = use_ll ? launch_persist_fwd(pa, s) : launch_persist_fwd_f32(pa, s);
       }
+      if (e == hipErrorCooperativeLaunchTooLarge && h0) e = hipErrorLaunchFailure;   // the pre-activations are no longer what the per-step path expects
       if (e == hipSuccess) done = true;
       else if (e == hipErrorCooperativeLaunchTooLarge) {   // nothing was launched (does not fit on the device all at once): one launch per step
         (void)hipGetLastError();
-        if ((rc = pack_fwd())) return rc;
+        if (use_ll && (rc = pack_w())) return rc;
+        if ((rc = state_in())) return rc;
       } else {                                      // a later batch slab failed after earlier ones ran: no second attempt on advanced state
-        (void)hipGetLastError();
-        return LSTM_ERR_HIP;
-      }
-    }
-    // float storage: one launch for the whole time loop as well (the kernel works on the per-step path's packed W_h and
-    // h buffers)
-    if (!done && !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2) {
-      PFwdArgs pa = {};
-      pa.lens = seq_lens; pa.B = p.B; pa.n = p.n; pa.nkc = p.nkc_f; pa.T = p.T; pa.ndir = p.D; pa.write_gates = infer ? 0 : 1;
-      pa.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
-      pa.sync = (unsigned*)(ws + p.ws_sync); pa.spin_limit = kSpinLimit;
-      pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
-      const size_t frag_dir = (size_t)p.nrt * p.nkc_f * 1024;
-      for (size_t d = 0; d < D; ++d) {
-        PFwdDir& fd = pa.d[d];
-        fd.Wf = (const uint4*)(ws + p.ws_Wf + d * (size_t)p.ntile_f * 2 * p.nkc_f * 1024);
-        fd.ring0 = (uint4*)(ws + p.ws_hfrag0 + d * frag_dir);
-        fd.ring1 = (uint4*)(ws + p.ws_hfrag1 + d * frag_dir);
-        fd.gates = gates + d * gates_stride;
-        fd.hstate = hstate + d * B * n;
-        fd.cstate = cstate + d * B * n;
-        fd.y = (char*)y + d * n * p.esz;
-        fd.ldy = (long)(D * n);
-        fd.cs = c ? (float*)c + d * T * B * n : nullptr;
-        fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev;
-        fd.ldh = p.ldh;
-        fd.rev = bidir ? d == 1 : desc->direction == -1;
-      }
-      hipError_t e = hipErrorCooperativeLaunchTooLarge;
-      if (persist_fwd_f32_fits(pa)) {
-        if (h0) {   // (as on the bfloat16 path: the initial state enters through the pre-activations of every row's first frame)
-          Phase ph(LSTM_PHASE_PREP, 1, s);
-          HIPCHK(launch_h0_term((const float*)h0, W_h, false, gates, gates_stride, seq_lens, p.T, p.B, p.n, p.D, pa.d[0].rev, pa.d[D - 1].rev, s));
-        }
-        Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
-        e = launch_persist_fwd_f32(pa, s);
-        if (e == hipErrorCooperativeLaunchTooLarge && h0) e = hipErrorLaunchFailure;   // the pre-activations are no longer what the per-step path expects
-      }
-      if (e == hipSuccess) done = true;
-      else if (e == hipErrorCooperativeLaunchTooLarge) {   // nothing of the loop ran, but the h buffers may have been initialised for it
-        (void)hipGetLastError();
-        if ((rc = pack_fwd())) return rc;
-      } else {
         (void)hipGetLastError();
         return LSTM_ERR_HIP;
       }
@@ -588,6 +577,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     }
     }
   }
+  if (done) return LSTM_OK;
   Phase ph(LSTM_PHASE_PREP, 2, s);
   if (hT) HIPCHK(launch_copy(hT, hstate, state_bytes, s));
   if (cT) HIPCHK(launch_copy(cT, cstate, state_bytes, s));
@@ -683,8 +673,6 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       Phase ph(LSTM_PHASE_PREP, 5, s);
       ZeroRegions z;
       z.add(ws + p.ws_sync, p.sync_bytes);
-      if (dhT) HIPCHK(launch_copy(Dh, dhT, state_bytes, s)); else z.add(Dh, state_bytes);
-      if (dcT) HIPCHK(launch_copy(Dc, dcT, state_bytes, s)); else z.add(Dc, state_bytes);
       z.add(ws + p.ws_dzfrag0, p.dzfrag_bytes);
       z.add(ws + p.ws_dzfrag1, p.dzfrag_bytes);
       if (2 * p.nrt <= kColsumSlices) z.add(ws + p.ws_colsum, D * kColsumSlices * 4 * n * 4);   // bias-gradient slices of row groups the grid lacks
@@ -725,8 +713,8 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         bd.dy = (const char*)dy + d * n * p.esz;
         bd.lddy = (long)(D * n);
         bd.DZ = DZ + d * p.DZ_dir_elems * p.esz;
-        bd.Dh = Dh + d * B * n;
-        bd.Dc = Dc + d * B * n;
+        bd.dhT = dhT ? (const float*)dhT + d * B * n : nullptr; bd.dcT = dcT ? (const float*)dcT + d * B * n : nullptr;
+        bd.dh0 = dh0 ? (float*)dh0 + d * B * n : nullptr; bd.dc0 = dc0 ? (float*)dc0 + d * B * n : nullptr;
         bd.dbpart = db_in_loop ? (float*)(ws + p.ws_colsum) + d * kColsumSlices * 4 * n : nullptr;
         bd.rev = bidir ? d == 1 : desc->direction == -1;
       }
@@ -750,7 +738,13 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     }
     BwdArgs a = {};
     a.lens = seq_lens; a.B = p.B; a.n = p.n; a.nkc = p.nkc_b; a.T = p.T; a.ndir = p.D;
-    if (!done) {
+    if (done) return LSTM_OK;
+    {
+      Phase ph(LSTM_PHASE_PREP, 2, s);
+      if (dhT) HIPCHK(launch_copy(Dh, dhT, state_bytes, s)); else HIPCHK(launch_fill_zero(Dh, state_bytes, s));
+      if (dcT) HIPCHK(launch_copy(Dc, dcT, state_bytes, s)); else HIPCHK(launch_fill_zero(Dc, state_bytes, s));
+    }
+    {
     Phase ph(LSTM_PHASE_LOOP_BWD, (long)T + 1, s);
     for (long tau = (long)T - 1; tau >= -1; --tau) {
       a.do_matmul = tau < (long)T - 1;

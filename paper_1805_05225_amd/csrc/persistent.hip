@@ -337,8 +337,8 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   float c = 0.f, h = 0.f;
   int L = 0;
   if (active) {
-    c = d.cstate[(long)b * n + j];
-    h = d.hstate[(long)b * n + j];
+    if (d.c0) c = d.c0[(long)b * n + j];
+    if (d.h0) h = d.h0[(long)b * n + j];
     L = clamp_len(a.lens, b, T);
   }
   // The unit this thread publishes.  A unit is four consecutive units' h of one row (the tag is a bit of the fourth), and a
@@ -582,8 +582,8 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   }
   PROF_DUMP("fwd8", T)
   if (active) {
-    d.cstate[(long)b * n + j] = c;
-    d.hstate[(long)b * n + j] = h;
+    if (d.cT) d.cT[(long)b * n + j] = c;
+    if (d.hT) d.hT[(long)b * n + j] = h;
   }
 }
 
@@ -645,8 +645,8 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
     const int b = rt * 16 + r8 + 8 * k;
     active[k] = b < B && j < n;
     if (active[k]) {
-      c[k] = d.cstate[(long)b * n + j];
-      h[k] = d.hstate[(long)b * n + j];
+      if (d.c0) c[k] = d.c0[(long)b * n + j];
+      if (d.h0) h[k] = d.h0[(long)b * n + j];
       L[k] = clamp_len(a.lens, b, T);
     }
   }
@@ -933,8 +933,8 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   for (int k = 0; k < 2; ++k) {
     const int b = rt * 16 + r8 + 8 * k;
     if (active[k]) {
-      d.cstate[(long)b * n + j] = c[k];
-      d.hstate[(long)b * n + j] = h[k];
+      if (d.cT) d.cT[(long)b * n + j] = c[k];
+      if (d.hT) d.hT[(long)b * n + j] = h[k];
     }
   }
 }
@@ -994,8 +994,8 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   float dbsum[4] = {0.f, 0.f, 0.f, 0.f};
   int L = 0;
   if (active) {
-    Dh = d.Dh[(long)b * n + j];
-    Dc = d.Dc[(long)b * n + j];
+    if (d.dhT) Dh = d.dhT[(long)b * n + j];
+    if (d.dcT) Dc = d.dcT[(long)b * n + j];
     L = clamp_len(a.lens, b, T);
   }
   // What the gate gradients of one frame need.  dy stays as the 16 bits that were loaded: a conversion right behind
@@ -1296,8 +1296,8 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   }
   PROF_DUMP("bwdp", T)
   if (active) {
-    d.Dh[(long)b * n + j] = Dh;
-    d.Dc[(long)b * n + j] = Dc;
+    if (d.dh0) d.dh0[(long)b * n + j] = Dh;
+    if (d.dc0) d.dc0[(long)b * n + j] = Dc;
   }
   if (d.dbpart) {                       // bias gradient: sum this work-group's 8 rows, one slice per row group
     __shared__ float dbred[8][129];
@@ -1353,8 +1353,8 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
     active[k] = b < B && j < n;
     Dh[k] = 0.f; Dc[k] = 0.f; L[k] = 0;
     if (active[k]) {
-      Dh[k] = d.Dh[(long)b * n + j];
-      Dc[k] = d.Dc[(long)b * n + j];
+      if (d.dhT) Dh[k] = d.dhT[(long)b * n + j];
+      if (d.dcT) Dc[k] = d.dcT[(long)b * n + j];
       L[k] = clamp_len(a.lens, b, T);
     }
   }
@@ -1685,8 +1685,8 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
 #pragma unroll
   for (int k = 0; k < 2; ++k)
     if (active[k]) {
-      d.Dh[(long)(b0 + 8 * k) * n + j] = Dh[k];
-      d.Dc[(long)(b0 + 8 * k) * n + j] = Dc[k];
+      if (d.dh0) d.dh0[(long)(b0 + 8 * k) * n + j] = Dh[k];
+      if (d.dc0) d.dc0[(long)(b0 + 8 * k) * n + j] = Dc[k];
     }
   if (d.dbpart) {                       // bias gradient: sum this work-group's 16 rows into the first of its two slices (the other stays zero)
     __shared__ float dbred[8][129];
@@ -1721,7 +1721,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
 // bfloat16 value in the other kernels).  The ring is the per-step kernel's fragment-ordered h buffer [row tile][chunk][lane]
 // x 16 bytes, a lane's 16 bytes being two such units, so the reader of the other kernels applies unchanged.  An initial
 // hidden state never enters the ring (it is not bounded by 1): rows publish zeros until their first frame is done, and
-// launch_h0_term has added h0 W_h to that frame's pre-activations.
+// h0 W_h has been added to that frame's pre-activations.
 // Rows are dealt to row tiles by falling length, and a slab is a long tile together with a short one: a row tile leaves its
 // loop (reversed: enters it) at its longest row's last frame - every work-group of the exchange group knows it from the lengths - and its
 // half of every step beyond that costs nothing but the stores of padding.  (Config 2, rows of 10 - 50 frames in any order: the four tiles
@@ -1804,15 +1804,15 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
   int L[2] = {0, 0};
   bool active[2];
   // A row publishes zeros until its first frame has been processed: its initial hidden state (not bounded by 1, so not
-  // fit for the ring) reaches that frame through the pre-activations instead (launch_h0_term).
+  // fit for the ring) reaches that frame through the pre-activations instead.
   bool started[2] = {false, false};
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int b = rows.row[k];
     active[k] = b >= 0 && j < n;
     if (active[k]) {
-      c[k] = d.cstate[(long)b * n + j];
-      h[k] = d.hstate[(long)b * n + j];
+      if (d.c0) c[k] = d.c0[(long)b * n + j];
+      if (d.h0) h[k] = d.h0[(long)b * n + j];
       L[k] = clamp_len(a.lens, b, T);
     }
   }
@@ -1943,8 +1943,8 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
   for (int k = 0; k < 2; ++k)
     if (active[k]) {
       const int b = rows.row[k];
-      d.cstate[(long)b * n + j] = c[k];
-      d.hstate[(long)b * n + j] = h[k];
+      if (d.cT) d.cT[(long)b * n + j] = c[k];
+      if (d.hT) d.hT[(long)b * n + j] = h[k];
     }
 }
 
@@ -2004,8 +2004,8 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
     const int b = rows.row[k];
     active[k] = b >= 0 && j < n;
     if (active[k]) {
-      Dh[k] = d.Dh[(long)b * n + j];
-      Dc[k] = d.Dc[(long)b * n + j];
+      if (d.dhT) Dh[k] = d.dhT[(long)b * n + j];
+      if (d.dcT) Dc[k] = d.dcT[(long)b * n + j];
       L[k] = clamp_len(a.lens, b, T);
     }
   }
@@ -2188,8 +2188,8 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   for (int k = 0; k < 2; ++k)
     if (active[k]) {
       const int b = rows.row[k];
-      d.Dh[(long)b * n + j] = Dh[k];
-      d.Dc[(long)b * n + j] = Dc[k];
+      if (d.dh0) d.dh0[(long)b * n + j] = Dh[k];
+      if (d.dc0) d.dc0[(long)b * n + j] = Dc[k];
     }
   if (d.dbpart) {                       // bias gradient: this work-group's rows summed into the first slice of its first row tile (the others stay zero)
     __syncthreads();
@@ -2287,21 +2287,20 @@ __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
     frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.cidx, a.fidx, a.count);
   }
 }
-// The initial state's share of the first frame: gates[t0(b)][b][col] += sum_k bf16(h0[b][k]) W_h[k][col], t0 = the row's
-// first frame in processing order.  One thread per column, a row per blockIdx.y; W_h rows are read coalesced.  Runs only
-// when the caller passes an initial state.
-template <typename TW>                                     // bfloat16 storage: h0 rounded as the recurrence would feed it
-__global__ __launch_bounds__(256) void h0_term_kernel(const float* h0, const TW* W, float* gates, long gates_stride, const int* lens,
-                                                      int T, int B, int n, int rev0, int rev1) {
-  const int col = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y, dir = blockIdx.z;
-  const int L = clamp_len(lens, b, T);
-  if (col >= 4 * n || L <= 0) return;
-  const float* hb = h0 + ((long)dir * B + b) * n;
-  const TW* Wd = W + (long)dir * n * 4 * n + col;
-  float acc = 0.f;
-  for (int k = 0; k < n; ++k) acc += (sizeof(TW) == 2 ? bf_bits2f(f2bf_bits(hb[k])) : hb[k]) * (float)Wd[(long)k * 4 * n];
-  const int t0 = (dir == 0 ? rev0 : rev1) ? L - 1 : 0;
-  gates[dir * gates_stride + ((long)t0 * B + b) * 4 * n + col] += acc;
+// The initial state as the left operand of its product with W_h: rows of `ld` elements, rounded to the storage type as the recurrence
+// would feed it and padded with zeros; rows[dir][b] = the frame and row whose pre-activations it goes into (a row without frames: one that nobody reads).
+template <typename TW>
+__global__ __launch_bounds__(256) void h0_rows_kernel(const float* h0, TW* out, int ld, int* rows, const int* lens, int T, int B, int n, int rev0, int rev1) {
+  const int k = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y, dir = blockIdx.z;
+  if (k == 0) {
+    const int L = clamp_len(lens, b, T);
+    rows[dir * B + b] = ((dir == 0 ? rev0 : rev1) && L > 0 ? L - 1 : 0) * B + b;
+  }
+  if (k >= ld) return;
+  const float v = k < n ? h0[((long)dir * B + b) * n + k] : 0.f;
+  const long o = ((long)dir * B + b) * ld + k;
+  if constexpr (sizeof(TW) == 2) ((uint16_t*)out)[o] = f2bf_bits(v);
+  else out[o] = v;
 }
 
 std::mutex g_capacity_mu;
@@ -2531,12 +2530,11 @@ hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s) {
   const auto kernel = bwd_f32_for(a.n);
   return coop_slabs(kernel, cdiv(a.n, 16), f32_rows_per_group(kernel, cdiv(a.n, 16), a.B, a.ndir), a, s);
 }
-hipError_t launch_h0_term(const float* h0, const void* W_h, bool bf16, float* gates, long gates_stride, const int* lens, int T, int B, int n,
-                          int ndir, int rev0, int rev1, hipStream_t s) {
-  if (B <= 0 || T <= 0) return hipSuccess;
-  const dim3 grid(cdiv(4L * n, 256), B, ndir);
-  if (bf16) hipLaunchKernelGGL(h0_term_kernel<bf16_t>, grid, dim3(256), 0, s, h0, (const bf16_t*)W_h, gates, gates_stride, lens, T, B, n, rev0, rev1);
-  else hipLaunchKernelGGL(h0_term_kernel<float>, grid, dim3(256), 0, s, h0, (const float*)W_h, gates, gates_stride, lens, T, B, n, rev0, rev1);
+hipError_t launch_h0_rows(const float* h0, bool bf16, void* out, int ld, int* rows, const int* lens, int T, int B, int n, int ndir, int rev0, int rev1,
+                          hipStream_t s) {
+  const dim3 grid(cdiv(ld, 256), B, ndir);
+  if (bf16) hipLaunchKernelGGL(h0_rows_kernel<bf16_t>, grid, dim3(256), 0, s, h0, (bf16_t*)out, ld, rows, lens, T, B, n, rev0, rev1);
+  else hipLaunchKernelGGL(h0_rows_kernel<float>, grid, dim3(256), 0, s, h0, (float*)out, ld, rows, lens, T, B, n, rev0, rev1);
   return hipGetLastError();
 }
 
