@@ -2228,25 +2228,29 @@ __device__ __forceinline__ void pack_wh_fwd_ll_body(long idx, const bf16_t* W, u
   out[idx] = *(uint4*)v;
 }
 // partial-sum backward kernel: chunk index = ((((dir*ntile2 + J)*4 + wave)*4 + kc)*nct + c)*64 + lane ; B fragment of
-// gate kc, K = the 32 units of tile J, columns = outputs (wave*nct + c)*16 .. +15
+// gate kc, K = the 32 units of tile J, columns = outputs (wave*nct + c)*16 .. +15: eight consecutive units of a row of W_h.
+// (16-byte reads: the set-up of config 3's backward loops, with its fills, 27 -> 17 us.)  Scaled by 2^-32, exactly: the partial sums of Dh leave the MFMAs scaled, which keeps a bit of their bf16 form free.
 __device__ __forceinline__ void pack_wh_bwdp_body(long idx, const bf16_t* W, uint4* out, int n, int ntile2, int nct, long total) {
   if (idx >= total) return;
-  const int lane = idx & 63;
+  const int lane = idx & 63, g = lane & 3, col = lane >> 2;  // (four neighbouring threads read 64 consecutive bytes)
   long rest = idx >> 6;
   const int c = rest % nct; rest /= nct;
   const int kc = rest & 3, wave = (rest >> 2) & 3;
   rest >>= 4;
   const int J = rest % ntile2, dir = rest / ntile2;
-  const int jout = (wave * nct + c) * 16 + (lane & 15), g = lane >> 4;
-  const bf16_t* Wd = W + (long)dir * n * 4 * n;
-  bf16_t v[8];
+  const int jout = (wave * nct + c) * 16 + col, u0 = J * 32 + g * 8;
+  const uint16_t* p = (const uint16_t*)W + ((long)dir * n + min(jout, n - 1)) * 4 * n + kc * n;
+  unsigned v[8];
+  if (n % 8 == 0) {
+    const uint4 x = *(const uint4*)(p + min(u0, n - 8));
+    v[0] = x.x & 0xffffu; v[1] = x.x >> 16; v[2] = x.y & 0xffffu; v[3] = x.y >> 16; v[4] = x.z & 0xffffu; v[5] = x.z >> 16; v[6] = x.w & 0xffffu; v[7] = x.w >> 16;
+  } else {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int unit = J * 32 + g * 8 + e;
-    // (scaled by 2^-32, exactly: the partial sums of Dh leave the MFMAs scaled, which keeps a bit of their bf16 form free)
-    v[e] = (jout < n && unit < n) ? (bf16_t)((float)Wd[(long)jout * 4 * n + kc * n + unit] * kPartScale) : (bf16_t)0.f;
+    for (int e = 0; e < 8; ++e) v[e] = p[min(u0 + e, n - 1)];
   }
-  out[idx] = *(uint4*)v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = jout < n && u0 + e < n ? f2bf_bits(bf_bits2f((uint16_t)v[e]) * kPartScale) : 0u;
+  out[(idx & ~63l) + g * 16 + col] = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
 }
 // Initial contents of the forward ring, one 8-byte unit per thread: slot 0 = zeros that carry the tag of step 0, slot 1 = zeros.
 __device__ __forceinline__ void pack_state_ll_body(long idx, uint4* ring0, uint4* ring1, long total) {
