@@ -95,17 +95,11 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s);
 constexpr int kSkinnyMaxRows = 1024;
 bool gemm_skinny_ok(const GemmArgs& g);
 hipError_t launch_gemm_skinny(const GemmArgs& g, bool relu, hipStream_t s);
-// dst[c][r] = src[r][c] (16-bit elements), r < R, c < C, dst rows zero-padded up to ld_dst; nz problems with
-// strides s_src / s_dst.  lens != NULL: rows of src are frames (t = r / Bt, b = r % Bt) and are read as zero
-// unless t < lens[b].  With cidx / fidx / count from launch_frame_map the kept frames are packed instead: column
-// cidx[r] receives row r, padded frames are dropped, and columns count[0] .. count[1]-1 are zeroed (ld_dst must
-// then be a multiple of 64).
-hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst,
-                            const int* lens, int Bt, int T, hipStream_t s, const int* cidx = nullptr, const int* fidx = nullptr,
-                            const int* count = nullptr);
-// Numbers the frames (t, b) with t < lens[b] in (t, b) order: cidx[T*B] frame -> number or -1, fidx[number] -> frame,
-// count[0] = how many, count[1] = that rounded up to a multiple of 64.
-hipError_t launch_frame_map(const int* lens, int T, int B, int* cidx, int* fidx, int* count, hipStream_t s);
+// dst[c][r] = src[r][c] (16-bit elements), r < R, c < C, dst rows zero-padded up to ld_dst; nz problems with strides s_src / s_dst.
+hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst, hipStream_t s);
+// Numbers the frames (t, b) with t < lens[b] in (t, b) order: fidx[number] -> frame, count[0] = how many, count[1] = that rounded up
+// to a multiple of 64.
+hipError_t launch_frame_map(const int* lens, int T, int B, int* fidx, int* count, hipStream_t s);
 // dst[r][0..ld_dst) = src[r][0..C) followed by zeros (16-bit elements)
 hipError_t launch_pad_rows(const void* src, void* dst, long R, int C, int ld_dst, hipStream_t s);
 
@@ -232,7 +226,7 @@ struct PBwdArgs {
 bool persist_bwd_fits(const PBwdArgs& a);
 hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s);
 // Float storage: the same exchange of partial sums in float.  W_h^T via launch_pack_wh_bwd_f32p (bwd_f32_wh_bytes per
-// direction), rings of bwd_f32_ring_bytes per direction and slot, zero-filled; gates, cs, dy, DZ float; dbpart unused.
+// direction), rings of bwd_f32_ring_bytes per direction and slot, zero-filled; gates, cs, dy, DZ float.
 bool persist_bwd_f32_fits(const PBwdArgs& a);
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s);
 hipError_t launch_pack_wh_bwd_f32p(const void* W_h, void* Wb, int n, int ndir, hipStream_t s);
@@ -365,8 +359,8 @@ struct ZeroRegions {
 };
 hipError_t launch_fill_zero_many(const ZeroRegions& r, hipStream_t s);
 // The set-up of a bfloat16 single-launch loop in one launch: the fills of `z`, W_h in the kernel's order, (forward) the initial
-// ring, and the frame map of launch_frame_map if fm.cidx is not NULL.
-struct FrameMapArgs { const int* lens; int T, B; int* cidx; int* fidx; int* count; };
+// ring, and the frame map of launch_frame_map if fm.fidx is not NULL.
+struct FrameMapArgs { const int* lens; int T, B; int* fidx; int* count; };
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, uint4* ring0, uint4* ring1,
                               int nrt, const FrameMapArgs& fm, hipStream_t s);
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s);

@@ -250,12 +250,18 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
   float* C = to_parts ? g.parts + ((long)z * ksplit + ks) * g.M * g.ldp : g.C + g.sCz * z;
   const long ldc = to_parts ? g.ldp : g.ldc;
   const float* bias = (g.bias && !to_parts) ? g.bias + g.sbiasz * z : nullptr;
-  const bool vec_ok = (ldc % 4 == 0) && (((uintptr_t)C & 15u) == 0);
+  const bool vec_ok = (ldc % 4 == 0) && (((uintptr_t)C & 15u) == 0), add = g.accumulate && !to_parts;
+  int crow[4];                                                   // (looked up before the first store)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = min(m0 + wm * 64 + i * 16 + i16, M - 1);
+    crow[i] = (g.c_rows && !to_parts) ? g.c_rows[row] : row;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = m0 + wm * 64 + i * 16 + i16;
     if (row >= M) continue;
-    const long prow = (g.c_rows && !to_parts) ? g.c_rows[row] : row;
+    const long prow = crow[i];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int col = n0 + wn * 64 + j * 16 + 4 * q;
@@ -267,17 +273,15 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
         for (int v = 0; v < 4; ++v)
           if (col + v < g.N) e[v] += bias[col + v];
       }
-      if (vec_ok && col + 3 < g.N) {
-        float4 o = make_float4(e[0], e[1], e[2], e[3]);
-        if (g.accumulate && !to_parts) {
-          const float4 old = *(const float4*)p;
-          o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w;
-        }
-        *(float4*)p = o;
+      const bool whole = vec_ok && col + 3 < g.N;
+      if (whole && !add) *(float4*)p = make_float4(e[0], e[1], e[2], e[3]);      // (by itself: joined with the read below, every store waits for the one before)
+      else if (whole) {
+        const float4 old = *(const float4*)p;
+        *(float4*)p = make_float4(old.x + e[0], old.y + e[1], old.z + e[2], old.w + e[3]);
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (col + v < g.N) p[v] = (g.accumulate && !to_parts) ? p[v] + e[v] : e[v];
+          if (col + v < g.N) p[v] = add ? p[v] + e[v] : e[v];
       }
     }
   }

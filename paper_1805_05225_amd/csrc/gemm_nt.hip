@@ -1,15 +1,11 @@
 // Fast path of the hoisted matrix products for bfloat16 storage.
 //
-// All four products of a layer (Zx = X W_x + b, dX = DZ W_x^T, dW_x = X^T DZ, dW_h = Hprev^T DZ;
-// paper Sec. 3: work moved out of the recurrent loop) are brought into ONE shape,
+// gemm_dl8_* (operands loaded straight into LDS, eight wavefronts; described where it is defined):
 //     C[M,N] (+)= sum_seg A_seg[M,K] . B_seg[N,K]^T  (+ bias[N]),
-// with both operands k-contiguous, rows 16-byte aligned and K a multiple of 8.  Operands that are
-// stored the other way round (W_x for Zx; X, Hprev and DZ for the weight gradients) are transposed
-// once by `launch_transpose` below - a bandwidth-bound pass that costs a few percent of the product
-// it feeds - instead of being transposed on the fly inside the MFMA loop.
-//
-// gemm_dl8_* (operands loaded straight into LDS, eight wavefronts; described where it is defined) serves every K that
-// is a multiple of 8; gemm_tn8_f32 serves the k-major operand pair of the weight gradients.
+// both operands k-contiguous, rows 16-byte aligned, K a multiple of 8: Zx = X W_x + b (W_x transposed once by `launch_transpose`, a pass that
+// costs a few percent of the product) and dX = DZ W_x^T of long batches.
+// gemm_tn8_f32: the k-major operand pair of the weight gradients dW_x = X^T DZ, dW_h = Hprev^T DZ.
+// Products with fewer 256 x 256 tiles than fill the device are gemm_tile.hip's.
 #include "common.h"
 #include "recurrent_dev.h"
 #include <algorithm>
@@ -32,8 +28,8 @@ struct NtArgs {
   const int* k_rows; int k_phys_rows;     // k-major kernel: k -> row of A and B in memory (NULL: identity), rows in memory
   const int* m_dev; const int* k_dev;     // device-resident M / K (NULL: use M / K above)
   int a_phys_rows;                        // rows of A in memory when a_rows is given
-  int ksplit;                             // > 1: K is cut into that many ranges, each adds its part to C atomically ...
-  float* parts; long sPart;               // ... or, if parts != NULL, stores it at parts + (z * ksplit + range) * sPart (layout of C)
+  int ksplit;                             // > 1: K is cut into that many ranges, each stores its part at parts + (z * ksplit + range) * sPart
+  float* parts; long sPart;               // (layout of C)
   int blocked;                            // tile raster: 1 = blocks of kSupM x kSupN tiles per XCD, 0 = bands of 8 tile columns
 };
 
@@ -88,14 +84,14 @@ template <typename TC, int TN>
 __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, const NtArgs& g, int M, int m0, int n0, int z, int ks,
                                            int ksplit) {
   constexpr int WN = 8 / TN, NW = 2 * WN;            // wavefronts along N, wavefronts in all
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;     // (uniform: rows of C are looked up by scalar loads)
   const int wm = wave / WN, wn = wave % WN;
   const int r = lane & 31, gq = lane >> 5;
   // Epilogue.  A lane holds column (lane % 32), rows 8*(v/4) + 4*(lane/32) + v%4 of each 32x32 block: stored as
   // it is that would be 128-byte pieces, eight of them per row at different times.  The tile goes through LDS
   // instead (two halves of 128 rows, the main loop's buffers are free by now) and leaves as whole rows: one
   // wavefront store = 256 consecutive columns of one row.
-  const bool to_parts = ksplit > 1 && g.parts != nullptr;      // this K range keeps its own copy: plain stores, no atomics
+  const bool to_parts = ksplit > 1;                  // this K range keeps its own copy
   TC* C = to_parts ? (TC*)(g.parts + ((long)z * ksplit + ks) * g.sPart) : (TC*)g.C + g.sCz * z;
   const float* bias = g.bias ? g.bias + g.sbiasz * z : nullptr;
   constexpr int kEpStride = 260;                      // floats per staged row (16-byte aligned, off the bank period)
@@ -132,21 +128,16 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
       const bool whole = vec_ok && col + 3 < g.N;
       if constexpr (sizeof(TC) == 4) {
         float* Cf = (float*)C + off;
-        if (ksplit > 1 && !to_parts) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (col + k < g.N) unsafeAtomicAdd(Cf + k, e[k]);
-        } else if (whole) {
-          float4 o = val;
-          if (g.accumulate && !to_parts) {
-            const float4 old = *(const float4*)Cf;
-            o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w;
-          }
-          *(float4*)Cf = o;
+        const bool add = g.accumulate && !to_parts;
+        // (by itself: joined with the read below, every row waits for the one before; non-temporal: the operand panels stay in L2)
+        if (whole && !add) __builtin_nontemporal_store((f32x4){val.x, val.y, val.z, val.w}, (f32x4*)Cf);
+        else if (whole) {
+          const float4 old = *(const float4*)Cf;
+          *(float4*)Cf = make_float4(val.x + old.x, val.y + old.y, val.z + old.z, val.w + old.w);
         } else {
 #pragma unroll
           for (int k = 0; k < 4; ++k)
-            if (col + k < g.N) Cf[k] = (g.accumulate && !to_parts) ? Cf[k] + e[k] : e[k];
+            if (col + k < g.N) Cf[k] = add ? Cf[k] + e[k] : e[k];
         }
       } else {
         uint16_t* Cb = (uint16_t*)C + off;
@@ -542,45 +533,8 @@ __global__ void sum_parts_kernel(const float* parts, float* C, int M, int N, lon
   C[z * sCz + off] = v;
 }
 
-// The same for a bfloat16 C without z: C[rows[m]][n] = sum over the K ranges of parts[range][m][n], m below *m_dev
-// when given (the rows above it were never computed); four columns per lane.
-__global__ void sum_parts_bf16_kernel(const float* parts, uint16_t* C, int M, int N, long ldc, long sPart, int ksplit, const int* c_rows,
-                                      const int* m_dev) {
-  const int nq = (N + 3) / 4;
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int m = (int)(idx / nq), n = (int)(idx % nq) * 4;
-  if (m >= (m_dev ? min(M, *m_dev) : M)) return;
-  const long src = (long)m * ldc + n, dst = (long)(c_rows ? c_rows[m] : m) * ldc + n;
-  float v[4] = {0.f, 0.f, 0.f, 0.f};
-  const bool whole = n + 3 < N && ldc % 4 == 0;
-  for (int ks = 0; ks < ksplit; ++ks) {
-    const float* p = parts + ks * sPart + src;
-    if (whole) {
-      typedef __attribute__((ext_vector_type(4))) float f32x4_;
-      const f32x4_ q = __builtin_nontemporal_load((const f32x4_*)p);
-      v[0] += q[0]; v[1] += q[1]; v[2] += q[2]; v[3] += q[3];
-    } else {
-      for (int k = 0; k < 4; ++k)
-        if (n + k < N) v[k] += p[k];
-    }
-  }
-  if (whole && (((uintptr_t)C & 7u) == 0)) {
-    uint2 o;
-    o.x = f2bf_bits(v[0]) | ((unsigned)f2bf_bits(v[1]) << 16);
-    o.y = f2bf_bits(v[2]) | ((unsigned)f2bf_bits(v[3]) << 16);
-    *(uint2*)(C + dst) = o;
-  } else {
-    for (int k = 0; k < 4; ++k)
-      if (n + k < N) C[dst + k] = f2bf_bits(v[k]);
-  }
-}
-
-// dst[c][r] = keep(r) ? src[r][c] : 0 for r < R, c < C ; dst rows are padded with zeros up to ldd.
-// keep(r): rows of src are frames (t = r / Bt, b = r % Bt), kept iff lens == NULL or t < lens[b].
-// With `cidx` (compact index of every frame, -1 for padded frames) the kept frames are packed instead:
-// dst[c][cidx[r]] = src[r][c]; columns past the last kept frame are left to zero_tail_kernel.
-__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd,
-                                                        long s_src, long s_dst, const int* lens, int Bt, int T, const int* cidx) {
+// dst[c][r] = src[r][c] for r < R, c < C ; dst rows are padded with zeros up to ldd.
+__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd, long s_src, long s_dst) {
   __shared__ uint16_t tile[64][66];
   src += s_src * blockIdx.z;
   dst += s_dst * blockIdx.z;
@@ -589,32 +543,9 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uin
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int rr = r0 + ty + 4 * i, cc = c0 + tx;
-    uint16_t v = 0;
-    if (rr < R && cc < C) {
-      bool keep = true;
-      if (lens) {
-        const int t = rr / Bt, b = rr - t * Bt;
-        int L = lens[b];
-        L = L < 0 ? 0 : (L > T ? T : L);
-        keep = t < L;
-      }
-      if (cidx) keep = cidx[rr] >= 0;
-      if (keep) v = src[(long)rr * lds_ + cc];
-    }
-    tile[ty + 4 * i][tx] = v;
+    tile[ty + 4 * i][tx] = rr < R && cc < C ? src[(long)rr * lds_ + cc] : (uint16_t)0;
   }
   __syncthreads();
-  if (cidx) {
-    const int rr = r0 + tx;
-    const int dcol = rr < R ? cidx[rr] : -1;
-    if (dcol < 0) return;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int cc = c0 + ty + 4 * i;
-      if (cc < C) dst[(long)cc * ldd + dcol] = tile[tx][ty + 4 * i];
-    }
-    return;
-  }
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int cc = c0 + ty + 4 * i, rr = r0 + tx;
@@ -622,40 +553,25 @@ __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uin
   }
 }
 
-// Same operation for 16-byte aligned operands (C, lds_, ldd, strides all multiples of 8 elements), written around
-// the destination: a work-group produces 64 consecutive destination columns (packed frames when `fidx` maps them
-// back to source rows) for 256 source columns.  Source rows are read as 16-byte vectors, the tile is turned in
-// LDS, and every destination row receives one aligned 128-byte run.  Columns from the last kept frame up to
-// the next multiple of 64 (packed) or up to ldd (not packed) are written as zeros here.
-__global__ __launch_bounds__(256) void transpose_frames_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd,
-                                                               long s_src, long s_dst, const int* lens, int Bt, int T,
-                                                               const int* fidx, const int* count) {
+// The same for 16-byte aligned operands (C, lds_, ldd, strides all multiples of 8 elements): a work-group produces 64 consecutive destination
+// columns for 256 source columns.  Source rows are read as 16-byte vectors, the tile is turned in LDS, and every destination row
+// receives one aligned 128-byte run.
+__global__ __launch_bounds__(256) void transpose_rows_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd, long s_src, long s_dst) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[64][264];
   src += s_src * blockIdx.z;
   dst += s_dst * blockIdx.z;
   const int tid = threadIdx.x;
   const int f0 = blockIdx.x * 64, c0 = blockIdx.y * 256;
-  const int nkeep = fidx ? min(count[0], R) : R;
-  if (fidx && f0 >= count[1]) return;            // past the zeroed tail of the packed columns
   {
     const int cv = tid & 31, fr = tid >> 5;
     const int col = c0 + cv * 8;
+    uint4 v[8];                                    // (all loads in flight: rows and columns outside are read from the edge and dropped)
+#pragma unroll
+    for (int pass = 0; pass < 8; ++pass) v[pass] = *(const uint4*)(src + (long)min(f0 + pass * 8 + fr, R - 1) * lds_ + min(col, C - 8));
 #pragma unroll
     for (int pass = 0; pass < 8; ++pass) {
-      const int f = pass * 8 + fr, c = f0 + f;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (c < nkeep && col < C) {
-        const int row = fidx ? fidx[c] : c;
-        bool keep = row >= 0 && row < R;
-        if (keep && lens && !fidx) {
-          const int t = row / Bt, b = row - t * Bt;
-          int L = lens[b];
-          L = L < 0 ? 0 : (L > T ? T : L);
-          keep = t < L;
-        }
-        if (keep) v = *(const uint4*)(src + (long)row * lds_ + col);
-      }
-      *(uint4*)&tile[f][cv * 8] = v;
+      const bool in = f0 + pass * 8 + fr < R && col < C;
+      *(uint4*)&tile[pass * 8 + fr][cv * 8] = in ? v[pass] : make_uint4(0, 0, 0, 0);
     }
   }
   __syncthreads();
@@ -678,20 +594,11 @@ __global__ __launch_bounds__(256) void transpose_frames_kernel(const uint16_t* s
   }
 }
 
-// dst[row][count[0] .. count[1]) = 0 for every row: the k tail of packed operands (count[1] = count[0] rounded up to 64)
-__global__ void zero_tail_kernel(uint16_t* dst, long rows, long ldd, const int* count) {
-  const int k0 = count[0], k1 = count[1];
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long row = idx >> 6;
-  const int k = k0 + (int)(idx & 63);
-  if (row < rows && k < k1 && k < ldd) dst[row * ldd + k] = 0;
-}
-
 // Frame map of a batch of end-padded sequences: frame (t, b) is kept iff t < lens[b].  Kept frames are numbered
-// in (t, b) order: cidx[t*B + b] = that number or -1, fidx[number] = t*B + b, count[0] = how many are kept,
+// in (t, b) order: fidx[number] = t*B + b, count[0] = how many are kept,
 // count[1] = count[0] rounded up to a multiple of 64.  One wavefront per time step.
-__global__ __launch_bounds__(256) void frame_map_kernel(const int* lens, int T, int B, int* cidx, int* fidx, int* count) {
-  frame_map_body(blockIdx.x, lens, T, B, cidx, fidx, count);
+__global__ __launch_bounds__(256) void frame_map_kernel(const int* lens, int T, int B, int* fidx, int* count) {
+  frame_map_body(blockIdx.x, lens, T, B, fidx, count);
 }
 
 // dst[r][c] = src[r][c] for c < C, zero for C <= c < ldd  (rows made 16-byte aligned)
@@ -729,7 +636,7 @@ bool gemm_tn_ok(const GemmArgs& g) {
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
   const long rows = g.k_rows ? g.k_phys_rows : g.K;
   if (rows * g.lda * 2 > lim || rows * g.ldb * 2 > lim) return false;
-  return g.in_bf16 && !g.out_bf16 && !g.a_kcontig && !g.b_kcontig && !g.lens && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
+  return g.in_bf16 && !g.out_bf16 && !g.a_kcontig && !g.b_kcontig && !g.lens && g.nseg == 1 && g.ksplit <= 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
          g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B);
 }
 
@@ -740,8 +647,7 @@ hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s) {
   a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz; a.nseg = 1;
   a.accumulate = g.accumulate; a.k_dev = g.k_dev; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
-  a.ksplit = g.ksplit > 1 ? g.ksplit : 1;
-  a.parts = a.ksplit > 1 ? g.parts : nullptr; a.sPart = (long)g.M * g.ldc;
+  a.ksplit = 1;
   const int sups = cdiv(cdiv(g.M, kT), kSupM) * cdiv(cdiv(g.N, kT), kSupN);
   a.blocked = sups >= 32 ? 1 : 0;
   const int tiles = a.blocked ? cdiv(sups, 8) * 8 * kSupM * kSupN : cdiv(g.M, kT) * cdiv(g.N, kT);
@@ -750,8 +656,8 @@ hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s) {
     return hipFuncSetAttribute((const void*)gemm_tn8_f32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
   });
   if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL(gemm_tn8_f32_kernel, dim3(tiles, g.nz * a.ksplit), dim3(512), kDlLds, s, a);
-  return sum_parts(a, s);
+  hipLaunchKernelGGL(gemm_tn8_f32_kernel, dim3(tiles, g.nz), dim3(512), kDlLds, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
@@ -762,72 +668,47 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
   a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.m_dev = g.m_dev; a.k_dev = g.k_dev; a.a_phys_rows = g.a_phys_rows;
-  // bfloat16 output over K ranges: float parts (packed rows) from the float kernel, then one pass that adds them,
-  // rounds once and scatters the rows; needs the direct-to-LDS kernel (segments and ranges share its stage counter)
-  const bool dl = !g.k_dev || g.K % kKB == 0;
-  const bool parts_bf16 = g.out_bf16 && g.ksplit > 1 && g.parts && dl && g.nz == 1 && !g.accumulate && !g.bias;
-  a.ksplit = (g.ksplit > 1 && ((!g.out_bf16 && g.nseg == 1) || parts_bf16)) ? g.ksplit : 1;
-  a.parts = a.ksplit > 1 && (!g.c_rows || parts_bf16) ? g.parts : nullptr; a.sPart = (long)g.M * g.ldc;
+  a.ksplit = g.ksplit > 1 && g.parts && !g.out_bf16 && !g.c_rows ? g.ksplit : 1;
+  a.parts = a.ksplit > 1 ? g.parts : nullptr; a.sPart = (long)g.M * g.ldc;
   // the blocked raster pays when every XCD gets several blocks; with few tiles it would leave XCDs idle
   const int sups = cdiv(cdiv(g.M, kT), kSupM) * cdiv(cdiv(g.N, kT), kSupN);
   a.blocked = sups >= 32 ? 1 : 0;
   const int tiles = a.blocked ? cdiv(sups, 8) * 8 * kSupM * kSupN : cdiv(g.M, kT) * cdiv(g.N, kT);
-  // operands go straight into LDS; K any multiple of 8 (a device-resident K is a multiple of 64 by contract, and so
-  // must then be the host's bound on it)
-  if (dl) {
-    static std::atomic<unsigned long long> dl_attr_set{0};
-    const hipError_t ea = once_per_device(dl_attr_set, [] {
-      for (const void* k : {(const void*)gemm_dl8_f32_kernel<false>, (const void*)gemm_dl8_f32_kernel<true>,
-                            (const void*)gemm_dl8_bf16_kernel<false>, (const void*)gemm_dl8_bf16_kernel<true>}) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
-    });
-    if (ea != hipSuccess) return ea;
-    const dim3 grid(tiles, g.nz * a.ksplit);
-    const bool ragged = g.K % kKB != 0, bf = g.out_bf16 && !parts_bf16;
-    if (bf && ragged) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<true>, grid, dim3(512), kDlLds, s, a);
-    else if (bf) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<false>, grid, dim3(512), kDlLds, s, a);
-    else if (ragged) hipLaunchKernelGGL(gemm_dl8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
-    else hipLaunchKernelGGL(gemm_dl8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);
-    if (parts_bf16) {
-      const hipError_t e = hipGetLastError();
+  static std::atomic<unsigned long long> dl_attr_set{0};
+  const hipError_t ea = once_per_device(dl_attr_set, [] {
+    for (const void* k : {(const void*)gemm_dl8_f32_kernel<false>, (const void*)gemm_dl8_f32_kernel<true>,
+                          (const void*)gemm_dl8_bf16_kernel<false>, (const void*)gemm_dl8_bf16_kernel<true>}) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
       if (e != hipSuccess) return e;
-      const long total = (long)a.M * ((a.N + 3) / 4);
-      hipLaunchKernelGGL(sum_parts_bf16_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, a.parts, (uint16_t*)a.C, a.M, a.N, a.ldc, a.sPart,
-                         a.ksplit, a.c_rows, a.m_dev);
-      return hipGetLastError();
     }
-    return sum_parts(a, s);
-  }
-  return hipErrorInvalidValue;       // unreachable: gemm_nt_ok() refuses a device-resident K whose bound is not a multiple of 64
+    return hipSuccess;
+  });
+  if (ea != hipSuccess) return ea;
+  const dim3 grid(tiles, g.nz * a.ksplit);
+  const bool ragged = g.K % kKB != 0, bf = g.out_bf16;
+  if (bf && ragged) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<true>, grid, dim3(512), kDlLds, s, a);
+  else if (bf) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<false>, grid, dim3(512), kDlLds, s, a);
+  else if (ragged) hipLaunchKernelGGL(gemm_dl8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
+  else hipLaunchKernelGGL(gemm_dl8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);
+  return sum_parts(a, s);
 }
 
-
-hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst,
-                            const int* lens, int Bt, int T, hipStream_t s, const int* cidx, const int* fidx, const int* count) {
+hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst, hipStream_t s) {
   if (R <= 0 || C <= 0 || nz <= 0) return hipSuccess;
   const bool aligned = C % 8 == 0 && ld_src % 8 == 0 && ld_dst % 8 == 0 && s_src % 8 == 0 && s_dst % 8 == 0 &&
                        ((uintptr_t)src & 15u) == 0 && ((uintptr_t)dst & 15u) == 0;
-  if (aligned) {
-    hipLaunchKernelGGL(transpose_frames_kernel, dim3(cdiv(ld_dst, 64), cdiv(C, 256), nz), dim3(256), 0, s, (const uint16_t*)src,
-                       (uint16_t*)dst, R, C, ld_src, ld_dst, s_src, s_dst, lens, Bt, T, cidx ? fidx : nullptr, count);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(transpose_kernel, dim3(cdiv(ld_dst, 64), cdiv(C, 64), nz), dim3(256), 0, s, (const uint16_t*)src,
-                     (uint16_t*)dst, R, C, ld_src, ld_dst, s_src, s_dst, lens, Bt, T, cidx);
-  if (cidx) {                           // packed columns: zero from the last kept frame to the next multiple of 64
-    for (int z = 0; z < nz; ++z)
-      hipLaunchKernelGGL(zero_tail_kernel, dim3(cdiv((long)C * 64, 256)), dim3(256), 0, s, (uint16_t*)dst + s_dst * z, (long)C,
-                         ld_dst, count);
-  }
+  if (aligned)
+    hipLaunchKernelGGL(transpose_rows_kernel, dim3(cdiv(ld_dst, 64), cdiv(C, 256), nz), dim3(256), 0, s, (const uint16_t*)src, (uint16_t*)dst, R, C,
+                       ld_src, ld_dst, s_src, s_dst);
+  else
+    hipLaunchKernelGGL(transpose_kernel, dim3(cdiv(ld_dst, 64), cdiv(C, 64), nz), dim3(256), 0, s, (const uint16_t*)src, (uint16_t*)dst, R, C,
+                       ld_src, ld_dst, s_src, s_dst);
   return hipGetLastError();
 }
 
-hipError_t launch_frame_map(const int* lens, int T, int B, int* cidx, int* fidx, int* count, hipStream_t s) {
+hipError_t launch_frame_map(const int* lens, int T, int B, int* fidx, int* count, hipStream_t s) {
   if (T <= 0 || B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(frame_map_kernel, dim3(cdiv(T, 4)), dim3(256), 0, s, lens, T, B, cidx, fidx, count);
+  hipLaunchKernelGGL(frame_map_kernel, dim3(cdiv(T, 4)), dim3(256), 0, s, lens, T, B, fidx, count);
   return hipGetLastError();
 }
 

@@ -298,8 +298,16 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileArgs g) {
       for (int v = 0; v < 16; ++v) ep[(wm * 32 + 8 * (v >> 2) + 4 * gq + (v & 3)) * kEpStride + (wn * TJ + j) * 32 + r] = acc[i][j][v];
     __syncthreads();
     if (col < g.N) {
-      for (int rl = tid / kTpr; rl < WM * 32; rl += 64 * NW / kTpr) {
-        const int row = m0 + (rl >> 5) * TI * 32 + i * 32 + (rl & 31);
+      constexpr int kStep = 64 * NW / kTpr, kIts = WM * 32 / kStep;
+      int crow[kIts];                                          // (looked up before the first store: a load behind a store waits for it)
+#pragma unroll
+      for (int q = 0; q < kIts; ++q) {
+        const int rl = tid / kTpr + q * kStep, row = min(m0 + (rl >> 5) * TI * 32 + i * 32 + (rl & 31), M - 1);
+        crow[q] = g.c_rows && !to_parts ? g.c_rows[row] : row;
+      }
+#pragma unroll
+      for (int q = 0; q < kIts; ++q) {
+        const int rl = tid / kTpr + q * kStep, row = m0 + (rl >> 5) * TI * 32 + i * 32 + (rl & 31);
         if (row >= M) continue;
         const float4 val = *(const float4*)&ep[rl * kEpStride + (tid % kTpr) * 4];
         if (to_parts) {                                        // (ldp is a multiple of 4; what lies past N is padding)
@@ -307,12 +315,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileArgs g) {
           continue;
         }
         float e[4] = {val.x + bv[0], val.y + bv[1], val.z + bv[2], val.w + bv[3]};
-        const long off = (long)(g.c_rows ? g.c_rows[row] : row) * g.ldc + col;
+        const long off = (long)crow[q] * g.ldc + col;
         if constexpr (sizeof(TC) == 4) {
           float* Cf = (float*)C + off;
-          if (vec) {
-            if (g.accumulate) { const float4 o = *(const float4*)Cf; e[0] += o.x; e[1] += o.y; e[2] += o.z; e[3] += o.w; }
-            *(float4*)Cf = make_float4(e[0], e[1], e[2], e[3]);
+          if (vec && !g.accumulate) __builtin_nontemporal_store((f32x4){e[0], e[1], e[2], e[3]}, (f32x4*)Cf);
+          else if (vec) {
+            const float4 o = *(const float4*)Cf;
+            *(float4*)Cf = make_float4(e[0] + o.x, e[1] + o.y, e[2] + o.z, e[3] + o.w);
           } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k) if (col + k < g.N) Cf[k] = g.accumulate ? Cf[k] + e[k] : e[k];

@@ -28,8 +28,7 @@ struct Plan {
   size_t res_gates, res_hprev, res_dir_stride, reserve_bytes;
   // workspace
   size_t ws_Wf, ws_Wb, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
-      ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_cidx, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
-  int ks_dwx, ks_dwh, ks_dx;                // K ranges of the weight-gradient products and of dX (few output tiles: the whole device works on them)
+      ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool small;                               // narrow layer: loop_small.hip
   bool blocks;                              // wide bfloat16 layer: loop_block.hip, if the device holds it
@@ -154,29 +153,11 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_xpad = take(fg || !p->bf16 ? TB * std::max(fg && !p->zx_nn && p->n_in_pad != d->n_in ? p->n_in_pad : 0, p->n_in8 != d->n_in ? p->n_in8 : 0) * p->esz : 0);
   // frame map of the batch (which frames are real), used to leave padded frames out of the products
   const bool fm = fg || !p->bf16;             // (float storage: its product kernels take the same row maps)
-  p->ws_cidx = take(fm ? (size_t)TB * 4 : 0);
   p->ws_fidx = take(fm ? (size_t)p->TBp * 4 : 0);
   p->ws_count = take(fm ? 256 : 0);
   p->ws_Wcat = take(p->single_step ? D * std::max((size_t)4 * n, wcell_rows(d->n)) * p->Kc * 2 : 0);
   p->ws_Acat = take(p->single_step ? D * std::max((size_t)B * p->Kc * 2, frag_bytes(d->B, p->Kc)) : 0);
-  // weight-gradient products with few output tiles cut K into ranges whose partial results are summed afterwards
-  const auto ksplit_for = [&](long M, long N) {
-    const long tiles = (long)cdiv(M, 256) * cdiv(N, 256) * p->D;
-    const long want = 256 / (tiles > 0 ? tiles : 1);
-    const long most = p->TBp / 1024 > 0 ? p->TBp / 1024 : 1;        // every range keeps at least 16 stages of 64 frames
-    return (int)std::max(1L, std::min(std::min(want, most), 8L));
-  };
-  // dX on a short batch has few output tiles too (rows = frames): K = 4n per direction cut into ranges of >= 16 stages
-  {
-    const long tiles = (long)cdiv(TB, 256) * cdiv(d->n_in, 256), stages = (long)p->D * cdiv(4L * d->n, 64);
-    // (tiles counts the padded frames; about two thirds of them are real with the benchmarks' length mixes, and only those
-    // rows' tiles do any work: 384 instead of 256 work-groups are aimed at.  Config 3: 160 tiles, 96 of them real, two
-    // ranges instead of one: dX 1.44 -> 0.89 ms per step.)
-    p->ks_dx = fg && !infer && p->bf16 && tiles > 0 ? (int)std::max(1L, std::min(std::min(384 / tiles, stages / 16), 8L)) : 1;
-  }
-  p->ks_dwx = fg && !infer ? ksplit_for(d->n_in, 4L * d->n) : 1;
-  p->ks_dwh = fg && !infer ? ksplit_for(d->n, 4L * d->n) : 1;
-  // (the same products where gemm_tile.hip or gemm_float.hip take them: their own ranges)
+  // products with few output tiles: K ranges, whose parts gemm_tile.hip and gemm_float.hip sum
   const auto tile_parts = [&](long M, long N, long K, int nz, int nseg, bool frames) {
     if (!p->bf16) return gemm_float_parts_bytes(M, N, K, nz, nseg, frames);
     return fg && gemm_tile_small(M, N, nz) ? gemm_tile_parts_bytes(M, N, K, nz, nseg) : (size_t)0;
@@ -185,8 +166,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   if (TB > 0) tp = std::max(tp, tile_parts(d->B, 4L * d->n, p->ldh, 1, 1, false));      // (h0 W_h)
   if (!infer && TB > 0)
     tp = std::max({tp, tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true), tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false), tile_parts(d->n, 4L * d->n, TB, p->D, 1, false)});
-  p->parts_bytes = std::max({tp, p->ks_dwx > 1 ? D * p->ks_dwx * d->n_in * 4 * n * 4 : 0, p->ks_dwh > 1 ? D * p->ks_dwh * n * 4 * n * 4 : 0,
-                               p->ks_dx > 1 ? (size_t)p->ks_dx * TB * d->n_in * 4 : 0});
+  p->parts_bytes = tp;
   p->ws_parts = take(p->parts_bytes);
   p->blocks = p->bf16 && loop_block_width(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
   p->ws_blocks = take(p->blocks ? loop_block_wh_bytes(d->n) + std::max(loop_block_ring_bytes(d->n), loop_block_ring_bytes_bwd(d->n)) : 0);
@@ -359,7 +339,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           if (!gemm_tile_ok(g)) { g.K = p.n_in; g.k_phys_rows = 0; g.parts = nullptr; }   // (operands past 2 GB: the generic kernel, which knows no padding)
         } else {                         // W_x is transposed once so that both operands are k-contiguous
           HIPCHK(launch_transpose(W_x, ws + p.ws_WxT, p.n_in, 4 * p.n, 4 * n, p.n_in_pad, p.D, (long)p.n_in * 4 * n,
-                                  (long)(4 * n) * p.n_in_pad, nullptr, 1, 0, s));
+                                  (long)(4 * n) * p.n_in_pad, s));
           g.B = ws + p.ws_WxT; g.ldb = p.n_in_pad; g.sBz = (long)(4 * n) * p.n_in_pad; g.b_kcontig = true;
         }
         if (seq_lens && (p.zx_nn ? gemm_tile_ok(g) : gemm_nt_ok(g))) {
@@ -367,7 +347,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           // frames stay unwritten and are never read
           int* fidx = (int*)(ws + p.ws_fidx);
           int* count = (int*)(ws + p.ws_count);
-          if (!frames_mapped) HIPCHK(launch_frame_map(seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), fidx, count, s));
+          if (!frames_mapped) HIPCHK(launch_frame_map(seq_lens, p.T, p.B, fidx, count, s));
           g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = g.M; g.m_dev = count;
         }
       } else if (!p.bf16) {              // float storage: the same padding, the same selection of real frames
@@ -383,7 +363,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         if (seq_lens) {
           int* fidx = (int*)(ws + p.ws_fidx);
           int* count = (int*)(ws + p.ws_count);
-          HIPCHK(launch_frame_map(seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), fidx, count, s));
+          HIPCHK(launch_frame_map(seq_lens, p.T, p.B, fidx, count, s));
           g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = g.M; g.m_dev = count;
         }
       }
@@ -452,7 +432,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd) {
       FrameMapArgs fm = {};
       if (p.fast_gemm && seq_lens) {   // the input projection below goes over the real frames
-        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
+        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
         frames_mapped = true;
       }
       HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
@@ -680,7 +660,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       if (use_ll) {
         FrameMapArgs fm = {};
         if (compact) {
-          fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_cidx), (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
+          fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
           frames_mapped = true;
         }
         if (compact && dx && ((size_t)TB * n_in * p.esz) % 4 == 0) {   // dX is scattered to the real frames' rows: the padded frames' rows are cleared here
@@ -813,12 +793,11 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
 
   if ((rc = p.small ? narrow_loop() : p.blocks && loop_block_fits(p.B, p.n, (long)(D * n)) ? block_loop() : split_loop())) return rc;
 
-  int* cidx = (int*)(ws + p.ws_cidx);
   int* fidx = (int*)(ws + p.ws_fidx);
   int* count = (int*)(ws + p.ws_count);
   if (compact && !frames_mapped && !p.dw_tiny) {
     Phase ph(LSTM_PHASE_PREP, 1, s);
-    HIPCHK(launch_frame_map(seq_lens, p.T, p.B, cidx, fidx, count, s));
+    HIPCHK(launch_frame_map(seq_lens, p.T, p.B, fidx, count, s));
   }
   auto products = [&]() -> int {
     if (dx) {                        // dX = sum over directions of DZ W_x^T
@@ -837,13 +816,12 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       }
       g.parts_bytes = 0;
       if (p.bf16 && gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
-      else if (p.ks_dx > 1 && gemm_nt_ok(g)) { g.ksplit = p.ks_dx; g.parts = (float*)(ws + p.ws_parts); }
       if (!p.bf16) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
       HIPCHK(launch_gemm(g, s));
     }
     // Weight gradients straight from the frame-major tensors (a row per frame in X, Hprev and DZ: both operands of
     // X^T DZ are k-major), over the packed list of real frames when lengths are given.
-    auto frame_major = [&](const void* A, long lda, long sAz, int M, void* C, int ks) {
+    auto frame_major = [&](const void* A, long lda, long sAz, int M, void* C) {
       GemmArgs g = {};
       g.A = A; g.B = DZ; g.C = C;
       g.M = M; g.N = 4 * p.n; g.K = (int)TB; g.lda = lda; g.ldb = 4 * n; g.ldc = 4 * n;
@@ -852,12 +830,11 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.vecA = 16; g.vecB = 16;
       if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
       if (gemm_tile_small(M, 4L * p.n, p.D)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
-      else if (ks > 1) { g.ksplit = ks; g.parts = (float*)(ws + p.ws_parts); }
       return g;
     };
     const bool pad_x = p.n_in8 != p.n_in;                          // rows of x are not 16-byte aligned: padded copy
-    const GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x, p.ks_dwx);
-    const GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h, p.ks_dwh);
+    const GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x);
+    const GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h);
     const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
     if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
       {

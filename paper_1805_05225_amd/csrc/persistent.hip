@@ -2267,7 +2267,7 @@ struct PrepArgs {
   ZeroRegions z;
   const bf16_t* W; uint4* Wout; int n, nk, nct; long w_total;   // nk: nkc (forward) / ntile2 (backward)
   uint4* ring0; uint4* ring1; long ring_total;
-  const int* lens; int T, B; int* cidx; int* fidx; int* count;     // frame map (cidx == NULL: none)
+  const int* lens; int T, B; int* fidx; int* count;     // frame map (fidx == NULL: none)
   int first_pack, first_ring, first_map, backward;
 };
 __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
@@ -2288,7 +2288,7 @@ __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
   } else if (bid < a.first_map) {
     pack_state_ll_body((long)(bid - a.first_ring) * 256 + threadIdx.x, a.ring0, a.ring1, a.ring_total);
   } else {
-    frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.cidx, a.fidx, a.count);
+    frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.fidx, a.count);
   }
 }
 // The initial state as the left operand of its product with W_h: rows of `ld` elements, rounded to the storage type as the recurrence
@@ -2441,8 +2441,8 @@ hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, in
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.first_map = a.first_ring + cdiv(a.ring_total, 256);
   a.backward = 0;
-  a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.cidx = fm.cidx; a.fidx = fm.fidx; a.count = fm.count;
-  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.cidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
+  a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
+  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s) {
@@ -2453,8 +2453,8 @@ hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, in
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.first_map = a.first_ring;
   a.backward = 1;
-  a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.cidx = fm.cidx; a.fidx = fm.fidx; a.count = fm.count;
-  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.cidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
+  a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
+  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 // float ring, before the first step: slot 0 holds zeros that carry the tag of step 0 in every unit, slot 1 is cleared

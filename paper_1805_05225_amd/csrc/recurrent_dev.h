@@ -7,7 +7,7 @@ namespace {
 
 // Frame map of a batch of end-padded sequences (see launch_frame_map), the work of one block of 256 threads: four time steps,
 // one wavefront each.  Shared by the kernel of its own and by the set-up kernel of the single-launch loops.
-__device__ __forceinline__ void frame_map_body(int block, const int* lens, int T, int B, int* cidx, int* fidx, int* count) {
+__device__ __forceinline__ void frame_map_body(int block, const int* lens, int T, int B, int* fidx, int* count) {
   const int lane = threadIdx.x & 63;
   const int t = block * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
@@ -39,7 +39,6 @@ __device__ __forceinline__ void frame_map_body(int block, const int* lens, int T
     }
     const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
     const int mine = base + __popcll(m & ((1ull << lane) - 1ull));
-    if (b < B) cidx[(long)t * B + b] = keep ? mine : -1;
     if (keep) fidx[mine] = t * B + b;
     base += __popcll(m);
   }
