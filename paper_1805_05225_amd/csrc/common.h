@@ -35,6 +35,27 @@ template <> struct Store<bf16_t> {
   __device__ static void store(void* p, long i, float v) { ((uint16_t*)p)[i] = f2bf_bits(v); }
 };
 
+// K ranges of a product: parts[z][range][m][n] (rows of ldp floats, ldp a multiple of 4; sPz floats per z), added into C (gemm_sum.hip).
+struct SumJob {
+  const float* parts; void* C; const float* bias;
+  int M, N, ksplit, nz;
+  long ldp, sPz, ldc, sCz, sbiasz;
+  const int* c_rows; const int* m_dev;
+  int accumulate, out_bf16;
+};
+// Sums collected for one launch; `used`: bytes of the parts' memory that they hold until then.
+struct SumList {
+  static constexpr int kMax = 4;
+  int count = 0;
+  SumJob j[kMax];
+  int first[kMax + 1] = {0, 0, 0, 0, 0};
+  size_t used = 0;
+  bool add(const SumJob& job);            // false: full
+};
+hipError_t launch_sums(const SumList& l, hipStream_t s);
+// The sum of one product's parts (`bytes` of them): now, or with the others of `later` if that is given and has room.
+hipError_t finish_parts(const SumJob& job, size_t bytes, SumList* later, hipStream_t s);
+
 // ------------------------------------------------------------------------------------------
 // Hoisted GEMM:  C[m,n] (+)= sum_seg sum_k A(m,k) B(k,n) + bias[n]
 //   a_kcontig: A is stored [M][lda] (k contiguous); otherwise [K][lda] (m contiguous).
@@ -64,6 +85,7 @@ struct GemmArgs {
   int ksplit;                             // > 1 (gemm_nt.hip's kernels): K cut into that many ranges ...
   float* parts;                           // ... every range stores its part there (nz * ksplit * M * ldc floats, no c_rows) and a
                                           // second kernel writes C (+)= their sum (`accumulate` honoured)
+  SumList* sums;                          // not NULL: the parts' sum is left for the caller's launch_sums (gemm_tile.hip, gemm_float.hip)
   size_t parts_bytes;                     // what `parts` holds (gemm_tile.hip and gemm_float.hip, which plan their own ranges)
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
@@ -79,9 +101,9 @@ hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s);
 // It cuts K into ranges of its own if `parts` holds gemm_tile_parts_bytes.
 bool gemm_tile_ok(const GemmArgs& g);
 bool gemm_tile_small(long M, long N, int nz);
-int gemm_tile_ranges(long M, long N, long K, int nz, int nseg);
 size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg);
 hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_tile_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s);      // two products of k-major operands, in one launch
 // Float storage (gemm_float.hip): operands as they lie in memory, rows 16-byte aligned, K a multiple of 4 for a k-contiguous
 // operand; row maps, device-resident M / K and segments as above; K ranges of its own if `parts` holds gemm_float_parts_bytes
 // (launch_gemm routes to it by itself; what it does not take goes to the generic kernel).
@@ -367,7 +389,6 @@ hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, in
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]
 constexpr int kColsumSlices = 64;
-hipError_t launch_colsum_final(const float* part, float* db, int ncols, int ndir, int nslices, int accumulate, hipStream_t s);
 hipError_t launch_colsum(const void* DZ, float* db, float* part, int rows, int ncols, int ndir, long sDZ,
                          bool bf16, int accumulate, hipStream_t s);
 

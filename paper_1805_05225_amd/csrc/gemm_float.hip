@@ -287,27 +287,6 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
   }
 }
 
-// C[z][rows[m]][n] (+)= sum over the K ranges of parts[z][range][m][n] (+ bias[n]), m below *m_dev when given; four columns per lane.
-__global__ void sum_ranges_kernel(FArgs g) {
-  const int nq = (g.N + 3) / 4;
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int m = (int)(idx / nq), n = (int)(idx % nq) * 4, z = blockIdx.y;
-  if (m >= (g.m_dev ? min(g.M, *g.m_dev) : g.M)) return;
-  const float* p = g.parts + (long)z * g.ksplit * g.M * g.ldp + (long)m * g.ldp + n;      // (ldp is a multiple of 4: whole quads)
-  float* dst = g.C + g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int r = 0; r < g.ksplit; ++r) v += __builtin_nontemporal_load((const f32x4*)(p + (long)r * g.M * g.ldp));
-  const float* bias = g.bias ? g.bias + g.sbiasz * z + n : nullptr;
-  const int cols = min(4, g.N - n);
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (k < cols) v[k] += (bias ? bias[k] : 0.f) + (g.accumulate ? dst[k] : 0.f);
-  if (cols == 4 && ((uintptr_t)dst & 15u) == 0) *(f32x4*)dst = v;
-  else
-    for (int k = 0; k < cols; ++k) dst[k] = v[k];
-}
-
 __global__ __launch_bounds__(256, 2) void gemm_float_nn_kernel(FArgs g) { gemm_float_body<true, false>(g); }
 __global__ __launch_bounds__(256, 2) void gemm_float_nt_kernel(FArgs g) { gemm_float_body<true, true>(g); }
 __global__ __launch_bounds__(256, 2) void gemm_float_tn_kernel(FArgs g) { gemm_float_body<false, false>(g); }
@@ -392,11 +371,12 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s) {
   if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL(gemm_float_nt_kernel, grid, block, kLds, s, a);
   else if (g.a_kcontig) hipLaunchKernelGGL(gemm_float_nn_kernel, grid, block, kLds, s, a);
   else hipLaunchKernelGGL(gemm_float_tn_kernel, grid, block, kLds, s, a);
-  if (a.ksplit > 1) {
-    const long lanes = (long)g.M * ((g.N + 3) / 4);
-    hipLaunchKernelGGL(sum_ranges_kernel, dim3((unsigned)cdiv(lanes, 256L), g.nz), dim3(256), 0, s, a);
-  }
-  return hipGetLastError();
+  if (a.ksplit == 1) return hipGetLastError();
+  SumJob j = {};
+  j.parts = a.parts; j.C = a.C; j.bias = a.bias; j.M = a.M; j.N = a.N; j.ksplit = a.ksplit; j.nz = g.nz;
+  j.ldp = a.ldp; j.sPz = (long)a.ksplit * a.M * a.ldp; j.ldc = a.ldc; j.sCz = a.sCz; j.sbiasz = a.sbiasz;
+  j.c_rows = a.c_rows; j.m_dev = a.m_dev; j.accumulate = a.accumulate;
+  return finish_parts(j, (size_t)g.nz * j.sPz * 4, g.sums, s);
 }
 
 }  // namespace lstm

@@ -41,6 +41,8 @@ struct TileArgs {
   int ksplit; float* parts; long ldp;     // > 1: range r of problem z stores its part at parts[(z * ksplit + r) * M * ldp ..], rows packed
 };
 
+struct TileGroup { TileArgs p[2]; int first1; };         // blocks from first1 on are the second product's
+
 __device__ __forceinline__ void load_to_lds_b128(const u32x4& rsrc, unsigned lds_addr, unsigned voff, unsigned soff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
@@ -69,11 +71,13 @@ struct Geo {
 
 // KROWS: k-major operands whose row k is row k_rows[k] in memory.
 template <typename TC, bool AK, bool BK, bool KROWS, int TI, int TJ, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileArgs g) {
+__global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileGroup grp) {
   typedef Geo<TI, TJ, WM, WN> G;
   constexpr int kBM = G::kBM, kBN = G::kBN, NW = G::kNW, kOpA = G::kOpA, kStage = G::kStage, kLA = G::kLA, kLB = G::kLB;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
+  const bool second = (int)blockIdx.x >= grp.first1;
+  const TileArgs g = second ? grp.p[1] : grp.p[0];
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   const int r = lane & 31, gq = lane >> 5;
@@ -81,11 +85,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileArgs g) {
   // bands of 8 tile columns, row-major inside a band: work-groups are dealt to the 8 XCDs round-robin, so each keeps one tile
   // column of B in its L2
   const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
-  const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN, bid = blockIdx.x;
+  const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
+  const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), zk = mine / (tiles_m * tiles_n), bid = mine - zk * (tiles_m * tiles_n);
   const int band = bid / (8 * tiles_m), width = min(8, tiles_n - band * 8), rel = bid - band * 8 * tiles_m;
   const int m0 = __builtin_amdgcn_readfirstlane((rel / width) * kBM), n0 = __builtin_amdgcn_readfirstlane((band * 8 + rel % width) * kBN);
   if (m0 >= M) return;
-  const int ksplit = g.ksplit, z = __builtin_amdgcn_readfirstlane(blockIdx.y / ksplit), ks = blockIdx.y - z * ksplit;
+  const int ksplit = g.ksplit, z = __builtin_amdgcn_readfirstlane(zk / ksplit), ks = __builtin_amdgcn_readfirstlane(zk - z * ksplit);
 
   const int ktiles = (K + kKB - 1) / kKB, nstage = ktiles * g.nseg;
   const int tail_chunks = (K - (ktiles - 1) * kKB + 7) >> 3;   // 16-byte chunks of a k-contiguous operand in the last k-tile
@@ -339,55 +344,56 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileArgs g) {
   }
 }
 
-// C[z][rows[m]][n] (+)= bias[n] + sum over the ranges of parts[z][range][m][n]; four columns per thread.  It reads each part once: bandwidth bound.
-template <typename TC>
-__global__ __launch_bounds__(256) void sum_tile_parts_kernel(TileArgs g) {
-  const int nq = (g.N + 3) / 4, z = blockIdx.y;
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  const int m = (int)(idx / nq), n = (int)(idx % nq) * 4;
-  if (m >= (g.m_dev ? min(g.M, *g.m_dev) : g.M)) return;
-  typedef __attribute__((ext_vector_type(4))) float f4;
-  f4 v = {0.f, 0.f, 0.f, 0.f};
-  for (int ks = 0; ks < g.ksplit; ++ks) v += __builtin_nontemporal_load((const f4*)(g.parts + ((long)(z * g.ksplit + ks) * g.M + m) * g.ldp + n));
-  const float* bias = g.bias ? g.bias + g.sbiasz * z : nullptr;
-  const long off = g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
-  float e[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) e[k] = v[k] + (bias && n + k < g.N ? bias[n + k] : 0.f);
-  if (n + 3 < g.N && (off & 3) == 0 && ((uintptr_t)g.C & 15u) == 0) {
-    if constexpr (sizeof(TC) == 4) {
-      float* p = (float*)g.C + off;
-      if (g.accumulate) { const float4 o = *(const float4*)p; e[0] += o.x; e[1] += o.y; e[2] += o.z; e[3] += o.w; }
-      *(float4*)p = make_float4(e[0], e[1], e[2], e[3]);
-    } else {
-      *(uint2*)((uint16_t*)g.C + off) = make_uint2(f2bf_bits(e[0]) | ((unsigned)f2bf_bits(e[1]) << 16), f2bf_bits(e[2]) | ((unsigned)f2bf_bits(e[3]) << 16));
-    }
-    return;
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if (n + k >= g.N) break;
-    if constexpr (sizeof(TC) == 4) { float* p = (float*)g.C + off + k; *p = g.accumulate ? *p + e[k] : e[k]; }
-    else ((uint16_t*)g.C)[off + k] = f2bf_bits(e[k]);
-  }
-}
-
 template <typename TC, bool AK, bool BK, bool KROWS, int TI, int TJ, int WM, int WN>
-hipError_t launch_as(const TileArgs& a, hipStream_t s) {
+hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
   typedef Geo<TI, TJ, WM, WN> G;
   const auto kernel = gemm_tile_kernel<TC, AK, BK, KROWS, TI, TJ, WM, WN>;
   static std::atomic<unsigned long long> attr_set{0};
   const hipError_t ea = once_per_device(attr_set, [&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds); });
   if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL(kernel, dim3(cdiv(a.M, G::kBM) * cdiv(a.N, G::kBN), a.nz * a.ksplit), dim3(64 * G::kNW), G::kLds, s, a);
+  TileGroup c = a;
+  int blocks[2] = {0, 0};
+  for (int i = 0; i < count; ++i) blocks[i] = cdiv(c.p[i].M, G::kBM) * cdiv(c.p[i].N, G::kBN) * c.p[i].nz * c.p[i].ksplit;
+  c.first1 = count == 2 ? blocks[0] : 0x7fffffff;
+  hipLaunchKernelGGL(kernel, dim3(blocks[0] + blocks[1]), dim3(64 * G::kNW), G::kLds, s, c);
   return hipGetLastError();
 }
 template <typename TC>
-hipError_t launch_layout(const TileArgs& a, bool ak, bool bk, hipStream_t s) {
-  if (ak && bk) return launch_as<TC, true, true, false, 2, 2, 2, 2>(a, s);
-  if (ak) return launch_as<TC, true, false, false, 2, 2, 2, 2>(a, s);
-  if (a.k_rows) return launch_as<TC, false, false, true, 2, 2, 2, 2>(a, s);
-  return launch_as<TC, false, false, false, 2, 2, 2, 2>(a, s);
+hipError_t launch_layout(const TileGroup& a, int count, bool ak, bool bk, hipStream_t s) {
+  if (ak && bk) return launch_as<TC, true, true, false, 2, 2, 2, 2>(a, count, s);
+  if (ak) return launch_as<TC, true, false, false, 2, 2, 2, 2>(a, count, s);
+  if (a.p[0].k_rows) return launch_as<TC, false, false, true, 2, 2, 2, 2>(a, count, s);
+  return launch_as<TC, false, false, false, 2, 2, 2, 2>(a, count, s);
+}
+
+long tiles_of(const GemmArgs& g) { return (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.nz; }
+// `others`: tiles of the product that shares the launch
+int ranges(long tiles, long others, long K, int nseg) {
+  const long stages = (long)cdiv(K, kKB) * nseg;
+  return (int)std::max(1L, std::min(std::min(512 / std::max(tiles + others, 1L), stages / 4), 16L));
+}
+size_t bytes_of(long M, long N, int nz, int ks) { return ks > 1 ? (size_t)ks * nz * M * ((N + 3) / 4 * 4) * 4 : 0; }
+TileArgs tile_args(const GemmArgs& g, long others, size_t parts_used) {
+  TileArgs a = {};
+  a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
+  a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
+  a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
+  a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
+  a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.a_phys_rows = g.a_phys_rows; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
+  a.m_dev = g.m_dev; a.k_dev = g.k_dev;
+  a.ldp = (g.N + 3) / 4 * 4;
+  a.ksplit = g.parts ? ranges(tiles_of(g), others, g.K, g.nseg) : 1;
+  if (parts_used + bytes_of(g.M, g.N, g.nz, a.ksplit) > g.parts_bytes) a.ksplit = 1;
+  a.parts = a.ksplit > 1 ? (float*)((char*)g.parts + parts_used) : nullptr;
+  return a;
+}
+hipError_t finish(const TileArgs& a, const GemmArgs& g, hipStream_t s) {
+  if (a.ksplit == 1) return hipGetLastError();
+  SumJob j = {};
+  j.parts = a.parts; j.C = a.C; j.bias = a.bias; j.M = a.M; j.N = a.N; j.ksplit = a.ksplit; j.nz = a.nz;
+  j.ldp = a.ldp; j.sPz = (long)a.ksplit * a.M * a.ldp; j.ldc = a.ldc; j.sCz = a.sCz; j.sbiasz = a.sbiasz;
+  j.c_rows = a.c_rows; j.m_dev = a.m_dev; j.accumulate = a.accumulate; j.out_bf16 = g.out_bf16;
+  return finish_parts(j, bytes_of(a.M, a.N, a.nz, a.ksplit), g.sums, s);
 }
 
 }  // namespace
@@ -408,33 +414,27 @@ bool gemm_tile_ok(const GemmArgs& g) {
 // lies between 192 tiles (1600 real of 3000 rows x 4000 x 1000: 55 us there, 24 here) and 237 (768 x 20000 x 1000: 44 us there, 49 here).
 bool gemm_tile_small(long M, long N, int nz) { return (long)cdiv(M, 256) * cdiv(N, 256) * nz <= 200; }
 
-int gemm_tile_ranges(long M, long N, long K, int nz, int nseg) {
-  const long tiles = (long)cdiv(M, 128) * cdiv(N, 128) * nz, stages = (long)cdiv(K, kKB) * nseg;
-  return (int)std::max(1L, std::min(std::min(512 / std::max(tiles, 1L), stages / 4), 16L));
-}
 size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg) {
-  const int ks = gemm_tile_ranges(M, N, K, nz, nseg);
-  return ks > 1 ? (size_t)ks * nz * M * ((N + 3) / 4 * 4) * 4 : 0;
+  return bytes_of(M, N, nz, ranges((long)cdiv(M, 128) * cdiv(N, 128) * nz, 0, K, nseg));
 }
 
 hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s) {
-  TileArgs a = {};
-  a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
-  a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
-  a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
-  a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
-  a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.a_phys_rows = g.a_phys_rows; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
-  a.m_dev = g.m_dev; a.k_dev = g.k_dev;
-  a.ldp = (g.N + 3) / 4 * 4;
-  a.ksplit = g.parts && gemm_tile_parts_bytes(g.M, g.N, g.K, g.nz, g.nseg) <= g.parts_bytes ? gemm_tile_ranges(g.M, g.N, g.K, g.nz, g.nseg) : 1;
-  a.parts = a.ksplit > 1 ? g.parts : nullptr;
-  const bool bf = g.out_bf16 && a.ksplit == 1;
-  const hipError_t e = bf ? launch_layout<uint16_t>(a, g.a_kcontig, g.b_kcontig, s) : launch_layout<float>(a, g.a_kcontig, g.b_kcontig, s);
-  if (e != hipSuccess || a.ksplit == 1) return e;
-  const dim3 grid(cdiv((long)a.M * ((a.N + 3) / 4), 256), a.nz);
-  if (g.out_bf16) hipLaunchKernelGGL(sum_tile_parts_kernel<uint16_t>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(sum_tile_parts_kernel<float>, grid, dim3(256), 0, s, a);
-  return hipGetLastError();
+  TileGroup a = {};
+  a.p[0] = tile_args(g, 0, 0);
+  const bool bf = g.out_bf16 && a.p[0].ksplit == 1;
+  const hipError_t e = bf ? launch_layout<uint16_t>(a, 1, g.a_kcontig, g.b_kcontig, s) : launch_layout<float>(a, 1, g.a_kcontig, g.b_kcontig, s);
+  return e == hipSuccess ? finish(a.p[0], g, s) : e;
+}
+
+// dW_x and dW_h: each alone leaves the device's last work-groups waiting for it, and wants twice the K ranges to fill the device.
+hipError_t launch_gemm_tile_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s) {
+  if (g.M <= 0 || h.M <= 0 || g.N <= 0 || h.N <= 0 || g.nz <= 0) return hipErrorInvalidValue;
+  TileGroup a = {};
+  a.p[0] = tile_args(g, tiles_of(h), 0);
+  a.p[1] = tile_args(h, tiles_of(g), (bytes_of(g.M, g.N, g.nz, a.p[0].ksplit) + 255) / 256 * 256);
+  hipError_t e = launch_layout<float>(a, 2, false, false, s);
+  if (e != hipSuccess || (e = finish(a.p[0], g, s)) != hipSuccess) return e;
+  return finish(a.p[1], h, s);
 }
 
 }  // namespace lstm

@@ -164,8 +164,9 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   };
   size_t tp = TB > 0 && (p->zx_nn || !p->bf16) && !p->single_step ? tile_parts(TB, 4L * d->n, p->n_in8, p->D, 1, true) : 0;
   if (TB > 0) tp = std::max(tp, tile_parts(d->B, 4L * d->n, p->ldh, 1, 1, false));      // (h0 W_h)
-  if (!infer && TB > 0)
-    tp = std::max({tp, tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true), tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false), tile_parts(d->n, 4L * d->n, TB, p->D, 1, false)});
+  if (!infer && TB > 0)                   // (the backward products' are added together at the end)
+    tp = std::max(tp, up(tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true)) + up(tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false)) +
+                          up(tile_parts(d->n, 4L * d->n, TB, p->D, 1, false)));
   p->parts_bytes = tp;
   p->ws_parts = take(p->parts_bytes);
   p->blocks = p->bf16 && loop_block_width(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
@@ -799,6 +800,8 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     Phase ph(LSTM_PHASE_PREP, 1, s);
     HIPCHK(launch_frame_map(seq_lens, p.T, p.B, fidx, count, s));
   }
+  SumList sums;                        // what the products' K ranges and the loop's bias-gradient slices still have to be added to
+  auto parts_of = [&](GemmArgs& g) { g.parts = (float*)(ws + p.ws_parts + sums.used); g.parts_bytes = p.parts_bytes - sums.used; g.sums = &sums; };
   auto products = [&]() -> int {
     if (dx) {                        // dX = sum over directions of DZ W_x^T
       GemmArgs g = {};
@@ -814,9 +817,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         if (!dx_cleared) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
         g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = TB; g.m_dev = count;
       }
-      g.parts_bytes = 0;
-      if (p.bf16 && gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
-      if (!p.bf16) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+      if (!p.bf16 || (gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz))) parts_of(g);
       HIPCHK(launch_gemm(g, s));
     }
     // Weight gradients straight from the frame-major tensors (a row per frame in X, Hprev and DZ: both operands of
@@ -829,23 +830,26 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
       g.vecA = 16; g.vecB = 16;
       if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
-      if (gemm_tile_small(M, 4L * p.n, p.D)) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+      if (gemm_tile_small(M, 4L * p.n, p.D)) parts_of(g);
       return g;
     };
     const bool pad_x = p.n_in8 != p.n_in;                          // rows of x are not 16-byte aligned: padded copy
-    const GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x);
-    const GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h);
+    GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x);
+    GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h);
     const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
     if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
       {
         Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
         if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
+        if (gx.parts && gh.parts) {    // both in few tiles
+          HIPCHK(launch_gemm_tile_pair(gx, gh, s));
+          return LSTM_OK;
+        }
         HIPCHK(launch_gemm(gx, s));
       }
-      {
-        Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
-        HIPCHK(launch_gemm(gh, s));
-      }
+      Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
+      if (gh.parts) parts_of(gh);
+      HIPCHK(launch_gemm(gh, s));
     } else {                         // dW_x = X^T DZ, padded frames of X masked out
       GemmArgs g = {};
       g.A = x; g.B = DZ; g.C = dW_x;
@@ -858,7 +862,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.vecA = widest(g.lda, 0, 0, p.esz, 4);
       g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
       if (!p.bf16) {
-        g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
+        parts_of(g);
         if (pad_x) {
           GemmArgs gp = g;
           gp.A = ws + p.ws_xpad; gp.lda = p.n_in8;
@@ -876,6 +880,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.A = rs + p.res_hprev; g.C = dW_h; g.M = p.n; g.lda = p.ldh;
       g.sAz = (long)(p.res_dir_stride / p.esz); g.sCz = (long)(n * 4 * n);
       g.lens = nullptr;
+      if (!p.bf16) parts_of(g);
       g.vecA = widest(g.lda, g.sAz, 0, p.esz, 4);
       Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
       HIPCHK(launch_gemm(g, s));
@@ -886,12 +891,15 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
     HIPCHK(launch_gemm_tiny(tiny, p.bf16, (unsigned*)(ws + p.ws_tiny_cnt), (float*)(ws + p.ws_tiny_parts), s));
   } else if ((rc = products())) return rc;
-  if (db_done) return LSTM_OK;
   Phase ph(LSTM_PHASE_DB, 2, s);
-  if (db_slices) {
-    HIPCHK(launch_colsum_final((const float*)(ws + p.ws_colsum), (float*)db, 4 * p.n, p.D, db_slices, acc, s));
-    return LSTM_OK;
+  if (db_slices && !db_done) {
+    SumJob j = {};
+    j.parts = (const float*)(ws + p.ws_colsum); j.C = db; j.M = 1; j.N = 4 * p.n; j.ksplit = db_slices; j.nz = p.D;
+    j.ldp = 4 * n; j.sPz = (long)kColsumSlices * 4 * n; j.ldc = 4 * n; j.sCz = 4 * n; j.accumulate = acc;
+    sums.add(j);                         // (three products and this: the list holds four)
   }
+  HIPCHK(launch_sums(sums, s));
+  if (db_slices || db_done) return LSTM_OK;
   HIPCHK(launch_colsum(DZ, (float*)db, (float*)(ws + p.ws_colsum), TB, 4 * p.n, p.D, (long)p.DZ_dir_elems, p.bf16, acc, s));
   return LSTM_OK;
 }

@@ -356,9 +356,4 @@ hipError_t launch_colsum(const void* DZ, float* db, float* part, int rows, int n
   hipLaunchKernelGGL(colsum_final_kernel, dim3(cdiv(ncols, 256), ndir), block, 0, s, part, db, ncols, kColsumSplit, accumulate);
   return hipGetLastError();
 }
-hipError_t launch_colsum_final(const float* part, float* db, int ncols, int ndir, int nslices, int accumulate, hipStream_t s) {
-  hipLaunchKernelGGL(colsum_final_kernel, dim3(cdiv(ncols, 256), ndir), dim3(256), 0, s, part, db, ncols, nslices, accumulate);
-  return hipGetLastError();
-}
-
 }  // namespace lstm
