@@ -27,6 +27,9 @@
  *     point states a weaker requirement), row-major,
  *     time-major.  The library allocates and frees nothing; scratch comes from `workspace`,
  *     state saved for the backward pass goes to `reserve`; sizes come from lstm_query().
+ *   - hT may be h0 and cT may be c0 (state carried in place, the same address).  Other outputs of a layer call must not overlap
+ *     its inputs; the stepped cell (T == 1 with LSTM_FLAG_INFERENCE) and lstm_readout read their inputs before they
+ *     store, so y, hT, cT and out may lie where x, h0 or the readout's inputs did.
  *   - `stream` is a hipStream_t cast to void* (NULL = the default stream).  Calls only enqueue
  *     work; they never synchronise.  Buffers must stay alive until the stream has passed the call.
  *   - dtype LSTM_F32: every tensor is float.  dtype LSTM_BF16_F32STATE: x, W_x, W_h, y, dy, dx

@@ -428,6 +428,17 @@ hipError_t launch_cell_step(const float* z, long part, int nparts, const float* 
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
+// Do two arrays of `rows` rows share a byte?  Row strides and widths in bytes; column blocks of one matrix (same stride) do not.
+inline bool rows_overlap(const void* a, long ld_a, long width_a, const void* b, long ld_b, long width_b, long rows) {
+  if (!a || !b || rows < 1 || width_a < 1 || width_b < 1) return false;
+  const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+  if (a0 + (rows - 1) * ld_a + width_a <= b0 || b0 + (rows - 1) * ld_b + width_b <= a0) return false;
+  if (ld_a != ld_b || rows == 1) return true;
+  const long d = ((long)(b0 - a0) % ld_a + ld_a) % ld_a;             // column of a's rows in which b's begin
+  return d < width_a || d + width_b > ld_a;
+}
+inline bool bytes_overlap(const void* a, size_t na, const void* b, size_t nb) { return rows_overlap(a, 0, (long)na, b, 0, (long)nb, 1); }
+
 // Host-side set-up that HIP keeps per device (function attributes, what a device is and holds): done once on every
 // device the library is used on, whichever thread gets there first.  `done` holds one bit per device ordinal (ordinals
 // 64 apart share a bit: the set-up is then simply repeated); the set-up must be idempotent, since two threads may both run it.

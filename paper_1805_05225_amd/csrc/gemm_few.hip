@@ -217,6 +217,8 @@ __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
 // neighbouring lanes per row (64 bytes in a row), turns it into fragment order through 1 KiB of LDS of its own - LDS
 // operations of a wavefront happen in order, so nothing has to be waited for - and the weights, asked for first, arrive
 // behind all of that.  B in fragment order, at most 16 * U * 32 values of k.
+// Every work-group reads all of the pieces while others already store: outputs must not share a byte with them (a step in place,
+// hT = h0, takes the concatenation).
 template <int U, bool F32, bool CELL>
 __global__ __launch_bounds__(1024) void few_gather_kernel(SkinnyArgs g, ConcatArgs ca, int ct) {
   constexpr int NW = 16, kHalf = U / 2;
@@ -415,7 +417,12 @@ hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void
   a.A = (const char*)A; a.B = (const char*)Wfrag; a.bias = bias; a.M = B; a.N = 4 * n; a.K = K; a.frag = 1;
   a.sAz = (long)cdiv(B, 16) * nkc * 512; a.sBz = (long)cdiv(n, 4) * nkc * 512; a.nz = ndir;
   a.n = n; a.h_in = h_in; a.c_in = c_in; a.h_out = h_out; a.c_out = c_out; a.y = (uint16_t*)y; a.ldy = ldy; a.cs = cs; a.lens = lens;
-  if (B <= 16 && nkc <= 16 * kGatherU) {
+  const size_t state = (size_t)ndir * B * n * 4;
+  bool in_place = false;
+  for (const void* o : {(const void*)h_out, (const void*)c_out, (const void*)cs})
+    in_place |= bytes_overlap(o, state, h_in, state) || bytes_overlap(o, state, x, (size_t)B * n_in * 2);
+  in_place |= bytes_overlap(y, (size_t)B * ldy * 2, h_in, state) || bytes_overlap(y, (size_t)B * ldy * 2, x, (size_t)B * n_in * 2);
+  if (B <= 16 && nkc <= 16 * kGatherU && !in_place) {
     hipLaunchKernelGGL((few_gather_kernel<kGatherU, true, true>), dim3(cdiv(n, 4), 1, ndir), dim3(1024), 0, s, a, c, 16);
     return hipGetLastError();
   }
@@ -438,7 +445,9 @@ hipError_t launch_few_readout(const void* x0, long ld0, int k0, const void* x1, 
   SkinnyArgs a = {};
   a.A = (const char*)A; a.B = (const char*)Wfrag; a.C = out; a.bias = bias; a.M = B; a.N = R; a.K = c.nkc * 32; a.ldc = ldo; a.nz = 1;
   a.out_bf16 = 1; a.relu = 1; a.frag = 1;
-  if (B <= 16 && c.nkc <= 16 * kGatherU) {
+  const bool in_place = rows_overlap(out, 2 * ldo, 2L * R, x0, 2 * ld0, 2L * k0, B) || rows_overlap(out, 2 * ldo, 2L * R, x1, 2 * ld1, 2L * k1, B) ||
+                        rows_overlap(out, 2 * ldo, 2L * R, x2, 2 * ld2, 2L * k2, B);
+  if (B <= 16 && c.nkc <= 16 * kGatherU && !in_place) {
     const int ct = few_columns(B, R);
     hipLaunchKernelGGL((few_gather_kernel<kGatherU, false, false>), dim3(cdiv(R, ct)), dim3(1024), 0, s, a, c, ct);
     return hipGetLastError();

@@ -60,3 +60,41 @@ def test_product(M, N, K):
     C = Bn.gemm(A.cuda(), B.cuda(), a_kcontig=True, b_kcontig=True, M=M, N=N, K=K, bias=dev(bias))
     torch.cuda.synchronize()
     check("C", C, A.double().numpy() @ B.double().numpy().T + bias, 1e-4)
+
+
+@pytest.mark.parametrize("B,n_in,n", [(1, 64, 64), (12, 2620, 1000), (16, 300, 104), (17, 300, 104), (193, 64, 66)])
+def test_stepped_cell_in_place(B, n_in, n):
+    """hT = h0 and cT = c0: every work-group needs all of h, so none may store its part before the others have read it."""
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(B + n)
+    Wx, Wh, x = _bf(rng, n_in, 4 * n, w=0.1).cuda(), _bf(rng, n, 4 * n, w=0.1).cuda(), _bf(rng, 1, B, n_in).cuda()
+    b, h, c = dev(rng.uniform(-.1, .1, 4 * n)), dev(rng.uniform(-1, 1, (B, n))), dev(rng.standard_normal((B, n)))
+    lens = torch.ones(B, dtype=torch.int32, device="cuda")
+    lens[B // 2] = 0                                         # this row keeps its state
+    for step in range(6):                                    # (the weights stay packed, the state moves on)
+        s = Bn.forward(x, Wx, Wh, b, h, c, lens, bidirectional=False, flags=Bn.FLAG_INFERENCE, want_c=False)
+        d = Bn.make_desc(1, B, n_in, n, Bn.LSTM_BF16_F32STATE, 1, Bn.FLAG_INFERENCE)
+        d.workspace_bytes = s["workspace"].numel()
+        y = torch.empty_like(s["y"])
+        p = lambda t: t.data_ptr()
+        assert Bn.lib.lstm_fwd(Bn.ctypes.byref(d), p(x), p(Wx), p(Wh), p(b), p(h), p(c), p(lens), p(y), None, p(h), p(c), None, p(s["workspace"]),
+                               Bn._stream()) == 0
+        torch.cuda.synchronize()
+        # (in place K is summed in another order for up to 16 rows: float sums of bf16 products, y may round the other way: one unit in 8 bits)
+        check("hT", h, s["hT"].double().cpu().numpy(), 1e-5)
+        check("cT", c, s["cT"].double().cpu().numpy(), 1e-5)
+        check("y", y, s["y"].double().cpu().numpy(), 2 ** -7)
+
+
+@pytest.mark.parametrize("B", [1, 12, 16, 17])
+def test_readout_over_its_inputs(B):
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(B)
+    n, nt, E = 200, 62, 136
+    W, br = _bf(rng, n, n + nt + E, w=0.1).cuda(), dev(rng.uniform(-.1, .1, n))
+    wide = _bf(rng, B, n + nt + E).cuda()                    # s | trg | att, one row after the other
+    s, trg, att = wide[:, :n], wide[:, n:n + nt], wide[:, n + nt:]
+    want = Bn.readout(s, trg, att, W, br)
+    Bn.readout(s, trg, att, W, br, out=s)                    # the result where s was
+    torch.cuda.synchronize()
+    check("readout", s, want.double().cpu().numpy(), 2 ** -7)
