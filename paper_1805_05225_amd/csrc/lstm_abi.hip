@@ -397,6 +397,12 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     return LSTM_OK;
   }
   if (p.blocks && loop_block_fits(p.B, p.n, (long)(D * n))) {    // a wide layer: projection, then a launch per direction and 32 rows
+    // Until a row's first frame every column of the grid reads its h0 from memory, and the columns do not end together: a state in
+    // place (hT over h0) is read from a copy.
+    if (bytes_overlap(h0, state_bytes, hT, state_bytes) || bytes_overlap(h0, state_bytes, cT, state_bytes)) {
+      HIPCHK(launch_copy(hstate, h0, state_bytes, s));
+      h0 = hstate;
+    }
     if ((rc = project())) return rc;
     hipError_t e = hipSuccess;
     for (size_t d = 0; d < D && e == hipSuccess; ++d) {

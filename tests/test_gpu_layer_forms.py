@@ -3,11 +3,12 @@ widths where the bfloat16 loops change their split, products with tile edges and
 frames and in untouched workspace, against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 pytestmark = pytest.mark.gpu
 
 from tests import test_gpu_parity as P
-from tests.gpu_util import TOL
+from tests.gpu_util import TOL, check, dev, host
 
 
 def _lens(rng, T, B):
@@ -59,3 +60,25 @@ def _layer(T, B, n_in, n, bidir, dt):
         for direction in ((1,) if bidir else (1, -1)):
             f, g = P.run_gpu(c, dt, bidir, direction, x_override=x, dy_override=dy, poison=True)
             P.compare(f, g, *P.run_oracle(c, bidir, direction), TOL[dt])
+
+
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 4, 33, 1040), ("bf16", 3, 16, 2048), ("bf16", 5, 9, 330), ("bf16", 4, 6, 64), ("f32", 5, 33, 331),
+                                      ("f32", 4, 6, 64), ("f32", 3, 5, 1100)])
+@pytest.mark.parametrize("direction", [1, -1])
+def test_state_in_place(dt, T, B, n, direction):
+    """hT = h0 and cT = c0; rows of length 1 begin in the last step of the reversed direction, rows of length 0 keep their state."""
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(n + T)
+    lens = rng.integers(0, T + 1, B)
+    lens[::3], lens[1] = 1, 0
+    c = P.rnd_case(rng, T, B, 40, n, 1, lens, dt, scale=2.0 / np.sqrt(n + 40))
+    x, Wx, Wh, b, ln = dev(c["x"], dt), dev(c["W_x"][0], dt), dev(c["W_h"][0], dt), dev(c["b"][0]), dev(c["lens"])
+    h, cc = dev(c["h0"][0]), dev(c["c0"][0])
+    s = Bn.forward(x, Wx, Wh, b, h, cc, ln, bidirectional=False, direction=direction, flags=Bn.FLAG_INFERENCE, want_c=False)
+    assert not Bn.sync_status(s["workspace"])
+    y, p = torch.empty_like(s["y"]), lambda t: t.data_ptr()
+    assert Bn.lib.lstm_fwd(Bn.ctypes.byref(s["desc"]), p(x), p(Wx), p(Wh), p(b), p(h), p(cc), p(ln), p(y), None, p(h), p(cc), None, p(s["workspace"]),
+                           Bn._stream()) == 0
+    assert not Bn.sync_status(s["workspace"])
+    for name, got, ref in (("y", y, s["y"]), ("hT", h, s["hT"]), ("cT", cc, s["cT"])):
+        check(name, got, host(ref), TOL[dt])
