@@ -283,7 +283,7 @@ struct BlockFwdArgs {
   int B, n, T, write_gates;
   char* ring; size_t ring_bytes;
   unsigned* sync; unsigned* xcc; unsigned spin_limit;
-  bool plain_launch;
+  bool plain_launch, first;               // first: of the call's launches; clears the error word
   int row0, ni;                           // set by the launcher: first row; K ranges
 };
 struct BlockBwdArgs {
@@ -296,7 +296,7 @@ struct BlockBwdArgs {
   int B, n, T;
   char* ring; size_t ring_bytes;
   unsigned* sync; unsigned* xcc; unsigned spin_limit;
-  bool plain_launch;
+  bool plain_launch, first;
   int row0;
 };
 bool loop_block_width(int n);

@@ -481,7 +481,7 @@ hipError_t launch_blocks(K one, K two, int blocks, A a, hipStream_t s) {
     ZeroRegions z;                                         // the rings, and the words in which columns find out that they share an XCD
     z.add(a.ring, a.ring_bytes);
     z.add(a.xcc, 256 * 4);
-    if (row0 == 0) z.add(a.sync, 4);
+    if (row0 == 0 && a.first) z.add(a.sync, 4);            // (a wait that expired in an earlier direction stays on record)
     if ((e = launch_fill_zero_many(z, s)) != hipSuccess) return hipErrorLaunchFailure;
     void* args[] = {&a};
     const void* kernel = (const void*)(a.B - row0 <= 16 ? one : two);
