@@ -417,7 +417,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       a.lens = seq_lens; a.B = p.B; a.n = p.n; a.T = p.T; a.write_gates = infer ? 0 : 1;
       a.ring = ws + p.ws_blocks + loop_block_wh_bytes(p.n); a.ring_bytes = loop_block_ring_bytes(p.n);
       a.sync = (unsigned*)(ws + p.ws_sync); a.xcc = a.sync + 64; a.spin_limit = kSpinLimit;
-      a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
+      a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0; a.first = d == 0;
       {
         Phase ph(LSTM_PHASE_PREP, 1, s);
         HIPCHK(launch_pack_blocks((const char*)W_h + d * n * 4 * n * p.esz, ws + p.ws_blocks, p.n, s));
@@ -785,7 +785,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       a.lens = seq_lens; a.B = p.B; a.n = p.n; a.T = p.T;
       a.ring = ws + p.ws_blocks + loop_block_wh_bytes(p.n); a.ring_bytes = loop_block_ring_bytes_bwd(p.n);
       a.sync = (unsigned*)(ws + p.ws_sync); a.xcc = a.sync + 64; a.spin_limit = kSpinLimit;
-      a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0;
+      a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0; a.first = d == 0;
       Phase ph(LSTM_PHASE_LOOP_BWD, 2, s);
       const hipError_t e = launch_block_bwd(a, s);
       if (e == hipErrorCooperativeLaunchTooLarge && d == 0) {      // refused before anything ran
