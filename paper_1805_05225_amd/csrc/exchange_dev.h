@@ -12,6 +12,33 @@ constexpr int kBufFlags = 0x00020000;   // raw buffer descriptor word 3 for gfx9
 // bit 31 = volatile, so the compiler re-issues the load in every poll
 constexpr int kSc1 = (int)(16u | 0x80000000u);
 
+// Floats that travel with a tag in bit 30 (partial sums scaled by 2^-32).  Below 1 in magnitude - 2^32 before the scaling - that
+// bit is 0 and the value travels as it is.  Anything else, infinities and NaN included, is folded into the patterns between 1 and 2:
+// sign, exponent and 15 bits of the mantissa, rounded.  One bit pattern either way, so value and tag still arrive together.  Exactly
+// 1 is no value: it says that the folded one follows (a writer that looks for wide values only after it has published).
+constexpr unsigned kOneBits = 0x3f800000u, kInfBits = 0x7f800000u;
+__host__ __device__ constexpr unsigned fold_wide(unsigned v) {
+  const unsigned m = v & 0x7fffffffu;
+  if (m < kOneBits) return v;
+  const unsigned t = m > kInfBits ? 0x40400000u : m - kOneBits + 0x80u;          // (every NaN: the quiet one)
+  return (v & 0x80000000u) | (kOneBits + 1u + (t >> 8));
+}
+__host__ __device__ constexpr unsigned unfold_wide(unsigned v) {
+  const unsigned m = v & 0x7fffffffu;
+  return m <= kOneBits ? v : (v & 0x80000000u) | (((m - kOneBits - 1u) << 8) + kOneBits);
+}
+static_assert(unfold_wide(fold_wide(0x3f7fffffu)) == 0x3f7fffffu && unfold_wide(fold_wide(0xbf800000u)) == 0xbf800000u, "in range, and 1");
+static_assert(unfold_wide(fold_wide(kInfBits)) == kInfBits && unfold_wide(fold_wide(0xff800000u)) == 0xff800000u, "infinities");
+static_assert(unfold_wide(fold_wide(0x7fffffffu)) > kInfBits && unfold_wide(fold_wide(0x7f800001u)) > kInfBits, "NaN");
+static_assert(unfold_wide(fold_wide(0x6f12347fu)) == 0x6f123400u && unfold_wide(fold_wide(0xef123480u)) == 0xef123500u, "16 bits, rounded");
+static_assert(fold_wide(0x7fffffffu) < 0x40000000u && fold_wide(0x7f7fffffu) < 0x40000000u && fold_wide(kOneBits) > kOneBits, "bit 30 is free, 1 is none");
+// the largest of m and the magnitudes of two floats; NaN if one of them is
+__device__ __forceinline__ float max_magnitude(float m, float a, float b) {
+  asm("v_maximum3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(m), "v"(a), "v"(b));
+  return m;
+}
+__device__ __forceinline__ bool is_wide(float m) { return !(m < 1.f); }        // of a magnitude
+
 __device__ __forceinline__ unsigned ld_relaxed(const unsigned* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -11,9 +11,14 @@
 // Shares stay inside column j, whose members are placed on one XCD; h and dz go to row j of the grid, across XCDs.
 //
 // Exchange as in persistent.hip: two slots per ring, and in every 8 bytes a tag bit - bit 30 of the second dword - of the step that wrote
-// them; 16 bytes of a share are four rows of one column.  Values that travel are scaled by 2^-32 where they are not bounded by 1 (shares, dz),
-// so that bit 30 is free for every value below 2^33; it is cleared before the tag is put in, so no value, NaN included, can make a reader wait for ever
-// (a NaN stays in its own unit's outputs).  Sums are taken in the order of the producers.
+// them; 16 bytes of a share are four rows of one column, 8 of h or dz four units of one row.  Values that travel are scaled by 2^-32 where
+// they are not bounded by 1 (shares, dz), which leaves that bit free below 2^32.  What is not in that range, NaN and infinities included, arrives all the same:
+//   shares  folded into the patterns between 1 and 2 (exchange_dev.h), in a second store that corrects the first;
+//   h       is bounded or NaN: a NaN in the tagged unit goes into its untagged neighbours of the same row, every product with that row is NaN either way;
+//   dz      has no patterns to spare in 16 bits: the tagged unit says "wide", and the reader fetches the row's values from DZ, which their
+//           writer has stored and released before it published.
+// (Looking for such values costs 0.15 us of a backward step, 4.38 -> 4.53 us over 140 steps with the launch, and nothing forward, 4.16 -> 4.11.)
+// Sums are taken in the order of the producers.
 // A slot may be written again because its readers have had to finish with it: h of step s + 2 needs shares of step s + 1 from column j,
 // those need h of step s + 1 from every block, and that needs the shares of step s from every work-group; likewise for the shares and backward.
 //
@@ -43,23 +48,34 @@ __device__ __forceinline__ unsigned tag_of(int step) { return ll_fwd_tag((unsign
 // Fetches N 16-byte pieces per lane, 4 KiB apart, until the first `count` (uniform) carry `tag` in both halves (bounded); the others read as zeros.
 // The first piece is asked for alone until it has turned: all of them in every poll would be 8 MB of reads a round.  No load is predicated
 // (what lies behind the pieces is ring memory too): with a branch per load the compiler waited for each before the next, 3.7 us instead of 1.
-template <int N>
+// wide(x) is called when all tags have turned and some lane's tagged dwords, tags off, hold something of 1 or more in magnitude; it returns
+// whether x, changed by it, will do.  Looked at together with the tags: a branch of its own on every step's way cost 0.04 us.
+template <bool WIDE, int N, typename F>
 __device__ __forceinline__ void await_pieces(u32x4 (&x)[N], int count, __amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned slot, unsigned tag, bool& dead,
-                                             unsigned* err, unsigned limit) {
-  const auto stale = [&](const u32x4& v) { return (((v[1] ^ tag) | (v[3] ^ tag)) & kTagBit) != 0u; };
+                                             unsigned* err, unsigned limit, F&& wide) {
+  const auto differs = [&](const u32x4& v) { return (v[1] ^ tag) | (v[3] ^ tag); };
+  // With the tag still in it a dword of 1 or more in magnitude reads as that, or, if the tag is set, as infinity or NaN.
+  const float one = __uint_as_float(kOneBits | tag);
+  unsigned clear = ~kTagBit;
   for (unsigned poll = 0, first = 1; !dead && count > 0; ++poll) {
-    bool again;
     if (first) {
-      again = __builtin_amdgcn_ballot_w64(stale(__builtin_amdgcn_raw_buffer_load_b128(rs, voff, slot, kSc1))) != 0ull;
-      if (!again) { first = 0; continue; }
+      if (__builtin_amdgcn_ballot_w64((differs(__builtin_amdgcn_raw_buffer_load_b128(rs, voff, slot, kSc1)) & kTagBit) != 0u) == 0ull) { first = 0; continue; }
     } else {
 #pragma unroll
       for (int it = 0; it < N; ++it) x[it] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, slot + it * 4096u, kSc1);
-      bool any = false;
+      unsigned bits = 0u;
 #pragma unroll
-      for (int it = 0; it < N; ++it) any |= stale(x[it]) & (it < count);
-      again = __builtin_amdgcn_ballot_w64(any) != 0ull;
-      if (!again) break;
+      for (int it = 0; it < N; ++it) bits |= differs(x[it]) & (it < count ? kTagBit : 0u);
+      float m[2] = {0.f, 0.f};
+#pragma unroll
+      for (int it = 0; it < N && WIDE; ++it) m[it & 1] = max_magnitude(m[it & 1], __uint_as_float(x[it][1]), __uint_as_float(x[it][3]));
+      const bool big = WIDE && !(max_magnitude(0.f, m[0], m[1]) < one);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64((bits != 0u) | big) == 0ull, 1)) break;
+      if (WIDE && __builtin_amdgcn_ballot_w64(bits != 0u) == 0ull) {
+#pragma unroll
+        for (int it = 0; it < N; ++it) { x[it][1] &= ~kTagBit; x[it][3] &= ~kTagBit; }
+        if (wide(x)) { clear = ~0u; break; }
+      }
     }
     if (poll >= limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
       st_relaxed(err, 1u);
@@ -69,18 +85,53 @@ __device__ __forceinline__ void await_pieces(u32x4 (&x)[N], int count, __amdgpu_
 #pragma unroll
   for (int it = 0; it < N; ++it) {
     const unsigned keep = it < count && !dead ? ~0u : 0u;
-    x[it] = (u32x4){x[it][0] & keep, x[it][1] & keep & ~kTagBit, x[it][2] & keep, x[it][3] & keep & ~kTagBit};
+    x[it] = (u32x4){x[it][0] & keep, x[it][1] & keep & clear, x[it][2] & keep, x[it][3] & keep & clear};
   }
 }
-__device__ __forceinline__ u32x4 tagged(const f32x4& v, unsigned tag) {
-  return (u32x4){__float_as_uint(v[0]), (__float_as_uint(v[1]) & ~kTagBit) | tag, __float_as_uint(v[2]), (__float_as_uint(v[3]) & ~kTagBit) | tag};
+// Shares in: folded ones unfolded; where one of them only says that it follows, the pieces are fetched again.
+__device__ __forceinline__ void await_shares(u32x4 (&x)[4], int count, __amdgpu_buffer_rsrc_t rs, unsigned voff, unsigned slot, unsigned tag, bool& dead,
+                                             unsigned* err, unsigned limit) {
+  await_pieces<true>(x, count, rs, voff, slot, tag, dead, err, limit, [&](u32x4 (&v)[4]) {
+    bool follows = false;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      follows |= it < count && ((v[it][1] & 0x7fffffffu) == kOneBits || (v[it][3] & 0x7fffffffu) == kOneBits);
+      v[it][1] = unfold_wide(v[it][1]);
+      v[it][3] = unfold_wide(v[it][3]);
+    }
+    return __builtin_amdgcn_ballot_w64(follows) == 0ull;
+  });
 }
-// Four neighbouring lanes' 16 bits in the first of them (the others get something else), tagged.
+// Shares out: clamped to 1, which is nothing to wait for, and looked at behind the stores.
+template <int NRT>
+__device__ __forceinline__ void publish_shares(f32x4 (&acc)[NRT][2], __amdgpu_buffer_rsrc_t rs, const unsigned (&off)[NRT], unsigned slot, unsigned tag,
+                                               int local) {
+  const auto store = [&](auto&& on_wire) __attribute__((always_inline)) {
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) {
+        const f32x4& a = acc[rt][ct];
+        const u32x4 v = {__float_as_uint(a[0]), on_wire(a[1]) | tag, __float_as_uint(a[2]), on_wire(a[3]) | tag};
+        if (local) __builtin_amdgcn_raw_buffer_store_b128(v, rs, off[rt], slot + ct * 256u, 1);
+        else __builtin_amdgcn_raw_buffer_store_b128(v, rs, off[rt], slot + ct * 256u, 16);
+      }
+  };
+  store([](float v) { return __float_as_uint(__builtin_amdgcn_fmed3f(v, -1.f, 1.f)); });       // (NaN: -1)
+  float m = 0.f;
+#pragma unroll
+  for (int f = 0; f < 2 * NRT; ++f) m = max_magnitude(m, acc[f >> 1][f & 1][1], acc[f >> 1][f & 1][3]);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(is_wide(m)) != 0ull, 0)) store([](float v) { return fold_wide(__float_as_uint(v)); });
+}
+// Four neighbouring lanes' 16 bits in the first of them (the others get something else), tagged.  H: a tagged value
+// that does not leave its bit free is NaN, and makes the two beside it NaN.
+template <bool H>
 __device__ __forceinline__ u32x2 four_lanes(unsigned x0, unsigned tag) {
   const unsigned x1 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x0, 0x101, 0xf, 0xf, true);
   const unsigned x2 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x0, 0x102, 0xf, 0xf, true);
   const unsigned x3 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x0, 0x103, 0xf, 0xf, true);
-  return (u32x2){x0 | (x1 << 16), ((x2 | (x3 << 16)) & ~kTagBit) | tag};
+  const unsigned nan = H ? (unsigned)((int)(x3 << 17) >> 31) : 0u;     // bit 14
+  return (u32x2){x0 | (x1 << 16) | nan, ((x2 | (x3 << 16)) & ~kTagBit) | tag};
 }
 __device__ __forceinline__ f32x4 mma(const u32x4& a, const u32x4& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -185,7 +236,7 @@ __global__ __launch_bounds__(256) void block_fwd_kernel(BlockFwdArgs a) {
     const unsigned tag = tag_of(tau), p_slot = (tau & 1) * part_slot;
     {                                                      // h of this range, into LDS
       u32x4 x[4 * NRT];
-      if (tau > 0) await_pieces<4 * NRT>(x, h_pieces, h_rs, h_in, ((tau - 1) & 1) * h_slot, tag_of(tau - 1), dead, a.sync, a.spin_limit);
+      if (tau > 0) await_pieces<false>(x, h_pieces, h_rs, h_in, ((tau - 1) & 1) * h_slot, tag_of(tau - 1), dead, a.sync, a.spin_limit, [](auto&) { return true; });
       else {
 #pragma unroll
         for (int p = 0; p < 4 * NRT; ++p) x[p] = (u32x4){0u, 0u, 0u, 0u};
@@ -210,20 +261,13 @@ __global__ __launch_bounds__(256) void block_fwd_kernel(BlockFwdArgs a) {
     __syncthreads();
     f32x4 acc[NRT][2];
     product<NRT>(acc, zs, w, lane);
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        const u32x4 v = tagged(acc[rt][ct], tag);
-        if (local) __builtin_amdgcn_raw_buffer_store_b128(v, p_rs, p_out[rt], p_slot + ct * 256u, 1);
-        else __builtin_amdgcn_raw_buffer_store_b128(v, p_rs, p_out[rt], p_slot + ct * 256u, 16);
-      }
+    publish_shares<NRT>(acc, p_rs, p_out, p_slot, tag, local);
     // the shares of this work-group's tasks: thread = (half of the rows, gate, unit), four rows
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       if (!on[k]) continue;
       u32x4 x[4];
-      await_pieces<4>(x, I, p_rs, p_in[k], p_slot, tag, dead, a.sync, a.spin_limit);
+      await_shares(x, I, p_rs, p_in[k], p_slot, tag, dead, a.sync, a.spin_limit);
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         zb[k][4 * (tid >> 7) + v][(tid >> 5) & 3][tid & 31] =
@@ -241,7 +285,7 @@ __global__ __launch_bounds__(256) void block_fwd_kernel(BlockFwdArgs a) {
         o[k] = lstm_cell(zh, zx[k], c[k]);
         c[k] = o[k].c; h[k] = o[k].h; started[k] = true;
       }
-      __builtin_amdgcn_raw_buffer_store_b64(four_lanes(started[k] ? f2bf_bits(h[k]) : 0u, tag), h_rs, h_out[k], (tau & 1) * h_slot, 16);
+      __builtin_amdgcn_raw_buffer_store_b64(four_lanes<true>(started[k] ? f2bf_bits(h[k]) : 0u, tag), h_rs, h_out[k], (tau & 1) * h_slot, 16);
     }
     const __amdgpu_buffer_rsrc_t y_rs = frame(a.y, t, (long)B * a.ldy * 2), hp_rs = frame(a.hprev, t, (long)B * a.ldh * 2), c_rs = frame(a.cs, t, (long)B * n * 4),
                                  g_rs = frame(a.gates, t, g_frame);
@@ -362,13 +406,14 @@ __global__ __launch_bounds__(256) void block_bwd_kernel(BlockBwdArgs a) {
       for (int k = 0; k < 2; ++k) {
         if (!on[k]) continue;
         u32x4 x[4];                                        // producers wave, wave + 4, ...
-        await_pieces<4>(x, (nb - wave + 3) / 4, p_rs, p_in[k], part_slot - p_slot, tag_of(sigma - 1), dead, a.sync, a.spin_limit);
+        await_shares(x, (nb - wave + 3) / 4, p_rs, p_in[k], part_slot - p_slot, tag_of(sigma - 1), dead, a.sync, a.spin_limit);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           red[k][wave][v][lane] = (__uint_as_float(x[0][v]) + __uint_as_float(x[1][v])) + (__uint_as_float(x[2][v]) + __uint_as_float(x[3][v]));
       }
     }
     __syncthreads();
+    const __amdgpu_buffer_rsrc_t d_rs = frame(a.DZ, sigma == Tn ? 0 : t, g_frame / 2);
     float dz[2][4] = {};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -377,14 +422,26 @@ __global__ __launch_bounds__(256) void block_bwd_kernel(BlockBwdArgs a) {
         Dh[k] = ((red[k][0][wave][lane] + red[k][1][wave][lane]) + (red[k][2][wave][lane] + red[k][3][wave][lane])) * (1.f / kScale);
       if (sigma == Tn) continue;
       if (t < L[k]) lstm_cell_grad(gi[k], gf[k], gg[k], go[k], c_new[k], c_prev[k], bf_bits2f(dy[k]) + Dh[k], Dc[k], dz[k]);
+      float v[4];
+      unsigned x[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {                        // (scaled by a power of two: exact)
-        const unsigned x = __float_as_uint(bf_bits2f(f2bf_bits(dz[k][g])) * kScale) >> 16;
-        __builtin_amdgcn_raw_buffer_store_b64(four_lanes(x, tag), z_rs, z_out[k], z_slot + g * (4 * NRT * 1024u), 16);
+        v[g] = bf_bits2f(f2bf_bits(dz[k][g])) * kScale;
+        x[g] = __float_as_uint(v[g]) >> 16;
       }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(is_wide(max_magnitude(max_magnitude(0.f, v[0], v[1]), v[2], v[3]))) != 0ull, 0)) {
+        const unsigned off = active[k] ? (unsigned)(b[k] * 4 * n + u[k]) * 2u : kParked;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          __builtin_amdgcn_raw_buffer_store_b16(f2bf_bits(dz[k][g]), d_rs, off, (unsigned)(g * n) * 2u, 16);
+          if ((lane & 3) == 3 && (x[g] & 0x7fffu) >= 0x3f80u) x[g] = 0x3f80u;        // "wide": 1 in magnitude
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) __builtin_amdgcn_raw_buffer_store_b64(four_lanes<false>(x[g], tag), z_rs, z_out[k], z_slot + g * (4 * NRT * 1024u), 16);
     }
     if (sigma == Tn) break;
-    const __amdgpu_buffer_rsrc_t d_rs = frame(a.DZ, t, g_frame / 2);
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       if (!on[k]) continue;
@@ -397,21 +454,32 @@ __global__ __launch_bounds__(256) void block_bwd_kernel(BlockBwdArgs a) {
     if (sigma + 1 < Tn) fetch(sigma + 1);
     {                                                      // dz of block i, into LDS
       u32x4 x[4 * NRT];
-      await_pieces<4 * NRT>(x, 4 * NRT, z_rs, (unsigned)i * (16u * NRT * 1024u) + tid * 16u, z_slot, tag, dead, a.sync, a.spin_limit);
+      await_pieces<true>(x, 4 * NRT, z_rs, (unsigned)i * (16u * NRT * 1024u) + tid * 16u, z_slot, tag, dead, a.sync, a.spin_limit, [&](u32x4 (&v)[4 * NRT]) {
+        // values that the ring cannot hold: from DZ, eight units of a row and gate
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        int at = lane;                                     // (opaque: what is computed from it stays in here instead of in registers all the way)
+        asm volatile("" : "+v"(at));
+#pragma unroll
+        for (int p = 0; p < 4 * NRT; ++p) {
+          if (!is_wide(max_magnitude(0.f, __uint_as_float(v[p][1]), __uint_as_float(v[p][3])))) continue;
+          const int piece = p * 4 + wave, ch = piece / NRT, row = a.row0 + (piece % NRT) * 16 + (at & 15), u0 = i * kBlk + (ch & 3) * 32 + (at >> 4) * 8;
+          unsigned e[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const unsigned off = row < B && u0 + k < n ? (unsigned)((row * 4 + (ch >> 2)) * n + u0 + k) * 2u : kParked;
+            e[k] = __float_as_uint(bf_bits2f(__builtin_amdgcn_raw_buffer_load_b16(d_rs, off, 0, kSc1)) * kScale) >> 16;
+          }
+          v[p] = (u32x4){e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+        }
+        return true;
+      });
 #pragma unroll
       for (int p = 0; p < 4 * NRT; ++p) zs[p * 256 + tid] = x[p];
     }
     __syncthreads();
     f32x4 acc[NRT][2];
     product<NRT>(acc, zs, w, lane);
-#pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const u32x4 v = tagged(acc[rt][c], tag);
-        if (local) __builtin_amdgcn_raw_buffer_store_b128(v, p_rs, p_out[rt], p_slot + c * 256u, 1);
-        else __builtin_amdgcn_raw_buffer_store_b128(v, p_rs, p_out[rt], p_slot + c * 256u, 16);
-      }
+    publish_shares<NRT>(acc, p_rs, p_out, p_slot, tag, local);
   }
   __syncthreads();
 #pragma unroll

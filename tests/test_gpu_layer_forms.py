@@ -82,3 +82,45 @@ def test_state_in_place(dt, T, B, n, direction):
     assert not Bn.sync_status(s["workspace"])
     for name, got, ref in (("y", y, s["y"]), ("hT", h, s["hT"]), ("cT", cc, s["cT"])):
         check(name, got, host(ref), TOL[dt])
+
+
+# Outside the range of what the loops exchange: the result is the per-step kernels', which exchange nothing between work-groups of a launch.
+@pytest.mark.parametrize("what", ["nan_x", "nan_W", "large_W", "inf_dy", "large_dy"])
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 4, 9, 1040), ("bf16", 3, 33, 2048)])
+def test_values_outside_the_exchange_range(dt, T, B, n, what):
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(n)
+    c = P.rnd_case(rng, T, B, 24, n, 1, None, dt, scale=2.0 / np.sqrt(n))
+    if what == "nan_x":
+        c["x"][1, 1, 0] = c["x"][1, 2, 3] = np.nan
+    elif what == "nan_W":
+        c["W_h"][0, 5, 7] = np.nan
+    elif what == "large_W":
+        # Pre-activations of the i, f, o gates beyond 2^33, of either sign but far from 0, where 16 bits of a share would decide the
+        # gate: h and a column's weights do not change sign (g = tanh(4 + ...), c > 0).
+        for k in ("h0", "c0"):
+            c[k] = np.abs(c[k])
+        c["b"][0, 2 * n:3 * n] += 4
+        for gate in (0, 1, 3):
+            cols = slice(gate * n + gate % 2, (gate + 1) * n, 3)
+            c["W_h"][0, :, cols] = np.abs(c["W_h"][0, :, cols]) * 2.0 ** 44
+            c["W_h"][0, :, cols][:, ::2] *= -1
+    elif what == "inf_dy":
+        c["dy"][2, 1, 3] = np.inf
+    else:                                                 # dz and partial sums of Dh beyond 2^33 in some rows, in tagged units and others
+        c["dy"][:, 1::4, 3::4] *= 2.0 ** 40
+        c["dy"][:, 2::8, 1::8] *= -2.0 ** 45
+    for direction in (1, -1):
+        f, g = P.run_gpu(c, dt, False, direction)
+        fs, gs = P.run_gpu(c, dt, False, direction, flags=Bn.FLAG_PER_STEP)
+        for name, got, ref in [(k, f[k], fs[k]) for k in ("y", "c", "hT", "cT")] + [(k, g[k], gs[k]) for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0")]:
+            got, ref = host(got), host(ref)
+            print("  ", name, "not finite: %d" % (~np.isfinite(ref)).sum(), flush=True)
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(got)], ref[np.isinf(ref)]), name
+            ok = np.isfinite(ref)
+            # by row where there are rows: the large ones must not hide the others
+            ax = -1 if name in ("dx", "dh0", "dc0", "c", "cT") else None
+            size = np.abs(np.where(ok, ref, 0)).max(axis=ax, keepdims=True)
+            err = np.abs(np.where(ok, got, 0) - np.where(ok, ref, 0)) / np.maximum(size, 1e-30)
+            assert err.max() < TOL[dt], (name, err.max())
