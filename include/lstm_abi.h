@@ -42,8 +42,8 @@
  *   - NaN, infinities and large values follow the arithmetic above, row by row, with one exception: the bfloat16 loops of
  *     128 < n <= 1024 exchange h and sums of gradients between work-groups in a form that has no room for NaN, nor for gradient
  *     sums of 2^33 and more.  There such a value may make the loop's bounded wait expire (lstm_sync_status reports it);
- *     LSTM_FLAG_PER_STEP has no such limit.  The wide bfloat16 loops (n > 1024) carry values of 2^32 and more between work-groups with
- *     16 significant bits.
+ *     LSTM_FLAG_PER_STEP has no such limit.  The float loops of n <= 1024 and the wide bfloat16 loops (n > 1024) carry sums of 2^32 and more
+ *     between work-groups with 16 significant bits.
  *   - Return value: 0 on success, a negative lstm_status otherwise.  Arguments are validated on
  *     the host before the first HIP call, so every argument error is reported without a GPU.
  *     Nothing throws or aborts across this boundary.  LSTM_OK says that the work was enqueued; it does not cover

@@ -225,6 +225,7 @@ bool persist_fwd_f32_fits(const PFwdArgs& a);
 struct PBwdDir {
   const uint4* Wb;    // as launch_prep_bwd_ll writes it
   uint4* ring0; uint4* ring1;
+  uint4* wide;        // float storage: scratch as large as a ring
   const float* gates; const float* cs; const float* c0;
   const void* dy; long lddy;
   void* DZ;           // [T][B][4n]

@@ -27,7 +27,7 @@ struct Plan {
   long ldh;
   size_t res_gates, res_hprev, res_dir_stride, reserve_bytes;
   // workspace
-  size_t ws_Wf, ws_Wb, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
+  size_t ws_Wf, ws_Wb, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_dzwide, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
       ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool small;                               // narrow layer: loop_small.hip
@@ -117,6 +117,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_hfrag1 = take(p->hfrag_bytes);
   p->ws_dzfrag0 = take(infer ? 0 : p->dzfrag_bytes);
   p->ws_dzfrag1 = take(infer ? 0 : p->dzfrag_bytes);
+  p->ws_dzwide = take(!infer && part32 ? D * bwd_f32_ring_bytes(d->B, d->n) : 0);
   p->ws_hstate = take(D * B * n * 4);
   p->ws_cstate = take(D * B * n * 4);
   p->ws_Dh = take(infer ? 0 : D * B * n * 4);
@@ -694,6 +695,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         bd.Wb = (const uint4*)(ws + p.ws_Wb + d * wb_dir);
         bd.ring0 = (uint4*)(ws + p.ws_dzfrag0 + d * ring_dir);
         bd.ring1 = (uint4*)(ws + p.ws_dzfrag1 + d * ring_dir);
+        bd.wide = use_ll32 ? (uint4*)(ws + p.ws_dzwide + d * ring_dir) : nullptr;
         bd.gates = (const float*)(rs + d * p.res_dir_stride + p.res_gates);
         bd.cs = (const float*)c + d * T * B * n;
         bd.c0 = c0 ? (const float*)c0 + d * B * n : nullptr;

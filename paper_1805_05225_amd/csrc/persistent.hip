@@ -1717,8 +1717,8 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
 // while the other's h travels.
 // The K axis is split over the four wavefronts (chunks of 16 k, wavefront w takes chunks w, w + 4, ...), their accumulators
 // meet in LDS, a thread updates one cell per row tile, and two neighbouring units are published as ONE 8-byte unit of the
-// ring: two float h values, the tag in bit 30 of the second (|h| < 1 leaves the top exponent bit 0, as bit 14 of a
-// bfloat16 value in the other kernels).  The ring is the per-step kernel's fragment-ordered h buffer [row tile][chunk][lane]
+// ring: two float h values, the tag in bit 30 of the second (|h| <= 1 leaves the top exponent bit 0, as bit 14 of a
+// bfloat16 value in the other kernels; a NaN there goes into the first).  The ring is the per-step kernel's fragment-ordered h buffer [row tile][chunk][lane]
 // x 16 bytes, a lane's 16 bytes being two such units, so the reader of the other kernels applies unchanged.  An initial
 // hidden state never enters the ring (it is not bounded by 1): rows publish zeros until their first frame is done, and
 // h0 W_h has been added to that frame's pre-activations.
@@ -1920,7 +1920,9 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
       {                               // the recurrence's critical store goes out first (16: agent scope, written through)
         const unsigned h_pub = started[k] ? __float_as_uint(h[k]) : 0u;
         const unsigned h_odd = (unsigned)__builtin_amdgcn_mov_dpp((int)h_pub, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]: the neighbour's h
-        const u32x2 unit = {h_pub, h_odd | (ll_fwd_tag((unsigned)step + 1u) << 30)};
+        // h is below 1 in magnitude, or NaN: a NaN in the tagged half makes its neighbour of the same row NaN instead, as every product with the row is
+        const unsigned nan = (unsigned)((int)(h_odd << 1) >> 31);      // bit 30
+        const u32x2 unit = {h_pub | nan, (h_odd & ~kLLFwdTagBit) | (ll_fwd_tag((unsigned)step + 1u) << 30)};
         const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((step & 1) ? d.ring0 : d.ring1), 0, ring_bytes, kBufFlags);
         const unsigned off = publishes ? (unsigned)rows.tile[k] * (unsigned)nkc * 1024u + pub_in_tile : kParked;
         if (local) __builtin_amdgcn_raw_buffer_store_b64(unit, ro, off, 0, 1);
@@ -1956,7 +1958,10 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 // per destination tile of 16 units, the accumulator tile as it stands: a lane's four floats (rows 4g .. 4g+3 of one output)
 // are two 8-byte units, the tag bit 30 of each unit's second float.  Partial sums are not bounded by 1, so they travel scaled
 // by 2^-32 (the packed W_h^T carries the factor; the consumer multiplies its sum by 2^32): bit 30 is then 0 for every partial
-// sum below 2^33 in magnitude, and no other bit of a value above 2^-94 changes.  A consumer adds the blocks of its tile from
+// sum below 2^32 in magnitude, and no other bit of a value above 2^-94 changes.  Larger ones, infinities and NaN travel folded
+// (exchange_dev.h): a half step whose largest dz and W_h could make one looks at each sum, the others at none (config 2's loop 525 -> 536 us; with a
+// look at every sum 548, with a second copy of the products for such half steps 550).  To a consumer a folded value looks like a stale
+// tag, and the pass that fetches such loads again unfolds it.  A consumer adds the blocks of its tile from
 // all producers (1 KiB each, one 16-byte load per lane: the producer's accumulator layout), wavefront w taking producers
 // w, w + 4, ..., and the four sums meet in LDS.
 // Ring per direction and slot: [row tile][destination tile][producer tile] x 1 KiB.  K axis of the product: gate column
@@ -1988,6 +1993,18 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) w[ci][s4] = load_to_agpr((const uint4*)d.Wb + ((((long)J * 4 + wave) * NCT + ci) * 4 + s4) * 64 + lane);
   agpr_loads_done();
+  float w_bound = 0.f;                                     // 64 times the slice's largest weight, over all lanes: a sum of products is no larger than
+#pragma unroll                                             // this times the largest dz
+  for (int ci = 0; ci < NCT; ++ci)
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) {
+      asm volatile("" : "+a"(w[ci][s4]));                  // (read behind the wait, not in front of it)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) w_bound = max_magnitude(w_bound, __uint_as_float(w[ci][s4][e]), __uint_as_float(w[ci][s4][e + 1]));
+    }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) w_bound = max_magnitude(w_bound, __shfl_xor(w_bound, o), 0.f);
+  w_bound *= 64.f;
   const int local = NCT <= 8 ? group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit) : 0;      // (more than 32 members never are)
 
   // pointwise: row r16 of each row tile, unit u of the tile's 16
@@ -2077,9 +2094,9 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       if (st > 0) {                                        // the partial sums of Dh that the step before published
         const RingReader rd = reader(st, k);
         const unsigned tagw = rd.tag << 16;
+        const float one = __uint_as_float(kOneBits | tagw);      // (what a magnitude of 1 reads as with the tag in it)
         float ps[4] = {ps_c[0], ps_c[1], ps_c[2], ps_c[3]};
         unsigned long long redo = redo_c;
-        auto add = [&](int, const u32x4& v) __attribute__((always_inline)) { add_to(ps, v); };
         if (!have_c) {
           // nothing was collected ahead: a slab of one row tile has no other half step to hide behind (what it consumes
           // is published by the half step before it), and the collecting step follows no products
@@ -2090,11 +2107,16 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           for (int it = 0; it < NCT; ++it) x[it] = rd.load_it(it);
 #pragma unroll
           for (int it = 0; it < NCT; ++it) {
-            if (__builtin_amdgcn_ballot_w64(rd.tag_diff(x[it], it, tagw) != 0u) == 0ull) add(it, x[it]);
+            const bool wide = !(max_magnitude(0.f, __uint_as_float(x[it][1]), __uint_as_float(x[it][3])) < one);
+            if (__builtin_amdgcn_ballot_w64((rd.tag_diff(x[it], it, tagw) != 0u) | wide) == 0ull) add_to(ps, x[it]);
             else { redo |= 1ull << it; PROF_REDO(1) }
           }
         }
-        if (redo) rd.template fix_up_batch<NCT>(redo, dead, add);
+        if (redo)
+          rd.template fix_up_batch<NCT>(redo, dead, [&](int, const u32x4& v) {
+            ps[0] += __uint_as_float(v[0]); ps[1] += __uint_as_float(unfold_wide(v[1] & ~kLLFwdTagBit));
+            ps[2] += __uint_as_float(v[2]); ps[3] += __uint_as_float(unfold_wide(v[3] & ~kLLFwdTagBit));
+          });
         // a lane's sums: rows 4 (lane / 16) + v of output lane % 16
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[wave][4 * (lane >> 4) + v][lane & 15] = ps[v];
@@ -2127,6 +2149,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
         const unsigned tagw_n = rn.tag << 16;
         float psn[4] = {0.f, 0.f, 0.f, 0.f};
         unsigned stale_n = 0u;
+        float largest_n = 0.f;
         if (collect) {
 #pragma unroll
           for (int it = 0; it < kWin; ++it) x[it] = rn.load_it(it);
@@ -2144,11 +2167,22 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
         const unsigned pub0 = (unsigned)(((rows.tile[k] * ntile + wave) * ntile + J) * 1024 + lane * 16);
         // The accumulator of column tile ci is published behind the MFMAs of column tile ci + 1: by then its last MFMA has long
         // finished (the compiler does not see the MFMAs in the assembly text and inserts no wait states for their results).
+        // Could a sum of 64 products not be below 1?  Asked of the operands, once per half step.  Then the same code leaves the sums as they
+        // are in this work-group's part of d.wide, and they are folded on their way from there.
+        float largest = 0.f;
+#pragma unroll
+        for (int s = 0; s < 16; s += 2) largest = max_magnitude(largest, av[s], av[s + 1]);
+        // (scalar arithmetic by hand: a choice between two descriptors is applied lane by lane)
+        const unsigned long long which = 0ull - (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(__builtin_amdgcn_ballot_w64(is_wide(largest * w_bound)) != 0ull);
+        const bool wide = which != 0ull;
+        const unsigned long long ring = (unsigned long long)((st & 1) ? d.ring1 : d.ring0);
+        const __amdgpu_buffer_rsrc_t to = __builtin_amdgcn_make_buffer_rsrc((void*)(ring ^ ((ring ^ (unsigned long long)d.wide) & which)), 0, ring_bytes, kBufFlags);
+        const unsigned mark = tag_hi & ~(unsigned)which;
         auto publish = [&](int ci, const f32x4& acc) __attribute__((always_inline)) {
-          const u32x4 unit = {__float_as_uint(acc[0]), __float_as_uint(acc[1]) | tag_hi, __float_as_uint(acc[2]), __float_as_uint(acc[3]) | tag_hi};
+          const u32x4 unit = {__float_as_uint(acc[0]), __float_as_uint(acc[1]) | mark, __float_as_uint(acc[2]), __float_as_uint(acc[3]) | mark};
           const unsigned off = wave + 4 * ci < ntile ? pub0 + (unsigned)(4 * ci) * (unsigned)ntile * 1024u : 0x7ff00000u;
-          if (local) __builtin_amdgcn_raw_buffer_store_b128(unit, ro, off, 0, 1);
-          else __builtin_amdgcn_raw_buffer_store_b128(unit, ro, off, 0, 16);    // 16: agent scope, written through
+          if (local) __builtin_amdgcn_raw_buffer_store_b128(unit, to, off, 0, 1);
+          else __builtin_amdgcn_raw_buffer_store_b128(unit, to, off, 0, 16);    // 16: agent scope, written through
         };
         f32x4 acc2[2];
 #pragma unroll
@@ -2163,16 +2197,29 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           if (collect) {                                   // (behind the MFMAs just issued: they run while this does)
             wait_loads_but((NCT - 1 - ci) < (kWin - 1) ? (NCT - 1 - ci) : (kWin - 1), x[ci % kWin]);     // the younger loads: the window's others
             stale_n |= rn.tag_diff(x[ci % kWin], ci, tagw_n);      // looked at once, behind the last load
+            largest_n = max_magnitude(largest_n, __uint_as_float(x[ci % kWin][1]), __uint_as_float(x[ci % kWin][3]));
             add_to(psn, x[ci % kWin]);
             if (ci + kWin < NCT) x[ci % kWin] = rn.load_it(ci + kWin);
           }
         }
         mfma_settle(acc2[(NCT - 1) & 1]);
         publish(NCT - 1, acc2[(NCT - 1) & 1]);
+        if (__builtin_expect(wide, 0)) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a wavefront reads what it stored itself, past its L1)
+#pragma unroll 1
+          for (int c = wave; c < ntile; c += 4) {
+            const unsigned off = pub0 + (unsigned)(c - wave) * (unsigned)ntile * 1024u;
+            u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(to, off, 0, kSc1);
+            v[1] = fold_wide(v[1]) | tag_hi;
+            v[3] = fold_wide(v[3]) | tag_hi;
+            if (local) __builtin_amdgcn_raw_buffer_store_b128(v, ro, off, 0, 1);
+            else __builtin_amdgcn_raw_buffer_store_b128(v, ro, off, 0, 16);
+          }
+        }
         if (collect) {
           // The tags are looked at once, here: a test and a branch per load cost a twentieth of the step.  A stale tag anywhere
           // (a tenth of the half steps): the sums are dropped and the next half step fetches every load again.
-          const bool again = __builtin_amdgcn_ballot_w64(stale_n != 0u) != 0ull;
+          const bool again = __builtin_amdgcn_ballot_w64((stale_n != 0u) | !(largest_n < __uint_as_float(kOneBits | tagw_n))) != 0ull;
           if (again) { PROF_REDO(NCT) }
 #pragma unroll
           for (int v = 0; v < 4; ++v) ps_c[v] = again ? 0.f : psn[v];

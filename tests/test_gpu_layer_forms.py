@@ -86,7 +86,7 @@ def test_state_in_place(dt, T, B, n, direction):
 
 # Outside the range of what the loops exchange: the result is the per-step kernels', which exchange nothing between work-groups of a launch.
 @pytest.mark.parametrize("what", ["nan_x", "nan_W", "large_W", "inf_dy", "large_dy"])
-@pytest.mark.parametrize("dt,T,B,n", [("bf16", 4, 9, 1040), ("bf16", 3, 33, 2048)])
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 4, 9, 1040), ("bf16", 3, 33, 2048), ("f32", 4, 9, 331), ("f32", 3, 40, 200), ("f32", 4, 17, 1000), ("f32", 3, 70, 1001)])
 def test_values_outside_the_exchange_range(dt, T, B, n, what):
     from paper_1805_05225_amd import binding as Bn
     P.Bn = Bn
