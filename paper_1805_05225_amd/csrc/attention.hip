@@ -464,7 +464,7 @@ int lstm_readout(int flags, int B, int R, const void* s, int64_t ld_s, int n, co
   uint16_t* cat = (uint16_t*)(Wf + up256(frag_bytes(R, Kp)));
   float* z = (float*)((char*)cat + up256(std::max((size_t)B * Kp * 2, frag_bytes(B, Kp))));
   float* parts = (float*)((char*)z + up256((size_t)B * R * 4));
-  if (!(flags & LSTM_FLAG_WEIGHTS_PACKED) && (launch_pad_rows(W_r, Wp, R, K, (int)Kp, st) != hipSuccess || launch_pack_rows_frag(W_r, Wf, R, K, st) != hipSuccess)) {
+  if (!(flags & LSTM_FLAG_WEIGHTS_PACKED) && launch_pack_rows_both(W_r, Wp, Wf, R, K, (int)Kp, st) != hipSuccess) {
     (void)hipGetLastError();
     return LSTM_ERR_HIP;
   }

@@ -415,8 +415,8 @@ hipError_t launch_step_cell(const void* Acat, const void* Wcell, const float* bi
 hipError_t launch_pack_cell_frag(const void* W_x, const void* W_h, void* out, int n_in, int n_in_pad, int n, int K, int ndir, hipStream_t s);
 hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void* Wfrag, const float* bias, const float* c_in, float* h_out,
                            float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n_in, int n_in_pad, int n, int ndir, hipStream_t s);
-// out[B][R] = bf16(max(0, [x0 | x1 | x2] W^T + bias)), W in the fragment order of launch_pack_rows_frag, A scratch of frag_bytes(B, K)
-hipError_t launch_pack_rows_frag(const void* W, void* out, int R, int K, hipStream_t s);
+// out[B][R] = bf16(max(0, [x0 | x1 | x2] W^T + bias)), W in the fragment order of launch_pack_rows_both, A scratch of frag_bytes(B, K)
+hipError_t launch_pack_rows_both(const void* W, void* rows, void* frag, int R, int K, int Kp, hipStream_t s);
 hipError_t launch_few_readout(const void* x0, long ld0, int k0, const void* x1, long ld1, int k1, const void* x2, long ld2, int k2, void* A,
                               const void* Wfrag, const float* bias, void* out, long ldo, int B, int R, hipStream_t s);
 inline size_t frag_bytes(long rows, long K) { return (size_t)((rows + 15) / 16) * ((K + 31) / 32) * 1024; }

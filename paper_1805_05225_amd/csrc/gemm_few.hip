@@ -336,19 +336,22 @@ __global__ __launch_bounds__(256) void pack_cell_frag_kernel(const uint16_t* Wx,
   }
 }
 
-// rows of W[R][K] -> fragment order
-__global__ void pack_rows_frag_kernel(const uint16_t* W, uint4* out, int R, int K, int nkc, long total) {
+// W[R][K] twice from one read: rows padded with zeros to Kp columns (a multiple of 8), and in fragment order.  Threads run along the rows.
+__global__ __launch_bounds__(256) void pack_rows_both_kernel(const uint16_t* W, uint4* rows, uint4* frag, int R, int K, int Kp, int nkc, long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= total) return;
-  const int lane = (int)(idx & 63), kc = (int)((idx >> 6) % nkc);
-  const long row = ((idx >> 6) / nkc) * 16 + (lane & 15);
-  uint16_t v[8];
+  const int kk = (int)(idx % (nkc * 4)), k = kk * 8;           // total = rows of whole tiles x groups of eight columns
+  const long row = idx / (nkc * 4);
+  uint4 o = make_uint4(0, 0, 0, 0);
+  if (row < R && k + 8 <= K) o = *(const uint4_u*)(W + row * K + k);
+  else if (row < R) {
+    uint16_t v[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = kc * 32 + (lane >> 4) * 8 + e;
-    v[e] = row < R && k < K ? W[row * K + k] : (uint16_t)0;
+    for (int e = 0; e < 8; ++e) v[e] = k + e < K ? W[row * K + k + e] : (uint16_t)0;
+    o = frag_pack(v);
   }
-  out[idx] = frag_pack(v);
+  if (row < R && k < Kp) rows[(row * Kp + k) / 8] = o;
+  frag[((row >> 4) * nkc + (kk >> 2)) * 64 + (kk & 3) * 16 + (row & 15)] = o;
 }
 
 // [x0 | x1 | x2] in fragment order (grid y: direction); the rows that fill up the last tile are zero
@@ -398,9 +401,10 @@ hipError_t launch_pack_cell_frag(const void* W_x, const void* W_h, void* out, in
                      (const uint16_t*)W_h, (uint4*)out, n_in, n_in_pad, n, nkc, ntile);
   return hipGetLastError();
 }
-hipError_t launch_pack_rows_frag(const void* W, void* out, int R, int K, hipStream_t s) {
-  const long total = (long)cdiv(R, 16) * cdiv(K, 32) * 64;
-  hipLaunchKernelGGL(pack_rows_frag_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const uint16_t*)W, (uint4*)out, R, K, cdiv(K, 32), total);
+hipError_t launch_pack_rows_both(const void* W, void* rows, void* frag, int R, int K, int Kp, hipStream_t s) {
+  const int nkc = cdiv(K, 32);
+  const long total = (long)cdiv(R, 16) * 16 * nkc * 4;
+  hipLaunchKernelGGL(pack_rows_both_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const uint16_t*)W, (uint4*)rows, (uint4*)frag, R, K, Kp, nkc, total);
   return hipGetLastError();
 }
 
