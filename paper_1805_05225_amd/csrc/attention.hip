@@ -334,22 +334,22 @@ hipError_t launch_concat3(const uint16_t* x0, long ld0, int k0, const uint16_t* 
 
 inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
-// C[M][N] float = A[M][lda] (bf16) . W[N][ldw]^T (bf16, a row per output) + bias, K cut into ranges when the product has
-// few output tiles; `parts` holds ksplit * M * N floats.
+// C[M][N] float = A[M][lda] (bf16) . W[N][ldw]^T (bf16, a row per output) + bias; `parts` (may be NULL): room for the parts of K's ranges
 hipError_t linear_rows(const void* A, long lda, const void* W, long ldw, const float* bias, float* C, int M, int N, int K, float* parts,
-                       int ksplit, hipStream_t s) {
+                       size_t parts_bytes, hipStream_t s) {
   GemmArgs g = {};
   g.A = A; g.B = W; g.C = C; g.bias = bias; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldw; g.ldc = N;
   g.nz = 1; g.nseg = 1; g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = true; g.out_bf16 = false;
   const auto vec = [](const void* p, long ld) { int v = 16; while (v > 2 && (((uintptr_t)p % v) || ((ld * 2) % v))) v >>= 1; return v; };
   g.vecA = vec(A, lda); g.vecB = vec(W, ldw);
   if (gemm_skinny_ok(g)) return launch_gemm_skinny(g, false, s);       // few rows: one work-group per tile walks the whole K
-  if (ksplit > 1 && gemm_nt_ok(g)) { g.ksplit = ksplit; g.parts = parts; }
+  g.parts = parts; g.parts_bytes = parts_bytes;
   return launch_gemm(g, s);
 }
-int ranges_for(int M, int N, int K) {
-  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256), stages = (K + 63) / 64;
-  return (int)std::max(1L, std::min(std::min(256 / std::max(tiles, 1L), stages / 4), 8L));
+// Ranges of K pay in the readout's product (N = 1000, K = 3620: 1025 rows 59.5 -> 39.4 us a call, 1500 rows 62.9 -> 43.9, 3000 rows 70.3 -> 70.6)
+// and not in the attention's (K = 1000: 1500 rows 77.9 -> 79.1, 3000 rows 121.7 -> 127.9).
+size_t readout_parts(int B, int R, long Kp) {
+  return B > kSkinnyMaxRows && gemm_tile_small(B, R, 1) ? gemm_tile_parts_bytes(B, R, Kp, 1, 1) : 0;
 }
 
 }  // namespace
@@ -372,8 +372,7 @@ int lstm_attention_query(const lstm_att_desc* d, uint64_t* workspace_bytes) {
   if (rc) return rc;
   if (!workspace_bytes) return LSTM_ERR_NULL;
   const size_t B = (size_t)d->Q * d->beam;
-  const int ks = ranges_for((int)B, d->A, d->n);
-  *workspace_bytes = 256 + up256(B * d->A * 4) + up256(B * d->S * 4) + (ks > 1 ? up256((size_t)ks * B * d->A * 4) : 0) + up256(B * d->S * 4);
+  *workspace_bytes = 256 + up256(B * d->A * 4) + up256(B * d->S * 4) + up256(B * d->S * 4);
   return LSTM_OK;
 }
 
@@ -397,9 +396,7 @@ int lstm_attention_step(const lstm_att_desc* d, const void* enc, const void* enc
   char* ws = (char*)(((uintptr_t)workspace + 255) / 256 * 256);
   float* s_tr = (float*)ws;
   float* e = (float*)(ws + up256((size_t)B * d->A * 4));
-  float* parts = (float*)(ws + up256((size_t)B * d->A * 4) + up256((size_t)B * d->S * 4));
-  const int ks = ranges_for(B, d->A, d->n);
-  if (linear_rows(s, ld_s, W_s, d->n, b_s, s_tr, B, d->A, d->n, parts, ks, st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
+  if (linear_rows(s, ld_s, W_s, d->n, b_s, s_tr, B, d->A, d->n, nullptr, 0, st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
   if ((long)d->Q * d->S < 512)          // fewer work-groups than the device has compute units in the form for many sentences
     hipLaunchKernelGGL(att_energy_few_kernel, dim3(d->S, d->Q, (d->beam + kFewHyp - 1) / kFewHyp), dim3(256), 0, st, (const uint16_t*)enc_ctx, s_tr,
                        accum_in, w_fb, b_fb, v, b_e, src_lens, e, d->S, d->Q, d->beam, d->A);
@@ -433,9 +430,8 @@ int lstm_readout_query(int B, int R, int n, int n_trg, int E, uint64_t* workspac
   const int rc = readout_dims(B, R, n, n_trg, E);
   if (rc) return rc;
   const long Kp = readout_kpad(n, n_trg, E);
-  const int ks = ranges_for(B, R, (int)Kp);
   *workspace_bytes = 256 + up256((size_t)R * Kp * 2) + up256(frag_bytes(R, Kp)) + up256(std::max((size_t)B * Kp * 2, frag_bytes(B, Kp))) +
-                     up256((size_t)B * R * 4) + (ks > 1 ? up256((size_t)ks * B * R * 4) : 0);
+                     up256((size_t)B * R * 4) + up256(readout_parts(B, R, Kp));
   return LSTM_OK;
 }
 
@@ -486,7 +482,7 @@ int lstm_readout(int flags, int B, int R, const void* s, int64_t ld_s, int n, co
       return LSTM_OK;
     }
   }
-  if (linear_rows(cat, Kp, Wp, Kp, b_r, z, B, R, (int)Kp, parts, ranges_for(B, R, (int)Kp), st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
+  if (linear_rows(cat, Kp, Wp, Kp, b_r, z, B, R, (int)Kp, parts, readout_parts(B, R, Kp), st) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
   const long total = (long)B * R;
   hipLaunchKernelGGL(relu_bf16_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, z, (uint16_t*)out, B, R, (long)ld_out);
   if (hipGetLastError() != hipSuccess) return LSTM_ERR_HIP;

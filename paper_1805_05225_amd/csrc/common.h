@@ -76,17 +76,15 @@ struct GemmArgs {
   const int* lens; int Bt; int T;
   bool a_kcontig, b_kcontig;
   bool in_bf16, out_bf16;
-  // Row maps (the fast kernels and the generic one; not the few-rows kernel, and not together with `parts` or ksplit there):
+  // Row maps (the fast kernels and the generic one; not the few-rows kernel, and not together with `parts` there):
   const int* a_rows; const int* c_rows;   // k-contiguous A: logical row r of A / C lives at physical row a_rows[r] / c_rows[r]
   int a_phys_rows;                        // rows of A in memory when a_rows is given
   const int* m_dev; const int* k_dev;     // M / K read from device memory (capped by M / K above, which size the grid)
   const int* k_rows; int k_phys_rows;     // both operands k-major: k -> row of A and of B in memory; rows each holds in memory
                                           // (A k-contiguous, B k-major: k_phys_rows > 0 = rows of B, where A's rows are padded up to K)
-  int ksplit;                             // > 1 (gemm_nt.hip's kernels): K cut into that many ranges ...
-  float* parts;                           // ... every range stores its part there (nz * ksplit * M * ldc floats, no c_rows) and a
-                                          // second kernel writes C (+)= their sum (`accumulate` honoured)
-  SumList* sums;                          // not NULL: the parts' sum is left for the caller's launch_sums (gemm_tile.hip, gemm_float.hip)
-  size_t parts_bytes;                     // what `parts` holds (gemm_tile.hip and gemm_float.hip, which plan their own ranges)
+  float* parts; size_t parts_bytes;       // gemm_tile.hip and gemm_float.hip, which plan their own ranges of K: room for the ranges' parts (their bytes,
+                                          // or K stays whole); a second kernel writes C (+)= their sum (`accumulate` honoured)
+  SumList* sums;                          // not NULL: that sum is left for the caller's launch_sums
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for problems with both operands k-contiguous, 16-byte aligned rows and K % 8 == 0

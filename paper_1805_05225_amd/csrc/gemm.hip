@@ -315,7 +315,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
 template <typename T, typename TC>
 hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
-  if (g.ksplit > 1) return hipErrorInvalidValue;
   dim3 grid(tiles_m * tiles_n, g.nz), block(kThreads);
   if (g.a_kcontig && !g.b_kcontig) hipLaunchKernelGGL((gemm_kernel<T, TC, true, false, false>), grid, block, 0, s, g);
   else if (g.a_kcontig && g.b_kcontig) hipLaunchKernelGGL((gemm_kernel<T, TC, true, true, false>), grid, block, 0, s, g);

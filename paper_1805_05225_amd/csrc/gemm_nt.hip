@@ -28,8 +28,6 @@ struct NtArgs {
   const int* k_rows; int k_phys_rows;     // k-major kernel: k -> row of A and B in memory (NULL: identity), rows in memory
   const int* m_dev; const int* k_dev;     // device-resident M / K (NULL: use M / K above)
   int a_phys_rows;                        // rows of A in memory when a_rows is given
-  int ksplit;                             // > 1: K is cut into that many ranges, each stores its part at parts + (z * ksplit + range) * sPart
-  float* parts; long sPart;               // (layout of C)
   int blocked;                            // tile raster: 1 = blocks of kSupM x kSupN tiles per XCD, 0 = bands of 8 tile columns
 };
 
@@ -41,7 +39,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 constexpr int kBufFlags = 0x00020000;   // raw buffer descriptor word 3 for gfx9-family devices
 
 // What every kernel variant needs to know about its tile.
-struct TileCoord { int M, K, m0, n0, z, ks, ksplit, pos; bool live; };
+struct TileCoord { int M, K, m0, n0, z, pos; bool live; };
 __device__ __forceinline__ TileCoord tile_coord(const NtArgs& g) {
   TileCoord t;
   t.live = false;
@@ -72,8 +70,7 @@ __device__ __forceinline__ TileCoord tile_coord(const NtArgs& g) {
   }
   t.m0 = tm * kT; t.n0 = tn * kT;
   if (t.m0 >= t.M) return t;
-  t.ksplit = g.ksplit > 1 ? g.ksplit : 1;
-  t.z = blockIdx.y / t.ksplit; t.ks = blockIdx.y - t.z * t.ksplit;
+  t.z = blockIdx.y;
   t.live = true;
   return t;
 }
@@ -81,8 +78,7 @@ __device__ __forceinline__ TileCoord tile_coord(const NtArgs& g) {
 // Writes a work-group's 256x256 accumulator tile to C.  The tile is held by 2 x (8 / TN) wavefronts, each
 // 4 x TN MFMA blocks of 32x32 (TN = 4: 2x2 wavefronts of 128x128; TN = 2: 2x4 wavefronts of 128x64).
 template <typename TC, int TN>
-__device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, const NtArgs& g, int M, int m0, int n0, int z, int ks,
-                                           int ksplit) {
+__device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, const NtArgs& g, int M, int m0, int n0, int z) {
   constexpr int WN = 8 / TN, NW = 2 * WN;            // wavefronts along N, wavefronts in all
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;     // (uniform: rows of C are looked up by scalar loads)
   const int wm = wave / WN, wn = wave % WN;
@@ -91,8 +87,7 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
   // it is that would be 128-byte pieces, eight of them per row at different times.  The tile goes through LDS
   // instead (two halves of 128 rows, the main loop's buffers are free by now) and leaves as whole rows: one
   // wavefront store = 256 consecutive columns of one row.
-  const bool to_parts = ksplit > 1;                  // this K range keeps its own copy
-  TC* C = to_parts ? (TC*)(g.parts + ((long)z * ksplit + ks) * g.sPart) : (TC*)g.C + g.sCz * z;
+  TC* C = (TC*)g.C + g.sCz * z;
   const float* bias = g.bias ? g.bias + g.sbiasz * z : nullptr;
   constexpr int kEpStride = 260;                      // floats per staged row (16-byte aligned, off the bank period)
   float* ep = (float*)lds;
@@ -101,7 +96,7 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int col = n0 + wn * (TN * 32) + j * 32 + r;
-    bv[j] = (bias && ks == 0 && col < g.N) ? bias[col] : 0.f;
+    bv[j] = (bias && col < g.N) ? bias[col] : 0.f;
   }
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
@@ -124,11 +119,11 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
       if (col >= g.N) continue;
       const float4 val = *(const float4*)&ep[rowl * kEpStride + lane * 4];
       const float e[4] = {val.x, val.y, val.z, val.w};
-      const long off = (long)((g.c_rows && !to_parts) ? g.c_rows[row] : row) * g.ldc + col;     // parts keep the packed rows
+      const long off = (long)(g.c_rows ? g.c_rows[row] : row) * g.ldc + col;
       const bool whole = vec_ok && col + 3 < g.N;
       if constexpr (sizeof(TC) == 4) {
         float* Cf = (float*)C + off;
-        const bool add = g.accumulate && !to_parts;
+        const bool add = g.accumulate;
         // (by itself: joined with the read below, every row waits for the one before; non-temporal: the operand panels stay in L2)
         if (whole && !add) __builtin_nontemporal_store((f32x4){val.x, val.y, val.z, val.w}, (f32x4*)Cf);
         else if (whole) {
@@ -208,7 +203,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
 
   const TileCoord tc = tile_coord(g);
   if (!tc.live) return;
-  const int M = tc.M, K = tc.K, m0 = tc.m0, n0 = tc.n0, z = tc.z, ks = tc.ks, ksplit = tc.ksplit;
+  const int M = tc.M, K = tc.K, m0 = tc.m0, n0 = tc.n0, z = tc.z;
 
   f32x16 acc[4][TN];
 #pragma unroll
@@ -223,9 +218,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   const int ktiles = (K + kKB - 1) / kKB;
   const int tail_chunks = (K - (ktiles - 1) * kKB) >> 3;       // 1 .. 8 chunks in the last k-tile
   const bool ragged = RAGGED && tail_chunks < 8;              // RAGGED = false: the launcher saw K % 64 == 0
-  const int nstage = ktiles * g.nseg;
-  const int it0 = (int)((long)nstage * ks / ksplit);
-  const int total = (int)((long)nstage * (ks + 1) / ksplit) - it0;
+  const int total = ktiles * g.nseg;                           // stages
 
   // Loads.  Wavefront-load i of this wavefront fills rows 8 * (i * NW + wave) .. + 7 of an operand; lane l fills
   // slot l & 7 of row (l >> 3) of those, i.e. fetches k-chunk (l & 7) ^ swizzle(row).  Rows past the operand's end
@@ -259,8 +252,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)lds;
   const int a_rec = a_bytes > 0x7fffffffL ? 0x7fffffff : (int)a_bytes, b_rec = b_bytes > 0x7fffffffL ? 0x7fffffff : (int)b_bytes;
   // Wavefront-loads of a stage are numbered 0 .. 2*NLD-1 (even: A, odd: B); `issue` enqueues numbers [first, last).
-  auto issue = [&](int rel_it, int buf, int first, int last) __attribute__((always_inline)) {
-    const int it = it0 + rel_it;
+  auto issue = [&](int it, int buf, int first, int last) __attribute__((always_inline)) {
     const int seg = it / ktiles, kt = it - seg * ktiles;
     const u32x4 ra = make_rsrc(g.A + (g.sAz * z + g.sAseg * seg) * 2, (unsigned)a_rec);
     const u32x4 rb = make_rsrc(g.B + (g.sBz * z + g.sBseg * seg) * 2, (unsigned)b_rec);
@@ -339,7 +331,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
     kstep(1, it + 2 < total, it + 2, cur);
     __builtin_amdgcn_sched_barrier(0);
   }
-  store_tile<TC, TN>(acc, lds, g, M, m0, n0, z, ks, ksplit);
+  store_tile<TC, TN>(acc, lds, g, M, m0, n0, z);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -367,7 +359,7 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 
   const TileCoord tc = tile_coord(g);
   if (!tc.live) return;
-  const int M = tc.M, K = tc.K, m0 = tc.m0, n0 = tc.n0, z = tc.z, ks = tc.ks, ksplit = tc.ksplit;
+  const int M = tc.M, K = tc.K, m0 = tc.m0, n0 = tc.n0, z = tc.z;
 
   f32x16 acc[4][TN];
 #pragma unroll
@@ -377,9 +369,7 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int nstage = (K + kKB - 1) / kKB;                      // rows past K arrive as zeros
-  const int it0 = (int)((long)nstage * ks / ksplit);
-  const int total = (int)((long)nstage * (ks + 1) / ksplit) - it0;
+  const int total = (K + kKB - 1) / kKB;                       // stages; rows past K arrive as zeros
 
   // Loads.  Wavefront-load i of this wavefront fills k-rows 2*(i*NW + wave) and +1 of the stage; lane l fills
   // 16-byte slot l % 32 of row l / 32, i.e. fetches column chunk (l % 32) ^ 4*(k % 4).
@@ -404,12 +394,12 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
   typedef __attribute__((ext_vector_type(2))) int i32x2;
   i32x2 prow2[NLD];
   int pk0 = 0;
-  auto lookup = [&](int rel_it) __attribute__((always_inline)) {
-    pk0 = (it0 + rel_it) * kKB + krow_in_stage;                // k of wavefront-load 0 for this lane; load i adds 2 * NW * i
-    if (g.k_rows && rel_it < total) {
+  auto lookup = [&](int it) __attribute__((always_inline)) {
+    pk0 = it * kKB + krow_in_stage;                // k of wavefront-load 0 for this lane; load i adds 2 * NW * i
+    if (g.k_rows && it < total) {
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
-        const int* p = g.k_rows + (long)(it0 + rel_it) * kKB + 2 * (NW * ((i + rot) % NLD) + wave);
+        const int* p = g.k_rows + (long)it * kKB + 2 * (NW * ((i + rot) % NLD) + wave);
         asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(prow2[i]) : "s"(p) : "memory");
       }
     }
@@ -510,28 +500,13 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
     __builtin_amdgcn_sched_barrier(0);
     lookup(it + 3);
   }
-  store_tile<TC, TN>(acc, lds, g, M, m0, n0, z, ks, ksplit);
+  store_tile<TC, TN>(acc, lds, g, M, m0, n0, z);
 }
 __global__ __launch_bounds__(512, 1) void gemm_tn8_f32_kernel(NtArgs g) { gemm_tn_body<float>(g); }
 
 // (kernels with literal launch bounds: a bound that depends on a template parameter loses the host-side stub)
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_kernel(NtArgs g) { gemm_dl_body<float, 2, RAGGED>(g); }
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_bf16_kernel(NtArgs g) { gemm_dl_body<uint16_t, 2, RAGGED>(g); }
-
-// C[z][m][n] (+)= sum over the K ranges of parts[z][range][m][n]  (parts in the layout of C, one after the other)
-__global__ void sum_parts_kernel(const float* parts, float* C, int M, int N, long ldc, long sCz, long sPart, int ksplit, int accumulate,
-                                 long total) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int n = (int)(idx % N);
-  const long rest = idx / N;
-  const int m = (int)(rest % M);
-  const long z = rest / M;
-  const long off = (long)m * ldc + n;
-  float v = accumulate ? C[z * sCz + off] : 0.f;
-  for (int ks = 0; ks < ksplit; ++ks) v += __builtin_nontemporal_load(parts + (z * ksplit + ks) * sPart + off);
-  C[z * sCz + off] = v;
-}
 
 // dst[c][r] = src[r][c] for r < R, c < C ; dst rows are padded with zeros up to ldd.
 __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd, long s_src, long s_dst) {
@@ -621,22 +596,12 @@ bool gemm_nt_ok(const GemmArgs& g) {
          g.sAz % 8 == 0 && g.sBz % 8 == 0 && g.sAseg % 8 == 0 && g.sBseg % 8 == 0 && a16(g.A) && a16(g.B);
 }
 
-// second half of a product whose K ranges stored their parts side by side: C (+)= their sum
-static hipError_t sum_parts(const NtArgs& a, hipStream_t s) {
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !a.parts) return e;
-  const long total = (long)a.nz * a.M * a.N;
-  hipLaunchKernelGGL(sum_parts_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, a.parts, (float*)a.C, a.M, a.N, a.ldc, a.sCz, a.sPart, a.ksplit,
-                     a.accumulate, total);
-  return hipGetLastError();
-}
-
 bool gemm_tn_ok(const GemmArgs& g) {
   const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
   const long rows = g.k_rows ? g.k_phys_rows : g.K;
   if (rows * g.lda * 2 > lim || rows * g.ldb * 2 > lim) return false;
-  return g.in_bf16 && !g.out_bf16 && !g.a_kcontig && !g.b_kcontig && !g.lens && g.nseg == 1 && g.ksplit <= 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
+  return g.in_bf16 && !g.out_bf16 && !g.a_kcontig && !g.b_kcontig && !g.lens && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
          g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B);
 }
 
@@ -647,7 +612,6 @@ hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s) {
   a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz; a.nseg = 1;
   a.accumulate = g.accumulate; a.k_dev = g.k_dev; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
-  a.ksplit = 1;
   const int sups = cdiv(cdiv(g.M, kT), kSupM) * cdiv(cdiv(g.N, kT), kSupN);
   a.blocked = sups >= 32 ? 1 : 0;
   const int tiles = a.blocked ? cdiv(sups, 8) * 8 * kSupM * kSupN : cdiv(g.M, kT) * cdiv(g.N, kT);
@@ -668,8 +632,6 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
   a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.m_dev = g.m_dev; a.k_dev = g.k_dev; a.a_phys_rows = g.a_phys_rows;
-  a.ksplit = g.ksplit > 1 && g.parts && !g.out_bf16 && !g.c_rows ? g.ksplit : 1;
-  a.parts = a.ksplit > 1 ? g.parts : nullptr; a.sPart = (long)g.M * g.ldc;
   // the blocked raster pays when every XCD gets several blocks; with few tiles it would leave XCDs idle
   const int sups = cdiv(cdiv(g.M, kT), kSupM) * cdiv(cdiv(g.N, kT), kSupN);
   a.blocked = sups >= 32 ? 1 : 0;
@@ -684,13 +646,13 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
     return hipSuccess;
   });
   if (ea != hipSuccess) return ea;
-  const dim3 grid(tiles, g.nz * a.ksplit);
+  const dim3 grid(tiles, g.nz);
   const bool ragged = g.K % kKB != 0, bf = g.out_bf16;
   if (bf && ragged) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<true>, grid, dim3(512), kDlLds, s, a);
   else if (bf) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<false>, grid, dim3(512), kDlLds, s, a);
   else if (ragged) hipLaunchKernelGGL(gemm_dl8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
   else hipLaunchKernelGGL(gemm_dl8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);
-  return sum_parts(a, s);
+  return hipGetLastError();
 }
 
 hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst, hipStream_t s) {

@@ -394,7 +394,7 @@ bool gemm_skinny_ok(const GemmArgs& g) {
   // from about half a device's worth of tiles: 768 x 20000 x 1000 takes 49 us there and 72 us here)
   if ((long)cdiv(g.M, 256) * cdiv(g.N, 256) * g.nz >= 128) return false;
   return g.in_bf16 && g.a_kcontig && g.b_kcontig && !g.lens && g.M <= kSkinnyMaxRows && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
-         !g.k_dev && !g.accumulate && g.ksplit <= 1 && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 &&
+         !g.k_dev && !g.accumulate && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 &&
          a16(g.A) && a16(g.B) && (long)g.N * g.ldb * 2 <= 0x7fffff00L;
 }
 hipError_t launch_gemm_skinny(const GemmArgs& g, bool relu, hipStream_t s) {

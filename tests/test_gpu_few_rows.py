@@ -18,7 +18,7 @@ def _bf(rng, *shape, w=1.0):
 
 
 @pytest.mark.parametrize("B,n_in,n", [(1, 37, 50), (16, 300, 104), (17, 300, 104), (32, 1100, 36), (33, 40, 1000), (64, 2620, 130),
-                                      (65, 77, 34), (192, 1200, 66), (193, 1200, 66), (12, 4100, 24)])
+                                      (65, 77, 34), (192, 1200, 66), (193, 1200, 66), (12, 4100, 24), (1025, 300, 104), (1300, 77, 34)])
 def test_stepped_cell(B, n_in, n):
     from paper_1805_05225_amd import binding as Bn
     rng = np.random.default_rng(B + n_in)
@@ -44,7 +44,7 @@ def test_readout_packed_once_for_any_row_count(n, nt, E, R):
     rng = np.random.default_rng(n)
     W, br = _bf(rng, R, n + nt + E, w=0.1), rng.uniform(-.1, .1, R)
     ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
-    for k, B in enumerate((300, 1, 16, 17, 64, 192, 193)):
+    for k, B in enumerate((300, 1, 16, 17, 64, 192, 193, 1024, 1025, 1300)):
         s, t, a = _bf(rng, B, n), _bf(rng, B, nt), _bf(rng, B, E)
         out = Bn.readout(s.cuda(), t.cuda(), a.cuda(), W.cuda(), dev(br), workspace=ws, flags=Bn.FLAG_WEIGHTS_PACKED if k else 0)
         f64 = lambda v: v.float().numpy().astype(np.float64)
