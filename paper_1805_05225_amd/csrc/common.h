@@ -299,7 +299,8 @@ struct BlockBwdArgs {
   int row0;
 };
 bool loop_block_width(int n);
-bool loop_block_fits(int B, int n, long ld_out);      // does the current device hold the launch?
+bool loop_block_fits(int B, int n, long ld_out);
+bool loop_block_pays(int T, int B, int n, int ndir, bool plain_launch, bool backward);      // is it faster than the per-step kernels?      // does the current device hold the launch?
 size_t loop_block_ring_bytes(int n);
 size_t loop_block_ring_bytes_bwd(int n);
 size_t loop_block_wh_bytes(int n);

@@ -571,6 +571,28 @@ bool loop_block_fits(int B, int n, long ld_out) {
   return loop_block_width(n) && (long)B * 16 * n < lim && (long)B * ld_out * 2 < lim && std::min(device_capacity((const void*)block_fwd_kernel<1>), device_capacity((const void*)block_fwd_kernel<2>)) >= fwd_grid(n) &&
          std::min(device_capacity((const void*)block_bwd_kernel<1>), device_capacity((const void*)block_bwd_kernel<2>)) >= bwd_grid(n);
 }
+// A launch is 32 rows of one direction and walks all steps, while the per-step kernels take every row and both directions in one pass over
+// W_h: with many rows, above all of the narrower layers, those are faster (n = 1032, 256 rows, both directions, us a step: 82 forward and 104
+// backward here, 32 and 38 there; n = 2048, 64 rows, one direction: 9.4 and 10.1 here, 14.8 and 23.5 there).  Both sides as they were measured,
+// in us, for n from 1032 to 2048, 4 to 256 rows, 2 to 100 steps, one and two directions, plain and cooperative launches (624 shapes, each
+// pass both ways: the choice is within 5 % of the faster side in 98 % of them, never 1.35 times it, while always one launch was up to 6.4
+// times the other).  A column's tasks are two to a member up to 1536 units forward and 1920 backward, one above.
+bool loop_block_pays(int T, int B, int n, int ndir, bool plain_launch, bool backward) {
+  const double w = (double)n * n / (2048.0 * 2048.0), nr = (double)n * ndir * B * 1e-5;
+  const int slabs = cdiv(B, kSlab), half = B % kSlab != 0 && B % kSlab <= 16, whole = slabs - half;      // half: a slab of one row tile
+  const double start = 14.5 + (plain_launch ? 0.0 : 18.2);
+  double here, there;
+  if (backward) {
+    const bool one_task = n > 1920;
+    here = 24 + ndir * (23 * w + slabs * start + T * (whole * (one_task ? 5.45 : 6.85) + half * (one_task ? 4.3 : 3.8)));
+    there = 42 + ndir * 51 * w + T * std::max(2 + 9.6e-3 * n + 3.8 * nr, 10.2 * nr);
+  } else {
+    const bool one_task = n > 1536;
+    here = 10.5 + ndir * (17.8 * w + slabs * start + T * (whole * (one_task ? 4.05 : 4.65) + half * (one_task ? 3.4 : 3.15)));
+    there = 23.5 + ndir * 20.5 * w + T * std::max(2.2 + 3.1e-3 * n + 5.45 * nr + 2.1 * (ndir - 1) * w, 6.9 * nr);
+  }
+  return here < there;
+}
 size_t loop_block_ring_bytes(int n) { return 2 * (64 * 2048 + (size_t)cdiv(n, 32) * 4 * 4 * 4096); }
 size_t loop_block_ring_bytes_bwd(int n) {
   const size_t nb = cdiv(n, kBlk);

@@ -398,7 +398,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     HIPCHK(launch_small_fwd(a, p.bf16, s));
     return LSTM_OK;
   }
-  if (p.blocks && loop_block_fits(p.B, p.n, (long)(D * n))) {    // a wide layer: projection, then a launch per direction and 32 rows
+  if (p.blocks && loop_block_pays(p.T, p.B, p.n, p.D, (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0, false) && loop_block_fits(p.B, p.n, (long)(D * n))) {    // a wide layer: projection, then a launch per direction and 32 rows
     // Until a row's first frame every column of the grid reads its h0 from memory, and the columns do not end together: a state in
     // place (hT over h0) is read from a copy.
     if (bytes_overlap(h0, state_bytes, hT, state_bytes) || bytes_overlap(h0, state_bytes, cT, state_bytes)) {
@@ -801,7 +801,9 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     return LSTM_OK;
   };
 
-  if ((rc = p.small ? narrow_loop() : p.blocks && loop_block_fits(p.B, p.n, (long)(D * n)) ? block_loop() : split_loop())) return rc;
+  const bool blocks = p.blocks && loop_block_pays(p.T, p.B, p.n, p.D, (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0, true) &&
+                      loop_block_fits(p.B, p.n, (long)(D * n));
+  if ((rc = p.small ? narrow_loop() : blocks ? block_loop() : split_loop())) return rc;
 
   int* fidx = (int*)(ws + p.ws_fidx);
   int* count = (int*)(ws + p.ws_count);

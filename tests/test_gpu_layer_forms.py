@@ -62,7 +62,7 @@ def _layer(T, B, n_in, n, bidir, dt):
             P.compare(f, g, *P.run_oracle(c, bidir, direction), TOL[dt])
 
 
-@pytest.mark.parametrize("dt,T,B,n", [("bf16", 4, 33, 1040), ("bf16", 3, 16, 2048), ("bf16", 5, 9, 330), ("bf16", 4, 6, 64), ("f32", 5, 33, 331),
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 20, 1040), ("bf16", 16, 33, 2048), ("bf16", 5, 9, 330), ("bf16", 4, 6, 64), ("f32", 5, 33, 331),
                                       ("f32", 4, 6, 64), ("f32", 3, 5, 1100)])
 @pytest.mark.parametrize("direction", [1, -1])
 def test_state_in_place(dt, T, B, n, direction):
@@ -86,7 +86,7 @@ def test_state_in_place(dt, T, B, n, direction):
 
 # Outside the range of what the loops exchange: the result is the per-step kernels', which exchange nothing between work-groups of a launch.
 @pytest.mark.parametrize("what", ["nan_x", "nan_W", "large_W", "inf_dy", "large_dy"])
-@pytest.mark.parametrize("dt,T,B,n", [("bf16", 4, 9, 1040), ("bf16", 3, 33, 2048), ("f32", 4, 9, 331), ("f32", 3, 40, 200), ("f32", 4, 17, 1000), ("f32", 3, 70, 1001)])
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 9, 1040), ("bf16", 24, 33, 2048), ("f32", 4, 9, 331), ("f32", 3, 40, 200), ("f32", 4, 17, 1000), ("f32", 3, 70, 1001)])
 def test_values_outside_the_exchange_range(dt, T, B, n, what):
     from paper_1805_05225_amd import binding as Bn
     P.Bn = Bn
@@ -124,3 +124,49 @@ def test_values_outside_the_exchange_range(dt, T, B, n, what):
             size = np.abs(np.where(ok, ref, 0)).max(axis=ax, keepdims=True)
             err = np.abs(np.where(ok, got, 0) - np.where(ok, ref, 0)) / np.maximum(size, 1e-30)
             assert err.max() < TOL[dt], (name, err.max())
+
+
+@pytest.mark.parametrize("T,B,n,bidir", [(150, 5, 1032, False), (64, 32, 1536, True), (90, 33, 2048, False), (40, 64, 2048, True), (33, 17, 1921, False)])
+def test_wide_loops_over_many_steps(T, B, n, bidir):
+    """The rings of the wide loops are used over and over: many steps, ordinary and cooperative launch, against the per-step kernels; the same
+    call gives the same bits every time."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(T + n)
+    D = 2 if bidir else 1
+    c = P.rnd_case(rng, T, B, 24, n, D, _lens(rng, T, B), "bf16", scale=2.0 / np.sqrt(n))
+    grads = ("dx", "dW_x", "dW_h", "db", "dh0", "dc0")
+    fs, gs = P.run_gpu(c, "bf16", bidir, flags=Bn.FLAG_PER_STEP)
+    first = None
+    for flags in (Bn.FLAG_PLAIN_LAUNCH, 0, Bn.FLAG_PLAIN_LAUNCH, Bn.FLAG_PLAIN_LAUNCH):
+        Bn.profile_enable(1)
+        f, g = P.run_gpu(c, "bf16", bidir, flags=flags, poison=True)
+        Bn.profile_enable(0)
+        launches = Bn.profile_read()
+        assert launches["loop_fwd"][1] == launches["loop_bwd"][1] == 2 * D      # (a launch per step otherwise)
+        got = [f[k] for k in ("y", "c", "hT", "cT")] + [g[k] for k in grads]
+        if first is None:
+            first = [t.clone() for t in got]
+            for name, a, b in zip(("y", "c", "hT", "cT") + grads, got, [fs[k] for k in ("y", "c", "hT", "cT")] + [gs[k] for k in grads]):
+                check(name, a, host(b), TOL["bf16"])
+        for a, b in zip(got, first):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,n,bidir", [(64, 1032, True), (96, 1280, False), (64, 1536, True), (256, 2048, True), (3, 2048, False)])
+@pytest.mark.parametrize("T", [2, 60])
+def test_wide_layer_on_either_side_of_the_rule(T, B, n, bidir):
+    """Forward and backward choose their loop by themselves: any pairing gives the per-step result."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(T + B + n)
+    if T * B > 4000:
+        T = 9
+    c = P.rnd_case(rng, T, B, 24, n, 2 if bidir else 1, _lens(rng, T, B), "bf16", scale=2.0 / np.sqrt(n))
+    fs, gs = P.run_gpu(c, "bf16", bidir, flags=Bn.FLAG_PER_STEP)
+    for flags in (0, Bn.FLAG_PLAIN_LAUNCH):
+        f, g = P.run_gpu(c, "bf16", bidir, flags=flags, poison=True)
+        for k in ("y", "c", "hT", "cT"):
+            check(k, f[k], host(fs[k]), TOL["bf16"])
+        for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0"):
+            check(k, g[k], host(gs[k]), TOL["bf16"])
