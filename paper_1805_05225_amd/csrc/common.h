@@ -85,6 +85,7 @@ struct GemmArgs {
   float* parts; size_t parts_bytes;       // gemm_tile.hip and gemm_float.hip, which plan their own ranges of K: room for the ranges' parts (their bytes,
                                           // or K stays whole); a second kernel writes C (+)= their sum (`accumulate` honoured)
   SumList* sums;                          // not NULL: that sum is left for the caller's launch_sums
+  bool frames;                            // rows of A and C are frames, padded ones included (gemm_float_ranges)
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for problems with both operands k-contiguous, 16-byte aligned rows and K % 8 == 0

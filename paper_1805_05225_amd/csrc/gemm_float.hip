@@ -297,7 +297,12 @@ __global__ __launch_bounds__(256, 2) void gemm_float_tn_kernel(FArgs g) { gemm_f
 // unit has a single work-group and nothing hides its waits), work-groups come in whole rounds of 256 units, and the parts are
 // written and read once.  (Config 2, dW_x: 320 tiles leave 3 of 8 units idle in the second round; dW of 64 units over 10240 frames
 // was 4 tiles on 4 units, 1.4 ms, and is now 0.04.)
-// `frames`: rows are frames, padded ones included: judged with 0.6 of the rows real as well as with all.
+// `frames`: rows are frames, padded ones included: judged with 0.6 of the rows real (lengths spread evenly from a fifth of the longest on) as
+// well as with all.
+// Checked against every count up to 24 for the four products of 16 layers (256 to 1536 units, 240 to 25600 frames of which 0.5 to all are
+// real, one and two directions): with the factor for eight ranges anywhere from 0.65 to 0.85 the choice costs a whole pass 0.5 % on average against the
+// best count, 2 % at most but for one product (7 %: Zx of 1029 real of 2037 frames, whose 352 tiles it does not cut); at 0.6 and at 0.9 it goes
+// wrong by 11 and 9 %.
 int gemm_float_ranges(long M, long N, long K, int nz, int nseg, bool frames) {
   const long tiles = (long)cdiv(M, kTile) * cdiv(N, kTile) * nz, fewer = frames ? (long)cdiv(M * 3 / 5, kTile) * cdiv(N, kTile) * nz : tiles;
   const long stages = nseg * (long)cdiv(K, kKS);
@@ -309,7 +314,7 @@ int gemm_float_ranges(long M, long N, long K, int nz, int nseg, bool frames) {
   double best_us = 1e30;
   for (int r = 1; r <= 64 && (r == 1 || stages / r >= 4); ++r) {
     double us = 0.5 * (loop_us(tiles, r) + loop_us(fewer, r)) + (r > 1 ? 6.0 + (double)r * M * N * nz * 8 / 4.5e6 : 0.0);
-    if (frames && r == 8) us *= 0.65;    // a range per XCD, operands from its own L2: dX of config 2 218 us, with six ranges 327
+    if (frames && r == 8) us *= 0.75;    // a range per XCD, operands from its own L2: dX of config 2 218 us, with six ranges 327
     if (us < 0.95 * best_us) { best = r; best_us = us; }
   }
   return best;
@@ -351,8 +356,8 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s) {
   a.accumulate = g.accumulate;
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.a_phys_rows = g.a_phys_rows; a.m_dev = g.m_dev;
   a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows; a.k_dev = g.k_dev;
-  a.ksplit = g.parts ? gemm_float_ranges(g.M, g.N, g.K, g.nz, g.nseg, g.a_kcontig) : 1;
-  if (a.ksplit > 1 && gemm_float_parts_bytes(g.M, g.N, g.K, g.nz, g.nseg, g.a_kcontig) > g.parts_bytes) a.ksplit = 1;
+  a.ksplit = g.parts ? gemm_float_ranges(g.M, g.N, g.K, g.nz, g.nseg, g.frames) : 1;
+  if (a.ksplit > 1 && gemm_float_parts_bytes(g.M, g.N, g.K, g.nz, g.nseg, g.frames) > g.parts_bytes) a.ksplit = 1;
   a.parts = g.parts; a.ldp = (g.N + 3) / 4 * 4;
   a.tiles_m = cdiv(g.M, kTile); a.tiles_n = cdiv(g.N, kTile);
   a.per_xcd = cdiv(a.tiles_m * a.tiles_n, 8);

@@ -323,7 +323,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     g.A = x; g.B = W_x; g.C = gates; g.bias = (const float*)b;
     g.M = (int)(T * B); g.N = 4 * p.n; g.K = p.n_in;
     g.lda = p.n_in; g.ldb = 4 * n; g.ldc = 4 * n;
-    g.sAz = 0; g.sBz = (long)p.n_in * 4 * n; g.sCz = gates_stride; g.sbiasz = 4 * n; g.nz = p.D;
+    g.sAz = 0; g.sBz = (long)p.n_in * 4 * n; g.sCz = gates_stride; g.sbiasz = 4 * n; g.nz = p.D; g.frames = true;
     g.nseg = 1; g.a_kcontig = true; g.b_kcontig = false; g.in_bf16 = p.bf16; g.out_bf16 = false;
     g.vecA = widest(g.lda, 0, 0, p.esz, 16);
     g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
@@ -819,7 +819,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.A = DZ; g.B = W_x; g.C = dx;
       g.M = TB; g.N = p.n_in; g.K = 4 * p.n;
       g.lda = 4 * n; g.ldb = 4 * n; g.ldc = n_in; g.nz = 1;
-      g.nseg = p.D; g.sAseg = (long)p.DZ_dir_elems; g.sBseg = (long)(n_in * 4 * n);
+      g.nseg = p.D; g.sAseg = (long)p.DZ_dir_elems; g.sBseg = (long)(n_in * 4 * n); g.frames = true;
       g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = p.bf16; g.out_bf16 = p.bf16;
       g.vecA = widest(g.lda, g.sAseg, 0, p.esz, 16);
       g.vecB = widest(g.ldb, g.sBseg, 0, p.esz, 16);
