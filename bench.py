@@ -808,7 +808,7 @@ def main():
         "roofline_hoisted_gemms": {"bound": "mfma", "achieved": gemm_tflops, "peak": mfma_peak, "unit": "TFLOP/s",
                                    "frac": gemm_tflops / mfma_peak, "tflops_per_product": per_product,
                                    "note": "flops of the four hoisted products per layer over the real frames; the operand "
-                                           "transposes and the frame map are inside the timed phases"},
+                                           "transposes, the frame map and the sums of K ranges are inside the timed phases"},
         "phases_ms_per_step": {k: v[0] / args.steps for k, v in prof.items()},
     }
     if not args.no_cpu:

@@ -300,6 +300,9 @@ int lstm_sync_status(const void* workspace, int32_t* timed_out);
  * lstm_profile_enable(1) the recurrent loops and the hoisted products (LSTM_PHASE_GEMM_*, LSTM_PHASE_LOOP_*),
  * lstm_profile_enable(2) also the short phases around them (LSTM_PHASE_PREP, LSTM_PHASE_DB), 0 none.  An event
  * between two kernels costs a few microseconds of idle device, which is why the short phases are optional.
+ * Where one launch serves several phases its time is divided among them: dW_x and dW_h (and dX) formed in one launch by their
+ * flops, the launch that adds the parts of the products' K ranges and the slices of db by the elements it reads; the launch
+ * is counted once, for the first of the phases.
  * lstm_profile_read() waits for the recorded events, adds each phase's elapsed milliseconds and
  * kernel-launch count into ms[LSTM_PHASE_COUNT] / launches[LSTM_PHASE_COUNT] (caller zeroes them),
  * and releases the events.  Not thread-safe; meant for a single benchmarking thread. */
@@ -308,10 +311,10 @@ enum {
   LSTM_PHASE_GEMM_ZX = 1,   /* Zx = X W_x + b for all frames                                      */
   LSTM_PHASE_LOOP_FWD = 2,  /* forward recurrence                                                 */
   LSTM_PHASE_LOOP_BWD = 3,  /* backward recurrence                                                */
-  LSTM_PHASE_GEMM_DX = 4,   /* dX = DZ W_x^T                                                      */
-  LSTM_PHASE_GEMM_DWX = 5,  /* dW_x = X^T DZ                                                      */
-  LSTM_PHASE_GEMM_DWH = 6,  /* dW_h = Hprev^T DZ                                                  */
-  LSTM_PHASE_DB = 7,        /* db = column sums of DZ                                             */
+  LSTM_PHASE_GEMM_DX = 4,   /* dX = DZ W_x^T, the sum of its K ranges included                    */
+  LSTM_PHASE_GEMM_DWX = 5,  /* dW_x = X^T DZ, likewise                                            */
+  LSTM_PHASE_GEMM_DWH = 6,  /* dW_h = Hprev^T DZ, likewise                                        */
+  LSTM_PHASE_DB = 7,        /* db = column sums of DZ (where the loop has not summed them itself) */
   LSTM_PHASE_COUNT = 8
 };
 int lstm_profile_enable(int on);

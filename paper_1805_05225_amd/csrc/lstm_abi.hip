@@ -215,19 +215,29 @@ int check_device() {                 // is the current device one this library i
 }
 
 // ---- optional phase timing (hipEvents on the caller's stream) -----------------------------------
-struct PhaseRec { int phase; long launches; hipEvent_t e0, e1; };
+// A bracket's time belongs to one phase, or to several that share its launches, in proportion to `weight`.
+struct PhaseShare { int phase; double weight; };
+struct PhaseRec { PhaseShare share[4]; int count; long launches; hipEvent_t e0, e1; };
 int g_profile = 0;              // 0 off, 1 recurrent loops and hoisted products, 2 every phase
 std::vector<PhaseRec> g_recs;
 
 struct Phase {
   int idx = -1;
   hipStream_t s;
-  Phase(int phase, long launches, hipStream_t stream) : s(stream) {
+  Phase(int phase, long launches, hipStream_t stream) : Phase(std::initializer_list<PhaseShare>{{phase, 1.0}}, launches, stream) {}
+  Phase(std::initializer_list<PhaseShare> shares, long launches, hipStream_t stream) : s(stream) {
     if (!g_profile) return;
+    PhaseRec r = {};
     // (an event between two kernels leaves the device idle for some microseconds: the short set-up phases are
     // bracketed only on request)
-    if (g_profile < 2 && (phase == LSTM_PHASE_PREP || phase == LSTM_PHASE_DB)) return;
-    PhaseRec r{phase, launches, nullptr, nullptr};
+    bool wanted = g_profile >= 2;
+    for (const PhaseShare& p : shares) {
+      if (p.weight <= 0.0 || r.count == 4) continue;
+      r.share[r.count++] = p;
+      wanted |= p.phase != LSTM_PHASE_PREP && p.phase != LSTM_PHASE_DB;
+    }
+    if (!wanted || r.count == 0) return;
+    r.launches = launches;
     if (hipEventCreate(&r.e0) != hipSuccess || hipEventCreate(&r.e1) != hipSuccess) { (void)hipGetLastError(); return; }
     (void)hipEventRecord(r.e0, s);
     g_recs.push_back(r);
@@ -849,10 +859,11 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h);
     const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
     if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
+      const bool pair = gx.parts && gh.parts;    // both in few tiles
       {
-        Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+        Phase ph({{LSTM_PHASE_GEMM_DWX, (double)p.n_in}, {LSTM_PHASE_GEMM_DWH, pair ? (double)n : 0.0}}, 1, s);
         if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
-        if (gx.parts && gh.parts) {    // both in few tiles
+        if (pair) {
           HIPCHK(launch_gemm_tile_pair(gx, gh, s));
           return LSTM_OK;
         }
@@ -899,18 +910,26 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     return LSTM_OK;
   };
   if (p.dw_tiny) {
-    Phase ph(LSTM_PHASE_GEMM_DWX, 1, s);
+    Phase ph({{LSTM_PHASE_GEMM_DWX, (double)n_in}, {LSTM_PHASE_GEMM_DWH, (double)n}, {LSTM_PHASE_GEMM_DX, dx ? (double)n_in : 0.0}}, 1, s);
     HIPCHK(launch_gemm_tiny(tiny, p.bf16, (unsigned*)(ws + p.ws_tiny_cnt), (float*)(ws + p.ws_tiny_parts), s));
   } else if ((rc = products())) return rc;
-  Phase ph(LSTM_PHASE_DB, 2, s);
   if (db_slices && !db_done) {
     SumJob j = {};
     j.parts = (const float*)(ws + p.ws_colsum); j.C = db; j.M = 1; j.N = 4 * p.n; j.ksplit = db_slices; j.nz = p.D;
     j.ldp = 4 * n; j.sPz = (long)kColsumSlices * 4 * n; j.ldc = 4 * n; j.sCz = 4 * n; j.accumulate = acc;
     sums.add(j);                         // (three products and this: the list holds four)
   }
-  HIPCHK(launch_sums(sums, s));
+  if (sums.count > 0) {                // one launch: its time by what each sum reads
+    PhaseShare sh[4] = {{LSTM_PHASE_DB, 0}, {LSTM_PHASE_GEMM_DX, 0}, {LSTM_PHASE_GEMM_DWX, 0}, {LSTM_PHASE_GEMM_DWH, 0}};
+    for (int i = 0; i < sums.count; ++i) {
+      const SumJob& j = sums.j[i];
+      sh[j.C == dx ? 1 : j.C == dW_x ? 2 : j.C == dW_h ? 3 : 0].weight += (double)j.M * j.N * j.nz * j.ksplit;
+    }
+    Phase ph({sh[0], sh[1], sh[2], sh[3]}, 1, s);
+    HIPCHK(launch_sums(sums, s));
+  }
   if (db_slices || db_done) return LSTM_OK;
+  Phase ph(LSTM_PHASE_DB, 2, s);
   HIPCHK(launch_colsum(DZ, (float*)db, (float*)(ws + p.ws_colsum), TB, 4 * p.n, p.D, (long)p.DZ_dir_elems, p.bf16, acc, s));
   return LSTM_OK;
 }
@@ -1037,8 +1056,10 @@ int lstm_profile_read(double* ms, int64_t* launches) {
       (void)hipGetLastError();
       rc = LSTM_ERR_HIP;
     } else {
-      ms[r.phase] += t;
-      launches[r.phase] += r.launches;
+      double all = 0.0;
+      for (int i = 0; i < r.count; ++i) all += r.share[i].weight;
+      for (int i = 0; i < r.count; ++i) ms[r.share[i].phase] += t * (r.share[i].weight / all);
+      launches[r.share[0].phase] += r.launches;
     }
     (void)hipEventDestroy(r.e0);
     (void)hipEventDestroy(r.e1);

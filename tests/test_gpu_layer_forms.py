@@ -170,3 +170,23 @@ def test_wide_layer_on_either_side_of_the_rule(T, B, n, bidir):
             check(k, f[k], host(fs[k]), TOL["bf16"])
         for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0"):
             check(k, g[k], host(gs[k]), TOL["bf16"])
+
+
+@pytest.mark.parametrize("dt,T,B,n_in,n", [("bf16", 40, 21, 123, 330), ("f32", 20, 4, 32, 64), ("f32", 30, 16, 100, 200), ("bf16", 60, 32, 40, 1024)])
+def test_phase_times_name_every_product(dt, T, B, n_in, n):
+    """Products that share a launch share its time, and none of them goes without."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(n)
+    c = P.rnd_case(rng, T, B, n_in, n, 2, _lens(rng, T, B), dt, scale=2.0 / np.sqrt(n))
+    P.run_gpu(c, dt, True)
+    total = {}
+    for level in (1, 2):
+        Bn.profile_enable(level)
+        P.run_gpu(c, dt, True)
+        Bn.profile_enable(0)
+        p = Bn.profile_read()
+        print("  ", {k: "%.1f us, %d" % (v[0] * 1e3, v[1]) for k, v in p.items()}, flush=True)
+        assert all(p[k][0] > 0 for k in ("gemm_zx", "gemm_dx", "gemm_dwx", "gemm_dwh", "loop_fwd", "loop_bwd"))
+        total[level] = sum(v[1] for k, v in p.items() if k.startswith("gemm"))
+    assert total[1] == total[2]
