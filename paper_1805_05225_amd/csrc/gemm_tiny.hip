@@ -123,8 +123,13 @@ __device__ __forceinline__ void product(const TinyProduct& p, int tile, float (&
     float* mine = parts + (long)(first_part + tile) * (kT * kT);
 #pragma unroll
     for (int i = 0; i < 4; ++i) __hip_atomic_store(&mine[tid + 256 * i], sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // The parts are written and read as device-scope atomics, past the L2 caches, so all that has to be waited for is that they have
-    // arrived; a release would write the XCD's whole L2 back (80 instead of 27 us for the launch).
+    // What a release at device scope does on this device is (1) write the XCD's dirty L2 lines back, (2) wait until every store before it
+    // has been acknowledged (vmcnt 0), (3) let the atomic behind it go.  The parts need no (1): a device-scope atomic store is
+    // written through (sc1), and it is acknowledged where all XCDs meet, not by the L2 on the way - (2) would order nothing otherwise.
+    // Their readers are device-scope atomic loads, which take nothing from an L2 that another XCD may have overtaken, and go out
+    // only after the counter's value has come back and the barrier behind it.  So (2) is all there is to do; a whole release costs 80
+    // instead of 27 us for the launch.  (vmcnt 0 counts everything: nothing here hangs on the order in which loads and stores
+    // are acknowledged, which the single-launch loops have found not to be that of issue.)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) last = (int)__hip_atomic_fetch_add(&counters[first_part + out_tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.ksplit - 1;
