@@ -3,7 +3,7 @@
 // What bounds a small call (a decoder step for one sentence, a short sentence's encoding) is not the device but the time
 // the host needs to hand the work over: in Python, with ctypes, a call cost 16 - 21 us before the first kernel was enqueued
 // (a dozen tensors checked and their addresses taken, the descriptor built, four outputs allocated, fifteen arguments
-// converted).  The same work here takes 2 - 4 us.  The functions are positional and private to binding.py, which keeps the public
+// converted).  The same work here takes 7 - 11 us.  The functions are positional and private to binding.py, which keeps the public
 // names, keyword arguments and results.
 //
 // The library's entry points are handed over as addresses (`bind`), so that binding.py alone decides which library is
@@ -283,13 +283,18 @@ FAST(gather_many) {
     const Py_ssize_t count = PySequence_Size(a[0]);
     if (count < 0) throw Failed();
     std::vector<lstm_gather_item> item(count);
+    std::vector<at::Tensor> held;                    // (a sequence may make its items on access)
+    held.reserve(2 * count);
+    const auto item_of = [&](PyObject* seq, Py_ssize_t i) -> const at::Tensor& {
+      struct Ref { PyObject* o; ~Ref() { Py_XDECREF(o); } } ref{PySequence_GetItem(seq, i)};
+      if (!ref.o) throw Failed();
+      held.push_back(tensor(ref.o));
+      return held.back();
+    };
     const at::Tensor& src = tensor(a[2]);
     require(src.dim() == 2 && PySequence_Size(a[1]) == count, "src is [Q, beam], one output per state");
     for (Py_ssize_t i = 0; i < count; ++i) {
-      PyObject *pi = PySequence_GetItem(a[0], i), *po = PySequence_GetItem(a[1], i);
-      Py_XDECREF(pi); Py_XDECREF(po);                // (the sequences keep them alive)
-      if (!pi || !po) throw Failed();
-      const at::Tensor &in = tensor(pi), &out = tensor(po);
+      const at::Tensor &in = item_of(a[0], i), &out = item_of(a[1], i);
       require(in.dim() == 2 && in.stride(1) == 1 && out.dim() == 2 && out.stride(1) == 1 && in.scalar_type() == out.scalar_type() &&
                   in.sizes() == out.sizes(), "states are matrices with contiguous rows, outputs like them");
       item[i] = {(int32_t)in.element_size(), (int32_t)in.size(1), in.data_ptr(), in.stride(0), out.data_ptr(), out.stride(0)};

@@ -200,3 +200,40 @@ def test_strerror():
     for s in range(0, -8, -1):
         assert Bn.strerror(s) and "unknown" not in Bn.strerror(s)
     assert "unknown" in Bn.strerror(-99)
+
+
+def test_gather_many_keeps_items_made_on_access_alive():
+    """A sequence may make its items when they are asked for: they have to live until the call has returned."""
+    import ctypes
+    import weakref
+
+    import torch
+    from paper_1805_05225_amd import _marshal, binding as Bn
+
+    made, alive = [], []
+
+    class OnAccess:
+        def __len__(self):
+            return 3
+
+        def __getitem__(self, i):
+            if i >= 3:
+                raise IndexError
+            t = torch.zeros(4, 8)
+            made.append(weakref.ref(t.untyped_storage()))
+            return t
+
+    table = {name: ctypes.cast(getattr(Bn.lib, name), ctypes.c_void_p).value for name in Bn.EXPORTS}
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p)
+    def instead(Q, beam, count, items, src, stream):
+        got = (Bn.GatherItem * count).from_address(items)
+        alive.append(len({it.inp for it in got} | {it.out for it in got}))      # (freed memory is handed out again: fewer addresses)
+        return 0
+
+    try:
+        _marshal.bind({**table, "lstm_beam_gather_many": ctypes.cast(instead, ctypes.c_void_p).value})
+        assert _marshal.gather_many(OnAccess(), OnAccess(), torch.zeros(2, 2, dtype=torch.int32), 0) == 0
+    finally:
+        _marshal.bind(table)
+    assert len(made) == 6 and alive == [6]
