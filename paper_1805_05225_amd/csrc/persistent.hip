@@ -1959,8 +1959,9 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 // are two 8-byte units, the tag bit 30 of each unit's second float.  Partial sums are not bounded by 1, so they travel scaled
 // by 2^-32 (the packed W_h^T carries the factor; the consumer multiplies its sum by 2^32): bit 30 is then 0 for every partial
 // sum below 2^32 in magnitude, and no other bit of a value above 2^-94 changes.  Larger ones, infinities and NaN travel folded
-// (exchange_dev.h): a half step whose largest dz and W_h could make one looks at each sum, the others at none (config 2's loop 525 -> 536 us; with a
-// look at every sum 548, with a second copy of the products for such half steps 550).  To a consumer a folded value looks like a stale
+// (exchange_dev.h): a half step whose largest dz and W_h could make one looks at each sum, the others at none (config 2's loop 525 -> 534 us, a slab of one row
+// tile of 1000 units 6.95 -> 7.13 us a step; with a look at every sum 548, with a second copy of the products for such half steps 550, with the
+// operands looked at behind the first tiles' MFMAs instead of in front of them 546 and 7.38).  To a consumer a folded value looks like a stale
 // tag, and the pass that fetches such loads again unfolds it.  A consumer adds the blocks of its tile from
 // all producers (1 KiB each, one 16-byte load per lane: the producer's accumulator layout), wavefront w taking producers
 // w, w + 4, ..., and the four sums meet in LDS.
@@ -2105,15 +2106,23 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           redo = 0ull;
 #pragma unroll
           for (int it = 0; it < NCT; ++it) x[it] = rd.load_it(it);
+          float largest = 0.f;
 #pragma unroll
           for (int it = 0; it < NCT; ++it) {
-            const bool wide = !(max_magnitude(0.f, __uint_as_float(x[it][1]), __uint_as_float(x[it][3])) < one);
-            if (__builtin_amdgcn_ballot_w64((rd.tag_diff(x[it], it, tagw) != 0u) | wide) == 0ull) add_to(ps, x[it]);
-            else { redo |= 1ull << it; PROF_REDO(1) }
+            if (__builtin_amdgcn_ballot_w64(rd.tag_diff(x[it], it, tagw) != 0u) == 0ull) {
+              add_to(ps, x[it]);
+              largest = max_magnitude(largest, __uint_as_float(x[it][1]), __uint_as_float(x[it][3]));
+            } else { redo |= 1ull << it; PROF_REDO(1) }
+          }
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(largest < one)) != 0ull, 0)) {      // something folded among them: all again
+#pragma unroll
+            for (int v = 0; v < 4; ++v) ps[v] = 0.f;
+            redo = (1ull << NCT) - 1ull;
           }
         }
         if (redo)
           rd.template fix_up_batch<NCT>(redo, dead, [&](int, const u32x4& v) {
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(max_magnitude(0.f, __uint_as_float(v[1]), __uint_as_float(v[3])) < one)) == 0ull, 1)) return add_to(ps, v);
             ps[0] += __uint_as_float(v[0]); ps[1] += __uint_as_float(unfold_wide(v[1] & ~kLLFwdTagBit));
             ps[2] += __uint_as_float(v[2]); ps[3] += __uint_as_float(unfold_wide(v[3] & ~kLLFwdTagBit));
           });
