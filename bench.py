@@ -217,7 +217,7 @@ def cpu_baseline(inp):
         cores = max([p.get("num_threads", 1) for p in threadpool_info()] or [1])
     except Exception:
         cores = os.cpu_count() or 1
-    cap = 320                          # about 11 s of CPU work on the 16 host threads of the GPU machine
+    cap = 320                          # about 11 s of CPU work on 16 host threads
     nl = len(inp["layers"])
     L = inp["layers"][min(1, nl - 1)]
     lens = np.minimum(inp["seq_lens"], cap)
