@@ -17,13 +17,13 @@
 //   h       is bounded or NaN: a NaN in the tagged unit goes into its untagged neighbours of the same row, every product with that row is NaN either way;
 //   dz      has no patterns to spare in 16 bits: the tagged unit says "wide", and the reader fetches the row's values from DZ, which their
 //           writer has stored and released before it published.
-// (Looking for such values costs 0.15 us of a backward step, 4.38 -> 4.53 us over 140 steps with the launch, and nothing forward, 4.16 -> 4.11.)
+// (Looking for such values costs 0.15 us of a backward step, 4.33 -> 4.48 us, and nothing forward, 4.04 -> 3.94.)
 // Sums are taken in the order of the producers.
 // A slot may be written again because its readers have had to finish with it: h of step s + 2 needs shares of step s + 1 from column j,
 // those need h of step s + 1 from every block, and that needs the shares of step s from every work-group; likewise for the shares and backward.
 //
 // What bounds a step is the two exchanges, about 0.8 us for shares and 1.4 for h or dz, not the product (0.8 us, half of it operand reads from LDS).
-// Measured at n = 2048, 32 rows: 3.5 us a step forward and 4.1 backward, 11.1 and 21.9 in the per-step kernels.
+// Measured at n = 2048, 32 rows, 140 steps, the kernels alone: 3.9 us a step forward and 4.5 backward; 11.1 and 21.9 in the per-step kernels.
 #include "exchange_dev.h"
 #include <algorithm>
 
