@@ -220,6 +220,7 @@ bool persist_fwd_fits(const PFwdArgs& a);     // would launch_persist_fwd launch
 // fragment-ordered h buffers (initialised here), y / hprev float; nkc = chunks of 16 k.
 hipError_t launch_persist_fwd_f32(const PFwdArgs& a, hipStream_t s);
 bool persist_fwd_f32_fits(const PFwdArgs& a);
+bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward);      // are the float loops faster than the per-step kernels?
 
 struct PBwdDir {
   const uint4* Wb;    // as launch_prep_bwd_ll writes it

@@ -525,7 +525,8 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     pa.nkc = p.nkc_f;                    // (float storage: the per-step kernels' packed W_h and h buffers)
     set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile_f * 2 * p.nkc_f * 1024, (size_t)p.nrt * p.nkc_f * 1024);
   }
-  const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_fwd_f32_fits(pa);
+  const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_fwd_f32_fits(pa) &&
+                        persist_f32_pays(p.T, p.B, p.n, p.D, seq_lens != nullptr, pa.plain_launch, false);
   const bool single = use_ll ? persist_fwd_fits(pa) : use_ll32;
   if (T > 0 && (!use_ll || !single) && (rc = pack_w())) return rc;
   if (!single && (rc = state_in())) return rc;
@@ -667,7 +668,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     for (size_t d = 0; d < D; ++d) pa.d[d].lddy = (long)(D * n);       // (the check looks at the frame sizes)
     const bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_bwd_fits(pa);
     const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n <= 1024 && p.B <= 256 &&
-                          persist_bwd_f32_fits(pa);
+                          persist_bwd_f32_fits(pa) && persist_f32_pays(p.T, p.B, p.n, p.D, seq_lens != nullptr, pa.plain_launch, true);
     {
       Phase ph(LSTM_PHASE_PREP, 5, s);
       ZeroRegions z;

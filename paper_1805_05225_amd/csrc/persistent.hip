@@ -2529,6 +2529,27 @@ BwdKernel bwd_f32_for(int n) { return bwd_f32_nct(n) == 4 ? persist_bwd_f32_kern
 template <typename K>
 int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntile * cdiv(B, 16) * ndir <= capacity(kernel) ? 16 : 32; }
 
+// Few steps, or batches that take several launches, are faster in the per-step kernels (n = 700, 300 rows, both directions, 20 steps: forward
+// 1351 us here, 773 there).  Both sides as they were measured, in us, for n from 130 to 1024, 1 to 512 rows, 2 to 60 steps, one and two
+// directions, plain and cooperative launches (1573 shapes): the choice is within 5 % of the faster side in 99 % of them and never 1.25 times
+// it; always the loops was up to 2.8 times the other.  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
+bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward) {
+  const int form = n <= 256 ? 0 : n <= 512 ? 1 : 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
+  const bool one = (long)ntile * cdiv(B, 16) * ndir <= cap, pair = !one && B > 16;
+  const int launches = one ? 1 : cdiv(cdiv(B, 32), std::max(1, cap / (ntile * ndir)));
+  const double w = (double)n * n / (1024.0 * 1024.0) * ndir, nr = (double)n * ndir * B * 1e-5, nnr = nr * n * 1e-3, part = lens && pair ? 0.8 : 1.0;
+  double here, there;
+  if (backward) {
+    const double step[2][3] = {{3.4, 5.7, 8.4}, {9.9, 17.5, 20.4}};
+    here = 31.4 + 18.0 * w + launches * (plain_launch ? 23.6 : 44.5) + launches * T * step[pair][form] * part;
+    there = 58.3 + 16.0 * w + T * std::max(4.25 + 17.1e-3 * n + 6.6 * nr + 10.4 * nnr, 22.0 * nnr);
+  } else {
+    const double step[2][3] = {{2.9, 4.7, 6.9}, {5.4, 7.9, 12.6}};
+    here = 15.4 + 11.7 * w + launches * (plain_launch ? 10.6 : 31.9) + launches * T * step[pair][form] * part;
+    there = 27.9 + 7.8 * w + T * std::max(3.8 + 6.15e-3 * n + 4.15 * nr + 4.9 * nnr, 10.9 * nnr);
+  }
+  return here < there;
+}
 bool persist_fwd_f32_fits(const PFwdArgs& a) {
   if (a.n > 1024 || a.T < 2) return false;
   const long ring_bytes = (long)cdiv(a.B, 16) * a.nkc * 1024;

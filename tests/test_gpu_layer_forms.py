@@ -62,7 +62,7 @@ def _layer(T, B, n_in, n, bidir, dt):
             P.compare(f, g, *P.run_oracle(c, bidir, direction), TOL[dt])
 
 
-@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 20, 1040), ("bf16", 16, 33, 2048), ("bf16", 5, 9, 330), ("bf16", 4, 6, 64), ("f32", 5, 33, 331),
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 20, 1040), ("bf16", 16, 33, 2048), ("bf16", 5, 9, 330), ("bf16", 4, 6, 64), ("f32", 40, 33, 331),
                                       ("f32", 4, 6, 64), ("f32", 3, 5, 1100)])
 @pytest.mark.parametrize("direction", [1, -1])
 def test_state_in_place(dt, T, B, n, direction):
@@ -86,7 +86,7 @@ def test_state_in_place(dt, T, B, n, direction):
 
 # Outside the range of what the loops exchange: the result is the per-step kernels', which exchange nothing between work-groups of a launch.
 @pytest.mark.parametrize("what", ["nan_x", "nan_W", "large_W", "inf_dy", "large_dy"])
-@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 9, 1040), ("bf16", 24, 33, 2048), ("f32", 4, 9, 331), ("f32", 3, 40, 200), ("f32", 4, 17, 1000), ("f32", 3, 70, 1001)])
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 9, 1040), ("bf16", 24, 33, 2048), ("f32", 24, 9, 331), ("f32", 24, 40, 200), ("f32", 16, 17, 1000), ("f32", 16, 70, 1001)])
 def test_values_outside_the_exchange_range(dt, T, B, n, what):
     from paper_1805_05225_amd import binding as Bn
     P.Bn = Bn
@@ -112,7 +112,11 @@ def test_values_outside_the_exchange_range(dt, T, B, n, what):
         c["dy"][:, 1::4, 3::4] *= 2.0 ** 40
         c["dy"][:, 2::8, 1::8] *= -2.0 ** 45
     for direction in (1, -1):
+        Bn.profile_enable(1)
         f, g = P.run_gpu(c, dt, False, direction)
+        Bn.profile_enable(0)
+        launches = Bn.profile_read()
+        assert launches["loop_fwd"][1] < T and launches["loop_bwd"][1] < T       # (the loops it is about)
         fs, gs = P.run_gpu(c, dt, False, direction, flags=Bn.FLAG_PER_STEP)
         for name, got, ref in [(k, f[k], fs[k]) for k in ("y", "c", "hT", "cT")] + [(k, g[k], gs[k]) for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0")]:
             got, ref = host(got), host(ref)
@@ -170,6 +174,29 @@ def test_wide_layer_on_either_side_of_the_rule(T, B, n, bidir):
             check(k, f[k], host(fs[k]), TOL["bf16"])
         for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0"):
             check(k, g[k], host(gs[k]), TOL["bf16"])
+
+
+@pytest.mark.parametrize("T,B,n,bidir,loops", [(60, 100, 1000, True, True), (100, 5, 700, False, True), (30, 20, 300, True, True), (2, 40, 300, False, False),
+                                               (20, 300, 700, True, False), (9, 256, 200, True, None)])
+def test_float_layer_on_either_side_of_the_rule(T, B, n, bidir, loops):
+    """The single-launch loops where they pay (several launches of row tiles among them), the per-step kernels elsewhere; any lengths, against the
+    per-step result (another order of the float sums)."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(T + B + n)
+    c = P.rnd_case(rng, T, B, 24, n, 2 if bidir else 1, _lens(rng, T, B), "f32", scale=1.0 / np.sqrt(n))
+    fs, gs = P.run_gpu(c, "f32", bidir, flags=Bn.FLAG_PER_STEP)
+    for flags in (0, Bn.FLAG_PLAIN_LAUNCH):
+        Bn.profile_enable(1)
+        f, g = P.run_gpu(c, "f32", bidir, flags=flags, poison=True)
+        Bn.profile_enable(0)
+        launches = Bn.profile_read()
+        if loops is not None and not flags:       # (a plain launch costs the loops less: the rule may choose them then)
+            assert launches["loop_fwd"][1] == (1 if loops else T)
+        for k in ("y", "c", "hT", "cT"):
+            check(k, f[k], host(fs[k]), 5e-5)
+        for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0"):
+            check(k, g[k], host(gs[k]), 5e-5)
 
 
 @pytest.mark.parametrize("dt,T,B,n_in,n", [("bf16", 40, 21, 123, 330), ("f32", 20, 4, 32, 64), ("f32", 30, 16, 100, 200), ("bf16", 60, 32, 40, 1024)])
