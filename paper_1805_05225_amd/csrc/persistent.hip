@@ -2530,7 +2530,7 @@ template <typename K>
 int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntile * cdiv(B, 16) * ndir <= capacity(kernel) ? 16 : 32; }
 
 // Few steps, or batches that take several launches, are faster in the per-step kernels (n = 700, 300 rows, both directions, 20 steps: forward
-// 1351 us here, 773 there).  Both sides as they were measured, in us, for n from 130 to 1024, 1 to 512 rows, 2 to 60 steps, one and two
+// 1387 us here, 838 there).  Both sides as they were measured, in us, for n from 130 to 1024, 1 to 512 rows, 2 to 60 steps, one and two
 // directions, plain and cooperative launches (1573 shapes): the choice is within 5 % of the faster side in 99 % of them and never 1.25 times
 // it; always the loops was up to 2.8 times the other.  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward) {
