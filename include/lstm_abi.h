@@ -44,6 +44,8 @@
  *     sums of 2^33 and more.  There such a value may make the loop's bounded wait expire (lstm_sync_status reports it);
  *     LSTM_FLAG_PER_STEP has no such limit.  The float loops of n <= 1024 and the wide bfloat16 loops (n > 1024) carry sums of 2^32 and more
  *     between work-groups with 16 significant bits.
+ *   - The loops of 128 < n <= 1024 add a step's products in the order in which the other work-groups' values arrive: two calls with the same inputs
+ *     agree to the rounding of float sums (and of what is stored in bfloat16), not bit for bit.  LSTM_FLAG_PER_STEP repeats its bits.
  *   - Return value: 0 on success, a negative lstm_status otherwise.  Arguments are validated on
  *     the host before the first HIP call, so every argument error is reported without a GPU.
  *     Nothing throws or aborts across this boundary.  LSTM_OK says that the work was enqueued; it does not cover
