@@ -183,6 +183,8 @@ constexpr int kLLValsFwd = 16, kLLSlotsFwd = 16;     // 16 h values  -> 4 units 
 constexpr int kLLMaxNkcFwd = 32;                     // register budget of the kernels (n <= 1024)
 constexpr unsigned kLLFwdTagBit = 0x40000000u;       // in the upper dword of a unit: bit 14 of the fourth value
 inline int ll_nkc(int n, int slots) { return (int)((((long)(n + 15) / 16) * slots + 31) / 32); }
+// packed W_h of one direction; `paired`: in whole tiles of 32 units, for the 8-row kernel
+inline size_t ll_wf_bytes(int n, int nkc, bool paired) { return (size_t)(paired ? 2 * ((n + 31) / 32) : (n + 15) / 16) * 4 * nkc * 1024; }
 // The tag bit of the data that step tau consumes (written by step tau - 1 into slot tau & 1; the initial contents of
 // slot 0 carry it for tau = 0): it alternates between consecutive uses of a slot and is 1 at a slot's first use, so a
 // zero-filled slot never looks written.
@@ -193,7 +195,7 @@ __host__ __device__ inline unsigned ll_fwd_tag(unsigned tau) { return ((tau >> 1
 struct GridMap { int ntile, nrow, gpx; };
 
 struct PFwdDir {
-  const uint4* Wf;    // [unit tile][gate][nkc][64] chunks
+  const uint4* Wf;    // as launch_prep_fwd_ll writes it
   const uint4* Wzero; // one chunk (64 x 16 bytes) of zeros
   uint4* ring0; uint4* ring1;   // [row tile][nkc][64] chunks each
   float* gates;       // [T][B][4n]
@@ -215,6 +217,8 @@ struct PFwdArgs {
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
 };
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s);
+int persist_fwd_rows(int B, int n, int ndir); // rows per work-group, 8 or 16, which decides how W_h is packed (8: `paired`)
+int persist_bwd_rows(int B, int n, int ndir);
 bool persist_fwd_fits(const PFwdArgs& a);     // would launch_persist_fwd launch anything on this device?
 // Float storage (an initial hidden state goes into the pre-activations, as for bfloat16): Wf is the per-step kernel's packed W_h (launch_pack_wh_fwd), ring0 / ring1 its
 // fragment-ordered h buffers (initialised here), y / hprev float; nkc = chunks of 16 k.
@@ -385,9 +389,9 @@ hipError_t launch_fill_zero_many(const ZeroRegions& r, hipStream_t s);
 // The set-up of a bfloat16 single-launch loop in one launch: the fills of `z`, W_h in the kernel's order, (forward) the initial
 // ring, and the frame map of launch_frame_map if fm.fidx is not NULL.
 struct FrameMapArgs { const int* lens; int T, B; int* fidx; int* count; };
-hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, uint4* ring0, uint4* ring1,
+hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
                               int nrt, const FrameMapArgs& fm, hipStream_t s);
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s);
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]
 constexpr int kColsumSlices = 64;

@@ -103,7 +103,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   // error word, per-row-tile words, then one word per work-group of a single-launch kernel (its XCD)
   p->sync_bytes = up((64 + 2 * (size_t)p->nrt) * 4 + std::max(D * 2 * (size_t)p->nrt * cdiv(d->n, 32), (size_t)256) * 4);
   p->ws_sync = take(p->sync_bytes);              // first, so that lstm_sync_status() finds it without a plan
-  p->Wf_bytes = D * std::max((size_t)p->ntile_f * 2 * p->nkc_f, (size_t)p->ntile16 * 4 * p->nkc_ll_f) * 1024;
+  p->Wf_bytes = D * std::max((size_t)p->ntile_f * 2 * p->nkc_f * 1024, ll_wf_bytes(d->n, p->nkc_ll_f, true));
   p->ws_Wf = take(p->Wf_bytes + 1024);            // packed W_h, then one chunk of zeros
   const bool part = p->bf16 && d->n <= 1024;          // the partial-sum backward kernel may be chosen
   // float storage: the single-launch backward kernel (batches of up to 256 rows: its rings grow with B n^2 / 16)
@@ -441,6 +441,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     if (e == hipSuccess) return LSTM_OK;
     (void)hipGetLastError();               // refused before anything ran: the per-step path
   }
+  const bool paired = persist_fwd_rows(p.B, p.n, p.D) == 8;    // (how the bf16 single-launch kernel wants W_h)
   {
     Phase ph(LSTM_PHASE_PREP, 5, s);
     ZeroRegions z;
@@ -454,7 +455,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
         frames_mapped = true;
       }
-      HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
+      HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
                                 p.nrt, fm, s));
     } else HIPCHK(launch_fill_zero_many(z, s));
   }
@@ -520,7 +521,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   PFwdArgs pa = {};                      // the single-launch kernels' arguments, if one of them takes this problem
   if (use_ll) {
     pa.nkc = p.nkc_ll_f;
-    set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile16 * 4 * p.nkc_ll_f * 1024, (size_t)p.nrt * p.nkc_ll_f * 1024);
+    set_dirs(pa, ws + p.ws_Wf, ll_wf_bytes(p.n, p.nkc_ll_f, paired), (size_t)p.nrt * p.nkc_ll_f * 1024);
   } else {
     pa.nkc = p.nkc_f;                    // (float storage: the per-step kernels' packed W_h and h buffers)
     set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile_f * 2 * p.nkc_f * 1024, (size_t)p.nrt * p.nkc_f * 1024);
@@ -687,7 +688,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           z.add(dx, (size_t)TB * n_in * p.esz);
           dx_cleared = true;
         }
-        HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, fm, s));
+        HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, persist_bwd_rows(p.B, p.n, p.D) == 8, fm, s));
       } else HIPCHK(launch_fill_zero_many(z, s));
     }
     if (!use_ll) {

@@ -92,6 +92,20 @@ struct RingReader {
     const unsigned d = ((x[1] >> 16) ^ tag) | ((x[3] >> 16) ^ tag);
     return lim_step * it < lim ? d & (kLLFwdTagBit >> 16) : 0u;
   }
+  // The poll after its first, mostly successful, look (which stays in line: a loop around it costs its branches in every step).
+  template <typename L, typename S>
+  __device__ __forceinline__ void poll_again(bool& dead, L&& loads, S&& stale) const {
+    for (unsigned poll = 1;; ++poll) {
+      PROF_POLLS(1)
+      loads();
+      if (!stale()) return;
+      if (poll >= limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
+        st_relaxed(err, 1u);
+        dead = true;
+        return;
+      }
+    }
+  }
   // Second pass over the loads marked in `redo`, all of them in flight at once: every round fetches those still
   // marked, hands the ones whose tags have all turned to `use` (operand as loaded, tags included) and keeps the
   // rest for the next round (bounded).
@@ -137,9 +151,7 @@ __device__ __forceinline__ RingReader make_reader(const uint4* base, int nkc, in
 // Reader for a work-group that owns only 8 of a row tile's 16 rows (`half` selects which).  A load would
 // leave half the lanes idle, and the time of a ring read goes with the number of loads, not their bytes; so one
 // load serves TWO chunks: lanes whose fragment row is below 8 fetch our rows of chunk wave + 8*it, the others
-// our rows of chunk wave + 8*it + 4.  The registers as loaded are the A operand of the first chunk with our rows
-// in fragment rows 0-7 (rows 8-15 hold the other chunk's data: rows of a matrix product are independent, and
-// those output rows are never read); rotating each group of 16 lanes by 8 gives the operand of the second.
+// our rows of chunk wave + 8*it + 4; rows_from_low and rows_from_high make the two operands of it.
 __device__ __forceinline__ RingReader make_reader_half(const uint4* base, int nkc, int nchunk_valid, int wave, int lane, int half,
                                                         unsigned tag, unsigned* err, unsigned limit, int rot) {
   RingReader r;
@@ -153,16 +165,6 @@ __device__ __forceinline__ RingReader make_reader_half(const uint4* base, int nk
   r.tag = tag; r.err = err; r.limit = limit;
   return r;
 }
-__device__ __forceinline__ uint4 rotate_rows_by_8(uint4 v) {
-  constexpr int kRowRor8 = 0x128;        // DPP control: rotate right by 8 inside each row of 16 lanes
-  uint4 o;
-  o.x = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v.x, kRowRor8, 0xf, 0xf, false);
-  o.y = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v.y, kRowRor8, 0xf, 0xf, false);
-  o.z = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v.z, kRowRor8, 0xf, 0xf, false);
-  o.w = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v.w, kRowRor8, 0xf, 0xf, false);
-  return o;
-}
-
 // two floats -> two bf16 (round to nearest even) in one register, low half first
 __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
   typedef __attribute__((ext_vector_type(2))) float f32x2_;
@@ -197,6 +199,34 @@ __device__ __forceinline__ void mfma_b_agpr(f32x4& acc, const u32x4& a, const u3
 __device__ __forceinline__ void mfma_b_vgpr(f32x4& acc, const u32x4& a, const u32x4& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
+// --- eight rows, no wasted half --------------------------------------------------------------------------------
+// The dense 16x16x32 product of a work-group of 8 rows multiplies 8 rows of nothing.  The sparse instruction (16x16x64, the same 16
+// cycles) takes an A of which two of every four k are stored, and WHICH two may differ from row to row.  Fragment rows 0-7 and 8-15
+// both hold our rows; the former say that their values belong to the k that are 0 or 1 mod 4, the latter 2 or 3 mod 4 (kSparseLow,
+// kSparseHigh: the positions, two bits each).  With the weights of one column tile at the former k of B and those of the next tile at the
+// latter, one instruction does the work of two: fragment rows 0-7 of the result are the first tile's, rows 8-15 the second's.  The bits
+// are those of the dense product (51200 sums of 8 x 32 products compared on the device).
+// Lane l supplies for A row l%16 the eight stored values of k = 16 (l/16) .. +15, for B column l%16 the k 8 (l/16) .. +7 in the
+// first four registers and 32 + those in the last four (measured on the device).
+constexpr int kSparseLow = 0x44444444, kSparseHigh = (int)0xeeeeeeeeu;
+// What element e of lane group g holds in B register set `set` (0, 1): column tile, and which of the 32 k.
+__host__ __device__ constexpr int sparse_tile(int e) { return (e >> 1) & 1; }
+__host__ __device__ constexpr int sparse_k(int set, int g, int e) { return 8 * (2 * set + (g >> 1)) + ((g & 1) * 2 + (e >> 2)) * 2 + (e & 1); }
+typedef __attribute__((ext_vector_type(8))) unsigned u32x8;
+// two register sets as one operand (behind agpr_loads_done: until then nothing may copy them)
+__device__ __forceinline__ u32x8 agpr_join(u32x4& lo, u32x4& hi) {
+  asm volatile("" : "+a"(lo), "+a"(hi));
+  u32x8 r = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  asm volatile("" : "+a"(r));            // (an accumulation-register value from here on: no copy at its uses)
+  return r;
+}
+__device__ __forceinline__ void smfmac_b_agpr(f32x4& acc, const u32x4& a, const u32x8& b, int idx) {
+  asm volatile("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+v"(acc) : "v"(a), "a"(b), "v"(idx));
+}
+// The operands of a load whose lanes hold one chunk in fragment rows 0-7 and another in rows 8-15 (make_reader_half): its first
+// (second) chunk in all rows.  Rotated by 8 inside each row of 16 lanes, written to the upper (lower) eight only.
+__device__ __forceinline__ unsigned rows_from_low(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xf, 0xc, false); }
+__device__ __forceinline__ unsigned rows_from_high(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xf, 0x3, false); }
 // acc = A x B: the first product of a chain takes the constant 0 as its addend, so the accumulators need no clearing
 // (64 moves per step in the backward kernel, and the wait states between them and the first MFMA).  The result may not share
 // registers with an operand: early clobber.
@@ -247,6 +277,7 @@ __device__ __forceinline__ void static_for(F&& f) {
     f(std::integral_constant<int, N - 1>{});
   }
 }
+__device__ __forceinline__ void operands_settle(u32x4& a) { asm volatile("s_nop " LSTM_OPERAND_NOPS : "+v"(a)); }
 __device__ __forceinline__ void operands_settle(u32x4& a, u32x4& b) { asm volatile("s_nop " LSTM_OPERAND_NOPS : "+v"(a), "+v"(b)); }
 __device__ __forceinline__ void operands_settle(u32x4& a, u32x4& b, u32x4& c, u32x4& d) {
   asm volatile("s_nop " LSTM_OPERAND_NOPS : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
@@ -255,6 +286,7 @@ __device__ __forceinline__ void operands_settle(f32x4& a, f32x4& b, f32x4& c, f3
   asm volatile("s_nop " LSTM_OPERAND_NOPS : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
 }
 // 20 wait states: more than any MFMA of this shape needs before its result may be read or overwritten
+__device__ __forceinline__ void mfma_settle(f32x4& a0, f32x4& a1) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(a0), "+v"(a1)); }
 __device__ __forceinline__ void mfma_settle(f32x4& a0, f32x4& a1, f32x4& a2, f32x4& a3) {
   asm volatile("s_nop 15\n\ts_nop 3" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3));
 }
@@ -292,11 +324,13 @@ __device__ __forceinline__ WgCoord wg_coord(const GridMap& m, int ndir) {
 
 // ------------------------------------------------------------------------------------------------
 // forward: z[8 rows, 4 gates x 32 units] = h[8 rows, K] W[K, 128].  A work-group owns 32 units for 8 batch rows
-// (half a row tile); one load serves two chunks (see make_reader_half).  The W_h slice fills the 256 accumulation
-// registers of every lane (n = 1024: 8 register sets of 8 fragments).
-template <int NIT>
+// (half a row tile); one load serves two chunks (see make_reader_half), one product two column tiles (see smfmac_b_agpr).  The W_h
+// slice fills the 256 accumulation registers of every lane (n = 1024).
+template <int NL>                                          // ring loads per wavefront and step: n <= 256 NL
 __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   __shared__ float red[2][4][8][129];                    // two copies, used by even and odd steps: one barrier per step
+  constexpr int kAhead = 2;                              // frames of x W_x + b that are fetched together (fetch_zx below)
+  __shared__ float zxs[kAhead][4][2][4][32];             // [frame][wavefront][row][gate][unit]: a wavefront reads back what it asked for
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
@@ -309,27 +343,25 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   bool dead = false;
 
   const int nitv = (nkc + 7) / 8, rot = tile2 % nitv;
-  // Register sets 2p, 2p+1 hold the two chunks that load p of the stream fetches.  The first kAccIts sets fill the
-  // 256 accumulation registers, the rest sit in vector registers.  Sets of chunks past the end (or of a unit tile
-  // past the end) are loaded from a chunk of zeros that the host keeps behind the packed weights.
-  constexpr int kAccIts = NIT < 8 ? NIT : 8;
-  u32x4 wa[kAccIts][2][4];
-  u32x4 wv[NIT - kAccIts > 0 ? NIT - kAccIts : 1][2][4];
+  // Operands 2p, 2p + 1 of a gate are the two chunks that load p of the stream fetches.  Those of chunks past the end are loaded
+  // from a chunk of zeros that the host keeps behind the packed weights.
+  u32x4 w4[2 * NL][4][2];
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
+  for (int it = 0; it < 2 * NL; ++it) {
     const int kc = wave + 4 * (2 * rot_index(it >> 1, rot, nitv) + (it & 1));
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-      const int t16 = tile2 * 2 + ct;
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint4* src = (kc < nkc && t16 < ntiles16) ? &d.Wf[((long)(t16 * 4 + q) * nkc + kc) * 64 + lane] : &d.Wzero[lane];
-        if (it < kAccIts) wa[it][ct][q] = load_to_agpr(src);
-        else wv[it - kAccIts][ct][q] = *(const u32x4*)src;
-      }
-    }
+      for (int set = 0; set < 2; ++set)
+        w4[it][q][set] = load_to_agpr(kc < nkc ? &d.Wf[(((long)(tile2 * 4 + q) * nkc + kc) * 2 + set) * 64 + lane] : &d.Wzero[lane]);
   }
   agpr_loads_done();
+  u32x8 w[2 * NL][4];
+#pragma unroll
+  for (int it = 0; it < 2 * NL; ++it)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[it][q] = agpr_join(w4[it][q][0], w4[it][q][1]);
+  const int sparse = (lane & 8) ? kSparseHigh : kSparseLow;
 
   const int r8 = tid >> 5, u = tid & 31;                 // pointwise pair of this thread: row r8 of the half, unit u of 32
   const int b = rt * 16 + half * 8 + r8, j = tile2 * 32 + u;
@@ -357,9 +389,8 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
 
   // x W_x + b of a frame is read through a buffer descriptor that covers exactly that frame: a lane with nothing to
   // fetch (row past the batch, unit past n, frame past the row's length) has its offset parked outside and gets zeros
-  // without touching memory, as does every lane once the frames are used up (zero-sized descriptor).  Nothing is
-  // predicated, so every step issues the same four loads: with loads that may or may not have been issued the
-  // compiler has to assume the fewest when it places the waits.
+  // without touching memory, as does every lane once the frames are used up (zero-sized descriptor); of four units that end past
+  // the frame the check drops those.  Nothing is predicated, so every step issues the same loads.
   // The outputs go the same way: one descriptor per array and frame (zero-sized if the array is absent), offsets
   // that never change, parked where a lane has nothing to store; and so does the ring store, whose descriptor ends
   // below the parking offset.  Frame sizes in bytes: gates [B,4n] float, y [B,ldy] bf16, cs [B,n] float, hprev [B,ldh] bf16.
@@ -373,23 +404,31 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   auto frame_of = [&](const void* base, int t, unsigned bytes, bool present = true) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)t * bytes), 0, present && base != nullptr ? bytes : 0u, kBufFlags);
   };
-  auto fetch_zx = [&](int tau, float (&z)[4]) {
-    const bool ok = tau < T;
-    const int t = d.rev ? T - 1 - tau : tau;
-    const __amdgpu_buffer_rsrc_t rg =
-        __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)d.gates + (unsigned long long)(unsigned)(ok ? t : 0) * g_bytes), 0, ok ? g_bytes : 0u, kBufFlags);
-    const unsigned go = t < L ? g_off : kParked;           // (L is 0 in lanes without a row)
+  // The frames' values come from HBM, 450-530 ns away (1 us for the slowest of a group's 128 wavefronts), and a compute unit hands
+  // loads back in the order of issue: ring loads asked for meanwhile wait for them.  With four loads a frame, one frame at a time,
+  // that was a third of the step once the products took half their time (n = 1024, 32 rows, both directions: 2.18 us a step, 1.29
+  // without the fetch, 1.34 with it from L2).  So a lane brings four units of one gate, a wavefront's two rows of a frame being ONE
+  // load into LDS, and kAhead frames are fetched together: every other step pays, and hardly (2 frames: 1.40, 4: 1.51, 8: 1.45;
+  // 256 units, 16 rows: 1.03, 1.16, 1.12).  With all of it the step went from 1.61 to 1.33 us (330 units, 21 rows: 1.24 to 0.96).
+  const int zq = (lane >> 3) & 3, zu = tile2 * 32 + 4 * (lane & 7);
+  const int L_row = b < B && zu < n ? clamp_len(a.lens, b, T) : 0;
+  const unsigned zx_off = ((unsigned)b * 4u * n + (unsigned)zq * n + zu) * 4u;
+  const unsigned zxs_wave = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&zxs[0][wave][0][0][0]);
+  // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight)
+  auto fetch_zx = [&](int tau0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) z[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, go, (unsigned)q * 4u * n, 2));   // 2: non-temporal
+    for (int f = 0; f < kAhead; ++f) {
+      const bool ok = tau0 + f < T;
+      const int t = d.rev ? T - 1 - tau0 - f : tau0 + f;
+      const __amdgpu_buffer_rsrc_t rg =
+          __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)d.gates + (unsigned long long)(unsigned)(ok ? t : 0) * g_bytes), 0, ok ? g_bytes : 0u, kBufFlags);
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(zxs_wave + (unsigned)f * (unsigned)sizeof(zxs[0])), "v"(t < L_row ? zx_off : kParked), "s"(rg) : "memory");
+    }
   };
-  float zx_a[4], zx_b[4];
   unsigned h_prev_bits = pack_bf16x2(h, 0.f) & 0xffffu;     // what hprev receives: h before the step, as bf16
-  fetch_zx(0, zx_a);
+  fetch_zx(0);
   PROF_DECL
-  // One time step.  `zx` holds this step's x W_x + b and `zx_next` receives the next step's; the loop below calls it
-  // with the two in alternating roles, because a copy at the end of a step would have to wait for the loads (and,
-  // counted with them, the step's stores) at that point.
-  auto step = [&](const int tau, const float (&zx)[4], float (&zx_next)[4], auto parity) __attribute__((always_inline)) {
+  auto step = [&](const int tau, auto parity) __attribute__((always_inline)) {
     float (&red_)[4][8][129] = red[decltype(parity)::value];
     const int t = d.rev ? T - 1 - tau : tau;
     const bool valid = active && t < L;
@@ -397,36 +436,38 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
     const uint4* rin = ((tau & 1) ? d.ring1 : d.ring0) + (long)rt * nkc * 64;
     uint4* rout = (tau & 1) ? d.ring0 : d.ring1;
     RingReader rd = make_reader_half(rin, nkc, ntiles16 * 2, wave, lane, half, ll_fwd_tag((unsigned)tau) << 14, err, a.spin_limit, rot);
-    f32x4 acc[2][4];
+    constexpr int zslot = decltype(parity)::value;
+    constexpr bool fetches = zslot == kAhead - 1;
+    float zx[4];
+    auto fetch_next = [&]() __attribute__((always_inline)) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // the last of the frames has been read
+      fetch_zx(tau + 1);
+    };
+    f32x4 acc[4];
     {
-      // One MFMA of register set `it` into accumulator (ct, q).
-      auto mma_one = [&](int it, int ct, int q, const u32x4& a_op) __attribute__((always_inline)) {
-        if (it < kAccIts) mfma_b_agpr(acc[ct][q], a_op, wa[it < kAccIts ? it : 0][ct][q]);
-        else mfma_b_vgpr(acc[ct][q], a_op, wv[it >= kAccIts ? it - kAccIts : 0][ct][q]);
-      };
       auto use_single = [&](int p, const u32x4& raw) {     // a load fetched again after the stream, tags still in it
-        const uint4 av_ = make_uint4(raw[0], raw[1] & ~kLLFwdTagBit, raw[2], raw[3] & ~kLLFwdTagBit);
-        const uint4 av2_ = rotate_rows_by_8(av_);
-        u32x4 av = {av_.x, av_.y, av_.z, av_.w}, av2 = {av2_.x, av2_.y, av2_.z, av2_.w};
-        operands_settle(av, av2);
+        u32x4 av[2];
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
+        for (int c = 0; c < 4; ++c) {
+          const unsigned v = raw[c] & ((c & 1) ? ~kLLFwdTagBit : ~0u);
+          av[0][c] = rows_from_low(v);
+          av[1][c] = rows_from_high(v);
+        }
+        operands_settle(av[0], av[1]);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            mma_one(2 * p, ct, q, av);
-            mma_one(2 * p + 1, ct, q, av2);
-          }
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) smfmac_b_agpr(acc[q], av[o], w[2 * p + o][q], sparse);
       };
-      // The stream.  The loads are consumed in pairs: a pair is four chunks, and every accumulator takes its four
-      // products in a row.  An MFMA of this shape issues every 16 cycles (7.05 ns measured, in any order of the
-      // accumulators) and occupies the issue slot of the wavefront for 4 of them: one independent instruction behind
-      // it is free (7.4 ns per MFMA measured), three dependent ones are not (12.4 ns).  What turns the next pair's loads
-      // into operands (tag test, masking the tags off, the rotated copies) is cut into single instructions, and one
-      // is placed behind each of the first MFMAs of the pair before: there it costs nothing, in front of the pair's
-      // own MFMAs it was a fifth of the step.  A pair with a stale tag in any lane is skipped (wave-uniform branch)
+      // The stream.  The loads are consumed in pairs: a pair is four chunks, and every accumulator takes its four products in that
+      // order.  A product of this shape issues every 16 cycles (7.05 ns measured, in any order of the
+      // accumulators) and occupies the issue slot of the wavefront for 4 of them: independent instructions behind
+      // it are free, dependent ones are not (three: 12.4 ns).  What turns the loads
+      // into operands (tag test, masking the tags off, chunks into all rows) is cut into single instructions that follow the
+      // products of the chunk before.  A pair with a stale tag in any lane is skipped (wave-uniform branch)
       // and both its loads are fetched again by fix_up.
-      static_assert((NIT / 2) % 2 == 0, "loads are consumed in pairs");
-      constexpr int NL = NIT / 2, NP = NL / 2, kPrepSteps = 14;
+      static_assert(NL % 2 == 0, "loads are consumed in pairs");
+      constexpr int NP = NL / 2;
       u32x4 x[NL];
       const unsigned tagw = rd.tag << 16;
       // The poll IS the first pair of loads: they are repeated (bounded) until all their tags have turned, and what
@@ -434,108 +475,93 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
       // first pair's MFMAs instead of in front of the whole stream (a poll of its own followed by all loads cost one
       // round trip more per step, a tenth of it).  (Nine times out of ten the first round succeeds; yet issuing
       // everything at once without looking was measured slower: the values arrive while the poll is in flight.)
-      for (unsigned poll = 0;; ++poll) {
+      auto poll_loads = [&]() __attribute__((always_inline)) {
         x[0] = rd.load_it(rd.it_of(0));
         x[1] = rd.load_it(rd.it_of(1));
-        // The accumulators are cleared while the poll is in flight.  (By moves: starting each chain with an MFMA that
-        // adds to the constant 0, as the backward kernel does, was measured 10 % slower per step here.)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[ct][q] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        operands_settle(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
-        operands_settle(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (dead) break;
+      };
+      auto polled_stale = [&]() __attribute__((always_inline)) {
         const unsigned stale = rd.tag_diff(x[0], rd.it_of(0), tagw) | rd.tag_diff(x[1], rd.it_of(1), tagw);
-        if (__builtin_amdgcn_ballot_w64(stale > 0xffffu) == 0ull) break;
-        if (poll >= rd.limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
-          st_relaxed(err, 1u);
-          dead = true;
-          break;
-        }
-        PROF_POLLS(1)
-      }
+        return __builtin_amdgcn_ballot_w64(stale > 0xffffu) != 0ull;
+      };
+      poll_loads();
+      // The accumulators are cleared while the poll is in flight.  (By moves: starting each chain with an MFMA that
+      // adds to the constant 0, as the 16-row backward kernel does, was measured 10 % slower per step here.)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      operands_settle(acc[0], acc[1], acc[2], acc[3]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (__builtin_expect(polled_stale() && !dead, 0)) rd.poll_again(dead, poll_loads, polled_stale);
       PROF_MARK(5)
+      __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0): nothing is in flight behind the poll, frames included
 #pragma unroll
       for (int i = 2; i < NL; ++i) x[i] = rd.load_it(rd.it_of(i));
       __builtin_amdgcn_sched_barrier(0);
-      u32x4 ops[NP][4];                                    // [0] load 2p as fetched, [1] its rows rotated by 8, [2], [3]: load 2p+1
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < 4; ++q) zx[q] = zxs[zslot][wave][lane >> 5][q][u];
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 ops[NL][2];
       unsigned bad[NP];                                    // tag mismatches of the pair, per lane, in the upper 16 bits
-      auto prep = [&](int p, int k) __attribute__((always_inline)) {
-        const int second = k >= kPrepSteps / 2, i = 2 * p + second, kk = second ? k - kPrepSteps / 2 : k;
+      // step 0: tag test; 1, 2: tags off; 3 .. 6: first chunk into all rows; 7 .. 10: second chunk
+      auto prep = [&](int i, int kk) __attribute__((always_inline)) {
         if (kk == 0) {
           const unsigned m = rd.tag_diff(x[i], rd.it_of(i), tagw);
-          bad[p] = second ? (bad[p] | m) : m;
-        } else if (kk == 1) {
-          x[i][1] &= ~kLLFwdTagBit;
-        } else if (kk == 2) {
-          x[i][3] &= ~kLLFwdTagBit;
-          ops[p][2 * second] = x[i];
+          bad[i >> 1] = (i & 1) ? (bad[i >> 1] | m) : m;
+        } else if (kk < 3) {
+          x[i][2 * kk - 1] &= ~kLLFwdTagBit;
+        } else if (kk < 7) {
+          ops[i][0][kk - 3] = rows_from_low(x[i][kk - 3]);
         } else {
-          ops[p][2 * second + 1][kk - 3] = (unsigned)__builtin_amdgcn_mov_dpp((int)x[i][kk - 3], 0x128, 0xf, 0xf, false);
+          ops[i][1][kk - 7] = rows_from_high(x[i][kk - 7]);
         }
       };
       unsigned long long redo = 0ull;
 #pragma unroll
-      for (int k = 0; k < kPrepSteps; ++k) prep(0, k);
-#pragma unroll
       for (int p = 0; p < NP; ++p) {
         __builtin_amdgcn_sched_barrier(0);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad[p] > 0xffffu) == 0ull, 1)) {
-          operands_settle(ops[p][0], ops[p][1], ops[p][2], ops[p][3]);
-          // The next frame's x W_x + b, from HBM, goes out where this wavefront's last ring load has arrived.  The CU hands
-          // loads back in the order of issue, other wavefronts' included: a pair earlier, it holds up the ring loads still
-          // in flight (+17 % per step); behind the last pair's MFMAs, where it used to be, it is in the next step's poll's way (+3 %).
-          if (p == NP - 1) fetch_zx(tau + 1, zx_next);
+        if (p > 0) { prep(2 * p, 0); prep(2 * p + 1, 0); }  // (the poll has looked at the first pair)
+        if (p == 0 || __builtin_expect(__builtin_amdgcn_ballot_w64(bad[p] > 0xffffu) == 0ull, 1)) {
 #pragma unroll
-          for (int ct = 0; ct < 2; ++ct)
+          for (int kk = 1; kk < 7; ++kk) prep(2 * p, kk);
+          operands_settle(ops[2 * p][0]);
+          // The next frames go out where this wavefront's last ring load has arrived: the compute unit hands loads back in the
+          // order of issue, other wavefronts' included, so earlier they hold up ring loads still in flight, and later they are in the
+          // next step's poll's way.
+          if (fetches && p == NP - 1 && redo == 0ull) fetch_next();
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+          for (int o = 0; o < 4; ++o)
 #pragma unroll
-              for (int o = 0; o < 4; ++o) {
-                mma_one(4 * p + o, ct, q, ops[p][o]);
-                // the second pair's loads were issued just before the first pair's MFMAs: their turn comes late
-                const int m = (ct * 4 + q) * 4 + o - (p == 0 ? 32 - kPrepSteps : kPrepDelay);
-                if (p + 1 < NP && m >= 0 && m < kPrepSteps) {
-                  __builtin_amdgcn_sched_barrier(0);
-                  prep(p + 1, m);
-                  __builtin_amdgcn_sched_barrier(0);
-                }
-
-              }
+            for (int q = 0; q < 4; ++q) {
+              smfmac_b_agpr(acc[q], ops[2 * p + (o >> 1)][o & 1], w[4 * p + o][q], sparse);
+              __builtin_amdgcn_sched_barrier(0);
+              // the pair's other operands, two products ahead of theirs (the wait states between the two)
+              const int i = 2 * p + (o > 0), kk = o == 1 ? 3 : 7;
+              if (o < 3 && q < 2) { prep(i, kk + 2 * q); prep(i, kk + 2 * q + 1); }
+              if (o == 0 && q == 2) { prep(i + 1, 1); prep(i + 1, 2); }
+              __builtin_amdgcn_sched_barrier(0);
+            }
         } else {                                           // rare once the sample has turned
           redo |= 3ull << (2 * p);
-          if (p == NP - 1) fetch_zx(tau + 1, zx_next);
-          if (p + 1 < NP) {
-            // The empty statement makes the loads' registers new values on this path: instructions that are the
-            // same on both paths are moved in front of the branch, and with them the wait for the next pair's loads.
-            asm volatile("" : "+v"(x[2 * p + 2]), "+v"(x[2 * p + 3]));
-#pragma unroll
-            for (int k = 0; k < kPrepSteps; ++k) prep(p + 1, k);
-          }
         }
       }
       PROF_REDO(__popcll(redo))
+      const bool asked_again = redo != 0ull;
       if (redo) {
         rd.fix_up_batch<NL>(redo, dead, use_single);
         // (nothing of that is outstanding any more - said with an instruction the compiler takes note of: it cannot tell
         // from the loop's exits, and would make whatever reuses those registers below wait for every load in flight)
         __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0)
       }
-      mfma_settle(acc[0][0], acc[0][1], acc[0][2], acc[0][3], acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
+      mfma_settle(acc[0], acc[1], acc[2], acc[3]);
+      if (fetches && asked_again) fetch_next();
     }
     PROF_MARK(0)
-    // accumulator rows 4*(lane/16) + v; this work-group's rows sit in fragment rows 0..7
-    if (lane < 32) {
+    // fragment rows 4*(lane/16) + v: rows 0-7 of the unit tile's first 16 columns, then of the others
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) red_[wave][4 * (lane >> 4) + v][q * 32 + ct * 16 + (lane & 15)] = acc[ct][q][v];
-    }
+      for (int v = 0; v < 4; ++v) red_[wave][4 * ((lane >> 4) & 1) + v][q * 32 + (lane >> 5) * 16 + (lane & 15)] = acc[q][v];
     PROF_MARK(1)
     __syncthreads();
 
@@ -577,8 +603,8 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
     PROF_MARK(3)
   };
   for (int tau = 0; tau < T; tau += 2) {
-    step(tau, zx_a, zx_b, std::integral_constant<int, 0>{});
-    if (tau + 1 < T) step(tau + 1, zx_b, zx_a, std::integral_constant<int, 1>{});
+    step(tau, std::integral_constant<int, 0>{});
+    if (tau + 1 < T) step(tau + 1, std::integral_constant<int, 1>{});
   }
   PROF_DUMP("fwd8", T)
   if (active) {
@@ -950,7 +976,8 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
 // With one wavefront per SIMD every instruction's latency is exposed (about 2 ns each), so the formats are chosen
 // to keep instruction counts low: an 8-byte unit holds values of ONE output for four ROWS, which
 // is how an MFMA accumulator lane holds them, so a producer stores straight from its accumulators - no staging,
-// no cross-lane moves.  Ring layout per direction and slot:
+// no cross-lane moves.  (n = 1024, 32 rows, both directions: 1.75 us a step with dense products that compute every row twice and
+// inputs fetched a frame at a time, 1.33 now; 330 units, 21 rows 1.41, 1.03.)  Ring layout per direction and slot:
 //   [row group][destination tile][producer tile][32 outputs][2 row halves] x 8 bytes (rows 4g .. 4g+3 as bf16).
 // The tag is ONE BIT, bit 14 of the fourth value (see the forward ring): the partial sums travel scaled by 2^-32 - the
 // packed W_h carries the factor, so the MFMAs deliver them scaled, and the consumer multiplies its sum by 2^32 - which
@@ -970,6 +997,11 @@ template <int NPW, int NCT>                               // n <= 128 * NPW (pro
 __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   __shared__ float red[8][8][33];                        // [wavefront, producer of the pair][row][output]
   __shared__ __attribute__((aligned(16))) unsigned short zb[8][136];
+  constexpr int kAhead = NCT == 16 ? 2 : 4;              // frames whose inputs are fetched together (fetch_in below)
+  static_assert(kAhead >= 2, "a step reads its inputs before its poll: they have to be there from the step before");
+  // inputs of the next frames, [frame][wavefront][...][lane or row, unit]: a wavefront reads back what it asked for
+  __shared__ float in_g[2 * kAhead][4][2][4][32], in_c[2 * kAhead][4][64];
+  __shared__ unsigned in_y[2 * kAhead][4][64];
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
@@ -980,12 +1012,20 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   unsigned* err = a.sync;
   bool dead = false;
 
-  u32x4 w[4][NCT];                                       // all 256 accumulation registers at NCT = 16
+  u32x4 w4[4][NCT / 2][2];                               // all 256 accumulation registers at NCT = 16
 #pragma unroll
   for (int kc = 0; kc < 4; ++kc)
 #pragma unroll
-    for (int c = 0; c < NCT; ++c) w[kc][c] = load_to_agpr(&d.Wb[((((long)J * 4 + wave) * 4 + kc) * NCT + c) * 64 + lane]);
+    for (int P = 0; P < NCT / 2; ++P)
+#pragma unroll
+      for (int set = 0; set < 2; ++set) w4[kc][P][set] = load_to_agpr(&d.Wb[((((long)J * 4 + wave) * 4 + kc) * NCT + 2 * P + set) * 64 + lane]);
   agpr_loads_done();
+  u32x8 w[4][NCT / 2];                                   // gate kc, destination tile P of this wavefront (two column tiles)
+#pragma unroll
+  for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+    for (int P = 0; P < NCT / 2; ++P) w[kc][P] = agpr_join(w4[kc][P][0], w4[kc][P][1]);
+  const int sparse = (lane & 8) ? kSparseHigh : kSparseLow;
 
   const int r8 = tid >> 5, u = tid & 31;                 // pointwise pair of this thread
   const int b = R * 8 + r8, j = J * 32 + u;
@@ -998,82 +1038,76 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
     if (d.dcT) Dc = d.dcT[(long)b * n + j];
     L = clamp_len(a.lens, b, T);
   }
-  // What the gate gradients of one frame need.  dy stays as the 16 bits that were loaded: a conversion right behind
-  // the load would make the wavefront wait for it - and for every load in front of it - where it is issued.
-  struct In { float gi, gf, gg, go, c_new, c_prev; unsigned dy_bits; };
+  // What the gate gradients of a frame need: gates, the cell state entering it, dy.
   // The per-frame arrays are read through buffer descriptors that cover exactly one frame: the frame's address is
   // scalar arithmetic, a lane's offset inside the frame never changes, and a lane with nothing to fetch (row past the
   // batch, unit past n, frame past the row's length) has its offset parked outside the frame and gets zeros without
   // touching memory - as does every lane when the frame itself does not exist (zero-sized descriptor).  Nothing is
-  // predicated, so every step issues the same six loads; with loads that may or may not have been issued the
-  // compiler has to assume the fewest, and made the wavefront wait for the loads of the NEXT frame, just issued and
-  // on their way from HBM, where it only needed those of this one.
+  // predicated.  They come from HBM, and a compute unit hands loads back in the order of issue: the ring loads behind them wait.
+  // Six loads a step cost 0.17 us of it; so a lane brings four units of a gate, the loads write LDS, three a frame, and kAhead frames
+  // are fetched together (see the forward kernel; n = 1024: 2 frames 1.34 us a step, 4 1.33; 256 units: 0.99, 0.97).
   constexpr unsigned kParked = 0x7ff00000u;
   const unsigned g_bytes = (unsigned)B * 4u * n * 4u, s_bytes = (unsigned)B * n * 4u, y_bytes = (unsigned)B * d.lddy * 2u;
   const unsigned g_off = active ? ((unsigned)b * 4u * n + j) * 4u : kParked;
   const unsigned s_off = active ? ((unsigned)b * n + j) * 4u : kParked;
   const unsigned y_off = active ? ((unsigned)b * d.lddy + j) * 2u : kParked;
+  // (a frame that does not exist: the lanes that would read it are parked, whatever the address)
   auto frame_of = [&](const void* base, int t, unsigned bytes) {
-    const bool ok = t >= 0 && t < T;
-    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)(ok ? t : 0) * bytes), 0, ok ? bytes : 0u, kBufFlags);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (long long)t * bytes), 0, bytes, kBufFlags);
   };
-  auto ld_f = [&](__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {     // 2: non-temporal
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 2));
+  const int zq = (lane >> 3) & 3, zu = J * 32 + 4 * (lane & 7);
+  const int L_row = b < B && zu < n ? clamp_len(a.lens, b, T) : 0;
+  const unsigned gq_off = ((unsigned)b * 4u * n + (unsigned)zq * n + zu) * 4u;
+  auto lds_addr = [](const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p); };
+  const unsigned lds_g = lds_addr(&in_g[0][wave][0][0][0]), lds_c = lds_addr(&in_c[0][wave][0]), lds_y = lds_addr(&in_y[0][wave][0]);
+  // Frames of backward steps sigma, sigma + 1, ... (sigma = T-1-tau) into places sigma % (2 kAhead), ...; t < 0 and t >= L as one
+  // comparison.  The cell state entering frame t is the state leaving the frame before it in processing order, which is the NEXT
+  // backward step's frame: that step takes its c_new from here instead of loading it again.  So the value is also fetched where
+  // frame t itself is padding but the frame before it is real (direction +1, t = the row's length).  The state entering the first
+  // frame is the caller's and kept in a register.
+  const int t_first = d.rev ? 0 : T - 1, dt = d.rev ? 1 : -1;          // frame of backward step sigma: t_first + dt * sigma
+  const unsigned L_prev = (unsigned)(d.rev ? min(L, T - 1) : L);
+  // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight)
+  auto fetch_in = [&](int sigma) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < kAhead; ++f) {
+      const unsigned place = (unsigned)(sigma + f) & (2 * kAhead - 1);
+      const int t = t_first + dt * (sigma + f), tp = t + dt;
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds_g + place * (unsigned)sizeof(in_g[0])), "v"((unsigned)t < (unsigned)L_row ? gq_off : kParked), "s"(frame_of(d.gates, t, g_bytes)) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(lds_c + place * (unsigned)sizeof(in_c[0])), "v"((unsigned)(d.rev ? t : tp) < L_prev ? s_off : kParked), "s"(frame_of(d.cs, tp, s_bytes)) : "memory");
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ushort %1, %2, 0 offen nt lds" ::"s"(lds_y + place * (unsigned)sizeof(in_y[0])), "v"((unsigned)t < (unsigned)L ? y_off : kParked), "s"(frame_of(d.dy, t, y_bytes)) : "memory");
+    }
   };
-  auto fetch_in = [&](int tau) {
-    const int t = tau < 0 ? -1 : (d.rev ? T - 1 - tau : tau);
-    const bool lane_on = t < L;                            // (L is 0 in lanes without a row)
-    const unsigned go = lane_on ? g_off : kParked, so = lane_on ? s_off : kParked, yo = lane_on ? y_off : kParked;
-    In in;
-    const __amdgpu_buffer_rsrc_t rg = frame_of(d.gates, t, g_bytes);
-    in.gi = ld_f(rg, go, 0u); in.gf = ld_f(rg, go, 4u * n); in.gg = ld_f(rg, go, 8u * n); in.go = ld_f(rg, go, 12u * n);
-    const int tp = d.rev ? t + 1 : t - 1;                  // the frame before t in processing order
-    const bool inside = t >= 0 && tp >= 0 && tp < T, initial = t >= 0 && !inside && d.c0 != nullptr;
-    const __amdgpu_buffer_rsrc_t rp = initial ? __builtin_amdgcn_make_buffer_rsrc((void*)d.c0, 0, s_bytes, kBufFlags)
-                                              : frame_of(d.cs, inside ? tp : -1, s_bytes);
-    // The cell state entering frame t is the state leaving the frame before it, which is the NEXT backward step's
-    // frame: that step takes its c_new from here instead of loading it again (one load per step less).  So the value is
-    // also fetched where frame t itself is padding but the frame before it is real (direction +1, t = the row's length).
-    in.c_prev = ld_f(rp, (d.rev ? t : t - 1) < L ? s_off : kParked, 0u);
-    in.c_new = 0.f;                                        // supplied by the caller
-    in.dy_bits = __builtin_amdgcn_raw_buffer_load_b16(frame_of(d.dy, t, y_bytes), yo, 0, 2);
-    return in;
-  };
+  fetch_in(0);
+  const float c_first = active && d.c0 ? d.c0[(long)b * n + j] : 0.f;
+  // cell state leaving the next step's frame: of the first one loaded as such
+  float c_new = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(frame_of(d.cs, t_first, s_bytes), t_first < L ? s_off : kParked, 0u, 2));
   // entries of DZ, which this thread stores: a pointer that moves by one frame per step
   const long row_last = (long)(d.rev ? 0 : T - 1) * B + b, g_step = (d.rev ? (long)B : -(long)B) * 4 * n;
   unsigned short* dz_p = (unsigned short*)d.DZ + row_last * 4 * n + j;
-  In in_a = fetch_in(T - 1), in_b = in_a;
-  {                                                        // the first frame's own cell state: the only one loaded as such
-    const int t0 = d.rev ? 0 : T - 1;
-    in_a.c_new = ld_f(frame_of(d.cs, t0, s_bytes), t0 < L ? s_off : kParked, 0u);
-  }
 
   // consumer side: a load covers two producers' blocks; lane reads output lane%32, all eight rows, of producer lane/32
   const int ccol = lane & 31, chalf = lane >> 5;
   const int nitv = (ntile2 + 7) / 8, rot = J % nitv;
   // (row group's part of the ring in bytes, below 2^31; wave-uniform by decree, see wg_coord)
   const unsigned ring_group = __builtin_amdgcn_readfirstlane((unsigned)R * ntile2 * ntile2 * kPartBytes), ring_tile = __builtin_amdgcn_readfirstlane(ring_group + (unsigned)(J * ntile2 * kPartBytes));
-  // producer side: lanes 0..31 hold rows 4*(lane/16) .. +3 of output column lane%16 of each accumulator tile
-  const int pg = (lane >> 4) & 1, pcol = lane & 15;
+  // producer side: of a destination tile's two column tiles, lanes 0..31 publish the first and lanes 32..63 the second; a lane
+  // rows 4*(lane/16 % 2) .. +3 of output column lane%16 + 16*(lane/32)
+  const int pg = (lane >> 4) & 1, pcol = (lane >> 5) * 16 + (lane & 15);
   const int local = group_is_xcd_local(a.xcc, wg.base, ntile2, a.spin_limit);
-  // byte offset, from row group R's part of the ring, of what this lane stores for accumulator tile c: destination tile
-  // wave*8 + c/2 (one past the last falls outside the buffer), this producer's block, output column, row half.  Lanes
-  // 32..63 hold copies of the same rows; their offset is parked outside the buffer and the store is dropped.
-  unsigned pub_off[NCT];
+  // byte offset, from row group R's part of the ring, of what this lane stores for destination tile wave*(NCT/2) + P (one past the
+  // last falls outside the buffer): this producer's block, output column, row half
+  unsigned pub_off[NCT / 2];
 #pragma unroll
-  for (int c = 0; c < NCT; ++c) {
-    const int Jd = wave * (NCT / 2) + (c >> 1);
-    pub_off[c] = lane < 32 ? (unsigned)(((Jd * ntile2 + J) * 32 + (c & 1) * 16 + pcol) * 2 + pg) * 8u : 0xfff00000u;
-  }
+  for (int P = 0; P < NCT / 2; ++P) pub_off[P] = (unsigned)((((wave * (NCT / 2) + P) * ntile2 + J) * 32 + pcol) * 2 + pg) * 8u;
 
   PROF_DECL
-  // One time step.  `in` holds the inputs of this step's frame and `in_next` receives those of the next; the loop
-  // below calls it with the two in alternating roles, because a copy at the end of a step would have to wait for
-  // the loads (and, counted with them, the step's stores) at that point.
+  // One time step.
   // `ring_c`: the step reads partial sums (every step but the first); `pointwise_c`: it has a frame (every step but the
   // last, which only collects the Dh that leaves the layer).  Constants of the call, so that the loop below is free
   // of the two exceptions: with them inside, the compiler's wait counts in the loop allowed for paths it never takes.
-  auto step = [&](const int tau, const In& in, In& in_next, auto ring_c, auto pointwise_c) __attribute__((always_inline)) {
+  // `local_c`: the cache policy of the publishing stores.
+  auto step = [&](const int tau, auto local_c, auto ring_c, auto pointwise_c) __attribute__((always_inline)) {
     PROF_MARK(4)
     // (told to be wave-uniform: computed next to per-lane uses of tau it ends up in vector registers, and a buffer
     // descriptor derived from it is then applied lane by lane in a loop)
@@ -1086,6 +1120,21 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
     // The gate gradients of a valid frame, dh = dy + Dh (recurrent_dev.h has the plain form):
     //   dc = Dc + dh go (1 - tanh(c)^2), Dc' = dc gf, dz = (dc gg gi (1-gi), dc c_prev gf (1-gf), dc gi (1-gg^2), dh tanh(c) go (1-go)).
     // Everything that does not involve dh or Dc is computed while the ring loads are in flight.
+    struct { float gi, gf, gg, go, c_new, c_prev; unsigned dy_bits; } in;
+    auto take_in = [&]() __attribute__((always_inline)) {
+      const int place = sigma & (2 * kAhead - 1);
+      asm volatile("" ::: "memory");
+      in.gi = in_g[place][wave][lane >> 5][0][u]; in.gf = in_g[place][wave][lane >> 5][1][u];
+      in.gg = in_g[place][wave][lane >> 5][2][u]; in.go = in_g[place][wave][lane >> 5][3][u];
+      in.c_new = c_new; in.c_prev = in_c[place][wave][lane]; in.dy_bits = in_y[place][wave][lane];
+      if (tau == 0) in.c_prev = c_first;
+      c_new = in.c_prev;
+    };
+    // Frames are asked for a step earlier than they could be: what a step computes from its inputs alone then runs while its poll is
+    // in flight.
+    auto fetch_next = [&]() __attribute__((always_inline)) {
+      if ((sigma & (kAhead - 1)) == 0) fetch_in(sigma + kAhead);
+    };
     float f_c = 0.f, f_i = 0.f, f_f = 0.f, f_g = 0.f, f_o = 0.f;
     auto factors = [&]() __attribute__((always_inline)) {
       if (valid) {
@@ -1096,6 +1145,15 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
         f_g = in.gi * (1.f - in.gg * in.gg);
         f_o = tc * in.go * (1.f - in.go);
       }
+    };
+    // Accumulators, cleared while the ring loads are in flight (behind an assembly statement, or the compiler clears them where
+    // they are used, in the way of what publishes).
+    f32x4 acc[NCT / 2];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int P = 0; P < NCT / 2; ++P) acc[P] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int P = 0; P < NCT / 2; ++P) asm volatile("" : "+v"(acc[P]));
     };
     if constexpr (decltype(ring_c)::value) {
       RingReader rd;
@@ -1127,32 +1185,32 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
         const unsigned tagw = rd.tag << 16;
         // The poll is the first two loads, repeated (bounded) until their tags have turned and then kept; the others
         // are issued behind it (see the forward kernel).
-        for (unsigned poll = 0;; ++poll) {
+        auto poll_loads = [&]() __attribute__((always_inline)) {
           x[0] = rd.load_it(rd.it_of(0));
           x[1] = rd.load_it(rd.it_of(1));
-          if (dead) break;
+        };
+        auto polled_stale = [&]() __attribute__((always_inline)) {
           const unsigned stale = rd.tag_diff(x[0], rd.it_of(0), tagw) | rd.tag_diff(x[1], rd.it_of(1), tagw);
-          if (__builtin_amdgcn_ballot_w64(stale > 0xffffu) == 0ull) break;
-          if (poll >= rd.limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
-            st_relaxed(err, 1u);
-            dead = true;
-            break;
-          }
-          PROF_POLLS(1)
+          return __builtin_amdgcn_ballot_w64(stale > 0xffffu) != 0ull;
+        };
+        poll_loads();
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (pointwise) {                         // while the poll is in flight: all that does not need Dh
+          take_in();
+          clear();
+          factors();
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (__builtin_expect(polled_stale() && !dead, 0)) rd.poll_again(dead, poll_loads, polled_stale);
         PROF_MARK(5)
-        // Nothing is outstanding here (the poll has just been waited for, and loads complete in order).  Said with an
-        // instruction the compiler takes note of: otherwise it makes the pointwise part below wait for this frame's
-        // inputs, asked for a step ago, with a count that also waits for the next frame's, just asked for.
+        // (nothing is in flight behind the poll, the next step's inputs included)
         __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0)
 #pragma unroll
         for (int i = 2; i < NLD; ++i) x[i] = rd.load_it(rd.it_of(i));
         __builtin_amdgcn_sched_barrier(0);
-        // while those loads are on their way: the polled loads' values, and the part of the gate gradients that
-        // does not need Dh
+        // while those loads are on their way: the polled loads' values
         add(ps, x[0]);
         add(ps, x[1]);
-        factors();
         __builtin_amdgcn_sched_barrier(0);
         unsigned long long redo = 0ull;
         if (NLD > 2) {
@@ -1179,10 +1237,9 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
           // from the loop's exits, and would make whatever reuses those registers below wait for every load in flight)
           __builtin_amdgcn_s_waitcnt(0x0f70);              // vmcnt(0)
         }
-        // The next frame's inputs, from HBM.  Loads complete in the order of issue: asked for in front of the groups
+        // The next frames' inputs, from HBM.  Loads complete in the order of issue: asked for in front of the groups
         // above (where their latency would be covered best) they held up every ring load behind them - a tenth of the step.
-        in_next = fetch_in(tau - 1);
-        in_next.c_new = in.c_prev;
+        if constexpr (pointwise) fetch_next();
       }
       PROF_MARK(0)
 #pragma unroll
@@ -1195,9 +1252,11 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
         Dh = sum * (1.f / kPartScale);                     // the partial sums travel scaled (see above)
       }
     } else {
+      __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
+      take_in();
+      clear();
       factors();
-      in_next = fetch_in(tau - 1);
-      in_next.c_new = in.c_prev;
+      fetch_next();
     }
     if (pointwise) {
       float dz[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1215,61 +1274,41 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
       }
       __syncthreads();
       PROF_MARK(2)
-      // partial sums of Dh for all n outputs: [16 rows (8 real, repeated), K = 128] x [128, 256 outputs of this wave],
-      // in four groups of four column tiles: while the MFMAs of one group run, the previous group's results are
-      // converted and stored.  One 16-byte store per accumulator tile: the 32 storing lanes of a wavefront cover 512
-      // consecutive bytes.  Each 8-byte half carries its own tag in its upper dword, so the only thing relied on
-      // beyond the 64-bit units of the other kernels is that an aligned 16-byte lane store is not split below 8 bytes.
+      // Partial sums of Dh for all n outputs: [8 rows, K = 128] x [128, 256 outputs of this wave], four products for a destination
+      // tile's two column tiles (see smfmac_b_agpr), published by ONE store of 8 bytes a lane.
       const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
           (void*)((const char*)((sigma & 1) ? d.ring1 : d.ring0) + ring_group), 0, __builtin_amdgcn_readfirstlane(ntile2 * ntile2 * kPartBytes), kBufFlags);
       const unsigned tag_hi = part_tag(sigma + 1) << 30;
       u32x4 av[4];
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) av[kc] = *(const u32x4*)&zb[lane & 7][kc * 32 + (lane >> 4) * 8];
-      f32x4 acc[NCT];
-      // NCT column tiles, the k loop inside.  An MFMA of this shape issues every 16 cycles, of which the wavefront's
-      // issue slot is taken for 4 (see the forward kernel for the measurements).  What publishes a tile (two conversions,
-      // three moves and one store) is cut into single instructions that follow the MFMAs of the tile two behind it:
-      // by then its last result has been written (more than the 20 wait states mfma_settle would spend), the
-      // instructions cost little there, and only the last two tiles are published behind the last MFMA (with groups of
-      // four tiles, as this was first written, a whole group's publishing - a quarter of it - trailed the stream).
-      // Nothing is predicated: lanes that hold no result have their store offset parked outside the buffer (pub_off),
-      // and the two cache policies are two copies of the code.
-      constexpr int kPubSteps = 4, kPubLag = 2;             // a tile is published behind the MFMAs of the tile kPubLag after it
-      auto mma_publish = [&](auto local_c) __attribute__((always_inline)) {
-        constexpr bool kLocal = decltype(local_c)::value;
-        u32x2 val[4];
-        auto pub_step = [&](int c, int kk) __attribute__((always_inline)) {
-          u32x2& v = val[c & 3];
-          if (kk == 0) v[0] = pack_bf16x2(acc[c][0], acc[c][1]);
-          else if (kk == 1) v[1] = pack_bf16x2(acc[c][2], acc[c][3]);
-          else if (kk == 2) v[1] |= tag_hi;                  // (bit 14 of the fourth value is 0 below 2^33: see the format)
-          else __builtin_amdgcn_raw_buffer_store_b64(v, ro, pub_off[c], 0, kLocal ? 0 : 16);   // 16: sc1, agent scope, written through
-        };
-        operands_settle(av[0], av[1], av[2], av[3]);
-#pragma unroll
-        for (int c = 0; c < NCT; ++c)
-#pragma unroll
-          for (int kc = 0; kc < 4; ++kc) {
-            if (kc == 0) mfma_b_agpr_first(acc[c], av[kc], w[kc][c]);
-            else mfma_b_agpr(acc[c], av[kc], w[kc][c]);
-            if (c >= kPubLag) {                              // one step of the earlier tile behind each MFMA
-              __builtin_amdgcn_sched_barrier(0);
-              pub_step(c - kPubLag, kc);
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-        mfma_settle(acc[NCT - 4], acc[NCT - 3], acc[NCT - 2], acc[NCT - 1]);
-#pragma unroll
-        for (int c = NCT - kPubLag; c < NCT; ++c)
-#pragma unroll
-          for (int k = 0; k < kPubSteps; ++k) pub_step(c, k);
+      // A product issues every 16 cycles, of which the wavefront's issue slot is taken for 4 (see the forward kernel for the
+      // measurements).  What publishes a tile is cut into single instructions that follow the products of the next tiles,
+      // from two products behind its last one on (by then its results have been written: more than the wait states between the two).
+      // Nothing is predicated.
+      constexpr bool kLocal = decltype(local_c)::value;
+      constexpr int kPubSteps = 4, kPubLag = 2, kMma = 2 * NCT, kOps = NCT / 2 * kPubSteps;
+      u32x2 val[2];
+      auto pub_step = [&](int o) __attribute__((always_inline)) {
+        if (o < 0 || o >= kOps) return;
+        const int P = o / kPubSteps, kk = o % kPubSteps;
+        u32x2& v = val[P & 1];
+        if (kk == 0) v[0] = pack_bf16x2(acc[P][0], acc[P][1]);
+        else if (kk == 1) v[1] = pack_bf16x2(acc[P][2], acc[P][3]);
+        else if (kk == 2) v[1] |= tag_hi;                  // (bit 14 of the fourth value is 0 below 2^33: see the format)
+        else __builtin_amdgcn_raw_buffer_store_b64(v, ro, pub_off[P], 0, kLocal ? 0 : 16);   // 16: sc1, agent scope, written through
       };
-      // (opaque in every step: the compiler would make two copies of the whole time loop otherwise)
-      int local_ = local;
-      asm volatile("" : "+s"(local_));
-      if (local_) mma_publish(std::true_type{});
-      else mma_publish(std::false_type{});
+      operands_settle(av[0], av[1], av[2], av[3]);
+#pragma unroll
+      for (int i = 0; i < kMma; ++i) {
+        smfmac_b_agpr(acc[i >> 2], av[i & 3], w[i & 3][i >> 2], sparse);
+        __builtin_amdgcn_sched_barrier(0);
+        pub_step(i - 3 - kPubLag);                         // (product 4P + 3 is destination tile P's last)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mfma_settle(acc[NCT / 2 - 2], acc[NCT / 2 - 1]);
+#pragma unroll
+      for (int o = kMma - 3 - kPubLag; o < kOps; ++o) pub_step(o);
       PROF_MARK(1)
       if (active) {
 #pragma unroll
@@ -1279,21 +1318,19 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
       PROF_MARK(3)
     }
   };
+  // The time loop, once for each cache policy: with a branch around the products of every step both sides' accumulators are
+  // alive together, and the compiler copies one set in front of its products.
   // (tau is told to be wave-uniform: computed next to per-lane uses it ends up in vector registers)
-  constexpr std::true_type yes{};
-  constexpr std::false_type no{};
-  step(T - 1, in_a, in_b, no, yes);                        // (T >= 2)
-  int tau = T - 2;
-  for (; tau >= 1; tau = __builtin_amdgcn_readfirstlane(tau) - 2) {
-    step(tau, in_b, in_a, yes, yes);
-    step(__builtin_amdgcn_readfirstlane(tau - 1), in_a, in_b, yes, yes);
-  }
-  if (tau == 0) {
-    step(0, in_b, in_a, yes, yes);
-    step(-1, in_a, in_b, yes, no);
-  } else {
-    step(-1, in_b, in_a, yes, no);
-  }
+  auto all_steps = [&](auto local_c) __attribute__((always_inline)) {
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    step(T - 1, local_c, no, yes);                         // (T >= 2)
+    int tau = T - 2;
+    for (; tau >= 0; tau = __builtin_amdgcn_readfirstlane(tau) - 1) step(tau, local_c, yes, yes);
+    step(-1, local_c, yes, no);
+  };
+  if (local) all_steps(std::true_type{});
+  else all_steps(std::false_type{});
   PROF_DUMP("bwdp", T)
   if (active) {
     if (d.dh0) d.dh0[(long)b * n + j] = Dh;
@@ -1316,7 +1353,7 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
 
 // The same kernel for work-groups of 16 rows (two per thread: rows r8 and r8 + 8 of the group), for batches that the
 // 8-row form cannot hold in one launch.  The MFMAs and the publishing stores are the same instructions with all 64 lanes
-// doing real work (the 8-row form computes every row twice); a (producer, destination tile) block is 1 KiB -
+// doing real work; a (producer, destination tile) block is 1 KiB -
 // [32 outputs][4 row quarters] x 8 bytes -, a consumer's load covers one producer (lane = output lane/2, row half lane%2),
 // so a wavefront reads eight loads per step instead of four, and the pointwise part runs twice.
 template <int NPW, int NCT>                               // n <= 128 * NPW (producers per wavefront) and n <= 64 * NCT (its output column tiles)
@@ -2264,29 +2301,34 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // packing for the ring layout
-// forward weights: chunk index = (((dir*ntile + tile)*4 + q)*nkc + kc)*64 + lane
-__device__ __forceinline__ void pack_wh_fwd_ll_body(long idx, const bf16_t* W, uint4* out, int n, int nkc, long total) {
+// forward weights: chunk index = (((dir*ntile + tile)*4 + q)*nkc + kc)*64 + lane, or (`paired`: the 8-row kernel)
+// ((((dir*ntile2 + tile2)*4 + q)*nkc + kc)*2 + set)*64 + lane, two column tiles in one operand (smfmac_b_agpr)
+__device__ __forceinline__ void pack_wh_fwd_ll_body(long idx, const bf16_t* W, uint4* out, int n, int nkc, int paired, long total) {
   if (idx >= total) return;
-  const int lane = idx & 63;
+  const int lane = idx & 63, g = lane >> 4;
   long rest = idx >> 6;
+  int set = 0;
+  if (paired) { set = rest & 1; rest >>= 1; }
   const int kc = rest % nkc; rest /= nkc;
   const int q = rest & 3; rest >>= 2;
-  const int ntile = (n + 15) / 16;
+  const int ntile = paired ? (n + 31) / 32 : (n + 15) / 16;
   const int tile = rest % ntile, dir = rest / ntile;
-  const int j = tile * 16 + (lane & 15), g = lane >> 4;
   const bf16_t* Wd = W + (long)dir * n * 4 * n;
   bf16_t v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const int k = (kc * 4 + g) * 8 + e;                    // forward ring: slot = unit index (kLLSlotsFwd = kLLValsFwd)
+    // forward ring: slot = unit index (kLLSlotsFwd = kLLValsFwd)
+    const int k = kc * 32 + (paired ? sparse_k(set, g, e) : g * 8 + e);
+    const int j = (paired ? tile * 32 + 16 * sparse_tile(e) : tile * 16) + (lane & 15);
     v[e] = (k < n && j < n) ? Wd[(long)k * 4 * n + q * n + j] : (bf16_t)0.f;
   }
   out[idx] = *(uint4*)v;
 }
-// partial-sum backward kernel: chunk index = ((((dir*ntile2 + J)*4 + wave)*4 + kc)*nct + c)*64 + lane ; B fragment of
-// gate kc, K = the 32 units of tile J, columns = outputs (wave*nct + c)*16 .. +15: eight consecutive units of a row of W_h.
+// partial-sum backward kernels: chunk index = ((((dir*ntile2 + J)*4 + wave)*4 + kc)*nct + c)*64 + lane ; B fragment of
+// gate kc, K = the 32 units of tile J, columns = outputs (wave*nct + c)*16 .. +15: eight consecutive units of a row of W_h, or
+// (`paired`: the 8-row kernel, c = 2P + set) four consecutive ones of two rows 16 apart, two by two (smfmac_b_agpr).
 // (16-byte reads: the set-up of config 3's backward loops, with its fills, 27 -> 17 us.)  Scaled by 2^-32, exactly: the partial sums of Dh leave the MFMAs scaled, which keeps a bit of their bf16 form free.
-__device__ __forceinline__ void pack_wh_bwdp_body(long idx, const bf16_t* W, uint4* out, int n, int ntile2, int nct, long total) {
+__device__ __forceinline__ void pack_wh_bwdp_body(long idx, const bf16_t* W, uint4* out, int n, int ntile2, int nct, int paired, long total) {
   if (idx >= total) return;
   const int lane = idx & 63, g = lane & 3, col = lane >> 2;  // (four neighbouring threads read 64 consecutive bytes)
   long rest = idx >> 6;
@@ -2294,18 +2336,39 @@ __device__ __forceinline__ void pack_wh_bwdp_body(long idx, const bf16_t* W, uin
   const int kc = rest & 3, wave = (rest >> 2) & 3;
   rest >>= 4;
   const int J = rest % ntile2, dir = rest / ntile2;
-  const int jout = (wave * nct + c) * 16 + col, u0 = J * 32 + g * 8;
-  const uint16_t* p = (const uint16_t*)W + ((long)dir * n + min(jout, n - 1)) * 4 * n + kc * n;
+  const uint16_t* Wd = (const uint16_t*)W + (long)dir * n * 4 * n + kc * n;
+  auto scaled = [](unsigned bits) { return (unsigned)f2bf_bits(bf_bits2f((uint16_t)bits) * kPartScale); };
   unsigned v[8];
-  if (n % 8 == 0) {
-    const uint4 x = *(const uint4*)(p + min(u0, n - 8));
-    v[0] = x.x & 0xffffu; v[1] = x.x >> 16; v[2] = x.y & 0xffffu; v[3] = x.y >> 16; v[4] = x.z & 0xffffu; v[5] = x.z >> 16; v[6] = x.w & 0xffffu; v[7] = x.w >> 16;
+  if (paired) {
+    const int u0 = J * 32 + sparse_k(c & 1, g, 0);           // elements 0, 1, 4, 5: u0 .. u0 + 3 of the first row; 2, 3, 6, 7: of the second
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int jout = (wave * nct + (c & ~1) + h) * 16 + col;
+      const uint16_t* p = Wd + (long)min(jout, n - 1) * 4 * n;
+      unsigned x[4];
+      if (n % 4 == 0) {
+        const uint2 y = *(const uint2*)(p + min(u0, n - 4));
+        x[0] = y.x & 0xffffu; x[1] = y.x >> 16; x[2] = y.y & 0xffffu; x[3] = y.y >> 16;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = p[min(u0 + e, n - 1)];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[(e & 1) + 2 * h + 4 * (e >> 1)] = jout < n && u0 + e < n ? scaled(x[e]) : 0u;
+    }
   } else {
+    const int u0 = J * 32 + g * 8, jout = (wave * nct + c) * 16 + col;
+    const uint16_t* p = Wd + (long)min(jout, n - 1) * 4 * n;
+    if (n % 8 == 0) {
+      const uint4 x = *(const uint4*)(p + min(u0, n - 8));
+      v[0] = x.x & 0xffffu; v[1] = x.x >> 16; v[2] = x.y & 0xffffu; v[3] = x.y >> 16; v[4] = x.z & 0xffffu; v[5] = x.z >> 16; v[6] = x.w & 0xffffu; v[7] = x.w >> 16;
+    } else {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = p[min(u0 + e, n - 1)];
+      for (int e = 0; e < 8; ++e) v[e] = p[min(u0 + e, n - 1)];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = jout < n && u0 + e < n ? scaled(v[e]) : 0u;
   }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = jout < n && u0 + e < n ? f2bf_bits(bf_bits2f((uint16_t)v[e]) * kPartScale) : 0u;
   out[(idx & ~63l) + g * 16 + col] = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
 }
 // Initial contents of the forward ring, one 8-byte unit per thread: slot 0 = zeros that carry the tag of step 0, slot 1 = zeros.
@@ -2324,7 +2387,7 @@ struct PrepArgs {
   const bf16_t* W; uint4* Wout; int n, nk, nct; long w_total;   // nk: nkc (forward) / ntile2 (backward)
   uint4* ring0; uint4* ring1; long ring_total;
   const int* lens; int T, B; int* fidx; int* count;     // frame map (fidx == NULL: none)
-  int first_pack, first_ring, first_map, backward;
+  int first_pack, first_ring, first_map, backward, paired;
 };
 __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
   const int bid = blockIdx.x;
@@ -2339,8 +2402,8 @@ __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
     for (size_t i = (size_t)(bid - a.z.first_block[k]) * 256 + threadIdx.x; i < nwords; i += nb * 256) p[i] = 0u;
   } else if (bid < a.first_ring) {
     const long idx = (long)(bid - a.first_pack) * 256 + threadIdx.x;
-    if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, a.w_total);
-    else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, a.w_total);
+    if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, a.paired, a.w_total);
+    else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, a.paired, a.w_total);
   } else if (bid < a.first_map) {
     pack_state_ll_body((long)(bid - a.first_ring) * 256 + threadIdx.x, a.ring0, a.ring1, a.ring_total);
   } else {
@@ -2447,24 +2510,26 @@ bool slab_fits(K kernel, int ntile, int rows_per_group, int nrow, int ndir) {
 // for n <= 512 (256).
 typedef void (*FwdKernel)(PFwdArgs);
 typedef void (*BwdKernel)(PBwdArgs);
-FwdKernel fwd8_for(int n) { return n <= 512 ? persist_fwd8_kernel<4> : persist_fwd8_kernel<8>; }
+FwdKernel fwd8_for(int n) { return n <= 512 ? persist_fwd8_kernel<2> : persist_fwd8_kernel<4>; }
 FwdKernel fwd16_for(int n) { return n <= 512 ? persist_fwd16r_kernel<4> : persist_fwd16r_kernel<8>; }
 BwdKernel bwd8_for(int n) { return n <= 256 ? persist_bwdp_kernel<4, 4> : n <= 512 ? persist_bwdp_kernel<4, 8> : persist_bwdp_kernel<8, 16>; }
 BwdKernel bwd16_for(int n) { return n <= 256 ? persist_bwdp16_kernel<4, 4> : n <= 512 ? persist_bwdp16_kernel<4, 8> : persist_bwdp16_kernel<8, 16>; }
 
 }  // namespace
 
+// More rows than the 8-row form holds in one launch go to the 16-row form, if that takes a single launch.
+int persist_fwd_rows(int B, int n, int ndir) {
+  const long t32 = cdiv(n, 32);
+  return t32 * cdiv(B, 8) * ndir > capacity(fwd8_for(n)) && t32 * cdiv(B, 16) * ndir <= capacity(fwd16_for(n)) ? 16 : 8;
+}
+int persist_bwd_rows(int B, int n, int ndir) {
+  const long t32 = cdiv(n, 32);
+  return t32 * cdiv(B, 8) * ndir > capacity(bwd8_for(n)) && t32 * cdiv(B, 16) * ndir <= capacity(bwd16_for(n)) ? 16 : 8;
+}
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s) {
   if (!persist_fwd_fits(a)) return hipErrorCooperativeLaunchTooLarge;
-  const int t32 = cdiv(a.n, 32);
-  // more rows than the 32 x 8 form holds in one launch: 32 units x 16 rows, if that takes a single launch
-  if ((long)t32 * cdiv(a.B, 8) * a.ndir > capacity(fwd8_for(a.n)) && (long)t32 * cdiv(a.B, 16) * a.ndir <= capacity(fwd16_for(a.n))) {
-    const hipError_t e16 = coop_slabs(fwd16_for(a.n), t32, 16, a, s);
-    if (e16 != hipErrorCooperativeLaunchTooLarge) return e16;
-    (void)hipGetLastError();
-  }
-  // 32 units x 8 rows per work-group
-  return coop_slabs(fwd8_for(a.n), t32, 8, a, s);
+  const int rows = persist_fwd_rows(a.B, a.n, a.ndir);
+  return coop_slabs(rows == 16 ? fwd16_for(a.n) : fwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
 // Would launch_persist_fwd launch anything?  (Asked before the initial state's term is added to the pre-activations,
 // which only the single-launch kernels expect there.)
@@ -2478,20 +2543,14 @@ bool persist_bwd_fits(const PBwdArgs& a) {
   return a.n <= 1024 && slab_fits(bwd8_for(a.n), cdiv(a.n, 32), 8, cdiv(a.B, 8), a.ndir);
 }
 hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s) {
-  const int t32 = cdiv(a.n, 32);
-  // more rows than the 8-row form holds in one launch: 16 rows per work-group, if that takes a single launch
-  if ((long)t32 * cdiv(a.B, 8) * a.ndir > capacity(bwd8_for(a.n)) && (long)t32 * cdiv(a.B, 16) * a.ndir <= capacity(bwd16_for(a.n))) {
-    const hipError_t e16 = coop_slabs(bwd16_for(a.n), t32, 16, a, s);
-    if (e16 != hipErrorCooperativeLaunchTooLarge) return e16;
-    (void)hipGetLastError();
-  }
-  return coop_slabs(bwd8_for(a.n), t32, 8, a, s);
+  const int rows = persist_bwd_rows(a.B, a.n, a.ndir);
+  return coop_slabs(rows == 16 ? bwd16_for(a.n) : bwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
-hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, uint4* ring0, uint4* ring1,
+hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
                               int nrt, const FrameMapArgs& fm, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
-  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.nk = nkc; a.w_total = (long)ndir * cdiv(n, 16) * 4 * nkc * 64;
+  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.paired = paired; a.nk = nkc; a.w_total = (long)(ndir * ll_wf_bytes(n, nkc, paired) / 16);
   a.ring0 = ring0; a.ring1 = ring1; a.ring_total = (long)ndir * nrt * nkc * 64 * 2;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
@@ -2501,14 +2560,14 @@ hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, in
   hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s) {
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
   a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.nct = bwdp_nct(n); a.w_total = (long)ndir * a.nk * 4 * 4 * a.nct * 64;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.first_map = a.first_ring;
-  a.backward = 1;
+  a.backward = 1; a.paired = paired;
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
   hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
   return hipGetLastError();

@@ -46,6 +46,13 @@ def test_wider_float_layer(T, B, n_in, n, bidir):
     _layer(T, B, n_in, n, bidir, "f32")
 
 
+@pytest.mark.parametrize("T,B,n,bidir", [(2, 3, 129, True), (3, 8, 130, False), (4, 25, 255, True), (5, 9, 258, False), (9, 2, 511, True), (6, 7, 1002, False), (13, 16, 1024, True)])
+def test_eight_row_loops(T, B, n, bidir):
+    """Frames fetched two and four together: any number of steps, also fewer; units that end inside a tile, and inside the four units of a
+    load; the last row's last units at the end of a frame."""
+    _layer(T, B, 32, n, bidir, "bf16")
+
+
 def _layer(T, B, n_in, n, bidir, dt):
     from paper_1805_05225_amd import binding
     P.Bn = binding
