@@ -160,17 +160,17 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
 // are avoided by the placement instead of padding: the 16-byte slot p of row r holds k-chunk p ^ ((r >> 1) & 7),
 // which the loading lane arranges by choosing WHICH global chunk it fetches.
 //
-// Wavefronts: 2 x (8 / TN), each 4 x TN MFMA blocks; the kernels below use TN = 2: eight wavefronts of 128x64,
-// two per SIMD, so one wavefront's LDS reads and waits hide behind the other's MFMAs (four wavefronts of 128x128
-// measured 15-20 % slower).  Measured on the device: what bounds this kernel is the path from L2 to LDS - with the
-// MFMAs taken out the loop needs the same number of cycles (about 3500 per stage against 2050 of MFMA work), because
-// a fifth of a stage's lines is a first touch per XCD and the work-groups sharing a panel wait for the same miss.
-//
-// Loop, per stage `it` (k advances 64 = four MFMA k-steps): fragments of k-step s+1 are read while the MFMAs of
-// step s run.  Before the last k-step the wavefront waits for its own loads of stage it+1 and meets the others at
-// the barrier; after it every load of stage it+1 has landed and every read of stage it's buffer has completed,
-// so the loads of stage it+2 are issued into that buffer and the first fragments of stage it+1 are read - both
-// under the MFMAs of the last k-step.  A load therefore has a whole stage of MFMAs to complete.
+// Eight wavefronts (2 x 4) of 128x64 = 4 x 2 MFMA blocks, two per SIMD, so one wavefront's LDS reads and waits hide behind the
+// other's MFMAs (four wavefronts of 128x128 measured 15-20 % slower).  A stage (k advances 64) is four phases, a quarter of the
+// wavefront's blocks each over all 64 k: blocks (rows 0-1, column 0), (0-1, 1), (2-3, 1), (2-3, 0).  A phase reads the fragments it lacks
+// - A's first half and B's first, B's second, A's second, none -, meets the others, multiplies, meets them again; wavefronts 4-7 are
+// half a phase behind, so that on every SIMD one wavefront multiplies while the other reads.  A half of an operand is free for the stage
+// after next as soon as all have read it, and its two wavefront-loads go out in the next phase: every load has six or seven phases
+// to arrive, 80 to 96 KiB are always on their way, and no wait ever drains them (vmcnt(10)).
+// Before, a stage's loads went out together and were waited for together, a stage later, at a barrier all wavefronts met at once: 8192^3
+// 1137 TFLOP/s, 24576 x 2048 x 8192 1121, 27136 x 8192 x 2048 (float C) 1074, 3200 x 8000 x 2000 771; now 1208, 1252, 1136, 857 (without
+// the half phase between the wavefronts 1083, 1082, 1021, 740).  On zeros 8192^3 runs at 1680: what is left is the clock, which the
+// data's switching brings down to about 1.7 GHz, and where N is small the loads (without MFMAs 24576 x 2048 x 8192 takes the same time).
 constexpr int kDlRow = 128;                  // bytes per LDS row
 constexpr int kDlOp = kT * kDlRow;           // one operand, one stage (32 KiB)
 constexpr int kDlStage = 2 * kDlOp;
@@ -192,13 +192,13 @@ __device__ __forceinline__ u32x4 make_rsrc(const void* base, unsigned bytes) {
   return r;
 }
 
-template <typename TC, int TN, bool RAGGED>
+template <typename TC, bool RAGGED>
 __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int WN = 8 / TN, NW = 2 * WN, NLD = 32 / NW;       // loads per wavefront, operand and stage
+  constexpr int TN = 2;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 2, wn = wave & 3;
   const int r = lane & 31, gq = lane >> 5;
 
   const TileCoord tc = tile_coord(g);
@@ -220,116 +220,107 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   const bool ragged = RAGGED && tail_chunks < 8;              // RAGGED = false: the launcher saw K % 64 == 0
   const int total = ktiles * g.nseg;                           // stages
 
-  // Loads.  Wavefront-load i of this wavefront fills rows 8 * (i * NW + wave) .. + 7 of an operand; lane l fills
-  // slot l & 7 of row (l >> 3) of those, i.e. fetches k-chunk (l & 7) ^ swizzle(row).  Rows past the operand's end
-  // point outside the buffer descriptor and arrive as zeros.
-  // The order in which a work-group asks for the row groups of a stage is rotated by its place in the XCD's block of
-  // tiles: the 4 (8) work-groups that share an A (B) panel each start with a different quarter (half) of it, so the
-  // first request for a line - the one that has to fetch it from beyond L2 - goes out early in every work-group's
-  // burst instead of all sharers asking for the same lines in the same order.
-  const int rotA = tc.pos % kSupN, rotB = (tc.pos / kSupN) >> 1;
-  unsigned voa[NLD], vob[NLD], lda_off[NLD], ldb_off[NLD];
-  bool a_past[NLD], b_past[NLD];                                // this lane's chunk lies past K in a ragged last k-tile
-  {
-    const long a_rows_mem = g.a_rows ? g.a_phys_rows : M;
+  // Loads.  A quarter of a stage (two wavefront-loads of every wavefront) is half an operand: rows of every wavefront's first or second
+  // two (A) or one (B) MFMA blocks.  Wavefront-load j of it fills 8 rows; lane l fills slot l & 7 of row l >> 3 of those, i.e. fetches
+  // k-chunk (l & 7) ^ swizzle(row).  Rows past the operand's end point outside the buffer descriptor and arrive as zeros.
+  const int chunk = (lane & 7) ^ ((((wave & 1) * 8 + (lane >> 3)) >> 1) & 7);
+  const bool past = chunk >= tail_chunks;                      // this lane's chunk lies past K in a ragged last k-tile
+  unsigned vo[2][2][2], lrow[2][2][2];                         // [operand][half][load]
+  const long a_rows_mem = g.a_rows ? g.a_phys_rows : M;
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int ia = (i + rotA) % NLD, ib = (i + rotB) % NLD;
-      lda_off[i] = ia * NW * 1024; ldb_off[i] = kDlOp + ib * NW * 1024;
-      const int rl = (ia * NW + wave) * 8 + (lane >> 3), rlb = (ib * NW + wave) * 8 + (lane >> 3);
-      const int chunk = (lane & 7) ^ ((rl >> 1) & 7), chunkb = (lane & 7) ^ ((rlb >> 1) & 7);
-      long ra = m0 + rl;
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int ta = j * 128 + h * 64 + wave * 8, tb = (j * 2 + (wave >> 2)) * 64 + h * 32 + (wave & 3) * 8;
+      lrow[0][h][j] = ta * kDlRow; lrow[1][h][j] = kDlOp + tb * kDlRow;
+      long ra = m0 + ta + (lane >> 3), rb = n0 + tb + (lane >> 3);
       if (g.a_rows) ra = ra < M ? (long)g.a_rows[ra] : 0x7fffffffL; else if (ra >= M) ra = 0x7fffffffL;
-      long rb = n0 + rlb;
       if (rb >= g.N) rb = 0x7fffffffL;
-      const long oa = (ra * g.lda) * 2 + chunk * 16, ob = (rb * g.ldb) * 2 + chunkb * 16;
-      voa[i] = (ra >= a_rows_mem || oa > 0x7ffffff0L) ? 0x7ffffff0u : (unsigned)oa;
-      vob[i] = (rb >= g.N || ob > 0x7ffffff0L) ? 0x7ffffff0u : (unsigned)ob;
-      a_past[i] = chunk >= tail_chunks; b_past[i] = chunkb >= tail_chunks;
+      const long oa = (ra * g.lda) * 2 + chunk * 16, ob = (rb * g.ldb) * 2 + chunk * 16;
+      vo[0][h][j] = (ra >= a_rows_mem || oa > 0x7ffffff0L) ? 0x7ffffff0u : (unsigned)oa;
+      vo[1][h][j] = (rb >= g.N || ob > 0x7ffffff0L) ? 0x7ffffff0u : (unsigned)ob;
     }
-  }
-  const long a_bytes = (long)(g.a_rows ? g.a_phys_rows : M) * g.lda * 2, b_bytes = (long)g.N * g.ldb * 2;
+  const long a_bytes = a_rows_mem * g.lda * 2, b_bytes = (long)g.N * g.ldb * 2;
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)lds;
-  const int a_rec = a_bytes > 0x7fffffffL ? 0x7fffffff : (int)a_bytes, b_rec = b_bytes > 0x7fffffffL ? 0x7fffffff : (int)b_bytes;
-  // Wavefront-loads of a stage are numbered 0 .. 2*NLD-1 (even: A, odd: B); `issue` enqueues numbers [first, last).
-  auto issue = [&](int it, int buf, int first, int last) __attribute__((always_inline)) {
-    const int seg = it / ktiles, kt = it - seg * ktiles;
-    const u32x4 ra = make_rsrc(g.A + (g.sAz * z + g.sAseg * seg) * 2, (unsigned)a_rec);
-    const u32x4 rb = make_rsrc(g.B + (g.sBz * z + g.sBseg * seg) * 2, (unsigned)b_rec);
-    const unsigned dst = lds_base + buf * kDlStage + wave * 1024;
-    const unsigned koff = kt * (kKB * 2);
-    const bool cut = ragged && kt == ktiles - 1;
-#pragma unroll
-    for (int q = 0; q < 2 * NLD; ++q) {
-      if (q < first || q >= last) continue;
-      const int i = q >> 1;
-      if (q & 1) load_to_lds_b128(rb, dst + ldb_off[i], (cut && b_past[i]) ? 0x7ffffff0u : vob[i], koff);
-      else load_to_lds_b128(ra, dst + lda_off[i], (cut && a_past[i]) ? 0x7ffffff0u : voa[i], koff);
-    }
+  const unsigned rec[2] = {a_bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)a_bytes, b_bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)b_bytes};
+  const char* const base[2] = {g.A + g.sAz * z * 2, g.B + g.sBz * z * 2};
+  const long seg_bytes[2] = {g.sAseg * 2, g.sBseg * 2};
+  struct Stage { int it, seg, kt; };                           // a stage whose loads go out
+  auto advance = [&](Stage& t) __attribute__((always_inline)) {
+    ++t.it;
+    if (++t.kt == ktiles) { t.kt = 0; ++t.seg; }
   };
-  constexpr int NQ = 2 * NLD;                               // wavefront-loads per stage and wavefront
+  // (past the last stage the same loads are issued with every lane outside the descriptor: the counted waits below count them)
+  auto issue = [&](const Stage& t, int op, int h) __attribute__((always_inline)) {
+    const u32x4 rs = make_rsrc(base[op] + seg_bytes[op] * t.seg, t.it < total ? rec[op] : 0u);
+    const unsigned dst = lds_base + (t.it & 1) * kDlStage, koff = t.kt * (kKB * 2);
+    const bool cut = ragged && t.kt == ktiles - 1;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) load_to_lds_b128(rs, dst + lrow[op][h][j], (cut && past) ? 0x7ffffff0u : vo[op][h][j], koff);
+  };
 
-  // Fragment reads: row (wm*128 + i*32 + r) of A / (wn*TN*32 + j*32 + r) of B, k-chunk 2*s + gq, which sits in
+  // Fragment reads: row (wm*128 + i*32 + r) of A / (wn*64 + j*32 + r) of B, k-chunk 2*s + gq, which sits in
   // slot (2*s + gq) ^ ((r >> 1) & 7): one XOR with s * 32 per k-step on a per-lane base offset.
   const int fa_off = (wm * 128 + r) * kDlRow + ((gq ^ ((r >> 1) & 7)) * 16);
-  const int fb_off = kDlOp + (wn * TN * 32 + r) * kDlRow + ((gq ^ ((r >> 1) & 7)) * 16);
-  uint4 fa[2][4], fb[2][TN];
-  auto read_frags = [&](int buf, int s, int c) __attribute__((always_inline)) {
-    const char* base = lds + buf * kDlStage;
+  const int fb_off = kDlOp + (wn * 64 + r) * kDlRow + ((gq ^ ((r >> 1) & 7)) * 16);
+  uint4 fa[2][4], fb[TN][4];                                   // [block][k-step]
+  auto read_a = [&](int it, int h) __attribute__((always_inline)) {
+    const char* p = lds + (it & 1) * kDlStage;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fa[c][i] = *(const uint4*)(base + (fa_off ^ (s * 32)) + i * 32 * kDlRow);
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[c][j] = *(const uint4*)(base + (fb_off ^ (s * 32)) + j * 32 * kDlRow);
+      for (int s = 0; s < 4; ++s) fa[i][s] = *(const uint4*)(p + (fa_off ^ (s * 32)) + (2 * h + i) * 32 * kDlRow);
   };
-
-  // One k-step: the MFMAs of fragment buffer c.  With `ld`, the NQ wavefront-loads of stage `ld_it` go out between
-  // them, one after every second MFMA, the rest behind the last.  (Spreading them over three k-steps measured
-  // slower: the last ones then have too little time left; so did L2 prefetches of the coming stages.)
-  auto kstep = [&](int c, bool ld, int ld_it, int ld_buf) __attribute__((always_inline)) {
-    int q = 0;
+  auto read_b = [&](int it, int j) __attribute__((always_inline)) {
+    const char* p = lds + (it & 1) * kDlStage;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int s = 0; s < 4; ++s) fb[j][s] = *(const uint4*)(p + (fb_off ^ (s * 32)) + j * 32 * kDlRow);
+  };
+  // The end of a phase's reading half: this wavefront's reads have returned (what they read may be overwritten once all have met), and
+  // the quarter that the next phase reads has landed (ten younger loads).
+  auto meet = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+  auto multiply = [&](int h, int j) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0x007a);                        // vmcnt(10) lgkmcnt(0)
+    meet();
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        acc[i][j] = mma(fa[c][i], fb[c][j], acc[i][j]);
-        if (((i * TN + j) & 1) && q < NQ) {
-          if (ld) issue(ld_it, ld_buf, q, q + 1);
-          ++q;
-        }
-      }
-    if (q < NQ && ld) issue(ld_it, ld_buf, q, NQ);
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[2 * h + i][j] = mma(fa[i][s], fb[j][s], acc[2 * h + i][j]);
+    __builtin_amdgcn_s_setprio(0);
+    meet();
   };
 
   if (total > 0) {
-    issue(0, 0, 0, NQ);
-    __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0)
-    __syncthreads();
-    if (total > 1) issue(1, 1, 0, NQ);
-    read_frags(0, 0, 0);
-  }
-  for (int it = 0; it < total; ++it) {
-    const int cur = it & 1;
-    read_frags(cur, 1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(0, false, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(cur, 2, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(1, false, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(cur, 3, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(0, false, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    // last k-step: stage it+1 must be in LDS and this stage's buffer free
-    if (it + 1 < total) {
-      __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0): own loads of stage it+1 landed, own reads of this stage done
-      __syncthreads();
-      read_frags(cur ^ 1, 0, 0);
+    Stage nx = {0, 0, 0};
+    issue(nx, 0, 0); issue(nx, 1, 0); issue(nx, 1, 1); issue(nx, 0, 1);
+    advance(nx);
+    issue(nx, 0, 0); issue(nx, 1, 0); issue(nx, 1, 1);
+    __builtin_amdgcn_s_waitcnt(0x0f7a);                        // vmcnt(10): the first stage's first halves
+    meet();
+    if (wm == 1) meet();                                       // the second four wavefronts stay half a phase behind
+    for (int it = 0; it < total; ++it) {
+      read_a(it, 0); read_b(it, 0);
+      issue(nx, 0, 1);                                         // stage it + 1
+      advance(nx);                                             // stage it + 2, into this stage's buffer
+      multiply(0, 0);
+      read_b(it, 1);
+      issue(nx, 0, 0);
+      multiply(0, 1);
+      read_a(it, 1);
+      issue(nx, 1, 0);
+      multiply(1, 1);
+      issue(nx, 1, 1);
+      multiply(1, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(1, it + 2 < total, it + 2, cur);
-    __builtin_amdgcn_sched_barrier(0);
+    if (wm == 0) meet();
+    __builtin_amdgcn_s_waitcnt(0x0f70);                        // vmcnt(0): the epilogue uses LDS
   }
   store_tile<TC, TN>(acc, lds, g, M, m0, n0, z);
 }
@@ -505,8 +496,8 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 __global__ __launch_bounds__(512, 1) void gemm_tn8_f32_kernel(NtArgs g) { gemm_tn_body<float>(g); }
 
 // (kernels with literal launch bounds: a bound that depends on a template parameter loses the host-side stub)
-template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_kernel(NtArgs g) { gemm_dl_body<float, 2, RAGGED>(g); }
-template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_bf16_kernel(NtArgs g) { gemm_dl_body<uint16_t, 2, RAGGED>(g); }
+template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_kernel(NtArgs g) { gemm_dl_body<float, RAGGED>(g); }
+template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_bf16_kernel(NtArgs g) { gemm_dl_body<uint16_t, RAGGED>(g); }
 
 // dst[c][r] = src[r][c] for r < R, c < C ; dst rows are padded with zeros up to ldd.
 __global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd, long s_src, long s_dst) {
