@@ -622,10 +622,9 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
 template <int NIT>
 __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   __shared__ float red[2][4][16][129];                   // two copies, used by even and odd steps: one barrier per step
-  // x W_x + b of the next frame, fetched one step ahead by loads that write LDS instead of registers (the register
-  // file has no room for two sets of 8 values per thread): [set][wavefront][row k, gate q][lane], each thread reading
-  // back exactly what it asked for, so no barrier is involved - only the loads' completion.
-  __shared__ float zxs[2][4][8][64];
+  // x W_x + b of the next frames, fetched two together (see the 32 x 8 kernel): [frame][row half][wavefront][row][gate][unit], a
+  // wavefront reading back what it asked for, so no barrier is involved - only the loads' completion.
+  __shared__ float zxs[2][2][4][2][4][32];
   __shared__ u32x4 rbuf[4][NIT][64];                     // the ring loads of a step: [wavefront][load][lane], written by the memory unit
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
@@ -701,27 +700,29 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   auto frame_of = [&](const void* base, int t, unsigned bytes, bool present = true) {
     return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)t * bytes), 0, present && base != nullptr ? bytes : 0u, kBufFlags);
   };
-  const unsigned zxs_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&zxs[0][0][0][0];
+  const unsigned zxs_wave = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&zxs[0][0][wave][0][0][0]);
   const unsigned rbuf_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&rbuf[0][0][0];
-  // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight;
-  // the kernel counts them itself - see the wait in front of the cell update)
-  auto fetch_zx = [&](int tau, int set) __attribute__((always_inline)) {
-    const bool ok = tau < T;
-    const int t = d.rev ? T - 1 - tau : tau;
-    const __amdgpu_buffer_rsrc_t rg =
-        __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)d.gates + (unsigned long long)(unsigned)(ok ? t : 0) * g_bytes), 0, ok ? g_bytes : 0u, kBufFlags);
+  const int zu = tile2 * 32 + 4 * (lane & 7);
+  int L_row[2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const unsigned go = t < L[k] ? g_off(k) : kParked;     // (L is 0 in lanes without a row)
+  for (int k = 0; k < 2; ++k) L_row[k] = (int)b0 + 8 * k < B && zu < n ? clamp_len(a.lens, b0 + 8 * k, T) : 0;
+  const unsigned zx_off = (b0 * 4u * n + ((unsigned)lane >> 3 & 3u) * n + zu) * 4u;
+  // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight)
+  auto fetch_zx = [&](int tau0) __attribute__((always_inline)) {      // frames of steps tau0 and tau0 + 1
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const unsigned dst = zxs_base + (unsigned)(((set * 4 + wave) * 8 + k * 4 + q) * 256);
-        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen nt lds" ::"s"(dst), "v"(go), "s"(rg), "s"((unsigned)q * 4u * n) : "memory");
-      }
+    for (int f = 0; f < 2; ++f) {
+      const bool ok = tau0 + f < T;
+      const int t = d.rev ? T - 1 - tau0 - f : tau0 + f;
+      const __amdgpu_buffer_rsrc_t rg =
+          __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)d.gates + (unsigned long long)(unsigned)(ok ? t : 0) * g_bytes), 0, ok ? g_bytes : 0u, kBufFlags);
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(zxs_wave + (unsigned)(f * sizeof(zxs[0]) + k * sizeof(zxs[0][0]))),
+                     "v"(t < L_row[k] ? zx_off : kParked), "s"(rg), "s"((unsigned)k * 8u * 4u * n * 4u) : "memory");
     }
   };
   unsigned h_prev_bits[2] = {pack_bf16x2(h[0], 0.f) & 0xffffu, pack_bf16x2(h[1], 0.f) & 0xffffu};
-  fetch_zx(0, 0);
+  fetch_zx(0);
   PROF_DECL
   auto step = [&](const int tau, auto parity) __attribute__((always_inline)) {
     constexpr int kSet = decltype(parity)::value;
@@ -731,6 +732,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
     const uint4* rin = ((tau & 1) ? d.ring1 : d.ring0) + (long)rt * nkc * 64;
     RingReader rd = make_reader(rin, nkc, ntiles16 * 2, wave, lane, ll_fwd_tag((unsigned)tau) << 14, err, a.spin_limit, rot);
     f32x4 acc[2][4];
+    float zx_[2][4];
     {
       auto mma_one = [&](int it, int ct, int q, const u32x4& a_op) __attribute__((always_inline)) {
         if (it < kAccIts) mfma_b_agpr(acc[ct][q], a_op, wa[it < kAccIts ? it : 0][ct][q]);
@@ -759,32 +761,33 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
       };
       // (Fetching everything along with the first poll - stale loads now being cheap to repeat - was measured 15 % slower
       // per step: the polled pair then returns behind 10 KiB of other loads, most of which are repeated anyway.)
-      for (unsigned poll = 0;; ++poll) {
+      auto poll_loads = [&]() __attribute__((always_inline)) {
         x[0][0] = rd.load_it(rd.it_of(0));
         x[0][1] = rd.load_it(rd.it_of(1));
-        __builtin_amdgcn_sched_barrier(0);
-        if (poll == 0) {
-#pragma unroll
-          for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[ct][q] = (f32x4){0.f, 0.f, 0.f, 0.f};
-          operands_settle(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
-          operands_settle(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (dead) break;
+      };
+      auto polled_stale = [&]() __attribute__((always_inline)) {
         const unsigned stale = rd.tag_diff(x[0][0], rd.it_of(0), tagw) | rd.tag_diff(x[0][1], rd.it_of(1), tagw);
-        if (__builtin_amdgcn_ballot_w64(stale > 0xffffu) == 0ull) break;
-        if (poll >= rd.limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
-          st_relaxed(err, 1u);
-          dead = true;
-          break;
-        }
-        PROF_POLLS(1)
-      }
+        return __builtin_amdgcn_ballot_w64(stale > 0xffffu) != 0ull;
+      };
+      poll_loads();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[ct][q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      operands_settle(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+      operands_settle(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (__builtin_expect(polled_stale() && !dead, 0)) rd.poll_again(dead, poll_loads, polled_stale);
       PROF_MARK(5)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing is in flight behind the poll, frames included
 #pragma unroll
       for (int i = 2; i < NIT; ++i) issue_dma(i);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zx_[k][q] = zxs[kSet][k][wave][lane >> 5][q][u];
       __builtin_amdgcn_sched_barrier(0);
       unsigned bad[NP];
       // pair p + 1 becomes operands behind MFMA `at` of pair p: wait for its loads, read them from LDS (step -1);
@@ -823,8 +826,8 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
           operands_settle(x[p & 1][0], x[p & 1][1]);
           // The next frame's x W_x + b goes out where this wavefront's last ring load has arrived (see the 32 x 8 kernel) -
           // unless a pair is being fetched again: the second look below waits for everything in flight, and these come from HBM.
-          if (p == NP - 1 && redo == 0ull) {
-            fetch_zx(tau + 1, kSet ^ 1);
+          if (kSet == 1 && p == NP - 1 && redo == 0ull) {
+            fetch_zx(tau + 1);
             zx_asked = true;
           }
 #pragma unroll
@@ -883,7 +886,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
         rd.template fix_up_batch<NIT / 4, 3 * (NIT / 4)>(redo, dead, use_single);
       }
       mfma_settle(acc[0][0], acc[0][1], acc[0][2], acc[0][3], acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
-      if (!zx_asked) fetch_zx(tau + 1, kSet ^ 1);
+      if (kSet == 1 && !zx_asked) fetch_zx(tau + 1);
     }
     PROF_MARK(0)
     // (LDS addresses are formed anew in every step: hoisted out of the loop they stay in registers the loop does not have)
@@ -897,8 +900,6 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) red_[wave][4 * (lane_ >> 4) + v][q * 32 + ct * 16 + (lane_ & 15)] = acc[ct][q][v];
     PROF_MARK(1)
-    // this frame's x W_x + b was asked for one step ago: everything but the 8 loads just issued has completed
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     __syncthreads();
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc((void*)((tau & 1) ? d.ring0 : d.ring1), 0, kParked, kBufFlags);
     const __amdgpu_buffer_rsrc_t ry = frame_of(d.y, t, y_bytes), rc = frame_of(d.cs, t, s_bytes), rh = frame_of(d.hprev, t, h_bytes);
@@ -918,7 +919,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
         for (int q = 0; q < 4; ++q) zh[q] = red_[0][rr][q * 32 + u_] + red_[1][rr][q * 32 + u_] + red_[2][rr][q * 32 + u_] + red_[3][rr][q * 32 + u_];
         float zx[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) zx[q] = zxs[kSet][wave][k * 4 + q][lane_];
+        for (int q = 0; q < 4; ++q) zx[q] = zx_[k][q];
         o[k] = lstm_cell(zh, zx, c[k]);
         c[k] = o[k].c; h[k] = o[k].h;
       }
@@ -1360,6 +1361,9 @@ template <int NPW, int NCT>                               // n <= 128 * NPW (pro
 __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   __shared__ float red[4][16][33];                       // [wavefront][row][output]
   __shared__ __attribute__((aligned(16))) unsigned short zb[16][136];
+  constexpr int kAhead = 2;                              // frames whose inputs are fetched together (see the 8-row kernel)
+  __shared__ float in_g[2 * kAhead][2][4][2][4][32], in_c[2 * kAhead][2][4][64];     // [frame][row half][wavefront]...
+  __shared__ unsigned in_y[2 * kAhead][2][4][64];
   constexpr int kBlock = 2 * kPartBytes;                 // one (producer, destination tile)
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
@@ -1395,16 +1399,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
       L[k] = clamp_len(a.lens, b, T);
     }
   }
-  // What the gate gradients of one frame need.  dy stays as the 16 bits that were loaded: a conversion right behind
-  // the load would make the wavefront wait for it - and for every load in front of it - where it is issued.
-  struct In { float gi, gf, gg, go, c_new, c_prev; unsigned dy_bits; };
-  // The per-frame arrays are read through buffer descriptors that cover exactly one frame: the frame's address is
-  // scalar arithmetic, a lane's offset inside the frame never changes, and a lane with nothing to fetch (row past the
-  // batch, unit past n, frame past the row's length) has its offset parked outside the frame and gets zeros without
-  // touching memory - as does every lane when the frame itself does not exist (zero-sized descriptor).  Nothing is
-  // predicated, so every step issues the same six loads; with loads that may or may not have been issued the
-  // compiler has to assume the fewest, and made the wavefront wait for the loads of the NEXT frame, just issued and
-  // on their way from HBM, where it only needed those of this one.
+  // What the gate gradients of a frame need, and how it is fetched: see the 8-row kernel.
   constexpr unsigned kParked = 0x7ff00000u;
   const unsigned g_bytes = (unsigned)B * 4u * n * 4u, s_bytes = (unsigned)B * n * 4u, y_bytes = (unsigned)B * d.lddy * 2u;
   // offsets of row r8 inside a frame; row r8 + 8 lies a wave-uniform distance behind it (and exists only if row r8 does)
@@ -1415,42 +1410,48 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   auto s_off = [&](int k) { return k == 0 ? s_off0 : (active[1] ? s_off0 + 8u * n * 4u : kParked); };
   auto y_off = [&](int k) { return k == 0 ? y_off0 : (active[1] ? y_off0 + 8u * (unsigned)d.lddy * 2u : kParked); };
   auto frame_of = [&](const void* base, int t, unsigned bytes) {
-    const bool ok = t >= 0 && t < T;
-    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)(ok ? t : 0) * bytes), 0, ok ? bytes : 0u, kBufFlags);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (long long)t * bytes), 0, bytes, kBufFlags);
   };
-  auto ld_f = [&](__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {     // 2: non-temporal
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 2));
+  const int zu = J * 32 + 4 * (lane & 7);
+  int L_row[2];
+  unsigned L_prev[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    L_row[k] = b0 + 8 * k < B && zu < n ? clamp_len(a.lens, b0 + 8 * k, T) : 0;
+    L_prev[k] = (unsigned)(d.rev ? min(L[k], T - 1) : L[k]);
+  }
+  const unsigned gq_off = ((unsigned)b0 * 4u * n + ((unsigned)lane >> 3 & 3u) * n + zu) * 4u;
+  auto lds_addr = [](const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p); };
+  const unsigned lds_g = lds_addr(&in_g[0][0][wave][0][0][0]), lds_c = lds_addr(&in_c[0][0][wave][0]), lds_y = lds_addr(&in_y[0][0][wave][0]);
+  const int t_first = d.rev ? 0 : T - 1, dt = d.rev ? 1 : -1;          // frame of backward step sigma: t_first + dt * sigma
+  // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight)
+  auto fetch_in = [&](int sigma) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < kAhead; ++f) {
+      const unsigned place = (unsigned)(sigma + f) & (2 * kAhead - 1);
+      const int t = t_first + dt * (sigma + f), tp = t + dt;
+      const __amdgpu_buffer_rsrc_t rg = frame_of(d.gates, t, g_bytes), rc = frame_of(d.cs, tp, s_bytes), ry = frame_of(d.dy, t, y_bytes);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds_g + place * (unsigned)sizeof(in_g[0]) + (unsigned)(k * sizeof(in_g[0][0]))),
+                     "v"((unsigned)t < (unsigned)L_row[k] ? gq_off : kParked), "s"(rg), "s"((unsigned)k * 8u * 4u * n * 4u) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(lds_c + place * (unsigned)sizeof(in_c[0]) + (unsigned)(k * sizeof(in_c[0][0]))),
+                     "v"((unsigned)(d.rev ? t : tp) < L_prev[k] ? s_off(k) : kParked), "s"(rc) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ushort %1, %2, 0 offen nt lds" ::"s"(lds_y + place * (unsigned)sizeof(in_y[0]) + (unsigned)(k * sizeof(in_y[0][0]))),
+                     "v"((unsigned)t < (unsigned)L[k] ? y_off(k) : kParked), "s"(ry) : "memory");
+      }
+    }
   };
-  auto fetch_in = [&](int tau, int k) {
-    const int t = tau < 0 ? -1 : (d.rev ? T - 1 - tau : tau);
-    const bool lane_on = t < L[k];                         // (L is 0 in lanes without a row)
-    const unsigned go = lane_on ? g_off(k) : kParked, yo = lane_on ? y_off(k) : kParked;
-    In in;
-    const __amdgpu_buffer_rsrc_t rg = frame_of(d.gates, t, g_bytes);
-    in.gi = ld_f(rg, go, 0u); in.gf = ld_f(rg, go, 4u * n); in.gg = ld_f(rg, go, 8u * n); in.go = ld_f(rg, go, 12u * n);
-    const int tp = d.rev ? t + 1 : t - 1;                  // the frame before t in processing order
-    const bool inside = t >= 0 && tp >= 0 && tp < T, initial = t >= 0 && !inside && d.c0 != nullptr;
-    const __amdgpu_buffer_rsrc_t rp = initial ? __builtin_amdgcn_make_buffer_rsrc((void*)d.c0, 0, s_bytes, kBufFlags)
-                                              : frame_of(d.cs, inside ? tp : -1, s_bytes);
-    // The cell state entering frame t is the state leaving the frame before it, which is the NEXT backward step's
-    // frame: that step takes its c_new from here instead of loading it again (one load per step less).  So the value is
-    // also fetched where frame t itself is padding but the frame before it is real (direction +1, t = the row's length).
-    in.c_prev = ld_f(rp, (d.rev ? t : t - 1) < L[k] ? s_off(k) : kParked, 0u);
-    in.c_new = 0.f;                                        // supplied by the caller
-    in.dy_bits = __builtin_amdgcn_raw_buffer_load_b16(frame_of(d.dy, t, y_bytes), yo, 0, 2);
-    return in;
-  };
+  fetch_in(0);
+  float c_first[2], c_new[2];                              // cell state entering the first frame; leaving the next step's frame
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    c_first[k] = active[k] && d.c0 ? d.c0[(long)(b0 + 8 * k) * n + j] : 0.f;
+    c_new[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(frame_of(d.cs, t_first, s_bytes), t_first < L[k] ? s_off(k) : kParked, 0u, 2));
+  }
   // entries of DZ, which this thread stores: a pointer that moves by one frame per step
   const long row_last = (long)(d.rev ? 0 : T - 1) * B + b0, g_step = (d.rev ? (long)B : -(long)B) * 4 * n;
   unsigned short* dz_p = (unsigned short*)d.DZ + row_last * 4 * n + j;
-  In in_a[2], in_b[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    in_a[k] = fetch_in(T - 1, k);
-    in_b[k] = in_a[k];
-    const int t0 = d.rev ? 0 : T - 1;                      // the first frame's own cell state: the only one loaded as such
-    in_a[k].c_new = ld_f(frame_of(d.cs, t0, s_bytes), t0 < L[k] ? s_off(k) : kParked, 0u);
-  }
 
   // consumer side: a load covers one producer's block; lane reads output lane/2, rows 8 * (lane%2) .. + 7
   const int ccol = lane >> 1, chalf = lane & 1;
@@ -1470,13 +1471,11 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   }
 
   PROF_DECL
-  // One time step.  `in` holds the inputs of this step's frame and `in_next` receives those of the next; the loop
-  // below calls it with the two in alternating roles, because a copy at the end of a step would have to wait for
-  // the loads (and, counted with them, the step's stores) at that point.
+  // One time step.
   // `ring_c`: the step reads partial sums (every step but the first); `pointwise_c`: it has a frame (every step but the
   // last, which only collects the Dh that leaves the layer).  Constants of the call, so that the loop below is free
   // of the two exceptions: with them inside, the compiler's wait counts in the loop allowed for paths it never takes.
-  auto step = [&](const int tau, const In (&in)[2], In (&in_next)[2], auto ring_c, auto pointwise_c) __attribute__((always_inline)) {
+  auto step = [&](const int tau, auto ring_c, auto pointwise_c) __attribute__((always_inline)) {
     PROF_MARK(4)
     // (told to be wave-uniform: computed next to per-lane uses of tau it ends up in vector registers, and a buffer
     // descriptor derived from it is then applied lane by lane in a loop)
@@ -1491,6 +1490,19 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
     // The gate gradients of a valid frame, dh = dy + Dh (recurrent_dev.h has the plain form):
     //   dc = Dc + dh go (1 - tanh(c)^2), Dc' = dc gf, dz = (dc gg gi (1-gi), dc c_prev gf (1-gf), dc gi (1-gg^2), dh tanh(c) go (1-go)).
     // Everything that does not involve dh or Dc is computed while the ring loads are in flight.
+    struct { float gi, gf, gg, go, c_new, c_prev; unsigned dy_bits; } in[2];
+    auto take_in = [&]() __attribute__((always_inline)) {
+      const int place = sigma & (2 * kAhead - 1);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        in[k].gi = in_g[place][k][wave][lane >> 5][0][u]; in[k].gf = in_g[place][k][wave][lane >> 5][1][u];
+        in[k].gg = in_g[place][k][wave][lane >> 5][2][u]; in[k].go = in_g[place][k][wave][lane >> 5][3][u];
+        in[k].c_new = c_new[k]; in[k].c_prev = in_c[place][k][wave][lane]; in[k].dy_bits = in_y[place][k][wave][lane];
+        if (tau == 0) in[k].c_prev = c_first[k];
+        c_new[k] = in[k].c_prev;
+      }
+    };
     float f_c[2], f_i[2], f_f[2], f_g[2], f_o[2];
     auto factors = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -1507,11 +1519,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
       }
     };
     auto fetch_next = [&]() __attribute__((always_inline)) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        in_next[k] = fetch_in(tau - 1, k);
-        in_next[k].c_new = in[k].c_prev;
-      }
+      if ((sigma & (kAhead - 1)) == 0) fetch_in(sigma + kAhead);
     };
     if constexpr (decltype(ring_c)::value) {
       RingReader rd;
@@ -1543,32 +1551,31 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
         const unsigned tagw = rd.tag << 16;
         // The poll is the first two loads, repeated (bounded) until their tags have turned and then kept; the others
         // are issued behind it (see the forward kernel).
-        for (unsigned poll = 0;; ++poll) {
+        auto poll_loads = [&]() __attribute__((always_inline)) {
           x[0] = rd.load_it(rd.it_of(0));
           x[1] = rd.load_it(rd.it_of(1));
-          if (dead) break;
+        };
+        auto polled_stale = [&]() __attribute__((always_inline)) {
           const unsigned stale = rd.tag_diff(x[0], rd.it_of(0), tagw) | rd.tag_diff(x[1], rd.it_of(1), tagw);
-          if (__builtin_amdgcn_ballot_w64(stale > 0xffffu) == 0ull) break;
-          if (poll >= rd.limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
-            st_relaxed(err, 1u);
-            dead = true;
-            break;
-          }
-          PROF_POLLS(1)
+          return __builtin_amdgcn_ballot_w64(stale > 0xffffu) != 0ull;
+        };
+        poll_loads();
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (pointwise) {                         // while the poll is in flight: all that does not need Dh
+          take_in();
+          factors();
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if (__builtin_expect(polled_stale() && !dead, 0)) rd.poll_again(dead, poll_loads, polled_stale);
         PROF_MARK(5)
-        // Nothing is outstanding here (the poll has just been waited for, and loads complete in order).  Said with an
-        // instruction the compiler takes note of: otherwise it makes the pointwise part below wait for this frame's
-        // inputs, asked for a step ago, with a count that also waits for the next frame's, just asked for.
+        // (nothing is in flight behind the poll, the next step's inputs included)
         __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0)
 #pragma unroll
         for (int i = 2; i < NLD; ++i) x[i] = rd.load_it(rd.it_of(i));
         __builtin_amdgcn_sched_barrier(0);
-        // while those loads are on their way: the polled loads' values, and the part of the gate gradients that
-        // does not need Dh
+        // while those loads are on their way: the polled loads' values
         add(ps, x[0]);
         add(ps, x[1]);
-        factors();
         __builtin_amdgcn_sched_barrier(0);
         unsigned long long redo = 0ull;
         constexpr int kGroup = (NLD - 2) / 2;              // the other loads: two groups
@@ -1600,7 +1607,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
         }
         // The next frame's inputs, from HBM.  Loads complete in the order of issue: asked for in front of the groups
         // above (where their latency would be covered best) they held up every ring load behind them - a tenth of the step.
-        fetch_next();
+        if constexpr (pointwise) fetch_next();
       }
       PROF_MARK(0)
 #pragma unroll
@@ -1613,6 +1620,8 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
           Dh[k] = (red[0][rr][u] + red[1][rr][u] + red[2][rr][u] + red[3][rr][u]) * (1.f / kPartScale);   // the partial sums travel scaled
         }
     } else {
+      __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
+      take_in();
       factors();
       fetch_next();
     }
@@ -1706,18 +1715,9 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   // (tau is told to be wave-uniform: computed next to per-lane uses it ends up in vector registers)
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
-  step(T - 1, in_a, in_b, no, yes);                        // (T >= 2)
-  int tau = T - 2;
-  for (; tau >= 1; tau = __builtin_amdgcn_readfirstlane(tau) - 2) {
-    step(tau, in_b, in_a, yes, yes);
-    step(__builtin_amdgcn_readfirstlane(tau - 1), in_a, in_b, yes, yes);
-  }
-  if (tau == 0) {
-    step(0, in_b, in_a, yes, yes);
-    step(-1, in_a, in_b, yes, no);
-  } else {
-    step(-1, in_b, in_a, yes, no);
-  }
+  step(T - 1, no, yes);                                    // (T >= 2)
+  for (int tau = T - 2; tau >= 0; tau = __builtin_amdgcn_readfirstlane(tau) - 1) step(tau, yes, yes);
+  step(-1, yes, no);
   PROF_DUMP("bwdp16", T)
 #pragma unroll
   for (int k = 0; k < 2; ++k)
