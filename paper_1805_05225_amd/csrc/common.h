@@ -184,7 +184,7 @@ constexpr int kLLMaxNkcFwd = 32;                     // register budget of the k
 constexpr unsigned kLLFwdTagBit = 0x40000000u;       // in the upper dword of a unit: bit 14 of the fourth value
 inline int ll_nkc(int n, int slots) { return (int)((((long)(n + 15) / 16) * slots + 31) / 32); }
 // packed W_h of one direction; `paired`: in whole tiles of 32 units, for the 8-row kernel
-inline size_t ll_wf_bytes(int n, int nkc, bool paired) { return (size_t)(paired ? 2 * ((n + 31) / 32) : (n + 15) / 16) * 4 * nkc * 1024; }
+inline size_t ll_wf_bytes(int n, int nkc) { return (size_t)(2 * ((n + 31) / 32)) * 4 * nkc * 1024; }
 // The tag bit of the data that step tau consumes (written by step tau - 1 into slot tau & 1; the initial contents of
 // slot 0 carry it for tau = 0): it alternates between consecutive uses of a slot and is 1 at a slot's first use, so a
 // zero-filled slot never looks written.
@@ -194,7 +194,20 @@ __host__ __device__ inline unsigned ll_fwd_tag(unsigned tau) { return ((tau >> 1
 // (of 8 or 16 rows) in the launch, groups per XCD.
 struct GridMap { int ntile, nrow, gpx; };
 
+// Rows of different lengths one behind the other in a launch's row places (persistent.hip): built by the set-up launch, read by the loop.
+struct PackRows {
+  const int* lens; int T, B, slots, tab_steps, max_steps; // slots = 0: not used; more than max_steps steps: steps[0] = -1 and no table
+  unsigned* up; unsigned* down; int* steps;               // [group of 8 places][tab_steps][8] frames ascending / descending in time; steps of a group
+};
+int persist_pack_slots(int T, int B, int n, int ndir, bool backward);
+int pack_tab_steps(int T, int B, int slots);
+int pack_max_steps(int T, bool backward);
+constexpr int kPackMaxSlots = 128, kPackMaxRows = 256;
+// y = 0 and the carried cell state at padded frames (which such a launch leaves out; nothing if steps[0] < 0); y [T][B][ndir * n] bfloat16, n even
+hipError_t launch_fill_padded(const int* lens, const int* steps, int T, int B, int n, int ndir, void* y, float* const* cs, const float* const* c0, const int* rev, hipStream_t s);
+
 struct PFwdDir {
+  const unsigned* tab;  // rows one behind the other: frames in this direction's order
   const uint4* Wf;    // as launch_prep_fwd_ll writes it
   const uint4* Wzero; // one chunk (64 x 16 bytes) of zeros
   uint4* ring0; uint4* ring1;   // [row tile][nkc][64] chunks each
@@ -208,6 +221,7 @@ struct PFwdDir {
 struct PFwdArgs {
   PFwdDir d[2];
   const int* lens;
+  int slots, tab_steps; const int* steps;                 // PackRows (slots = 0: every row has a place of its own)
   int B, n, nkc, T, ndir, write_gates;
   unsigned* sync; unsigned spin_limit;
   unsigned* xcc;      // NULL or one zeroed word per work-group (see PBwdArgs)
@@ -227,6 +241,7 @@ bool persist_fwd_f32_fits(const PFwdArgs& a);
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward);      // are the float loops faster than the per-step kernels?
 
 struct PBwdDir {
+  const unsigned* tab;  // as in PFwdDir, in the order of the backward steps
   const uint4* Wb;    // as launch_prep_bwd_ll writes it
   uint4* ring0; uint4* ring1;
   uint4* wide;        // float storage: scratch as large as a ring
@@ -240,6 +255,7 @@ struct PBwdDir {
 struct PBwdArgs {
   PBwdDir d[2];
   const int* lens;
+  int slots, tab_steps; const int* steps;
   int B, n, T, ndir;
   unsigned* sync; unsigned spin_limit;
   unsigned* xcc;      // NULL or one zeroed word per work-group: lets an exchange group find out whether it shares an XCD
@@ -390,8 +406,8 @@ hipError_t launch_fill_zero_many(const ZeroRegions& r, hipStream_t s);
 // ring, and the frame map of launch_frame_map if fm.fidx is not NULL.
 struct FrameMapArgs { const int* lens; int T, B; int* fidx; int* count; };
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
-                              int nrt, const FrameMapArgs& fm, hipStream_t s);
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, hipStream_t s);
+                              int nrt, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]
 constexpr int kColsumSlices = 64;

@@ -27,7 +27,7 @@ struct Plan {
   long ldh;
   size_t res_gates, res_hprev, res_dir_stride, reserve_bytes;
   // workspace
-  size_t ws_Wf, ws_Wb, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_dzwide, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
+  size_t ws_Wf, ws_Wb, ws_rows, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_dzwide, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
       ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool small;                               // narrow layer: loop_small.hip
@@ -103,7 +103,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   // error word, per-row-tile words, then one word per work-group of a single-launch kernel (its XCD)
   p->sync_bytes = up((64 + 2 * (size_t)p->nrt) * 4 + std::max(D * 2 * (size_t)p->nrt * cdiv(d->n, 32), (size_t)256) * 4);
   p->ws_sync = take(p->sync_bytes);              // first, so that lstm_sync_status() finds it without a plan
-  p->Wf_bytes = D * std::max((size_t)p->ntile_f * 2 * p->nkc_f * 1024, ll_wf_bytes(d->n, p->nkc_ll_f, true));
+  p->Wf_bytes = D * std::max((size_t)p->ntile_f * 2 * p->nkc_f * 1024, ll_wf_bytes(d->n, p->nkc_ll_f));
   p->ws_Wf = take(p->Wf_bytes + 1024);            // packed W_h, then one chunk of zeros
   const bool part = p->bf16 && d->n <= 1024;          // the partial-sum backward kernel may be chosen
   // float storage: the single-launch backward kernel (batches of up to 256 rows: its rings grow with B n^2 / 16)
@@ -172,6 +172,8 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_parts = take(p->parts_bytes);
   p->blocks = p->bf16 && loop_block_width(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
   p->ws_blocks = take(p->blocks ? loop_block_wh_bytes(d->n) + std::max(loop_block_ring_bytes(d->n), loop_block_ring_bytes_bwd(d->n)) : 0);
+  // tables of rows one behind the other (whatever the device's size makes of them)
+  p->ws_rows = take(p->bf16 && d->n <= 1024 && d->B > 8 && d->B <= kPackMaxRows ? 2 * (TB + kPackMaxSlots * ((size_t)d->T + 1)) * 4 + kPackMaxSlots / 8 * 4 : 0);
   p->ws_h0 = take(D * B * p->ldh * p->esz);
   p->ws_h0rows = take(D * B * 4);
   // (one step runs as one step of LSTM_FLAG_PER_STEP does, bit for bit)
@@ -195,6 +197,19 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
 }
 
 bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
+
+// rows one behind the other: the tables' places in the workspace
+PackRows pack_rows(const Plan& p, char* ws, const int* lens, bool backward, const lstm_desc* desc) {
+  PackRows r = {};
+  if (!p.fast_gemm || !lens || p.B <= 8 || p.T < 2 || (desc->flags & LSTM_FLAG_PER_STEP)) return r;
+  r.slots = persist_pack_slots(p.T, p.B, p.n, p.D, backward);
+  if (r.slots == 0) return r;
+  r.lens = lens; r.T = p.T; r.B = p.B; r.tab_steps = pack_tab_steps(p.T, p.B, r.slots); r.max_steps = pack_max_steps(p.T, backward);
+  r.up = (unsigned*)(ws + p.ws_rows);
+  r.down = r.up + (size_t)r.slots * r.tab_steps;
+  r.steps = (int*)(r.down + (size_t)r.slots * r.tab_steps);
+  return r;
+}
 
 int widest(long ld_elems, long s1, long s2, size_t esz, int cap) {
   int v = cap;
@@ -441,7 +456,8 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     if (e == hipSuccess) return LSTM_OK;
     (void)hipGetLastError();               // refused before anything ran: the per-step path
   }
-  const bool paired = persist_fwd_rows(p.B, p.n, p.D) == 8;    // (how the bf16 single-launch kernel wants W_h)
+  const PackRows rows = pack_rows(p, ws, seq_lens, false, desc);
+  const bool paired = rows.slots > 0 || persist_fwd_rows(p.B, p.n, p.D) == 8;    // (how the bf16 single-launch kernel wants W_h)
   {
     Phase ph(LSTM_PHASE_PREP, 5, s);
     ZeroRegions z;
@@ -456,7 +472,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         frames_mapped = true;
       }
       HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
-                                p.nrt, fm, s));
+                                p.nrt, fm, rows, s));
     } else HIPCHK(launch_fill_zero_many(z, s));
   }
   // single-launch path: bf16 storage, at least two steps, register budget of the kernel
@@ -516,12 +532,13 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       fd.hprev = infer ? nullptr : rs + d * p.res_dir_stride + p.res_hprev;
       fd.ldh = p.ldh;
       fd.rev = bidir ? d == 1 : desc->direction == -1;
+      fd.tab = fd.rev ? rows.down : rows.up;
     }
   };
   PFwdArgs pa = {};                      // the single-launch kernels' arguments, if one of them takes this problem
   if (use_ll) {
-    pa.nkc = p.nkc_ll_f;
-    set_dirs(pa, ws + p.ws_Wf, ll_wf_bytes(p.n, p.nkc_ll_f, paired), (size_t)p.nrt * p.nkc_ll_f * 1024);
+    pa.nkc = p.nkc_ll_f; pa.slots = rows.slots; pa.tab_steps = rows.tab_steps; pa.steps = rows.steps;
+    set_dirs(pa, ws + p.ws_Wf, ll_wf_bytes(p.n, p.nkc_ll_f), (size_t)p.nrt * p.nkc_ll_f * 1024);
   } else {
     pa.nkc = p.nkc_f;                    // (float storage: the per-step kernels' packed W_h and h buffers)
     set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile_f * 2 * p.nkc_f * 1024, (size_t)p.nrt * p.nkc_f * 1024);
@@ -541,6 +558,12 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         e = use_ll ? launch_persist_fwd(pa, s) : launch_persist_fwd_f32(pa, s);
       }
       if (e == hipErrorCooperativeLaunchTooLarge && h0) e = hipErrorLaunchFailure;   // the pre-activations are no longer what the per-step path expects
+      if (e == hipSuccess && pa.slots > 0) {
+        float* cs[2] = {pa.d[0].cs, pa.d[D - 1].cs};
+        const float* cz[2] = {pa.d[0].c0, pa.d[D - 1].c0};
+        const int rev[2] = {pa.d[0].rev, pa.d[D - 1].rev};
+        HIPCHK(launch_fill_padded(seq_lens, rows.steps, p.T, p.B, p.n, p.D, y, cs, cz, rev, s));
+      }
       if (e == hipSuccess) done = true;
       else if (e == hipErrorCooperativeLaunchTooLarge) {   // nothing was launched (does not fit on the device all at once): one launch per step
         (void)hipGetLastError();
@@ -668,6 +691,9 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     pa.xcc = (unsigned*)(ws + p.ws_sync) + 64 + 2 * (size_t)p.nrt;
     for (size_t d = 0; d < D; ++d) pa.d[d].lddy = (long)(D * n);       // (the check looks at the frame sizes)
     const bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_bwd_fits(pa);
+    PackRows rows = {};
+    if (use_ll && compact) rows = pack_rows(p, ws, seq_lens, true, desc);
+    pa.slots = rows.slots; pa.tab_steps = rows.tab_steps; pa.steps = rows.steps;
     const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n <= 1024 && p.B <= 256 &&
                           persist_bwd_f32_fits(pa) && persist_f32_pays(p.T, p.B, p.n, p.D, seq_lens != nullptr, pa.plain_launch, true);
     {
@@ -688,7 +714,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           z.add(dx, (size_t)TB * n_in * p.esz);
           dx_cleared = true;
         }
-        HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, persist_bwd_rows(p.B, p.n, p.D) == 8, fm, s));
+        HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || persist_bwd_rows(p.B, p.n, p.D) == 8, fm, rows, s));
       } else HIPCHK(launch_fill_zero_many(z, s));
     }
     if (!use_ll) {
@@ -719,6 +745,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         bd.dh0 = dh0 ? (float*)dh0 + d * B * n : nullptr; bd.dc0 = dc0 ? (float*)dc0 + d * B * n : nullptr;
         bd.dbpart = db_in_loop ? (float*)(ws + p.ws_colsum) + d * kColsumSlices * 4 * n : nullptr;
         bd.rev = bidir ? d == 1 : desc->direction == -1;
+        bd.tab = bd.rev ? rows.up : rows.down;
       }
       hipError_t e;
       {

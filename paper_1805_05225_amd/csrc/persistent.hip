@@ -96,7 +96,6 @@ struct RingReader {
   template <typename L, typename S>
   __device__ __forceinline__ void poll_again(bool& dead, L&& loads, S&& stale) const {
     for (unsigned poll = 1;; ++poll) {
-      PROF_POLLS(1)
       loads();
       if (!stale()) return;
       if (poll >= limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
@@ -318,19 +317,63 @@ __device__ __forceinline__ WgCoord wg_coord(const GridMap& m, int ndir) {
   tile = __builtin_amdgcn_readfirstlane(tile);
   group = __builtin_amdgcn_readfirstlane(group);
   const int dir = __builtin_amdgcn_readfirstlane(group / m.nrow);
-  WgCoord c = {tile, group - dir * m.nrow, dir, group * m.ntile, group < groups};
+  WgCoord c = {tile, group - dir * m.nrow, dir, group * m.ntile, group < groups && tile < m.ntile};     // (a grid may be meant for more groups)
   return c;
 }
+
+// --- rows one behind the other -----------------------------------------------------------------------------------
+// More rows than a launch of the 8-row kernels holds, of different lengths: the launch's row places (`slots`, eight to a group) take rows
+// one after the other, so that a layer takes about (all frames / slots) steps instead of the longest row's for every 16 rows.  What a
+// place does in a step is a word of a table that the set-up launch writes from the lengths (pack_rows_body): frame t * B + b, and
+// whether it is a row's first or last.  Nothing crosses from row to row: a row's last step publishes zeros, its first takes the
+// caller's state, and h0 W_h is in its pre-activations already (see `started`).
+// 64 rows of 20-80 frames, n = 1000, both directions: 80 steps of 2.5 us on the 16-row kernels, 100 of 1.45 (backward 1.65) here: a layer 204 -> 162 us and 203 -> 172.
+constexpr unsigned kRowValid = 1u << 28, kRowFirst = 1u << 29, kRowLast = 1u << 30, kRowFrame = kRowValid - 1u;
+constexpr int kTabSteps = 512;                             // steps whose table words are kept in LDS (and a few more, asked for ahead)
+// A uniform value, held where buffer descriptors are formed from it.
+__device__ __forceinline__ unsigned in_sgpr(unsigned v) {
+  v = __builtin_amdgcn_readfirstlane(v);
+  asm("" : "+s"(v));
+  return v;
+}
+// A load on a path that few steps take, waited for there: the compiler would wait where the paths meet, for everything in flight.
+__device__ __forceinline__ float rare_load(const float* p) {
+  float v = *p;
+  asm volatile("" : "+v"(v));
+  return v;
+}
+// byte offset of a word's frame (frames and their sizes are below 2^24)
+__device__ __forceinline__ unsigned frame_off(unsigned e, unsigned bytes) { return __umul24(e & kRowFrame & 0xffffffu, bytes); }
+template <bool PACKED> struct RowTable {
+  static constexpr int kSteps = PACKED ? kTabSteps + 8 : 1;
+  unsigned (*lds)[8]; const unsigned* mem; int steps, slot;
+  // words of the steps from s0 on (s0 a multiple of kTabSteps); all threads of the work-group
+  __device__ __forceinline__ void load(int s0) const {
+    if constexpr (PACKED) {
+      __syncthreads();
+      for (int i = threadIdx.x; i < kSteps * 8; i += 256) lds[i >> 3][i & 7] = s0 + (i >> 3) < steps ? mem[(long)s0 * 8 + i] : 0u;
+      __syncthreads();
+    }
+  }
+  __device__ __forceinline__ unsigned at(int step, int now) const { return PACKED ? lds[step - (now & ~(kTabSteps - 1))][slot] : 0u; }
+};
 
 // ------------------------------------------------------------------------------------------------
 // forward: z[8 rows, 4 gates x 32 units] = h[8 rows, K] W[K, 128].  A work-group owns 32 units for 8 batch rows
 // (half a row tile); one load serves two chunks (see make_reader_half), one product two column tiles (see smfmac_b_agpr).  The W_h
 // slice fills the 256 accumulation registers of every lane (n = 1024).
-template <int NL>                                          // ring loads per wavefront and step: n <= 256 NL
-__global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
-  __shared__ float red[2][4][8][129];                    // two copies, used by even and odd steps: one barrier per step
-  constexpr int kAhead = 2;                              // frames of x W_x + b that are fetched together (fetch_zx below)
-  __shared__ float zxs[kAhead][4][2][4][32];             // [frame][wavefront][row][gate][unit]: a wavefront reads back what it asked for
+template <bool PACKED> struct Fwd8Lds {
+  static constexpr int kAhead = 2;                       // frames of x W_x + b that are fetched together (fetch_zx below)
+  alignas(16) float red[2][4][8][129];                   // two copies, used by even and odd steps: one barrier per step
+  alignas(16) float zxs[kAhead][4][2][4][32];            // [frame][wavefront][row][gate][unit]: a wavefront reads back what it asked for
+  alignas(16) unsigned tab[RowTable<PACKED>::kSteps][8];
+};
+template <int NL, bool PACKED>                             // ring loads per wavefront and step: n <= 256 NL; rows one behind the other
+__device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& lds) {
+  constexpr int kAhead = Fwd8Lds<PACKED>::kAhead;
+  auto& red = lds.red;
+  auto& zxs = lds.zxs;
+  auto& tab_lds = lds.tab;
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
@@ -364,11 +407,12 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   const int sparse = (lane & 8) ? kSparseHigh : kSparseLow;
 
   const int r8 = tid >> 5, u = tid & 31;                 // pointwise pair of this thread: row r8 of the half, unit u of 32
-  const int b = rt * 16 + half * 8 + r8, j = tile2 * 32 + u;
+  const int b = PACKED ? 0 : rt * 16 + half * 8 + r8, j = tile2 * 32 + u;
   const bool active = b < B && j < n;
+  const RowTable<PACKED> tab = {tab_lds, PACKED ? d.tab + (long)wg.rt * a.tab_steps * 8 : nullptr, PACKED ? __builtin_amdgcn_readfirstlane(a.steps[wg.rt]) : T, r8};
   float c = 0.f, h = 0.f;
   int L = 0;
-  if (active) {
+  if (active && !PACKED) {
     if (d.c0) c = d.c0[(long)b * n + j];
     if (d.h0) h = d.h0[(long)b * n + j];
     L = clamp_len(a.lens, b, T);
@@ -401,7 +445,9 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   const unsigned s_off = active ? ((unsigned)b * n + j) * 4u : kParked;
   const unsigned h_bytes = (unsigned)B * (unsigned)d.ldh * 2u, h_off = active ? ((unsigned)b * (unsigned)d.ldh + j) * 2u : kParked;
   const unsigned pub_off = publishes ? (unsigned)unit_index * 8u : kParked;
+  // (rows one behind the other: one descriptor covers all frames - they end below the parking offset -, a lane's offset names its frame)
   auto frame_of = [&](const void* base, int t, unsigned bytes, bool present = true) {
+    if constexpr (PACKED) return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, present && base != nullptr ? bytes * (unsigned)T : 0u, kBufFlags);
     return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (unsigned long long)(unsigned)t * bytes), 0, present && base != nullptr ? bytes : 0u, kBufFlags);
   };
   // The frames' values come from HBM, 450-530 ns away (1 us for the slowest of a group's 128 wavefronts), and a compute unit hands
@@ -415,9 +461,20 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
   const unsigned zx_off = ((unsigned)b * 4u * n + (unsigned)zq * n + zu) * 4u;
   const unsigned zxs_wave = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&zxs[0][wave][0][0][0]);
   // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight)
+  unsigned e_ahead[kAhead] = {};                           // table words of the frames that are fetched next
+  auto look_ahead = [&](int tau0, int now) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < kAhead; ++f) e_ahead[f] = tab.at(tau0 + f, now);
+  };
   auto fetch_zx = [&](int tau0) __attribute__((always_inline)) {
 #pragma unroll
     for (int f = 0; f < kAhead; ++f) {
+      if constexpr (PACKED) {
+        const unsigned e = e_ahead[f];
+        const unsigned off = frame_off(e, 16u * n) + ((unsigned)zq * n + zu) * 4u;
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(zxs_wave + (unsigned)f * (unsigned)sizeof(zxs[0])), "v"((e & kRowValid) && zu < n ? off : kParked), "s"(frame_of(d.gates, 0, g_bytes)) : "memory");
+        continue;
+      }
       const bool ok = tau0 + f < T;
       const int t = d.rev ? T - 1 - tau0 - f : tau0 + f;
       const __amdgpu_buffer_rsrc_t rg =
@@ -426,12 +483,15 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
     }
   };
   unsigned h_prev_bits = pack_bf16x2(h, 0.f) & 0xffffu;     // what hprev receives: h before the step, as bf16
+  tab.load(0);
+  look_ahead(0, 0);
   fetch_zx(0);
   PROF_DECL
   auto step = [&](const int tau, auto parity) __attribute__((always_inline)) {
     float (&red_)[4][8][129] = red[decltype(parity)::value];
     const int t = d.rev ? T - 1 - tau : tau;
-    const bool valid = active && t < L;
+    const unsigned e = tab.at(tau, tau);
+    const bool valid = active && (PACKED ? (e & kRowValid) != 0u : t < L);
     PROF_MARK(4)
     const uint4* rin = ((tau & 1) ? d.ring1 : d.ring0) + (long)rt * nkc * 64;
     uint4* rout = (tau & 1) ? d.ring0 : d.ring1;
@@ -500,6 +560,7 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
       asm volatile("" ::: "memory");
 #pragma unroll
       for (int q = 0; q < 4; ++q) zx[q] = zxs[zslot][wave][lane >> 5][q][u];
+      if (PACKED && fetches) look_ahead(tau + 1, tau);
       __builtin_amdgcn_sched_barrier(0);
       u32x4 ops[NL][2];
       unsigned bad[NP];                                    // tag mismatches of the pair, per lane, in the upper 16 bits
@@ -565,6 +626,17 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
     PROF_MARK(1)
     __syncthreads();
 
+    if constexpr (PACKED) {
+      if ((e & kRowFirst) && active) {
+        c = 0.f; h = 0.f;
+        if (d.c0 || d.h0) {
+          const long s0 = (long)((e & kRowFrame) % (unsigned)B) * n + j;
+          if (d.c0) c = rare_load(&d.c0[s0]);
+          if (d.h0) h = rare_load(&d.h0[s0]);
+        }
+        h_prev_bits = pack_bf16x2(h, 0.f) & 0xffffu;
+      }
+    }
     CellOut o = {};
     if (valid) {
       float zh[4];
@@ -574,7 +646,7 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
       c = o.c; h = o.h;
     }
     const unsigned h_bits = pack_bf16x2(h, 0.f) & 0xffffu; // inactive threads hold h = 0: padding rows / units publish zeros
-    started = started || valid;
+    started = PACKED ? valid && !(e & kRowLast) : started || valid;
     PROF_MARK(2)
     {                                 // the recurrence's critical store goes out first
       // h of the next three units of the tile (DPP row_shl:1, :2, :3; past the row of 16 lanes: zero)
@@ -589,25 +661,44 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
       else __builtin_amdgcn_raw_buffer_store_b64(unit, ro, pub_off, 0, 16);
     }
     {                                 // layer outputs and what the backward pass needs (2: non-temporal)
-      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(valid ? h_bits : 0u), frame_of(d.y, t, y_bytes), y_off, 0, 2);
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c), frame_of(d.cs, t, s_bytes), s_off, 0, 2);
-      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)h_prev_bits, frame_of(d.hprev, t, h_bytes), h_off, 0, 2);
+      // (padded frames are filled by a launch of its own where rows run one behind the other)
+      const unsigned yo = PACKED ? (valid ? frame_off(e, 2u * (unsigned)d.ldy) + 2u * j : kParked) : y_off, so = PACKED ? (valid ? frame_off(e, 4u * n) + 4u * j : kParked) : s_off;
+      const unsigned ho = PACKED ? (valid ? frame_off(e, 2u * (unsigned)d.ldh) + 2u * j : kParked) : h_off;
+      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(valid ? h_bits : 0u), frame_of(d.y, t, y_bytes), yo, 0, 2);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c), frame_of(d.cs, t, s_bytes), so, 0, 2);
+      __builtin_amdgcn_raw_buffer_store_b16((unsigned short)h_prev_bits, frame_of(d.hprev, t, h_bytes), ho, 0, 2);
       const __amdgpu_buffer_rsrc_t rw = frame_of(d.gates, t, g_bytes, a.write_gates != 0);
-      const unsigned gw = valid ? g_off : kParked;
+      const unsigned gw = valid ? (PACKED ? frame_off(e, 16u * n) + 4u * j : g_off) : kParked;
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.gi), rw, gw, 0u, 2);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.gf), rw, gw, 4u * n, 2);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.gg), rw, gw, 8u * n, 2);
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o.go), rw, gw, 12u * n, 2);
     }
+    if constexpr (PACKED) {
+      if ((e & kRowLast) && active && (d.cT || d.hT)) {
+        const long s0 = (long)((e & kRowFrame) % (unsigned)B) * n + j;
+        if (d.cT) d.cT[s0] = c;
+        if (d.hT) d.hT[s0] = h;
+      }
+    }
     h_prev_bits = h_bits;
     PROF_MARK(3)
   };
-  for (int tau = 0; tau < T; tau += 2) {
+  for (int tau = 0; tau < tab.steps; tau += 2) {
+    if (PACKED && tau > 0 && (tau & (kTabSteps - 1)) == 0) tab.load(tau);
     step(tau, std::integral_constant<int, 0>{});
-    if (tau + 1 < T) step(tau + 1, std::integral_constant<int, 1>{});
+    if (tau + 1 < tab.steps) step(tau + 1, std::integral_constant<int, 1>{});
   }
   PROF_DUMP("fwd8", T)
-  if (active) {
+  if constexpr (PACKED) {
+    if (wg.rt == 0 && active && (d.cT || d.hT))            // rows without frames keep their state
+      for (int bb = r8; bb < B; bb += 8)
+        if (clamp_len(a.lens, bb, T) == 0) {
+          const long s0 = (long)bb * n + j;
+          if (d.cT) d.cT[s0] = d.c0 ? d.c0[s0] : 0.f;
+          if (d.hT) d.hT[s0] = d.h0 ? d.h0[s0] : 0.f;
+        }
+  } else if (active) {
     if (d.cT) d.cT[(long)b * n + j] = c;
     if (d.hT) d.hT[(long)b * n + j] = h;
   }
@@ -619,14 +710,19 @@ __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
 // that each walk all T steps.  Every MFMA row is a real row (96 MFMAs per wavefront and step, as in the 32 x 8 form,
 // for twice the rows), a load is one whole chunk (12 loads per wavefront and step instead of 6), and a thread
 // updates two cells (rows r8 and r8 + 8).  Ring layout, tags and publishing are those of the 32 x 8 form.
-template <int NIT>
-__global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
-  __shared__ float red[2][4][16][129];                   // two copies, used by even and odd steps: one barrier per step
+template <int NIT> struct Fwd16Lds {
+  alignas(16) float red[2][4][16][129];                  // two copies, used by even and odd steps: one barrier per step
   // x W_x + b of the next frames, fetched two together (see the 32 x 8 kernel): [frame][row half][wavefront][row][gate][unit], a
   // wavefront reading back what it asked for, so no barrier is involved - only the loads' completion.
-  __shared__ float zxs[2][2][4][2][4][32];
-  __shared__ u32x4 rbuf[4][NIT][64];                     // the ring loads of a step: [wavefront][load][lane], written by the memory unit
-  const WgCoord wg = wg_coord(a.map, a.ndir);
+  alignas(16) float zxs[2][2][4][2][4][32];
+  u32x4 rbuf[4][NIT][64];                                // the ring loads of a step: [wavefront][load][lane], written by the memory unit
+};
+template <int NIT>
+__device__ __forceinline__ void fwd16_body(const PFwdArgs& a, const GridMap& map, Fwd16Lds<NIT>& lds) {
+  auto& red = lds.red;
+  auto& zxs = lds.zxs;
+  auto& rbuf = lds.rbuf;
+  const WgCoord wg = wg_coord(map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
   const PFwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
@@ -683,7 +779,7 @@ __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
   const bool local = group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit);
 
   constexpr unsigned kParked = 0x7ff00000u;
-  const unsigned g_bytes = (unsigned)B * 4u * n * 4u, y_bytes = (unsigned)B * d.ldy * 2u, s_bytes = (unsigned)B * n * 4u;
+  const unsigned g_bytes = in_sgpr((unsigned)B * 4u * n * 4u), y_bytes = in_sgpr((unsigned)B * d.ldy * 2u), s_bytes = in_sgpr((unsigned)B * n * 4u);
   // offsets of row r8 inside a frame; row r8 + 8 lies a wave-uniform distance behind it (a row of the second half
   // that exists implies its partner in the first half does), which keeps four registers free
   const unsigned b0 = (unsigned)(rt * 16 + r8);
@@ -994,15 +1090,29 @@ constexpr float kPartScale = 1.f / 4294967296.f;          // 2^-32
 // (sigma - 1) & 1; alternates between consecutive uses of a slot and is 1 at the first, so zero-filled slots look unwritten
 __device__ __forceinline__ unsigned part_tag(int sigma) { return ((((unsigned)sigma - 1u) >> 1) & 1u) ^ 1u; }
 
-template <int NPW, int NCT>                               // n <= 128 * NPW (producers per wavefront) and n <= 64 * NCT (its output column tiles)
-__global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
-  __shared__ float red[8][8][33];                        // [wavefront, producer of the pair][row][output]
-  __shared__ __attribute__((aligned(16))) unsigned short zb[8][136];
-  constexpr int kAhead = NCT == 16 ? 2 : 4;              // frames whose inputs are fetched together (fetch_in below)
+template <int NCT, bool PACKED> struct Bwd8Lds {
+  static constexpr int kAhead = NCT == 16 ? 2 : 4;       // frames whose inputs are fetched together (fetch_in below)
   static_assert(kAhead >= 2, "a step reads its inputs before its poll: they have to be there from the step before");
+  alignas(16) float red[8][8][33];                       // [wavefront, producer of the pair][row][output]
+  alignas(16) unsigned short zb[8][136];
   // inputs of the next frames, [frame][wavefront][...][lane or row, unit]: a wavefront reads back what it asked for
-  __shared__ float in_g[2 * kAhead][4][2][4][32], in_c[2 * kAhead][4][64];
-  __shared__ unsigned in_y[2 * kAhead][4][64];
+  alignas(16) float in_g[2 * kAhead][4][2][4][32];
+  alignas(16) float in_c[2 * kAhead][4][64];
+  alignas(16) unsigned in_y[2 * kAhead][4][64];
+  alignas(16) float in_n[PACKED ? 2 * kAhead : 1][4][64];
+  alignas(16) unsigned tab[RowTable<PACKED>::kSteps][8];
+  float dbred[8][129];
+};
+template <int NPW, int NCT, bool PACKED>                  // n <= 128 * NPW (producers per wavefront) and n <= 64 * NCT (its output column tiles)
+__device__ __forceinline__ void bwd8_body(const PBwdArgs& a, Bwd8Lds<NCT, PACKED>& lds) {
+  constexpr int kAhead = Bwd8Lds<NCT, PACKED>::kAhead;
+  auto& red = lds.red;
+  auto& zb = lds.zb;
+  auto& in_g = lds.in_g;
+  auto& in_c = lds.in_c;
+  auto& in_y = lds.in_y;
+  auto& in_n = lds.in_n;
+  auto& tab_lds = lds.tab;
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
@@ -1029,12 +1139,15 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   const int sparse = (lane & 8) ? kSparseHigh : kSparseLow;
 
   const int r8 = tid >> 5, u = tid & 31;                 // pointwise pair of this thread
-  const int b = R * 8 + r8, j = J * 32 + u;
+  const int b = PACKED ? 0 : R * 8 + r8, j = J * 32 + u;
   const bool active = b < B && j < n;
+  const RowTable<PACKED> tab = {tab_lds, PACKED ? d.tab + (long)wg.rt * a.tab_steps * 8 : nullptr, PACKED ? __builtin_amdgcn_readfirstlane(a.steps[wg.rt]) : T, r8};
+  const int Tn = tab.steps;                                // backward steps
+  unsigned e_prev = 0u;                                    // (rows one behind the other) the step before
   float Dh = 0.f, Dc = 0.f;
   float dbsum[4] = {0.f, 0.f, 0.f, 0.f};
   int L = 0;
-  if (active) {
+  if (active && !PACKED) {
     if (d.dhT) Dh = d.dhT[(long)b * n + j];
     if (d.dcT) Dc = d.dcT[(long)b * n + j];
     L = clamp_len(a.lens, b, T);
@@ -1054,13 +1167,14 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   const unsigned y_off = active ? ((unsigned)b * d.lddy + j) * 2u : kParked;
   // (a frame that does not exist: the lanes that would read it are parked, whatever the address)
   auto frame_of = [&](const void* base, int t, unsigned bytes) {
+    if constexpr (PACKED) return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes * (unsigned)T, kBufFlags);      // (see the forward kernel)
     return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (long long)t * bytes), 0, bytes, kBufFlags);
   };
   const int zq = (lane >> 3) & 3, zu = J * 32 + 4 * (lane & 7);
   const int L_row = b < B && zu < n ? clamp_len(a.lens, b, T) : 0;
   const unsigned gq_off = ((unsigned)b * 4u * n + (unsigned)zq * n + zu) * 4u;
   auto lds_addr = [](const void* p) { return __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p); };
-  const unsigned lds_g = lds_addr(&in_g[0][wave][0][0][0]), lds_c = lds_addr(&in_c[0][wave][0]), lds_y = lds_addr(&in_y[0][wave][0]);
+  const unsigned lds_g = lds_addr(&in_g[0][wave][0][0][0]), lds_c = lds_addr(&in_c[0][wave][0]), lds_y = lds_addr(&in_y[0][wave][0]), lds_n = lds_addr(&in_n[0][wave][0]);
   // Frames of backward steps sigma, sigma + 1, ... (sigma = T-1-tau) into places sigma % (2 kAhead), ...; t < 0 and t >= L as one
   // comparison.  The cell state entering frame t is the state leaving the frame before it in processing order, which is the NEXT
   // backward step's frame: that step takes its c_new from here instead of loading it again.  So the value is also fetched where
@@ -1069,18 +1183,36 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   const int t_first = d.rev ? 0 : T - 1, dt = d.rev ? 1 : -1;          // frame of backward step sigma: t_first + dt * sigma
   const unsigned L_prev = (unsigned)(d.rev ? min(L, T - 1) : L);
   // (assembly: the compiler makes every later LDS read wait for all loads of this kind that it knows to be in flight)
+  const unsigned before_off = (unsigned)dt * s_bytes;      // from a frame's cell state to that of the frame before it
+  unsigned e_ahead[kAhead] = {};                           // table words of the frames that are fetched next
+  auto look_ahead = [&](int sigma, int now) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < kAhead; ++f) e_ahead[f] = tab.at(sigma + f, now);
+  };
   auto fetch_in = [&](int sigma) __attribute__((always_inline)) {
 #pragma unroll
     for (int f = 0; f < kAhead; ++f) {
       const unsigned place = (unsigned)(sigma + f) & (2 * kAhead - 1);
+      if constexpr (PACKED) {
+        const unsigned e = e_ahead[f];
+        const bool on = (e & kRowValid) != 0u, before = on && !(e & kRowLast), first = on && (e & kRowFirst) != 0u;
+        const unsigned so = frame_off(e, 4u * n) + 4u * j;
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds_g + place * (unsigned)sizeof(in_g[0])), "v"(on && zu < n ? frame_off(e, 16u * n) + ((unsigned)zq * n + zu) * 4u : kParked), "s"(frame_of(d.gates, 0, g_bytes)) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(lds_c + place * (unsigned)sizeof(in_c[0])), "v"(before && active ? so + before_off : kParked), "s"(frame_of(d.cs, 0, s_bytes)) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(lds_n + place * (unsigned)sizeof(in_n[0])), "v"(first && active ? so : kParked), "s"(frame_of(d.cs, 0, s_bytes)) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ushort %1, %2, 0 offen nt lds" ::"s"(lds_y + place * (unsigned)sizeof(in_y[0])), "v"(on && active ? frame_off(e, 2u * (unsigned)d.lddy) + 2u * j : kParked), "s"(frame_of(d.dy, 0, y_bytes)) : "memory");
+        continue;
+      }
       const int t = t_first + dt * (sigma + f), tp = t + dt;
       asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds_g + place * (unsigned)sizeof(in_g[0])), "v"((unsigned)t < (unsigned)L_row ? gq_off : kParked), "s"(frame_of(d.gates, t, g_bytes)) : "memory");
       asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(lds_c + place * (unsigned)sizeof(in_c[0])), "v"((unsigned)(d.rev ? t : tp) < L_prev ? s_off : kParked), "s"(frame_of(d.cs, tp, s_bytes)) : "memory");
       asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_ushort %1, %2, 0 offen nt lds" ::"s"(lds_y + place * (unsigned)sizeof(in_y[0])), "v"((unsigned)t < (unsigned)L ? y_off : kParked), "s"(frame_of(d.dy, t, y_bytes)) : "memory");
     }
   };
+  tab.load(0);
+  look_ahead(0, 0);
   fetch_in(0);
-  const float c_first = active && d.c0 ? d.c0[(long)b * n + j] : 0.f;
+  const float c_first = !PACKED && active && d.c0 ? d.c0[(long)b * n + j] : 0.f;
   // cell state leaving the next step's frame: of the first one loaded as such
   float c_new = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(frame_of(d.cs, t_first, s_bytes), t_first < L ? s_off : kParked, 0u, 2));
   // entries of DZ, which this thread stores: a pointer that moves by one frame per step
@@ -1112,11 +1244,12 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
     PROF_MARK(4)
     // (told to be wave-uniform: computed next to per-lane uses of tau it ends up in vector registers, and a buffer
     // descriptor derived from it is then applied lane by lane in a loop)
-    const int sigma = __builtin_amdgcn_readfirstlane(T - 1 - tau);
+    const int sigma = __builtin_amdgcn_readfirstlane(Tn - 1 - tau);
+    const unsigned e = pointwise_c ? tab.at(sigma, sigma) : 0u;
     const int t = d.rev ? T - 1 - tau : tau;
     const int t_next = d.rev ? t - 1 : t + 1;
     constexpr bool pointwise = decltype(pointwise_c)::value;
-    const bool valid = pointwise && active && t < L;
+    const bool valid = pointwise && active && (PACKED ? (e & kRowValid) != 0u : t < L);
 
     // The gate gradients of a valid frame, dh = dy + Dh (recurrent_dev.h has the plain form):
     //   dc = Dc + dh go (1 - tanh(c)^2), Dc' = dc gf, dz = (dc gg gi (1-gi), dc c_prev gf (1-gf), dc gi (1-gg^2), dh tanh(c) go (1-go)).
@@ -1128,7 +1261,13 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
       in.gi = in_g[place][wave][lane >> 5][0][u]; in.gf = in_g[place][wave][lane >> 5][1][u];
       in.gg = in_g[place][wave][lane >> 5][2][u]; in.go = in_g[place][wave][lane >> 5][3][u];
       in.c_new = c_new; in.c_prev = in_c[place][wave][lane]; in.dy_bits = in_y[place][wave][lane];
-      if (tau == 0) in.c_prev = c_first;
+      if constexpr (PACKED) {
+        if ((sigma & (kAhead - 1)) == 0) look_ahead(sigma + kAhead, sigma);
+        if (e & kRowFirst) in.c_new = in_n[place][wave][lane];
+        if ((e & kRowLast) && active && d.c0) in.c_prev = rare_load(&d.c0[(long)((e & kRowFrame) % (unsigned)B) * n + j]);
+      } else if (tau == 0) {
+        in.c_prev = c_first;
+      }
       c_new = in.c_prev;
     };
     // Frames are asked for a step earlier than they could be: what a step computes from its inputs alone then runs while its poll is
@@ -1246,11 +1385,18 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
 #pragma unroll
       for (int v = 0; v < 8; ++v) red[2 * wave + chalf][v][ccol] = ps[v];
       __syncthreads();
-      if (active && t_next < L) {
+      if (active && (PACKED || t_next < L)) {
         float sum = 0.f;
 #pragma unroll
         for (int k = 0; k < 8; ++k) sum += red[k][r8][u];
         Dh = sum * (1.f / kPartScale);                     // the partial sums travel scaled (see above)
+        if constexpr (PACKED) {
+          if ((e_prev & kRowLast) && (d.dh0 || d.dc0)) {   // the gradients that leave the row that ended
+            const long s0 = (long)((e_prev & kRowFrame) % (unsigned)B) * n + j;
+            if (d.dh0) d.dh0[s0] = Dh;
+            if (d.dc0) d.dc0[s0] = Dc;
+          }
+        }
       }
     } else {
       __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
@@ -1260,6 +1406,17 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
       fetch_next();
     }
     if (pointwise) {
+      if constexpr (PACKED) {
+        if ((e & kRowFirst) && active) {
+          Dh = 0.f; Dc = 0.f;
+          if (d.dhT || d.dcT) {
+            const long s0 = (long)((e & kRowFrame) % (unsigned)B) * n + j;
+            if (d.dhT) Dh = rare_load(&d.dhT[s0]);
+            if (d.dcT) Dc = rare_load(&d.dcT[s0]);
+          }
+        }
+        e_prev = e;
+      }
       float dz[4] = {0.f, 0.f, 0.f, 0.f};
       if (valid) {
         const float dh = bf_bits2f((unsigned short)in.dy_bits) + Dh, dc = Dc + dh * f_c;
@@ -1311,11 +1468,18 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
 #pragma unroll
       for (int o = kMma - 3 - kPubLag; o < kOps; ++o) pub_step(o);
       PROF_MARK(1)
-      if (active) {
+      if constexpr (PACKED) {
+        const __amdgpu_buffer_rsrc_t rz = frame_of(d.DZ, 0, g_bytes / 2u);
+        const unsigned zo = valid ? frame_off(e, 8u * n) + 2u * j : kParked;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) st_stream(dz_p + q * n, bits[q]);
+        for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b16(bits[q], rz, zo, (unsigned)q * 2u * n, 2);
+      } else {
+        if (active) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) st_stream(dz_p + q * n, bits[q]);
+        }
+        dz_p += g_step;
       }
-      dz_p += g_step;
       PROF_MARK(3)
     }
   };
@@ -1325,20 +1489,32 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
   auto all_steps = [&](auto local_c) __attribute__((always_inline)) {
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
-    step(T - 1, local_c, no, yes);                         // (T >= 2)
-    int tau = T - 2;
-    for (; tau >= 0; tau = __builtin_amdgcn_readfirstlane(tau) - 1) step(tau, local_c, yes, yes);
-    step(-1, local_c, yes, no);
+    if (Tn > 0) {
+      step(Tn - 1, local_c, no, yes);
+      for (int tau = Tn - 2; tau >= 0; tau = __builtin_amdgcn_readfirstlane(tau) - 1) {
+        if (PACKED && ((Tn - 1 - tau) & (kTabSteps - 1)) == 0) tab.load(Tn - 1 - tau);
+        step(tau, local_c, yes, yes);
+      }
+      step(-1, local_c, yes, no);
+    }
   };
   if (local) all_steps(std::true_type{});
   else all_steps(std::false_type{});
   PROF_DUMP("bwdp", T)
-  if (active) {
+  if constexpr (PACKED) {
+    if (wg.rt == 0 && active && (d.dh0 || d.dc0))          // rows without frames
+      for (int bb = r8; bb < B; bb += 8)
+        if (clamp_len(a.lens, bb, T) == 0) {
+          const long s0 = (long)bb * n + j;
+          if (d.dh0) d.dh0[s0] = d.dhT ? d.dhT[s0] : 0.f;
+          if (d.dc0) d.dc0[s0] = d.dcT ? d.dcT[s0] : 0.f;
+        }
+  } else if (active) {
     if (d.dh0) d.dh0[(long)b * n + j] = Dh;
     if (d.dc0) d.dc0[(long)b * n + j] = Dc;
   }
   if (d.dbpart) {                       // bias gradient: sum this work-group's 8 rows, one slice per row group
-    __shared__ float dbred[8][129];
+    auto& dbred = lds.dbred;
 #pragma unroll
     for (int q = 0; q < 4; ++q) dbred[r8][q * 32 + u] = dbsum[q];
     __syncthreads();
@@ -1357,15 +1533,25 @@ __global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
 // doing real work; a (producer, destination tile) block is 1 KiB -
 // [32 outputs][4 row quarters] x 8 bytes -, a consumer's load covers one producer (lane = output lane/2, row half lane%2),
 // so a wavefront reads eight loads per step instead of four, and the pointwise part runs twice.
+struct Bwd16Lds {
+  static constexpr int kAhead = 2;                       // frames whose inputs are fetched together (see the 8-row kernel)
+  alignas(16) float red[4][16][33];                      // [wavefront][row][output]
+  alignas(16) unsigned short zb[16][136];
+  alignas(16) float in_g[2 * kAhead][2][4][2][4][32];    // [frame][row half][wavefront]...
+  alignas(16) float in_c[2 * kAhead][2][4][64];
+  alignas(16) unsigned in_y[2 * kAhead][2][4][64];
+  float dbred[8][129];
+};
 template <int NPW, int NCT>                               // n <= 128 * NPW (producers per wavefront) and n <= 64 * NCT (its output column tiles)
-__global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
-  __shared__ float red[4][16][33];                       // [wavefront][row][output]
-  __shared__ __attribute__((aligned(16))) unsigned short zb[16][136];
-  constexpr int kAhead = 2;                              // frames whose inputs are fetched together (see the 8-row kernel)
-  __shared__ float in_g[2 * kAhead][2][4][2][4][32], in_c[2 * kAhead][2][4][64];     // [frame][row half][wavefront]...
-  __shared__ unsigned in_y[2 * kAhead][2][4][64];
+__device__ __forceinline__ void bwd16_body(const PBwdArgs& a, const GridMap& map, Bwd16Lds& lds) {
+  constexpr int kAhead = Bwd16Lds::kAhead;
+  auto& red = lds.red;
+  auto& zb = lds.zb;
+  auto& in_g = lds.in_g;
+  auto& in_c = lds.in_c;
+  auto& in_y = lds.in_y;
   constexpr int kBlock = 2 * kPartBytes;                 // one (producer, destination tile)
-  const WgCoord wg = wg_coord(a.map, a.ndir);
+  const WgCoord wg = wg_coord(map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
   const PBwdDir d = a.d[wg.dir];       // a copy: fields read through a reference are fetched again in every time step
@@ -1401,7 +1587,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
   }
   // What the gate gradients of a frame need, and how it is fetched: see the 8-row kernel.
   constexpr unsigned kParked = 0x7ff00000u;
-  const unsigned g_bytes = (unsigned)B * 4u * n * 4u, s_bytes = (unsigned)B * n * 4u, y_bytes = (unsigned)B * d.lddy * 2u;
+  const unsigned g_bytes = in_sgpr((unsigned)B * 4u * n * 4u), s_bytes = in_sgpr((unsigned)B * n * 4u), y_bytes = in_sgpr((unsigned)B * d.lddy * 2u);
   // offsets of row r8 inside a frame; row r8 + 8 lies a wave-uniform distance behind it (and exists only if row r8 does)
   const unsigned g_off0 = active[0] ? ((unsigned)b0 * 4u * n + j) * 4u : kParked;
   const unsigned s_off0 = active[0] ? ((unsigned)b0 * n + j) * 4u : kParked;
@@ -1726,7 +1912,7 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
       if (d.dc0) d.dc0[(long)(b0 + 8 * k) * n + j] = Dc[k];
     }
   if (d.dbpart) {                       // bias gradient: sum this work-group's 16 rows into the first of its two slices (the other stays zero)
-    __shared__ float dbred[8][129];
+    auto& dbred = lds.dbred;
 #pragma unroll
     for (int q = 0; q < 4; ++q) dbred[r8][q * 32 + u] = dbsum[q];
     __syncthreads();
@@ -1738,6 +1924,44 @@ __global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
       if (jj < n) d.dbpart[(long)2 * R * 4 * n + q * n + jj] = sum;
     }
   }
+}
+
+// The kernels.  Fewer rows than a launch holds: every row has a place of its own (8 rows a group).  More: 16 rows a group, or, for n
+// where the choice below is offered, rows one behind the other in the places of the 8-row form.
+template <int NL>
+__global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
+  __shared__ Fwd8Lds<false> lds;
+  fwd8_body<NL, false>(a, lds);
+}
+template <int NIT>
+__global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
+  __shared__ Fwd16Lds<NIT> lds;
+  fwd16_body<NIT>(a, a.map, lds);
+}
+template <int NPW, int NCT>
+__global__ __launch_bounds__(256) void persist_bwdp_kernel(PBwdArgs a) {
+  __shared__ Bwd8Lds<NCT, false> lds;
+  bwd8_body<NPW, NCT, false>(a, lds);
+}
+template <int NPW, int NCT>
+__global__ __launch_bounds__(256) void persist_bwdp16_kernel(PBwdArgs a) {
+  __shared__ Bwd16Lds lds;
+  bwd16_body<NPW, NCT>(a, a.map, lds);
+}
+__device__ __forceinline__ GridMap rows16_map(GridMap m, int B) {
+  m.nrow = (B + 15) / 16;                                  // (no more groups than the grid is for: persist_pack_slots)
+  return m;
+}
+// The lengths decide (rows_pay), and they are on the device: the set-up launch writes the decision with the table.
+__global__ __launch_bounds__(256) void persist_fwd_rows_kernel(PFwdArgs a) {
+  __shared__ union { Fwd8Lds<true> r8; Fwd16Lds<8> r16; } lds;
+  if (__builtin_amdgcn_readfirstlane(a.steps[0]) >= 0) fwd8_body<4, true>(a, lds.r8);
+  else fwd16_body<8>(a, rows16_map(a.map, a.B), lds.r16);
+}
+__global__ __launch_bounds__(256) void persist_bwd_rows_kernel(PBwdArgs a) {
+  __shared__ union { Bwd8Lds<16, true> r8; Bwd16Lds r16; } lds;
+  if (__builtin_amdgcn_readfirstlane(a.steps[0]) >= 0) bwd8_body<8, 16, true>(a, lds.r8);
+  else bwd16_body<8, 16>(a, rows16_map(a.map, a.B), lds.r16);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2311,7 +2535,7 @@ __device__ __forceinline__ void pack_wh_fwd_ll_body(long idx, const bf16_t* W, u
   if (paired) { set = rest & 1; rest >>= 1; }
   const int kc = rest % nkc; rest /= nkc;
   const int q = rest & 3; rest >>= 2;
-  const int ntile = paired ? (n + 31) / 32 : (n + 15) / 16;
+  const int ntile = ((n + 31) / 32) << (paired ? 0 : 1);   // (as many bytes either way)
   const int tile = rest % ntile, dir = rest / ntile;
   const bf16_t* Wd = W + (long)dir * n * 4 * n;
   bf16_t v[8];
@@ -2382,15 +2606,136 @@ __device__ __forceinline__ void pack_state_ll_body(long idx, uint4* ring0, uint4
 // blocks [first_pack, first_ring) bring W_h into the kernel's order (forward: ring order; backward: the partial-sum kernel's),
 // blocks [first_ring, first_map) (forward only) write the initial ring, blocks from first_map on number the real frames
 // (frame_map_body) when the products that follow go over real frames only.
+// Are rows one behind the other faster?  The same for every wavefront of a launch: about as many steps as the table will have (more than the
+// average place or the longest row only where few long rows are left for the end).
+__device__ __forceinline__ bool rows_pay(const PackRows& p) {
+  int sum = 0, most = 0;
+  for (int b = threadIdx.x & 63; b < p.B; b += 64) {
+    const int L = clamp_len(p.lens, b, p.T);
+    sum += L;
+    most = max(most, L);
+  }
+#pragma unroll
+  for (int o = 32; o; o >>= 1) {
+    sum += __shfl_xor(sum, o);
+    most = max(most, __shfl_xor(most, o));
+  }
+  return __builtin_amdgcn_readfirstlane(max(most, (sum + p.slots - 1) / p.slots)) <= p.max_steps;
+}
+// The table of rows one behind the other (see RowTable), by one block: rows by falling length, each to the place with the fewest
+// frames so far (the first `slots` rows start a place each).  Two tables, frames ascending and descending in time; B <= 256.
+__device__ __forceinline__ void pack_rows_body(const PackRows& p) {
+  __shared__ int len[256], order[256], start[256], place[256], total[256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (!rows_pay(p)) {
+    if (tid == 0) p.steps[0] = -1;
+    return;
+  }
+  if (tid < p.B) len[tid] = clamp_len(p.lens, tid, p.T);
+  __syncthreads();
+  if (tid < p.B) {
+    const int L = len[tid];
+    int rank = 0;
+    for (int b = 0; b < p.B; ++b) rank += len[b] > L || (len[b] == L && b < tid);
+    order[rank] = tid;
+  }
+  __syncthreads();
+  if (wave == 0) {                                         // one wavefront: places (lane + 64 i) and rows (rank lane + 64 i) in registers
+    int sum[4], row[4], rlen[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = lane + 64 * i;
+      row[i] = k < p.B ? order[k] : 0;
+      rlen[i] = k < p.B ? len[row[i]] : 0;
+      sum[i] = k < p.slots ? (k < p.B ? rlen[i] : 0) : 0x7fffff;
+      if (k < p.slots && k < p.B) { place[row[i]] = k; start[row[i]] = 0; }
+    }
+    for (int k = p.slots; k < p.B; ++k) {
+      const int i = k >> 6;
+      const int b = __builtin_amdgcn_readlane(i == 0 ? row[0] : i == 1 ? row[1] : i == 2 ? row[2] : row[3], k & 63);
+      const int L = __builtin_amdgcn_readlane(i == 0 ? rlen[0] : i == 1 ? rlen[1] : i == 2 ? rlen[2] : rlen[3], k & 63);
+      unsigned best = ~0u;                                 // frames so far (below 2^23) and place
+#pragma unroll
+      for (int j = 0; j < 4; ++j) best = min(best, ((unsigned)sum[j] << 8) | (unsigned)(lane + 64 * j));
+      best = min(best, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)best, 0x111, 0xf, 0xf, false));   // row_shr 1, 2, 4, 8; row_bcast 15, 31
+      best = min(best, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)best, 0x112, 0xf, 0xf, false));
+      best = min(best, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)best, 0x114, 0xf, 0xf, false));
+      best = min(best, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)best, 0x118, 0xf, 0xf, false));
+      best = min(best, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)best, 0x142, 0xa, 0xf, false));
+      best = min(best, (unsigned)__builtin_amdgcn_update_dpp(-1, (int)best, 0x143, 0xc, 0xf, false));
+      const unsigned won = (unsigned)__builtin_amdgcn_readlane((int)best, 63);
+      const int q = (int)(won & 255u), before = (int)(won >> 8);
+      if (lane == 0) { place[b] = q; start[b] = before; }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (lane + 64 * j == q) sum[j] += L;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (lane + 64 * j < p.slots) total[lane + 64 * j] = sum[j];
+  }
+  __syncthreads();
+  for (int b = wave; b < p.B; b += 4) {
+    const int L = len[b], q = place[b];
+    const long at = ((long)(q >> 3) * p.tab_steps + start[b]) * 8 + (q & 7);
+    for (int i = lane; i < L; i += 64) {
+      const unsigned flags = kRowValid | (i == 0 ? kRowFirst : 0u) | (i == L - 1 ? kRowLast : 0u);
+      p.up[at + (long)i * 8] = (unsigned)(i * p.B + b) | flags;
+      p.down[at + (long)i * 8] = (unsigned)((L - 1 - i) * p.B + b) | flags;
+    }
+  }
+  for (int q = wave; q < p.slots; q += 4) {                // places that are done before their group is
+    int most = 0;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) most = max(most, total[(q & ~7) + r]);
+    if (lane == 0 && (q & 7) == 0) p.steps[q >> 3] = most;
+    for (int i = total[q] + lane; i < most; i += 64) {
+      const long at = ((long)(q >> 3) * p.tab_steps + i) * 8 + (q & 7);
+      p.up[at] = 0u;
+      p.down[at] = 0u;
+    }
+  }
+}
+// What the loops leave out where rows run one behind the other: y = 0 and the carried cell state at padded frames.  A wavefront takes
+// a frame, 16 bytes a lane where rows allow it.
+struct FillArgs { const int* lens; const int* steps; int T, B, n, ndir; uint16_t* y; float* cs[2]; const float* c0[2]; int rev[2]; int vec_y, vec_c; };
+__global__ __launch_bounds__(256) void fill_padded_kernel(FillArgs a) {
+  const int b = blockIdx.x, t = blockIdx.y * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int L = clamp_len(a.lens, b, a.T);
+  if (t < L || t >= a.T || a.steps[0] < 0) return;
+  const long row = (long)t * a.B + b, width = (long)a.ndir * a.n;         // (n is even: whole words)
+  if (a.vec_y) {
+    uint4* y = (uint4*)(a.y + row * width);
+    for (int i = lane; i < width / 8; i += 64) y[i] = make_uint4(0, 0, 0, 0);
+  } else {
+    unsigned* y = (unsigned*)(a.y + row * width);
+    for (int i = lane; i < width / 2; i += 64) y[i] = 0u;
+  }
+  for (int d = 0; d < a.ndir; ++d) {
+    if (!a.cs[d]) continue;
+    const float* src = !a.rev[d] && L > 0 ? a.cs[d] + ((long)(L - 1) * a.B + b) * a.n : a.c0[d] ? a.c0[d] + (long)b * a.n : nullptr;
+    float* dst = a.cs[d] + row * a.n;
+    if (a.vec_c) {
+      for (int i = lane; i < a.n / 4; i += 64) ((float4*)dst)[i] = src ? ((const float4*)src)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+      for (int i = lane; i < a.n; i += 64) dst[i] = src ? src[i] : 0.f;
+    }
+  }
+}
 struct PrepArgs {
   ZeroRegions z;
   const bf16_t* W; uint4* Wout; int n, nk, nct; long w_total;   // nk: nkc (forward) / ntile2 (backward)
   uint4* ring0; uint4* ring1; long ring_total;
   const int* lens; int T, B; int* fidx; int* count;     // frame map (fidx == NULL: none)
+  PackRows rows;                                          // rows one behind the other: one more block (slots > 0)
   int first_pack, first_ring, first_map, backward, paired;
 };
 __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
-  const int bid = blockIdx.x;
+  if (a.rows.slots > 0 && blockIdx.x == 0) {               // (a chain of its own: the longest, so it starts first)
+    pack_rows_body(a.rows);
+    return;
+  }
+  const int bid = (int)blockIdx.x - (a.rows.slots > 0 ? 1 : 0);
   if (bid < a.first_pack) {
     int k = 0;
 #pragma unroll
@@ -2402,8 +2747,9 @@ __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
     for (size_t i = (size_t)(bid - a.z.first_block[k]) * 256 + threadIdx.x; i < nwords; i += nb * 256) p[i] = 0u;
   } else if (bid < a.first_ring) {
     const long idx = (long)(bid - a.first_pack) * 256 + threadIdx.x;
-    if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, a.paired, a.w_total);
-    else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, a.paired, a.w_total);
+    const int paired = a.rows.slots > 0 ? rows_pay(a.rows) : a.paired;
+    if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, paired, a.w_total);
+    else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, paired, a.w_total);
   } else if (bid < a.first_map) {
     pack_state_ll_body((long)(bid - a.first_ring) * 256 + threadIdx.x, a.ring0, a.ring1, a.ring_total);
   } else {
@@ -2464,8 +2810,9 @@ namespace {
 // kernel form or the per-step path on the untouched state); any other error = a later slab failed after earlier
 // slabs had already advanced the state of their rows, so the call as a whole has failed and nothing may be re-run.
 template <typename K, typename A>
-hipError_t coop_slabs(K kernel, int ntile, int rows_per_group, const A& a, hipStream_t s) {
-  const int per_rt = rows_per_group > 16 ? 1 : 16 / rows_per_group, nrow = cdiv(a.B, rows_per_group);
+hipError_t coop_slabs(K kernel, int ntile, int rows_per_group, const A& a, hipStream_t s, int nrow = 0) {
+  const int per_rt = rows_per_group > 16 ? 1 : 16 / rows_per_group;
+  if (nrow == 0) nrow = cdiv(a.B, rows_per_group);
   const long cap = capacity(kernel);
   const long most = cap / ((long)ntile * a.ndir);                      // row groups per launch
   const int slab = most >= nrow ? nrow : (int)(most / per_rt * per_rt);
@@ -2526,8 +2873,32 @@ int persist_bwd_rows(int B, int n, int ndir) {
   const long t32 = cdiv(n, 32);
   return t32 * cdiv(B, 8) * ndir > capacity(bwd8_for(n)) && t32 * cdiv(B, 16) * ndir <= capacity(bwd16_for(n)) ? 16 : 8;
 }
+// Row places of a launch that may take rows of different lengths one behind the other; 0: not this batch.  Batches that one launch of the
+// 8-row kernels holds have nothing to gain (for n <= 512 that is 128 rows at least); with this, the others are those of a single
+// launch of the 16-row kernels, which the lengths choose from (rows_pay).
+int persist_pack_slots(int T, int B, int n, int ndir, bool backward) {
+  if (n <= 512 || n > 1024 || B > kPackMaxRows || (long)T * B * n * 16 >= 0x7ff00000L) return 0;
+  if ((backward ? persist_bwd_rows(B, n, ndir) : persist_fwd_rows(B, n, ndir)) != 16) return 0;
+  const long per_group = (long)cdiv(n, 32) * ndir;
+  const int groups = (int)std::min((backward ? capacity(persist_bwd_rows_kernel) : capacity(persist_fwd_rows_kernel)) / per_group, (long)kPackMaxSlots / 8);
+  return groups < cdiv(B, 8) && groups >= cdiv(B, 16) ? groups * 8 : 0;
+}
+// Longest table that still pays, against T steps of the 16-row kernels.  n = 1000, 64 rows of 300 frames, both directions, start-up included:
+// forward 777 us there, 863 for 600 steps here (line at 1.75 T with the padded frames' fill); backward 760 and 982 (1.53 T).  Rows of 30 to
+// 300 frames, a table of 330 steps: 711 and 720 us there, 508 and 557 here.
+int pack_max_steps(int T, bool backward) { return (int)((long)T * (backward ? 24 : 27) / 16); }
+int pack_tab_steps(int T, int B, int slots) { return (int)((long)T * B / slots) + T + 1; }      // (fewest frames so far: at most the average, and the row's own)
+hipError_t launch_fill_padded(const int* lens, const int* steps, int T, int B, int n, int ndir, void* y, float* const* cs, const float* const* c0, const int* rev, hipStream_t s) {
+  const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  FillArgs a = {lens, steps, T, B, n, ndir, (uint16_t*)y, {cs[0], cs[1]}, {c0[0], c0[1]}, {rev[0], rev[1]}, 0, 0};
+  a.vec_y = a16(y) && (long)ndir * n % 8 == 0;
+  a.vec_c = n % 4 == 0 && a16(cs[0]) && a16(cs[1]) && a16(c0[0]) && a16(c0[1]);
+  hipLaunchKernelGGL(fill_padded_kernel, dim3(B, cdiv(T, 4)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s) {
   if (!persist_fwd_fits(a)) return hipErrorCooperativeLaunchTooLarge;
+  if (a.slots > 0) return coop_slabs(persist_fwd_rows_kernel, cdiv(a.n, 32), 8, a, s, a.slots / 8);
   const int rows = persist_fwd_rows(a.B, a.n, a.ndir);
   return coop_slabs(rows == 16 ? fwd16_for(a.n) : fwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
@@ -2543,24 +2914,26 @@ bool persist_bwd_fits(const PBwdArgs& a) {
   return a.n <= 1024 && slab_fits(bwd8_for(a.n), cdiv(a.n, 32), 8, cdiv(a.B, 8), a.ndir);
 }
 hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s) {
+  if (a.slots > 0) return coop_slabs(persist_bwd_rows_kernel, cdiv(a.n, 32), 8, a, s, a.slots / 8);
   const int rows = persist_bwd_rows(a.B, a.n, a.ndir);
   return coop_slabs(rows == 16 ? bwd16_for(a.n) : bwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
-                              int nrt, const FrameMapArgs& fm, hipStream_t s) {
+                              int nrt, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
-  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.paired = paired; a.nk = nkc; a.w_total = (long)(ndir * ll_wf_bytes(n, nkc, paired) / 16);
+  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.paired = paired; a.nk = nkc; a.w_total = (long)(ndir * ll_wf_bytes(n, nkc) / 16);
   a.ring0 = ring0; a.ring1 = ring1; a.ring_total = (long)ndir * nrt * nkc * 64 * 2;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.first_map = a.first_ring + cdiv(a.ring_total, 256);
   a.backward = 0;
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
-  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
+  a.rows = rows;
+  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0) + (rows.slots > 0 ? 1 : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, hipStream_t s) {
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
   a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.nct = bwdp_nct(n); a.w_total = (long)ndir * a.nk * 4 * 4 * a.nct * 64;
@@ -2569,7 +2942,8 @@ hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, in
   a.first_map = a.first_ring;
   a.backward = 1; a.paired = paired;
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
-  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
+  a.rows = rows;
+  hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0) + (rows.slots > 0 ? 1 : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 // float ring, before the first step: slot 0 holds zeros that carry the tag of step 0 in every unit, slot 1 is cleared

@@ -53,6 +53,33 @@ def test_eight_row_loops(T, B, n, bidir):
     _layer(T, B, 32, n, bidir, "bf16")
 
 
+@pytest.mark.parametrize("T,B,n,bidir", [(7, 40, 1000, True), (3, 70, 1022, False), (9, 100, 514, True), (5, 200, 520, False), (2, 49, 900, True)])
+def test_rows_one_behind_the_other(T, B, n, bidir):
+    """More rows than places, lengths from 0 to T, every optional state, against the oracle."""
+    _layer(T, B, 24, n, bidir, "bf16")
+
+
+@pytest.mark.parametrize("T,B,n,shortest,longest", [(600, 100, 520, 0, 600), (600, 100, 520, 0, 9), (40, 37, 1024, 0, 0), (30, 64, 1000, 1, 1),
+                                                    (40, 64, 1000, 38, 40), (40, 64, 1000, 26, 40), (40, 33, 1000, 0, 40)])
+def test_rows_one_behind_the_other_per_step(T, B, n, shortest, longest):
+    """More steps than the table in LDS holds, groups that are done at once, batches without any frame, lengths for which neither loop or only
+    the forward one takes rows so: the per-step path's results."""
+    from paper_1805_05225_amd import binding
+    P.Bn = binding
+    rng = np.random.default_rng(n + longest)
+    lens = rng.integers(shortest, longest + 1, B)
+    lens[3] = longest
+    c = P.rnd_case(rng, T, B, 16, n, 2, lens, "bf16", scale=1.0 / np.sqrt(n))
+    f1, g1 = P.run_gpu(c, "bf16", True)
+    f2, g2 = P.run_gpu(c, "bf16", True, flags=binding.FLAG_PER_STEP)
+    for got, ref, names in ((f1, f2, ("y", "c", "hT", "cT")), (g1, g2, ("dx", "dW_x", "dW_h", "db", "dh0", "dc0"))):
+        for k in names:
+            if longest == 0 or float(ref[k].abs().max()) == 0.0:
+                assert torch.equal(got[k], ref[k]), k
+            else:
+                check(k, got[k], host(ref[k]), 1e-2)
+
+
 def _layer(T, B, n_in, n, bidir, dt):
     from paper_1805_05225_amd import binding
     P.Bn = binding
