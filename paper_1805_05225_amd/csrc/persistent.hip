@@ -67,21 +67,17 @@ __device__ __forceinline__ int rot_index(int i, int rot, int nitv) {
   const int j = i + rot;
   return i >= nitv ? i : (j >= nitv ? j - nitv : j);
 }
-struct RingReader {
+template <typename Reader> struct RingReads {           // what readers have in common; where a load lies is the reader's
   __amdgpu_buffer_rsrc_t rs;
-  int rot, nitv;                         // load i of the stream fetches iteration (i + rot) mod nitv of the row tile
-  unsigned voff;                         // byte offset of this lane's first load (parked out of range if the lane is off)
-  unsigned it_bytes;                     // byte distance between consecutive loads of a lane
-  int lim, lim_step;                     // load `it` carries awaited tags for this lane iff lim_step*it < lim
   unsigned tag;                          // the awaited tag as it sits in the upper half of a unit's second dword
   unsigned* err;
   unsigned limit;
 
-  __device__ __forceinline__ int it_of(int i) const { return rot_index(i, rot, nitv); }
+  __device__ __forceinline__ int it_of(int i) const { return static_cast<const Reader*>(this)->it_of(i); }
   __device__ __forceinline__ u32x4 load_it(int it) const {
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, voff + (unsigned)it * it_bytes, 0, kSc1);
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, static_cast<const Reader*>(this)->offset(it), 0, kSc1);
   }
-  __device__ __forceinline__ bool expects(int it) const { return lim_step * it < lim; }   // does this lane's unit of load `it` carry a tag?
+  __device__ __forceinline__ bool expects(int it) const { return static_cast<const Reader*>(this)->expects(it); }   // does this lane's unit of load `it` carry a tag?
   // Tag differences of one load, per lane: a bit above the low half iff one of the lane's two tags is not `tagw >> 16`.
   // Lanes whose units carry no tag (padding inside the ring, chunks past the end) report nothing, whatever they read.
   __device__ __forceinline__ unsigned tag_diff(const u32x4& x, int it, unsigned tagw) const {
@@ -90,7 +86,7 @@ struct RingReader {
   }
   __device__ __forceinline__ unsigned stale_bits(const u32x4& x, int it) const {
     const unsigned d = ((x[1] >> 16) ^ tag) | ((x[3] >> 16) ^ tag);
-    return lim_step * it < lim ? d & (kLLFwdTagBit >> 16) : 0u;
+    return expects(it) ? d & (kLLFwdTagBit >> 16) : 0u;
   }
   // The poll after its first, mostly successful, look (which stays in line: a loop around it costs its branches in every step).
   template <typename L, typename S>
@@ -131,6 +127,15 @@ struct RingReader {
     }
   }
 };
+struct RingReader : RingReads<RingReader> {
+  int rot, nitv;                         // load i of the stream fetches iteration (i + rot) mod nitv of the row tile
+  unsigned voff;                         // byte offset of this lane's first load (parked out of range if the lane is off)
+  unsigned it_bytes;                     // byte distance between consecutive loads of a lane
+  int lim, lim_step;                     // load `it` carries awaited tags for this lane iff lim_step*it < lim
+  __device__ __forceinline__ int it_of(int i) const { return rot_index(i, rot, nitv); }
+  __device__ __forceinline__ unsigned offset(int it) const { return voff + (unsigned)it * it_bytes; }
+  __device__ __forceinline__ bool expects(int it) const { return lim_step * it < lim; }
+};
 
 // `nchunk_valid` counts the 16-lane groups (quarter chunks) that producers write; `lane_on` is false for lanes
 // whose fragment rows belong to another work-group.
@@ -161,6 +166,29 @@ __device__ __forceinline__ RingReader make_reader_half(const uint4* base, int nk
   r.it_bytes = 8192u;
   r.lim = nchunk_valid - g - 4 * wave - 16 * second;
   r.lim_step = 32;
+  r.tag = tag; r.err = err; r.limit = limit;
+  return r;
+}
+// The same with the chunks in the order of the 16-row kernel (load i: its chunks 2i and 2i + 1), so that sums come out as they do there: a
+// batch may take either, and results that differ in the last place pick other frames in a maximum over time further up.
+template <int NL> struct PairReader : RingReads<PairReader<NL>> {
+  unsigned off[NL]; int lim[NL];
+  __device__ __forceinline__ int it_of(int i) const { return i; }
+  __device__ __forceinline__ unsigned offset(int i) const { return off[i]; }
+  __device__ __forceinline__ bool expects(int i) const { return lim[i] > 0; }
+};
+template <int NL>
+__device__ __forceinline__ PairReader<NL> make_reader_pairs(const uint4* base, int nkc, int nchunk_valid, int wave, int lane, int half,
+                                                            unsigned tag, unsigned* err, unsigned limit, int rot) {
+  PairReader<NL> r;
+  const int row = lane & 15, g = lane >> 4, second = row >> 3;
+  r.rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, nkc * 1024, kBufFlags);
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int kc = wave + 4 * rot_index(2 * i + second, rot, (nkc + 3) / 4);
+    r.off[i] = (unsigned)(kc * 1024 + (g * 16 + half * 8 + (row & 7)) * 16);
+    r.lim[i] = nchunk_valid - g - 4 * kc;
+  }
   r.tag = tag; r.err = err; r.limit = limit;
   return r;
 }
@@ -385,13 +413,13 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& ld
   unsigned* err = a.sync;
   bool dead = false;
 
-  const int nitv = (nkc + 7) / 8, rot = tile2 % nitv;
+  const int nitv = PACKED ? (nkc + 3) / 4 : (nkc + 7) / 8, rot = tile2 % nitv;
   // Operands 2p, 2p + 1 of a gate are the two chunks that load p of the stream fetches.  Those of chunks past the end are loaded
   // from a chunk of zeros that the host keeps behind the packed weights.
   u32x4 w4[2 * NL][4][2];
 #pragma unroll
   for (int it = 0; it < 2 * NL; ++it) {
-    const int kc = wave + 4 * (2 * rot_index(it >> 1, rot, nitv) + (it & 1));
+    const int kc = wave + 4 * (PACKED ? rot_index(it, rot, nitv) : 2 * rot_index(it >> 1, rot, nitv) + (it & 1));
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -495,7 +523,11 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& ld
     PROF_MARK(4)
     const uint4* rin = ((tau & 1) ? d.ring1 : d.ring0) + (long)rt * nkc * 64;
     uint4* rout = (tau & 1) ? d.ring0 : d.ring1;
-    RingReader rd = make_reader_half(rin, nkc, ntiles16 * 2, wave, lane, half, ll_fwd_tag((unsigned)tau) << 14, err, a.spin_limit, rot);
+    const auto rd = [&]() __attribute__((always_inline)) {
+      const unsigned tag = ll_fwd_tag((unsigned)tau) << 14;
+      if constexpr (PACKED) return make_reader_pairs<NL>(rin, nkc, ntiles16 * 2, wave, lane, half, tag, err, a.spin_limit, rot);
+      else return make_reader_half(rin, nkc, ntiles16 * 2, wave, lane, half, tag, err, a.spin_limit, rot);
+    }();
     constexpr int zslot = decltype(parity)::value;
     constexpr bool fetches = zslot == kAhead - 1;
     float zx[4];
@@ -609,7 +641,7 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& ld
       PROF_REDO(__popcll(redo))
       const bool asked_again = redo != 0ull;
       if (redo) {
-        rd.fix_up_batch<NL>(redo, dead, use_single);
+        rd.template fix_up_batch<NL>(redo, dead, use_single);
         // (nothing of that is outstanding any more - said with an instruction the compiler takes note of: it cannot tell
         // from the loop's exits, and would make whatever reuses those registers below wait for every load in flight)
         __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0)
