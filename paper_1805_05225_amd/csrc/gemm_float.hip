@@ -1,5 +1,5 @@
-// The hoisted products in float storage (paper Sec. 3: work taken out of the recurrent loop), float in, float out,
-// float MFMA (16x16x4), operands used as they lie in memory:
+// The hoisted products in float storage (paper Sec. 3: work taken out of the recurrent loop), float in, float out, operands used
+// as they lie in memory:
 //     <AK, BK> = <true,  false>   Zx   = X W_x + b      A[M][K] rows of frames,  B[K][N]
 //                <true,  true >   dX   = DZ W_x^T       A[M][K],                 B[N][K]     (summed over `nseg` directions)
 //                <false, false>   dW   = X^T DZ         A[K][M], B[K][N]: a row per frame in both
@@ -10,15 +10,24 @@
 // go from global memory straight into LDS (16 bytes per lane, no staging registers, no LDS store instructions); a
 // wavefront-load writes 1 KiB, lane l its bytes 16 l .., and what a lane fetches is chosen so that the fragment
 // reads meet no bank conflicts:
-//   * k-major operand (a memory row is one k): a float MFMA wants ONE value per lane, element (k-row = lane / 16,
-//     column = lane % 16) of a 4 x 16 block - 16 lanes reading 16 consecutive floats, no transposition needed.  A
+//   * k-major operand (a memory row is one k): a lane wants eight k-rows of ONE column, column = lane % 16 of a
+//     block - 16 lanes reading 16 consecutive floats, no transposition needed.  A
 //     stage is 16 pieces of 1 KiB + 16 bytes; piece p holds k-rows p and p + 16 of the stage (512 bytes each).
 //   * k-contiguous operand (a memory row is a row of the tile): a stage is 128 rows of 128 bytes, unpadded; the
 //     16-byte slot s of row r holds k-chunk s ^ ((r >> 1) & 7).  A lane reads 16 bytes: four consecutive k of its row.
-// Since a k-contiguous lane gets four consecutive k at once, the MFMAs walk k in this order: step s (0..3) of group
-// G (0..1) of a stage multiplies, in its lane group q (0..3), k = 16 G + 4 q + s.  Both operands follow it, so every
-// k meets its partner; a k-major fragment of that step reads k-rows 16 G + s + {0, 4, 8, 12}: four pieces that lie
-// 4 x 1040 bytes apart, 16 banks from one another.
+// The eight k of a fragment's lane group q (0..3) are 16 G + 4 q + s, s (0..3), G (0..1): two reads of 16 bytes, or, k-major, eight of 4
+// (the four lane groups' pieces lie 4 x 1040 bytes apart, 16 banks from one another).  Both operands follow it, so every k meets its partner.
+//
+// The matrix cores multiply bfloat16 sixteen times as fast as float, so a float goes as the sum of three bfloat16 (`split`: its 24 bits,
+// exactly) and a product as the six of their nine products that matter: 16 x 16 x 32 at 6 x 16 cycles instead of 8 x 32.  The five small ones have
+// sums of their own: what the matrix cores cut off where they add to a large sum would otherwise be cut off six times.  Against 64 bits the error is a
+// third of the float MFMA's (sum of K products of normal values, root mean square over that of the result: K = 64 0.5e-7 against 1.4e-7, 620
+// 1.4e-7 against 4.5e-7, 8000 5.7e-7 against 1.6e-6), for positive values half, and as large where single products dominate the
+// sums (lognormal, sigma 3).  What three bfloat16 cannot hold ends as NaN or infinity (infinities, values that round to one) or may be lost
+// (bits below 2^-134: only results below 2^-100 can feel it); a tile where a result says so is computed again with float MFMAs (16x16x4).
+// Bound by the splitting, 320 vector instructions for 96 products, which is therefore cut into the products (without that 4096^3 780 us, 740 with), and then by power
+// (zeros: 620 us).  4096^3: nn 1060 -> 750 us, nt 1025 -> 692, tn 1080 -> 742 (147 to 199 TFLOP/s, where float MFMAs have a peak of 157);
+// 1920 x 8000 x 620 200 -> 141 us.
 // The MFMA takes the B fragment (columns n) as its row operand and the A fragment as its column operand: a lane then
 // holds four CONSECUTIVE n of one row m of C and stores them as 16 bytes.
 // Rows of a k-contiguous A (and of C) may be mapped (`a_rows`, `c_rows`, `m_dev`: the packed list of real frames), as
@@ -39,6 +48,7 @@ constexpr unsigned kParked = 0x7ffffff0u;        // offset outside every descrip
 
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
 struct FArgs {
   const char* A; const char* B; float* C; const float* bias;
@@ -69,6 +79,39 @@ __device__ __forceinline__ u32x4 make_rsrc(const void* base, unsigned bytes) {
   r[2] = __builtin_amdgcn_readfirstlane(bytes);
   r[3] = kBufFlags;
   return r;
+}
+
+// A float is the sum of three bfloat16 (8 + 8 + 8 bits, each rounded to nearest, the last exactly); what the six products leave out is below 2^-25 of theirs.
+struct Parts { u32x4 p[3]; };
+constexpr float kLeast = 0x1p-100f;
+constexpr int kPairA[6] = {0, 0, 1, 1, 0, 2}, kPairB[6] = {0, 1, 0, 1, 2, 0};
+__device__ __forceinline__ Parts split(const float (&x)[8]) {
+  Parts r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float lo = x[2 * e], hi = x[2 * e + 1];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      typedef __attribute__((ext_vector_type(2))) float f32x2;
+      typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+      const unsigned v = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+      r.p[p][e] = v;
+      lo -= __uint_as_float(v << 16);
+      hi -= __uint_as_float(v & 0xffff0000u);
+    }
+  }
+  return r;
+}
+__device__ __forceinline__ f32x4 mma(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+template <int N, int V> __device__ __forceinline__ void interleave() {       // N times a product and V vector instructions
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x2, V, 0);
+  }
 }
 
 template <bool AK, bool BK>
@@ -177,73 +220,123 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
     fa_base[G] = AK ? lds + (wm * 64 + i16) * 128 + (((4 * G + q) ^ sw) * 16) : lds + 4 * q * kPiece + (wm * 64 + i16) * 4 + G * 512;
     fb_base[G] = BK ? lds + kOp + (wn * 64 + i16) * 128 + (((4 * G + q) ^ sw) * 16) : lds + kOp + 4 * q * kPiece + (wn * 64 + i16) * 4 + G * 512;
   }
-  f32x4 acc[4][4];                                               // [m block][n block]; element v: n = 4 q + v
+  f32x4 acc[4][4], low[4][4];                                    // [m block][n block]; element v: n = 4 q + v
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  // Fragments.  A k-contiguous operand is read a group at a time (16 bytes per lane and block = the four steps of the
-  // group), a k-major one a step at a time (4 bytes per lane and block); both are read ahead of their use, a piece
-  // behind each step's MFMAs, so that only the first read of a stage is waited for.
-  float fa[2][4][4], fb[2][4][4];                                // k-contiguous: [group][block][step]; k-major: [step % 2][block][0]
-  auto read_a = [&](int buf, int e, int blk) __attribute__((always_inline)) {       // e = 4 G + s
-    const int G = e >> 2, sx = e & 3;
-    if (AK) {
-      const float4 v = *(const float4*)(fa_base[G] + buf * kStage + blk * 2048);
-      fa[G][blk][0] = v.x; fa[G][blk][1] = v.y; fa[G][blk][2] = v.z; fa[G][blk][3] = v.w;
-    } else {
-      fa[e & 1][blk][0] = *(const float*)(fa_base[G] + buf * kStage + sx * kPiece + blk * 64);
+    for (int j = 0; j < 4; ++j) acc[i][j] = low[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  int4 rows_next;
+  auto stages = [&](auto&& products) __attribute__((always_inline)) {
+    rows_next = lookup(0);
+    if (total > 0) {
+      issue(0, 0, rows_next);
+      rows_next = lookup(1);
+    }
+    for (int it = 0; it < total; ++it) {
+      const int cur = it & 1;
+      __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0): this wavefront's loads of stage `it` (and the look-up) are in
+      __syncthreads();                             // everybody's are, and everybody has finished reading the other buffer
+      if (it + 1 < total) issue(it + 1, cur ^ 1, rows_next);
+      rows_next = lookup(it + 2);
+      // (fenced: left alone, the compiler moves each read down to its first use and waits for it there)
+      __builtin_amdgcn_sched_barrier(0);
+      products(cur);
     }
   };
-  auto read_b = [&](int buf, int e, int blk) __attribute__((always_inline)) {
-    const int G = e >> 2, sx = e & 3;
-    if (BK) {
-      const float4 v = *(const float4*)(fb_base[G] + buf * kStage + blk * 2048);
-      fb[G][blk][0] = v.x; fb[G][blk][1] = v.y; fb[G][blk][2] = v.z; fb[G][blk][3] = v.w;
-    } else {
-      fb[e & 1][blk][0] = *(const float*)(fb_base[G] + buf * kStage + sx * kPiece + blk * 64);
-    }
-  };
-
-  int4 rows_next = lookup(0);
-  if (total > 0) {
-    issue(0, 0, rows_next);
-    rows_next = lookup(1);
-  }
-  for (int it = 0; it < total; ++it) {
-    const int cur = it & 1;
-    __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0) lgkmcnt(0): this wavefront's loads of stage `it` (and the look-up) are in
-    __syncthreads();                               // everybody's are, and everybody has finished reading the other buffer
-    if (it + 1 < total) issue(it + 1, cur ^ 1, rows_next);
-    rows_next = lookup(it + 2);
-    // (fenced: left alone, the compiler moves each read down to its first use and waits for it there)
+  stages([&](int cur) __attribute__((always_inline)) {
+    // the eight k of a lane's fragment: k = 16 G + 4 q + s, element 4 G + s
+    auto raw_a = [&](int blk, float (&x)[8]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int G = 0; G < 2; ++G) {
+        if (AK) {
+          const float4 v = *(const float4*)(fa_base[G] + cur * kStage + blk * 2048);
+          x[4 * G] = v.x; x[4 * G + 1] = v.y; x[4 * G + 2] = v.z; x[4 * G + 3] = v.w;
+        } else {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[4 * G + s] = *(const float*)(fa_base[G] + cur * kStage + s * kPiece + blk * 64);
+        }
+      }
+    };
+    auto raw_b = [&](int blk, float (&x)[8]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int G = 0; G < 2; ++G) {
+        if (BK) {
+          const float4 v = *(const float4*)(fb_base[G] + cur * kStage + blk * 2048);
+          x[4 * G] = v.x; x[4 * G + 1] = v.y; x[4 * G + 2] = v.z; x[4 * G + 3] = v.w;
+        } else {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[4 * G + s] = *(const float*)(fb_base[G] + cur * kStage + s * kPiece + blk * 64);
+        }
+      }
+    };
+    // Operands are split two products ahead, between the products: a split is 40 instructions of 4 cycles, six products are 96 cycles.
+    Parts a[4], b[2];
+    float x[2][8];
+    auto pair = [&](int m, int n) __attribute__((always_inline)) {
+#pragma unroll
+      for (int o = 5; o >= 0; --o) {                       // (the smallest first)
+        f32x4& to = o == 0 ? acc[m][n] : low[m][n];
+        to = mma(b[n & 1].p[kPairB[o]], a[m].p[kPairA[o]], to);
+      }
+    };
+    raw_a(0, x[0]);
+    raw_b(0, x[1]);
+    a[0] = split(x[0]);
+    raw_a(1, x[0]);
+    b[0] = split(x[1]);
+    raw_a(2, x[1]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk) {
-      read_a(cur, 0, blk);
-      read_b(cur, 0, blk);
+    for (int m = 0; m < 4; ++m) {
+      pair(m, 0);
+      Parts& to = m < 3 ? a[m + 1] : b[1];
+      to = split(x[m & 1]);
+      if (m == 0) raw_a(3, x[0]);
+      else raw_b(m, x[m & 1]);
+      interleave<6, 7>();
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      __builtin_amdgcn_sched_barrier(0);
-      // k-major: the next step, all four blocks; k-contiguous: during group 0, block e of group 1
+    for (int n = 1; n < 4; ++n) {
 #pragma unroll
-      for (int blk = 0; blk < 4; ++blk) {
-        if (!AK && e + 1 < 8) read_a(cur, e + 1, blk);
-        if (!BK && e + 1 < 8) read_b(cur, e + 1, blk);
+      for (int m = 0; m < 4; ++m) pair(m, n);
+      if (n < 3) b[(n + 1) & 1] = split(x[(n + 1) & 1]);
+      interleave<24, 2>();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  });
+  bool odd = false;                                              // (see above: NaN, infinity, or too small to be sure of)
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        acc[m][n][v] += low[m][n][v];
+        const float size = __builtin_fabsf(acc[m][n][v]);
+        odd |= !(size < __builtin_inff()) | (size < kLeast && size != 0.f);
       }
-      if (AK && e < 4) read_a(cur, 4, e);
-      if (BK && e < 4) read_b(cur, 4, e);
-      __builtin_amdgcn_sched_barrier(0);
+  if (__builtin_expect(__syncthreads_or(odd), 0)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float av = AK ? fa[e >> 2][i][e & 3] : fa[e & 1][i][0];
-          const float bv = BK ? fb[e >> 2][j][e & 3] : fb[e & 1][j][0];
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv, av, acc[i][j], 0, 0, 0);
+      for (int n = 0; n < 4; ++n) acc[m][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    stages([&](int cur) __attribute__((always_inline)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {                        // e = 4 G + s
+        const int G = e >> 2, sx = e & 3;
+        float fa[4], fb[4];
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk) {
+          fa[blk] = *(const float*)(fa_base[G] + cur * kStage + (AK ? sx * 4 + blk * 2048 : sx * kPiece + blk * 64));
+          fb[blk] = *(const float*)(fb_base[G] + cur * kStage + (BK ? sx * 4 + blk * 2048 : sx * kPiece + blk * 64));
         }
-    }
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+          for (int n = 0; n < 4; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[n], fa[m], acc[m][n], 0, 0, 0);
+      }
+    });
   }
 
   // Epilogue: lane l holds C[m = block_m * 16 + l % 16][n = block_n * 16 + 4 (l / 16) .. + 3].
@@ -293,9 +386,10 @@ __global__ __launch_bounds__(256, 2) void gemm_float_tn_kernel(FArgs g) { gemm_f
 
 }  // namespace
 
-// K ranges for a product with few 128 x 128 tiles.  A tile's stage of 32 k is 1.75 us of a compute unit's matrix cores (2.6 when the
-// unit has a single work-group and nothing hides its waits), work-groups come in whole rounds of 256 units, and the parts are
-// written and read once.  (Config 2, dW_x: 320 tiles leave 3 of 8 units idle in the second round; dW of 64 units over 10240 frames
+// K ranges for a product with few 128 x 128 tiles.  A tile's stage of 32 k is taken as 1.75 us of a compute unit's matrix cores (2.6 when the
+// unit has a single work-group and nothing hides its waits; measured 1.46 and 1.65 now, and with 1.25 and 1.95 here eight networks'
+// products took the same time within 1 %), work-groups come in whole rounds of 256 units, and the parts are
+// written and read once.  (Two directions, 620 inputs, 1000 units, dW_x: 320 tiles leave 3 of 8 units idle in the second round; dW of 64 units over 10240 frames
 // was 4 tiles on 4 units, 1.4 ms, and is now 0.04.)
 // `frames`: rows are frames, padded ones included: judged with 0.6 of the rows real (lengths spread evenly from a fifth of the longest on) as
 // well as with all.
@@ -314,7 +408,7 @@ int gemm_float_ranges(long M, long N, long K, int nz, int nseg, bool frames) {
   double best_us = 1e30;
   for (int r = 1; r <= 64 && (r == 1 || stages / r >= 4); ++r) {
     double us = 0.5 * (loop_us(tiles, r) + loop_us(fewer, r)) + (r > 1 ? 6.0 + (double)r * M * N * nz * 8 / 4.5e6 : 0.0);
-    if (frames && r == 8) us *= 0.75;    // a range per XCD, operands from its own L2: dX of config 2 218 us, with six ranges 327
+    if (frames && r == 8) us *= 0.75;    // a range per XCD, operands from its own L2: dX of two directions, 620 inputs, 1000 units 218 us, with six ranges 327
     if (us < 0.95 * best_us) { best = r; best_us = us; }
   }
   return best;

@@ -104,6 +104,55 @@ def test_gemm_layouts(dt, M, N, K):
         check("NT->bf16", C, ref.numpy(), 1e-2)
 
 
+def _float_forms(A, B):
+    M, K = A.shape
+    kw = dict(M=M, N=B.shape[1], K=K)
+    At, Bt = A.t().contiguous(), B.t().contiguous()
+    return {"NN": Bn.gemm(A, B, a_kcontig=True, b_kcontig=False, **kw), "NT": Bn.gemm(A, Bt, a_kcontig=True, b_kcontig=True, **kw),
+            "TN": Bn.gemm(At, B, a_kcontig=False, b_kcontig=False, **kw)}
+
+
+@pytest.mark.parametrize("K", [64, 620, 8000])
+def test_gemm_float_error(K):
+    """A float product adds K / 32 partial sums, each sum cut off at 2^-23 of itself at worst: for values of random sign, whose partial sums grow as
+    the root of their number, 2^-23 sqrt(K / 64) of the result, root mean square.  (A float MFMA adds K products one by one and is above that.)"""
+    g = torch.Generator().manual_seed(K)
+    A, B = torch.randn(260, K, generator=g), torch.randn(K, 200, generator=g)
+    ref = A.double() @ B.double()
+    for form, C in _float_forms(A.cuda(), B.cuda()).items():
+        assert float((C.cpu().double() - ref).norm() / ref.norm()) < 2.0 ** -23 * (K / 64) ** 0.5, form
+
+
+@pytest.mark.parametrize("kind", ["infinities", "nan", "largest", "overflow", "denormal", "tiny", "zero"])
+def test_gemm_float_odd_values(kind):
+    """What three bfloat16 cannot hold arrives as in 64 bits, rounded to float at the end; the tile beside it as always."""
+    g = torch.Generator().manual_seed(5)
+    A, B = torch.randn(200, 100, generator=g), torch.randn(100, 260, generator=g)
+    if kind == "infinities":
+        A[3, 5], B[7, 9], A[60, 7] = float("inf"), -float("inf"), 0.0
+    elif kind == "nan":
+        A[150, 50] = float("nan")
+    elif kind == "largest":
+        A[3, 5] = torch.finfo(torch.float32).max
+        B[5] *= 1e-3
+    elif kind == "overflow":
+        A[3] = 1e30
+        B[:, 4] = 1e10
+    else:
+        A *= dict(denormal=1e-40, tiny=1e-34, zero=0.0)[kind]
+    ref = A.double() @ B.double()
+    f32 = ref.float()
+    for form, C in _float_forms(A.cuda(), B.cuda()).items():
+        C = C.cpu()
+        assert torch.equal(C.isnan(), f32.isnan()) and torch.equal(C.isinf(), f32.isinf()), form
+        assert torch.equal(C[C.isinf()], f32[f32.isinf()]), form
+        ok = f32.isfinite()
+        # 100 sums, each rounded (to 2^-149 at the smallest): of the sum of magnitudes, beside which a product cancels
+        scale = (A.double().abs() @ B.double().abs())[ok]
+        bound = 1e-5 * scale.nan_to_num(0.0) + 200 * 2.0 ** -149
+        assert bool(((C.double() - ref)[ok].abs() <= bound).all()), form
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_gemm_frame_mask_ignores_nan_rows(dt):
     rng = np.random.default_rng(3)
