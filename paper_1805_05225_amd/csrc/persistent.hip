@@ -264,6 +264,9 @@ __device__ __forceinline__ void mfma_b_agpr_first(f32x4& acc, const u32x4& a, co
 __device__ __forceinline__ void mfma4_b_agpr(f32x4& acc, float a, unsigned b) {
   asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
 }
+__device__ __forceinline__ void mfma4_b_vgpr(f32x4& acc, float a, float b) {
+  asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
 __device__ __forceinline__ void mfma4_b_agpr_first(f32x4& acc, float a, unsigned b) {
   asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
 }
@@ -1997,13 +2000,17 @@ __global__ __launch_bounds__(256) void persist_bwd_rows_kernel(PBwdArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// forward, float storage.  The float MFMA (16x16x4) runs at a sixteenth of the bfloat16 rate: 7.1 us per step for 64 rows
-// x 2 directions of n = 1000 on the whole device, so here the matrix cores bound the step, and the exchange has to stay
-// out of their way.  Two things compete with them.  (1) Every work-group reads the whole h of its rows in float, from
+// forward, float storage.  The float MFMA (16x16x4) runs at a sixteenth of the bfloat16 rate, 7.1 us per step for 64 rows
+// x 2 directions of n = 1000 on the whole device; so a product is six bfloat16 ones of three-part sums (Splitter: 24 bits, as float), 2.7 us, and
+// errors against 64 bits are 0.6 of what float MFMAs gave (y 2.6e-7 -> 1.6e-7 of its size, dW_h 5.0e-7 -> 2.8e-7; n = 160 to 1000, weights up to 6 / sqrt n).  A step's tags
+// are looked at before its products, all of them, and h is split between products of the pair before.  What bounds a step now is the exchange:
+// us a step, forward and backward, 64 rows x 2 directions of n = 1024 12.0 and 14.3 -> 8.8 and 12.2, 16 rows 6.8 and 6.9 -> 4.2 and 5.5, of
+// n = 512 4.4 and 4.4 -> 2.4 and 3.4, of 256 2.8 and 2.9 -> 1.85 and 2.4.
+// Two things matter to it.  (1) Every work-group reads the whole h of its rows in float, from
 // beyond L2 (an exchange group spans several XCDs), so rows per work-group are traded against copies of W_h: a work-group
 // owns 16 units - 64 gate columns, four MFMA column tiles - for a slab of 32 rows: 63 x 2 slabs x 2 directions = 252
 // work-groups for config 2, W_h held twice on the device (256 registers per lane: the per-step kernel's packed slices of
-// two 8-unit tiles), 128 KiB of ring read per work-group and step (with 8 units x 64 rows, 256 KiB, the step took 13.8 us
+// two 8-unit tiles), 128 KiB of ring read per work-group and step (with 8 units x 64 rows, 256 KiB, a step of float MFMAs took 13.8 us
 // against 11 for its products alone).  (2) The round trip of the exchange - reduce, cell, publish, and the consumers' loads,
 // about 2.5 us - which nothing overlaps if all rows move in lock step (12.0 us per step).  The two row tiles of a slab
 // are different batch rows, i.e. independent recurrences: they are walked HALF A STEP APART, one's products running
@@ -2055,9 +2062,26 @@ __device__ __forceinline__ F32Rows f32_rows(const int* lens, int B, int T, bool 
   return f;
 }
 
+// A float as the sum of three bfloat16 (8 + 8 + 8 bits, rounded to nearest, the last exactly; gemm_float.hip), eight of them in twelve small steps that
+// fit between products: part e / 4 of elements 2 (e % 4) and the next.  W_h is scaled by a power of two first, or parts of small weights would end below 2^-133.
+struct Splitter {
+  float v[8];
+  u32x4 part[3];
+  __device__ __forceinline__ void step(int e) {
+    float &lo = v[2 * (e & 3)], &hi = v[2 * (e & 3) + 1];
+    const unsigned u = pack_bf16x2(lo, hi);
+    part[e >> 2][e & 3] = u;
+    if (e < 8) { lo -= __uint_as_float(u << 16); hi -= __uint_as_float(u & 0xffff0000u); }
+  }
+};
+constexpr float kWScale = 0x1p40f;
+constexpr unsigned kWMost = 0x79800000u;                   // 2^116: a sum of 256 products with h stays finite
 template <int NCH>                                         // chunks per wavefront at most: n <= 64 * NCH
 __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
+  constexpr int NP = NCH / 2;                              // pairs of chunks: 32 k, the depth of a bfloat16 product
   __shared__ float red[4][16][65];
+  __shared__ u32x4 w_low[4][NP][4][64];                    // [wavefront][pair][column tile][lane]
+  __shared__ float zxs[2][4][4][NCH <= 8 ? 64 : 1];        // [step][wavefront][gate][lane]
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
@@ -2072,22 +2096,42 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 
   // W_h slice: chunk kc = wave + 4 it; column tile ct = tile of 8 units (ct >> 1), its gates i,f (ct & 1 = 0) or g,o
   // (the per-step kernel's packing)
-  // It fills the 256 accumulation registers of every lane and the MFMAs read it there (inline assembly, as in the bfloat16
-  // kernels).  A chunk past the end of K or a column tile past n takes the last valid one's weights instead of zeros: the h
-  // values of such a chunk arrive as zeros (the ring's descriptor ends before them), and such columns are never stored.
-  u32x4 w[NCH][4];
+  // In three bfloat16 parts: two fill the 256 accumulation registers of every lane and the MFMAs read them there (inline assembly, as in the
+  // bfloat16 kernels), the smallest lies in LDS, where a wavefront reads back what it wrote.  A chunk past the end of K or a column
+  // tile past n takes the last valid one's weights instead of zeros: the h values of such a chunk arrive as zeros (the ring's descriptor ends before
+  // them), and such columns are never stored.
+  u32x4 wh[NP][4], wm[NP][4];
+  unsigned w_most = 0u;
+  auto w_at = [&](int it, int ct) __attribute__((always_inline)) {
+    const int kc = min(wave + 4 * it, nkc - 1), tile8 = min(tile * 2 + (ct >> 1), ntile8 - 1);
+    return *((const u32x4*)d.Wf + ((long)(tile8 * 2 + (ct & 1)) * nkc + kc) * 64 + lane);
+  };
 #pragma unroll
-  for (int it = 0; it < NCH; ++it) {
-    const int kc = min(wave + 4 * it, nkc - 1);
+  for (int p = 0; p < NP; ++p) {
+    u32x4 v[4][2];
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) { v[ct][0] = w_at(2 * p, ct); v[ct][1] = w_at(2 * p + 1, ct); }
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
-      const int tile8 = min(tile * 2 + (ct >> 1), ntile8 - 1);
-      w[it][ct] = load_to_agpr(&d.Wf[((long)(tile8 * 2 + (ct & 1)) * nkc + kc) * 64 + lane]);
+      Splitter s;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        s.v[e] = __uint_as_float(v[ct][e >> 2][e & 3]) * kWScale;
+        w_most = max(w_most, __float_as_uint(s.v[e]) & 0x7fffffffu);
+      }
+#pragma unroll
+      for (int e = 0; e < 12; ++e) s.step(e);
+      wh[p][ct] = s.part[0];
+      wm[p][ct] = s.part[1];
+      w_low[wave][p][ct][lane] = s.part[2];
+      asm volatile("" : "+a"(wh[p][ct]), "+a"(wm[p][ct]));
     }
   }
-  agpr_loads_done();
+  // Weights that the parts cannot hold (infinities, NaN, 2^76 and more): this wavefront's products are float MFMAs, W_h from memory.
+  const bool plain = __builtin_amdgcn_ballot_w64(w_most >= kWMost) != 0ull;
   const int local = NCH <= 8 ? group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit) : 0;      // (more than 32 members never are)
 
+  const unsigned zxs_wave = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&zxs[0][wave][0][0]);
   // pointwise: row r16 of each row tile, unit u of the tile's 16
   const int r16 = tid >> 4, u = tid & 15;
   const int j = tile * 16 + u;
@@ -2118,35 +2162,50 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
   // columns of this thread's cell among the work-group's 64: 32 per tile of 8 units, then gate q, unit
   const int col0 = (u >> 3) * 32 + (u & 7);
   PROF_DECL
-  // The first half of a half step's ring loads goes out before the reduction and the cell update of the half step
-  // before it (their values were published half a step earlier) and is there when the products begin; the second half
-  // goes out then and arrives behind the first half's products.  (All of them early does not fit the register file.)
-#ifndef LSTM_FWD_F32_EARLY
-#define LSTM_FWD_F32_EARLY (NCH / 2)
-#endif
-  constexpr int kEarly = LSTM_FWD_F32_EARLY;
-  u32x4 x[NCH];
+  // A half step's ring loads go out before the reduction and the cell update of the half step before it (their values were published half a
+  // step earlier) and are there when the products begin.
   auto in_loop = [&](int tau, int k) { return k < nrt_here && tau >= rows.first[k] && tau < rows.first[k] + rows.count[k]; };
   auto reader = [&](int step, int k) __attribute__((always_inline)) {       // step: of the row tile's own steps
     return make_reader(((step & 1) ? d.ring1 : d.ring0) + (long)rows.tile[k] * nkc * 64, nkc, (n + 3) / 4, wave, lane,
                        ll_fwd_tag((unsigned)step) << 14, err, a.spin_limit, 0);
   };
+  // (a loop for slabs of two row tiles and one for a single one: where they met, the compiler would copy loads in flight, behind a wait of its own)
+  auto all_steps = [&](auto two) __attribute__((always_inline)) {
+  constexpr bool kTwo = decltype(two)::value, kZxAhead = !kTwo && NCH <= 8;
+  u32x4 x[NCH];
   auto issue_loads = [&](int tau, int k) __attribute__((always_inline)) {
     const RingReader rn = reader(tau - rows.first[k], k);
 #pragma unroll
-    for (int it = 0; it < kEarly; ++it) x[it] = rn.load_it(it);
+    for (int it = 0; it < NCH; ++it) x[it] = rn.load_it(it);
   };
   // (a row tile takes part in no step before the longer one of its slab, and in none after it)
-  if (rows.count[0] > 0) issue_loads(rows.first[0], 0);
+  if (kTwo && rows.count[0] > 0) issue_loads(rows.first[0], 0);
 
+  // A single row tile's x W_x + b is fetched a step ahead, behind its ring loads (loads come back in the order of issue: in front of the poll they would hold it
+  // up), into LDS, where a wavefront reads back what it asked for: 16 rows of n = 512 2.70 -> 2.50 us a step, of 256 1.99 -> 1.81; wider layers, whose
+  // products hide it, lose by it (n = 1024 4.47 -> 4.64).  (Assembly: the compiler makes every later LDS read wait for loads of this kind.)
+  auto fetch_zx = [&](int tau) __attribute__((always_inline)) {
+    const int t = d.rev ? T - 1 - tau : tau;
+    const bool ok = tau < T && active[0] && t < L[0];
+    const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void*)(d.gates + (tau < T ? t : 0) * fg), 0, 0x7ff00000, kBufFlags);
+    const unsigned off = ok ? (unsigned)(rows.row[0] * 4 * n + j) * 4u : kParked;
+    const unsigned to = zxs_wave + (unsigned)((tau & 1) * sizeof(zxs[0])), gate = (unsigned)n * 4u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen nt lds" ::"s"(to + (unsigned)(q * sizeof(zxs[0][0][0]))), "v"(off), "s"(rg), "s"(q * gate) : "memory");
+  };
+  if constexpr (kZxAhead) fetch_zx(0);
   for (int tau = 0; tau < T; ++tau) {
     const int t = d.rev ? T - 1 - tau : tau;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {                          // the slab's two row tiles, half a step apart
-      if (k >= nrt_here) break;                            // (the same in every work-group of the exchange group)
+    for (int k = 0; k < (kTwo ? 2 : 1); ++k) {             // the slab's row tiles, half a step apart
       PROF_MARK(4)
       const int b = rows.row[k], step = tau - rows.first[k];
       if (!in_loop(tau, k)) {                              // every row of the tile is padding here
+        if (kZxAhead && in_loop(tau + 1, 0)) {
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+          fetch_zx(tau + 1);
+        }
         if (active[k]) {
           ((float*)d.y)[t * fy + (long)b * d.ldy + j] = 0.f;
           if (d.cs) d.cs[t * fs + (long)b * n + j] = c[k];
@@ -2158,45 +2217,144 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
       const bool valid = active[k] && t < L[k];
       // this frame's x W_x + b: in flight while the products run
       float zx[4];
+      if constexpr (!kZxAhead) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) zx[q] = valid ? d.gates[t * fg + (long)b * 4 * n + q * n + j] : 0.f;
-      f32x4 acc[4];
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) acc[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      operands_settle(acc[0], acc[1], acc[2], acc[3]);     // (the MFMAs are assembly text: wait states by hand)
-      const RingReader rd = reader(step, k);
-      auto use = [&](int it, const u32x4& x) __attribute__((always_inline)) {
-        u32x4 av = {x[0], x[1] & ~kLLFwdTagBit, x[2], x[3] & ~kLLFwdTagBit};
-        asm volatile("s_nop 4" : "+v"(av));                // masked just now by the vector ALU
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int ct = 0; ct < 4; ++ct) mfma4_b_agpr(acc[ct], __uint_as_float(av[e]), w[it][ct][e]);
-      };
-#pragma unroll
-      for (int it = kEarly; it < NCH; ++it) x[it] = rd.load_it(it);
-      // a load with a stale tag is fetched again (bounded) - rare, since the values were published half a step ago
-      unsigned long long redo = 0ull;
-#pragma unroll
-      for (int it = 0; it < NCH; ++it) {
-        wait_loads_but(NCH - 1 - it, x[it]);               // (the first half went out before the last half step's stores)
-        if (__builtin_amdgcn_ballot_w64(rd.tag_diff(x[it], it, tagw) != 0u) == 0ull) use(it, x[it]);
-        else { redo |= 1ull << it; PROF_REDO(1) }
+        for (int q = 0; q < 4; ++q) zx[q] = valid ? d.gates[t * fg + (long)b * 4 * n + q * n + j] : 0.f;
       }
-      if (redo) rd.template fix_up_batch<NCH>(redo, dead, use);
-      if (k == 0 && in_loop(tau, 1)) issue_loads(tau, 1);
-      else if (in_loop(tau + 1, 0)) issue_loads(tau + 1, 0);
-      mfma_settle(acc[0], acc[1], acc[2], acc[3]);         // (behind the loads: their issue covers part of the wait)
-      PROF_MARK(0)
+      const RingReader rd = reader(step, k);
+      auto next_loads = [&]() __attribute__((always_inline)) {
+        if constexpr (kTwo) {
+          if (k == 0 && in_loop(tau, 1)) issue_loads(tau, 1);
+          else if (in_loop(tau + 1, 0)) issue_loads(tau + 1, 0);
+        }
+        PROF_MARK(0)
+      };
       // accumulator rows 4 * (lane / 16) + v of the row tile, column lane % 16 of the column tile
+      auto to_sum = [&](auto&& value) __attribute__((always_inline)) {
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
+        for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[wave][4 * (lane >> 4) + v][ct * 16 + (lane & 15)] = acc[ct][v];
+          for (int v = 0; v < 4; ++v) red[wave][4 * (lane >> 4) + v][ct * 16 + (lane & 15)] = value(ct, v);
+      };
+      if (__builtin_expect(plain, 0)) {
+        f32x4 acc[4];
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) acc[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        operands_settle(acc[0], acc[1], acc[2], acc[3]);   // (assembly text: the compiler's own would take accumulation registers from W_h)
+#pragma unroll 1
+        for (int it = 0; it < NCH; ++it) {
+          u32x4 v = rd.load_it(it);
+          for (unsigned poll = 0; !dead && __builtin_amdgcn_ballot_w64(rd.tag_diff(v, it, tagw) != 0u) != 0ull; ++poll) {
+            if (poll >= a.spin_limit || ((poll & 63u) == 63u && ld_relaxed(err) != 0u)) {
+              st_relaxed(err, 1u);
+              dead = true;
+            }
+            v = rd.load_it(it);
+          }
+          v[1] &= ~kLLFwdTagBit; v[3] &= ~kLLFwdTagBit;
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct) {
+            const u32x4 wv = w_at(it, ct);
+            u32x4 av = v, bv = wv;
+            operands_settle(av, bv);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mfma4_b_vgpr(acc[ct], __uint_as_float(av[e]), __uint_as_float(bv[e]));
+          }
+        }
+        next_loads();
+        if constexpr (kZxAhead) fetch_zx(tau + 1);
+        mfma_settle(acc[0], acc[1], acc[2], acc[3]);
+        to_sum([&](int ct, int v) { return acc[ct][v]; });
+      } else {
+        // Every tag is looked at in front of the products (no branch may come between them: where two paths meet the compiler moves accumulators,
+        // and it does not know what is still being written); loads with a stale one are repeated (bounded).  In a slab of two row
+        // tiles they went out half a step ago and that is rare; a slab of one waits here for what the half step before published, with two loads, and the others go out then.
+        auto fetch = [&](auto from, auto to) __attribute__((always_inline)) {
+#pragma unroll
+          for (int it = decltype(from)::value; it < decltype(to)::value; ++it) x[it] = rd.load_it(it);
+        };
+        auto await = [&](auto from, auto to) __attribute__((always_inline)) {
+          auto stale = [&]() __attribute__((always_inline)) {
+            unsigned bits = 0u;
+#pragma unroll
+            for (int it = decltype(from)::value; it < decltype(to)::value; ++it) bits |= rd.tag_diff(x[it], it, tagw);
+            return __builtin_amdgcn_ballot_w64(bits != 0u) != 0ull;
+          };
+          if (__builtin_expect(stale() && !dead, 0)) rd.poll_again(dead, [&]() __attribute__((always_inline)) { fetch(from, to); }, stale);
+        };
+        constexpr std::integral_constant<int, 0> first;
+        constexpr std::integral_constant<int, 2> rest;
+        constexpr std::integral_constant<int, NCH> all;
+        if constexpr (kTwo) {
+#pragma unroll
+          for (int it = 0; it < NCH; ++it) wait_loads_but(NCH - 1 - it, x[it]);       // (before the stores of the last half step)
+          await(first, all);
+        } else {
+          fetch(first, rest);
+          await(first, rest);
+          fetch(rest, all);
+          await(rest, all);
+          if constexpr (kZxAhead) fetch_zx(tau + 1);
+        }
+        f32x4 acc[4], low[4];                              // the sum of the largest parts' products, and of the others'
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) acc[ct] = low[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        operands_settle(acc[0], acc[1], acc[2], acc[3]);   // (the MFMAs are assembly text: wait states by hand)
+        operands_settle(low[0], low[1], low[2], low[3]);
+        Splitter s[2];
+        auto unpack = [&](Splitter& to, int p) __attribute__((always_inline)) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) to.v[e] = __uint_as_float(x[2 * p + (e >> 2)][e & 3] & ((e & 1) ? ~kLLFwdTagBit : ~0u));
+        };
+        unpack(s[0], 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[0].step(e);
+        static_for<NP>([&](auto pc) __attribute__((always_inline)) {
+          constexpr int p = decltype(pc)::value;
+          Splitter &now = s[p & 1], &then = s[(p + 1) & 1];
+          __builtin_amdgcn_sched_barrier(0);
+          u32x4 wl[4];
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct) wl[ct] = w_low[wave][p][ct][lane];
+          operands_settle(now.part[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          // 24 products, and between them the operand's other parts and the next pair's first
+#pragma unroll
+          for (int o = 0; o < 6; ++o)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) {
+              if (o == 0) mfma_b_agpr(acc[ct], now.part[0], wh[p][ct]);
+              else if (o == 1) mfma_b_agpr(low[ct], now.part[0], wm[p][ct]);
+              else if (o == 2) mfma_b_agpr(low[ct], now.part[1], wh[p][ct]);
+              else if (o == 3) mfma_b_agpr(low[ct], now.part[1], wm[p][ct]);
+              else if (o == 4) mfma_b_vgpr(low[ct], now.part[0], wl[ct]);
+              else mfma_b_agpr(low[ct], now.part[2], wh[p][ct]);
+              __builtin_amdgcn_sched_barrier(0);
+              const int m = 4 * o + ct;
+              if (m < 4) now.step(4 + m);                  // second part, in front of the ninth product
+              else if (m >= 8 && m < 12) now.step(m);      // third part, in front of the twenty-first
+              if constexpr (p + 1 < NP) {
+                if (m == 15) unpack(then, p + 1);
+                if (m >= 16 && m < 20) then.step(m - 16);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+        mfma_settle(acc[0], acc[1], acc[2], acc[3]);
+        mfma_settle(low[0], low[1], low[2], low[3]);
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) acc[ct] += low[ct];
+        next_loads();
+        to_sum([&](int ct, int v) { return acc[ct][v] * (1.f / kWScale); });
+      }
       PROF_MARK(1)
       __syncthreads();
       const float hprev = h[k];
       CellOut o = {};
+      if constexpr (kZxAhead) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zx[q] = zxs[tau & 1][wave][q][lane];
+      }
       if (valid) {
         float zh[4];
 #pragma unroll
@@ -2233,6 +2391,9 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
       PROF_MARK(3)
     }
   }
+  };
+  if (nrt_here == 2) all_steps(std::true_type{});
+  else all_steps(std::false_type{});
   PROF_DUMP("fwdf32", T)
 #pragma unroll
   for (int k = 0; k < 2; ++k)
@@ -2247,9 +2408,11 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 // backward, float storage: partial sums of Dh, as in the bfloat16 kernels, in the decomposition of the float forward
 // kernel (16 units x a slab of 32 rows per work-group, the slab's two row tiles half a step apart).  A work-group
 // multiplies ITS dz (16 rows x 64 gate columns, through LDS, never leaving the compute unit) by the matching 64 rows of W_h^T
-// for ALL n outputs - 256 registers per lane hold that slice, 16 column tiles x 16 k-steps per wavefront - and publishes,
+// for ALL n outputs - 256 registers per lane hold two parts of that slice, LDS the third - and publishes,
 // per destination tile of 16 units, the accumulator tile as it stands: a lane's four floats (rows 4g .. 4g+3 of one output)
-// are two 8-byte units, the tag bit 30 of each unit's second float.  Partial sums are not bounded by 1, so they travel scaled
+// are two 8-byte units, the tag bit 30 of each unit's second float.  (Products of three-part sums as forward: 16 k-steps of a column tile are two
+// halves of 32 of K.  What the next step's gate gradients need is fetched into LDS a step ahead: loads come back in the order of issue, and from
+// memory they would hold up the ring's; n = 512, 32 rows 3.8 -> 3.55 us a step.)  Partial sums are not bounded by 1, so they travel scaled
 // by 2^-32 (the packed W_h^T carries the factor; the consumer multiplies its sum by 2^32): bit 30 is then 0 for every partial
 // sum below 2^32 in magnitude, and no other bit of a value above 2^-94 changes.  Larger ones, infinities and NaN travel folded
 // (exchange_dev.h): a half step whose largest dz and W_h could make one looks at each sum, the others at none (config 2's loop 525 -> 534 us, a slab of one row
@@ -2265,6 +2428,8 @@ template <int NCT>                                         // column tiles per w
 __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   __shared__ float red[4][16][17];                         // [wavefront][row][output]
   __shared__ __attribute__((aligned(16))) float zb[16][68];// dz of the row tile in hand: [row][gate column kappa]
+  __shared__ u32x4 w_low[4][NCT][2][64];                   // [wavefront][column tile][half of K][lane]
+  __shared__ float in_f[2][4][7][64];                      // [row tile][wavefront][gates, cells, dy][lane]: what the next step's gate gradients need
   const WgCoord wg = wg_coord(a.map, a.ndir);
   if (!wg.live) return;
   publish_xcd(a.xcc, wg.base, wg.tile);
@@ -2278,24 +2443,35 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   bool dead = false;
 
   // W_h^T slice: column tile wave + 4 ci of the outputs, k-step s (launch_pack_wh_bwd_f32p)
-  // It fills the 256 accumulation registers of every lane and stays there: the MFMAs read it from them (inline assembly, as in
-  // the bfloat16 kernels; left to the compiler the slice is spread over both register files and copied back before every use, with
-  // the architectural registers filled to the last one).
-  u32x4 w[NCT][4];
-#pragma unroll
-  for (int ci = 0; ci < NCT; ++ci)
-#pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) w[ci][s4] = load_to_agpr((const uint4*)d.Wb + ((((long)J * 4 + wave) * NCT + ci) * 4 + s4) * 64 + lane);
-  agpr_loads_done();
+  // In three bfloat16 parts, as forward: two fill the 256 accumulation registers of every lane, the smallest lies in LDS.
+  u32x4 wh[NCT][2], wm[NCT][2];
   float w_bound = 0.f;                                     // 64 times the slice's largest weight, over all lanes: a sum of products is no larger than
-#pragma unroll                                             // this times the largest dz
-  for (int ci = 0; ci < NCT; ++ci)
+  unsigned w_most = 0u;                                    // this times the largest dz
+  auto w_at = [&](int ci, int s4) __attribute__((always_inline)) { return *((const u32x4*)d.Wb + ((((long)J * 4 + wave) * NCT + ci) * 4 + s4) * 64 + lane); };
 #pragma unroll
-    for (int s4 = 0; s4 < 4; ++s4) {
-      asm volatile("" : "+a"(w[ci][s4]));                  // (read behind the wait, not in front of it)
+  for (int c2 = 0; c2 < NCT; c2 += 2) {
+    u32x4 v[2][4];
 #pragma unroll
-      for (int e = 0; e < 4; e += 2) w_bound = max_magnitude(w_bound, __uint_as_float(w[ci][s4][e]), __uint_as_float(w[ci][s4][e + 1]));
+    for (int s4 = 0; s4 < 8; ++s4) v[s4 >> 2][s4 & 3] = w_at(c2 + (s4 >> 2), s4 & 3);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int ci = c2 + (g >> 1), c = g & 1;
+      Splitter s;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        s.v[e] = __uint_as_float(v[g >> 1][2 * c + (e >> 2)][e & 3]);
+        w_bound = max_magnitude(w_bound, s.v[e], 0.f);
+        w_most = max(w_most, __float_as_uint(s.v[e]) & 0x7fffffffu);
+      }
+#pragma unroll
+      for (int e = 0; e < 12; ++e) s.step(e);
+      wh[ci][c] = s.part[0];
+      wm[ci][c] = s.part[1];
+      w_low[wave][ci][c][lane] = s.part[2];
+      asm volatile("" : "+a"(wh[ci][c]), "+a"(wm[ci][c]));
     }
+  }
+  const bool plain = __builtin_amdgcn_ballot_w64(w_most >= kWMost) != 0ull;      // (as forward)
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) w_bound = max_magnitude(w_bound, __shfl_xor(w_bound, o), 0.f);
   w_bound *= 64.f;
@@ -2330,7 +2506,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   // everything again) into the next half step.
   constexpr int kWin = NCT < 6 ? NCT : 6;
   static_assert(kWin >= 1 && kWin <= 16 && kWin <= NCT, "wait_loads_but covers up to 15 younger loads");
-  u32x4 x[NCT];
+  u32x4 x[NCT < 16 ? 16 : NCT];                            // (an array of up to 128 bytes becomes one register tuple, moved as a whole)
   float ps_c[4] = {0.f, 0.f, 0.f, 0.f};
   unsigned long long redo_c = 0ull;
   bool have_c = false;
@@ -2354,6 +2530,34 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
     ps[2] += __uint_as_float(v[2]); ps[3] += __uint_as_float(v[3] & ~kLLFwdTagBit);
   };
 
+  // Step sigma's inputs of row tile k, fetched a step ahead into LDS, where a wavefront reads back what it asked for.  (Assembly: the compiler makes every
+  // later LDS read wait for loads of this kind.)
+  const unsigned in_lds = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&in_f[0][wave][0][0]);
+  auto fetch_in = [&](int sigma, int k) __attribute__((always_inline)) {
+    constexpr unsigned kParked = 0x7ff00000u;
+    const int tau = T - 1 - sigma, t = d.rev ? sigma : tau, tp = d.rev ? t + 1 : t - 1;        // tp: the frame before t in processing order
+    const bool frame = tau >= 0, before = tp >= 0 && tp < T;
+    const bool on = frame && active[k] && t < L[k];
+    const int b = rows.row[k];
+    auto from = [&](const void* base, long elements) {
+      return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + elements * 4), 0, base ? (int)kParked : 0, kBufFlags);
+    };
+    const long at = frame ? t : 0;
+    const __amdgpu_buffer_rsrc_t rg = from(d.gates, at * fg), rc = from(d.cs, at * fs), rp = from(before ? d.cs : d.c0, before ? tp * fs : 0), ry = from(d.dy, at * fy);
+    const unsigned g_off = on ? (unsigned)(b * 4 * n + j) * 4u : kParked, s_off = on ? (unsigned)(b * n + j) * 4u : kParked, y_off = on ? (unsigned)(b * d.lddy + j) * 4u : kParked;
+    const unsigned to = in_lds + (unsigned)(k * sizeof(in_f[0])), gate = (unsigned)n * 4u;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // what was there has been read
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen nt lds" ::"s"(to + q * 256u), "v"(g_off), "s"(rg), "s"(q * gate) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(to + 4 * 256u), "v"(s_off), "s"(rc) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(to + 5 * 256u), "v"(s_off), "s"(rp) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen nt lds" ::"s"(to + 6 * 256u), "v"(y_off), "s"(ry) : "memory");
+  };
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    if (in_loop(0, k)) fetch_in(0, k);
+
   // Steps sigma = 0 .. T-1 work on frames (the last frame in processing order first); step T only collects the Dh that
   // leaves the layer.
   for (int sigma = 0; sigma <= T; ++sigma) {
@@ -2367,6 +2571,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       const int b = rows.row[k], st = step_of(sigma, k);
       if (!in_loop(sigma, k) || (st == rows.count[k] && tau >= 0)) {
         // every row of the tile is padding here; the tile's collecting step falls on such a frame if the tile is reversed and shorter
+        if (!in_loop(sigma, k) && in_loop(sigma + 1, k)) fetch_in(sigma + 1, k);
         if (active[k] && tau >= 0) {
           float* zp = (float*)d.DZ + t * fg + (long)b * 4 * n + j;
           zp[0] = 0.f; zp[n] = 0.f; zp[2 * n] = 0.f; zp[3 * n] = 0.f;
@@ -2375,16 +2580,6 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       }
       const bool pointwise = st < rows.count[k];
       const bool valid = pointwise && active[k] && t < L[k];
-      // what the gate gradients of the frame need: in flight while the partial sums are collected
-      float gi = 0.f, gf = 0.f, gg = 0.f, go = 0.f, c_new = 0.f, c_prev = 0.f, dy = 0.f;
-      if (valid) {
-        const float* gp = d.gates + t * fg + (long)b * 4 * n + j;
-        gi = gp[0]; gf = gp[n]; gg = gp[2 * n]; go = gp[3 * n];
-        c_new = d.cs[t * fs + (long)b * n + j];
-        const int tp = d.rev ? t + 1 : t - 1;              // the frame before t in processing order
-        c_prev = (tp >= 0 && tp < T) ? d.cs[tp * fs + (long)b * n + j] : (d.c0 ? d.c0[(long)b * n + j] : 0.f);
-        dy = ((const float*)d.dy)[t * fy + (long)b * d.lddy + j];
-      }
       if (st > 0) {                                        // the partial sums of Dh that the step before published
         const RingReader rd = reader(st, k);
         const unsigned tagw = rd.tag << 16;
@@ -2423,12 +2618,16 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) red[wave][4 * (lane >> 4) + v][lane & 15] = ps[v];
       }
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (elsewhere the ring loads, younger and waited for, say that the inputs are there)
       PROF_MARK(0)
       __syncthreads();
+      float in[7];
+#pragma unroll
+      for (int e = 0; e < 7; ++e) in[e] = in_f[k][wave][e][lane];
       if (st > 0 && active[k] && t_next >= 0 && t_next < L[k])
         Dh[k] = (red[0][r16][u] + red[1][r16][u] + red[2][r16][u] + red[3][r16][u]) * (1.f / kPartScale);
       float dz[4] = {0.f, 0.f, 0.f, 0.f};
-      if (valid) lstm_cell_grad(gi, gf, gg, go, c_new, c_prev, dy + Dh[k], Dc[k], dz);
+      if (valid) lstm_cell_grad(in[0], in[1], in[2], in[3], in[4], in[5], in[6] + Dh[k], Dc[k], dz);
       if (pointwise) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) dbsum[q] += dz[q];       // (zero where the frame is padding)
@@ -2443,10 +2642,11 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       __syncthreads();
       have_c = false;
       if (pointwise) {
+        if (nrt_here == 1) fetch_in(sigma + 1, k);         // (in a slab of two behind the products, whose loads from the ring it would hold up)
         // what the next half step consumes (the other row tile's partial sums, published half a step ago) is collected here
         const int k_n = k ^ 1, sigma_n = k == 0 ? sigma : sigma + 1, st_n = step_of(sigma_n, k_n);
         // (the next half step must be the other tile's, and not its first, which consumes nothing)
-        const bool collect = in_loop(sigma_n, k_n) && st_n >= 1;
+        bool collect = in_loop(sigma_n, k_n) && st_n >= 1;
         const RingReader rn = reader(st_n, k_n);
         const unsigned tagw_n = rn.tag << 16;
         float psn[4] = {0.f, 0.f, 0.f, 0.f};
@@ -2486,26 +2686,73 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           if (local) __builtin_amdgcn_raw_buffer_store_b128(unit, to, off, 0, 1);
           else __builtin_amdgcn_raw_buffer_store_b128(unit, to, off, 0, 16);    // 16: agent scope, written through
         };
-        f32x4 acc2[2];
+        // What the parts cannot hold: float MFMAs, W_h from memory, and the next half step fetches for itself.
+        const float bound = largest * w_bound;
+        if (__builtin_expect(plain || __builtin_amdgcn_ballot_w64(!(largest < 0x1p100f && bound < 0x1p100f)) != 0ull, 0)) {
+          collect = false;
+#pragma unroll 1
+          for (int ci = 0; ci < NCT; ++ci) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f}, o1 = acc, o2 = acc, o3 = acc;
+            operands_settle(acc, o1, o2, o3);
 #pragma unroll
-        for (int ci = 0; ci < NCT; ++ci) {
-          f32x4& acc = acc2[ci & 1];
+            for (int s4 = 0; s4 < 4; ++s4) {
+              u32x4 wv = w_at(ci, s4), none = wv;
+              operands_settle(wv, none);
 #pragma unroll
-          for (int s = 0; s < 16; ++s) {
-            if (s == 0) mfma4_b_agpr_first(acc, av[0], w[ci][0][0]);
-            else mfma4_b_agpr(acc, av[s], w[ci][s >> 2][s & 3]);
+              for (int e = 0; e < 4; ++e) mfma4_b_vgpr(acc, av[4 * s4 + e], __uint_as_float(wv[e]));
+            }
+            mfma_settle(acc);
+            publish(ci, acc);
           }
-          if (ci > 0) publish(ci - 1, acc2[(ci - 1) & 1]);
-          if (collect) {                                   // (behind the MFMAs just issued: they run while this does)
-            wait_loads_but((NCT - 1 - ci) < (kWin - 1) ? (NCT - 1 - ci) : (kWin - 1), x[ci % kWin]);     // the younger loads: the window's others
-            stale_n |= rn.tag_diff(x[ci % kWin], ci, tagw_n);      // looked at once, behind the last load
-            largest_n = max_magnitude(largest_n, __uint_as_float(x[ci % kWin][1]), __uint_as_float(x[ci % kWin][3]));
-            add_to(psn, x[ci % kWin]);
-            if (ci + kWin < NCT) x[ci % kWin] = rn.load_it(ci + kWin);
+        } else {
+          Splitter s[2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[c].v[e] = av[8 * c + e];
+#pragma unroll
+            for (int e = 0; e < 12; ++e) s[c].step(e);
           }
+          u32x4 wl[2][2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) wl[0][c] = w_low[wave][0][c][lane];
+          operands_settle(s[0].part[0], s[0].part[1], s[0].part[2], s[1].part[0]);
+          operands_settle(s[1].part[1], s[1].part[2]);
+          f32x4 acc2[2], low2[2];                          // (low: the products of all but the largest parts)
+#pragma unroll
+          for (int ci = 0; ci < NCT; ++ci) {
+            f32x4 &acc = acc2[ci & 1], &low = low2[ci & 1];
+            __builtin_amdgcn_sched_barrier(0);
+            if (ci + 1 < NCT) {
+#pragma unroll
+              for (int c = 0; c < 2; ++c) wl[(ci + 1) & 1][c] = w_low[wave][ci + 1][c][lane];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            mfma_b_agpr_first(acc, s[0].part[0], wh[ci][0]);
+            mfma_b_agpr_first(low, s[0].part[0], wm[ci][0]);
+            mfma_b_agpr(acc, s[1].part[0], wh[ci][1]);
+            mfma_b_agpr(low, s[1].part[0], wm[ci][1]);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              mfma_b_agpr(low, s[c].part[1], wh[ci][c]);
+              mfma_b_agpr(low, s[c].part[1], wm[ci][c]);
+              mfma_b_agpr(low, s[c].part[2], wh[ci][c]);
+              mfma_b_vgpr(low, s[c].part[0], wl[ci & 1][c]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (ci > 0) publish(ci - 1, acc2[(ci - 1) & 1] + low2[(ci - 1) & 1]);
+            if (collect) {                                 // (behind the MFMAs just issued: they run while this does)
+              wait_loads_but((NCT - 1 - ci) < (kWin - 1) ? (NCT - 1 - ci) : (kWin - 1), x[ci % kWin]);     // the younger loads: the window's others
+              stale_n |= rn.tag_diff(x[ci % kWin], ci, tagw_n);      // looked at once, behind the last load
+              largest_n = max_magnitude(largest_n, __uint_as_float(x[ci % kWin][1]), __uint_as_float(x[ci % kWin][3]));
+              add_to(psn, x[ci % kWin]);
+              if (ci + kWin < NCT) x[ci % kWin] = rn.load_it(ci + kWin);
+            }
+          }
+          mfma_settle(acc2[(NCT - 1) & 1]);
+          mfma_settle(low2[(NCT - 1) & 1]);
+          publish(NCT - 1, acc2[(NCT - 1) & 1] + low2[(NCT - 1) & 1]);
         }
-        mfma_settle(acc2[(NCT - 1) & 1]);
-        publish(NCT - 1, acc2[(NCT - 1) & 1]);
         if (__builtin_expect(wide, 0)) {
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a wavefront reads what it stored itself, past its L1)
 #pragma unroll 1
@@ -2518,6 +2765,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
             else __builtin_amdgcn_raw_buffer_store_b128(v, ro, off, 0, 16);
           }
         }
+        if (nrt_here == 2) fetch_in(sigma + 1, k);
         if (collect) {
           // The tags are looked at once, here: a test and a branch per load cost a twentieth of the step.  A stale tag anywhere
           // (a tenth of the half steps): the sums are dropped and the next half step fetches every load again.
@@ -2996,8 +3244,9 @@ int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntil
 
 // Few steps, or batches that take several launches, are faster in the per-step kernels (n = 700, 300 rows, both directions, 20 steps: forward
 // 1387 us here, 838 there).  Both sides as they were measured, in us, for n from 130 to 1024, 1 to 512 rows, 2 to 60 steps, one and two
-// directions, plain and cooperative launches (1573 shapes): the choice is within 5 % of the faster side in 99 % of them and never 1.25 times
-// it; always the loops was up to 2.8 times the other.  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
+// directions, plain and cooperative launches (1573 shapes): the choice was within 5 % of the faster side in 99 % of them and never 1.25 times
+// it; always the loops was up to 2.8 times the other.  The loops' side has been measured again since their products are bfloat16 parts (4 and 100 steps of 11
+// shapes): of 396 shapes of 2 to 24 steps the choice is within 5 % of the per-step kernels or faster in 95 %, never 1.16 times them.  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward) {
   const int form = n <= 256 ? 0 : n <= 512 ? 1 : 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
   const bool one = (long)ntile * cdiv(B, 16) * ndir <= cap, pair = !one && B > 16;
@@ -3005,12 +3254,12 @@ bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launc
   const double w = (double)n * n / (1024.0 * 1024.0) * ndir, nr = (double)n * ndir * B * 1e-5, nnr = nr * n * 1e-3, part = lens && pair ? 0.8 : 1.0;
   double here, there;
   if (backward) {
-    const double step[2][3] = {{3.4, 5.7, 8.4}, {9.9, 17.5, 20.4}};
-    here = 31.4 + 18.0 * w + launches * (plain_launch ? 23.6 : 44.5) + launches * T * step[pair][form] * part;
+    const double step[2][3] = {{2.8, 4.3, 7.2}, {7.2, 9.3, 17.4}};
+    here = 34.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
     there = 58.3 + 16.0 * w + T * std::max(4.25 + 17.1e-3 * n + 6.6 * nr + 10.4 * nnr, 22.0 * nnr);
   } else {
-    const double step[2][3] = {{2.9, 4.7, 6.9}, {5.4, 7.9, 12.6}};
-    here = 15.4 + 11.7 * w + launches * (plain_launch ? 10.6 : 31.9) + launches * T * step[pair][form] * part;
+    const double step[2][3] = {{1.9, 2.65, 4.25}, {4.7, 7.2, 9.9}};
+    here = 19.0 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
     there = 27.9 + 7.8 * w + T * std::max(3.8 + 6.15e-3 * n + 4.15 * nr + 4.9 * nnr, 10.9 * nnr);
   }
   return here < there;

@@ -164,6 +164,38 @@ def test_values_outside_the_exchange_range(dt, T, B, n, what):
             assert err.max() < TOL[dt], (name, err.max())
 
 
+@pytest.mark.parametrize("what", ["ordinary", "huge_W", "huge_dy", "tiny_W"])
+@pytest.mark.parametrize("T,B,n", [(24, 9, 200), (24, 17, 500), (24, 140, 500), (24, 70, 1001), (24, 12, 1024)])
+def test_float_loops_in_parts(T, B, n, what):
+    """Slabs of one and of two row tiles in each width: three bfloat16 parts, and the float MFMAs for what these cannot hold (weights from 2^76 on; dz from
+    2^100 on); weights whose parts end below the smallest bfloat16.  Against the per-step kernels, which multiply floats; by row and column."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(n + B)
+    c = P.rnd_case(rng, T, B, 24, n, 1, _lens(rng, T, B), "f32", scale=1.0 / np.sqrt(n))
+    if what == "huge_W":
+        c["W_h"][0, 3::16, 5] = 1e25
+        c["W_h"][0, 7, n + 9] = -1e30
+    elif what == "huge_dy":
+        c["dy"][:, 1::4, 3::4] *= 2.0 ** 105
+    elif what == "tiny_W":
+        c["W_h"][0, :, 1::2] *= 2.0 ** -120
+        c["W_h"][0, 1::2, :] *= 2.0 ** -20
+    Bn.profile_enable(1)
+    f, g = P.run_gpu(c, "f32", False, flags=Bn.FLAG_PLAIN_LAUNCH, poison=True)
+    Bn.profile_enable(0)
+    launches = Bn.profile_read()
+    assert launches["loop_fwd"][1] < T and launches["loop_bwd"][1] < T
+    fs, gs = P.run_gpu(c, "f32", False, flags=Bn.FLAG_PER_STEP)
+    for name, got, ref in [(k, f[k], fs[k]) for k in ("y", "c", "hT", "cT")] + [(k, g[k], gs[k]) for k in ("dx", "dW_x", "dW_h", "db", "dh0", "dc0")]:
+        got, ref = host(got), host(ref)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(got)], ref[np.isinf(ref)]), name
+        ok = np.isfinite(ref)
+        size = np.abs(np.where(ok, ref, 0)).max(axis=-1, keepdims=True)
+        err = np.abs(np.where(ok, got, 0) - np.where(ok, ref, 0)) / np.maximum(size, 1e-30)
+        assert err.max() < 5e-5, (name, err.max())
+
+
 @pytest.mark.parametrize("T,B,n,bidir", [(150, 5, 1032, False), (64, 32, 1536, True), (90, 33, 2048, False), (40, 64, 2048, True), (33, 17, 1921, False)])
 def test_wide_loops_over_many_steps(T, B, n, bidir):
     """The rings of the wide loops are used over and over: many steps, ordinary and cooperative launch, against the per-step kernels; the same
