@@ -283,3 +283,10 @@ def test_phase_times_name_every_product(dt, T, B, n_in, n):
         assert all(p[k][0] > 0 for k in ("gemm_zx", "gemm_dx", "gemm_dwx", "gemm_dwh", "loop_fwd", "loop_bwd"))
         total[level] = sum(v[1] for k, v in p.items() if k.startswith("gemm"))
     assert total[1] == total[2]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [128, 124, 72, 62, 60, 56, 8, 4, 3])
+def test_narrow_layer_widths(dt, n):
+    """W_h of a narrow layer is read by 16 bytes where its rows allow it, by single elements elsewhere; one step more than inputs are asked for ahead."""
+    _layer(5, 6, 24, n, True, dt)
