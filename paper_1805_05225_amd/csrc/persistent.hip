@@ -2004,7 +2004,7 @@ __global__ __launch_bounds__(256) void persist_bwd_rows_kernel(PBwdArgs a) {
 // x 2 directions of n = 1000 on the whole device; so a product is six bfloat16 ones of three-part sums (Splitter: 24 bits, as float), 2.7 us, and
 // errors against 64 bits are 0.6 of what float MFMAs gave (y 2.6e-7 -> 1.6e-7 of its size, dW_h 5.0e-7 -> 2.8e-7; n = 160 to 1000, weights up to 6 / sqrt n).  A step's tags
 // are looked at before its products, all of them, and h is split between products of the pair before.  What bounds a step now is the exchange:
-// us a step, forward and backward, 64 rows x 2 directions of n = 1024 12.0 and 14.3 -> 8.8 and 12.2, 16 rows 6.8 and 6.9 -> 4.2 and 5.5, of
+// us a step, forward and backward, 64 rows x 2 directions of n = 1024 12.0 and 14.3 -> 8.2 and 12.1, 16 rows 6.8 and 6.9 -> 4.2 and 5.5, of
 // n = 512 4.4 and 4.4 -> 2.4 and 3.4, of 256 2.8 and 2.9 -> 1.85 and 2.4.
 // Two things matter to it.  (1) Every work-group reads the whole h of its rows in float, from
 // beyond L2 (an exchange group spans several XCDs), so rows per work-group are traded against copies of W_h: a work-group
@@ -2215,12 +2215,17 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
       }
       const unsigned tagw = ll_fwd_tag((unsigned)step) << 30;
       const bool valid = active[k] && t < L[k];
-      // this frame's x W_x + b: in flight while the products run
+      // this frame's x W_x + b: in flight while the products run.  In a slab of two row tiles it is asked for when the ring's loads have arrived: their wait is
+      // for everything that is in flight (64 rows of n = 1024 8.8 -> 8.2 us a step, 100 of n = 512 5.75 -> 4.85).
       float zx[4];
-      if constexpr (!kZxAhead) {
+      const __amdgpu_buffer_rsrc_t zx_rs = __builtin_amdgcn_make_buffer_rsrc((void*)(d.gates + t * fg), 0, 0x7ff00000, kBufFlags);
+      const unsigned zx_off = valid ? (unsigned)(b * 4 * n + j) * 4u : kParked;
+      auto load_zx = [&]() __attribute__((always_inline)) {
+        if constexpr (!kZxAhead) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) zx[q] = valid ? d.gates[t * fg + (long)b * 4 * n + q * n + j] : 0.f;
-      }
+          for (int q = 0; q < 4; ++q) zx[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(zx_rs, zx_off, (unsigned)(q * n) * 4u, 0));      // (marked non-temporal: 4.22 -> 4.91 us a step for 32 rows of n = 1024)
+        }
+      };
       const RingReader rd = reader(step, k);
       auto next_loads = [&]() __attribute__((always_inline)) {
         if constexpr (kTwo) {
@@ -2261,6 +2266,7 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
             for (int e = 0; e < 4; ++e) mfma4_b_vgpr(acc[ct], __uint_as_float(av[e]), __uint_as_float(bv[e]));
           }
         }
+        load_zx();
         next_loads();
         if constexpr (kZxAhead) fetch_zx(tau + 1);
         mfma_settle(acc[0], acc[1], acc[2], acc[3]);
@@ -2289,7 +2295,9 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 #pragma unroll
           for (int it = 0; it < NCH; ++it) wait_loads_but(NCH - 1 - it, x[it]);       // (before the stores of the last half step)
           await(first, all);
+          load_zx();
         } else {
+          if constexpr (!kZxAhead) load_zx();              // (32 rows of n = 1024: 4.27 us a step, 4.70 with these behind the poll)
           fetch(first, rest);
           await(first, rest);
           fetch(rest, all);
@@ -3258,7 +3266,7 @@ bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launc
     here = 34.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
     there = 58.3 + 16.0 * w + T * std::max(4.25 + 17.1e-3 * n + 6.6 * nr + 10.4 * nnr, 22.0 * nnr);
   } else {
-    const double step[2][3] = {{1.9, 2.65, 4.25}, {4.7, 7.2, 9.9}};
+    const double step[2][3] = {{1.9, 2.65, 4.25}, {4.2, 6.2, 9.2}};
     here = 19.0 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
     there = 27.9 + 7.8 * w + T * std::max(3.8 + 6.15e-3 * n + 4.15 * nr + 4.9 * nnr, 10.9 * nnr);
   }
