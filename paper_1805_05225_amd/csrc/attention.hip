@@ -176,23 +176,24 @@ __global__ __launch_bounds__(256) void att_energy_few_kernel(const uint16_t* __r
 // works the softmax out for itself (beam x S exponentials from one round of loads: cheaper than a launch of its own and
 // a pass through memory); the last one writes a and accum'.  Softmax: 16 lanes per hypothesis, e staged
 // in LDS.  Context: lane l of every wavefront owns features 2l, 2l + 1 of the slice, the four wavefronts share the
-// source positions (wavefront w takes j = w, w + 4, ...), kU loads in flight per lane, and their partial sums meet in
-// LDS.  H is read once for all hypotheses of the sentence.  Dynamic LDS: S * kMaxBeam floats, w[j][r] (rows r >= beam
-// up to the next multiple of 4 hold zeros).
+// source positions (wavefront w takes j = w, w + 4, ...), kU loads in flight per lane - all of 64 positions before the weights are
+// known -, and their partial sums meet in LDS, a quarter of the hypotheses per wavefront.  H is read once for all hypotheses of the sentence.  Dynamic
+// LDS: S * NB floats, w[j][r] (rows r >= beam hold zeros).  The number of hypotheses is the kernel's, in fours: with branches on it the
+// loop spent its time in them (64 sentences of 60 positions, 12 hypotheses, 2000 features: 15.1 -> 9.6 us, of which reading H takes 3; one of 27: 7.4 -> 5.6).
+template <int NB>                                               // hypotheses, in fours
 __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __restrict__ H, const float* __restrict__ e,
                                                            const float* __restrict__ accum_in, const int* __restrict__ lens,
                                                            float* __restrict__ a_out, float* __restrict__ accum_out,
                                                            uint16_t* __restrict__ att, long ldatt, int S, int Q, int beam, int E) {
   extern __shared__ float w[];
-  __shared__ float red[3][kMaxBeam * 2][64];
+  __shared__ float2 red[4][NB][64];
   const int q = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int L = src_len(lens, q, S);
-  const int nb4 = (beam + 3) >> 2;                              // groups of four hypotheses
   const int f = (blockIdx.x * 64 + lane) * 2;
   const bool live = f < E;
   const uint16_t* Hq = H + (long)q * E + (live ? f : 0);        // E even, rows 4-byte aligned
   const long jstride = (long)Q * E;
-  constexpr int kU = 8;
+  constexpr int kU = 16;
   // the first kU positions of this wavefront are asked for before the weights are worked out
   unsigned hh[kU];
   if (L > 0) {
@@ -214,20 +215,20 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
 #pragma unroll
       for (int u = 0; u < kP; ++u)
         if (j0 + 16 * u < L) {
-          w[(j0 + 16 * u) * kMaxBeam + r_own] = ev[u];
+          w[(j0 + 16 * u) * NB + r_own] = ev[u];
           m = fmaxf(m, ev[u]);
         }
     }
-  } else if (r_own < nb4 * 4) {
-    for (int j = l_own; j < L; j += 16) w[j * kMaxBeam + r_own] = 0.f;
+  } else if (r_own < NB) {
+    for (int j = l_own; j < L; j += 16) w[j * NB + r_own] = 0.f;
   }
   // a lane reads back only what it wrote itself until the weights are complete
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if (r_own < beam) {
     for (int j = l_own; j < L; j += 16) {
-      const float p = __expf(w[j * kMaxBeam + r_own] - m);
-      w[j * kMaxBeam + r_own] = p;
+      const float p = __expf(w[j * NB + r_own] - m);
+      w[j * NB + r_own] = p;
       z += p;
     }
 #pragma unroll
@@ -235,9 +236,9 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
     if (l_own == 0) inv_z[r_own] = L > 0 ? 1.f / z : 0.f;       // (applied to the sums below)
   }
   __syncthreads();
-  float acc[kMaxBeam][2];
+  float2 acc[NB];
 #pragma unroll
-  for (int r = 0; r < kMaxBeam; ++r) acc[r][0] = acc[r][1] = 0.f;
+  for (int r = 0; r < NB; ++r) acc[r] = make_float2(0.f, 0.f);
   for (int j = wave; j < L; j += 4 * kU) {
     if (j != wave) {
 #pragma unroll
@@ -247,23 +248,19 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
     for (int u = 0; u < kU; ++u) {
       if (j + 4 * u >= L) break;                                // uniform within the wavefront
       const float h0 = __uint_as_float(hh[u] << 16), h1 = __uint_as_float(hh[u] & 0xffff0000u);
-      const float4* wj = (const float4*)(w + (j + 4 * u) * kMaxBeam);
+      const float4* wj = (const float4*)(w + (j + 4 * u) * NB);
 #pragma unroll
-      for (int g = 0; g < kMaxBeam / 4; ++g)
-        if (g < nb4) {                                          // uniform
-          const float4 p = wj[g];
-          acc[4 * g + 0][0] += p.x * h0; acc[4 * g + 0][1] += p.x * h1;
-          acc[4 * g + 1][0] += p.y * h0; acc[4 * g + 1][1] += p.y * h1;
-          acc[4 * g + 2][0] += p.z * h0; acc[4 * g + 2][1] += p.z * h1;
-          acc[4 * g + 3][0] += p.w * h0; acc[4 * g + 3][1] += p.w * h1;
-        }
+      for (int g = 0; g < NB / 4; ++g) {
+        const float4 p = wj[g];
+        acc[4 * g + 0].x += p.x * h0; acc[4 * g + 0].y += p.x * h1;
+        acc[4 * g + 1].x += p.y * h0; acc[4 * g + 1].y += p.y * h1;
+        acc[4 * g + 2].x += p.z * h0; acc[4 * g + 2].y += p.z * h1;
+        acc[4 * g + 3].x += p.w * h0; acc[4 * g + 3].y += p.w * h1;
+      }
     }
   }
-  if (wave > 0) {
 #pragma unroll
-    for (int r = 0; r < kMaxBeam; ++r)
-      if (r < beam) { red[wave - 1][2 * r][lane] = acc[r][0]; red[wave - 1][2 * r + 1][lane] = acc[r][1]; }
-  }
+  for (int r = 0; r < NB; ++r) red[wave][r][lane] = acc[r];
   __syncthreads();
   if (blockIdx.x == gridDim.x - 1 && r_own < beam) {            // one work-group of the sentence writes the weights
     const float inv = inv_z[r_own];
@@ -275,22 +272,22 @@ __global__ __launch_bounds__(256) void att_context_kernel(const uint16_t* __rest
       for (int u = 0; u < kP; ++u) {
         const int j = j0 + 16 * u;
         if (j >= S) break;
-        const float p = j < L ? w[j * kMaxBeam + r_own] * inv : 0.f;
+        const float p = j < L ? w[j * NB + r_own] * inv : 0.f;
         if (a_out) a_out[row_own * S + j] = p;
         accum_out[row_own * S + j] = j < L ? before[u] + p : 0.f;
       }
     }
   }
-  if (wave > 0 || !live) return;
+  if (!live) return;
 #pragma unroll
-  for (int r = 0; r < kMaxBeam; ++r)
-    if (r < beam) {
-      const float inv = inv_z[r];
-      const float s0 = (acc[r][0] + red[0][2 * r][lane] + red[1][2 * r][lane] + red[2][2 * r][lane]) * inv;
-      const float s1 = (acc[r][1] + red[0][2 * r + 1][lane] + red[1][2 * r + 1][lane] + red[2][2 * r + 1][lane]) * inv;
-      const unsigned o = (unsigned)f2bf_bits(s0) | ((unsigned)f2bf_bits(s1) << 16);
-      *(unsigned*)(att + ((long)q * beam + r) * ldatt + f) = o;
-    }
+  for (int i = 0; i < NB / 4; ++i) {                            // (the wavefronts' sums, a quarter of the hypotheses each)
+    const int r = 4 * i + wave;
+    if (r >= beam) break;
+    const float inv = inv_z[r];
+    const float2 s0 = red[0][r][lane], s1 = red[1][r][lane], s2 = red[2][r][lane], s3 = red[3][r][lane];
+    const unsigned o = (unsigned)f2bf_bits((s0.x + s1.x + s2.x + s3.x) * inv) | ((unsigned)f2bf_bits((s0.y + s1.y + s2.y + s3.y) * inv) << 16);
+    *(unsigned*)(att + ((long)q * beam + r) * ldatt + f) = o;
+  }
 }
 
 // out = bfloat16(max(0, z)) for a float z[M][N] that already holds product + bias
@@ -406,12 +403,18 @@ int lstm_attention_step(const lstm_att_desc* d, const void* enc, const void* enc
                        d->S, d->Q, d->beam, d->A);
   static std::atomic<unsigned long long> attr_set{0};            // S = 1024 needs 64 KiB of dynamic LDS beside the static arrays
   if (once_per_device(attr_set, [] {
-        return hipFuncSetAttribute((const void*)att_context_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxS * kMaxBeam * 4);
+        for (const void* kernel : {(const void*)att_context_kernel<4>, (const void*)att_context_kernel<8>, (const void*)att_context_kernel<12>, (const void*)att_context_kernel<16>}) {
+          const hipError_t err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxS * kMaxBeam * 4);
+          if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
       }) != hipSuccess) {
     (void)hipGetLastError();
     return LSTM_ERR_HIP;
   }
-  hipLaunchKernelGGL(att_context_kernel, dim3((d->E / 2 + 63) / 64, d->Q), dim3(256), (size_t)d->S * kMaxBeam * 4, st, (const uint16_t*)enc,
+  const int nb = (d->beam + 3) / 4 * 4;
+  hipLaunchKernelGGL(nb == 4 ? att_context_kernel<4> : nb == 8 ? att_context_kernel<8> : nb == 12 ? att_context_kernel<12> : att_context_kernel<16>,
+                     dim3((d->E / 2 + 63) / 64, d->Q), dim3(256), (size_t)d->S * nb * 4, st, (const uint16_t*)enc,
                      e, accum_in, src_lens, a, accum_out, (uint16_t*)att, (long)ld_att, d->S, d->Q, d->beam, d->E);
   if (hipGetLastError() != hipSuccess) return LSTM_ERR_HIP;
   return LSTM_OK;

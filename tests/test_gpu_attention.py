@@ -68,6 +68,13 @@ def test_attention_step_matches_oracle(over):
             assert np.all(got["att"][r].float().cpu().numpy() == 0)
 
 
+@pytest.mark.parametrize("beam,S", [(3, 1), (4, 63), (6, 64), (8, 65), (9, 66), (12, 129), (13, 64), (15, 200)])
+def test_attention_step_forms(beam, S):
+    """Beams inside and at the end of each group of four, positions around the 64 that are fetched at once."""
+    test_attention_step_matches_oracle(dict(Q=2, beam=beam, len_lo=S, len_hi=S, A=72, E=132, n=24))
+    test_attention_step_matches_oracle(dict(Q=3, beam=beam, len_lo=0, len_hi=S, A=72, E=132, n=24))
+
+
 def test_attention_step_without_lengths_and_into_a_wider_row():
     inp = synth.make_decoder(Q=3, beam=4, len_lo=11, len_hi=11, A=128, E=256, n=64)
     wide = torch.full((inp["B"], 64 + 20 + 256), 7.0, dtype=torch.bfloat16, device="cuda")
