@@ -762,9 +762,9 @@ def main():
         step_bytes = layer_bytes / T
         tr_bytes = None if per_step_path else traffic.get(phase)
         # the recurrent product itself (h W_h or dz W_h^T: 8 n^2 flops per real frame of a row) against the MFMA peak of
-        # the storage type: what bounds the float single-launch kernel (the float MFMA runs at 1/16 of the bf16 rate)
+        # the storage type: a float product is six bfloat16 ones of three-part operands
         rec_tflops = 8.0 * n * n * frames * 2 / (layer_ms * 1e-3) / 1e12 if ms > 0 else 0.0
-        mfma_peak_loop = BF16_PEAK_TFLOPS if esz == 2 else 157.3
+        mfma_peak_loop = BF16_PEAK_TFLOPS if esz == 2 else BF16_PEAK_TFLOPS / 6
         return {"bound": "hbm", "kernel": name + (" (one launch per time step)" if per_step_path else ""),
                 "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": tr_bytes,
@@ -790,7 +790,7 @@ def main():
     per_product = {k: (v * args.steps / (prof[k][0] * 1e-3) / 1e12 if prof[k][0] > 0 else 0.0) for k, v in gemm_flops.items()}
     gemm_ms = sum(prof[k][0] for k in gemm_flops)
     gemm_tflops = sum(gemm_flops.values()) * args.steps / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 else 0.0
-    mfma_peak = BF16_PEAK_TFLOPS if esz == 2 else 157.3
+    mfma_peak = BF16_PEAK_TFLOPS if esz == 2 else BF16_PEAK_TFLOPS / 6
     dominant = roof_bwd if prof["loop_bwd"][0] >= prof["loop_fwd"][0] else roof_fwd
 
     out = {
