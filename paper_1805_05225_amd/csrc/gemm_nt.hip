@@ -328,7 +328,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
 // ---------------------------------------------------------------------------------------------------------
 // The weight-gradient shape, C[M,N] = sum_k A[k][m] B[k][n] with BOTH operands stored k-major (a row per frame:
 // dW_x = X^T DZ, dW_h = Hprev^T DZ; float C), without transposing anything in memory.  Same tile, wavefront
-// layout, stage pipeline and epilogue as gemm_dl_body; what differs is how a stage sits in LDS and how MFMA
+// layout and epilogue as gemm_dl_body; what differs is how a stage sits in LDS and how MFMA
 // fragments leave it:
 //   * a stage is 64 k-rows of 256 columns (512 bytes) per operand; a wavefront-load brings two whole rows (full
 //     lines).  Row k may be any row of the operand in memory (`k_rows`: the packed list of real frames), looked up
@@ -339,10 +339,15 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
 //     of rows kbase .. kbase+3 (layout measured on the device).  Two such reads make one MFMA operand;
 //   * the four rows a 16-lane group reads together lie 512 bytes apart, i.e. in the same banks; so the 64-byte
 //     blocks of row k are stored XORed with k % 4 (again by choosing which global chunk a loading lane fetches).
-template <typename TC>
+// A stage is four phases, one k-step of all eight blocks each, run as in gemm_dl_body: reads, meeting, products, meeting, with four of the
+// wavefronts half a phase behind.  Sixteen k-rows of both operands are one wavefront-load per operand and wavefront; their place is free for the
+// stage after next once all have read them, so they go out in the next phase and have seven phases to arrive, 112 KiB on their way.
+// Before, a stage's loads went out between the products of one k-step and were waited for a stage later, at a barrier all wavefronts met at once: dW_x of 31597
+// frames (2048 x 4096, two directions) 987 TFLOP/s, of 3054 (2000 x 4000) 801; now 1226 and 953.
+template <typename TC, bool ROWS>                              // ROWS: the k-rows are those of a list (k_rows)
 __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int TN = 2, WN = 4, NW = 8, NLD = 4;               // 8 wavefronts of 128x64; 4 wavefront-loads per operand
+  constexpr int TN = 2, WN = 4, NW = 8, NS = 4;                // 8 wavefronts of 128x64; k-steps of a stage = wavefront-loads per operand
   constexpr int kRow = 512;                                    // bytes per k-row of a stage (256 columns)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -362,60 +367,43 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 
   const int total = (K + kKB - 1) / kKB;                       // stages; rows past K arrive as zeros
 
-  // Loads.  Wavefront-load i of this wavefront fills k-rows 2*(i*NW + wave) and +1 of the stage; lane l fills
+  // Loads.  The wavefront-load of k-step q fills k-rows 2*(q*NW + wave) and +1 of the stage; lane l fills
   // 16-byte slot l % 32 of row l / 32, i.e. fetches column chunk (l % 32) ^ 4*(k % 4).
-  const int krow_in_stage = 2 * wave + (lane >> 5);            // + 2*NW*i
-  const int chunk = (lane & 31) ^ (4 * (krow_in_stage & 3));   // 2*NW*i is a multiple of 4
+  const int krow_in_stage = 2 * wave + (lane >> 5);            // + 2*NW*q
+  const int chunk = (lane & 31) ^ (4 * (krow_in_stage & 3));   // 2*NW*q is a multiple of 4
   const bool a_col_ok = m0 + chunk * 8 < M, b_col_ok = n0 + chunk * 8 < g.N;
-  const long a_col = ((long)m0 + chunk * 8) * 2, b_col = ((long)n0 + chunk * 8) * 2;
-  const long a_rows_mem = g.k_rows ? g.k_phys_rows : K;
-  const long a_bytes = a_rows_mem * g.lda * 2, b_bytes = a_rows_mem * g.ldb * 2;
+  const unsigned a_col = (m0 + chunk * 8) * 2, b_col = (n0 + chunk * 8) * 2, lda2 = (unsigned)g.lda * 2, ldb2 = (unsigned)g.ldb * 2;
+  const unsigned rows_mem = ROWS ? (unsigned)g.k_phys_rows : (unsigned)K;
+  const long a_bytes = (long)rows_mem * g.lda * 2, b_bytes = (long)rows_mem * g.ldb * 2;
   const unsigned a_rec = a_bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)a_bytes, b_rec = b_bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)b_bytes;
   const u32x4 ra = make_rsrc(g.A + g.sAz * z * 2, a_rec), rb = make_rsrc(g.B + g.sBz * z * 2, b_rec);
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)lds;
-  // Work-groups that run side by side on an XCD all want the same 64 frame rows of a stage; each starts its burst
-  // of wavefront-loads with a different quarter of them, so that the first request for a line goes out early in
-  // some work-group's burst.
-  const int rot = (int)(blockIdx.x >> 3) % NLD;
   // Memory rows of the stage whose loads go out next.  A wavefront-load covers rows k and k+1 of the list, the same
   // for all lanes of a half, so the look-up is a scalar load of two consecutive entries - written as assembly and
-  // waited for by hand (together with the operand loads, before the barrier of the next stage): the compiler would
-  // wait for a look-up it knows about right where it is issued, and with vector loads that wait would also
-  // cover every operand load in flight.  The list must be readable up to the next multiple of 64 entries.
+  // waited for by hand, a phase later: the compiler would wait for a look-up it knows about right where it is issued, and with vector loads
+  // that wait would also cover every operand load in flight.  The list must be readable up to the next multiple of 64 entries.
   typedef __attribute__((ext_vector_type(2))) int i32x2;
-  i32x2 prow2[NLD];
-  int pk0 = 0;
+  i32x2 prow[NS];
   auto lookup = [&](int it) __attribute__((always_inline)) {
-    pk0 = it * kKB + krow_in_stage;                // k of wavefront-load 0 for this lane; load i adds 2 * NW * i
-    if (g.k_rows && it < total) {
+    if constexpr (ROWS) {
+      const int* p = g.k_rows + (long)min(it, total - 1) * kKB + 2 * wave;        // (past the last stage `issue` looks at no row)
 #pragma unroll
-      for (int i = 0; i < NLD; ++i) {
-        const int* p = g.k_rows + (long)it * kKB + 2 * (NW * ((i + rot) % NLD) + wave);
-        asm volatile("s_load_dwordx2 %0, %1, 0x0" : "=s"(prow2[i]) : "s"(p) : "memory");
-      }
+      for (int q = 0; q < NS; ++q) asm volatile("s_load_dwordx2 %0, %1, %2" : "=s"(prow[q]) : "s"(p), "n"(q * 2 * NW * 4) : "memory");
     }
   };
-  auto row_of = [&](int i) __attribute__((always_inline)) {
-    return g.k_rows ? ((lane >> 5) ? prow2[i][1] : prow2[i][0]) : pk0 + 2 * NW * ((i + rot) % NLD);
+  auto looked_up = [&]() __attribute__((always_inline)) {
+    if constexpr (ROWS) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(prow[0]), "+s"(prow[1]), "+s"(prow[2]), "+s"(prow[3])::"memory");
   };
-  auto issue = [&](int buf, int first, int last) __attribute__((always_inline)) {
-    const unsigned dst = lds_base + buf * kDlStage + wave * 1024;
-#pragma unroll
-    for (int q = 0; q < 2 * NLD; ++q) {
-      if (q < first || q >= last) continue;
-      const int i = q >> 1;
-      const int row = row_of(i), ir = (i + rot) % NLD;
-      const bool row_ok = pk0 + 2 * NW * ir < K && row >= 0 && row < a_rows_mem;
-      if (q & 1) {
-        const long o = (long)row * g.ldb * 2 + b_col;
-        load_to_lds_b128(rb, dst + kDlOp + ir * NW * 1024, (row_ok && b_col_ok && o <= 0x7ffffff0L) ? (unsigned)o : 0x7ffffff0u, 0);
-      } else {
-        const long o = (long)row * g.lda * 2 + a_col;
-        load_to_lds_b128(ra, dst + ir * NW * 1024, (row_ok && a_col_ok && o <= 0x7ffffff0L) ? (unsigned)o : 0x7ffffff0u, 0);
-      }
-    }
+  // (past K, also past the last stage, with every lane outside the descriptor: the counted waits below count these loads)
+  auto issue = [&](int it, int q) __attribute__((always_inline)) {
+    const unsigned dst = lds_base + (it & 1) * kDlStage + (q * NW + wave) * 1024;
+    const int k = it * kKB + 2 * NW * q + krow_in_stage;
+    const int row = ROWS ? ((lane >> 5) ? prow[q][1] : prow[q][0]) : k;
+    const bool row_ok = (k < K) & ((unsigned)row < rows_mem);
+    const unsigned oa = (unsigned)row * lda2 + a_col, ob = (unsigned)row * ldb2 + b_col;           // (below 2^31: gemm_tn_ok)
+    load_to_lds_b128(ra, dst, (row_ok & a_col_ok) ? oa : 0x7ffffff0u, 0);
+    load_to_lds_b128(rb, dst + kDlOp, (row_ok & b_col_ok) ? ob : 0x7ffffff0u, 0);
   };
-  constexpr int NQ = 2 * NLD;
 
   // Fragment reads (see the head of this function).  Lane L = 32*kg + 16*grp + l: source row kg*8 + l/4 (+4 for the
   // second read) of the 16-row k-step, columns block*32 + grp*16 + 4*(l%4) .. +3, 64-byte blocks XORed with row % 4.
@@ -427,73 +415,82 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 #pragma unroll
   for (int j = 0; j < TN; ++j) fb_off[j] = kDlOp + fr_row + ((((wn * TN + j) ^ fr_sw) & 7) << 6) + fr_low;
   typedef __attribute__((ext_vector_type(4))) short s16x4;
-  uint4 fa[2][4], fb[2][TN];
+  uint4 fa[4], fb[TN];
   auto tr_read = [&](const char* p) __attribute__((always_inline)) {
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 4 * kRow));
     const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
     return make_uint4(l2.x, l2.y, h2.x, h2.y);
   };
-  auto read_frags = [&](int buf, int s, int c) __attribute__((always_inline)) {
-    const char* base = lds + buf * kDlStage + s * 16 * kRow;
+  auto read_frags = [&](int it, int s) __attribute__((always_inline)) {
+    const char* base = lds + (it & 1) * kDlStage + s * 16 * kRow;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fa[c][i] = tr_read(base + fa_off[i]);
+    for (int i = 0; i < 4; ++i) fa[i] = tr_read(base + fa_off[i]);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[c][j] = tr_read(base + fb_off[j]);
+    for (int j = 0; j < TN; ++j) fb[j] = tr_read(base + fb_off[j]);
   };
-  auto kstep = [&](int c, bool ld, int ld_buf) __attribute__((always_inline)) {
-    int q = 0;
+  auto meet = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+  };
+  // The end of a phase's reading half: its reads have returned, and the loads of the next phase's k-step have landed (twelve younger ones).
+  auto end_of_reads = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x007c);                        // vmcnt(12) lgkmcnt(0)
+    meet();
+  };
+  auto multiply = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        acc[i][j] = mma(fa[c][i], fb[c][j], acc[i][j]);
-        if (((i * TN + j) & 1) && q < NQ) {
-          if (ld) issue(ld_buf, q, q + 1);
-          ++q;
-        }
-      }
-    if (q < NQ && ld) issue(ld_buf, q, NQ);
+      for (int j = 0; j < TN; ++j) acc[i][j] = mma(fa[i], fb[j], acc[i][j]);
+    __builtin_amdgcn_s_setprio(0);
+    meet();
   };
 
   if (total > 0) {
     lookup(0);
-    __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0): the look-up
-    issue(0, 0, NQ);
+    looked_up();
+#pragma unroll
+    for (int q = 0; q < NS; ++q) issue(0, q);
     lookup(1);
-    __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0) lgkmcnt(0)
-    __syncthreads();
-    if (total > 1) issue(1, 0, NQ);
-    lookup(2);
-    read_frags(0, 0, 0);
-  }
-  for (int it = 0; it < total; ++it) {
-    const int cur = it & 1;
-    read_frags(cur, 1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(0, false, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(cur, 2, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(1, false, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(cur, 3, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(0, false, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (it + 1 < total) {
-      __builtin_amdgcn_s_waitcnt(0x0070);          // vmcnt(0) lgkmcnt(0): own loads of stage it+1 (and row look-ups) landed, own reads done
-      __syncthreads();
-      read_frags(cur ^ 1, 0, 0);
+    looked_up();
+#pragma unroll
+    for (int q = 0; q < 3; ++q) issue(1, q);
+    __builtin_amdgcn_s_waitcnt(0x0f7c);                        // vmcnt(12): the first k-step's
+    meet();
+    if (wm == 1) meet();                                       // the second four wavefronts stay half a phase behind
+    for (int it = 0; it < total; ++it) {
+      read_frags(it, 0);
+      issue(it + 1, 3);
+      end_of_reads();
+      lookup(it + 2);
+      multiply();
+      read_frags(it, 1);
+      looked_up();
+      issue(it + 2, 0);
+      end_of_reads();
+      multiply();
+      read_frags(it, 2);
+      issue(it + 2, 1);
+      end_of_reads();
+      multiply();
+      read_frags(it, 3);
+      issue(it + 2, 2);
+      end_of_reads();
+      multiply();
     }
-    __builtin_amdgcn_sched_barrier(0);
-    kstep(1, it + 2 < total, cur);                 // loads of stage it+2 (rows looked up during the previous stage)
-    __builtin_amdgcn_sched_barrier(0);
-    lookup(it + 3);
+    if (wm == 0) meet();
+    __builtin_amdgcn_s_waitcnt(0x0f70);                        // vmcnt(0): the epilogue uses LDS
   }
   store_tile<TC, TN>(acc, lds, g, M, m0, n0, z);
 }
-__global__ __launch_bounds__(512, 1) void gemm_tn8_f32_kernel(NtArgs g) { gemm_tn_body<float>(g); }
+template <bool ROWS> __global__ __launch_bounds__(512, 1) void gemm_tn8_f32_kernel(NtArgs g) { gemm_tn_body<float, ROWS>(g); }
 
 // (kernels with literal launch bounds: a bound that depends on a template parameter loses the host-side stub)
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_kernel(NtArgs g) { gemm_dl_body<float, RAGGED>(g); }
@@ -608,10 +605,11 @@ hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s) {
   const int tiles = a.blocked ? cdiv(sups, 8) * 8 * kSupM * kSupN : cdiv(g.M, kT) * cdiv(g.N, kT);
   static std::atomic<unsigned long long> attr_set{0};
   const hipError_t ea = once_per_device(attr_set, [] {
-    return hipFuncSetAttribute((const void*)gemm_tn8_f32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
+    const hipError_t e = hipFuncSetAttribute((const void*)gemm_tn8_f32_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
+    return e != hipSuccess ? e : hipFuncSetAttribute((const void*)gemm_tn8_f32_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
   });
   if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL(gemm_tn8_f32_kernel, dim3(tiles, g.nz), dim3(512), kDlLds, s, a);
+  hipLaunchKernelGGL(g.k_rows ? gemm_tn8_f32_kernel<true> : gemm_tn8_f32_kernel<false>, dim3(tiles, g.nz), dim3(512), kDlLds, s, a);
   return hipGetLastError();
 }
 

@@ -290,3 +290,22 @@ def test_phase_times_name_every_product(dt, T, B, n_in, n):
 def test_narrow_layer_widths(dt, n):
     """W_h of a narrow layer is read by 16 bytes where its rows allow it, by single elements elsewhere; one step more than inputs are asked for ahead."""
     _layer(5, 6, 24, n, True, dt)
+
+
+@pytest.mark.parametrize("M,N", [(3600, 3592), (4088, 3608)])
+@pytest.mark.parametrize("K", [1, 16, 17, 48, 63, 64, 65, 127, 128, 129, 250])
+def test_weight_gradient_product_stages(M, N, K):
+    """Products of more than 200 tiles of 256 x 256, both operands k-major: one to four stages, k-steps that are part or all past K, ragged tiles."""
+    import torch
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator().manual_seed(M + K)
+    A, B = torch.randn(K, M, generator=g).bfloat16().cuda(), torch.randn(K, N, generator=g).bfloat16().cuda()
+    got = Bn.gemm(A, B, a_kcontig=False, b_kcontig=False, M=M, N=N, K=K)
+    ref = A.double().t().contiguous() @ B.double()
+    assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max())          # (exact inputs: the order of float sums)
+
+
+@pytest.mark.parametrize("T,B", [(1, 16), (5, 13), (9, 16), (13, 16), (30, 16)])
+def test_weight_gradients_over_listed_frames(T, B):
+    """The same product walking the list of real frames: fewer than a stage, one, and several."""
+    _layer(T, B, 2048, 1024, True, "bf16")
