@@ -96,6 +96,10 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s);
 // float C.  Row k of both operands is row k_rows[k] in memory if k_rows is given (launch_gemm routes to it by itself).
 bool gemm_tn_ok(const GemmArgs& g);
 hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s);
+// The same with K in gemm_tn_ranges(g) ranges (1: not worth it, or no room), whose parts go to `parts` and are added as gemm_tile's are.
+int gemm_tn_ranges(const GemmArgs& g);
+size_t gemm_tn_parts_bytes(long M, long N, long K, int nz);
+hipError_t launch_gemm_tn_ranges(const GemmArgs& g, hipStream_t s);
 // bfloat16 products with few 256 x 256 tiles, and A k-contiguous x B k-major at any size (gemm_tile.hip; launch_gemm routes to it by itself).
 // It cuts K into ranges of its own if `parts` holds gemm_tile_parts_bytes.
 bool gemm_tile_ok(const GemmArgs& g);

@@ -28,6 +28,7 @@ struct NtArgs {
   const int* k_rows; int k_phys_rows;     // k-major kernel: k -> row of A and B in memory (NULL: identity), rows in memory
   const int* m_dev; const int* k_dev;     // device-resident M / K (NULL: use M / K above)
   int a_phys_rows;                        // rows of A in memory when a_rows is given
+  int ksplit;                             // k-major kernel: K ranges, each a z of its own (0: one)
   int blocked;                            // tile raster: 1 = blocks of kSupM x kSupN tiles per XCD, 0 = bands of 8 tile columns
 };
 
@@ -344,7 +345,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
 // stage after next once all have read them, so they go out in the next phase and have seven phases to arrive, 112 KiB on their way.
 // Before, a stage's loads went out between the products of one k-step and were waited for a stage later, at a barrier all wavefronts met at once: dW_x of 31597
 // frames (2048 x 4096, two directions) 987 TFLOP/s, of 3054 (2000 x 4000) 801; now 1226 and 953.
-template <typename TC, bool ROWS>                              // ROWS: the k-rows are those of a list (k_rows)
+template <typename TC, bool ROWS, bool RANGES>                 // ROWS: the k-rows are those of a list (k_rows); RANGES: K in ksplit ranges
 __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   constexpr int TN = 2, WN = 4, NW = 8, NS = 4;                // 8 wavefronts of 128x64; k-steps of a stage = wavefront-loads per operand
@@ -355,7 +356,7 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 
   const TileCoord tc = tile_coord(g);
   if (!tc.live) return;
-  const int M = tc.M, K = tc.K, m0 = tc.m0, n0 = tc.n0, z = tc.z;
+  const int M = tc.M, K = tc.K, m0 = tc.m0, n0 = tc.n0, ks = RANGES ? g.ksplit : 1, z = RANGES ? tc.z / ks : tc.z;
 
   f32x16 acc[4][TN];
 #pragma unroll
@@ -365,7 +366,8 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  const int total = (K + kKB - 1) / kKB;                       // stages; rows past K arrive as zeros
+  const int stages = (K + kKB - 1) / kKB, each = (stages + ks - 1) / ks, first = RANGES ? (tc.z - z * ks) * each : 0;       // rows past K arrive as zeros
+  const int total = RANGES ? min(each, stages - first) : stages;         // this range's (0 or less: its part is zeros)
 
   // Loads.  The wavefront-load of k-step q fills k-rows 2*(q*NW + wave) and +1 of the stage; lane l fills
   // 16-byte slot l % 32 of row l / 32, i.e. fetches column chunk (l % 32) ^ 4*(k % 4).
@@ -386,7 +388,7 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
   i32x2 prow[NS];
   auto lookup = [&](int it) __attribute__((always_inline)) {
     if constexpr (ROWS) {
-      const int* p = g.k_rows + (long)min(it, total - 1) * kKB + 2 * wave;        // (past the last stage `issue` looks at no row)
+      const int* p = g.k_rows + (long)(first + min(it, total - 1)) * kKB + 2 * wave;        // (past the last stage `issue` looks at no row)
 #pragma unroll
       for (int q = 0; q < NS; ++q) asm volatile("s_load_dwordx2 %0, %1, %2" : "=s"(prow[q]) : "s"(p), "n"(q * 2 * NW * 4) : "memory");
     }
@@ -397,7 +399,7 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
   // (past K, also past the last stage, with every lane outside the descriptor: the counted waits below count these loads)
   auto issue = [&](int it, int q) __attribute__((always_inline)) {
     const unsigned dst = lds_base + (it & 1) * kDlStage + (q * NW + wave) * 1024;
-    const int k = it * kKB + 2 * NW * q + krow_in_stage;
+    const int k = RANGES && it >= total ? K : (first + it) * kKB + 2 * NW * q + krow_in_stage;
     const int row = ROWS ? ((lane >> 5) ? prow[q][1] : prow[q][0]) : k;
     const bool row_ok = (k < K) & ((unsigned)row < rows_mem);
     const unsigned oa = (unsigned)row * lda2 + a_col, ob = (unsigned)row * ldb2 + b_col;           // (below 2^31: gemm_tn_ok)
@@ -488,9 +490,9 @@ __device__ __forceinline__ void gemm_tn_body(const NtArgs& g) {
     if (wm == 0) meet();
     __builtin_amdgcn_s_waitcnt(0x0f70);                        // vmcnt(0): the epilogue uses LDS
   }
-  store_tile<TC, TN>(acc, lds, g, M, m0, n0, z);
+  store_tile<TC, TN>(acc, lds, g, M, m0, n0, tc.z);
 }
-template <bool ROWS> __global__ __launch_bounds__(512, 1) void gemm_tn8_f32_kernel(NtArgs g) { gemm_tn_body<float, ROWS>(g); }
+template <bool ROWS, bool RANGES> __global__ __launch_bounds__(512, 1) void gemm_tn8_f32_kernel(NtArgs g) { gemm_tn_body<float, ROWS, RANGES>(g); }
 
 // (kernels with literal launch bounds: a bound that depends on a template parameter loses the host-side stub)
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_kernel(NtArgs g) { gemm_dl_body<float, RAGGED>(g); }
@@ -593,24 +595,65 @@ bool gemm_tn_ok(const GemmArgs& g) {
          g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B);
 }
 
-hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0 || g.nz <= 0) return hipSuccess;
+namespace {
+hipError_t launch_tn(const GemmArgs& g, int ks, hipStream_t s) {
   NtArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
   a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz; a.nseg = 1;
   a.accumulate = g.accumulate; a.k_dev = g.k_dev; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
+  if (ks > 1) {
+    a.ksplit = ks; a.nz = g.nz * ks; a.accumulate = false; a.bias = nullptr;
+    a.C = g.parts; a.ldc = (g.N + 3) / 4 * 4; a.sCz = (long)g.M * a.ldc;
+  }
   const int sups = cdiv(cdiv(g.M, kT), kSupM) * cdiv(cdiv(g.N, kT), kSupN);
   a.blocked = sups >= 32 ? 1 : 0;
   const int tiles = a.blocked ? cdiv(sups, 8) * 8 * kSupM * kSupN : cdiv(g.M, kT) * cdiv(g.N, kT);
   static std::atomic<unsigned long long> attr_set{0};
   const hipError_t ea = once_per_device(attr_set, [] {
-    const hipError_t e = hipFuncSetAttribute((const void*)gemm_tn8_f32_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
-    return e != hipSuccess ? e : hipFuncSetAttribute((const void*)gemm_tn8_f32_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
+    for (const void* k : {(const void*)gemm_tn8_f32_kernel<false, false>, (const void*)gemm_tn8_f32_kernel<true, false>,
+                          (const void*)gemm_tn8_f32_kernel<false, true>, (const void*)gemm_tn8_f32_kernel<true, true>}) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   });
   if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL(g.k_rows ? gemm_tn8_f32_kernel<true> : gemm_tn8_f32_kernel<false>, dim3(tiles, g.nz), dim3(512), kDlLds, s, a);
+  const auto whole = g.k_rows ? gemm_tn8_f32_kernel<true, false> : gemm_tn8_f32_kernel<false, false>;
+  const auto ranged = g.k_rows ? gemm_tn8_f32_kernel<true, true> : gemm_tn8_f32_kernel<false, true>;
+  hipLaunchKernelGGL(ks > 1 ? ranged : whole, dim3(tiles, a.nz), dim3(512), kDlLds, s, a);
   return hipGetLastError();
+}
+// Products of few tiles whose K is long (dW_h of a long batch): as many K ranges as fill the device, at least seven eighths of it, with tiles of which no more than
+// a tenth lies outside C.  Parts of the whole device are 64 MiB, written and read, 30 us; the 128 x 128 tiles of gemm_tile.hip run at
+// 0.7 of this kernel's rate, which is 11 ns per k of a range: even at 2700 real frames a range.  K counts padded frames too, so the line is at 6144.
+// dW_h of 31597 frames (1024 x 4096, both directions) in two ranges: 874 -> 1058 TFLOP/s, sums included.
+int tn_ranges(long M, long N, long K, int nz) {
+  const long tiles = (M + kT - 1) / kT * ((N + kT - 1) / kT) * nz;
+  if (tiles <= 0 || tiles > 128 || M * N * nz * 10 < tiles * kT * kT * 9) return 1;
+  const long ks = 256 / tiles;
+  return tiles * ks >= 224 && K >= 6144 * ks ? (int)ks : 1;
+}
+}  // namespace
+
+size_t gemm_tn_parts_bytes(long M, long N, long K, int nz) {
+  const int ks = tn_ranges(M, N, K, nz);
+  return ks > 1 ? (size_t)ks * nz * M * ((N + 3) / 4 * 4) * 4 : 0;
+}
+int gemm_tn_ranges(const GemmArgs& g) {
+  const size_t need = gemm_tn_parts_bytes(g.M, g.N, g.K, g.nz);
+  return need && g.parts && need <= g.parts_bytes && gemm_tn_ok(g) ? tn_ranges(g.M, g.N, g.K, g.nz) : 1;
+}
+hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s) { return g.M <= 0 || g.N <= 0 || g.nz <= 0 ? hipSuccess : launch_tn(g, 1, s); }
+hipError_t launch_gemm_tn_ranges(const GemmArgs& g, hipStream_t s) {
+  const int ks = gemm_tn_ranges(g);
+  if (ks == 1) return launch_gemm_tn(g, s);
+  const hipError_t e = launch_tn(g, ks, s);
+  if (e != hipSuccess) return e;
+  SumJob j = {};
+  j.parts = g.parts; j.C = g.C; j.bias = g.bias; j.M = g.M; j.N = g.N; j.ksplit = ks; j.nz = g.nz;
+  j.ldp = (g.N + 3) / 4 * 4; j.sPz = (long)ks * g.M * j.ldp; j.ldc = g.ldc; j.sCz = g.sCz; j.sbiasz = g.sbiasz; j.accumulate = g.accumulate;
+  return finish_parts(j, gemm_tn_parts_bytes(g.M, g.N, g.K, g.nz), g.sums, s);
 }
 
 hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {

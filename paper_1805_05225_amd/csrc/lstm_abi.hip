@@ -166,8 +166,8 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   size_t tp = TB > 0 && (p->zx_nn || !p->bf16) && !p->single_step ? tile_parts(TB, 4L * d->n, p->n_in8, p->D, 1, true) : 0;
   if (TB > 0) tp = std::max(tp, tile_parts(d->B, 4L * d->n, p->ldh, 1, 1, false));      // (h0 W_h)
   if (!infer && TB > 0)                   // (the backward products' are added together at the end)
-    tp = std::max(tp, up(tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true)) + up(tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false)) +
-                          up(tile_parts(d->n, 4L * d->n, TB, p->D, 1, false)));
+    tp = std::max(tp, up(tile_parts(TB, d->n_in, 4L * d->n, 1, p->D, true)) + up(std::max(tile_parts(d->n_in, 4L * d->n, TB, p->D, 1, false), fg ? gemm_tn_parts_bytes(d->n_in, 4L * d->n, TB, p->D) : 0)) +
+                          up(std::max(tile_parts(d->n, 4L * d->n, TB, p->D, 1, false), fg ? gemm_tn_parts_bytes(d->n, 4L * d->n, TB, p->D) : 0)));
   p->parts_bytes = tp;
   p->ws_parts = take(p->parts_bytes);
   p->blocks = p->bf16 && loop_block_width(d->n) && !(d->flags & LSTM_FLAG_PER_STEP) && d->T >= 2 && TB > 0;
@@ -888,7 +888,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h);
     const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
     if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
-      const bool pair = gx.parts && gh.parts;    // both in few tiles
+      const bool pair = gx.parts && gh.parts && gemm_tn_ranges(gx) == 1 && gemm_tn_ranges(gh) == 1;    // both in few tiles
       {
         Phase ph({{LSTM_PHASE_GEMM_DWX, (double)p.n_in}, {LSTM_PHASE_GEMM_DWH, pair ? (double)n : 0.0}}, 1, s);
         if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
@@ -896,11 +896,11 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           HIPCHK(launch_gemm_tile_pair(gx, gh, s));
           return LSTM_OK;
         }
-        HIPCHK(launch_gemm(gx, s));
+        HIPCHK(gemm_tn_ranges(gx) > 1 ? launch_gemm_tn_ranges(gx, s) : launch_gemm(gx, s));
       }
       Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
       if (gh.parts) parts_of(gh);
-      HIPCHK(launch_gemm(gh, s));
+      HIPCHK(gemm_tn_ranges(gh) > 1 ? launch_gemm_tn_ranges(gh, s) : launch_gemm(gh, s));
     } else {                         // dW_x = X^T DZ, padded frames of X masked out
       GemmArgs g = {};
       g.A = x; g.B = DZ; g.C = dW_x;

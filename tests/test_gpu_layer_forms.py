@@ -309,3 +309,30 @@ def test_weight_gradient_product_stages(M, N, K):
 def test_weight_gradients_over_listed_frames(T, B):
     """The same product walking the list of real frames: fewer than a stage, one, and several."""
     _layer(T, B, 2048, 1024, True, "bf16")
+
+
+@pytest.mark.parametrize("n,n_in", [(1024, 1024), (1000, 40), (512, 72)])
+def test_weight_gradients_in_ranges_of_frames(n, n_in):
+    """Few tiles and many frames: K ranges on the 256 x 256 kernel (for n = 512 four of them), of real frames that end inside one.  Rows do not interact, so the weight
+    gradients are the sums of those of four quarters, which are too short for ranges; a value in bfloat16 may round the other way."""
+    import torch
+    from paper_1805_05225_amd import binding as Bn
+    T, B = 840, 32
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, device="cuda")
+    x, dy = rnd(T, B, n_in).bfloat16(), rnd(T, B, 2 * n).bfloat16()
+    W_x, W_h = (0.5 / n_in ** 0.5 * rnd(2, n_in, 4 * n)).bfloat16(), (0.5 / n ** 0.5 * rnd(2, n, 4 * n)).bfloat16()
+    lens = torch.randint(T // 2, T + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lens[0] = T
+
+    def grads(rows):
+        xs, dys, ls = x[:, rows].contiguous(), dy[:, rows].contiguous(), lens[rows].contiguous()
+        f = Bn.forward(xs, W_x, W_h, None, None, None, ls, bidirectional=True)
+        r = Bn.backward(f, xs, W_x, W_h, None, None, ls, dys)
+        assert not Bn.sync_status(f["workspace"])
+        return r
+    whole, lo, hi = grads(slice(0, B)), grads(slice(0, B // 4)), grads(slice(B // 4, B // 2))
+    hi2, hi3 = grads(slice(B // 2, 3 * B // 4)), grads(slice(3 * B // 4, B))
+    for k in ("dW_x", "dW_h"):
+        ref = lo[k].double() + hi[k].double() + hi2[k].double() + hi3[k].double()
+        assert float((whole[k].double() - ref).norm() / ref.norm()) < 2e-3, k
