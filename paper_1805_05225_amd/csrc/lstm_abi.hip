@@ -552,6 +552,14 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     if ((rc = project())) return rc;
     if (single) {
       if (h0 && (rc = h0_term(pa))) return rc;
+      // The fill behind rows one behind the other gives padded frames of a reversed direction the state that the call began with, and by then the
+      // loop has stored cT: a state in place (cT over c0) is read from a copy.
+      const float* c0_fill = (const float*)c0;
+      if (pa.slots > 0 && c && (pa.d[0].rev || pa.d[D - 1].rev) && bytes_overlap(c0, state_bytes, cT, state_bytes)) {
+        Phase ph(LSTM_PHASE_PREP, 1, s);
+        HIPCHK(launch_copy(cstate, c0, state_bytes, s));
+        c0_fill = cstate;
+      }
       hipError_t e;
       {
         Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
@@ -560,7 +568,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       if (e == hipErrorCooperativeLaunchTooLarge && h0) e = hipErrorLaunchFailure;   // the pre-activations are no longer what the per-step path expects
       if (e == hipSuccess && pa.slots > 0) {
         float* cs[2] = {pa.d[0].cs, pa.d[D - 1].cs};
-        const float* cz[2] = {pa.d[0].c0, pa.d[D - 1].c0};
+        const float* cz[2] = {c0_fill, c0_fill ? c0_fill + (D - 1) * B * n : nullptr};
         const int rev[2] = {pa.d[0].rev, pa.d[D - 1].rev};
         HIPCHK(launch_fill_padded(seq_lens, rows.steps, p.T, p.B, p.n, p.D, y, cs, cz, rev, s));
       }

@@ -118,6 +118,34 @@ def test_state_in_place(dt, T, B, n, direction):
         check(name, got, host(ref), TOL[dt])
 
 
+@pytest.mark.parametrize("T,B,n,bidir,lengths", [(12, 48, 1000, True, None), (9, 100, 1000, False, None),
+                                                 (30, 64, 1000, True, (30, 18))])      # (32 places: 48 steps, which only the forward loop takes so)
+def test_rows_one_behind_the_other_in_place(T, B, n, bidir, lengths):
+    """A training call with hT = h0 and cT = c0: the reversed direction's padded frames hold the state that the call began with, and the backward call,
+    which may read the state entering a row from there, gets the oracle's gradients."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(n + T)
+    lens = _lens(rng, T, B) if lengths is None else np.repeat(lengths, B // 2)
+    c = P.rnd_case(rng, T, B, 24, n, 2 if bidir else 1, lens, "bf16", scale=2.0 / np.sqrt(n))
+    d = -1
+    sq = (lambda a: a) if bidir else (lambda a: a[0])
+    x, dy, Wx, Wh = dev(c["x"], "bf16"), dev(c["dy"], "bf16"), dev(sq(c["W_x"]), "bf16"), dev(sq(c["W_h"]), "bf16")
+    b, h0, c0, dhT, dcT, ln = (dev(sq(c[k])) if k != "lens" else dev(c[k]) for k in ("b", "h0", "c0", "dhT", "dcT", "lens"))
+    f = Bn.forward(x, Wx, Wh, b, h0, c0, ln, bidirectional=bidir, direction=d, poison=True)      # (buffers and their sizes)
+    f["hT"], f["cT"] = h0.clone(), c0.clone()
+    for k in ("y", "c"):
+        f[k].fill_(float("nan"))
+    p = lambda t: t.data_ptr()
+    call = Bn.lib.blstm_fwd if bidir else Bn.lib.lstm_fwd
+    assert call(Bn.ctypes.byref(f["desc"]), p(x), p(Wx), p(Wh), p(b), p(f["hT"]), p(f["cT"]), p(ln), p(f["y"]), p(f["c"]), p(f["hT"]), p(f["cT"]),
+                p(f["reserve"]), p(f["workspace"]), Bn._stream()) == 0
+    assert not Bn.sync_status(f["workspace"])
+    g = Bn.backward(f, x, Wx, Wh, h0, c0, ln, dy, dhT, dcT)
+    assert not Bn.sync_status(f["workspace"])
+    P.compare(f, g, *P.run_oracle(c, bidir, d), TOL["bf16"])
+
+
 # Outside the range of what the loops exchange: the result is the per-step kernels', which exchange nothing between work-groups of a launch.
 @pytest.mark.parametrize("what", ["nan_x", "nan_W", "large_W", "inf_dy", "large_dy"])
 @pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 9, 1040), ("bf16", 24, 33, 2048), ("f32", 24, 9, 331), ("f32", 24, 40, 200), ("f32", 16, 17, 1000), ("f32", 16, 70, 1001)])
