@@ -23,11 +23,15 @@
 // sums of their own: what the matrix cores cut off where they add to a large sum would otherwise be cut off six times.  Against 64 bits the error is a
 // third of the float MFMA's (sum of K products of normal values, root mean square over that of the result: K = 64 0.5e-7 against 1.4e-7, 620
 // 1.4e-7 against 4.5e-7, 8000 5.7e-7 against 1.6e-6), for positive values half, and as large where single products dominate the
-// sums (lognormal, sigma 3).  What three bfloat16 cannot hold ends as NaN or infinity (infinities, values that round to one) or may be lost
-// (bits below 2^-134: only results below 2^-100 can feel it); a tile where a result says so is computed again with float MFMAs (16x16x4).
-// Bound by the splitting, 320 vector instructions for 96 products, which is therefore cut into the products (without that 4096^3 780 us, 740 with), and then by power
-// (zeros: 620 us).  4096^3: nn 1060 -> 750 us, nt 1025 -> 692, tn 1080 -> 742 (147 to 199 TFLOP/s, where float MFMAs have a peak of 157);
-// 1920 x 8000 x 620 200 -> 141 us.
+// sums (lognormal, sigma 3).
+// Both operands are multiplied by 2^24 before they are split: the last bit of the smallest float, 2^-149, is then a normal bfloat16 number, so the parts are exact for
+// every float below 2^104 in magnitude (as they stand, from 2^-110 up only: 2^-120 times 2^60 came out wrong by 6e-5 of itself).  What is not below that, and
+// sums from 2^80 on, end as NaN or infinity; a tile where a result says so is computed again with float MFMAs (16x16x4).  Nothing else depends on the values (small
+// results used to: dX of 2400 frames, 620 x 4000, ordinary gradients 188 us, ones that halve 300 times on their way back 448; now 199 and 198).
+// Bound by the splitting, 416 vector instructions of 4 cycles for 96 products of 16, which is therefore cut into the products, and by power.
+// 4096^3: nn 1060 -> 727 us, nt 1025 -> 702, tn 1080 -> 755 (182 to 196 TFLOP/s, where float MFMAs have a peak of 157);
+// 1920 x 8000 x 620 200 -> 121 us.  The factor's 64 instructions are 3 to 7 % of that (694, 655 and 728 without; differences by dot products of two
+// bfloat16, which drop the parts' unpacking, 787, 743 and 787).
 // The MFMA takes the B fragment (columns n) as its row operand and the A fragment as its column operand: a lane then
 // holds four CONSECUTIVE n of one row m of C and stores them as 16 bytes.
 // Rows of a k-contiguous A (and of C) may be mapped (`a_rows`, `c_rows`, `m_dev`: the packed list of real frames), as
@@ -81,15 +85,15 @@ __device__ __forceinline__ u32x4 make_rsrc(const void* base, unsigned bytes) {
   return r;
 }
 
-// A float is the sum of three bfloat16 (8 + 8 + 8 bits, each rounded to nearest, the last exactly); what the six products leave out is below 2^-25 of theirs.
+// A float times 2^24 is the sum of three bfloat16 (8 + 8 + 8 bits, each rounded to nearest, the last exactly); what the six products leave out is below 2^-25 of theirs.
 struct Parts { u32x4 p[3]; };
-constexpr float kLeast = 0x1p-100f;
+constexpr float kScale = 0x1p24f;
 constexpr int kPairA[6] = {0, 0, 1, 1, 0, 2}, kPairB[6] = {0, 1, 0, 1, 2, 0};
 __device__ __forceinline__ Parts split(const float (&x)[8]) {
   Parts r;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    float lo = x[2 * e], hi = x[2 * e + 1];
+    float lo = x[2 * e] * kScale, hi = x[2 * e + 1] * kScale;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -269,7 +273,7 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
         }
       }
     };
-    // Operands are split two products ahead, between the products: a split is 40 instructions of 4 cycles, six products are 96 cycles.
+    // Operands are split two products ahead, between the products: a split is 52 instructions of 4 cycles, six products are 96 cycles.
     Parts a[4], b[2];
     float x[2][8];
     auto pair = [&](int m, int n) __attribute__((always_inline)) {
@@ -305,7 +309,7 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
       __builtin_amdgcn_sched_barrier(0);
     }
   });
-  bool odd = false;                                              // (see above: NaN, infinity, or too small to be sure of)
+  bool odd = false;                                              // (see above)
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -313,8 +317,8 @@ __device__ __forceinline__ void gemm_float_body(const FArgs& g) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         acc[m][n][v] += low[m][n][v];
-        const float size = __builtin_fabsf(acc[m][n][v]);
-        odd |= !(size < __builtin_inff()) | (size < kLeast && size != 0.f);
+        odd |= !(__builtin_fabsf(acc[m][n][v]) < __builtin_inff());
+        acc[m][n][v] *= 1.f / (kScale * kScale);
       }
   if (__builtin_expect(__syncthreads_or(odd), 0)) {
 #pragma unroll

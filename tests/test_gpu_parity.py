@@ -123,6 +123,20 @@ def test_gemm_float_error(K):
         assert float((C.cpu().double() - ref).norm() / ref.norm()) < 2.0 ** -23 * (K / 64) ** 0.5, form
 
 
+@pytest.mark.parametrize("a_exp,b_exp", [(-115, 40), (-120, 60), (-126, 80), (-136, 100), (-145, 100), (-105, 0), (-75, -40)])
+def test_gemm_float_small_operands(a_exp, b_exp):
+    """Operands whose three bfloat16 parts, as they stand, would end below the smallest bfloat16 number, against larger ones: on either side of the product.
+    (Below 2^104, that is: a tile with larger ones is float MFMAs', whose error for these 256 products is 2.9e-7.)"""
+    g = torch.Generator().manual_seed(-a_exp)
+    A, B = torch.randn(132, 256, generator=g) * 2.0 ** a_exp, torch.randn(256, 140, generator=g) * 2.0 ** b_exp
+    for X, Y in ((A, B), (B.t().contiguous(), A.t().contiguous())):
+        ref = X.double() @ Y.double()
+        for form, C in _float_forms(X.cuda(), Y.cuda()).items():
+            err = (C.cpu().double() - ref).norm() / ref.norm()
+            print("    %s %.2e" % (form, err), flush=True)
+            assert float(err) < 2.0 ** -23 * 2.0, form
+
+
 @pytest.mark.parametrize("kind", ["infinities", "nan", "largest", "overflow", "denormal", "tiny", "zero"])
 def test_gemm_float_odd_values(kind):
     """What three bfloat16 cannot hold arrives as in 64 bits, rounded to float at the end; the tile beside it as always."""
