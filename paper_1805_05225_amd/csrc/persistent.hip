@@ -2063,7 +2063,8 @@ __device__ __forceinline__ F32Rows f32_rows(const int* lens, int B, int T, bool 
 }
 
 // A float as the sum of three bfloat16 (8 + 8 + 8 bits, rounded to nearest, the last exactly; gemm_float.hip), eight of them in twelve small steps that
-// fit between products: part e / 4 of elements 2 (e % 4) and the next.  W_h is scaled by a power of two first, or parts of small weights would end below 2^-133.
+// fit between products: part e / 4 of elements 2 (e % 4) and the next.  Exactly from 2^-110 up: what may be smaller is scaled by a power of two first (W_h, and dz of the
+// backward loop).  h is not: what its parts lose, 2^-134, times weights below 2^76 is below 2^-48 in a pre-activation, which gates that are good to 2^-24 cannot feel.
 struct Splitter {
   float v[8];
   u32x4 part[3];
@@ -2075,6 +2076,7 @@ struct Splitter {
   }
 };
 constexpr float kWScale = 0x1p40f;
+constexpr float kBwdScale = 0x1p24f, kSumScale = kPartScale / (kBwdScale * kBwdScale);    // backward: of dz and of W_h^T; of their sums on their way
 constexpr unsigned kWMost = 0x79800000u;                   // 2^116: a sum of 256 products with h stays finite
 template <int NCH>                                         // chunks per wavefront at most: n <= 64 * NCH
 __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
@@ -2421,7 +2423,7 @@ __global__ __launch_bounds__(256) void persist_fwd_f32_kernel(PFwdArgs a) {
 // are two 8-byte units, the tag bit 30 of each unit's second float.  (Products of three-part sums as forward: 16 k-steps of a column tile are two
 // halves of 32 of K.  What the next step's gate gradients need is fetched into LDS a step ahead: loads come back in the order of issue, and from
 // memory they would hold up the ring's; n = 512, 32 rows 3.8 -> 3.55 us a step.)  Partial sums are not bounded by 1, so they travel scaled
-// by 2^-32 (the packed W_h^T carries the factor; the consumer multiplies its sum by 2^32): bit 30 is then 0 for every partial
+// by 2^-32 (the consumer multiplies its sum by 2^32): bit 30 is then 0 for every partial
 // sum below 2^32 in magnitude, and no other bit of a value above 2^-94 changes.  Larger ones, infinities and NaN travel folded
 // (exchange_dev.h): a half step whose largest dz and W_h could make one looks at each sum, the others at none (config 2's loop 525 -> 534 us, a slab of one row
 // tile of 1000 units 6.95 -> 7.13 us a step; with a look at every sum 548, with a second copy of the products for such half steps 550, with the
@@ -2453,8 +2455,8 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   // W_h^T slice: column tile wave + 4 ci of the outputs, k-step s (launch_pack_wh_bwd_f32p)
   // In three bfloat16 parts, as forward: two fill the 256 accumulation registers of every lane, the smallest lies in LDS.
   u32x4 wh[NCT][2], wm[NCT][2];
-  float w_bound = 0.f;                                     // 64 times the slice's largest weight, over all lanes: a sum of products is no larger than
-  unsigned w_most = 0u;                                    // this times the largest dz
+  float w_bound = 0.f;                                     // 64 times the slice's largest weight, over all lanes: a sum of products, scaled by 2^-32, is no larger
+  unsigned w_most = 0u;                                    // than this times the largest dz
   auto w_at = [&](int ci, int s4) __attribute__((always_inline)) { return *((const u32x4*)d.Wb + ((((long)J * 4 + wave) * NCT + ci) * 4 + s4) * 64 + lane); };
 #pragma unroll
   for (int c2 = 0; c2 < NCT; c2 += 2) {
@@ -2467,8 +2469,9 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
       Splitter s;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        s.v[e] = __uint_as_float(v[g >> 1][2 * c + (e >> 2)][e & 3]);
-        w_bound = max_magnitude(w_bound, s.v[e], 0.f);
+        const float w = __uint_as_float(v[g >> 1][2 * c + (e >> 2)][e & 3]);
+        w_bound = max_magnitude(w_bound, w, 0.f);
+        s.v[e] = w * kBwdScale;
         w_most = max(w_most, __float_as_uint(s.v[e]) & 0x7fffffffu);
       }
 #pragma unroll
@@ -2482,7 +2485,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   const bool plain = __builtin_amdgcn_ballot_w64(w_most >= kWMost) != 0ull;      // (as forward)
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) w_bound = max_magnitude(w_bound, __shfl_xor(w_bound, o), 0.f);
-  w_bound *= 64.f;
+  w_bound *= 64.f * kPartScale;
   const int local = NCT <= 8 ? group_is_xcd_local(a.xcc, wg.base, a.map.ntile, a.spin_limit) : 0;      // (more than 32 members never are)
 
   // pointwise: row r16 of each row tile, unit u of the tile's 16
@@ -2694,9 +2697,9 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           if (local) __builtin_amdgcn_raw_buffer_store_b128(unit, to, off, 0, 1);
           else __builtin_amdgcn_raw_buffer_store_b128(unit, to, off, 0, 16);    // 16: agent scope, written through
         };
-        // What the parts cannot hold: float MFMAs, W_h from memory, and the next half step fetches for itself.
+        // What the parts or, scaled by 2^48, their sums cannot hold: float MFMAs, W_h from memory, and the next half step fetches for itself.
         const float bound = largest * w_bound;
-        if (__builtin_expect(plain || __builtin_amdgcn_ballot_w64(!(largest < 0x1p100f && bound < 0x1p100f)) != 0ull, 0)) {
+        if (__builtin_expect(plain || __builtin_amdgcn_ballot_w64(!(largest < 0x1p100f && bound < 0x1p44f)) != 0ull, 0)) {
           collect = false;
 #pragma unroll 1
           for (int ci = 0; ci < NCT; ++ci) {
@@ -2705,6 +2708,8 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
               u32x4 wv = w_at(ci, s4), none = wv;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) wv[e] = __float_as_uint(__uint_as_float(wv[e]) * kPartScale);
               operands_settle(wv, none);
 #pragma unroll
               for (int e = 0; e < 4; ++e) mfma4_b_vgpr(acc, av[4 * s4 + e], __uint_as_float(wv[e]));
@@ -2717,7 +2722,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
 #pragma unroll
           for (int c = 0; c < 2; ++c) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) s[c].v[e] = av[8 * c + e];
+            for (int e = 0; e < 8; ++e) s[c].v[e] = av[8 * c + e] * kBwdScale;
 #pragma unroll
             for (int e = 0; e < 12; ++e) s[c].step(e);
           }
@@ -2748,7 +2753,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
               mfma_b_vgpr(low, s[c].part[0], wl[ci & 1][c]);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (ci > 0) publish(ci - 1, acc2[(ci - 1) & 1] + low2[(ci - 1) & 1]);
+            if (ci > 0) publish(ci - 1, (acc2[(ci - 1) & 1] + low2[(ci - 1) & 1]) * kSumScale);
             if (collect) {                                 // (behind the MFMAs just issued: they run while this does)
               wait_loads_but((NCT - 1 - ci) < (kWin - 1) ? (NCT - 1 - ci) : (kWin - 1), x[ci % kWin]);     // the younger loads: the window's others
               stale_n |= rn.tag_diff(x[ci % kWin], ci, tagw_n);      // looked at once, behind the last load
@@ -2759,7 +2764,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
           }
           mfma_settle(acc2[(NCT - 1) & 1]);
           mfma_settle(low2[(NCT - 1) & 1]);
-          publish(NCT - 1, acc2[(NCT - 1) & 1] + low2[(NCT - 1) & 1]);
+          publish(NCT - 1, (acc2[(NCT - 1) & 1] + low2[(NCT - 1) & 1]) * kSumScale);
         }
         if (__builtin_expect(wide, 0)) {
           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (a wavefront reads what it stored itself, past its L1)
@@ -3286,7 +3291,7 @@ hipError_t launch_persist_fwd_f32(const PFwdArgs& a, hipStream_t s) {
   const auto kernel = fwd_f32_for(a.n);
   return coop_slabs(kernel, cdiv(a.n, 16), f32_rows_per_group(kernel, cdiv(a.n, 16), a.B, a.ndir), a, s);
 }
-// W_h^T for the float partial-sum backward kernel, scaled by 2^-32: float index
+// W_h^T for the float partial-sum backward kernel: float index
 // ((((dir*ntile + J)*4 + wave)*NCT + ci)*16 + s)*64 + lane holds W_h[unit (wave + 4 ci)*16 + lane%16][gate column
 // (kappa/16)*n + J*16 + kappa%16], kappa = 16 (lane/16) + s; stored so that a lane's k-steps 4 s4 .. 4 s4 + 3 are one float4:
 // float4 index ((((dir*ntile + J)*4 + wave)*NCT + ci)*4 + s4)*64 + lane.
@@ -3307,10 +3312,10 @@ __global__ void pack_wh_bwd_f32p_kernel(const float* W, float4* out, int n, int 
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     if (unit_in < n && n % 4 == 0 && unit_out < n) {
       const float4 x = *(const float4*)(row + q * n + unit_out);
-      v[0] = x.x * kPartScale; v[1] = x.y * kPartScale; v[2] = x.z * kPartScale; v[3] = x.w * kPartScale;
+      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     } else if (unit_in < n) {
       for (int e = 0; e < 4; ++e)
-        if (unit_out + e < n) v[e] = row[q * n + unit_out + e] * kPartScale;
+        if (unit_out + e < n) v[e] = row[q * n + unit_out + e];
     }
     out[((idx >> 6) * 4 + s4) * 64 + q * 16 + r] = make_float4(v[0], v[1], v[2], v[3]);
   }

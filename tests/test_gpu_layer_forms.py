@@ -224,6 +224,35 @@ def test_float_loops_in_parts(T, B, n, what):
         assert err.max() < 5e-5, (name, err.max())
 
 
+@pytest.mark.parametrize("dy_exp,w_exp", [(-118, 60), (60, -120)])
+@pytest.mark.parametrize("T,B,n", [(24, 9, 200), (24, 140, 500), (24, 12, 1024)])
+def test_float_backward_loop_small_operands(T, B, n, dy_exp, w_exp):
+    """Gate gradients and weights whose parts would end below the smallest bfloat16, against partners that make the product an ordinary number.  Every fourth
+    unit's output gate is shut, so its row of W_h, the only one that is not zero, has no effect but on dh0: 4 n products of one step (2^-23 of their
+    size, root mean square, as for a float product)."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(n + B)
+    c = P.rnd_case(rng, T, B, 24, n, 1, _lens(rng, T, B), "f32", scale=0.3)
+    shut = np.arange(n) % 4 == 0
+    c["b"][0, 3 * n:][shut] = -300.0
+    c["W_h"][0] *= shut[:, None] * 2.0 ** w_exp
+    c["h0"][0][:, shut] = 0.0
+    for k in ("dy", "dhT", "dcT"):
+        c[k] *= 2.0 ** dy_exp
+    Bn.profile_enable(1)
+    f, g = P.run_gpu(c, "f32", False, flags=Bn.FLAG_PLAIN_LAUNCH, poison=True)
+    Bn.profile_enable(0)
+    assert Bn.profile_read()["loop_bwd"][1] < T
+    fs, gs = P.run_gpu(c, "f32", False, flags=Bn.FLAG_PER_STEP)
+    live = c["lens"] > 0
+    got, ref = host(g["dh0"])[live][:, shut], host(gs["dh0"])[live][:, shut]
+    assert np.isfinite(ref).all() and np.abs(ref).max(axis=1).min() > 0
+    err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    print("    dh0 err", err.max(), flush=True)
+    assert err.max() < 4 * 2.0 ** -23 * (4 * n / 64) ** 0.5      # (gate gradients of either loop: another order of sums)
+
+
 @pytest.mark.parametrize("T,B,n,bidir", [(150, 5, 1032, False), (64, 32, 1536, True), (90, 33, 2048, False), (40, 64, 2048, True), (33, 17, 1921, False)])
 def test_wide_loops_over_many_steps(T, B, n, bidir):
     """The rings of the wide loops are used over and over: many steps, ordinary and cooperative launch, against the per-step kernels; the same
