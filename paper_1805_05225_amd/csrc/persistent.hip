@@ -199,11 +199,8 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
   const bf16x2_ r = __builtin_convertvector((f32x2_){lo, hi}, bf16x2_);
   return __builtin_bit_cast(unsigned, r);
 }
-// Streaming accesses of the recurrent kernels (every byte touched once): marked non-temporal so that they do not
+// Streaming stores of the recurrent kernels (every byte touched once): marked non-temporal so that they do not
 // push the exchange ring, which is re-read every step, out of the L2.
-__device__ __forceinline__ float ld_stream(const float* p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ unsigned short ld_stream(const unsigned short* p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ void st_stream(float* p, float v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void st_stream(unsigned short* p, unsigned short v) { __builtin_nontemporal_store(v, p); }
 
 // --- W_h in accumulation registers ---------------------------------------------------------------------------
@@ -260,26 +257,14 @@ __device__ __forceinline__ unsigned rows_from_high(unsigned v) { return (unsigne
 __device__ __forceinline__ void mfma_b_agpr_first(f32x4& acc, const u32x4& a, const u32x4& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
 }
-// The float MFMA (16x16x4): A one float per lane in a vector register, B one float per lane in an accumulation register.
-__device__ __forceinline__ void mfma4_b_agpr(f32x4& acc, float a, unsigned b) {
-  asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
-}
+// The float MFMA (16x16x4): one float of A and one of B per lane.
 __device__ __forceinline__ void mfma4_b_vgpr(f32x4& acc, float a, float b) {
   asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma4_b_agpr_first(f32x4& acc, float a, unsigned b) {
-  asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
 }
 __device__ __forceinline__ void mfma_settle(f32x4& a0) { asm volatile("s_nop 15\n\ts_nop 3" : "+v"(a0)); }
 // Wait states between the last ordinary (vector ALU, DPP, LDS) write of registers and an MFMA reading them.  For
 // MFMAs it emits itself the compiler knows what the hardware needs; for these it cannot, and an MFMA issued right
 // behind DPP moves was observed to read the old register contents.
-// first MFMA of a pair behind which a preparation step of the next pair is placed (the next pair's loads were
-// issued together with this pair's and have had that much more time to arrive)
-#ifndef LSTM_PREP_DELAY
-#define LSTM_PREP_DELAY 6
-#endif
-constexpr int kPrepDelay = LSTM_PREP_DELAY;
 #ifndef LSTM_OPERAND_NOPS
 #define LSTM_OPERAND_NOPS "7"
 #endif
