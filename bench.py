@@ -747,7 +747,7 @@ def main():
     def loop_roofline(phase, row_bytes, name):
         ms, launches = prof[phase]
         layer_runs = args.steps * nl                                # times the loop of one layer ran in the timed region
-        per_layer = launches / max(layer_runs, 1)                   # 1; 2 where the batch takes two launches; T on the per-step path
+        per_layer = launches / max(layer_runs, 1)                   # 1; 2 where the batch takes two launches, or one and a fill of the padded frames; T on the per-step path
         per_step_path = T > 2 and per_layer >= T                    # one launch per time step: W_h is not resident
         per_launch_ms = ms / max(launches, 1)
         layer_ms = ms / max(layer_runs, 1)

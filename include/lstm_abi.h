@@ -312,7 +312,7 @@ int lstm_sync_status(const void* workspace, int32_t* timed_out);
 enum {
   LSTM_PHASE_PREP = 0,      /* weight / state packing, state initialisation and copies            */
   LSTM_PHASE_GEMM_ZX = 1,   /* Zx = X W_x + b for all frames                                      */
-  LSTM_PHASE_LOOP_FWD = 2,  /* forward recurrence                                                 */
+  LSTM_PHASE_LOOP_FWD = 2,  /* forward recurrence, the fill of padded frames behind it included   */
   LSTM_PHASE_LOOP_BWD = 3,  /* backward recurrence                                                */
   LSTM_PHASE_GEMM_DX = 4,   /* dX = DZ W_x^T, the sum of its K ranges included                    */
   LSTM_PHASE_GEMM_DWX = 5,  /* dW_x = X^T DZ, likewise                                            */

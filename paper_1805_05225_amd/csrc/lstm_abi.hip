@@ -562,16 +562,16 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       }
       hipError_t e;
       {
-        Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
+        Phase ph(LSTM_PHASE_LOOP_FWD, pa.slots > 0 ? 2 : 1, s);
         e = use_ll ? launch_persist_fwd(pa, s) : launch_persist_fwd_f32(pa, s);
+        if (e == hipSuccess && pa.slots > 0) {
+          float* cs[2] = {pa.d[0].cs, pa.d[D - 1].cs};
+          const float* cz[2] = {c0_fill, c0_fill ? c0_fill + (D - 1) * B * n : nullptr};
+          const int rev[2] = {pa.d[0].rev, pa.d[D - 1].rev};
+          HIPCHK(launch_fill_padded(seq_lens, rows.steps, p.T, p.B, p.n, p.D, y, cs, cz, rev, s));
+        }
       }
       if (e == hipErrorCooperativeLaunchTooLarge && h0) e = hipErrorLaunchFailure;   // the pre-activations are no longer what the per-step path expects
-      if (e == hipSuccess && pa.slots > 0) {
-        float* cs[2] = {pa.d[0].cs, pa.d[D - 1].cs};
-        const float* cz[2] = {c0_fill, c0_fill ? c0_fill + (D - 1) * B * n : nullptr};
-        const int rev[2] = {pa.d[0].rev, pa.d[D - 1].rev};
-        HIPCHK(launch_fill_padded(seq_lens, rows.steps, p.T, p.B, p.n, p.D, y, cs, cz, rev, s));
-      }
       if (e == hipSuccess) done = true;
       else if (e == hipErrorCooperativeLaunchTooLarge) {   // nothing was launched (does not fit on the device all at once): one launch per step
         (void)hipGetLastError();

@@ -342,6 +342,18 @@ def test_phase_times_name_every_product(dt, T, B, n_in, n):
     assert total[1] == total[2]
 
 
+def test_phase_times_count_the_fill_of_padded_frames():
+    """Rows one behind the other: the launch that fills the padded frames is part of the forward recurrence."""
+    from paper_1805_05225_amd import binding as Bn
+    P.Bn = Bn
+    rng = np.random.default_rng(3)
+    c = P.rnd_case(rng, 12, 48, 24, 1000, 2, _lens(rng, 12, 48), "bf16", scale=2.0 / np.sqrt(1000))
+    Bn.profile_enable(1)
+    P.run_gpu(c, "bf16", True)
+    Bn.profile_enable(0)
+    assert Bn.profile_read()["loop_fwd"][1] == 2
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("n", [128, 124, 72, 62, 60, 56, 8, 4, 3])
 def test_narrow_layer_widths(dt, n):
