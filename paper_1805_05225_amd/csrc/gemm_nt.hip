@@ -625,9 +625,11 @@ hipError_t launch_tn(const GemmArgs& g, int ks, hipStream_t s) {
   return hipGetLastError();
 }
 // Products of few tiles whose K is long (dW_h of a long batch): as many K ranges as fill the device, at least seven eighths of it, with tiles of which no more than
-// a tenth lies outside C.  Parts of the whole device are 64 MiB, written and read, 30 us; the 128 x 128 tiles of gemm_tile.hip run at
-// 0.7 of this kernel's rate, which is 11 ns per k of a range: even at 2700 real frames a range.  K counts padded frames too, so the line is at 6144.
-// dW_h of 31597 frames (1024 x 4096, both directions) in two ranges: 874 -> 1058 TFLOP/s, sums included.
+// a tenth lies outside C; the others stay with the 128 x 128 tiles of gemm_tile.hip.  Parts of the whole device are 64 MiB, written and read, 30 us, so K has to be long.  Both
+// sides, dW_x (of 2 n inputs) and dW_h of two directions together, sums included, us: 5744 real of 9600 frames 273 there and 288 here for n = 1024; 12800 of 12800 586
+// and 579 (n = 1000 595 and 582, 960 552 and 546); 15344 of 25600 701 and 682; 28784 of 48000 1288 and 1230 (1332 and 1230, 1219 and 1171).  K counts padded frames
+// too: with 6144 of them a range n = 1024 begins at 12288.  Widths it leaves out, 28784 frames: 768 (three ranges of 72 tiles) 909 and 1136, 896 1350 and 1279,
+// 832 1313 and 1298; 640 and 704, whose tiles lie a sixth outside C, would gain from 12800 frames on (344 and 302, 374 and 340; 28784: 871 and 682, 885 and 744).
 int tn_ranges(long M, long N, long K, int nz) {
   const long tiles = (M + kT - 1) / kT * ((N + kT - 1) / kT) * nz;
   if (tiles <= 0 || tiles > 128 || M * N * nz * 10 < tiles * kT * kT * 9) return 1;
