@@ -43,7 +43,7 @@
  *     128 < n <= 1024 exchange h and sums of gradients between work-groups in a form that has no room for NaN, nor for gradient
  *     sums of 2^33 and more.  There such a value may make the loop's bounded wait expire (lstm_sync_status reports it);
  *     LSTM_FLAG_PER_STEP has no such limit.  The float loops of n <= 1024 and the wide bfloat16 loops (n > 1024) carry sums of 2^32 and more
- *     between work-groups with 16 significant bits, and sums of gradients as multiples of 2^-117 (fewer than 24 bits below 2^-94).
+ *     between work-groups with 16 significant bits, and the others as multiples of 2^-117 (fewer than 24 bits below 2^-94).
  *     Float products hold all 24 bits of their operands, the smallest floats included (but for an |h| below 2^-110, which no gate can feel).
  *   - The loops of 128 < n <= 1024 add a step's products in the order in which the other work-groups' values arrive: two calls with the same inputs
  *     agree to the rounding of float sums (and of what is stored in bfloat16), not bit for bit.  LSTM_FLAG_PER_STEP repeats its bits.

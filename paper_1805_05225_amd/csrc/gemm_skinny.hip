@@ -109,7 +109,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
   const int K = g.K, nstage = (K + 63) / 64;
   // The work-groups of an XCD that share an operand panel would ask for the same lines at the same time, and all of them would wait for the one
   // fetch from beyond L2.  So they start a little apart, an eighth of K between the first and the last of the 32 that an XCD runs together, and wrap around
-  // (the sum over k does not care about the order).  Not further: operands of 9 MB per XCD do not stay in 4 MB of L2 until the last
+  // (a sum's order follows from its work-group's position alone: the same call gives the same bits).  Not further: operands of 9 MB per XCD do not stay in 4 MB of L2 until the last
   // of them comes by (over all of K, half of the decoder cell's requests missed: 768 rows, K = 3620, N = 4000 39.9 us, 37.8 so; 37.3 with no
   // distance at all, but up to 2 % more for 640 rows and less).
   const int rot = (int)(((long)tl.pos * nstage) >> 8);
