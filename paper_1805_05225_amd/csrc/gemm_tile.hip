@@ -9,15 +9,26 @@
 // a walk over 32 stages of K at the latency of a load (1.6 us): 51 us for 0.9 GFLOP and 32 MB of weights, behind a transpose
 // of those weights (17 us).  Here: tiles of 128 x 128, four wavefronts of 64 x 64 (2 x 2 MFMA blocks of 32 x 32 x 16), two work-groups per
 // compute unit, and K cut into as many ranges as give the device 512 of them; the ranges' parts are added by a second kernel,
-// which also applies bias, row map and rounding.  (More stages in flight - three or four of them and one work-group per compute unit - were
-// slower: 37 -> 49 us for 1600 x 4000 x 1000; a second work-group hides more than a deeper pipeline.)
+// which also applies bias, row map and rounding.
 //
 // Operands go from global memory straight into LDS (16 bytes per lane), K in stages of 64, two stages; the order within a stage
 // and the reasons are those of gemm_nt.hip.  A k-contiguous operand sits there as rows of 128 bytes whose 16-byte slot p holds
 // chunk p ^ ((row / 2) % 8); a k-major one as 64 rows of one k each whose 64-byte blocks are XORed with k % 4, read with the LDS
 // transpose read.
+//
+// A stage is two phases of eight products: both operands k-contiguous, the first and the second row of blocks over all 64 k; else
+// k-steps 0-1 and 2-3.  A phase's reads fetch the next one's fragments while its products run, a load behind each; what they have read is free
+// when all wavefronts have met, once a phase, and is loaded again in the next one, so that half a stage to one and a half is always on its way.  A k-contiguous
+// A with a k-major B goes out a whole stage at a time (its lines hold all 64 k, and W_x comes from memory: half a stage of 4000 columns at a time took 2 us of 30 more),
+// B two stages ahead.  Before, a stage's loads went out together, a stage ahead, and were waited for together.  With the order of the tiles below, us, operands
+// from memory: both k-contiguous 3200 x 2000 x 8000 135 and 127, 4096 x 2048 x 8192 158 and 140, 1120 x 2048 x 8192 114 and 79; k-major B
+// 1120 x 8192 x 2048 69 and 56, 4096 x 2048 x 8192 178 and 144; both k-major 4096 x 2048 x 8192 163 and 148, 1000 x 8000 x 3200 70 and 68.  What bounds them now
+// is the path from L2 to LDS: of 138 us without the products 120 remain, without the loads 108 (1270 TFLOP/s).  Tried without gain: a phase
+// a quarter of a stage (130, 137 and 74 us of the first three), ten quarters of a stage in 80 KiB of LDS (128, 143, 80), three or four whole stages with one
+// work-group per compute unit.
 #include "recurrent_dev.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace lstm {
 namespace {
@@ -46,12 +57,12 @@ struct TileGroup { TileArgs p[2]; int first1; };         // blocks from first1 o
 __device__ __forceinline__ void load_to_lds_b128(const u32x4& rsrc, unsigned lds_addr, unsigned voff, unsigned soff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
-__device__ __forceinline__ u32x4 make_rsrc(const void* base, long bytes) {
+__device__ __forceinline__ u32x4 make_rsrc(const void* base, unsigned bytes) {
   const unsigned long long a = (unsigned long long)base;
   u32x4 r;
   r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
   r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu);
-  r[2] = __builtin_amdgcn_readfirstlane((unsigned)(bytes > 0x7fffff00L ? 0x7fffff00L : bytes));
+  r[2] = __builtin_amdgcn_readfirstlane(bytes);
   r[3] = kBufFlags;
   return r;
 }
@@ -59,37 +70,50 @@ __device__ __forceinline__ f32x16 mma(uint4 a, uint4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Tile of WM x WN wavefronts, each TI x TJ blocks of 32 x 32.
-template <int TI, int TJ, int WM, int WN>
-struct Geo {
-  static constexpr int kBM = WM * TI * 32, kBN = WN * TJ * 32, kNW = WM * WN;
-  static constexpr int kOpA = kBM * kKB * 2, kOpB = kBN * kKB * 2, kStage = kOpA + kOpB;
-  static constexpr int kLA = kOpA / 1024 / kNW, kLB = kOpB / 1024 / kNW;             // wavefront-loads per stage and wavefront
-  static constexpr int kEpStride = kBN + 4, kEpBytes = WM * 32 * kEpStride * 4;      // the epilogue stages WM x 32 rows at a time
-  static constexpr int kLds = 2 * kStage > kEpBytes ? 2 * kStage : kEpBytes;
-};
+constexpr int kTM = 128, kTN = 128;     // tile
+constexpr int kOpBytes = 128 * kKB * 2, kStageBytes = 2 * kOpBytes;                  // one operand of a stage, both
+constexpr int kEpStride = kTN + 4, kEpBytes = 64 * kEpStride * 4;                    // the epilogue stages 64 rows at a time
+constexpr int tile_lds(bool ak, bool bk) { return 2 * kStageBytes + (ak && !bk ? kOpBytes : 0); }      // (k-contiguous A, k-major B: a third stage of B)
+static_assert(2 * kStageBytes >= kEpBytes && 2 * tile_lds(true, false) <= 160 * 1024, "two work-groups to a compute unit");
 
 // KROWS: k-major operands whose row k is row k_rows[k] in memory.
-template <typename TC, bool AK, bool BK, bool KROWS, int TI, int TJ, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileGroup grp) {
-  typedef Geo<TI, TJ, WM, WN> G;
-  constexpr int kBM = G::kBM, kBN = G::kBN, NW = G::kNW, kOpA = G::kOpA, kStage = G::kStage, kLA = G::kLA, kLB = G::kLB;
+template <typename TC, bool AK, bool BK, bool KROWS>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
+  constexpr int NW = 4;
+  constexpr bool kMixed = AK && !BK;
+  constexpr bool kHalves = AK && BK;      // a phase is a quarter of the blocks over the stage's 64 k (else: all blocks over 16 k)
+  static_assert(!KROWS || (!AK && !BK), "a list of rows: both operands k-major");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const bool second = (int)blockIdx.x >= grp.first1;
   const TileArgs g = second ? grp.p[1] : grp.p[0];
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = wave >> 1, wn = wave & 1;
   const int r = lane & 31, gq = lane >> 5;
 
-  // bands of 8 tile columns, row-major inside a band: work-groups are dealt to the 8 XCDs round-robin, so each keeps one tile
-  // column of B in its L2
+  // Work-groups are dealt to the 8 XCDs round-robin.  Up to as many tile rows as columns: bands of 8 tile columns, row-major inside a band, so
+  // that each XCD keeps one tile column of B in its L2 and neighbouring columns are read and written at the same time.  More rows: each XCD would
+  // read all of A, and takes an eighth of all tiles instead, one behind the other in an order of bands of `high` rows, about as many rows as columns at a
+  // time (us, bands of columns and these: 4096 x 2048 x 8192 157 and 139, 3200 x 2000 x 8000 141 and 130; but 1120 x 8192 x 2048 with k-major B 55 and 57).
   const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
-  const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
-  const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), zk = mine / (tiles_m * tiles_n), bid = mine - zk * (tiles_m * tiles_n);
-  const int band = bid / (8 * tiles_m), width = min(8, tiles_n - band * 8), rel = bid - band * 8 * tiles_m;
-  const int m0 = __builtin_amdgcn_readfirstlane((rel / width) * kBM), n0 = __builtin_amdgcn_readfirstlane((band * 8 + rel % width) * kBN);
-  if (m0 >= M) return;
+  const int tiles_m = (M + kTM - 1) / kTM, tiles_n = (g.N + kTN - 1) / kTN, per_z = tiles_m * tiles_n, tiles = per_z * g.nz * g.ksplit;
+  const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), each = (tiles + 7) >> 3;
+  const bool by_rows = tiles_m > tiles_n;
+  const int idx = by_rows ? (mine & 7) * each + (mine >> 3) : mine;
+  if (idx >= tiles || (by_rows && (mine >> 3) >= each)) return;
+  const int zk = idx / per_z, bid = idx - zk * per_z;
+  int tm, tn;
+  if (by_rows) {
+    int side = 1;
+    while (side < 8 && (side + 1) * (side + 1) <= each) ++side;
+    const int bands = max(1, (tiles_m + side / 2) / side), high = (tiles_m + bands - 1) / bands;
+    const int band = bid / (high * tiles_n), height = min(high, tiles_m - band * high), rel = bid - band * high * tiles_n;
+    tm = band * high + rel % height; tn = rel / height;
+  } else {
+    const int band = bid / (8 * tiles_m), width = min(8, tiles_n - band * 8), rel = bid - band * 8 * tiles_m;
+    tm = rel / width; tn = band * 8 + rel % width;
+  }
+  const int m0 = __builtin_amdgcn_readfirstlane(tm * kTM), n0 = __builtin_amdgcn_readfirstlane(tn * kTN);
   const int ksplit = g.ksplit, z = __builtin_amdgcn_readfirstlane(zk / ksplit), ks = __builtin_amdgcn_readfirstlane(zk - z * ksplit);
 
   const int ktiles = (K + kKB - 1) / kKB, nstage = ktiles * g.nseg;
@@ -97,106 +121,85 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileGroup grp) 
   // (told to be wave-uniform: divisions leave them in vector registers)
   const int it0 = __builtin_amdgcn_readfirstlane(nstage * ks / ksplit), total = __builtin_amdgcn_readfirstlane(nstage * (ks + 1) / ksplit) - it0;
 
-  // k-contiguous operand, wavefront-load i: rows 8 (i NW + wave) .. + 7, lane l slot l & 7 of row l >> 3.
-  // k-major operand, wavefront-load i: k-rows (i NW + wave) RPL .. + RPL - 1 of the stage, lane l slot l % (64 / RPL).
-  constexpr int kRplA = 512 / kBM, kRplB = 512 / kBN;          // k-rows per load
-  unsigned va[kLA], vb[kLB];
-  bool pa[kLA], pb[kLB];                                       // k-contiguous: this lane's chunk lies past a ragged last k-tile
-  const int ka_lane = lane / (64 / kRplA), kb_lane = lane / (64 / kRplB);
+  // Loads.  k-contiguous operand, half h (rows of every wavefront's first or second block), load j: rows 64 j + 32 h + 8 wave .. + 7,
+  // lane l slot l & 7 of row l >> 3.  k-major operand, k-step s: k-rows 16 s + 4 wave .. + 3, lane l slot l % 16 of row l / 16.
+  const int kk = lane >> 4;                                    // k-major: this lane's row of a load's four
+  const int kc_chunk = (lane & 7) ^ ((((wave & 1) * 8 + (lane >> 3)) >> 1) & 7), km_chunk = (lane & 15) ^ (4 * kk);
+  const bool past = kc_chunk >= tail_chunks;                   // k-contiguous: this lane's chunk lies past a ragged last k-tile
+  const unsigned lda2 = (unsigned)g.lda * 2u, ldb2 = (unsigned)g.ldb * 2u;
   const auto clip = [](long o, bool ok) { return ok && o <= 0x7ffffe00L ? (unsigned)o : kParked; };
+  unsigned va[AK ? 4 : 1], vb[BK ? 4 : 1];                     // k-contiguous: [2 h + j]
+  if constexpr (AK) {
 #pragma unroll
-  for (int i = 0; i < kLA; ++i) {
-    pa[i] = false;
-    if constexpr (AK) {
-      const int rl = (i * NW + wave) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((rl >> 1) & 7);
-      const int row = m0 + rl;
+    for (int q = 0; q < 4; ++q) {
+      const int row = m0 + (q & 1) * 64 + (q >> 1) * 32 + wave * 8 + (lane >> 3);
       const long pr = row < M ? (g.a_rows ? (long)g.a_rows[row] : row) : -1;
-      va[i] = clip(pr * g.lda * 2 + chunk * 16, pr >= 0);
-      pa[i] = chunk >= tail_chunks;
-    } else {
-      const int kk = (i * NW + wave) * kRplA + ka_lane, chunk = (lane % (64 / kRplA)) ^ (4 * (kk & 3));
-      va[i] = clip((KROWS ? 0L : kk * g.lda * 2) + ((long)m0 + chunk * 8) * 2, m0 + chunk * 8 < M);
+      va[q] = clip(pr * g.lda * 2 + kc_chunk * 16, pr >= 0);
     }
+  } else {
+    va[0] = clip((KROWS ? 0L : (wave * 4 + kk) * g.lda * 2) + ((long)m0 + km_chunk * 8) * 2, m0 + km_chunk * 8 < M);
   }
+  if constexpr (BK) {
 #pragma unroll
-  for (int i = 0; i < kLB; ++i) {
-    pb[i] = false;
-    if constexpr (BK) {
-      const int rl = (i * NW + wave) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((rl >> 1) & 7);
-      const int row = n0 + rl;
-      vb[i] = clip((long)row * g.ldb * 2 + chunk * 16, row < g.N);
-      pb[i] = chunk >= tail_chunks;
-    } else {
-      const int kk = (i * NW + wave) * kRplB + kb_lane, chunk = (lane % (64 / kRplB)) ^ (4 * (kk & 3));
-      vb[i] = clip((KROWS ? 0L : kk * g.ldb * 2) + ((long)n0 + chunk * 8) * 2, n0 + chunk * 8 < g.N);
+    for (int q = 0; q < 4; ++q) {
+      const int row = n0 + (q & 1) * 64 + (q >> 1) * 32 + wave * 8 + (lane >> 3);
+      vb[q] = clip((long)row * g.ldb * 2 + kc_chunk * 16, row < g.N);
     }
+  } else {
+    vb[0] = clip((KROWS ? 0L : (wave * 4 + kk) * g.ldb * 2) + ((long)n0 + km_chunk * 8) * 2, n0 + km_chunk * 8 < g.N);
   }
   const int KB = AK && !BK && g.k_phys_rows > 0 ? g.k_phys_rows : K;
   const long k_mem = KROWS ? g.k_phys_rows : KB;
-  const long a_bytes = (AK ? (long)(g.a_rows ? g.a_phys_rows : M) : k_mem) * g.lda * 2, b_bytes = (BK ? (long)g.N : k_mem) * g.ldb * 2;
+  const auto rec_of = [](long b) { return (unsigned)(b > 0x7fffff00L ? 0x7fffff00L : b); };
+  const unsigned a_rec = rec_of((AK ? (long)(g.a_rows ? g.a_phys_rows : M) : k_mem) * g.lda * 2), b_rec = rec_of((BK ? (long)g.N : k_mem) * g.ldb * 2);
+  const char* const a_base = g.A + g.sAz * z * 2;
+  const char* const b_base = g.B + g.sBz * z * 2;
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)lds;
 
-  // The stage whose loads go out next: segment, k-tile inside it (counted up, not divided out), and, with KROWS, the memory rows of
-  // its k: entries of the packed list, by scalar loads that are waited for together with the operand loads (see gemm_nt.hip).  The
-  // list is readable up to the next multiple of 64 entries.
-  int seg = g.nseg > 1 ? __builtin_amdgcn_readfirstlane(it0 / ktiles) : 0, kt = it0 - seg * ktiles, left = total;
-  u32x4 ra = make_rsrc(g.A + (g.sAz * z + g.sAseg * seg) * 2, a_bytes), rb = make_rsrc(g.B + (g.sBz * z + g.sBseg * seg) * 2, b_bytes);
-  static_assert(!KROWS || (!AK && !BK && kLA == 4 && kRplA == 4 && kRplB == 4 && kLA == kLB), "four entries of the list per load, the same for A and B");
-  i32x4 prow[KROWS ? kLA : 1];
-  auto lookup = [&]() __attribute__((always_inline)) {         // for the stage that `kt` names
+  struct Stage { int it, seg, kt; };                           // the stage whose loads go out: place in this range, segment, k-tile inside it
+  const int seg0 = g.nseg > 1 ? __builtin_amdgcn_readfirstlane(it0 / ktiles) : 0;
+  Stage nx = {0, seg0, it0 - seg0 * ktiles};
+  Stage nb = nx;                                               // kMixed: of B
+  auto advance = [&](Stage& t) __attribute__((always_inline)) {
+    ++t.it;
+    if (++t.kt == ktiles && kHalves) { t.kt = 0; ++t.seg; }
+  };
+  int b_out = 0, b_in = 0;                                     // kMixed: stage it of B is the (it % 3)th
+  auto next = [&](int& slot) __attribute__((always_inline)) { slot = slot == 2 * kOpBytes ? 0 : slot + kOpBytes; };
+  // where stage `it` of an operand lies (`slot`: of a kMixed B)
+  auto place = [&](bool is_a, int it, int slot) __attribute__((always_inline)) {
+    if constexpr (kMixed) return is_a ? (it & 1) * kOpBytes : 2 * kOpBytes + slot;
+    return (it & 1) * kStageBytes + (is_a ? 0 : kOpBytes);
+  };
+  // (past the last stage the same loads are issued with every lane outside the descriptor: the counted waits below count them)
+  auto issue_half = [&](bool is_a, int h, int j) __attribute__((always_inline)) {
+    const u32x4 rs = is_a ? make_rsrc(a_base + (long)g.sAseg * nx.seg * 2, nx.it < total ? a_rec : 0u) : make_rsrc(b_base + (long)g.sBseg * nx.seg * 2, nx.it < total ? b_rec : 0u);
+    const unsigned dst = lds_base + place(is_a, nx.it, 0) + (h * 32 + wave * 8) * 128;
+    const bool cut = past && nx.kt == ktiles - 1;
+    load_to_lds_b128(rs, dst + j * 64 * 128, cut ? kParked : is_a ? va[AK ? 2 * h + j : 0] : vb[BK ? 2 * h + j : 0], (unsigned)nx.kt * (kKB * 2));
+  };
+  // With KROWS the memory rows are entries of the packed list, looked up a phase ahead by scalar loads that are waited for together with
+  // the operand loads (see gemm_nt.hip).  The list is readable up to the next multiple of 64 entries.
+  i32x4 prow[8];
+  auto lookup = [&](int dst, int kt, int s) __attribute__((always_inline)) {
     if constexpr (KROWS) {
-      if (left > 0) {
-#pragma unroll
-        for (int i = 0; i < kLA; ++i) {
-          const int* p = g.k_rows + (long)kt * kKB + (i * NW + wave) * 4;
-          asm volatile("s_load_dwordx4 %0, %1, 0x0" : "=s"(prow[i]) : "s"(p) : "memory");
-        }
-      }
+      const int* p = g.k_rows + (long)min(kt, ktiles - 1) * kKB + s * 16 + wave * 4;
+      asm volatile("s_load_dwordx4 %0, %1, 0x0" : "=s"(prow[dst]) : "s"(p) : "memory");
     }
   };
-  // Waits for the operand loads and the look-up.  The statement "rewrites" the entries, so that nothing that uses them is scheduled in
-  // front of it (the compiler does not know that they are still on their way).
-  auto wait_all = [&]() __attribute__((always_inline)) {
-    if constexpr (KROWS) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : "+s"(prow[0]), "+s"(prow[1]), "+s"(prow[2]), "+s"(prow[3])::"memory");
-    else __builtin_amdgcn_s_waitcnt(0x0070);                   // vmcnt(0) lgkmcnt(0)
-  };
-  const unsigned lda2 = (unsigned)g.lda * 2u, ldb2 = (unsigned)g.ldb * 2u;
-  const unsigned odd = (ka_lane & 1) ? ~0u : 0u, high = (ka_lane & 2) ? ~0u : 0u;        // which of a load's four entries is this lane's
-  auto issue = [&](int buf, int first, int last) __attribute__((always_inline)) {
-    const bool tail = kt == ktiles - 1;
-    const int k_left = KB - kt * kKB;                          // rows of a k-major operand from here on
-    const unsigned dst = lds_base + buf * kStage + wave * 1024;
-    const unsigned soA = AK ? (unsigned)kt * (kKB * 2) : KROWS ? 0u : (unsigned)kt * (kKB * lda2);
-    const unsigned soB = BK ? (unsigned)kt * (kKB * 2) : KROWS ? 0u : (unsigned)kt * (kKB * ldb2);
-#pragma unroll
-    for (int q = 0; q < kLA + kLB; ++q) {
-      if (q < first || q >= last) continue;
-      const bool is_a = q < kLA;
-      const int i = is_a ? q : q - kLA;
-      unsigned v = is_a ? va[is_a ? i : 0] : vb[is_a ? 0 : i];
-      if (is_a ? AK : BK) {
-        if (tail && (is_a ? pa[is_a ? i : 0] : pb[is_a ? 0 : i])) v = kParked;
-      } else {
-        const bool ok = (i * NW + wave) * (is_a ? kRplA : kRplB) + (is_a ? ka_lane : kb_lane) < k_left;
-        if constexpr (KROWS) {                                 // (32-bit arithmetic: the operands end below 2^31; a parked column stays past the end)
-          const i32x4 p4 = prow[KROWS ? i : 0];
-          const unsigned lo = ((unsigned)p4[0] & ~odd) | ((unsigned)p4[1] & odd), hi = ((unsigned)p4[2] & ~odd) | ((unsigned)p4[3] & odd);
-          const unsigned row = (lo & ~high) | (hi & high);
-          v = row * (is_a ? lda2 : ldb2) + v;
-        }
-        if (!ok) v = kParked;
-      }
-      load_to_lds_b128(is_a ? ra : rb, dst + (is_a ? 0 : kOpA) + i * NW * 1024, v, is_a ? soA : soB);
+  const unsigned odd = (kk & 1) ? ~0u : 0u, upper = (kk & 2) ? ~0u : 0u;                 // which of a load's four entries is this lane's
+  auto issue_rows = [&](bool is_a, int s, int entry) __attribute__((always_inline)) {    // k-step s of a k-major operand
+    const Stage& t = kMixed ? nb : nx;
+    const u32x4 rs = make_rsrc(is_a ? a_base : b_base, t.it < total ? (is_a ? a_rec : b_rec) : 0u);
+    const unsigned ld2 = is_a ? lda2 : ldb2;
+    unsigned v = is_a ? va[0] : vb[0];
+    if constexpr (KROWS) {                                     // (32-bit arithmetic: the operands end below 2^31; a parked column stays past the end)
+      const i32x4 p4 = prow[entry];
+      const unsigned lo = ((unsigned)p4[0] & ~odd) | ((unsigned)p4[1] & odd), hi = ((unsigned)p4[2] & ~odd) | ((unsigned)p4[3] & odd);
+      v = ((lo & ~upper) | (hi & upper)) * ld2 + v;
     }
-  };
-  auto advance = [&]() __attribute__((always_inline)) {        // every load of a stage has been issued
-    --left;
-    if (++kt == ktiles && AK && BK) {
-      kt = 0;
-      ++seg;
-      ra = make_rsrc(g.A + (g.sAz * z + g.sAseg * seg) * 2, a_bytes);
-      rb = make_rsrc(g.B + (g.sBz * z + g.sBseg * seg) * 2, b_bytes);
-    }
+    if (s * 16 + wave * 4 + kk >= KB - t.kt * kKB) v = kParked;
+    load_to_lds_b128(rs, lds_base + place(is_a, t.it, b_out) + (s * NW + wave) * 1024, v, KROWS ? 0u : (unsigned)(t.kt * kKB + s * 16) * ld2);
   };
 
   // Fragments of k-step s (16 k): k-contiguous: row r of a block, chunk 2 s + gq; k-major: two transpose reads (see gemm_nt.hip).
@@ -204,84 +207,162 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileGroup grp) 
   const int l16 = lane & 15, sw = (l16 >> 2) & 3;
   const int km_row = gq * 8 + (l16 >> 2), km_low = ((lane >> 4) & 1) * 32 + (l16 & 3) * 8;
   typedef __attribute__((ext_vector_type(4))) short s16x4;
-  auto tr_read = [&](const char* p, int row_bytes) __attribute__((always_inline)) {
+  auto tr_read = [&](const char* p) __attribute__((always_inline)) {
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 4 * row_bytes));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 4 * 256));
     const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
     return make_uint4(l2.x, l2.y, h2.x, h2.y);
   };
-  uint4 fa[2][TI], fb[2][TJ];
-  auto read_frags = [&](int buf, int s, int c) __attribute__((always_inline)) {
-    const char* base = lds + buf * kStage;
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      if constexpr (AK) fa[c][i] = *(const uint4*)(base + (wm * TI + i) * 32 * 128 + (kc_off ^ (s * 32)));
-      else fa[c][i] = tr_read(base + (s * 16 + km_row) * (kBM * 2) + ((((wm * TI + i) ^ sw) & (kBM / 32 - 1)) << 6) + km_low, kBM * 2);
-    }
-#pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      if constexpr (BK) fb[c][j] = *(const uint4*)(base + kOpA + (wn * TJ + j) * 32 * 128 + (kc_off ^ (s * 32)));
-      else fb[c][j] = tr_read(base + kOpA + (s * 16 + km_row) * (kBN * 2) + ((((wn * TJ + j) ^ sw) & (kBN / 32 - 1)) << 6) + km_low, kBN * 2);
-    }
+  // block i of this wavefront's two, k-step s
+  auto frag = [&](bool is_a, int it, int i, int s) __attribute__((always_inline)) {
+    const char* base = lds + place(is_a, it, b_in);
+    const int blk = (is_a ? wm : wn) * 2 + i;
+    if (is_a ? AK : BK) return *(const uint4*)(base + blk * 32 * 128 + (kc_off ^ (s * 32)));
+    return tr_read(base + (s * 16 + km_row) * 256 + (((blk ^ sw) & 3) << 6) + km_low);
   };
-  f32x16 acc[TI][TJ];
+  f32x16 acc[2][2];
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  constexpr int NQ = kLA + kLB, kPer = (NQ + TI * TJ - 1) / (TI * TJ);      // loads behind each MFMA of the last k-step
-  auto kstep = [&](int c, bool ld, int ld_buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int m = 0; m < TI * TJ; ++m) {
-      acc[m / TJ][m % TJ] = mma(fa[c][m / TJ], fb[c][m % TJ], acc[m / TJ][m % TJ]);
-      if (ld) issue(ld_buf, m * kPer, (m + 1) * kPer < NQ ? (m + 1) * kPer : NQ);
-    }
+  // The end of a phase: this wavefront's reads have returned (what they read may be overwritten once all have met), and what the phase
+  // after next multiplies has landed (`younger` loads went out behind it).
+  auto end_phase = [&](auto younger) __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070 | decltype(younger)::value);
+    if constexpr (KROWS) asm volatile("" : "+s"(prow[0]), "+s"(prow[1]), "+s"(prow[2]), "+s"(prow[3])::"memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
   };
+  const auto c4 = std::integral_constant<int, 4>{};
+  const auto c8 = std::integral_constant<int, 8>{};
+  const auto c10 = std::integral_constant<int, 10>{};
+  const auto c12 = std::integral_constant<int, 12>{};
 
-  if (total > 0) {
-    lookup();
-    if constexpr (KROWS) wait_all();
-    issue(0, 0, NQ);
-    advance();
-    lookup();
-    wait_all();
-    __syncthreads();
-    if (total > 1) {
-      issue(1, 0, NQ);
-      advance();
-      lookup();
-    }
-    read_frags(0, 0, 0);
-  }
-  for (int it = 0; it < total; ++it) {
-    const int cur = it & 1;
+  if constexpr (kHalves) {
+    uint4 fa[2][4], fb[2][2][4];
+    // the products of row i, a load behind each: f(number of the product)
+    auto mul = [&](int i, const uint4 (&y)[2][4], auto&& f) __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      read_frags(cur, s + 1, (s + 1) & 1);
+      for (int m = 0; m < 8; ++m) {
+        acc[i][m & 1] = mma(fa[i][m >> 1], y[m & 1][m >> 1], acc[i][m & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        f(m);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto read = [&](uint4 (&f)[4], bool is_a, int it, int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) f[s] = frag(is_a, it, i, s);
+    };
+    auto stage = [&](int it, auto parity) __attribute__((always_inline)) {
+      constexpr int par = decltype(parity)::value;
+      read(fa[1], true, it, 1);
+      mul(0, fb[par], [&](int m) __attribute__((always_inline)) { if (m < 6) issue_half(m < 2, m >> 2, m & 1); });
+      end_phase(c8);
+      read(fa[0], true, it + 1, 0);
+      read(fb[par ^ 1][0], false, it + 1, 0);
+      read(fb[par ^ 1][1], false, it + 1, 1);
+      mul(1, fb[par], [&](int m) __attribute__((always_inline)) {
+        if (m < 2) issue_half(true, 1, m);
+        if (m == 2) advance(nx);
+      });
+      end_phase(c8);
+    };
+    if (total > 0) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) issue_half(q < 2 || q > 5, q >> 2, q & 1);
+        advance(nx);
+      }
+      end_phase(c10);
+      read(fa[0], true, 0, 0);
+      read(fb[0][0], false, 0, 0);
+      read(fb[0][1], false, 0, 1);
+      end_phase(c8);
+      for (int it = 0; it < total; it += 2) {
+        stage(it, std::integral_constant<int, 0>{});
+        if (it + 1 < total) stage(it + 1, std::integral_constant<int, 1>{});
+      }
+    }
+  } else {
+    uint4 fa[2][2][2], fb[2][2][2];                            // [half of a stage][k-step][block]
+    auto read = [&](int it, int h) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          fa[h][s][i] = frag(true, it, i, 2 * h + s);
+          fb[h][s][i] = frag(false, it, i, 2 * h + s);
+        }
+      if (kMixed && h == 1) next(b_in);
+    };
+    // What goes out in half h: its k-steps of stage nx; with a k-contiguous A nothing in the first half, all of A's and B's stages in the second.
+    auto issue = [&](int h, int m, int entry) __attribute__((always_inline)) {         // the load behind product m of a phase
+      if constexpr (AK) {
+        if (h == 1 && m < 4) issue_half(true, m >> 1, m & 1);
+        if (h == 1 && m >= 4) issue_rows(false, m - 4, entry);
+        if (h == 1 && m == 7) { advance(nb); next(b_out); }
+      } else if (m < 4) {
+        issue_rows(m < 2, 2 * h + (m & 1), entry + (m & 1));
+      }
+      if (h == 1 && m == 7) advance(nx);
+    };
+    auto phase = [&](int it, int h, auto younger) __attribute__((always_inline)) {
+      // (first: a look-up that misses the scalar cache takes most of a phase)
+      lookup(2 * (h ^ 1), nx.kt + h, 2 * (h ^ 1));
+      lookup(2 * (h ^ 1) + 1, nx.kt + h, 2 * (h ^ 1) + 1);
+      read(it + h, h ^ 1);
       __builtin_amdgcn_sched_barrier(0);
-      kstep(s & 1, false, 0);
-      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        acc[(m >> 1) & 1][m & 1] = mma(fa[h][m >> 2][(m >> 1) & 1], fb[h][m >> 2][m & 1], acc[(m >> 1) & 1][m & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(h, m, 2 * h);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      end_phase(younger);
+    };
+    if (total > 0) {
+      if constexpr (KROWS) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) lookup(k, nx.kt + (k >> 2), k & 3);
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(prow[0]), "+s"(prow[1]), "+s"(prow[2]), "+s"(prow[3]), "+s"(prow[4]), "+s"(prow[5]), "+s"(prow[6]), "+s"(prow[7])::"memory");
+      }
+#pragma unroll
+      for (int k = 0; k < 32; ++k) {
+        if (kMixed && k == 8) {                                // B's first stage, then A's with B's next
+#pragma unroll
+          for (int s = 0; s < 4; ++s) issue_rows(false, s, 0);
+          advance(nb); next(b_out);
+        }
+        issue((k >> 3) & 1, k & 7, k >> 3 << 1);
+      }
+      lookup(0, nx.kt, 0);
+      lookup(1, nx.kt, 1);
+      end_phase(c12);
+      read(0, 0);
+      if constexpr (AK) end_phase(c12); else end_phase(c8);
+      for (int it = 0; it < total; ++it) {
+        if constexpr (AK) {
+          phase(it, 0, c4); phase(it, 1, c12);
+        } else {
+          phase(it, 0, c8); phase(it, 1, c8);
+        }
+      }
     }
-    if (it + 1 < total) {
-      wait_all();                                              // own loads of stage it+1 (and row look-ups) landed, own reads of this stage done
-      __syncthreads();
-      read_frags(cur ^ 1, 0, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (it + 2 < total) {
-      kstep(1, true, cur);
-      advance();
-      lookup();
-    } else {
-      kstep(1, false, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
   }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070);                          // vmcnt(0) lgkmcnt(0): the epilogue uses LDS
 
   // Epilogue: 32 rows of every wavefront row at a time through LDS, out as whole rows.
-  constexpr int kEpStride = G::kEpStride, kTpr = kBN / 4;       // threads per row
+  constexpr int kTpr = kTN / 4;                                 // threads per row
   const bool to_parts = ksplit > 1;
   TC* C = (TC*)g.C + g.sCz * z;
   float* P = g.parts + (long)(z * ksplit + ks) * g.M * g.ldp;
@@ -295,24 +376,24 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileGroup grp) 
   }
   const bool whole = col + 3 < g.N, vec = whole && g.ldc % 4 == 0 && g.sCz % 4 == 0 && ((uintptr_t)g.C & 15u) == 0;
 #pragma unroll
-  for (int i = 0; i < TI; ++i) {
+  for (int i = 0; i < 2; ++i) {
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < TJ; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) ep[(wm * 32 + 8 * (v >> 2) + 4 * gq + (v & 3)) * kEpStride + (wn * TJ + j) * 32 + r] = acc[i][j][v];
+      for (int v = 0; v < 16; ++v) ep[(wm * 32 + 8 * (v >> 2) + 4 * gq + (v & 3)) * kEpStride + (wn * 2 + j) * 32 + r] = acc[i][j][v];
     __syncthreads();
     if (col < g.N) {
-      constexpr int kStep = 64 * NW / kTpr, kIts = WM * 32 / kStep;
+      constexpr int kStep = 64 * NW / kTpr, kIts = 64 / kStep;
       int crow[kIts];                                          // (looked up before the first store: a load behind a store waits for it)
 #pragma unroll
       for (int q = 0; q < kIts; ++q) {
-        const int rl = tid / kTpr + q * kStep, row = min(m0 + (rl >> 5) * TI * 32 + i * 32 + (rl & 31), M - 1);
+        const int rl = tid / kTpr + q * kStep, row = min(m0 + (rl >> 5) * 64 + i * 32 + (rl & 31), M - 1);
         crow[q] = g.c_rows && !to_parts ? g.c_rows[row] : row;
       }
 #pragma unroll
       for (int q = 0; q < kIts; ++q) {
-        const int rl = tid / kTpr + q * kStep, row = m0 + (rl >> 5) * TI * 32 + i * 32 + (rl & 31);
+        const int rl = tid / kTpr + q * kStep, row = m0 + (rl >> 5) * 64 + i * 32 + (rl & 31);
         if (row >= M) continue;
         const float4 val = *(const float4*)&ep[rl * kEpStride + (tid % kTpr) * 4];
         if (to_parts) {                                        // (ldp is a multiple of 4; what lies past N is padding)
@@ -344,26 +425,25 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(TileGroup grp) 
   }
 }
 
-template <typename TC, bool AK, bool BK, bool KROWS, int TI, int TJ, int WM, int WN>
+template <typename TC, bool AK, bool BK, bool KROWS>
 hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
-  typedef Geo<TI, TJ, WM, WN> G;
-  const auto kernel = gemm_tile_kernel<TC, AK, BK, KROWS, TI, TJ, WM, WN>;
+  const auto kernel = gemm_tile_kernel<TC, AK, BK, KROWS>;
   static std::atomic<unsigned long long> attr_set{0};
-  const hipError_t ea = once_per_device(attr_set, [&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds); });
+  const hipError_t ea = once_per_device(attr_set, [&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds(AK, BK)); });
   if (ea != hipSuccess) return ea;
   TileGroup c = a;
   int blocks[2] = {0, 0};
-  for (int i = 0; i < count; ++i) blocks[i] = cdiv(c.p[i].M, G::kBM) * cdiv(c.p[i].N, G::kBN) * c.p[i].nz * c.p[i].ksplit;
+  for (int i = 0; i < count; ++i) blocks[i] = (cdiv(c.p[i].M, kTM) * cdiv(c.p[i].N, kTN) * c.p[i].nz * c.p[i].ksplit + 7) / 8 * 8;
   c.first1 = count == 2 ? blocks[0] : 0x7fffffff;
-  hipLaunchKernelGGL(kernel, dim3(blocks[0] + blocks[1]), dim3(64 * G::kNW), G::kLds, s, c);
+  hipLaunchKernelGGL(kernel, dim3(blocks[0] + blocks[1]), dim3(256), tile_lds(AK, BK), s, c);
   return hipGetLastError();
 }
 template <typename TC>
 hipError_t launch_layout(const TileGroup& a, int count, bool ak, bool bk, hipStream_t s) {
-  if (ak && bk) return launch_as<TC, true, true, false, 2, 2, 2, 2>(a, count, s);
-  if (ak) return launch_as<TC, true, false, false, 2, 2, 2, 2>(a, count, s);
-  if (a.p[0].k_rows) return launch_as<TC, false, false, true, 2, 2, 2, 2>(a, count, s);
-  return launch_as<TC, false, false, false, 2, 2, 2, 2>(a, count, s);
+  if (ak && bk) return launch_as<TC, true, true, false>(a, count, s);
+  if (ak) return launch_as<TC, true, false, false>(a, count, s);
+  if (a.p[0].k_rows) return launch_as<TC, false, false, true>(a, count, s);
+  return launch_as<TC, false, false, false>(a, count, s);
 }
 
 long tiles_of(const GemmArgs& g) { return (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.nz; }

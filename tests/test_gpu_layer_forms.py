@@ -374,6 +374,26 @@ def test_weight_gradient_product_stages(M, N, K):
     assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max())          # (exact inputs: the order of float sums)
 
 
+@pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128)])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312])
+def test_product_of_few_tiles_stages(M, N, K):
+    """128 x 128 tiles, all three layouts: one to five stages (the ring of two is walked by both parities), ragged last ones, more tile rows than columns (several
+    bands, the last one lower; work-groups of the grid that have no tile) and fewer."""
+    import torch
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator().manual_seed(M + K)
+    A, B = torch.randn(M, K, generator=g).bfloat16().cuda(), torch.randn(K, N, generator=g).bfloat16().cuda()
+    ref = A.double() @ B.double()
+    forms = {"NT": (A, B.t().contiguous(), True, True)}
+    if N % 8 == 0:
+        forms["NN"] = (A, B, True, False)
+    if M % 8 == 0 and N % 8 == 0:
+        forms["TN"] = (A.t().contiguous(), B, False, False)
+    for form, (a, b, ak, bk) in forms.items():
+        got = Bn.gemm(a, b, a_kcontig=ak, b_kcontig=bk, M=M, N=N, K=K)
+        assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max()), form          # (exact inputs: the order of float sums)
+
+
 @pytest.mark.parametrize("T,B", [(1, 16), (5, 13), (9, 16), (13, 16), (30, 16)])
 def test_weight_gradients_over_listed_frames(T, B):
     """The same product walking the list of real frames: fewer than a stage, one, and several."""
