@@ -374,6 +374,14 @@ def test_weight_gradient_product_stages(M, N, K):
     assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max())          # (exact inputs: the order of float sums)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 6, 7, 8, 9])
+@pytest.mark.parametrize("n,B,bidir", [(64, 5, True), (100, 4, False)])
+def test_narrow_layer_rounds(dt, T, n, B, bidir):
+    """Narrow loops walk rounds of four steps, those past the end without effect, and store a frame's outputs a step later."""
+    _layer(T, B, 16, n, bidir, dt)
+
+
 @pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128)])
 @pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312])
 def test_product_of_few_tiles_stages(M, N, K):
