@@ -212,7 +212,7 @@ hipError_t launch_fill_padded(const int* lens, const int* steps, int T, int B, i
 
 struct PFwdDir {
   const unsigned* tab;  // rows one behind the other: frames in this direction's order
-  const uint4* Wf;    // as launch_prep_fwd_ll writes it
+  const uint4* Wf;    // as launch_prep_fwd_ll writes it, or W_h as it lies in memory (w_rows)
   const uint4* Wzero; // one chunk (64 x 16 bytes) of zeros
   uint4* ring0; uint4* ring1;   // [row tile][nkc][64] chunks each
   float* gates;       // [T][B][4n]
@@ -233,6 +233,7 @@ struct PFwdArgs {
   int slab0, slab_tiles;   // likewise (float kernels): first slab of this launch, row tiles per slab
   GridMap map;
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
+  bool w_rows;        // (8 rows a group, n a multiple of 8)
 };
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s);
 int persist_fwd_rows(int B, int n, int ndir); // rows per work-group, 8 or 16, which decides how W_h is packed (8: `paired`)
@@ -406,11 +407,18 @@ struct ZeroRegions {
   void add(void* p, size_t bytes);
 };
 hipError_t launch_fill_zero_many(const ZeroRegions& r, hipStream_t s);
-// The set-up of a bfloat16 single-launch loop in one launch: the fills of `z`, W_h in the kernel's order, (forward) the initial
+// The set-up of a bfloat16 single-launch loop in one launch: the fills of `z`, W_h in the kernel's order (or fetched), (forward) the initial
 // ring, and the frame map of launch_frame_map if fm.fidx is not NULL.
 struct FrameMapArgs { const int* lens; int T, B; int* fidx; int* count; };
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
-                              int nrt, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
+                              int nrt, const FrameMapArgs& fm, const PackRows& rows, const GemmArgs* zx, hipStream_t s);
+// Wf NULL: W_h is not packed but fetched into the last-level cache (the loop reads it as it lies in memory: PFwdArgs::w_rows).
+// zx (few_zx_ok; neither a frame map nor PackRows): the input projection of all frames in the same launch.  W_x is read once per 64 rows, and the limit
+// lies where that has eaten up what the launches saved (a layer's forward pass, us, before / with it; n = 1000): n_in = 2000, two directions, 27 rows
+// 70 / 59, 128 rows 67 / 59, 192 rows 78 / 78, 256 rows 76 / 81; n_in = 620, 384 rows 71 / 62, 512 rows 78 / 70; n_in = 1000, one direction, 512 rows 67 / 60.
+constexpr int kFewZxRows = 512;
+constexpr long kFewZxMacs = 2200000000L;
+bool few_zx_ok(const GemmArgs& g);
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]

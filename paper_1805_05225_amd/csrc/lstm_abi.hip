@@ -343,7 +343,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   float* gates = infer ? (float*)(ws + p.ws_Zx) : (float*)(rs + p.res_gates);
   const long gates_stride = infer ? (long)p.Zx_dir_elems : (long)(p.res_dir_stride / 4);
   bool frames_mapped = false;            // the frame map was written by the set-up launch
-  auto project = [&]() -> int {
+  auto projection = [&]() {
     GemmArgs g = {};
     g.A = x; g.B = W_x; g.C = gates; g.bias = (const float*)b;
     g.M = (int)(T * B); g.N = 4 * p.n; g.K = p.n_in;
@@ -352,6 +352,12 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     g.nseg = 1; g.a_kcontig = true; g.b_kcontig = false; g.in_bf16 = p.bf16; g.out_bf16 = false;
     g.vecA = widest(g.lda, 0, 0, p.esz, 16);
     g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
+    return g;
+  };
+  bool projected = false;                // the set-up launch did it
+  auto project = [&]() -> int {
+    if (projected) return LSTM_OK;
+    GemmArgs g = projection();
     {
       Phase ph(LSTM_PHASE_GEMM_ZX, 1, s);
       if (p.fast_gemm) {
@@ -458,8 +464,11 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   }
   const PackRows rows = pack_rows(p, ws, seq_lens, false, desc);
   const bool paired = rows.slots > 0 || persist_fwd_rows(p.B, p.n, p.D) == 8;    // (how the bf16 single-launch kernel wants W_h)
+  const GemmArgs zx = projection();
+  const bool w_rows = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd && rows.slots == 0 && p.n % 8 == 0 && paired;
+  projected = w_rows && few_zx_ok(zx);
   {
-    Phase ph(LSTM_PHASE_PREP, 5, s);
+    Phase ph(projected ? LSTM_PHASE_GEMM_ZX : LSTM_PHASE_PREP, projected ? 1 : 5, s);
     ZeroRegions z;
     z.add(ws + p.ws_sync, p.sync_bytes);
     if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd)
@@ -467,12 +476,12 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     // (on the single-launch path the fills, the packed W_h and the initial ring are one launch)
     if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd) {
       FrameMapArgs fm = {};
-      if (p.fast_gemm && seq_lens) {   // the input projection below goes over the real frames
+      if (p.fast_gemm && seq_lens && !projected) {   // the input projection below goes over the real frames
         fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
         frames_mapped = true;
       }
-      HIPCHK(launch_prep_fwd_ll(z, W_h, (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
-                                p.nrt, fm, rows, s));
+      HIPCHK(launch_prep_fwd_ll(z, W_h, w_rows ? nullptr : (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
+                                p.nrt, fm, rows, projected ? &zx : nullptr, s));
     } else HIPCHK(launch_fill_zero_many(z, s));
   }
   // single-launch path: bf16 storage, at least two steps, register budget of the kernel
@@ -538,7 +547,9 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   PFwdArgs pa = {};                      // the single-launch kernels' arguments, if one of them takes this problem
   if (use_ll) {
     pa.nkc = p.nkc_ll_f; pa.slots = rows.slots; pa.tab_steps = rows.tab_steps; pa.steps = rows.steps;
-    set_dirs(pa, ws + p.ws_Wf, ll_wf_bytes(p.n, p.nkc_ll_f), (size_t)p.nrt * p.nkc_ll_f * 1024);
+    pa.w_rows = w_rows;
+    if (w_rows) set_dirs(pa, (const char*)W_h, n * 4 * n * p.esz, (size_t)p.nrt * p.nkc_ll_f * 1024);
+    else set_dirs(pa, ws + p.ws_Wf, ll_wf_bytes(p.n, p.nkc_ll_f), (size_t)p.nrt * p.nkc_ll_f * 1024);
   } else {
     pa.nkc = p.nkc_f;                    // (float storage: the per-step kernels' packed W_h and h buffers)
     set_dirs(pa, ws + p.ws_Wf, (size_t)p.ntile_f * 2 * p.nkc_f * 1024, (size_t)p.nrt * p.nkc_f * 1024);

@@ -374,19 +374,62 @@ template <bool PACKED> struct RowTable {
   __device__ __forceinline__ unsigned at(int step, int now) const { return PACKED ? lds[step - (now & ~(kTabSteps - 1))][slot] : 0u; }
 };
 
+// --- W_h as it lies in memory ------------------------------------------------------------------------------------
+// A fragment has a column's k side by side, W_h a row's units: 16 k x 32 units of a gate are one load that goes straight into LDS (64 bytes a row), and
+// ds_read_b64_tr_b16 turns them on the way out (sixteen lanes name eight bytes each of four rows of sixteen units and get a unit each).  Saves the packed
+// copy (n = 1000, both directions: 16 MB read, 17 MB written, 12 us).  A loop's start is then 1.5 us longer if W_h is in the last-level
+// cache and 5 if not, so this is for layers whose set-up fetches it there beforehand (prep_zx_kernel).  Neighbouring work-groups ask for neighbouring pieces at
+// the same time: with the chunks rotated tile by tile, as for packed weights, a start took 4 us more.
+// A chunk of 32 k is 8 KiB of a wavefront's buffer, kWChunks of them in flight.  n is a multiple of 8; units and rows from n on are outside the descriptor: zeros.
+constexpr int kWChunks = 3;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+__device__ __forceinline__ u32x2 turned(const char* p) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
+}
+// chunk_of(it): the chunk of the wavefront's it-th operands; use(it, rows): they are at `rows`, [gate][k][64 bytes].
+template <int ITS, typename C, typename U>
+__device__ __forceinline__ void walk_w_rows(const void* W, int n, int tile2, char (&buf)[kWChunks][8192], int lane, C&& chunk_of, U&& use) {
+  static_assert(ITS > kWChunks && kWChunks == 3, "the counted waits below");
+  const unsigned ldw = 8u * n, u0 = tile2 * 32 + (lane & 3) * 8;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, n * ldw, kBufFlags);
+  const unsigned off0 = u0 < (unsigned)n ? (lane >> 2) * ldw + u0 * 2u : 0x7ff00000u;
+  const unsigned to = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)&buf[0][0]);
+  auto ask = [&](int it) __attribute__((always_inline)) {
+    const unsigned row0 = chunk_of(it) * 32;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)                            // gate i / 2, rows 16 (i & 1) .. + 15
+      asm volatile("s_add_u32 m0, %0, %1\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds" ::"s"(to), "i"((it % kWChunks) * 8192 + i * 1024),
+                   "v"(off0 + ((row0 + (i & 1) * 16u) * ldw + (i >> 1) * 2u * n)), "s"(rs) : "memory", "scc");
+  };
+#pragma unroll
+  for (int it = 0; it < kWChunks; ++it) ask(it);
+#pragma unroll
+  for (int it = 0; it < ITS; ++it) {                       // (loads complete in the order of issue)
+    if (it + 2 < ITS) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else if (it + 1 < ITS) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    use(it, buf[it % kWChunks]);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (read out, before it is written again)
+    if (it + kWChunks < ITS) ask(it + kWChunks);
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // forward: z[8 rows, 4 gates x 32 units] = h[8 rows, K] W[K, 128].  A work-group owns 32 units for 8 batch rows
 // (half a row tile); one load serves two chunks (see make_reader_half), one product two column tiles (see smfmac_b_agpr).  The W_h
 // slice fills the 256 accumulation registers of every lane (n = 1024).
-template <bool PACKED> struct Fwd8Lds {
+template <bool PACKED> struct Fwd8Steps {
   static constexpr int kAhead = 2;                       // frames of x W_x + b that are fetched together (fetch_zx below)
   alignas(16) float red[2][4][8][129];                   // two copies, used by even and odd steps: one barrier per step
   alignas(16) float zxs[kAhead][4][2][4][32];            // [frame][wavefront][row][gate][unit]: a wavefront reads back what it asked for
   alignas(16) unsigned tab[RowTable<PACKED>::kSteps][8];
 };
-template <int NL, bool PACKED>                             // ring loads per wavefront and step: n <= 256 NL; rows one behind the other
-__device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& lds) {
-  constexpr int kAhead = Fwd8Lds<PACKED>::kAhead;
+// (first the rows of W_h, [wavefront][chunk in flight], where they come as they lie in memory)
+template <bool PACKED, bool ROWS> union Fwd8Lds { Fwd8Steps<PACKED> step; char w[4][ROWS ? kWChunks : 1][ROWS ? 8192 : 16]; };
+template <int NL, bool PACKED, bool ROWS = false>          // ring loads per wavefront and step: n <= 256 NL; rows one behind the other; W_h as it lies in memory
+__device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED, ROWS>& lds_) {
+  auto& lds = lds_.step;
+  constexpr int kAhead = Fwd8Steps<PACKED>::kAhead;
   auto& red = lds.red;
   auto& zxs = lds.zxs;
   auto& tab_lds = lds.tab;
@@ -401,10 +444,25 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& ld
   unsigned* err = a.sync;
   bool dead = false;
 
-  const int nitv = PACKED ? (nkc + 3) / 4 : (nkc + 7) / 8, rot = tile2 % nitv;
+  const int nitv = PACKED ? (nkc + 3) / 4 : (nkc + 7) / 8, rot = ROWS ? tile2 * nitv / ((n + 31) / 32) : tile2 % nitv;
   // Operands 2p, 2p + 1 of a gate are the two chunks that load p of the stream fetches.  Those of chunks past the end are loaded
   // from a chunk of zeros that the host keeps behind the packed weights.
   u32x4 w4[2 * NL][4][2];
+  if constexpr (ROWS) {
+    // rows k, k + 1 of the first column tile, then of the second: what elements 0 - 3 of lane group g hold (4 - 7: k + 2, k + 3)
+    const int at = ((lane >> 4) * 4 + ((lane >> 2) & 1)) * 64 + ((lane >> 3) & 1) * 32 + (lane & 3) * 8;
+    walk_w_rows<2 * NL>(d.Wf, n, tile2, lds_.w[wave], lane, [&](int it) { return wave + 4 * (2 * rot_index(it >> 1, rot, nitv) + (it & 1)); },
+        [&](int it, const char* rows) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int set = 0; set < 2; ++set) {
+              const u32x2 lo = turned(rows + q * 2048 + set * 1024 + at), hi = turned(rows + q * 2048 + set * 1024 + 128 + at);
+              w4[it][q][set] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
+            }
+        });
+    __syncthreads();                                       // (the buffer is the steps' from here on)
+  } else {
 #pragma unroll
   for (int it = 0; it < 2 * NL; ++it) {
     const int kc = wave + 4 * (PACKED ? rot_index(it, rot, nitv) : 2 * rot_index(it >> 1, rot, nitv) + (it & 1));
@@ -415,6 +473,7 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED>& ld
         w4[it][q][set] = load_to_agpr(kc < nkc ? &d.Wf[(((long)(tile2 * 4 + q) * nkc + kc) * 2 + set) * 64 + lane] : &d.Wzero[lane]);
   }
   agpr_loads_done();
+  }
   u32x8 w[2 * NL][4];
 #pragma unroll
   for (int it = 0; it < 2 * NL; ++it)
@@ -1950,8 +2009,13 @@ __device__ __forceinline__ void bwd16_body(const PBwdArgs& a, const GridMap& map
 // where the choice below is offered, rows one behind the other in the places of the 8-row form.
 template <int NL>
 __global__ __launch_bounds__(256) void persist_fwd8_kernel(PFwdArgs a) {
-  __shared__ Fwd8Lds<false> lds;
+  __shared__ Fwd8Lds<false, false> lds;
   fwd8_body<NL, false>(a, lds);
+}
+template <int NL>
+__global__ __launch_bounds__(256) void persist_fwd8_rows_w_kernel(PFwdArgs a) {
+  __shared__ Fwd8Lds<false, true> lds;
+  fwd8_body<NL, false, true>(a, lds);
 }
 template <int NIT>
 __global__ __launch_bounds__(256) void persist_fwd16r_kernel(PFwdArgs a) {
@@ -1974,7 +2038,7 @@ __device__ __forceinline__ GridMap rows16_map(GridMap m, int B) {
 }
 // The lengths decide (rows_pay), and they are on the device: the set-up launch writes the decision with the table.
 __global__ __launch_bounds__(256) void persist_fwd_rows_kernel(PFwdArgs a) {
-  __shared__ union { Fwd8Lds<true> r8; Fwd16Lds<8> r16; } lds;
+  __shared__ union { Fwd8Lds<true, false> r8; Fwd16Lds<8> r16; } lds;
   if (__builtin_amdgcn_readfirstlane(a.steps[0]) >= 0) fwd8_body<4, true>(a, lds.r8);
   else fwd16_body<8>(a, rows16_map(a.map, a.B), lds.r16);
 }
@@ -3008,12 +3072,8 @@ struct PrepArgs {
   PackRows rows;                                          // rows one behind the other: one more block (slots > 0)
   int first_pack, first_ring, first_map, backward, paired;
 };
-__global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
-  if (a.rows.slots > 0 && blockIdx.x == 0) {               // (a chain of its own: the longest, so it starts first)
-    pack_rows_body(a.rows);
-    return;
-  }
-  const int bid = (int)blockIdx.x - (a.rows.slots > 0 ? 1 : 0);
+constexpr int kTouch = 4;
+__device__ __forceinline__ void set_up_body(const PrepArgs& a, int bid, int tid) {       // (256 threads, no frame map)
   if (bid < a.first_pack) {
     int k = 0;
 #pragma unroll
@@ -3022,17 +3082,134 @@ __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
     uint32_t* p = (uint32_t*)a.z.ptr[k];
     const size_t nwords = a.z.words[k];
     const size_t nb = (size_t)(a.z.first_block[k + 1] - a.z.first_block[k]);
-    for (size_t i = (size_t)(bid - a.z.first_block[k]) * 256 + threadIdx.x; i < nwords; i += nb * 256) p[i] = 0u;
+    for (size_t i = (size_t)(bid - a.z.first_block[k]) * 256 + tid; i < nwords; i += nb * 256) p[i] = 0u;
   } else if (bid < a.first_ring) {
-    const long idx = (long)(bid - a.first_pack) * 256 + threadIdx.x;
+    const long idx = (long)(bid - a.first_pack) * 256 + tid;
+    if (!a.Wout) {                                         // the loop takes W_h as it is: fetched, for it to be in the last-level cache by then
+      const unsigned* W = (const unsigned*)a.W;            // (a word of every 64 bytes; here by the whole device, there by the XCDs of the loop)
+      unsigned v[kTouch];
+#pragma unroll
+      for (int t = 0; t < kTouch; ++t) v[t] = W[min((((long)(bid - a.first_pack) * kTouch + t) * 256 + tid) * 16, a.w_total - 1)];
+#pragma unroll
+      for (int t = 0; t < kTouch; ++t) asm volatile("" ::"v"(v[t]));
+      return;
+    }
     const int paired = a.rows.slots > 0 ? rows_pay(a.rows) : a.paired;
     if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, paired, a.w_total);
     else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, paired, a.w_total);
   } else if (bid < a.first_map) {
-    pack_state_ll_body((long)(bid - a.first_ring) * 256 + threadIdx.x, a.ring0, a.ring1, a.ring_total);
-  } else {
-    frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.fidx, a.count);
+    pack_state_ll_body((long)(bid - a.first_ring) * 256 + tid, a.ring0, a.ring1, a.ring_total);
   }
+}
+__global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
+  if (a.rows.slots > 0 && blockIdx.x == 0) {               // (a chain of its own: the longest, so it starts first)
+    pack_rows_body(a.rows);
+    return;
+  }
+  const int bid = (int)blockIdx.x - (a.rows.slots > 0 ? 1 : 0);
+  if (bid < a.first_map) set_up_body(a, bid, threadIdx.x);
+  else frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.fidx, a.count);
+}
+// A short batch: the input projection of all frames (few_zx_ok; padded ones too: nobody reads what they get) together with the set-up, which
+// it has nothing to do with.  The product is a read of W_x (32 MB at n_in = 2000, n = 1000, two directions).  As it lies in memory W_x has a row's units
+// side by side where MFMA wants a unit's k: a lane fetches kFewUnits units of eight rows and turns them in registers, after which
+// it holds the operands of that many products, unit kFewUnits i + h of lane i's being column i of product h.  So nothing is staged.
+// A work-group owns 32 units, its eight wavefronts share the chunks of 32 k, two chunks in flight each; their sums meet in LDS.
+// What bounds it is how much a compute unit has in flight, so it is narrow tiles that count: with 128 units a work-group (63 of them, 16-byte loads)
+// the launch took 20.0 us, with 64 16.2, with 32 (250 work-groups, 64 bytes of a row) 15.5; two to four chunks in flight the same, more slower.  Before: set-up
+// 11.8 us (most of it packing W_h), the product in K ranges 12.6, their sum 4.8.
+struct FewZxArgs { const uint16_t* x; const uint16_t* W; const float* bias; float* C; int M, K, N, tiles, ndir, blocks; long sC; };
+constexpr int kFewWaves = 8, kFewUnits = 2, kFewRing = 2;
+template <int MT>
+__device__ __forceinline__ void few_zx_body(const FewZxArgs& a, int block, f32x4 (&part)[kFewWaves][MT][kFewUnits][64]) {
+  constexpr int P = kFewUnits, kCols = 16 * P;             // (a lane's units: one word)
+  const int tile = block % a.tiles, dir = block / a.tiles % a.ndir, r0 = block / a.tiles / a.ndir * 16 * MT, tid = threadIdx.x, lane = tid & 63, g = lane >> 4, i = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), M = a.M, K = a.K, N = a.N;
+  constexpr unsigned kParked = 0x7ff00000u;
+  const unsigned ldw = 2u * N, col = tile * kCols + i * P;
+  const __amdgpu_buffer_rsrc_t w_rs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.W + (long)dir * K * N), 0, (unsigned)K * ldw, kBufFlags);   // (rows past K: outside)
+  const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.x, 0, (unsigned)M * K * 2u, kBufFlags);
+  const unsigned w0 = col < (unsigned)N ? g * 8 * ldw + col * 2u : kParked;
+  const int chunks = (K + 31) / 32;
+  unsigned w[kFewRing][8];
+  u32x4 x[kFewRing][MT];
+  auto fetch = [&](int c, unsigned (&wv)[8], u32x4 (&xv)[MT]) __attribute__((always_inline)) {
+    const unsigned k0 = c * 32 + g * 8;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      xv[m] = __builtin_amdgcn_raw_buffer_load_b128(x_rs, r0 + m * 16 + i < M && k0 < (unsigned)K ? ((r0 + m * 16 + i) * (unsigned)K + k0) * 2u : kParked, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) wv[e] = __builtin_amdgcn_raw_buffer_load_b32(w_rs, w0 + (c * 32 + e) * ldw, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  f32x4 acc[MT][P];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int h = 0; h < P; ++h) acc[m][h] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < kFewRing; ++s) fetch(wave + s * kFewWaves, w[s], x[s]);
+  for (int c = wave; c < chunks; c += kFewRing * kFewWaves) {            // (past the last chunk: zeros, which no memory is read for)
+#pragma unroll
+    for (int s = 0; s < kFewRing; ++s) {
+      const int k0 = (c + s * kFewWaves) * 32 + g * 8;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)                         // (the last piece of a row may reach into the next)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) x[s][m][d] = k0 + 2 * d < K ? x[s][m][d] : 0u;
+#pragma unroll
+      for (int h = 0; h < P; ++h) {
+        const unsigned sel = h & 1 ? 0x07060302u : 0x05040100u;          // the high, the low halves of two words
+        u32x4 b;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) b[d] = __builtin_amdgcn_perm(w[s][2 * d + 1], w[s][2 * d], sel);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+          acc[m][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[s][m]), __builtin_bit_cast(bf16x8, b), acc[m][h], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(c + (s + kFewRing) * kFewWaves, w[s], x[s]);
+    }
+  }
+  // Sums: a thread takes (row tile, product, lane).
+  constexpr int kSums = MT * P * 64;
+  static_assert(kSums <= 512, "a sum each");
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int h = 0; h < P; ++h) part[wave][m][h][lane] = acc[m][h];
+  __syncthreads();
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  if (tid < kSums) {
+#pragma unroll
+    for (int v = 0; v < kFewWaves; ++v) sum += (&part[0][0][0][0])[v * kSums + tid];
+  }
+  __syncthreads();
+  float* out = (float*)&part[0][0][0][0];                  // [row][kOut]: turned into rows
+  constexpr int kOut = kCols + 4;
+  static_assert(MT * 16 * kOut * 4 <= (int)sizeof(part), "the result must fit");
+  if (tid < kSums) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out[(tid / (64 * P) * 16 + (lane >> 4) * 4 + v) * kOut + (lane & 15) * P + wave % P] = sum[v];
+  }
+  __syncthreads();
+  for (int at = tid; at < MT * 4 * kCols; at += 512) {
+    const int row = at / (kCols / 4), c1 = at % (kCols / 4) * 4, c0 = tile * kCols + c1;
+    if (r0 + row >= M || c0 >= N) continue;                     // (N is a multiple of four)
+    float4 v = *(const float4*)&out[row * kOut + c1];
+    if (a.bias) {
+      const float* b = a.bias + (long)dir * N + c0;
+      v.x += b[0]; v.y += b[1]; v.z += b[2]; v.w += b[3];
+    }
+    *(float4*)(a.C + dir * a.sC + (long)(r0 + row) * N + c0) = v;
+  }
+}
+template <int MT>
+__global__ __launch_bounds__(512) void prep_zx_kernel(PrepArgs a, FewZxArgs f) {
+  __shared__ f32x4 part[kFewWaves][MT][kFewUnits][64];
+  if ((int)blockIdx.x < f.blocks) { few_zx_body<MT>(f, blockIdx.x, part); return; }
+  const int bid = ((int)blockIdx.x - f.blocks) * 2 + (threadIdx.x >> 8);
+  if (bid < a.first_map) set_up_body(a, bid, threadIdx.x & 255);
 }
 // The initial state as the left operand of its product with W_h: rows of `ld` elements, rounded to the storage type as the recurrence
 // would feed it and padded with zeros; rows[dir][b] = the frame and row whose pre-activations it goes into (a row without frames: one that nobody reads).
@@ -3136,6 +3313,7 @@ bool slab_fits(K kernel, int ntile, int rows_per_group, int nrow, int ndir) {
 typedef void (*FwdKernel)(PFwdArgs);
 typedef void (*BwdKernel)(PBwdArgs);
 FwdKernel fwd8_for(int n) { return n <= 512 ? persist_fwd8_kernel<2> : persist_fwd8_kernel<4>; }
+FwdKernel fwd8_rows_w_for(int n) { return n <= 512 ? persist_fwd8_rows_w_kernel<2> : persist_fwd8_rows_w_kernel<4>; }
 FwdKernel fwd16_for(int n) { return n <= 512 ? persist_fwd16r_kernel<4> : persist_fwd16r_kernel<8>; }
 BwdKernel bwd8_for(int n) { return n <= 256 ? persist_bwdp_kernel<4, 4> : n <= 512 ? persist_bwdp_kernel<4, 8> : persist_bwdp_kernel<8, 16>; }
 BwdKernel bwd16_for(int n) { return n <= 256 ? persist_bwdp16_kernel<4, 4> : n <= 512 ? persist_bwdp16_kernel<4, 8> : persist_bwdp16_kernel<8, 16>; }
@@ -3178,14 +3356,14 @@ hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s) {
   if (!persist_fwd_fits(a)) return hipErrorCooperativeLaunchTooLarge;
   if (a.slots > 0) return coop_slabs(persist_fwd_rows_kernel, cdiv(a.n, 32), 8, a, s, a.slots / 8);
   const int rows = persist_fwd_rows(a.B, a.n, a.ndir);
-  return coop_slabs(rows == 16 ? fwd16_for(a.n) : fwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
+  return coop_slabs(rows == 16 ? fwd16_for(a.n) : a.w_rows ? fwd8_rows_w_for(a.n) : fwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
 // Would launch_persist_fwd launch anything?  (Asked before the initial state's term is added to the pre-activations,
 // which only the single-launch kernels expect there.)
 bool persist_fwd_fits(const PFwdArgs& a) {
   if (a.nkc > kLLMaxNkcFwd) return false;
   if (!offsets_fit(a.B, a.n, std::max(a.d[0].ldy, a.d[a.ndir - 1].ldy), (long)cdiv(a.B, 16) * a.nkc * 1024)) return false;
-  return slab_fits(fwd8_for(a.n), cdiv(a.n, 32), 8, cdiv(a.B, 8), a.ndir);
+  return slab_fits(a.w_rows ? fwd8_rows_w_for(a.n) : fwd8_for(a.n), cdiv(a.n, 32), 8, cdiv(a.B, 8), a.ndir);
 }
 bool persist_bwd_fits(const PBwdArgs& a) {
   if (!offsets_fit(a.B, a.n, std::max(a.d[0].lddy, a.d[a.ndir - 1].lddy), (long)bwdp_ring_bytes(a.B, a.n))) return false;
@@ -3197,19 +3375,34 @@ hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s) {
   return coop_slabs(rows == 16 ? bwd16_for(a.n) : bwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
-                              int nrt, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s) {
+                              int nrt, const FrameMapArgs& fm, const PackRows& rows, const GemmArgs* zx, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
-  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.paired = paired; a.nk = nkc; a.w_total = (long)(ndir * ll_wf_bytes(n, nkc) / 16);
+  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.paired = paired; a.nk = nkc;
+  a.w_total = Wf ? (long)(ndir * ll_wf_bytes(n, nkc) / 16) : (long)ndir * n * n * 2;       // chunks, or dwords to fetch
   a.ring0 = ring0; a.ring1 = ring1; a.ring_total = (long)ndir * nrt * nkc * 64 * 2;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
-  a.first_ring = a.first_pack + cdiv(a.w_total, 256);
+  a.first_ring = a.first_pack + (int)cdiv(a.w_total, Wf ? 256 : 256 * 16 * kTouch);
   a.first_map = a.first_ring + cdiv(a.ring_total, 256);
   a.backward = 0;
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
   a.rows = rows;
+  if (zx) {
+    const GemmArgs& g = *zx;
+    FewZxArgs f = {(const uint16_t*)g.A, (const uint16_t*)g.B, g.bias, (float*)g.C, g.M, g.K, g.N, cdiv(g.N, 16 * kFewUnits), g.nz, cdiv(g.N, 16 * kFewUnits) * g.nz * cdiv(g.M, 64), g.sCz};
+    const dim3 grid(f.blocks + cdiv(a.first_map, 2)), block(512);
+    if (g.M <= 16) hipLaunchKernelGGL(prep_zx_kernel<1>, grid, block, 0, s, a, f);
+    else if (g.M <= 32) hipLaunchKernelGGL(prep_zx_kernel<2>, grid, block, 0, s, a, f);
+    else hipLaunchKernelGGL(prep_zx_kernel<4>, grid, block, 0, s, a, f);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0) + (rows.slots > 0 ? 1 : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
+}
+// g: the input projection, from the caller's arrays.  16-byte pieces of W_x, 4-byte pieces of x.
+bool few_zx_ok(const GemmArgs& g) {
+  return g.in_bf16 && !g.out_bf16 && g.M > 0 && g.M <= kFewZxRows && (long)g.M * g.K * g.N * g.nz <= kFewZxMacs && g.K % 2 == 0 && g.lda == g.K && g.ldb == g.N && g.ldc == g.N && g.N % 8 == 0 &&
+         g.sBz == (long)g.K * g.N && g.sCz % 4 == 0 && (long)(g.K + 1024) * g.N * 2 < 0x7ff00000L;
 }
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;

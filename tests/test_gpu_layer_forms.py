@@ -382,6 +382,15 @@ def test_narrow_layer_rounds(dt, T, n, B, bidir):
     _layer(T, B, 16, n, bidir, dt)
 
 
+@pytest.mark.parametrize("T,B,n_in,n,bidir", [(2, 1, 2, 104, True), (3, 5, 34, 200, False), (16, 1, 620, 328, True), (17, 1, 256, 1000, True), (4, 8, 94, 264, False),
+                                              (11, 3, 1000, 1000, False), (8, 8, 310, 512, True), (13, 5, 288, 520, True), (16, 32, 30, 136, False), (27, 19, 64, 128, True),
+                                              (9, 1, 33, 200, True), (2, 3, 40, 201, True)])
+def test_projection_with_the_set_up(T, B, n_in, n, bidir):
+    """Few frames: row tiles of 16, 32 and 64, several of them, the limit of 512 rows and one row past it, the last piece of a row of x reaching into the next, a last
+    chunk of k and a last tile of units in part; odd n_in and n, which go the general way.  (Padded frames of x hold NaN.)"""
+    _layer(T, B, n_in, n, bidir, "bf16")
+
+
 @pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128)])
 @pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312])
 def test_product_of_few_tiles_stages(M, N, K):
