@@ -386,9 +386,22 @@ def test_narrow_layer_rounds(dt, T, n, B, bidir):
                                               (11, 3, 1000, 1000, False), (8, 8, 310, 512, True), (13, 5, 288, 520, True), (16, 32, 30, 136, False), (27, 19, 64, 128, True),
                                               (9, 1, 33, 200, True), (2, 3, 40, 201, True)])
 def test_projection_with_the_set_up(T, B, n_in, n, bidir):
-    """Few frames: row tiles of 16, 32 and 64, several of them, the limit of 512 rows and one row past it, the last piece of a row of x reaching into the next, a last
-    chunk of k and a last tile of units in part; odd n_in and n, which go the general way.  (Padded frames of x hold NaN.)"""
-    _layer(T, B, n_in, n, bidir, "bf16")
+    """Inference over few frames: row tiles of 16, 32 and 64, several of them, the limit of 512 rows and one row past it, the last piece of a row of x reaching into the
+    next, a last chunk of k and a last tile of units in part; odd n_in and n, which go the general way.  Padded frames of x hold NaN.  Against a training call, whose
+    sums come in another order."""
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator().manual_seed(T * B + n_in)
+    D = 2 if bidir else 1
+    W_x, W_h = (torch.randn(D, k, 4 * n, generator=g).mul(0.7 / k ** 0.5).bfloat16().cuda() for k in (n_in, n))
+    b, h0, c0 = (torch.randn(D, *s, generator=g).cuda() for s in ((4 * n,), (B, n), (B, n)))
+    lens = torch.randint(1, T + 1, (B,), generator=g, dtype=torch.int32)
+    x = torch.randn(T, B, n_in, generator=g).bfloat16()
+    x[torch.arange(T)[:, None] >= lens[None, :]] = float("nan")
+    for state in ((None, None), (h0, c0)):
+        runs = [Bn.forward(x.cuda(), W_x, W_h, b, *state, lens.cuda(), bidirectional=bidir, flags=flags) for flags in (0, Bn.FLAG_INFERENCE)]
+        for what in ("y", "c", "hT", "cT"):
+            want, got = (r[what].float() for r in runs)
+            assert torch.isfinite(got).all() and float((got - want).norm()) <= 1e-2 * float(want.norm()), what       # (roundings of h and y that fall the other way)
 
 
 @pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128)])
