@@ -91,6 +91,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for problems with both operands k-contiguous, 16-byte aligned rows and K % 8 == 0
 // (launch_gemm routes such problems to it by itself).
 bool gemm_nt_ok(const GemmArgs& g);
+bool gemm_nn_ok(const GemmArgs& g);                   // (launch_gemm_nt takes these too)
 hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for the opposite storage: both operands k-major (A[K][lda], B[K][ldb], 16-byte aligned rows),
 // float C.  Row k of both operands is row k_rows[k] in memory if k_rows is given (launch_gemm routes to it by itself).

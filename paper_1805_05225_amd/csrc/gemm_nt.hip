@@ -2,8 +2,8 @@
 //
 // gemm_dl8_* (operands loaded straight into LDS, eight wavefronts; described where it is defined):
 //     C[M,N] (+)= sum_seg A_seg[M,K] . B_seg[N,K]^T  (+ bias[N]),
-// both operands k-contiguous, rows 16-byte aligned, K a multiple of 8: Zx = X W_x + b (W_x transposed once by `launch_transpose`, a pass that
-// costs a few percent of the product) and dX = DZ W_x^T of long batches.
+// both operands k-contiguous, rows 16-byte aligned, K a multiple of 8: Zx = X W_x + b (W_x k-major, as it lies in memory: gemm_nn8; with an odd n
+// transposed by `launch_transpose` first) and dX = DZ W_x^T of long batches.
 // gemm_tn8_f32: the k-major operand pair of the weight gradients dW_x = X^T DZ, dW_h = Hprev^T DZ.
 // Products with fewer 256 x 256 tiles than fill the device are gemm_tile.hip's.
 #include "common.h"
@@ -78,12 +78,13 @@ __device__ __forceinline__ TileCoord tile_coord(const NtArgs& g) {
 
 // Writes a work-group's 256x256 accumulator tile to C.  The tile is held by 2 x (8 / TN) wavefronts, each
 // 4 x TN MFMA blocks of 32x32 (TN = 4: 2x2 wavefronts of 128x128; TN = 2: 2x4 wavefronts of 128x64).
-template <typename TC, int TN>
+template <typename TC, int TN, bool SPREAD = false>           // SPREAD: the wavefronts' 32-column blocks alternate (block j of all of them, then j + 1)
 __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, const NtArgs& g, int M, int m0, int n0, int z) {
   constexpr int WN = 8 / TN, NW = 2 * WN;            // wavefronts along N, wavefronts in all
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;     // (uniform: rows of C are looked up by scalar loads)
   const int wm = wave / WN, wn = wave % WN;
   const int r = lane & 31, gq = lane >> 5;
+  const auto col_of = [&](int j) { return SPREAD ? j * (WN * 32) + wn * 32 + r : wn * (TN * 32) + j * 32 + r; };
   // Epilogue.  A lane holds column (lane % 32), rows 8*(v/4) + 4*(lane/32) + v%4 of each 32x32 block: stored as
   // it is that would be 128-byte pieces, eight of them per row at different times.  The tile goes through LDS
   // instead (two halves of 128 rows, the main loop's buffers are free by now) and leaves as whole rows: one
@@ -96,7 +97,7 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
   float bv[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    const int col = n0 + wn * (TN * 32) + j * 32 + r;
+    const int col = n0 + col_of(j);
     bv[j] = (bias && col < g.N) ? bias[col] : 0.f;
   }
 #pragma unroll
@@ -109,7 +110,7 @@ __device__ __forceinline__ void store_tile(f32x16 (&acc)[4][TN], char* lds, cons
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int rowl = wm * 64 + ii * 32 + 8 * (v >> 2) + 4 * gq + (v & 3);
-          ep[rowl * kEpStride + wn * (TN * 32) + j * 32 + r] = acc[2 * half + ii][j][v] + bv[j];
+          ep[rowl * kEpStride + col_of(j)] = acc[2 * half + ii][j][v] + bv[j];
         }
     __syncthreads();
     const int col = n0 + lane * 4;
@@ -193,7 +194,11 @@ __device__ __forceinline__ u32x4 make_rsrc(const void* base, unsigned bytes) {
   return r;
 }
 
-template <typename TC, bool RAGGED>
+//
+// BROWS: B lies k-major (W_x as the caller holds it: transposing it first took 17 us of 32 MB, a sixth of the product with 3200 rows).  Half h of a stage of B
+// is then 64 k-rows of columns 128 h .. + 127 (256 bytes in a row, four rows a wavefront-load), the wavefronts' blocks lie accordingly (store_tile: SPREAD),
+// and fragments leave LDS through the transpose read, its 64-byte blocks of row k XORed with k % 4 (see gemm_tn_body).
+template <typename TC, bool RAGGED, bool BROWS = false>
 __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   constexpr int TN = 2;
@@ -226,6 +231,8 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   // k-chunk (l & 7) ^ swizzle(row).  Rows past the operand's end point outside the buffer descriptor and arrive as zeros.
   const int chunk = (lane & 7) ^ ((((wave & 1) * 8 + (lane >> 3)) >> 1) & 7);
   const bool past = chunk >= tail_chunks;                      // this lane's chunk lies past K in a ragged last k-tile
+  const int b_row = wave * 4 + (lane >> 4), b_col = ((((lane >> 2) & 3) ^ (lane >> 4)) * 32) + (lane & 3) * 8;      // BROWS: of load 0 of a half (load 1: 32 rows on)
+  const int b_tail = (g.k_phys_rows ? g.k_phys_rows : K) - (ktiles - 1) * kKB;      // BROWS: rows of B in the last k-tile
   unsigned vo[2][2][2], lrow[2][2][2];                         // [operand][half][load]
   const long a_rows_mem = g.a_rows ? g.a_phys_rows : M;
 #pragma unroll
@@ -240,8 +247,13 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
       const long oa = (ra * g.lda) * 2 + chunk * 16, ob = (rb * g.ldb) * 2 + chunk * 16;
       vo[0][h][j] = (ra >= a_rows_mem || oa > 0x7ffffff0L) ? 0x7ffffff0u : (unsigned)oa;
       vo[1][h][j] = (rb >= g.N || ob > 0x7ffffff0L) ? 0x7ffffff0u : (unsigned)ob;
+      if constexpr (BROWS) {
+        lrow[1][h][j] = kDlOp + h * (kDlOp / 2) + (j * 8 + wave) * 1024;
+        const int col = n0 + h * 128 + b_col;
+        vo[1][h][j] = col < g.N ? (unsigned)(((long)(b_row + j * 32) * g.ldb + col) * 2) : 0x7ffffff0u;
+      }
     }
-  const long a_bytes = a_rows_mem * g.lda * 2, b_bytes = (long)g.N * g.ldb * 2;
+  const long a_bytes = a_rows_mem * g.lda * 2, b_bytes = (long)(BROWS ? (g.k_phys_rows ? g.k_phys_rows : K) : g.N) * g.ldb * 2;
   const unsigned lds_base = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)lds;
   const unsigned rec[2] = {a_bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)a_bytes, b_bytes > 0x7fffffffL ? 0x7fffffffu : (unsigned)b_bytes};
   const char* const base[2] = {g.A + g.sAz * z * 2, g.B + g.sBz * z * 2};
@@ -256,6 +268,13 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
     const u32x4 rs = make_rsrc(base[op] + seg_bytes[op] * t.seg, t.it < total ? rec[op] : 0u);
     const unsigned dst = lds_base + (t.it & 1) * kDlStage, koff = t.kt * (kKB * 2);
     const bool cut = ragged && t.kt == ktiles - 1;
+    if (BROWS && op == 1) {
+      const unsigned boff = (unsigned)t.kt * (unsigned)g.ldb * (kKB * 2u);
+      const int rows = RAGGED && t.kt == ktiles - 1 ? b_tail : kKB;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) load_to_lds_b128(rs, dst + lrow[op][h][j], RAGGED && b_row + j * 32 >= rows ? 0x7ffffff0u : vo[op][h][j], boff);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j) load_to_lds_b128(rs, dst + lrow[op][h][j], (cut && past) ? 0x7ffffff0u : vo[op][h][j], koff);
   };
@@ -264,6 +283,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   // slot (2*s + gq) ^ ((r >> 1) & 7): one XOR with s * 32 per k-step on a per-lane base offset.
   const int fa_off = (wm * 128 + r) * kDlRow + ((gq ^ ((r >> 1) & 7)) * 16);
   const int fb_off = kDlOp + (wn * 64 + r) * kDlRow + ((gq ^ ((r >> 1) & 7)) * 16);
+  const int ft_off = kDlOp + (gq * 8 + ((lane & 15) >> 2)) * 256 + ((wn ^ ((lane & 15) >> 2)) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;     // BROWS
   uint4 fa[2][4], fb[TN][4];                                   // [block][k-step]
   auto read_a = [&](int it, int h) __attribute__((always_inline)) {
     const char* p = lds + (it & 1) * kDlStage;
@@ -274,6 +294,16 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
   };
   auto read_b = [&](int it, int j) __attribute__((always_inline)) {
     const char* p = lds + (it & 1) * kDlStage;
+    if constexpr (BROWS) {
+      typedef __attribute__((ext_vector_type(4))) short s16x4;
+      const auto turned = [](const char* q) { return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)q)); };
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint2 lo = turned(p + ft_off + j * (kDlOp / 2) + s * 4096), hi = turned(p + ft_off + j * (kDlOp / 2) + s * 4096 + 1024);
+        fb[j][s] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < 4; ++s) fb[j][s] = *(const uint4*)(p + (fb_off ^ (s * 32)) + j * 32 * kDlRow);
   };
@@ -323,7 +353,7 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
     if (wm == 0) meet();
     __builtin_amdgcn_s_waitcnt(0x0f70);                        // vmcnt(0): the epilogue uses LDS
   }
-  store_tile<TC, TN>(acc, lds, g, M, m0, n0, z);
+  store_tile<TC, TN, BROWS>(acc, lds, g, M, m0, n0, z);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -496,6 +526,7 @@ template <bool ROWS, bool RANGES> __global__ __launch_bounds__(512, 1) void gemm
 
 // (kernels with literal launch bounds: a bound that depends on a template parameter loses the host-side stub)
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_kernel(NtArgs g) { gemm_dl_body<float, RAGGED>(g); }
+template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_nn8_f32_kernel(NtArgs g) { gemm_dl_body<float, RAGGED, true>(g); }
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_bf16_kernel(NtArgs g) { gemm_dl_body<uint16_t, RAGGED>(g); }
 
 // dst[c][r] = src[r][c] for r < R, c < C ; dst rows are padded with zeros up to ldd.
@@ -586,6 +617,15 @@ bool gemm_nt_ok(const GemmArgs& g) {
          g.sAz % 8 == 0 && g.sBz % 8 == 0 && g.sAseg % 8 == 0 && g.sBseg % 8 == 0 && a16(g.A) && a16(g.B);
 }
 
+// B k-major, as gemm_nt_ok otherwise (one segment, float C)
+bool gemm_nn_ok(const GemmArgs& g) {
+  const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
+  if ((long)g.M * g.lda * 2 > lim || ((long)g.K + kKB) * g.ldb * 2 > lim) return false;
+  return g.in_bf16 && !g.out_bf16 && g.a_kcontig && !g.b_kcontig && !g.lens && !g.k_dev && !g.k_rows && g.nseg == 1 && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
+         g.N % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B) && (!g.k_phys_rows || (g.k_phys_rows <= g.K && g.K - g.k_phys_rows < kKB));
+}
+
 bool gemm_tn_ok(const GemmArgs& g) {
   const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
@@ -660,12 +700,12 @@ hipError_t launch_gemm_tn_ranges(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nz <= 0) return hipSuccess;
-  NtArgs a;
+  NtArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
   a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
   a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
-  a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.m_dev = g.m_dev; a.k_dev = g.k_dev; a.a_phys_rows = g.a_phys_rows;
+  a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.m_dev = g.m_dev; a.k_dev = g.k_dev; a.a_phys_rows = g.a_phys_rows; a.k_phys_rows = g.b_kcontig ? 0 : g.k_phys_rows;
   // the blocked raster pays when every XCD gets several blocks; with few tiles it would leave XCDs idle
   const int sups = cdiv(cdiv(g.M, kT), kSupM) * cdiv(cdiv(g.N, kT), kSupN);
   a.blocked = sups >= 32 ? 1 : 0;
@@ -673,7 +713,8 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   static std::atomic<unsigned long long> dl_attr_set{0};
   const hipError_t ea = once_per_device(dl_attr_set, [] {
     for (const void* k : {(const void*)gemm_dl8_f32_kernel<false>, (const void*)gemm_dl8_f32_kernel<true>,
-                          (const void*)gemm_dl8_bf16_kernel<false>, (const void*)gemm_dl8_bf16_kernel<true>}) {
+                          (const void*)gemm_dl8_bf16_kernel<false>, (const void*)gemm_dl8_bf16_kernel<true>,
+                          (const void*)gemm_nn8_f32_kernel<false>, (const void*)gemm_nn8_f32_kernel<true>}) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kDlLds);
       if (e != hipSuccess) return e;
     }
@@ -682,7 +723,10 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   if (ea != hipSuccess) return ea;
   const dim3 grid(tiles, g.nz);
   const bool ragged = g.K % kKB != 0, bf = g.out_bf16;
-  if (bf && ragged) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<true>, grid, dim3(512), kDlLds, s, a);
+  if (!g.b_kcontig) {
+    if (ragged || a.k_phys_rows % kKB != 0) hipLaunchKernelGGL(gemm_nn8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
+    else hipLaunchKernelGGL(gemm_nn8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);
+  } else if (bf && ragged) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<true>, grid, dim3(512), kDlLds, s, a);
   else if (bf) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<false>, grid, dim3(512), kDlLds, s, a);
   else if (ragged) hipLaunchKernelGGL(gemm_dl8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
   else hipLaunchKernelGGL(gemm_dl8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);

@@ -371,12 +371,14 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           g.k_phys_rows = p.n_in;
           g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
           if (!gemm_tile_ok(g)) { g.K = p.n_in; g.k_phys_rows = 0; g.parts = nullptr; }   // (operands past 2 GB: the generic kernel, which knows no padding)
-        } else {                         // W_x is transposed once so that both operands are k-contiguous
+        } else if (gemm_nn_ok(g)) {      // many tiles: the same
+          g.k_phys_rows = p.n_in;
+        } else {                         // an odd n: W_x is transposed so that both operands are k-contiguous
           HIPCHK(launch_transpose(W_x, ws + p.ws_WxT, p.n_in, 4 * p.n, 4 * n, p.n_in_pad, p.D, (long)p.n_in * 4 * n,
                                   (long)(4 * n) * p.n_in_pad, s));
           g.B = ws + p.ws_WxT; g.ldb = p.n_in_pad; g.sBz = (long)(4 * n) * p.n_in_pad; g.b_kcontig = true;
         }
-        if (seq_lens && (p.zx_nn ? gemm_tile_ok(g) : gemm_nt_ok(g))) {
+        if (seq_lens && (p.zx_nn ? gemm_tile_ok(g) : gemm_nn_ok(g) || gemm_nt_ok(g))) {
           // only real frames are projected: row r of the product is frame fidx[r]; the pre-activations of padded
           // frames stay unwritten and are never read
           int* fidx = (int*)(ws + p.ws_fidx);

@@ -424,6 +424,19 @@ def test_product_of_few_tiles_stages(M, N, K):
         assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max()), form          # (exact inputs: the order of float sums)
 
 
+@pytest.mark.parametrize("M,N", [(4100, 4104), (2049, 8320)])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 136, 200, 320])
+def test_product_of_many_tiles_b_k_major(M, N, K):
+    """256 x 256 tiles with B as it lies in memory: one to five stages, ragged last ones, tiles of which a row or eight columns are left."""
+    import torch
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A, B = (torch.randn(*s, generator=g, device="cuda").bfloat16() for s in ((M, K), (K, N)))
+    got = Bn.gemm(A, B, a_kcontig=True, b_kcontig=False, M=M, N=N, K=K)
+    ref = A.float() @ B.float()
+    assert float((got - ref).abs().max()) < 2e-5 * float(ref.abs().max())          # (exact inputs: the order of float sums, twice)
+
+
 @pytest.mark.parametrize("T,B", [(1, 16), (5, 13), (9, 16), (13, 16), (30, 16)])
 def test_weight_gradients_over_listed_frames(T, B):
     """The same product walking the list of real frames: fewer than a stage, one, and several."""
