@@ -17,8 +17,10 @@
 // out of it: a frame's outputs are stored in the next step, behind its products, its inputs are asked for kAhead frames earlier, what the gate
 // gradients take from the inputs alone is computed behind the products of the step before, addresses are scalar pointers that move a frame a step.  And
 // no step may wait for loads it has just issued (see walk): a wait before the barrier of every step was a third of it backward.
-// us a step, forward and backward, before and now: four rows of n = 64, float 0.59 and 0.79, 0.57 and 0.63; bfloat16 0.48 and 0.72, 0.40 and 0.43; n = 128,
-// float 1.36 and 1.60, 1.27 and 1.50 (256 MFMAs a matrix core: 1.0); bfloat16 0.70 and 1.05, 0.61 and 0.77.  6 and 9 us to start (W_h, the first inputs; n = 82,
+// Two chains of products (four, for shorter chains, cost more in clearing and adding them than they gave:
+// forward 0.56 and 0.39 us for n = 64, backward 0.62 and 0.42).
+// us a step, forward and backward, before and now: four rows of n = 64, float 0.59 and 0.79, 0.54 and 0.58; bfloat16 0.48 and 0.72, 0.37 and 0.40; n = 128,
+// float 1.36 and 1.60, 1.24 and 1.35 (256 MFMAs a matrix core: 1.0); bfloat16 0.70 and 1.05, 0.60 and 0.75.  6 and 9 us to start (W_h, the first inputs; n = 82,
 // bfloat16, four layers of 9 steps, forward only: a call of 84 us is 64 since W_h is read by 16 bytes).
 #include "recurrent_dev.h"
 #include <type_traits>
@@ -238,9 +240,7 @@ __global__ __launch_bounds__(64 * NW) void small_fwd_kernel(SmallFwdArgs a) {
     for (int j4 = 0; j4 < NW / 4; ++j4) av[j4] = *(const operand*)(hbuf[s & 1] + (j4 * 64 + lane) * sizeof(operand));
     __builtin_amdgcn_sched_barrier(0);
     const bool some = tau > 0;
-    f32x4 acc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     // (the first two outputs while the LDS read is on its way, the others and the next inputs behind products)
     store(0, some);
     store(1, some);
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(64 * NW) void small_fwd_kernel(SmallFwdArgs a) {
         static_for<16>([&](auto Bk) __attribute__((always_inline)) {
           constexpr int bk = decltype(Bk)::value;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[i] = mma4<bk>(av[j4][i], w[(4 * j4 + i) * 16 + bk], acc[i]);
+          for (int i = 0; i < 4; ++i) acc[i & 1] = mma4<bk>(av[j4][i], w[(4 * j4 + i) * 16 + bk], acc[i & 1]);
           if (j4 == 0) behind(bk);
         });
       } else {
@@ -264,13 +264,13 @@ __global__ __launch_bounds__(64 * NW) void small_fwd_kernel(SmallFwdArgs a) {
           constexpr int bk = 4 * decltype(Bk)::value;
           acc[0] = mma4<bk>(av[j4], w[j4 * 16 + bk], acc[0]);
           acc[1] = mma4<bk + 1>(av[j4], w[j4 * 16 + bk + 1], acc[1]);
-          acc[2] = mma4<bk + 2>(av[j4], w[j4 * 16 + bk + 2], acc[2]);
-          acc[3] = mma4<bk + 3>(av[j4], w[j4 * 16 + bk + 3], acc[3]);
+          acc[0] = mma4<bk + 2>(av[j4], w[j4 * 16 + bk + 2], acc[0]);
+          acc[1] = mma4<bk + 3>(av[j4], w[j4 * 16 + bk + 3], acc[1]);
           if (j4 == 0 && bk < 12) { behind(bk / 2); behind(bk / 2 + 1); }
         });
       }
     });
-    f32x4 z = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    f32x4 z = acc[0] + acc[1];
     transpose_groups(z);                                     // lane (row r, unit u): its four gates
     was_valid = t < L;                                       // (L is 0 in lanes without a cell)
     const float zh[4] = {z[0], z[1], z[2], z[3]};
@@ -440,11 +440,11 @@ __global__ __launch_bounds__(64 * NW) void small_bwd_kernel(SmallBwdArgs a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) dz[q] = x.valid ? dz[q] : 0.f;
     const u32x2 bits = {pack_bf16x2(dz[0], dz[1]), pack_bf16x2(dz[2], dz[3])};
-    f32x4 acc[CG][4];
+    f32x4 acc[CG][2];
 #pragma unroll
     for (int cg = 0; cg < CG; ++cg)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[cg][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < 2; ++i) acc[cg][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
     // a fourth of the products: blocks of units bk, bk + 4, ... of the wavefront's sixteen
     auto products = [&](auto Part) __attribute__((always_inline)) {
       constexpr int part = decltype(Part)::value;
@@ -454,9 +454,9 @@ __global__ __launch_bounds__(64 * NW) void small_bwd_kernel(SmallBwdArgs a) {
         for (int cg = 0; cg < CG; ++cg) {
           if constexpr (kPer == 1) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[cg][q] = mma4<bk>(dz[q], w[(cg * 4 + q) * 16 + bk], acc[cg][q]);
+            for (int q = 0; q < 4; ++q) acc[cg][q & 1] = mma4<bk>(dz[q], w[(cg * 4 + q) * 16 + bk], acc[cg][q & 1]);
           } else {
-            acc[cg][bk & 3] = mma4<bk>(bits, w[cg * 16 + bk], acc[cg][bk & 3]);
+            acc[cg][bk & 1] = mma4<bk>(bits, w[cg * 16 + bk], acc[cg][bk & 1]);
           }
         }
       });
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(64 * NW) void small_bwd_kernel(SmallBwdArgs a) {
     take(in[(s + 1) % kAhead]);
     products(std::integral_constant<int, 3>{});
 #pragma unroll
-    for (int cg = 0; cg < CG; ++cg) *(f32x4*)&red[s & 1][wave][cg][lane][0] = (acc[cg][0] + acc[cg][1]) + (acc[cg][2] + acc[cg][3]);
+    for (int cg = 0; cg < CG; ++cg) *(f32x4*)&red[s & 1][wave][cg][lane][0] = acc[cg][0] + acc[cg][1];
     meet();
   };
   if (Tn > 0) {
