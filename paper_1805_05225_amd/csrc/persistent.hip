@@ -3046,6 +3046,19 @@ __global__ __launch_bounds__(256) void fill_padded_kernel(FillArgs a) {
   const int L = clamp_len(a.lens, b, a.T);
   if (t < L || t >= a.T || a.steps[0] < 0) return;
   const long row = (long)t * a.B + b, width = (long)a.ndir * a.n;         // (n is even: whole words)
+  const float* src[2];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+    src[d] = d < a.ndir && a.cs[d] ? !a.rev[d] && L > 0 ? a.cs[d] + ((long)(L - 1) * a.B + b) * a.n : a.c0[d] ? a.c0[d] + (long)b * a.n : nullptr : nullptr;
+  // n <= 1024 (persist_pack_slots): four pieces of a lane are a row's, all asked for before anything is stored (one at a time was a chain of up to eight
+  // latencies: 64 rows of 20 - 80 frames, n = 1000, both directions 8.7 us, now 7.4)
+  float4 v[2][4];
+  if (a.vec_c) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[d][k] = src[d] ? ((const float4*)src[d])[min(lane + 64 * k, a.n / 4 - 1)] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
   if (a.vec_y) {
     uint4* y = (uint4*)(a.y + row * width);
     for (int i = lane; i < width / 8; i += 64) y[i] = make_uint4(0, 0, 0, 0);
@@ -3053,14 +3066,16 @@ __global__ __launch_bounds__(256) void fill_padded_kernel(FillArgs a) {
     unsigned* y = (unsigned*)(a.y + row * width);
     for (int i = lane; i < width / 2; i += 64) y[i] = 0u;
   }
-  for (int d = 0; d < a.ndir; ++d) {
-    if (!a.cs[d]) continue;
-    const float* src = !a.rev[d] && L > 0 ? a.cs[d] + ((long)(L - 1) * a.B + b) * a.n : a.c0[d] ? a.c0[d] + (long)b * a.n : nullptr;
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    if (d >= a.ndir || !a.cs[d]) continue;
     float* dst = a.cs[d] + row * a.n;
     if (a.vec_c) {
-      for (int i = lane; i < a.n / 4; i += 64) ((float4*)dst)[i] = src ? ((const float4*)src)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (lane + 64 * k < a.n / 4) ((float4*)dst)[lane + 64 * k] = v[d][k];
     } else {
-      for (int i = lane; i < a.n; i += 64) dst[i] = src ? src[i] : 0.f;
+      for (int i = lane; i < a.n; i += 64) dst[i] = src[d] ? src[d][i] : 0.f;
     }
   }
 }
