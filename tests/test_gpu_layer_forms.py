@@ -384,10 +384,11 @@ def test_narrow_layer_rounds(dt, T, n, B, bidir):
 
 @pytest.mark.parametrize("T,B,n_in,n,bidir", [(2, 1, 2, 104, True), (3, 5, 34, 200, False), (16, 1, 620, 328, True), (17, 1, 256, 1000, True), (4, 8, 94, 264, False),
                                               (11, 3, 1000, 1000, False), (8, 8, 310, 512, True), (13, 5, 288, 520, True), (16, 32, 30, 136, False), (27, 19, 64, 128, True),
-                                              (9, 1, 33, 200, True), (2, 3, 40, 201, True)])
+                                              (9, 1, 33, 200, True), (2, 3, 40, 201, True), (40, 20, 40, 1000, True), (4, 300, 64, 200, True), (3, 40, 48, 1024, True)])
 def test_projection_with_the_set_up(T, B, n_in, n, bidir):
     """Inference over few frames: row tiles of 16, 32 and 64, several of them, the limit of 512 rows and one row past it, the last piece of a row of x reaching into the
-    next, a last chunk of k and a last tile of units in part; odd n_in and n, which go the general way.  Padded frames of x hold NaN.  Against a training call, whose
+    next, a last chunk of k and a last tile of units in part; odd n_in and n, which go the general way; more frames, where only
+    W_h is read as it lies in memory, also in several launches, and sixteen rows a group, where it is not.  Padded frames of x hold NaN.  Against a training call, whose
     sums come in another order."""
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator().manual_seed(T * B + n_in)
