@@ -332,7 +332,7 @@ bool loop_block_pays(int T, int B, int n, int ndir, bool plain_launch, bool back
 size_t loop_block_ring_bytes(int n);
 size_t loop_block_ring_bytes_bwd(int n);
 size_t loop_block_wh_bytes(int n);
-hipError_t launch_pack_blocks(const void* W_h, void* out, int n, hipStream_t s);
+hipError_t launch_pack_blocks(const void* W_h, const BlockFwdArgs& a, hipStream_t s);      // into a.W; clears what launch_block_fwd of the same arguments wants cleared
 hipError_t launch_block_fwd(const BlockFwdArgs& a, hipStream_t s);
 hipError_t launch_block_bwd(const BlockBwdArgs& a, hipStream_t s);
 int device_capacity(const void* kernel);  // work-groups of 256 threads that the device holds at once, one per compute unit at most

@@ -500,7 +500,13 @@ __global__ __launch_bounds__(256) void block_bwd_kernel(BlockBwdArgs a) {
 
 // Forward W_h: [j][i][gate][column tile][chunk][lane] x 16 bytes, scaled by 2^-32.  Thread = (eight k, eight units of a gate): 16-byte reads of eight
 // rows, the 8 x 8 block turned in registers (n = 2048: 23 us, 31 with two-byte reads and a turn through LDS).
-__global__ __launch_bounds__(256) void pack_blocks_kernel(const bf16_t* W_, uint4* out, int n, int I) {
+// Blocks from row `packs` on clear what the loop behind it wants cleared (a launch of its own: two layers of n = 2048, 32 rows, 1043 us a training pass, now 1036).
+__global__ __launch_bounds__(256) void pack_blocks_kernel(const bf16_t* W_, uint4* out, int n, int I, ZeroRegions z, int packs) {
+  if ((int)blockIdx.y >= packs) {
+    const int block = (blockIdx.y - packs) * gridDim.x + blockIdx.x;
+    if (block < z.first_block[z.count]) fill_zero_body(z, block, threadIdx.x);
+    return;
+  }
   const int J = (n + 31) / 32, cb = (J + I - 1) / I;
   const int lo = threadIdx.x & 7, gate = (threadIdx.x >> 3) & 3, k8 = (threadIdx.x >> 5) & 7;      // a block: 64 units, 64 k, the four gates
   const int kk = blockIdx.x * 8 + k8, u8 = blockIdx.y * 8 + lo, u0 = u8 * 8;                       // kk: eights of k, counted through the ranges (16 chunks each)
@@ -541,16 +547,21 @@ int ranges_for(int n) { return cdiv(n, 512); }             // K ranges of the fo
 int fwd_grid(int n) { return 8 * cdiv(cdiv(n, 32), 8) * ranges_for(n); }
 int bwd_grid(int n) { return 16 * cdiv(n, kBlk); }
 
+// Clear before a launch: the rings, and the words in which columns find out that they share an XCD.
+template <typename A>
+ZeroRegions regions_of(const A& a, bool first) {
+  ZeroRegions z;
+  z.add(a.ring, a.ring_bytes);
+  z.add(a.xcc, 256 * 4);
+  if (first) z.add(a.sync, 4);                             // (a wait that expired in an earlier direction stays on record)
+  return z;
+}
 template <typename K, typename A>
-hipError_t launch_blocks(K one, K two, int blocks, A a, hipStream_t s) {
+hipError_t launch_blocks(K one, K two, int blocks, A a, bool cleared, hipStream_t s) {
   for (int row0 = 0; row0 < a.B; row0 += kSlab) {          // (rows never interact; a launch walks all steps of its rows)
     a.row0 = row0;
     hipError_t e;
-    ZeroRegions z;                                         // the rings, and the words in which columns find out that they share an XCD
-    z.add(a.ring, a.ring_bytes);
-    z.add(a.xcc, 256 * 4);
-    if (row0 == 0 && a.first) z.add(a.sync, 4);            // (a wait that expired in an earlier direction stays on record)
-    if ((e = launch_fill_zero_many(z, s)) != hipSuccess) return hipErrorLaunchFailure;
+    if ((row0 > 0 || !cleared) && (e = launch_fill_zero_many(regions_of(a, row0 == 0 && a.first), s)) != hipSuccess) return hipErrorLaunchFailure;
     void* args[] = {&a};
     const void* kernel = (const void*)(a.B - row0 <= 16 ? one : two);
     e = a.plain_launch ? hipLaunchKernel(kernel, dim3(blocks), dim3(256), args, 0, s) : hipLaunchCooperativeKernel(kernel, dim3(blocks), dim3(256), args, 0, s);
@@ -599,15 +610,18 @@ size_t loop_block_ring_bytes_bwd(int n) {
   return 2 * (nb * 32768 + nb * nb * 16 * 1024) + 16384;   // (what unpredicated loads read behind the last share)
 }
 size_t loop_block_wh_bytes(int n) { return (size_t)cdiv(n, 32) * ranges_for(n) * 8 * 16 * 1024; }
-hipError_t launch_pack_blocks(const void* W_h, void* out, int n, hipStream_t s) {
-  hipLaunchKernelGGL(pack_blocks_kernel, dim3(ranges_for(n) * 8, cdiv(n, 64)), dim3(256), 0, s, (const bf16_t*)W_h, (uint4*)out, n, ranges_for(n));
+hipError_t launch_pack_blocks(const void* W_h, const BlockFwdArgs& a, hipStream_t s) {
+  const ZeroRegions z = regions_of(a, a.first);
+  if (z.overflow) return hipErrorInvalidValue;
+  const int columns = ranges_for(a.n) * 8, packs = cdiv(a.n, 64);
+  hipLaunchKernelGGL(pack_blocks_kernel, dim3(columns, packs + cdiv(z.first_block[z.count], columns)), dim3(256), 0, s, (const bf16_t*)W_h, (uint4*)a.W, a.n, ranges_for(a.n), z, packs);
   return hipGetLastError();
 }
 hipError_t launch_block_fwd(const BlockFwdArgs& a, hipStream_t s) {
   BlockFwdArgs c = a;
   c.ni = ranges_for(a.n);
-  return launch_blocks(block_fwd_kernel<1>, block_fwd_kernel<2>, fwd_grid(a.n), c, s);
+  return launch_blocks(block_fwd_kernel<1>, block_fwd_kernel<2>, fwd_grid(a.n), c, true, s);
 }
-hipError_t launch_block_bwd(const BlockBwdArgs& a, hipStream_t s) { return launch_blocks(block_bwd_kernel<1>, block_bwd_kernel<2>, bwd_grid(a.n), a, s); }
+hipError_t launch_block_bwd(const BlockBwdArgs& a, hipStream_t s) { return launch_blocks(block_bwd_kernel<1>, block_bwd_kernel<2>, bwd_grid(a.n), a, false, s); }
 
 }  // namespace lstm

@@ -455,9 +455,9 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       a.plain_launch = (desc->flags & LSTM_FLAG_PLAIN_LAUNCH) != 0; a.first = d == 0;
       {
         Phase ph(LSTM_PHASE_PREP, 1, s);
-        HIPCHK(launch_pack_blocks((const char*)W_h + d * n * 4 * n * p.esz, ws + p.ws_blocks, p.n, s));
+        HIPCHK(launch_pack_blocks((const char*)W_h + d * n * 4 * n * p.esz, a, s));
       }
-      Phase ph(LSTM_PHASE_LOOP_FWD, 2, s);
+      Phase ph(LSTM_PHASE_LOOP_FWD, 2, s);                 // (counted with the clearing, as backward, though that rides in the launch before)
       e = launch_block_fwd(a, s);
       if (e != hipSuccess && (d > 0 || e != hipErrorCooperativeLaunchTooLarge)) return LSTM_ERR_HIP;
     }

@@ -3090,14 +3090,7 @@ struct PrepArgs {
 constexpr int kTouch = 4;
 __device__ __forceinline__ void set_up_body(const PrepArgs& a, int bid, int tid) {       // (256 threads, no frame map)
   if (bid < a.first_pack) {
-    int k = 0;
-#pragma unroll
-    for (int j = 1; j < ZeroRegions::kMax; ++j)
-      if (j < a.z.count && bid >= a.z.first_block[j]) k = j;
-    uint32_t* p = (uint32_t*)a.z.ptr[k];
-    const size_t nwords = a.z.words[k];
-    const size_t nb = (size_t)(a.z.first_block[k + 1] - a.z.first_block[k]);
-    for (size_t i = (size_t)(bid - a.z.first_block[k]) * 256 + tid; i < nwords; i += nb * 256) p[i] = 0u;
+    fill_zero_body(a.z, bid, tid);
   } else if (bid < a.first_ring) {
     const long idx = (long)(bid - a.first_pack) * 256 + tid;
     if (!a.Wout) {                                         // the loop takes W_h as it is: fetched, for it to be in the last-level cache by then

@@ -236,17 +236,7 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t nwords, int tail16) {
   for (; i < nwords; i += stride) p[i] = 0u;
 }
 // several fills in one launch: block b works on the region whose block range holds b
-__global__ void fill_zero_many_kernel(ZeroRegions r) {
-  int k = 0;
-#pragma unroll
-  for (int j = 1; j < ZeroRegions::kMax; ++j)
-    if (j < r.count && (int)blockIdx.x >= r.first_block[j]) k = j;
-  uint32_t* p = (uint32_t*)r.ptr[k];
-  const size_t nwords = r.words[k];
-  const size_t nb = (size_t)(r.first_block[k + 1] - r.first_block[k]);
-  size_t i = (size_t)(blockIdx.x - r.first_block[k]) * blockDim.x + threadIdx.x;
-  for (; i < nwords; i += nb * blockDim.x) p[i] = 0u;
-}
+__global__ void fill_zero_many_kernel(ZeroRegions r) { fill_zero_body(r, blockIdx.x, threadIdx.x); }
 __global__ void copy_kernel(uint32_t* dst, const uint32_t* src, size_t nwords) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
   for (; i < nwords; i += stride) dst[i] = src[i];

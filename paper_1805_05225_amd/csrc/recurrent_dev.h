@@ -5,6 +5,16 @@
 namespace lstm {
 namespace {
 
+// Block `block` (256 threads) of those that clear the regions.
+__device__ __forceinline__ void fill_zero_body(const ZeroRegions& r, int block, int tid) {
+  int k = 0;
+#pragma unroll
+  for (int j = 1; j < ZeroRegions::kMax; ++j)
+    if (j < r.count && block >= r.first_block[j]) k = j;
+  uint32_t* p = (uint32_t*)r.ptr[k];
+  const size_t nwords = r.words[k], nb = (size_t)(r.first_block[k + 1] - r.first_block[k]);
+  for (size_t i = (size_t)(block - r.first_block[k]) * 256 + tid; i < nwords; i += nb * 256) p[i] = 0u;
+}
 // Frame map of a batch of end-padded sequences (see launch_frame_map), the work of one block of 256 threads: four time steps,
 // one wavefront each.  Shared by the kernel of its own and by the set-up kernel of the single-launch loops.
 __device__ __forceinline__ void frame_map_body(int block, const int* lens, int T, int B, int* fidx, int* count) {
