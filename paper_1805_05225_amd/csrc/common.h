@@ -234,10 +234,11 @@ struct PFwdArgs {
   int slab0, slab_tiles;   // likewise (float kernels): first slab of this launch, row tiles per slab
   GridMap map;
   bool plain_launch;  // ordinary instead of cooperative launch (the caller vouches that the device is otherwise idle)
-  bool w_rows;        // (8 rows a group, n a multiple of 8)
+  bool w_rows;        // (persist_fwd_w_rows)
 };
 hipError_t launch_persist_fwd(const PFwdArgs& a, hipStream_t s);
 int persist_fwd_rows(int B, int n, int ndir); // rows per work-group, 8 or 16, which decides how W_h is packed (8: `paired`)
+bool persist_fwd_w_rows(int B, int n, int ndir);   // with those 8: does it read W_h as it lies in memory?
 int persist_bwd_rows(int B, int n, int ndir);
 bool persist_fwd_fits(const PFwdArgs& a);     // would launch_persist_fwd launch anything on this device?
 // Float storage (an initial hidden state goes into the pre-activations, as for bfloat16): Wf is the per-step kernel's packed W_h (launch_pack_wh_fwd), ring0 / ring1 its

@@ -469,7 +469,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   const GemmArgs zx = projection();
   // Only without a reserve: sums come in another order here, and in training a last place decides which frame a maximum over time sends its gradient to
   // (six layers pooled by 8, 200 - 1500 frames: gradients moved by 2.7 %).
-  const bool w_rows = infer && p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd && rows.slots == 0 && p.n % 8 == 0 && paired;
+  const bool w_rows = infer && p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd && rows.slots == 0 && paired && persist_fwd_w_rows(p.B, p.n, p.D);
   projected = w_rows && few_zx_ok(zx);
   {
     Phase ph(projected ? LSTM_PHASE_GEMM_ZX : LSTM_PHASE_PREP, projected ? 1 : 5, s);

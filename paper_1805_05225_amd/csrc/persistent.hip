@@ -3333,6 +3333,10 @@ int persist_fwd_rows(int B, int n, int ndir) {
   const long t32 = cdiv(n, 32);
   return t32 * cdiv(B, 8) * ndir > capacity(fwd8_for(n)) && t32 * cdiv(B, 16) * ndir <= capacity(fwd16_for(n)) ? 16 : 8;
 }
+// W_h as it lies in memory (8 rows a group): where one launch holds the batch.  Not packing saves once, every further launch starts later (inference,
+// us, packed / as it lies; n = 1000, both directions: one launch 74 / 69, three 147 / 145, six 243 / 243; n = 1024: 74 / 71, 143 / 146, 243 / 255; n = 760,
+// one direction: 56 / 54, three launches 114 / 118, six 199 / 211; n = 520, both: 64 / 61, 179 / 184, 233 / 242).
+bool persist_fwd_w_rows(int B, int n, int ndir) { return n % 8 == 0 && (long)cdiv(n, 32) * cdiv(B, 8) * ndir <= capacity(fwd8_rows_w_for(n)); }
 int persist_bwd_rows(int B, int n, int ndir) {
   const long t32 = cdiv(n, 32);
   return t32 * cdiv(B, 8) * ndir > capacity(bwd8_for(n)) && t32 * cdiv(B, 16) * ndir <= capacity(bwd16_for(n)) ? 16 : 8;

@@ -388,7 +388,7 @@ def test_narrow_layer_rounds(dt, T, n, B, bidir):
 def test_projection_with_the_set_up(T, B, n_in, n, bidir):
     """Inference over few frames: row tiles of 16, 32 and 64, several of them, the limit of 512 rows and one row past it, the last piece of a row of x reaching into the
     next, a last chunk of k and a last tile of units in part; odd n_in and n, which go the general way; more frames, where only
-    W_h is read as it lies in memory, also in several launches, and sixteen rows a group, where it is not.  Padded frames of x hold NaN.  Against a training call, whose
+    W_h is read as it lies in memory, and several launches and sixteen rows a group, where it is not.  Padded frames of x hold NaN.  Against a training call, whose
     sums come in another order."""
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator().manual_seed(T * B + n_in)
@@ -403,6 +403,21 @@ def test_projection_with_the_set_up(T, B, n_in, n, bidir):
         for what in ("y", "c", "hT", "cT"):
             want, got = (r[what].float() for r in runs)
             assert torch.isfinite(got).all() and float((got - want).norm()) <= 1e-2 * float(want.norm()), what       # (roundings of h and y that fall the other way)
+
+
+@pytest.mark.parametrize("T,B,n,bidir", [(4, 136, 1000, False), (8, 72, 1024, True), (3, 240, 520, True), (2, 824, 136, False)])
+def test_inference_in_several_launches(T, B, n, bidir):
+    """More rows than a launch holds: W_h is packed, as in training.  Two calls add some sums in another order (the order in which other work-groups' values
+    arrive: below one in a thousand of c); W_h as it lies in memory adds all of them in another (a third of c and more)."""
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator().manual_seed(B)
+    D = 2 if bidir else 1
+    lead = (D,) if bidir else ()
+    W_x, W_h = (torch.randn(*lead, k, 4 * n, generator=g).mul(0.7 / k ** 0.5).bfloat16().cuda() for k in (96, n))
+    b, x = torch.randn(*lead, 4 * n, generator=g).cuda(), torch.randn(T, B, 96, generator=g).bfloat16().cuda()
+    want, got = (Bn.forward(x, W_x, W_h, b, bidirectional=bidir, flags=flags) for flags in (0, Bn.FLAG_INFERENCE))
+    assert torch.isfinite(got["c"]).all() and float((got["c"] - want["c"]).abs().max()) < 1e-4
+    assert float((got["c"] != want["c"]).float().mean()) < 0.05
 
 
 @pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128)])
