@@ -415,11 +415,14 @@ struct FrameMapArgs { const int* lens; int T, B; int* fidx; int* count; };
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
                               int nrt, const FrameMapArgs& fm, const PackRows& rows, const GemmArgs* zx, hipStream_t s);
 // Wf NULL: W_h is not packed but fetched into the last-level cache (the loop reads it as it lies in memory: PFwdArgs::w_rows).
-// zx (few_zx_ok; neither a frame map nor PackRows): the input projection of all frames in the same launch.  W_x is read once per 64 rows, and the limit
-// lies where that has eaten up what the launches saved (a layer's forward pass, us, before / with it; n = 1000): n_in = 2000, two directions, 27 rows
-// 70 / 59, 128 rows 67 / 59, 192 rows 78 / 78, 256 rows 76 / 81; n_in = 620, 384 rows 71 / 62, 512 rows 78 / 70; n_in = 1000, one direction, 512 rows 67 / 60.
+// zx (few_zx_ok; neither a frame map nor PackRows): the input projection of all frames in the same launch.  It pays for what the compute units take: a
+// work-group (32 units, 64 frames) walks all of K, so K times the rounds of 256 of them, and a round of its own costs, too.  A layer's forward pass, us, the
+// projection with the set-up / in launches of its own (8 rows, two directions unless said): n = 1000, n_in = 40, 320 frames (5 rounds) 89 / 90, 384 (6) 100 / 100,
+// 512 (8) 122 / 118; n = 1024, n_in = 128, 384 frames 105 / 102, 512 127 / 121; n = 1000, n_in = 1000, 256 frames (4) 94 / 99; n_in = 2000, 128 frames (2) 75 / 79;
+// n = 520, n_in = 1000, 512 frames (5) 129 / 130; n_in = 2000, 192 frames (2) 77 / 80, 256 (3) 95 / 92; n_in = 4000, 64 frames (1) 56 / 60, 128 (2) 82 / 75.
+// Rows of x that are not whole 16 bytes would be copied first: n = 1000, n_in = 620, 384 frames (6 rounds) 114 / 120, 512 (8) 142 / 142.
 constexpr int kFewZxRows = 512;
-constexpr long kFewZxMacs = 2200000000L;
+constexpr long kFewZxWalk = 5120;
 bool few_zx_ok(const GemmArgs& g);
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction

@@ -3411,10 +3411,11 @@ hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, in
   hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0) + (rows.slots > 0 ? 1 : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-// g: the input projection, from the caller's arrays.  16-byte pieces of W_x, 4-byte pieces of x.
+// g: the input projection, from the caller's arrays.  x by 16 bytes that begin at any whole word, W_x by words, results by 16 bytes.
 bool few_zx_ok(const GemmArgs& g) {
-  return g.in_bf16 && !g.out_bf16 && g.M > 0 && g.M <= kFewZxRows && (long)g.M * g.K * g.N * g.nz <= kFewZxMacs && g.K % 2 == 0 && g.lda == g.K && g.ldb == g.N && g.ldc == g.N && g.N % 8 == 0 &&
-         g.sBz == (long)g.K * g.N && g.sCz % 4 == 0 && (long)(g.K + 1024) * g.N * 2 < 0x7ff00000L;
+  const long rounds = cdiv((long)cdiv(g.N, 16 * kFewUnits) * g.nz * cdiv(g.M, 64), 256);
+  return g.in_bf16 && !g.out_bf16 && g.M > 0 && g.M <= kFewZxRows && rounds * g.K <= kFewZxWalk && rounds <= (g.K % 8 == 0 ? 5 : 6) &&
+         g.K % 2 == 0 && g.N % 4 == 0 && g.lda == g.K && g.ldb == g.N && g.ldc == g.N && g.sBz == (long)g.K * g.N && g.sCz % 4 == 0 && (long)(g.K + 1024) * g.N * 2 < 0x7ff00000L;
 }
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;

@@ -405,6 +405,31 @@ def test_projection_with_the_set_up(T, B, n_in, n, bidir):
             assert torch.isfinite(got).all() and float((got - want).norm()) <= 1e-2 * float(want.norm()), what       # (roundings of h and y that fall the other way)
 
 
+@pytest.mark.parametrize("T,B,n_in,n,bidir,together", [
+    (2, 1, 2, 136, True, True), (2, 3, 6, 200, True, True), (3, 1, 34, 1000, False, True),             # fewer k than a piece of a row, and one more chunk than a whole one
+    (32, 16, 64, 136, True, True), (27, 19, 64, 136, True, False),                                      # 512 rows, and one more
+    (40, 8, 40, 1000, True, True), (41, 8, 40, 1000, True, False), (48, 8, 44, 1000, True, True),       # five rounds of work-groups, six; six of rows that would be copied
+    (24, 8, 2000, 520, True, True), (32, 8, 2000, 520, True, False), (8, 8, 4000, 520, True, True), (9, 15, 4000, 520, True, False)])      # K times rounds
+def test_projection_with_the_set_up_against_the_oracle(T, B, n_in, n, bidir, together):
+    """Both sides of the rule that puts the projection into the set-up launch; which side it is shows in the launches that are counted."""
+    from paper_1805_05225_amd import binding as Bn
+    from oracle import lstm_oracle as O
+    rng = np.random.default_rng(n_in + T)
+    c = P.rnd_case(rng, T, B, n_in, n, 2 if bidir else 1, _lens(rng, T, B), "bf16", scale=2.0 / np.sqrt(n + n_in))
+    sq = (lambda a: a) if bidir else (lambda a: a[0])
+    x, Wx, Wh, b, ln = dev(c["x"], "bf16"), dev(sq(c["W_x"]), "bf16"), dev(sq(c["W_h"]), "bf16"), dev(sq(c["b"])), dev(c["lens"])
+    for state in (False, True):
+        h0, c0 = (sq(c[k]) if state else None for k in ("h0", "c0"))
+        Bn.profile_enable(2)
+        f = Bn.forward(x, Wx, Wh, b, dev(h0), dev(c0), ln, bidirectional=bidir, flags=Bn.FLAG_INFERENCE)
+        Bn.profile_enable(0)
+        launches = {k: v[1] for k, v in Bn.profile_read().items()}
+        assert state or (launches["prep"] == 0) == together, launches
+        want = O.blstm_fwd(c["x"], c["W_x"], c["W_h"], c["b"], h0, c0, c["lens"]) if bidir else O.lstm_fwd(c["x"], sq(c["W_x"]), sq(c["W_h"]), sq(c["b"]), h0, c0, c["lens"], 1)
+        for name, ref in zip(("y", "c", "hT", "cT"), want):
+            check(name, f[name], ref, TOL["bf16"])
+
+
 @pytest.mark.parametrize("T,B,n,bidir", [(4, 136, 1000, False), (8, 72, 1024, True), (3, 240, 520, True), (2, 824, 136, False)])
 def test_inference_in_several_launches(T, B, n, bidir):
     """More rows than a launch holds: W_h is packed, as in training.  Two calls add some sums in another order (the order in which other work-groups' values
