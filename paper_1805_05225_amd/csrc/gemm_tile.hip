@@ -76,8 +76,8 @@ constexpr int kEpStride = kTN + 4, kEpBytes = 64 * kEpStride * 4;               
 constexpr int tile_lds(bool ak, bool bk) { return 2 * kStageBytes + (ak && !bk ? kOpBytes : 0); }      // (k-contiguous A, k-major B: a third stage of B)
 static_assert(2 * kStageBytes >= kEpBytes && 2 * tile_lds(true, false) <= 160 * 1024, "two work-groups to a compute unit");
 
-// KROWS: k-major operands whose row k is row k_rows[k] in memory.
-template <typename TC, bool AK, bool BK, bool KROWS>
+// KROWS: k-major operands whose row k is row k_rows[k] in memory.  PACED (both k-contiguous): half as much on its way (see paced()).
+template <typename TC, bool AK, bool BK, bool KROWS, bool PACED>
 __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   constexpr int NW = 4;
   constexpr bool kMixed = AK && !BK;
@@ -262,9 +262,10 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
     };
     auto stage = [&](int it, auto parity) __attribute__((always_inline)) {
       constexpr int par = decltype(parity)::value;
+      const auto pace = std::integral_constant<int, PACED ? 4 : 8>{};
       read(fa[1], true, it, 1);
       mul(0, fb[par], [&](int m) __attribute__((always_inline)) { if (m < 6) issue_half(m < 2, m >> 2, m & 1); });
-      end_phase(c8);
+      end_phase(pace);
       read(fa[0], true, it + 1, 0);
       read(fb[par ^ 1][0], false, it + 1, 0);
       read(fb[par ^ 1][1], false, it + 1, 1);
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
         if (m < 2) issue_half(true, 1, m);
         if (m == 2) advance(nx);
       });
-      end_phase(c8);
+      end_phase(pace);
     };
     if (total > 0) {
 #pragma unroll
@@ -425,9 +426,9 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   }
 }
 
-template <typename TC, bool AK, bool BK, bool KROWS>
+template <typename TC, bool AK, bool BK, bool KROWS, bool PACED = false>
 hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
-  const auto kernel = gemm_tile_kernel<TC, AK, BK, KROWS>;
+  const auto kernel = gemm_tile_kernel<TC, AK, BK, KROWS, PACED>;
   static std::atomic<unsigned long long> attr_set{0};
   const hipError_t ea = once_per_device(attr_set, [&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, tile_lds(AK, BK)); });
   if (ea != hipSuccess) return ea;
@@ -438,9 +439,18 @@ hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
   hipLaunchKernelGGL(kernel, dim3(blocks[0] + blocks[1]), dim3(256), tile_lds(AK, BK), s, c);
   return hipGetLastError();
 }
+// Up to 256 work-groups have a compute unit each, from 512 on they share it two by two.  In between those alone run ahead of those that share, whose operands
+// have left L2 by the time that they ask for them.  With half as much on its way (a wait for 4 younger loads instead of 8) those alone are slower and the
+// launch ends earlier (work-groups; us, 8 / 4, operands from memory): 1408 x 4000 x 4000 (352) 81 / 76, 1600 x 4000 x 4000 (416) 77 / 72, 1920 x 4000 x 8000
+// (480) 138 / 125, 384 x 20000 x 1024 (471) 28 / 26; but 1280 x 4000 x 8000 (320) 109 / 111, 2400 x 4000 x 2048 (608) 51 / 60.  In the order by rows neighbours share
+// more of what they read, and less on its way is no gain: 6656 x 1000 x 2048 (416) 37 / 41.
+bool paced(const TileArgs& a) {
+  const long tiles_m = cdiv(a.M, kTM), tiles_n = cdiv(a.N, kTN), groups = tiles_m * tiles_n * a.nz * a.ksplit;
+  return tiles_m <= tiles_n && groups >= 352 && groups < 512;
+}
 template <typename TC>
 hipError_t launch_layout(const TileGroup& a, int count, bool ak, bool bk, hipStream_t s) {
-  if (ak && bk) return launch_as<TC, true, true, false>(a, count, s);
+  if (ak && bk) return paced(a.p[0]) ? launch_as<TC, true, true, false, true>(a, count, s) : launch_as<TC, true, true, false>(a, count, s);
   if (ak) return launch_as<TC, true, false, false>(a, count, s);
   if (a.p[0].k_rows) return launch_as<TC, false, false, true>(a, count, s);
   return launch_as<TC, false, false, false>(a, count, s);
