@@ -95,10 +95,13 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   // that each XCD keeps one tile column of B in its L2 and neighbouring columns are read and written at the same time.  More rows: each XCD would
   // read all of A, and takes an eighth of all tiles instead, one behind the other in an order of bands of `high` rows, about as many rows as columns at a
   // time (us, bands of columns and these: 4096 x 2048 x 8192 157 and 139, 3200 x 2000 x 8000 141 and 130; but 1120 x 8192 x 2048 with k-major B 55 and 57).
+  // Not for K ranges of up to five stages, which are over before neighbours drift apart (a layer's forward pass, n = 136, both directions, us: n_in = 620, five stages,
+  // 1600 frames 72 and 75, 1280 frames 69 and 70; n_in = 2000, 1600 frames, eight stages 79 and 75, 960 frames, a little more than five, 72 and 71).
   const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
+  const int ktiles = (K + kKB - 1) / kKB;
   const int tiles_m = (M + kTM - 1) / kTM, tiles_n = (g.N + kTN - 1) / kTN, per_z = tiles_m * tiles_n, tiles = per_z * g.nz * g.ksplit;
   const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), each = (tiles + 7) >> 3;
-  const bool by_rows = tiles_m > tiles_n;
+  const bool by_rows = tiles_m > tiles_n && (g.ksplit == 1 || ktiles * g.nseg > 5 * g.ksplit);
   const int idx = by_rows ? (mine & 7) * each + (mine >> 3) : mine;
   if (idx >= tiles || (by_rows && (mine >> 3) >= each)) return;
   const int zk = idx / per_z, bid = idx - zk * per_z;
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   const int m0 = __builtin_amdgcn_readfirstlane(tm * kTM), n0 = __builtin_amdgcn_readfirstlane(tn * kTN);
   const int ksplit = g.ksplit, z = __builtin_amdgcn_readfirstlane(zk / ksplit), ks = __builtin_amdgcn_readfirstlane(zk - z * ksplit);
 
-  const int ktiles = (K + kKB - 1) / kKB, nstage = ktiles * g.nseg;
+  const int nstage = ktiles * g.nseg;
   const int tail_chunks = (K - (ktiles - 1) * kKB + 7) >> 3;   // 16-byte chunks of a k-contiguous operand in the last k-tile
   // (told to be wave-uniform: divisions leave them in vector registers)
   const int it0 = __builtin_amdgcn_readfirstlane(nstage * ks / ksplit), total = __builtin_amdgcn_readfirstlane(nstage * (ks + 1) / ksplit) - it0;
