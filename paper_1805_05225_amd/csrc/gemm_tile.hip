@@ -246,7 +246,30 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   const auto c10 = std::integral_constant<int, 10>{};
   const auto c12 = std::integral_constant<int, 12>{};
 
-  if constexpr (kHalves) {
+  // One stage or two: nothing to overlap, so all loads and then all products.  The pipeline's loads past the end, its barriers and its last wait cost as
+  // much as the work (us, pipeline / this; k-major B: 3200 x 2000 x 40 10.2 / 9.4, x 128 11.1 / 10.2, 5000 x 2048 x 64 17.0 / 15.8; both k-contiguous: 3200 x 2000 x 64
+  // 10.0 / 9.4, x 128 10.6 / 10.2).
+  if (!KROWS && total <= 2) {
+    for (int k = 0; k < total; ++k) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (AK) issue_half(true, q >> 1, q & 1); else issue_rows(true, q, 0);
+        if constexpr (BK) issue_half(false, q >> 1, q & 1); else issue_rows(false, q, 0);
+      }
+      if constexpr (kMixed) { advance(nb); next(b_out); }
+      advance(nx);
+    }
+    end_phase(std::integral_constant<int, 0>{});
+    for (int it = 0; it < total; ++it) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint4 a[2] = {frag(true, it, 0, s), frag(true, it, 1, s)}, b[2] = {frag(false, it, 0, s), frag(false, it, 1, s)};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q >> 1][q & 1] = mma(a[q >> 1], b[q & 1], acc[q >> 1][q & 1]);
+      }
+      if constexpr (kMixed) next(b_in);
+    }
+  } else if constexpr (kHalves) {
     uint4 fa[2][4], fb[2][2][4];
     // the products of row i, a load behind each: f(number of the product)
     auto mul = [&](int i, const uint4 (&y)[2][4], auto&& f) __attribute__((always_inline)) {

@@ -23,6 +23,7 @@ def _lens(rng, T, B):
     (3, 260, 12, 20, True),                                                 # bias gradient: more slices than the workspace keeps
     (65, 64, 128, 128, False),                                              # products too large for the tiny ones
     (40, 2, 64, 64, False), (21, 17, 100, 96, True),
+    (70, 40, 130, 16, True),                                                # the data gradient: a stage per direction
 ])
 def test_narrow_layer(T, B, n_in, n, bidir, dt):
     _layer(T, B, n_in, n, bidir, dt)
@@ -441,7 +442,9 @@ def test_inference_in_several_launches(T, B, n, bidir):
     W_x, W_h = (torch.randn(*lead, k, 4 * n, generator=g).mul(0.7 / k ** 0.5).bfloat16().cuda() for k in (96, n))
     b, x = torch.randn(*lead, 4 * n, generator=g).cuda(), torch.randn(T, B, 96, generator=g).bfloat16().cuda()
     want, got = (Bn.forward(x, W_x, W_h, b, bidirectional=bidir, flags=flags) for flags in (0, Bn.FLAG_INFERENCE))
-    assert torch.isfinite(got["c"]).all() and float((got["c"] - want["c"]).abs().max()) < 1e-4
+    # (where a last place makes an h fall to the other bfloat16 beside it, 2^-8 of 1, a gate moves by at most 2^-8 times the largest weight, 0.7 / n^0.5 times five, and c by no
+    # more than twice that a step; such an h moves its row from there on, a hundredth of c)
+    assert torch.isfinite(got["c"]).all() and float((got["c"] - want["c"]).abs().max()) < 2 * T * 2 ** -8 * 3.5 / n ** 0.5
     assert float((got["c"] != want["c"]).float().mean()) < 0.05
 
 
