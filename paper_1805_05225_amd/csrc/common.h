@@ -92,6 +92,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // (launch_gemm routes such problems to it by itself).
 bool gemm_nt_ok(const GemmArgs& g);
 bool gemm_nn_ok(const GemmArgs& g);                   // (launch_gemm_nt takes these too)
+bool gemm_nn_pays(const GemmArgs& g);                 // (the others that are gemm_nn_ok are for launch_gemm_tile)
 hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s);
 // Fast bfloat16 kernel for the opposite storage: both operands k-major (A[K][lda], B[K][ldb], 16-byte aligned rows),
 // float C.  Row k of both operands is row k_rows[k] in memory if k_rows is given (launch_gemm routes to it by itself).

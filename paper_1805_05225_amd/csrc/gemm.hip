@@ -329,8 +329,7 @@ hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nz <= 0) return hipSuccess;
   if (gemm_skinny_ok(g)) return launch_gemm_skinny(g, false, s);
-  // B k-major, more tiles than the 128 x 128 kernel is for (us there / here): 4100 x 4104 x 1000 73 / 70, 3200 x 8000 x 2000 160 / 118, 12000 x 8192 x 2048 535 / 348.
-  if (gemm_nn_ok(g) && !gemm_tile_small(g.M, g.N, g.nz)) return launch_gemm_nt(g, s);
+  if (gemm_nn_ok(g) && (gemm_nn_pays(g) || !gemm_tile_ok(g))) return launch_gemm_nt(g, s);
   if (gemm_tile_ok(g) && (gemm_tile_small(g.M, g.N, g.nz) || (g.a_kcontig && !g.b_kcontig))) return launch_gemm_tile(g, s);
   if (gemm_nt_ok(g)) return launch_gemm_nt(g, s);
   if (gemm_tn_ok(g)) return launch_gemm_tn(g, s);

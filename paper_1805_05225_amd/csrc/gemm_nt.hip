@@ -626,6 +626,16 @@ bool gemm_nn_ok(const GemmArgs& g) {
          g.N % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B) && (!g.k_phys_rows || (g.k_phys_rows <= g.K && g.K - g.k_phys_rows < kKB));
 }
 
+// B k-major: on tiles of 256 x 256 (256 of them at a time) rather than 128 x 128?  us there / here, operands from memory.  Few tiles, gemm_tile_small: there.
+// A second round at most half full: there: 4100 x 4096 x 512 (272 tiles) 34 / 39, 10000 x 2048 x 1024 (320) 57 / 70, 6000 x 4000 x 256 (384) 34 / 37; but 3300 x 8000 x 256
+// (416) 38 / 35.  A third at most half full: with a short K: 4100 x 8000 x 256 (544) 47 / 49, 10000 x 4000 x 256 (640) 53 / 57, but 10000 x 4000 x 1024 106 / 101.
+// With the number of rows on the device the host cannot count rounds: here (a forward pass of 60 x 50 frames, half of them real, n_in = 620, n = 1000, both directions, 184 / 176).
+bool gemm_nn_pays(const GemmArgs& g) {
+  const long tiles = (long)cdiv(g.M, kT) * cdiv(g.N, kT) * g.nz;
+  if (gemm_tile_small(g.M, g.N, g.nz)) return false;
+  return g.m_dev || !((tiles > 256 && tiles <= 384) || (tiles > 512 && tiles <= 640 && g.K <= 320));
+}
+
 bool gemm_tn_ok(const GemmArgs& g) {
   const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets

@@ -32,6 +32,7 @@ def test_narrow_layer(T, B, n_in, n, bidir, dt):
 @pytest.mark.parametrize("T,B,n_in,n,bidir", [
     (4, 1, 200, 256, True), (4, 9, 64, 257, True), (5, 17, 250, 512, True), (4, 3, 500, 513, True), (3, 33, 130, 136, False),
     (60, 7, 333, 264, True),
+    (52, 32, 60, 1000, True),                                               # the input projection: many tiles, over listed frames, rows of W_x past the last one
     (3, 1, 40, 1025, False), (5, 17, 72, 1160, False), (4, 33, 33, 1027, True), (5, 32, 64, 2048, False), (6, 20, 40, 1900, False),
 ])
 def test_wider_layer(T, B, n_in, n, bidir):
@@ -468,10 +469,11 @@ def test_product_of_few_tiles_stages(M, N, K):
         assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max()), form          # (exact inputs: the order of float sums)
 
 
-@pytest.mark.parametrize("M,N", [(4100, 4104), (2049, 8320)])
+@pytest.mark.parametrize("M,N", [(4100, 4104), (2049, 8320), (3329, 7944), (2305, 14344)])
 @pytest.mark.parametrize("K", [8, 64, 72, 128, 136, 200, 320])
 def test_product_of_many_tiles_b_k_major(M, N, K):
-    """256 x 256 tiles with B as it lies in memory: one to five stages, ragged last ones, tiles of which a row or eight columns are left."""
+    """B as it lies in memory: one to five stages, ragged last ones, tiles of 256 x 256 of which a row or eight columns are left; 289 and 297 of them, which tiles of
+    128 x 128 take, 448, and 570, which K chooses for."""
     import torch
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator(device="cuda").manual_seed(M + K)
