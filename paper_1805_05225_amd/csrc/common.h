@@ -122,8 +122,6 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s);
 constexpr int kSkinnyMaxRows = 1024;
 bool gemm_skinny_ok(const GemmArgs& g);
 hipError_t launch_gemm_skinny(const GemmArgs& g, bool relu, hipStream_t s);
-// dst[c][r] = src[r][c] (16-bit elements), r < R, c < C, dst rows zero-padded up to ld_dst; nz problems with strides s_src / s_dst.
-hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst, hipStream_t s);
 // Numbers the frames (t, b) with t < lens[b] in (t, b) order: fidx[number] -> frame, count[0] = how many, count[1] = that rounded up
 // to a multiple of 64.
 hipError_t launch_frame_map(const int* lens, int T, int B, int* fidx, int* count, hipStream_t s);

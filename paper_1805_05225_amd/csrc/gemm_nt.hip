@@ -2,8 +2,8 @@
 //
 // gemm_dl8_* (operands loaded straight into LDS, eight wavefronts; described where it is defined):
 //     C[M,N] (+)= sum_seg A_seg[M,K] . B_seg[N,K]^T  (+ bias[N]),
-// both operands k-contiguous, rows 16-byte aligned, K a multiple of 8: Zx = X W_x + b (W_x k-major, as it lies in memory: gemm_nn8; with an odd n
-// transposed by `launch_transpose` first) and dX = DZ W_x^T of long batches.
+// both operands k-contiguous, rows 16-byte aligned, K a multiple of 8: dX = DZ W_x^T of long batches; gemm_nn8: the same with B k-major, Zx = X W_x + b
+// with W_x as it lies in memory.
 // gemm_tn8_f32: the k-major operand pair of the weight gradients dW_x = X^T DZ, dW_h = Hprev^T DZ.
 // Products with fewer 256 x 256 tiles than fill the device are gemm_tile.hip's.
 #include "common.h"
@@ -529,67 +529,6 @@ template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_f32_ke
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_nn8_f32_kernel(NtArgs g) { gemm_dl_body<float, RAGGED, true>(g); }
 template <bool RAGGED> __global__ __launch_bounds__(512, 1) void gemm_dl8_bf16_kernel(NtArgs g) { gemm_dl_body<uint16_t, RAGGED>(g); }
 
-// dst[c][r] = src[r][c] for r < R, c < C ; dst rows are padded with zeros up to ldd.
-__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd, long s_src, long s_dst) {
-  __shared__ uint16_t tile[64][66];
-  src += s_src * blockIdx.z;
-  dst += s_dst * blockIdx.z;
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int rr = r0 + ty + 4 * i, cc = c0 + tx;
-    tile[ty + 4 * i][tx] = rr < R && cc < C ? src[(long)rr * lds_ + cc] : (uint16_t)0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int cc = c0 + ty + 4 * i, rr = r0 + tx;
-    if (cc < C && rr < ldd) dst[(long)cc * ldd + rr] = tile[tx][ty + 4 * i];
-  }
-}
-
-// The same for 16-byte aligned operands (C, lds_, ldd, strides all multiples of 8 elements): a work-group produces 64 consecutive destination
-// columns for 256 source columns.  Source rows are read as 16-byte vectors, the tile is turned in LDS, and every destination row
-// receives one aligned 128-byte run.
-__global__ __launch_bounds__(256) void transpose_rows_kernel(const uint16_t* src, uint16_t* dst, int R, int C, long lds_, long ldd, long s_src, long s_dst) {
-  __shared__ __attribute__((aligned(16))) uint16_t tile[64][264];
-  src += s_src * blockIdx.z;
-  dst += s_dst * blockIdx.z;
-  const int tid = threadIdx.x;
-  const int f0 = blockIdx.x * 64, c0 = blockIdx.y * 256;
-  {
-    const int cv = tid & 31, fr = tid >> 5;
-    const int col = c0 + cv * 8;
-    uint4 v[8];                                    // (all loads in flight: rows and columns outside are read from the edge and dropped)
-#pragma unroll
-    for (int pass = 0; pass < 8; ++pass) v[pass] = *(const uint4*)(src + (long)min(f0 + pass * 8 + fr, R - 1) * lds_ + min(col, C - 8));
-#pragma unroll
-    for (int pass = 0; pass < 8; ++pass) {
-      const bool in = f0 + pass * 8 + fr < R && col < C;
-      *(uint4*)&tile[pass * 8 + fr][cv * 8] = in ? v[pass] : make_uint4(0, 0, 0, 0);
-    }
-  }
-  __syncthreads();
-  {
-    const int g = tid & 7, cl = tid >> 3;          // 8 lanes cover the 64 columns (128 bytes) of one destination row
-    const int c = f0 + g * 8;
-    if (c >= ldd) return;
-#pragma unroll
-    for (int pass = 0; pass < 8; ++pass) {
-      const int sc = cl + 32 * pass;               // source column inside the tile
-      if (c0 + sc >= C) break;
-      uint16_t e[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) e[k] = tile[g * 8 + k][sc];
-      uint4 o;
-      o.x = e[0] | ((unsigned)e[1] << 16); o.y = e[2] | ((unsigned)e[3] << 16);
-      o.z = e[4] | ((unsigned)e[5] << 16); o.w = e[6] | ((unsigned)e[7] << 16);
-      *(uint4*)(dst + (long)(c0 + sc) * ldd + c) = o;
-    }
-  }
-}
-
 // Frame map of a batch of end-padded sequences: frame (t, b) is kept iff t < lens[b].  Kept frames are numbered
 // in (t, b) order: fidx[number] = t*B + b, count[0] = how many are kept,
 // count[1] = count[0] rounded up to a multiple of 64.  One wavefront per time step.
@@ -740,19 +679,6 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   else if (bf) hipLaunchKernelGGL(gemm_dl8_bf16_kernel<false>, grid, dim3(512), kDlLds, s, a);
   else if (ragged) hipLaunchKernelGGL(gemm_dl8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
   else hipLaunchKernelGGL(gemm_dl8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_transpose(const void* src, void* dst, int R, int C, long ld_src, long ld_dst, int nz, long s_src, long s_dst, hipStream_t s) {
-  if (R <= 0 || C <= 0 || nz <= 0) return hipSuccess;
-  const bool aligned = C % 8 == 0 && ld_src % 8 == 0 && ld_dst % 8 == 0 && s_src % 8 == 0 && s_dst % 8 == 0 &&
-                       ((uintptr_t)src & 15u) == 0 && ((uintptr_t)dst & 15u) == 0;
-  if (aligned)
-    hipLaunchKernelGGL(transpose_rows_kernel, dim3(cdiv(ld_dst, 64), cdiv(C, 256), nz), dim3(256), 0, s, (const uint16_t*)src, (uint16_t*)dst, R, C,
-                       ld_src, ld_dst, s_src, s_dst);
-  else
-    hipLaunchKernelGGL(transpose_kernel, dim3(cdiv(ld_dst, 64), cdiv(C, 64), nz), dim3(256), 0, s, (const uint16_t*)src, (uint16_t*)dst, R, C,
-                       ld_src, ld_dst, s_src, s_dst);
   return hipGetLastError();
 }
 

@@ -28,16 +28,16 @@ struct Plan {
   size_t res_gates, res_hprev, res_dir_stride, reserve_bytes;
   // workspace
   size_t ws_Wf, ws_Wb, ws_rows, ws_hfrag0, ws_hfrag1, ws_dzfrag0, ws_dzfrag1, ws_dzwide, ws_hstate, ws_cstate, ws_Dh, ws_Dc, ws_DZ, ws_Zx,
-      ws_colsum, ws_sync, sync_bytes, ws_WxT, ws_xpad, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
+      ws_colsum, ws_sync, sync_bytes, ws_xpad, ws_fidx, ws_count, ws_Wcat, ws_Acat, ws_parts, parts_bytes, workspace_bytes;
   bool single_step, step_fused, step_few; int Kc, ksplit;         // T == 1 inference in bfloat16: the step is one product over [x | h], K cut in ksplit ranges
   bool small;                               // narrow layer: loop_small.hip
   bool blocks;                              // wide bfloat16 layer: loop_block.hip, if the device holds it
   size_t ws_blocks, ws_h0, ws_h0rows;
   bool zx_tiny, dw_tiny;                    // its products by gemm_tiny.hip
   size_t ws_tiny_cnt, ws_tiny_parts;
-  bool zx_nn;                               // few 256 x 256 tiles: Zx from W_x as it lies in memory (gemm_tile.hip)
+  bool zx_nn;                               // Zx of few 256 x 256 tiles: in K ranges (gemm_tile.hip)
   int n_in8;                                // n_in up to whole 16-byte chunks: row length of the padded copy of x there and for dW_x
-  bool fast_gemm; int n_in_pad; long TBp;   // bf16 products through the k-contiguous kernel (operands transposed once)
+  bool fast_gemm; int n_in_pad; long TBp;   // bf16 products through the kernels that load straight into LDS
   size_t hfrag_bytes, dzfrag_bytes, DZ_dir_elems, Zx_dir_elems, Wf_bytes;
 };
 
@@ -144,13 +144,12 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   }
   p->ws_Zx = take(infer && !p->step_fused ? D * p->Zx_dir_elems * 4 * (p->single_step ? p->ksplit : 1) : 0);
   p->ws_colsum = take(infer ? 0 : D * 64 * 4 * n * 4);
-  // transposed / padded operand copies for the fast bf16 products
+  // padded operand copies for the fast bf16 products
   p->fast_gemm = p->bf16 && d->n % 2 == 0;
   p->TBp = (TB + 63) / 64 * 64;
   const bool fg = p->fast_gemm;
   p->n_in8 = p->bf16 ? (d->n_in + 7) / 8 * 8 : (d->n_in + 3) / 4 * 4;
   p->zx_nn = fg && gemm_tile_small(TB, 4L * d->n, p->D);
-  p->ws_WxT = take(fg && !p->zx_nn ? D * 4 * n * p->n_in_pad * 2 : 0);
   p->ws_xpad = take(fg || !p->bf16 ? TB * std::max(fg && !p->zx_nn && p->n_in_pad != d->n_in ? p->n_in_pad : 0, p->n_in8 != d->n_in ? p->n_in8 : 0) * p->esz : 0);
   // frame map of the batch (which frames are real), used to leave padded frames out of the products
   const bool fm = fg || !p->bf16;             // (float storage: its product kernels take the same row maps)
@@ -367,18 +366,11 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           g.A = ws + p.ws_xpad;
         }
         g.K = ldx; g.lda = ldx;
-        if (p.zx_nn) {                   // few tiles: W_x as it lies in memory
-          g.k_phys_rows = p.n_in;
-          g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
-          if (!gemm_tile_ok(g)) { g.K = p.n_in; g.k_phys_rows = 0; g.parts = nullptr; }   // (operands past 2 GB: the generic kernel, which knows no padding)
-        } else if (gemm_nn_ok(g)) {      // many tiles: the same
-          g.k_phys_rows = p.n_in;
-        } else {                         // an odd n: W_x is transposed so that both operands are k-contiguous
-          HIPCHK(launch_transpose(W_x, ws + p.ws_WxT, p.n_in, 4 * p.n, 4 * n, p.n_in_pad, p.D, (long)p.n_in * 4 * n,
-                                  (long)(4 * n) * p.n_in_pad, s));
-          g.B = ws + p.ws_WxT; g.ldb = p.n_in_pad; g.sBz = (long)(4 * n) * p.n_in_pad; g.b_kcontig = true;
-        }
-        if (seq_lens && (p.zx_nn ? gemm_tile_ok(g) : gemm_nn_ok(g) || gemm_nt_ok(g))) {
+        g.k_phys_rows = p.n_in;          // (W_x as it lies in memory)
+        if (p.zx_nn) { g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes; }
+        const bool fast = p.zx_nn ? gemm_tile_ok(g) : gemm_nn_ok(g);
+        if (!fast) { g.K = p.n_in; g.k_phys_rows = 0; g.parts = nullptr; }      // (operands past 2 GiB: the generic kernel, which knows no padding)
+        if (seq_lens && fast) {
           // only real frames are projected: row r of the product is frame fidx[r]; the pre-activations of padded
           // frames stay unwritten and are never read
           int* fidx = (int*)(ws + p.ws_fidx);

@@ -113,6 +113,12 @@ def test_empty_batch_is_a_noop_and_inference_needs_no_reserve():
         assert _fwd(d, reserve=None, c=None) == -7             # valid call, but no gfx950 device here
 
 
+def test_workspace_of_long_batches_holds_no_copy_of_the_weights():
+    """W_x is read as it lies in memory: with whole 16-byte rows of x the workspace of an inference call does not grow with them."""
+    size = lambda n_in: Bn.query(Bn.make_desc(1500, 32, n_in, 1000, Bn.LSTM_BF16_F32STATE, 1, Bn.FLAG_INFERENCE), True)[1]
+    assert size(2048) == size(256)
+
+
 def test_time_pool_argument_errors():
     f, b = Bn.lib.lstm_time_pool_fwd, Bn.lib.lstm_time_pool_bwd
     ok = dict(dtype=1, T=8, B=2, F=16, pool=2)

@@ -483,6 +483,23 @@ def test_product_of_many_tiles_b_k_major(M, N, K):
     assert float((got - ref).abs().max()) < 2e-5 * float(ref.abs().max())          # (exact inputs: the order of float sums, twice)
 
 
+@pytest.mark.parametrize("n_in", [20800, 20803])
+def test_inputs_past_2_gib(n_in):
+    """More than 32-bit byte offsets reach: the generic product, on W_x as the caller holds it, with whole rows of x and with padded ones; the first rows and the last."""
+    from paper_1805_05225_amd import binding as Bn
+    from oracle import lstm_oracle as O
+    B, n, g = 52000, 2, torch.Generator(device="cuda").manual_seed(n_in)
+    x = torch.randn(1, B, n_in, generator=g, device="cuda", dtype=torch.bfloat16)
+    Wx, Wh = (torch.randn(k, 4 * n, generator=g, device="cuda").mul(0.7 / k ** 0.5).bfloat16() for k in (n_in, n))
+    lens = torch.ones(B, dtype=torch.int32, device="cuda")
+    lens[7] = 0
+    f = Bn.forward(x, Wx, Wh, None, None, None, lens, bidirectional=False)
+    for rows in (slice(0, 40), slice(B - 40, B)):
+        want = O.lstm_fwd(host(x[:, rows]), host(Wx), host(Wh), None, None, None, lens[rows].cpu().numpy(), 1)
+        check("y", f["y"][:, rows], want[0], TOL["bf16"])
+        check("c", f["c"].view(1, B, n)[:, rows], want[1], TOL["bf16"])
+
+
 @pytest.mark.parametrize("T,B", [(1, 16), (5, 13), (9, 16), (13, 16), (30, 16)])
 def test_weight_gradients_over_listed_frames(T, B):
     """The same product walking the list of real frames: fewer than a stage, one, and several."""
