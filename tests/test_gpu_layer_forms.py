@@ -98,7 +98,7 @@ def _layer(T, B, n_in, n, bidir, dt):
             P.compare(f, g, *P.run_oracle(c, bidir, direction), TOL[dt])
 
 
-@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 20, 1040), ("bf16", 16, 33, 2048), ("bf16", 5, 9, 330), ("bf16", 4, 6, 64), ("f32", 40, 33, 331),
+@pytest.mark.parametrize("dt,T,B,n", [("bf16", 24, 20, 1040), ("bf16", 16, 33, 2048), ("bf16", 5, 9, 330), ("bf16", 9, 5, 1000), ("bf16", 40, 20, 200), ("bf16", 6, 140, 1000), ("bf16", 4, 6, 64), ("f32", 40, 33, 331),
                                       ("f32", 4, 6, 64), ("f32", 3, 5, 1100)])
 @pytest.mark.parametrize("direction", [1, -1])
 def test_state_in_place(dt, T, B, n, direction):
@@ -388,10 +388,9 @@ def test_narrow_layer_rounds(dt, T, n, B, bidir):
                                               (11, 3, 1000, 1000, False), (8, 8, 310, 512, True), (13, 5, 288, 520, True), (16, 32, 30, 136, False), (27, 19, 64, 128, True),
                                               (9, 1, 33, 200, True), (2, 3, 40, 201, True), (40, 20, 40, 1000, True), (4, 300, 64, 200, True), (3, 40, 48, 1024, True)])
 def test_projection_with_the_set_up(T, B, n_in, n, bidir):
-    """Inference over few frames: row tiles of 16, 32 and 64, several of them, the limit of 512 rows and one row past it, the last piece of a row of x reaching into the
-    next, a last chunk of k and a last tile of units in part; odd n_in and n, which go the general way; more frames, where only
-    W_h is read as it lies in memory, and several launches and sixteen rows a group, where it is not.  Padded frames of x hold NaN.  Against a training call, whose
-    sums come in another order."""
+    """Inference over few frames: row tiles of 16, 32 and 64, several of them, the last piece of a row of x reaching into the next, a last chunk of k and a last tile of
+    units in part; odd n_in and n, and up to 128 units, which go other ways; more frames, where only W_h is read as it lies in memory, and several launches and
+    sixteen rows a group, where it is not.  Padded frames of x hold NaN.  Against a training call, whose sums come in another order; the test below has the oracle."""
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator().manual_seed(T * B + n_in)
     D = 2 if bidir else 1
