@@ -46,7 +46,8 @@
  *     between work-groups with 16 significant bits, and the others as multiples of 2^-117 (fewer than 24 bits below 2^-94).
  *     Float products hold all 24 bits of their operands, the smallest floats included (but for an |h| below 2^-110, which no gate can feel).
  *   - The loops of 128 < n <= 1024 add a step's products in the order in which the other work-groups' values arrive: two calls with the same inputs
- *     agree to the rounding of float sums (and of what is stored in bfloat16), not bit for bit.  LSTM_FLAG_PER_STEP repeats its bits.
+ *     agree to the rounding of float sums (and of what is stored in bfloat16), not bit for bit.  So do a call with LSTM_FLAG_INFERENCE and one
+ *     without it: in bfloat16 they may add all products of a layer in different orders.  LSTM_FLAG_PER_STEP repeats its bits.
  *   - Return value: 0 on success, a negative lstm_status otherwise.  Arguments are validated on
  *     the host before the first HIP call, so every argument error is reported without a GPU.
  *     Nothing throws or aborts across this boundary.  LSTM_OK says that the work was enqueued; it does not cover

@@ -102,7 +102,7 @@ hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s);
 int gemm_tn_ranges(const GemmArgs& g);
 size_t gemm_tn_parts_bytes(long M, long N, long K, int nz);
 hipError_t launch_gemm_tn_ranges(const GemmArgs& g, hipStream_t s);
-// bfloat16 products with few 256 x 256 tiles, and A k-contiguous x B k-major at any size (gemm_tile.hip; launch_gemm routes to it by itself).
+// bfloat16 products with few 256 x 256 tiles, and A k-contiguous x B k-major where gemm_nn_pays does not say otherwise (gemm_tile.hip; launch_gemm routes to it by itself).
 // It cuts K into ranges of its own if `parts` holds gemm_tile_parts_bytes.
 bool gemm_tile_ok(const GemmArgs& g);
 bool gemm_tile_small(long M, long N, int nz);

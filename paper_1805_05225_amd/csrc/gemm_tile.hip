@@ -81,7 +81,7 @@ template <typename TC, bool AK, bool BK, bool KROWS, bool PACED>
 __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   constexpr int NW = 4;
   constexpr bool kMixed = AK && !BK;
-  constexpr bool kHalves = AK && BK;      // a phase is a quarter of the blocks over the stage's 64 k (else: all blocks over 16 k)
+  constexpr bool kHalves = AK && BK;      // a phase is one row of blocks, half of them, over the stage's 64 k (else: all blocks over 32 k)
   static_assert(!KROWS || (!AK && !BK), "a list of rows: both operands k-major");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -526,8 +526,10 @@ bool gemm_tile_ok(const GemmArgs& g) {
          a16(g.A) && a16(g.B) && !(g.accumulate && g.out_bf16);
 }
 
-// Fewer 256 x 256 tiles than fill the device's 256 compute units: those of gemm_nt.hip would leave some idle for the whole product.  The line
-// lies between 192 tiles (1600 real of 3000 rows x 4000 x 1000: 55 us there, 24 here) and 237 (768 x 20000 x 1000: 44 us there, 49 here).
+// Fewer 256 x 256 tiles than fill the device's 256 compute units: those of gemm_nt.hip would leave some idle for the whole product.  us there / here, all rows real,
+// operands from memory: both k-contiguous 3000 x 2300 x 2048 (108 tiles) 46 / 38, 3300 x 2800 x 2048 (143) 47 / 53, 3300 x 4000 x 2048 (208) 56 / 74; k-major B, 143
+// tiles, 46 / 58; both k-major, 3000 x 3600 x 1000 (180) 35 / 38, 3296 x 4000 x 1000 (208) 37 / 46.  The count is of padded rows, though, and a batch of sequences is often half
+// padding: 200 tiles then hold 100 real ones, which is where the two are equal (1600 real of 3000 rows x 4000 x 1000, 192 tiles: 55 / 24).
 bool gemm_tile_small(long M, long N, int nz) { return (long)cdiv(M, 256) * cdiv(N, 256) * nz <= 200; }
 
 size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg) {

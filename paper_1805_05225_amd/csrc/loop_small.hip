@@ -69,7 +69,6 @@ template <> struct Elem<bf16_t> {
   typedef u32x2 reg;                     // four k
   static constexpr int kPer = 4;
 };
-__device__ __forceinline__ u32x2 pack4(uint16_t a, uint16_t b, uint16_t c, uint16_t d) { return (u32x2){a | ((unsigned)b << 16), c | ((unsigned)d << 16)}; }
 
 __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {      // round to nearest even, low half first
   typedef __attribute__((ext_vector_type(2))) float f32x2_;
@@ -397,7 +396,7 @@ __global__ __launch_bounds__(64 * NW) void small_bwd_kernel(SmallBwdArgs a) {
     for (int i = tid; i < a.ncounters; i += 64 * NW) a.counters[i] = 0u;
   const int L = !active ? 0 : a.lens ? max(0, min((int)len_bits, Tn)) : Tn;
   // What the gate gradients take from a frame's inputs alone: dc = Dc + dh f_c, Dc' = dc gf, dz = (dc f_i, dc f_f, dc f_g, dh f_o), dh = dy + Dh
-  // (lstm_cell_grad has the plain form).  The inputs are taken, and tanh of the state, behind the products of the step before; the rest
+  // (lstm_cell_grad has the plain form; the factors are multiplied in another order here, with as many roundings, so last places differ).  The inputs are taken, and tanh of the state, behind the products of the step before; the rest
   // goes where the compiler finds room, the read of the shares of Dh among it.  (Taken by moves that it cannot put off: what it does with a place that
   // is being loaded again is waited for together with all that has been asked for since.)
   struct { float gi, gf, gg, go, c_prev, dy, tc; bool valid; } x;
