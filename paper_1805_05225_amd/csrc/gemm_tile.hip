@@ -97,11 +97,15 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   // time (us, bands of columns and these: 4096 x 2048 x 8192 157 and 139, 3200 x 2000 x 8000 141 and 130; but 1120 x 8192 x 2048 with k-major B 55 and 57).
   // Not for K ranges of up to five stages, which are over before neighbours drift apart (a layer's forward pass, n = 136, both directions, us: n_in = 620, five stages,
   // 1600 frames 72 and 75, 1280 frames 69 and 70; n_in = 2000, 1600 frames, eight stages 79 and 75, 960 frames, a little more than five, 72 and 71).
+  // Both operands k-major, several K ranges or directions: no two of them read the same rows, so always an eighth each, whole ranges where they come out even; dealt
+  // round, every XCD read every row of A (both products of weight gradients, us, a round / an eighth: 24955 frames, both directions, n = 296, n_in = 592
+  // 221 / 153, n_in = 65 124 / 79; 9600 frames of n = 200, n_in = 400 66 / 42; 16000 of n = 512, n_in = 1024 222 / 220).
   const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
   const int ktiles = (K + kKB - 1) / kKB;
   const int tiles_m = (M + kTM - 1) / kTM, tiles_n = (g.N + kTN - 1) / kTN, per_z = tiles_m * tiles_n, tiles = per_z * g.nz * g.ksplit;
   const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), each = (tiles + 7) >> 3;
-  const bool by_rows = tiles_m > tiles_n && (g.ksplit == 1 || ktiles * g.nseg > 5 * g.ksplit);
+  const bool apart = !AK && !BK && g.nz * g.ksplit > 1;
+  const bool by_rows = apart || (tiles_m > tiles_n && (g.ksplit == 1 || ktiles * g.nseg > 5 * g.ksplit));
   const int idx = by_rows ? (mine & 7) * each + (mine >> 3) : mine;
   if (idx >= tiles || (by_rows && (mine >> 3) >= each)) return;
   const int zk = idx / per_z, bid = idx - zk * per_z;
