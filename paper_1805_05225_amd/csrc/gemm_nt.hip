@@ -569,9 +569,10 @@ bool gemm_nn_ok(const GemmArgs& g) {
 // A second round at most half full: there: 4100 x 4096 x 512 (272 tiles) 34 / 39, 10000 x 2048 x 1024 (320) 57 / 70, 6000 x 4000 x 256 (384) 34 / 37; but 3300 x 8000 x 256
 // (416) 38 / 35.  A third at most half full: with a short K: 4100 x 8000 x 256 (544) 47 / 49, 10000 x 4000 x 256 (640) 53 / 57, but 10000 x 4000 x 1024 106 / 101.
 // With the number of rows on the device the host cannot count rounds: here (a forward pass of 60 x 50 frames, half of them real, n_in = 620, n = 1000, both directions, 184 / 176).
+// One row of tiles of 128, or one column: there, where no tile is half empty: 64 x 60000 x 256 16 / 25, x 2048 55 / 64, 128 x 200000 x 768 94 / 110, 60000 x 128 x 256 17 / 21.
 bool gemm_nn_pays(const GemmArgs& g) {
   const long tiles = (long)cdiv(g.M, kT) * cdiv(g.N, kT) * g.nz;
-  if (gemm_tile_small(g.M, g.N, g.nz)) return false;
+  if (gemm_tile_small(g.M, g.N, g.nz) || g.M <= kT / 2 || g.N <= kT / 2) return false;
   return g.m_dev || !((tiles > 256 && tiles <= 384) || (tiles > 512 && tiles <= 640 && g.K <= 320));
 }
 
