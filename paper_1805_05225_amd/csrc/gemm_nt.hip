@@ -566,14 +566,29 @@ bool gemm_nn_ok(const GemmArgs& g) {
 }
 
 // B k-major: on tiles of 256 x 256 (256 of them at a time) rather than 128 x 128?  us there / here, operands from memory.  Few tiles, gemm_tile_small: there.
-// A second round at most half full: there: 4100 x 4096 x 512 (272 tiles) 34 / 39, 10000 x 2048 x 1024 (320) 57 / 70, 6000 x 4000 x 256 (384) 34 / 37; but 3300 x 8000 x 256
-// (416) 38 / 35.  A third at most half full: with a short K: 4100 x 8000 x 256 (544) 47 / 49, 10000 x 4000 x 256 (640) 53 / 57, but 10000 x 4000 x 1024 106 / 101.
-// With the number of rows on the device the host cannot count rounds: here (a forward pass of 60 x 50 frames, half of them real, n_in = 620, n = 1000, both directions, 184 / 176).
 // One row of tiles of 128, or one column: there, where no tile is half empty: 64 x 60000 x 256 16 / 25, x 2048 55 / 64, 128 x 200000 x 768 94 / 110, 60000 x 128 x 256 17 / 21.
+// A second round at most half full: there while K is short, how short hangs on what neighbours share.  About as many rows as columns, or more: 3300 x 5600 x 1024 64 / 69,
+// 9000 x 2048 x 1024 62 / 72, x 2048 101 / 113, but 6000 x 4000 x 2048 125 / 121.  Wider, or fewer than 16 tiles of 128 one way: 1772 x 11120 x 640 49 / 55, 1300 x 13000 x 640 46 / 54,
+// 18000 x 1000 x 640 53 / 58, but 2000 x 10000 x 1024 73 / 69, 20000 x 1024 x 1024 73 / 71.  Fewer than 8: 700 x 25000 x 256 37 / 40, x 640 57.4 / 56.9, 640 x 30000 x 256 (354 tiles, 83 % full)
+// 32 / 34, x 320 40 / 38, 500 x 45000 x 256 (352, full) 49 / 43; but with a quarter of the larger tiles empty at any K: 300 x 40000 x 640 44 / 51, x 2048 90 / 104.
+// A third at most half full: 4100 x 8000 x 256 (544 tiles) 47 / 49, 10000 x 4000 x 256 (640) 53 / 57, but x 1024 106 / 101, and 2000 x 19000 x 128 60 / 58.
+// One or two stages of K also with a second round full, a third nearly, a fourth half: 8192 x 4096 x 128 (512) 38 / 43, 380 x 60000 x 128 (470, a quarter empty) 29 / 32, 6000 x 8192 x 128
+// (768) 55 / 58, 5683 x 9152 x 128 (828) 58 / 63, 7000 x 8000 x 128 (896) 59 / 62, x 192 69 / 66; but 6000 x 7000 x 128 (672) 66 / 59, 6600 x 9000 x 128 (936) 87 / 82, 640 x 20000 x 128
+// (237) 21 / 19.
+// With the number of rows on the device the host cannot count rounds: here (a forward pass of 60 x 50 frames, half of them real, n_in = 620, n = 1000, both directions, 184 / 176).
 bool gemm_nn_pays(const GemmArgs& g) {
   const long tiles = (long)cdiv(g.M, kT) * cdiv(g.N, kT) * g.nz;
   if (gemm_tile_small(g.M, g.N, g.nz) || g.M <= kT / 2 || g.N <= kT / 2) return false;
-  return g.m_dev || !((tiles > 256 && tiles <= 384) || (tiles > 512 && tiles <= 640 && g.K <= 320));
+  if (g.m_dev || tiles <= 256) return true;
+  const long m = cdiv(g.M, kT / 2), n = cdiv(g.N, kT / 2), few = std::min(m, n), filled = 25 * m * n * g.nz / tiles;      // percent of the larger tiles that is not padding
+  if (tiles <= 384) {
+    if (filled <= 75) return false;
+    return g.K > (few < 8 ? (tiles <= 320 || filled <= 85 ? 256 : 0) : few >= 16 && n < 2 * m ? 1024 : 640);
+  }
+  if (n >= 8 * m) return tiles > 512 || filled > 75 || g.K > 128;
+  if (tiles <= 512) return g.K > 128;
+  if (tiles <= 640) return g.K > 320;
+  return tiles < 736 || tiles > 896 || g.K > 128;
 }
 
 bool gemm_tn_ok(const GemmArgs& g) {
