@@ -474,9 +474,12 @@ hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
 // launch ends earlier (work-groups; us, 8 / 4, operands from memory): 1408 x 4000 x 4000 (352) 81 / 76, 1600 x 4000 x 4000 (416) 77 / 72, 1920 x 4000 x 8000
 // (480) 138 / 125, 384 x 20000 x 1024 (471) 28 / 26; but 1280 x 4000 x 8000 (320) 109 / 111, 2400 x 4000 x 2048 (608) 51 / 60.  In the order by rows neighbours share
 // more of what they read, and less on its way is no gain: 6656 x 1000 x 2048 (416) 37 / 41.
+// They run ahead the further the longer K is, and A, which the rows of tiles share, the sooner the fewer rows there are.  On a shorter K less on its way is a loss: 1576 x 4696 (13 rows of
+// tiles) x 512 20.4 / 21.6, x 1536 33.4 / 35.0, x 2048 44.0 / 43.5; 2000 x 3000 (16) x 1024 23.5 / 24.8, x 2048 36.3 / 36.2; 900 x 8000 (8) x 768 21.0 / 21.2, x 1280 34.7 / 30.2;
+// 640 x 11000 (5) x 512 18.8 / 20.0, x 1024 30.1 / 28.0; 384 x 20000 (3) x 256 14.1 / 14.3, x 512 20.6 / 18.6.
 bool paced(const TileArgs& a) {
   const long tiles_m = cdiv(a.M, kTM), tiles_n = cdiv(a.N, kTN), groups = tiles_m * tiles_n * a.nz * a.ksplit;
-  return tiles_m <= tiles_n && groups >= 352 && groups < 512;
+  return tiles_m <= tiles_n && groups >= 352 && groups < 512 && (long)a.K * a.nseg / a.ksplit >= std::min(160 * tiles_m, 2048L);
 }
 template <typename TC>
 hipError_t launch_layout(const TileGroup& a, int count, bool ak, bool bk, hipStream_t s) {

@@ -449,10 +449,10 @@ def test_inference_in_several_launches(T, B, n, bidir):
 
 
 @pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128), (2400, 2440)])
-@pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312, 2048, 2120])
 def test_product_of_few_tiles_stages(M, N, K):
     """128 x 128 tiles, all three layouts: one to five stages (the ring of two is walked by both parities), ragged last ones, more tile rows than columns (several
-    bands, the last one lower; work-groups of the grid that have no tile) and fewer; 380 work-groups, which have less on its way."""
+    bands, the last one lower; work-groups of the grid that have no tile) and fewer; 380 work-groups, which have less on its way from K = 2048 on."""
     import torch
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator().manual_seed(M + K)
