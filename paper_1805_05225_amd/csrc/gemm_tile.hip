@@ -106,8 +106,15 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), each = (tiles + 7) >> 3;
   const bool apart = !AK && !BK && g.nz * g.ksplit > 1;
   const bool by_rows = apart || (tiles_m > tiles_n && (g.ksplit == 1 || ktiles * g.nseg > 5 * g.ksplit));
-  const int idx = by_rows ? (mine & 7) * each + (mine >> 3) : mine;
-  if (idx >= tiles || (by_rows && (mine >> 3) >= each)) return;
+  // B k-major, bands of columns, some units with two work-groups: an eighth of all tiles each as well, where a tile column is not one XCD's.  In whole eights of columns it is, and stays
+  // in that L2; else an XCD's column changes from row to row of the last band, and with loads a stage and a half ahead such products had become slower than before them (us, before those
+  // loads / a round / an eighth): both k-major 640 x 9000 x 3200 67 / 71 / 57, 1576 x 3704 x 6288 125 / 135 / 126, 408 x 9784 x 5000 103 / 109 / 89; A k-contiguous, the last, 101 / 108 / 100.  A round where
+  // it is no slower: whole eights (1280 x 4096 x 6288, both k-major, 89 / 99), fewer work-groups (1920 x 2280 x 2048, 270, 35.8 / 37.6) or more (608 x 11856 x 2584, both k-major, 465, 63 / 67), three
+  // rows of tiles (384 x 18000 x 1024 31.8 / 32.8), a short K (1376 x 4240 x 536 20.6 / 21.3).
+  const bool wanders = !BK && g.nz * g.ksplit == 1 && tiles_m >= 4 && tiles_m <= tiles_n && tiles_n % 8 != 0 && tiles >= 300 && tiles < 440 && ktiles >= 16;
+  const bool eighths = by_rows || wanders;
+  const int idx = eighths ? (mine & 7) * each + (mine >> 3) : mine;
+  if (idx >= tiles || (eighths && (mine >> 3) >= each)) return;
   const int zk = idx / per_z, bid = idx - zk * per_z;
   int tm, tn;
   if (by_rows) {

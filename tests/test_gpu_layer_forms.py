@@ -448,11 +448,12 @@ def test_inference_in_several_launches(T, B, n, bidir):
     assert float((got["c"] != want["c"]).float().mean()) < 0.05
 
 
-@pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128), (2400, 2440)])
-@pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312, 2048, 2120])
+@pytest.mark.parametrize("M,N", [(1100, 136), (1153, 513), (136, 1160), (129, 128), (2400, 2440), (1040, 5560), (1640, 3072)])
+@pytest.mark.parametrize("K", [8, 64, 72, 128, 184, 256, 312, 2120, 4104])
 def test_product_of_few_tiles_stages(M, N, K):
     """128 x 128 tiles, all three layouts: one to five stages (the ring of two is walked by both parities), ragged last ones, more tile rows than columns (several
-    bands, the last one lower; work-groups of the grid that have no tile) and fewer; 380 work-groups, which have less on its way from K = 2048 on."""
+    bands, the last one lower; work-groups of the grid that have no tile) and fewer; 352 to 511 work-groups,
+    which have less on its way from some K on, or another order where tile columns do not come in whole eights."""
     import torch
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator().manual_seed(M + K)
