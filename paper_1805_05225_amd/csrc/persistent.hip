@@ -3336,7 +3336,8 @@ int persist_fwd_rows(int B, int n, int ndir) {
 // W_h as it lies in memory (8 rows a group): where one launch holds the batch.  Not packing saves once, every further launch starts later (inference,
 // us, packed / as it lies; n = 1000, both directions: one launch 74 / 69, three 147 / 145, six 243 / 243; n = 1024: 74 / 71, 143 / 146, 243 / 255; n = 760,
 // one direction: 56 / 54, three launches 114 / 118, six 199 / 211; n = 520, both: 64 / 61, 179 / 184, 233 / 242).  Longer sequences, 34 steps: n = 1024, one direction, four launches
-// 339 / 356, n = 904 327 / 331, n = 664 433 / 430, but n = 760 441 / 424: its steps are 0.1 us shorter in the other's order of chunks, as it is in no other width measured (264 - 1024).
+// 339 / 356, n = 904 327 / 331, n = 664 433 / 430, but n = 760 441 / 424 and, in three, n = 664 328 / 320: with three loads a step the other's order of chunks makes steps
+// 0.1 us shorter there, but not in both directions at n = 760 (241 / 242).
 bool persist_fwd_w_rows(int B, int n, int ndir) { return n % 8 == 0 && (long)cdiv(n, 32) * cdiv(B, 8) * ndir <= capacity(fwd8_rows_w_for(n)); }
 int persist_bwd_rows(int B, int n, int ndir) {
   const long t32 = cdiv(n, 32);
