@@ -572,9 +572,9 @@ bool gemm_nn_ok(const GemmArgs& g) {
 // 18000 x 1000 x 640 53 / 58, but 2000 x 10000 x 1024 73 / 69, 20000 x 1024 x 1024 73 / 71.  Fewer than 8: 700 x 25000 x 256 37 / 40, x 640 57.4 / 56.9, 640 x 30000 x 256 (354 tiles, 83 % full)
 // 32 / 34, x 320 40 / 38, 500 x 45000 x 256 (352, full) 49 / 43; but with a quarter of the larger tiles empty at any K: 300 x 40000 x 640 44 / 51, x 2048 90 / 104.
 // A third at most half full: 4100 x 8000 x 256 (544 tiles) 47 / 49, 10000 x 4000 x 256 (640) 53 / 57, but x 1024 106 / 101, and 2000 x 19000 x 128 60 / 58.
-// One or two stages of K also with a second round full, a third nearly, a fourth half: 8192 x 4096 x 128 (512) 38 / 43, 380 x 60000 x 128 (470, a quarter empty) 29 / 32, 6000 x 8192 x 128
-// (768) 55 / 58, 5683 x 9152 x 128 (828) 58 / 63, 7000 x 8000 x 128 (896) 59 / 62, x 192 69 / 66; but 6000 x 7000 x 128 (672) 66 / 59, 6600 x 9000 x 128 (936) 87 / 82, 640 x 20000 x 128
-// (237) 21 / 19.
+// One or two stages of K are little more than storing C: a third or fourth round, and a second that is full, there only where rows of C are whole runs of 64 bytes (more tiles cut more of
+// them): 8192 x 4096 x 128 (512 tiles) 38 / 43, 380 x 60000 x 128 (470, a quarter empty) 29 / 32, 6400 x 7680 x 128 (750) 52 / 60, 5683 x 9152 x 128 (828) 58 / 63, 14055 x 4176 x 128 (935)
+// 69 / 75; but 5120 x 5632 x 128 (440) 35 / 34, 4000 x 16384 x 128 (1024) 74 / 63, and with rows that are not 6280 x 7560 x 128 (750) 75 / 65, 4097 x 7112 x 40 (476) 47 / 42.
 // With the number of rows on the device the host cannot count rounds: here (a forward pass of 60 x 50 frames, half of them real, n_in = 620, n = 1000, both directions, 184 / 176).
 bool gemm_nn_pays(const GemmArgs& g) {
   const long tiles = (long)cdiv(g.M, kT) * cdiv(g.N, kT) * g.nz;
@@ -585,10 +585,10 @@ bool gemm_nn_pays(const GemmArgs& g) {
     if (filled <= 75) return false;
     return g.K > (few < 8 ? (tiles <= 320 || filled <= 85 ? 256 : 0) : few >= 16 && n < 2 * m ? 1024 : 640);
   }
-  if (n >= 8 * m) return tiles > 512 || filled > 75 || g.K > 128;
-  if (tiles <= 512) return g.K > 128;
-  if (tiles <= 640) return g.K > 320;
-  return tiles < 736 || tiles > 896 || g.K > 128;
+  if (tiles > 512 && tiles <= 640 && n < 8 * m) return g.K > 320;
+  const bool whole = (long)g.ldc * (g.out_bf16 ? 2 : 4) % 64 == 0 && g.K <= 128;
+  if (tiles <= 512) return !(whole && (filled <= 75 || (tiles >= 490 && m >= n)));
+  return !(whole && tiles >= 736 && tiles <= 940 && n < 8 * m);
 }
 
 bool gemm_tn_ok(const GemmArgs& g) {

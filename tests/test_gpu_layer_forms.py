@@ -469,11 +469,12 @@ def test_product_of_few_tiles_stages(M, N, K):
         assert float((got.double() - ref).abs().max()) < 1e-5 * float(ref.abs().max()), form          # (exact inputs: the order of float sums)
 
 
-@pytest.mark.parametrize("M,N", [(4100, 4104), (2049, 8320), (3329, 7944), (2305, 14344), (104, 51464), (51300, 104)])
+@pytest.mark.parametrize("M,N", [(4100, 4104), (2049, 8320), (3329, 7944), (2305, 14344), (104, 51464), (51300, 104), (7681, 4096), (6145, 7632), (6145, 7640)])
 @pytest.mark.parametrize("K", [8, 64, 72, 128, 136, 200, 320])
 def test_product_of_many_tiles_b_k_major(M, N, K):
     """B as it lies in memory: one to five stages, ragged last ones, tiles of 256 x 256 of which a row or eight columns are left; 289 and 297 of them, which tiles of
-    128 x 128 take, 448, and 570, which K chooses for; a row and a column of them that would be half empty, which tiles of 128 x 128 take."""
+    128 x 128 take, 448, and 570, which K chooses for; a row and a column of them that would be half empty, which tiles of 128 x 128 take;
+    496, 750 with rows of whole runs of 64 bytes, and not."""
     import torch
     from paper_1805_05225_amd import binding as Bn
     g = torch.Generator(device="cuda").manual_seed(M + K)
