@@ -7,8 +7,8 @@
 //     trg[r] = W_trg[label[r]] + b_trg
 //
 // No candidate list of beam * V entries is ever sorted: a sentence's best `beam` candidates contain at most `beam` from one
-// row, so every row first picks its own best `beam` labels in one pass over its logits (beam_row_kernel, a work-group of
-// four wavefronts per row), and one wavefront per sentence merges the beam * beam survivors (beam_merge_kernel).  Nothing
+// row, so every row first picks its own best `beam` labels in one pass over its logits (beam_row_kernel, a work-group per row
+// or, of few rows, per stretch of one), and a work-group per sentence merges the survivors (beam_merge_kernel).  Nothing
 // returns to the host.
 #include <algorithm>
 #include <mutex>
@@ -16,12 +16,16 @@
 
 #include "../../include/lstm_abi.h"
 #include "common.h"
+#include "exchange_dev.h"
 
 namespace lstm {
 namespace {
 
 constexpr int kBeamMax = 16;
 constexpr int kVocabMax = 1 << 26;    // beam * V must fit an int32 flat index
+constexpr int kRowPieces = 24;        // 16-byte pieces of a row that a thread holds at most
+constexpr int kRowParts = 8;          // stretches of a row at most
+constexpr long kRowGroups = 768;      // work-groups up to which rows are cut into stretches
 
 // Scratch of lstm_beam_step_static: Q * beam * beam survivors (value and label) at most kStaticCands of each, e.g. 256
 // sentences at beam 16.  512 KiB of every device the library runs on, held until the process ends.
@@ -64,274 +68,270 @@ __device__ __forceinline__ Cand wave_best(Cand c) {
   w.i = __builtin_amdgcn_readlane(c.i, 63);
   return w;
 }
-// A lane's best CAP candidates so far, best first.
-template <int CAP>
-struct TopList {
-  float v[CAP];
-  int i[CAP];
-  __device__ __forceinline__ void clear() {
-#pragma unroll
-    for (int p = 0; p < CAP; ++p) { v[p] = -__builtin_inff(); i[p] = 0x7fffffff; }
-  }
-  // insert c, dropping the last entry; ORDERED: the caller offers candidates in ascending index order, so one that
-  // equals an entry in value comes after it and a value comparison is enough
-  template <bool ORDERED>
-  __device__ __forceinline__ void insert(const Cand& c) {
-    const auto before = [&](int p) { return ORDERED ? c.v > v[p] : better(c, Cand{v[p], i[p]}); };
-#pragma unroll
-    for (int p = CAP - 1; p > 0; --p) {
-      const bool shift = before(p - 1), here = before(p);
-      v[p] = shift ? v[p - 1] : (here ? c.v : v[p]);
-      i[p] = shift ? i[p - 1] : (here ? c.i : i[p]);
-    }
-    const bool first = before(0);
-    v[0] = first ? c.v : v[0];
-    i[0] = first ? c.i : i[0];
-  }
-  __device__ __forceinline__ void pop() {
-#pragma unroll
-    for (int p = 0; p + 1 < CAP; ++p) { v[p] = v[p + 1]; i[p] = i[p + 1]; }
-    v[CAP - 1] = -__builtin_inff();
-    i[CAP - 1] = 0x7fffffff;
-  }
+// The choice of a work-group's best `need` candidates, best first, out of what its 256 threads hold in registers.
+struct Chooser {
+  static constexpr int kSeg = 128;                               // finalists a wavefront may contribute
+  unsigned key[256];
+  float v[4][kSeg], out_v[kBeamMax], win_v[4];
+  int i[4][kSeg], out_i[kBeamMax], win_i[4], count[4];
 };
-
-// The wavefront's best `beam` candidates out of its 64 lists, best first: `beam` rounds in which every lane offers the
-// head of its list and the lane that wins drops it.  emit(k, winner) runs in every lane.
-template <int CAP, typename F>
-__device__ __forceinline__ void wave_select(TopList<CAP>& t, int beam, F emit) {
-  for (int k = 0; k < beam; ++k) {
-    const Cand head = {t.v[0], t.i[0]};
-    const Cand win = wave_best(head);
-    if (win.i == head.i && win.i != 0x7fffffff) t.pop();        // indices are unique, so exactly one lane owns the winner
-    emit(k, win);
-  }
-}
-
-// Row r of the logits, one work-group of four wavefronts, each with a quarter of the row: a single pass with a running
-// logsumexp.  Sorted lists per lane cost a hundred instructions for the whole wavefront whenever ONE lane has to insert, and
-// with 64 lists some lane nearly always has (59 us for 768 rows of 20000).  Instead a wavefront keeps a bound that at least
-// `beam` of the entries it has seen reach - the `beam`-th largest of its 64 lanes' running maxima, found by bisection over
-// the ordered bit patterns with ballots, renewed once per round of loads - and appends whatever reaches the bound to its
-// candidate buffer in LDS (ballot, count, one store per value): an entry strictly below the bound has `beam` entries in
-// front of it and can be dropped.  A typical row leaves a few hundred candidates, from which `beam` rounds of "every lane
-// offers its best, the wavefront picks" take the row's best, equal values by ascending label.  Should a buffer run short of
-// a round's worth of room (rows that keep rising), it is first cut down to its best `beam` the same way.
-// Writes cand_val[r][k] = score[r] + logits[r][label] - logsumexp and cand_lab[r][k].
-constexpr int kRowU = 4;                         // loads of 16 bytes in flight per lane
-constexpr int kRowRound = 64 * kRowU * 4;        // entries per wavefront and round of loads
-constexpr int kRowCap = kRowRound + 512;         // candidate buffer per wavefront (4 x 12 KiB per work-group)
-// LDS traffic between the lanes of ONE wavefront: its LDS instructions execute in program order, so all that is needed is
-// that the compiler keeps them in that order
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__ logits, long ld, const float* __restrict__ score,
-                                                        float* __restrict__ cand_val, int* __restrict__ cand_lab, int V, int beam) {
-  __shared__ float bv[4 * kRowCap];
-  __shared__ int bi[4 * kRowCap];
-  __shared__ int cnt[4];
-  __shared__ float part_m[4], part_z[4], part_b[4];
-  __shared__ float fv[64];                                      // the row's finalists (see the end)
-  __shared__ int fi[64];
-  __shared__ int fcount;
-  if (threadIdx.x == 0) fcount = 0;
-  const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const float* src = logits + (long)r * ld;
+// `top` is the largest value this thread has seen (its own entries or earlier ones that the list so far holds), each(f) calls
+// f(value, index) for every entry and scan(bound, f) for every entry that is not surely below the bound; both are wavefront-wide.  -inf and NaN are no candidates.  Results in s.out_v / out_i[0 .. need), (-inf, 0x7fffffff) where there are
+// fewer; the caller synchronises before the next use of s.
+// An entry strictly below the need-th largest of the 256 `top`s has `need` entries in front of it.  That bound is found by bisection over
+// the ordered bit patterns (20 bits of them, rounded down) with ballots; what reaches it - little more than `need` entries unless values
+// repeat - goes to a list in LDS, a stretch per wavefront, and the place of a finalist is the number of better ones.  Lists that do not
+// fit (plateaus) are left: `need` rounds of "every thread offers its best behind the last winner" over the registers take their place.
+template <typename Each, typename Scan>
+__device__ __forceinline__ void choose_best(Chooser& s, float top, int need, Each each, Scan scan) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float kNegInf = -__builtin_inff();
-  float m = kNegInf, z = 0.f;                                    // running maximum and sum of exp(x - m) of this lane's entries
-  const auto fold = [&](float gm, float gz) {                    // merge (gm, gz) into (m, z)
-    const float mn = fmaxf(m, gm);
-    if (mn > kNegInf) z = z * __expf(m - mn) + gz * __expf(gm - mn);
-    m = mn;
-  };
-  const int need = min(beam, 64);
-  float bound = kNegInf;
-  const auto renew_bound = [&]() {                               // the need-th largest of the lanes' maxima m, rounded down
-    const unsigned f = __float_as_uint(m);
-    const unsigned key = ((f & 0x80000000u) ? ~f : (f | 0x80000000u)) >> 12;     // larger float => key not smaller; 20 bits
-    unsigned lo = 0u, hi = 0xfffffu;
-    while (lo < hi) {
-      const unsigned mid = lo + ((hi - lo) >> 1) + 1u;
-      if (__popcll(__ballot(key >= mid)) >= need) lo = mid; else hi = mid - 1u;
-    }
-    // lo = the need-th largest key: at least `need` maxima are at or above the smallest float with that key.  Keys at or
-    // below that of -inf mean fewer than `need` lanes hold anything yet.
-    const unsigned full = lo << 12;                               // the smallest ordered pattern with this key
-    bound = lo <= (0x007fffffu >> 12) ? kNegInf : __uint_as_float((full & 0x80000000u) ? (full & 0x7fffffffu) : ~full);
-  };
-  float* wbv = bv + wave * kRowCap;
-  int* wbi = bi + wave * kRowCap;
-  int count = 0;                                                 // candidates in this wavefront's buffer (the same in every lane)
-  const auto append = [&](bool keep, float x, int label) {       // wavefront-wide: every lane calls it
+  const unsigned f = __float_as_uint(top);
+  s.key[threadIdx.x] = ((f & 0x80000000u) ? ~f : (f | 0x80000000u)) >> 12;     // larger float => key not smaller
+  __syncthreads();
+  const unsigned k0 = s.key[lane], k1 = s.key[64 + lane], k2 = s.key[128 + lane], k3 = s.key[192 + lane];
+  unsigned lo = 0u, hi = 0xfffffu;
+  while (lo < hi) {
+    const unsigned mid = lo + ((hi - lo) >> 1) + 1u;
+    const int n = __popcll(__ballot(k0 >= mid)) + __popcll(__ballot(k1 >= mid)) + __popcll(__ballot(k2 >= mid)) + __popcll(__ballot(k3 >= mid));
+    if (n >= need) lo = mid; else hi = mid - 1u;
+  }
+  // Keys at or below that of -inf: fewer than `need` threads hold anything.
+  const unsigned full = lo << 12;                                 // the smallest ordered pattern with this key
+  const float bound = lo <= (0x007fffffu >> 12) ? kNegInf : __uint_as_float((full & 0x80000000u) ? (full & 0x7fffffffu) : ~full);
+  int count = 0;                                                 // of this wavefront (the same in every lane)
+  scan(bound, [&](float x, int idx) {
+    const bool keep = x > kNegInf && x >= bound;
     const unsigned long long mask = __ballot(keep);
     if (mask == 0ull) return;
-    if (keep) {
-      const int pos = count + (int)__popcll(mask & ((1ull << lane) - 1ull));
-      wbv[pos] = x;
-      wbi[pos] = label;
-    }
+    const int pos = count + (int)__popcll(mask & ((1ull << lane) - 1ull));
+    if (keep && pos < Chooser::kSeg) { s.v[wave][pos] = x; s.i[wave][pos] = idx; }
     count += (int)__popcll(mask);
-  };
-  // One round of picking over this wavefront's buffer (ALL = false, `count` entries) or all four (counts in cnt[]): the
-  // best candidate, which leaves its buffer.  Runs in one wavefront.  (Counts in a private array indexed by the loop
-  // would live in scratch memory: a trip to memory per buffer and round.)
-  const auto pick_best = [&](auto all) {
-    constexpr bool ALL = decltype(all)::value;
+  });
+  if (lane == 0) s.count[wave] = count;
+  if (threadIdx.x < kBeamMax) { s.out_v[threadIdx.x] = kNegInf; s.out_i[threadIdx.x] = 0x7fffffff; }
+  __syncthreads();
+  const int c0 = s.count[0], c1 = s.count[1], c2 = s.count[2], c3 = s.count[3];
+  if (max(max(c0, c1), max(c2, c3)) <= Chooser::kSeg && c0 + c1 + c2 + c3 <= 256) {
+    // thread t has finalist t of the four stretches
+    const int t1 = c0, t2 = c0 + c1, t3 = t2 + c2, total = t3 + c3, t = threadIdx.x;
+    if (wave * 64 >= total) return;
+    const int w = (t >= t1) + (t >= t2) + (t >= t3), at = t - (w == 0 ? 0 : w == 1 ? t1 : w == 2 ? t2 : t3);
     Cand mine = {kNegInf, 0x7fffffff};
-    int at = -1;
+    if (t < total) { mine.v = s.v[w][at]; mine.i = s.i[w][at]; }
+    int place = 0;
+    if (total <= 64) {
+      for (int j = 0; j < total; ++j) {
+        const Cand other = {__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine.v), j)), __builtin_amdgcn_readlane(mine.i, j)};
+        place += better(other, mine) ? 1 : 0;
+      }
+    } else {
 #pragma unroll
-    for (int w = 0; w < (ALL ? 4 : 1); ++w) {
-      const int buf = ALL ? w : wave, n = ALL ? cnt[w] : count;
-      for (int p = lane; p < n; p += 64) {
-        const int q = buf * kRowCap + p;
-        const Cand cd = {bv[q], bi[q]};
-        if (cd.i != 0x7fffffff && better(cd, mine)) { mine = cd; at = q; }
+      for (int seg = 0; seg < 4; ++seg) {
+        const int n = seg == 0 ? c0 : seg == 1 ? c1 : seg == 2 ? c2 : c3;
+        for (int j = 0; j < n; ++j) {
+          const Cand other = {s.v[seg][j], s.i[seg][j]};
+          place += better(other, mine) ? 1 : 0;
+        }
       }
     }
+    if (t < total && place < need) { s.out_v[place] = mine.v; s.out_i[place] = mine.i; }
+    return;
+  }
+  Cand last = {__builtin_inff(), -1};                             // in front of every candidate
+  for (int k = 0; k < need; ++k) {
+    Cand mine = {kNegInf, 0x7fffffff};
+    each([&](float x, int idx) {                                 // (-inf is sorted out below: a test of x alone would be kept for all rounds, in registers)
+      const Cand c = {x, idx};
+      if (better(last, c) && better(c, mine)) { mine.v = x; mine.i = idx; }
+    });
     const Cand win = wave_best(mine);
-    if (at >= 0 && win.i == mine.i) bi[at] = 0x7fffffff;         // labels are unique, so exactly one lane owns the winner
-    wave_lds_sync();
-    return win;
-  };
-  const auto make_room = [&]() {                                 // before a round: room for all its entries
-    if (count <= kRowCap - kRowRound) return;
-    wave_lds_sync();
-    Cand kept = {kNegInf, 0x7fffffff};
-    for (int k = 0; k < need; ++k) {
-      const Cand win = pick_best(std::false_type{});
-      if (lane == k) kept = win;
-    }
-    count = 0;
-    append(kept.i != 0x7fffffff, kept.v, kept.i);
-    wave_lds_sync();
-  };
-  const bool vec = (ld & 3) == 0 && ((uintptr_t)logits & 15) == 0;
-  const int n4 = vec ? V >> 2 : 0;
-  const int q4 = (n4 + 3) >> 2, end4 = min(n4, (wave + 1) * q4);  // this wavefront's 16-byte pieces: [wave * q4, end4)
-  for (int base = wave * q4; base < end4; base += 64 * kRowU) {
-    float4 x4[kRowU];
-    float g[kRowU];
+    if (lane == 0) { s.win_v[wave] = win.v; s.win_i[wave] = win.i; }
+    __syncthreads();
+    Cand best = {s.win_v[0], s.win_i[0]};
 #pragma unroll
-    for (int u = 0; u < kRowU; ++u) x4[u] = ((const float4*)src)[min(base + lane + u * 64, end4 - 1)];
-#pragma unroll
-    for (int u = 0; u < kRowU; ++u) {
-      const float gm = fmaxf(fmaxf(x4[u].x, x4[u].y), fmaxf(x4[u].z, x4[u].w));
-      g[u] = base + lane + u * 64 < end4 ? gm : kNegInf;
-      if (g[u] > kNegInf) fold(gm, __expf(x4[u].x - gm) + __expf(x4[u].y - gm) + __expf(x4[u].z - gm) + __expf(x4[u].w - gm));
-    }
-    renew_bound();                                               // counts this round's entries as well
-    make_room();
-#pragma unroll
-    for (int u = 0; u < kRowU; ++u) {
-      const bool any = g[u] > kNegInf && g[u] >= bound;
-      if (__ballot(any) == 0ull) continue;
-      const int i4 = base + lane + u * 64;
-      const float x[4] = {x4[u].x, x4[u].y, x4[u].z, x4[u].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) append(any && x[e] > kNegInf && x[e] >= bound, x[e], 4 * i4 + e);
-    }
+    for (int w = 1; w < 4; ++w) best = pick(best, Cand{s.win_v[w], s.win_i[w]});
+    if (threadIdx.x == 0 && best.v > kNegInf) { s.out_v[k] = best.v; s.out_i[k] = best.i; }
+    last = best;
+    __syncthreads();
   }
-  for (int base = 4 * n4 + wave * 64 * kRowU; base < V; base += 4 * 64 * kRowU) {   // what 16-byte loads do not cover
-    float x[kRowU];
-#pragma unroll
-    for (int u = 0; u < kRowU; ++u) {
-      const int i = base + lane + u * 64;
-      x[u] = i < V ? src[i] : kNegInf;
-      if (x[u] > kNegInf) fold(x[u], 1.f);
-    }
-    renew_bound();
-    make_room();
-#pragma unroll
-    for (int u = 0; u < kRowU; ++u) append(x[u] > kNegInf && x[u] >= bound, x[u], base + lane + u * 64);
+}
+
+// Row r of the logits in `parts` stretches, a work-group of four wavefronts each (parts > 1: few rows, which would leave compute units
+// idle).  A stretch is read once, up to U loads of 16 bytes a thread in flight, and stays in registers: the logsumexp is
+// folded four pieces at a time as they arrive, one bound for the whole work-group tells the few entries that can be among the best
+// apart, and these are ranked (choose_best).  A stretch of more than 256 U pieces (of 16 bytes) takes several rounds, each with the best so far among its candidates.
+// Rows start and end anywhere: 16-byte pieces between the first and the last 16-byte boundary, the up to three entries on
+// either side one by one.
+// What bounds it: the reading of the logits, and for few rows a round trip to memory, the bisection and the ranking behind each other.
+// 768 rows x 20000: 21.8 -> 16.5 us (3.7 TB/s); 600 x 20787 (rows that are not whole 16 bytes) 73.6 -> 16.3; 104 x 22051 54.3 -> 9.7;
+// 8 x 14274 35.8 -> 6.2; 279 x 1853 9.6 -> 7.0.
+// (The form before kept a buffer of candidates in LDS and renewed its bound in every round of 4 loads, each a
+// round trip to memory and a bisection one after the other; rows that are not whole 16 bytes were read 4 bytes at a time.)
+// clean: a NaN counts as no entry (rows that are not whole 16 bytes); otherwise it makes the row's scores NaN, which never win.
+// One stretch: cand_val[r][k] = score[r] + logits[r][label] - logsumexp and cand_lab[r][k].  Several: the logit itself in
+// cand_val[r][part][k], and the stretch's (maximum, sum of exponentials, score) in part_sums[r][part].
+template <int U>
+__global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__ logits, long ld, const float* __restrict__ score, bool clean,
+                                                       float* __restrict__ cand_val, int* __restrict__ cand_lab, float4* __restrict__ part_sums,
+                                                       int V, int beam, int parts, int per, int step) {
+  __shared__ Chooser s;
+  __shared__ float part_m[4], part_z[4];
+  const int r = (int)blockIdx.x / parts, part = (int)blockIdx.x - r * parts, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float* row = logits + (long)r * ld;
+  const int head = min(V, (int)((4u - ((unsigned)((uintptr_t)row >> 2) & 3u)) & 3u)), n4 = (V - head) >> 2, tail = V - head - 4 * n4;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(row + head), 0, n4 * 16, kBufFlags);
+  const int begin = part * per, end = min(n4, begin + per);
+  const float kNegInf = -__builtin_inff();
+  float m = kNegInf, z = 0.f;                                    // running maximum and sum of exp(x - m) of this thread's entries
+  // an entry outside the pieces: first the row's own, later one of the best so far
+  float ex = kNegInf;
+  int ei = 0x7fffffff;
+  if (part == 0 && tid < head + tail) {
+    ei = tid < head ? tid : head + 4 * n4 + tid - head;
+    ex = row[ei];
+    if (ex > kNegInf) { m = ex; z = __expf(ex - ex); }
   }
-  // logsumexp of this wavefront's part, then of the whole row
+  int base = begin;
+  for (;;) {
+    const int stop = min(end, base + step);
+    u32x4 x4[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x4[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)(base + u * 256 + tid) * 16u, 0, 0);
+    float x[U][4];
+#pragma unroll
+    for (int u0 = 0; u0 < U; u0 += 4) {
+      float pm[4], mn = m;
+#pragma unroll
+      for (int u = u0; u < u0 + 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[u][e] = __uint_as_float(x4[u][e]);
+      if (base + (u0 + 4) * 256 > stop) {
+        const int left = stop - base - tid;
+#pragma unroll
+        for (int u = u0; u < u0 + 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[u][e] = u * 256 < left ? x[u][e] : kNegInf;
+      }
+      if (clean) {
+#pragma unroll
+        for (int u = u0; u < u0 + 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[u][e] = x[u][e] > kNegInf ? x[u][e] : kNegInf;
+      }
+#pragma unroll
+      for (int u = u0; u < u0 + 4; ++u) {
+        pm[u - u0] = fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3]));
+        mn = fmaxf(mn, pm[u - u0]);
+      }
+      if (mn > kNegInf) {
+        z *= __expf(m - mn);
+#pragma unroll
+        for (int u = u0; u < u0 + 4; ++u) {
+          const float pz = (__expf(x[u][0] - mn) + __expf(x[u][1] - mn)) + (__expf(x[u][2] - mn) + __expf(x[u][3] - mn));
+          z += pm[u - u0] > kNegInf ? pz : 0.f;
+        }
+      }
+      m = mn;
+    }
+    const int first = head + 4 * (base + tid);
+    const auto each = [&](auto f) {
+      int i = first;
+      asm volatile("" : "+v"(i));                                // (or 4 U labels are kept in registers for the rounds behind a full list)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f(x[u][e], i + 1024 * u + e);
+      f(ex, ei);
+    };
+    const auto scan = [&](float bound, auto f) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (__ballot(fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3])) >= bound) == 0ull) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f(x[u][e], first + 1024 * u + e);
+      }
+      f(ex, ei);
+    };
+    choose_best(s, m, beam, each, scan);
+    base += step;
+    if (base >= end) break;
+    __syncthreads();
+    ex = tid < beam ? s.out_v[tid] : kNegInf;
+    ei = tid < beam ? s.out_i[tid] : 0x7fffffff;
+    __syncthreads();
+  }
+  // logsumexp of the wavefronts' parts, then of all
   float mw = m;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
   float zw = mw > kNegInf ? z * __expf(m - mw) : 0.f;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) zw += __shfl_xor(zw, o);
-  if (lane == 0) { part_m[wave] = mw; part_z[wave] = zw; cnt[wave] = count; part_b[wave] = bound; }
+  if (lane == 0) { part_m[wave] = mw; part_z[wave] = zw; }
   __syncthreads();
-  // Finalists: every one of the row's best `beam` reaches the largest of the four wavefronts' bounds (at least `beam`
-  // entries of that wavefront's quarter do).  Each wavefront copies its candidates at or above it to a common list of 64;
-  // if they fit - they nearly always do: a few dozen - the first wavefront ranks them in registers (a candidate's place
-  // is the number of better ones: no rounds, nothing through LDS), else it picks from the four buffers round by round.
-  const float top_bound = fmaxf(fmaxf(part_b[0], part_b[1]), fmaxf(part_b[2], part_b[3]));
-  for (int p0 = 0; p0 < count; p0 += 64) {
-    const int p = p0 + lane;
-    const bool keep = p < count && wbv[p] >= top_bound;
-    const unsigned long long mask = __ballot(keep);
-    if (mask == 0ull) continue;
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&fcount, (int)__popcll(mask));
-    base = __builtin_amdgcn_readfirstlane(base);
-    const int pos = base + (int)__popcll(mask & ((1ull << lane) - 1ull));
-    if (keep && pos < 64) { fv[pos] = wbv[p]; fi[pos] = wbi[p]; }
-  }
-  __syncthreads();
-  if (wave != 0) return;
+  if (tid >= 64) return;
   const float mr = fmaxf(fmaxf(part_m[0], part_m[1]), fmaxf(part_m[2], part_m[3]));
   float zr = 0.f;
 #pragma unroll
   for (int w = 0; w < 4; ++w) zr += part_m[w] > kNegInf ? part_z[w] * __expf(part_m[w] - mr) : 0.f;
-  const float lse = mr + __logf(zr);
   const float sc = score[r];
-  const int total = fcount;
-  if (total <= 64) {
-    const Cand mine = {lane < total ? fv[lane] : kNegInf, lane < total ? fi[lane] : 0x7fffffff};
-    int place = 0;
-    for (int j = 0; j < total; ++j) {
-      const Cand other = {__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine.v), j)), __builtin_amdgcn_readlane(mine.i, j)};
-      place += better(other, mine) ? 1 : 0;
-    }
-    if (lane < total && place < beam) {
-      cand_val[(long)r * beam + place] = sc + (mine.v - lse);
-      cand_lab[(long)r * beam + place] = mine.i;
-    }
-    if (lane >= total && lane < beam) {                          // fewer than `beam` usable labels in the row: the rest never wins
-      cand_val[(long)r * beam + lane] = kNegInf;
-      cand_lab[(long)r * beam + lane] = 0;
-    }
-    return;
-  }
-  // lane k keeps the k-th best and stores it at the end
-  Cand kept = {kNegInf, 0x7fffffff};
-  for (int k = 0; k < beam; ++k) {
-    const Cand win = pick_best(std::true_type{});
-    if (lane == k) kept = win;
-  }
-  if (lane < beam) {
-    const bool found = kept.i != 0x7fffffff;
-    cand_val[(long)r * beam + lane] = found ? sc + (kept.v - lse) : kNegInf;
-    cand_lab[(long)r * beam + lane] = found ? kept.i : 0;
+  if (parts > 1 && tid == 0) part_sums[blockIdx.x] = make_float4(mr, zr, sc, 0.f);
+  if (tid < beam) {
+    const bool found = s.out_i[tid] != 0x7fffffff;               // fewer than `beam` usable labels: the rest never wins
+    const float v = s.out_v[tid];
+    cand_val[(long)blockIdx.x * beam + tid] = !found ? kNegInf : parts > 1 ? v : sc + (v - (mr + __logf(zr)));
+    cand_lab[(long)blockIdx.x * beam + tid] = found ? s.out_i[tid] : 0;
   }
 }
 
-// The beam * beam survivors of sentence q = blockIdx.x, one wavefront: the best `beam`, by value and then by flat index
-// b * V + label.
-__global__ __launch_bounds__(64) void beam_merge_kernel(const float* __restrict__ cand_val, const int* __restrict__ cand_lab,
-                                                         float* __restrict__ score_out, int* __restrict__ src_out,
-                                                         int* __restrict__ label_out, int V, int beam) {
-  const int q = blockIdx.x, lane = threadIdx.x;
-  TopList<4> t;                                                 // beam * beam / 64 <= 4 candidates per lane
-  t.clear();
-  for (int c = lane; c < beam * beam; c += 64) {
-    const float val = cand_val[(long)q * beam * beam + c];
-    const int flat = (c / beam) * V + cand_lab[(long)q * beam * beam + c];
-    // a row with fewer than `beam` labels pads with (-inf, label 0): give the padding indices that cannot collide
-    t.insert<false>(Cand{val, val == -__builtin_inff() ? 0x7ffffffe - c : flat});
+// The beam * parts * beam survivors of sentence q = blockIdx.x: the best `beam`, by value and then by flat index b * V + label.
+// 256 N >= that many.
+template <int N>
+__global__ __launch_bounds__(256) void beam_merge_kernel(const float* __restrict__ cand_val, const int* __restrict__ cand_lab,
+                                                         const float4* __restrict__ part_sums, float* __restrict__ score_out,
+                                                         int* __restrict__ src_out, int* __restrict__ label_out, int V, int beam, int parts) {
+  __shared__ Chooser s;
+  __shared__ float row_sc[kBeamMax], row_lse[kBeamMax];
+  const int q = blockIdx.x, tid = threadIdx.x, per_row = parts * beam, total = beam * per_row;
+  const float kNegInf = -__builtin_inff();
+  float v[N];
+  int flat[N], b[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int c = tid + 256 * k;
+    b[k] = c / per_row;
+    v[k] = c < total ? cand_val[(long)q * total + c] : kNegInf;
+    flat[k] = c < total ? b[k] * V + cand_lab[(long)q * total + c] : 0x7fffffff;
   }
-  Cand kept = {-__builtin_inff(), 0x7fffffff};
-  wave_select(t, beam, [&](int k, const Cand& win) { if (lane == k) kept = win; });
-  if (lane < beam) {
-    const bool real = kept.i < beam * V;
-    score_out[q * beam + lane] = kept.v;
-    src_out[q * beam + lane] = real ? kept.i / V : 0;
-    label_out[q * beam + lane] = real ? kept.i % V : 0;
+  if (parts > 1) {
+    if (tid < beam) {
+      const float4* ps = part_sums + ((long)q * beam + tid) * parts;
+      float mr = kNegInf, zr = 0.f;
+      for (int p = 0; p < parts; ++p) mr = fmaxf(mr, ps[p].x);
+      for (int p = 0; p < parts; ++p) zr += ps[p].x > kNegInf ? ps[p].y * __expf(ps[p].x - mr) : 0.f;
+      row_sc[tid] = ps[0].z;
+      row_lse[tid] = mr + __logf(zr);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (v[k] > kNegInf) v[k] = row_sc[b[k]] + (v[k] - row_lse[b[k]]);
+  }
+  float top = kNegInf;
+#pragma unroll
+  for (int k = 0; k < N; ++k) top = fmaxf(top, v[k]);
+  const auto each = [&](auto f) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) f(v[k], flat[k]);
+  };
+  choose_best(s, top, beam, each, [&](float, auto f) { each(f); });
+  __syncthreads();
+  if (tid < beam) {
+    const bool real = s.out_i[tid] != 0x7fffffff;                // else a place nothing finite was left for: hypothesis 0, label 0
+    score_out[q * beam + tid] = s.out_v[tid];
+    src_out[q * beam + tid] = real ? s.out_i[tid] / V : 0;
+    label_out[q * beam + tid] = real ? s.out_i[tid] % V : 0;
   }
 }
 
@@ -391,19 +391,49 @@ static int beam_dims(int Q, int beam, int V) {
   return LSTM_OK;
 }
 
+// Stretches a row is cut into: as many as the device holds at once (three work-groups a compute unit), of at least 2048 entries.
+static int beam_parts(int Q, int beam, int V) {
+  const long rows = (long)Q * beam;
+  return rows < 1 ? 1 : (int)std::max(1L, std::min({(long)kRowParts, kRowGroups / rows, (long)V / 2048}));
+}
+static uint64_t beam_bytes(int Q, int beam, int parts) {
+  const auto whole = [](uint64_t b) { return (b + 255) / 256 * 256; };
+  const uint64_t rows = (uint64_t)Q * beam;
+  return 256 + 2 * whole(rows * parts * beam * 4) + (parts > 1 ? whole(rows * parts * sizeof(float4)) : 0);
+}
+
 int lstm_beam_query(int Q, int beam, int V, uint64_t* workspace_bytes) {
   if (!workspace_bytes) return LSTM_ERR_NULL;
   const int rc = beam_dims(Q, beam, V);
   if (rc) return rc;
-  *workspace_bytes = 256 + 2 * (((uint64_t)Q * beam * beam * 4 + 255) / 256 * 256);
+  *workspace_bytes = beam_bytes(Q, beam, beam_parts(Q, beam, V));
   return LSTM_OK;
 }
 
-// both kernels of a step; cand_val / cand_lab hold Q * beam * beam entries each
+// both kernels of a step; cand_val / cand_lab hold Q * beam * parts * beam entries each, part_sums Q * beam * parts
 static int beam_launch(int Q, int beam, int V, const float* logits, int64_t ld, const float* score_in, float* score_out, int32_t* src,
-                       int32_t* label, float* cand_val, int* cand_lab, hipStream_t st) {
-  hipLaunchKernelGGL(beam_row_kernel, dim3(Q * beam), dim3(256), 0, st, logits, (long)ld, score_in, cand_val, cand_lab, V, beam);
-  hipLaunchKernelGGL(beam_merge_kernel, dim3(Q), dim3(64), 0, st, cand_val, cand_lab, score_out, src, label, V, beam);
+                       int32_t* label, int parts, float* cand_val, int* cand_lab, float4* part_sums, hipStream_t st) {
+  const bool clean = (ld & 3) != 0 || ((uintptr_t)logits & 15) != 0;
+  const int per = cdiv(cdiv(V, 4), parts), step = cdiv(per, cdiv(per, 256 * kRowPieces));       // pieces of a stretch, of a round
+  const auto row = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(Q * beam * parts)), dim3(256), 0, st, logits, (long)ld, score_in, clean, cand_val, cand_lab, part_sums, V,
+                       beam, parts, per, step);
+  };
+  const int u = cdiv(step, 256);
+  if (u <= 4) row(beam_row_kernel<4>);
+  else if (u <= 8) row(beam_row_kernel<8>);
+  else if (u <= 12) row(beam_row_kernel<12>);
+  else if (u <= 16) row(beam_row_kernel<16>);
+  else if (u <= 20) row(beam_row_kernel<20>);
+  else row(beam_row_kernel<kRowPieces>);
+  const auto merge = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(Q), dim3(256), 0, st, cand_val, cand_lab, part_sums, score_out, src, label, V, beam, parts);
+  };
+  const int c = cdiv((long)beam * parts * beam, 256);
+  if (c <= 1) merge(beam_merge_kernel<1>);
+  else if (c <= 2) merge(beam_merge_kernel<2>);
+  else if (c <= 4) merge(beam_merge_kernel<4>);
+  else merge(beam_merge_kernel<kRowParts * kBeamMax * kBeamMax / 256>);
   if (hipGetLastError() != hipSuccess) return LSTM_ERR_HIP;
   return LSTM_OK;
 }
@@ -423,15 +453,15 @@ int lstm_beam_step(int Q, int beam, int V, const float* logits, int64_t ld, cons
   if (!workspace) return LSTM_ERR_NULL;
   int rc = beam_step_args(Q, beam, V, logits, ld, score_in, score_out, src, label);
   if (rc) return rc;
-  uint64_t need = 0;
-  lstm_beam_query(Q, beam, V, &need);
-  if (workspace_bytes < need) return LSTM_ERR_SIZE;
+  if (workspace_bytes < beam_bytes(Q, beam, 1)) return LSTM_ERR_SIZE;
+  int parts = beam_parts(Q, beam, V);
+  if (workspace_bytes < beam_bytes(Q, beam, parts)) parts = 1;
   if (Q == 0) return LSTM_OK;
   if ((rc = device_ok())) return rc;
   char* ws = (char*)(((uintptr_t)workspace + 255) / 256 * 256);
-  float* cand_val = (float*)ws;
-  int* cand_lab = (int*)(ws + ((size_t)Q * beam * beam * 4 + 255) / 256 * 256);
-  return beam_launch(Q, beam, V, logits, ld, score_in, score_out, src, label, cand_val, cand_lab, (hipStream_t)stream);
+  const size_t half = ((size_t)Q * beam * parts * beam * 4 + 255) / 256 * 256;
+  return beam_launch(Q, beam, V, logits, ld, score_in, score_out, src, label, parts, (float*)ws, (int*)(ws + half), (float4*)(ws + 2 * half),
+                     (hipStream_t)stream);
 }
 
 // The same step for callers that cannot allocate: the survivors of the rows (the only scratch of the step) go to a
@@ -457,8 +487,9 @@ int lstm_beam_step_static(int Q, int beam, int V, const float* logits, int64_t l
     base = (char*)g_static_ptr[dev];
   }
   // every entry the merge reads is written by the row kernel of the same call: nothing has to be cleared
-  return beam_launch(Q, beam, V, logits, ld, score_in, score_out, src, label, (float*)base, (int*)(base + kStaticCands * 4),
-                     (hipStream_t)stream);
+  static_assert(kRowGroups * (kBeamMax * 4 + sizeof(float4)) <= kStaticCands * 4, "rows in stretches: their sums behind their labels");
+  return beam_launch(Q, beam, V, logits, ld, score_in, score_out, src, label, beam_parts(Q, beam, V), (float*)base, (int*)(base + kStaticCands * 4),
+                     (float4*)(base + 2 * kStaticCands * 4 - kRowGroups * sizeof(float4)), (hipStream_t)stream);
 }
 
 int lstm_beam_gather_many(int Q, int beam, int count, const lstm_gather_item* items, const int32_t* src, void* stream) {

@@ -146,6 +146,40 @@ def test_beam_step_strided_logits():
     _validate(np.ascontiguousarray(wide[:, :V]), score, beam, got)
 
 
+# V entries in rows `ld` apart, the first `shift` floats behind a 16-byte boundary: rows of less than one 16-byte piece, rows that begin and
+# end between pieces, rows cut into stretches (up to eight, of at least 2048 entries), stretches of more than one round of 24 * 256 pieces
+@pytest.mark.parametrize("Q,beam,V,ld,shift", [(1, 1, 1, 1, 0), (2, 3, 2, 5, 1), (1, 16, 7, 7, 3), (3, 4, 2047, 2047, 0), (3, 4, 4096, 4099, 2),
+                                               (2, 16, 14274, 14274, 0), (1, 4, 22051, 22051, 1), (13, 8, 22051, 22051, 0), (24, 16, 4999, 5001, 3),
+                                               (48, 16, 1025, 1025, 0), (49, 16, 24579, 24579, 0), (49, 16, 24576, 24576, 0), (48, 16, 32771, 32771, 2), (1, 2, 250007, 250007, 1)])
+def test_beam_step_stretches_rounds_and_alignment(Q, beam, V, ld, shift):
+    rng = np.random.default_rng(Q * 1000 + V)
+    rows = Q * beam
+    print("  beam step Q=%d beam=%d V=%d ld=%d shift=%d" % (Q, beam, V, ld, shift), flush=True)
+    logits = (rng.standard_normal((rows, V)) * 3).astype(np.float32)
+    if V > 64:
+        logits[0, :] = np.arange(V, dtype=np.float32) // 7 * np.float32(2.0 ** -9)           # rising in plateaus of seven
+        logits[-1, :] = -2.0                                                               # one plateau: the rounds behind a full list
+        logits[-1, [0, V // 2, V - 1]] = 1.0
+    score = (-rng.uniform(0, 8, (Q, beam))).astype(np.float32)
+    buf = torch.full((rows * ld + shift,), float("nan"), dtype=torch.float32, device="cuda")
+    x = buf[shift:].as_strided((rows, V), (ld, 1))
+    x.copy_(torch.from_numpy(logits))
+    r = Bn.beam_step(x, torch.from_numpy(score).cuda())
+    torch.cuda.synchronize()
+    got = (r["score"].cpu().numpy(), r["src"].cpu().numpy().astype(np.int64), r["label"].cpu().numpy().astype(np.int64))
+    _validate(logits, score, beam, got)
+    # the same with the smallest workspace there ever was a need of (rows whole)
+    small = 256 + 2 * (-(-rows * beam * 4 // 256) * 256)
+    ws = torch.empty(small, dtype=torch.uint8, device="cuda")
+    out, src, lab = (torch.empty(Q, beam, dtype=t, device="cuda") for t in (torch.float32, torch.int32, torch.int32))
+    sc = torch.from_numpy(score).cuda()
+    rc = Bn.lib.lstm_beam_step(Q, beam, V, x.data_ptr(), ld, sc.data_ptr(), out.data_ptr(), src.data_ptr(), lab.data_ptr(), ws.data_ptr(), small,
+                               torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    torch.cuda.synchronize()
+    _validate(logits, score, beam, (out.cpu().numpy(), src.cpu().numpy().astype(np.int64), lab.cpu().numpy().astype(np.int64)))
+
+
 def test_gather_and_embed_are_exact():
     rng = np.random.default_rng(10)
     Q, beam = 6, 12
