@@ -121,7 +121,10 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s);
 // max(0, .) and the rounding to bfloat16 happen in its epilogue (launch_gemm routes such problems to it by itself).
 constexpr int kSkinnyMaxRows = 1024;
 bool gemm_skinny_ok(const GemmArgs& g);
-hipError_t launch_gemm_skinny(const GemmArgs& g, bool relu, hipStream_t s);
+hipError_t launch_gemm_skinny(const GemmArgs& g, hipStream_t s);
+bool gemm_skinny_pays(long M, long N, int nz);
+// out[B][R] = bf16(max(0, A[B][lda] W^T + bias)): W in the fragment order of launch_pack_rows_both, A's rows at least ceil(K / 32) * 32 columns, zeros past K
+hipError_t launch_skinny_readout(const void* A, long lda, const void* Wfrag, const float* bias, void* out, long ldo, int B, int R, int K, hipStream_t s);
 // Numbers the frames (t, b) with t < lens[b] in (t, b) order: fidx[number] -> frame, count[0] = how many, count[1] = that rounded up
 // to a multiple of 64.
 hipError_t launch_frame_map(const int* lens, int T, int B, int* fidx, int* count, hipStream_t s);
@@ -447,7 +450,7 @@ inline size_t wcell_rows(int n) { return (size_t)128 * ((n + 31) / 32); }
 hipError_t launch_pack_wcell(const void* W_x, const void* W_h, void* Wcell, int n_in, int n_in_pad, int n, int Kc, int ndir, hipStream_t s);
 hipError_t launch_step_cell(const void* Acat, const void* Wcell, const float* bias, const float* h_in, const float* c_in, float* h_out,
                             float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n, int Kc, int ndir, hipStream_t s);
-// The same step for a handful of rows (gemm_few.hip, B <= kFewCellRows): weights packed in MFMA fragment order (at most wcell_rows(n) x Kc
+// The same step for a handful of rows (gemm_few.hip, few_cell_pays): weights packed in MFMA fragment order (at most wcell_rows(n) x Kc
 // elements per direction), K = n_in_pad + n; A is scratch for the concatenated rows in the same order.
 hipError_t launch_pack_cell_frag(const void* W_x, const void* W_h, void* out, int n_in, int n_in_pad, int n, int K, int ndir, hipStream_t s);
 hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void* Wfrag, const float* bias, const float* c_in, float* h_out,

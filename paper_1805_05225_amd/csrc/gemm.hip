@@ -328,7 +328,7 @@ hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nz <= 0) return hipSuccess;
-  if (gemm_skinny_ok(g)) return launch_gemm_skinny(g, false, s);
+  if (gemm_skinny_ok(g)) return launch_gemm_skinny(g, s);
   if (gemm_nn_ok(g) && (gemm_nn_pays(g) || !gemm_tile_ok(g))) return launch_gemm_nt(g, s);
   if (gemm_tile_ok(g) && (gemm_tile_small(g.M, g.N, g.nz) || (g.a_kcontig && !g.b_kcontig))) return launch_gemm_tile(g, s);
   if (gemm_nt_ok(g)) return launch_gemm_nt(g, s);

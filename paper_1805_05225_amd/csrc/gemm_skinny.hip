@@ -17,10 +17,9 @@
 // from L2 to LDS (about 47 bytes per clock and compute unit, measured for the large kernels): 28 KiB per stage
 // against 384 clocks of MFMA work, i.e. about 600 clocks per stage.
 //
-// A second tile shape, 64 rows x 64 columns (every wavefront one k-step of a 64 x 32 block), serves products whose
-// 96 x 128 tiles would occupy less than half the device (the decoder's query projection and readout, 768 x 1000: 64 tiles
-// against 192): what bounds the kernel is the rate at which ONE compute unit pulls operands from L2, so more, smaller
-// tiles finish sooner although they move more bytes in total.
+// Other tile shapes (64 x 64: every wavefront one k-step of a 64 x 32 block) serve products that 96 x 128 tiles would leave compute units
+// without (the decoder's query projection and readout, 768 x 1000: 64 tiles against 192) or take a second round for: what bounds the kernel is the
+// rate at which ONE compute unit pulls operands from L2, so more, smaller tiles finish sooner although they move more bytes in total (launch_tiles).
 #include "recurrent_dev.h"
 #include "gemm_skinny.h"
 
@@ -41,7 +40,7 @@ struct Geo {
   static constexpr int kDummy = kDepth * kStage;      // 4 KiB that the surplus loads of a stage write zeros to (see the kernel)
   static constexpr int kEpStride = kTN + 4;           // floats per staged row
   static constexpr int kLds = kDummy + 4096;          // <3,2>: 118784 bytes; the epilogue's staging reuses the stages
-  static_assert(2 * kTM * kEpStride * 4 <= kDummy, "the epilogue's staging must fit into the stage buffers");
+  static_assert(2 * kTM * kEpStride * 4 <= kLds, "the epilogue's staging (no load is in flight then)");
 };
 constexpr unsigned kParked = 0x7ffffff0u;
 
@@ -61,49 +60,49 @@ __device__ __forceinline__ f32x16 mma32(uint4 a, uint4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Work-group -> tile.  Work-groups are dealt to the eight XCDs round-robin (blockIdx & 7 is the XCD).  The tiles an XCD
-// runs at a time should share operand panels out of its L2: with tiles_m <= 32 row tiles, an XCD takes all row tiles of
-// 32 / bm column tiles at a time (bm = tiles_m rounded up to a power of two); otherwise tiles are dealt row-major.
 // s_waitcnt operand for vmcnt(n) lgkmcnt(0): vmcnt's low four bits sit in bits 3:0, its upper two in bits 15:14
 constexpr int vm_wait(unsigned n) { return (int)(0x0070u | (n & 15u) | ((n >> 4) << 14)); }
+
+// Work-group -> tile.  Work-groups are dealt to the eight XCDs round-robin (blockIdx & 7 is the XCD).  An XCD's tiles are a rectangle of
+// pr x pc of them, xr rectangles over the rows, 8 / xr over the columns: what its L2 has to fetch are pr row and pc column panels, so
+// xr is where these are fewest bytes, after the number of rounds (of 32 work-groups an XCD) that the largest rectangle takes.
+// What comes from beyond L2 arrives at a quarter of the rate of what is in it (11 against 47 bytes a clock and compute unit), and the two
+// add up: 768 x 1000 x 3620 in 64 x 64 tiles, 12 x 2 of them an XCD (every row of A in every L2, 7.2 MB) 21.5 us, 6 x 4 (5 MB) 20.2.
 struct Tile { int tm, tn, pos; bool live; };
-__host__ __device__ inline int pow2_at_least(int v) { int p = 1; while (p < v) p <<= 1; return p; }
-__device__ __forceinline__ Tile tile_of(int tiles_m, int tiles_n) {
-  Tile t = {0, 0, 0, false};
-  const int bid = blockIdx.x;
-  if (tiles_m <= 32) {
-    const int bm = pow2_at_least(tiles_m), bn = 32 / bm;
-    const int xcd = bid & 7, slot = bid >> 3, group = (slot / 32) * 8 + xcd, pos = slot % 32;
-    t.tm = pos % bm; t.tn = group * bn + pos / bm; t.pos = pos;
-    t.live = t.tm < tiles_m && t.tn < tiles_n;
-  } else {
-    t.tm = bid % tiles_m; t.tn = bid / tiles_m; t.pos = bid & 31;
-    t.live = t.tn < tiles_n;
-  }
+__device__ __forceinline__ Tile tile_of(const SkinnyArgs& g, int tiles_m, int tiles_n) {
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, across = slot / g.pr, down = slot - across * g.pr;
+  Tile t;
+  t.tm = (xcd & (g.xr - 1)) * g.pr + down; t.tn = xcd / g.xr * g.pc + across; t.pos = slot & 31;
+  t.live = t.tm < tiles_m && t.tn < tiles_n;
   return t;
 }
-inline int grid_for(int tiles_m, int tiles_n) {
-  if (tiles_m <= 32) {
-    const int bm = pow2_at_least(tiles_m), bn = 32 / bm;
-    const int groups = cdiv(tiles_n, bn);
-    return cdiv(groups, 8) * 8 * 32;
+// xr, pr, pc for tiles of tm x tn; the rounds
+int split_tiles(SkinnyArgs& a, int tm, int tn) {
+  const int tiles_m = cdiv(a.M, tm), tiles_n = cdiv(a.N, tn);
+  long best = 0;
+  int rounds = 0;
+  for (int xr = 1; xr <= 8; xr *= 2) {
+    const int pr = cdiv(tiles_m, xr), pc = cdiv(tiles_n, 8 / xr), r = cdiv((long)pr * pc, 32);
+    const long cost = ((long)r << 32) + (long)pr * tm + (long)pc * tn;
+    if (xr == 1 || cost < best) { best = cost; rounds = r; a.xr = xr; a.pr = pr; a.pc = pc; }
   }
-  return tiles_m * tiles_n;
+  return rounds;
 }
 
-template <int BI, int BJ, bool CELL>
+// BFRAG: B in fragment order, [row tile of 16][g.b_nkc chunks of 32 k][64 lanes] of 16 bytes (launch_pack_rows_both), a wavefront-load is a chunk of a tile.
+template <int BI, int BJ, bool CELL, bool BFRAG>
 __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
   typedef Geo<BI, BJ> G;
   constexpr int kTM = G::kTM, kTN = G::kTN, kAop = G::kAop, kStage = G::kStage, kLoads = G::kLoads, kDummy = G::kDummy,
                 kEpStride = G::kEpStride, kPerWave = G::kPerWave;
-  static_assert(!CELL || (BI == 3 && BJ == 2), "the cell epilogue expects the four gates of 32 units in a tile's 128 columns");
+  constexpr int kUnits = 16 * BJ;                   // cell: the tile's columns are the four gates of so many units
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kq = wave >> 1, wc = wave & 1;          // k-step of a stage (0..3) and column half (32 BJ columns) of this wavefront
   const int r = lane & 31, gq = lane >> 5;
   const int tiles_m = (g.M + kTM - 1) / kTM, tiles_n = (g.N + kTN - 1) / kTN;
-  const Tile tl = tile_of(tiles_m, tiles_n);
+  const Tile tl = tile_of(g, tiles_m, tiles_n);
   if (!tl.live) return;
   const int m0 = tl.tm * kTM, n0 = tl.tn * kTN, z = blockIdx.z;
   const int K = g.K, nstage = (K + 63) / 64;
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
   unsigned voff[kPerWave], dst[kPerWave];
   int chunk[kPerWave];
   bool is_b[kPerWave];
-  const long a_bytes = (long)g.M * g.lda * 2, b_bytes = (long)g.N * g.ldb * 2;
+  const long a_bytes = (long)g.M * g.lda * 2, b_bytes = BFRAG ? (long)((g.N + 15) / 16) * g.b_nkc * 1024 : (long)g.N * g.ldb * 2;
 #pragma unroll
   for (int i = 0; i < kPerWave; ++i) {
     const int q = wave + 8 * i;
@@ -139,9 +138,17 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
     const int rg = is_b[i] ? q - kTM / 8 : q;
     const int rl = rg * 8 + (lane >> 3);
     chunk[i] = real ? (lane & 7) ^ ((rl >> 1) & 7) : 0x10000;            // surplus load: "past K" in every stage
-    const long row = (is_b[i] ? n0 : m0) + rl;
-    const bool inside = real && (is_b[i] ? row < g.N : row < g.M);
-    const long off = row * (is_b[i] ? g.ldb : g.lda) * 2 + (chunk[i] & 7) * 16;
+    // (packed rows of the cell come in blocks of 32 units: 128 t + 32 gate + unit)
+    const int b_row = CELL ? 128 * (tl.tn * kUnits >> 5) + 32 * (rl / kUnits) + (tl.tn * kUnits & 31) + rl % kUnits : n0 + rl;
+    const long row = is_b[i] ? b_row : m0 + rl;
+    bool inside = real && (is_b[i] ? row < g.N : row < g.M);
+    long off = row * (is_b[i] ? g.ldb : g.lda) * 2 + (chunk[i] & 7) * 16;
+    if (BFRAG && real && is_b[i]) {                                      // (rows that fill up the last tile are zeros)
+      const int tile = (n0 >> 4) + (rg >> 1);
+      inside = tile * 16 < g.N;
+      chunk[i] = 4 * (rg & 1);
+      off = ((long)tile * g.b_nkc + (rg & 1)) * 1024 + lane * 16;
+    }
     voff[i] = (inside && off <= 0x7fffff00L) ? (unsigned)off : kParked;
     dst[i] = real ? (unsigned)((is_b[i] ? kAop : 0) + rg * 1024) : 0u;
   }
@@ -153,14 +160,16 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
     const int kt = it + rot < nstage ? it + rot : it + rot - nstage;       // which 64 k this stage holds
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
-      const bool past = kt * 64 + chunk[i] * 8 >= K;           // ragged last k-tile (and every surplus load)
+      const bool past = kt * 64 + chunk[i] * 8 >= K;           // ragged last k-tile (and every surplus load; K: up to whole chunks of 32 with BFRAG)
       const unsigned where = wave + 8 * i >= kLoads ? lds_base + kDummy + (unsigned)(wave & 3) * 1024u : buf + dst[i];
-      load_to_lds_b128(is_b[i] ? rb : ra, where, past ? kParked : voff[i], (unsigned)kt * 128u);
+      load_to_lds_b128(is_b[i] ? rb : ra, where, past ? kParked : voff[i], (unsigned)kt * (BFRAG && is_b[i] ? 2048u : 128u));
     }
   };
   // Fragment reads: row (i*32 + r) of A / (wc*32*BJ + j*32 + r) of B, k-chunk 2 kq + gq, in slot (2 kq + gq) ^ ((row >> 1) & 7)
   const int slot = ((2 * kq + gq) ^ ((r >> 1) & 7)) * 16;
-  const int fa_off = r * kRow + slot, fb_off = kAop + (wc * 32 * BJ + r) * kRow + slot;
+  const int fa_off = r * kRow + slot;
+  // (BFRAG: 2 KiB per tile of 16 columns; lanes of a chunk lie side by side)
+  const int fb_off = kAop + (BFRAG ? wc * 2 * BJ * 2048 + (r >> 4) * 2048 + ((2 * kq + gq) * 16 + (r & 15)) * 16 : (wc * 32 * BJ + r) * kRow + slot);
 
   // Pipeline: while the MFMAs of stage it run (fragments in registers), the fragments of stage it+1 are read from LDS
   // and the loads of stages it+2 .. it+4 are in flight (a load from beyond L2 takes longer than two stages of MFMAs:
@@ -194,8 +203,6 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
     else if (q <= BI) read_a(it, set, q - 1);
     else if (q < BI + BJ) read_b(it, set, q - BI);
   };
-#pragma unroll
-  for (int q = 0; q < BI + BJ; ++q) read_nr(0, 0, q);
   // The MFMAs of a stage in the order (row block, column block) = (0,0) (1,0) .. (0,1) (1,1) ..; with `next`, one
   // fragment read of the following stage goes out behind each MFMA (96 x 128 tile: behind the first five of six),
   // what is left of them behind the last.  (All reads in front of the MFMAs held the MFMAs back until the LDS had
@@ -226,17 +233,24 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
     mfmas(set, true, it + 1);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // (the last stage is in register set 1 whatever their number: two ends for two parities cost a second set of accumulators)
   int it = 0;
-  for (; it + 2 < nstage; it += 2) {
-    step(it, 0);
-    step(it + 1, 1);
-  }
-  if (it + 2 == nstage) {
-    step(it, 0);
-    mfmas(1, false, 0);
+  if (nstage & 1) {
+#pragma unroll
+    for (int q = 0; q < BI + BJ; ++q) read_nr(0, 1, q);
+    if (nstage > 1) step(it++, 1);
   } else {
-    mfmas(0, false, 0);
+#pragma unroll
+    for (int q = 0; q < BI + BJ; ++q) read_nr(0, 0, q);
   }
+  if (nstage > 1) {
+    for (; it + 2 < nstage; it += 2) {
+      step(it, 0);
+      step(it + 1, 1);
+    }
+    step(it, 0);
+  }
+  mfmas(1, false, 0);
   __syncthreads();                                 // the stage buffers are free for the epilogue
 
   // Epilogue.  The four k-steps' shares meet in LDS (the stage buffers are free): k-steps 2 and 3 store theirs side by side, 0 and 1
@@ -250,7 +264,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
 #pragma unroll
       for (int i = 0; i < BI; ++i)
 #pragma unroll
-        for (int j = 0; j < BJ; ++j)
+        for (int j = 0; j < BJ; ++j, __builtin_amdgcn_sched_barrier(0))      // (one block's reads at a time)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             float* e = &ep[(kq & 1) * kEpHalf + (i * 32 + 8 * (v >> 2) + 4 * gq + (v & 3)) * kEpStride + wc * 32 * BJ + j * 32 + r];
@@ -301,15 +315,15 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
       }
     }
   } else {
-    // thread -> (unit of the tile, row): 32 threads per row, 16 rows per pass; staged columns 32 q + unit
-    const int uu = tid & 31, j = tl.tn * 32 + uu, n = g.n;
+    // thread -> (unit of the tile, row): a thread per unit and row, 512 / kUnits rows per pass; staged columns kUnits q + unit
+    const int uu = tid % kUnits, j = tl.tn * kUnits + uu, n = g.n;
     if (j < n) {
       float bv[4] = {0.f, 0.f, 0.f, 0.f};
       if (g.bias) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) bv[q] = g.bias[(long)z * 4 * n + q * n + j];
       }
-      for (int rr = tid >> 5; rr < kTM; rr += 16) {
+      for (int rr = tid / kUnits; rr < kTM; rr += 512 / kUnits) {
         const int b = m0 + rr;
         if (b >= g.M) break;
         const long si = ((long)z * g.M + b) * n + j;
@@ -318,7 +332,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
         if (valid) {
           float zh[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) zh[q] = ep[rr * kEpStride + q * 32 + uu] + ep[kEpHalf + rr * kEpStride + q * 32 + uu] + bv[q];
+          for (int q = 0; q < 4; ++q) zh[q] = ep[rr * kEpStride + q * kUnits + uu] + ep[kEpHalf + rr * kEpStride + q * kUnits + uu] + bv[q];
           const float zx[4] = {0.f, 0.f, 0.f, 0.f};
           const CellOut o = lstm_cell(zh, zx, c);
           c = o.c; h = o.h;
@@ -332,25 +346,49 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
   }
 }
 
-template <int BI, int BJ, bool CELL>
+template <int BI, int BJ, bool CELL, bool BFRAG>
 hipError_t launch_as(const SkinnyArgs& a, hipStream_t s) {
   typedef Geo<BI, BJ> G;
   static std::atomic<unsigned long long> attr_set{0};
   const hipError_t ea = once_per_device(attr_set, [] {
-    return hipFuncSetAttribute((const void*)skinny_kernel<BI, BJ, CELL>, hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds);
+    return hipFuncSetAttribute((const void*)skinny_kernel<BI, BJ, CELL, BFRAG>, hipFuncAttributeMaxDynamicSharedMemorySize, G::kLds);
   });
   if (ea != hipSuccess) return ea;
-  const dim3 grid(grid_for(cdiv(a.M, G::kTM), cdiv(a.N, G::kTN)), 1, a.nz);
-  hipLaunchKernelGGL((skinny_kernel<BI, BJ, CELL>), grid, dim3(512), G::kLds, s, a);
+  const dim3 grid(8 * a.pr * a.pc, 1, a.nz);
+  hipLaunchKernelGGL((skinny_kernel<BI, BJ, CELL, BFRAG>), grid, dim3(512), G::kLds, s, a);
   return hipGetLastError();
+}
+template <bool CELL, bool BFRAG>
+hipError_t launch_tiles(SkinnyArgs a, hipStream_t s) {
+  // The tile whose work-groups are done first: rounds times what one reads, which is all of K of its rows and columns; what begins and ends
+  // a work-group counts as 1e5 / K rows more.  Of 46 products and cells measured with every tile the choice is the fastest one or within 6 %, in three
+  // within 12 % (64 x 32000 x 512 12.2 us, 10.9 in 64 x 64).  us, 96 x 128 (or 64 x 64) before and the choice: cells of n = 688, 915 rows, K = 1680 44.9 -> 26.0; n = 1000, 1024 rows,
+  // K = 3620 71.9 -> 49.0; n = 504, 504 rows, K = 2424 31.2 -> 19.8; products 1000 x 4000 x 2000 43.8 -> 30.2, 104 x 22051 x 960 29.8 -> 19.5, 504 x 920 x 2424 14.3 -> 12.5.
+  static constexpr int kTiles[][2] = {{3, 2}, {2, 1}, {2, 2}, {3, 1}, {4, 2}, {1, 1}};
+  int best = 0;
+  double least = 0.;
+  for (int i = 0; i < 6; ++i) {
+    const int tm = 32 * kTiles[i][0], tn = 64 * kTiles[i][1];
+    SkinnyArgs b = a;
+    const double cost = split_tiles(b, tm, tn) * ((a.M < tm ? a.M : tm) + tn + 1e5 / a.K);
+    if (i == 0 || cost < least) { least = cost; best = i; }
+  }
+  split_tiles(a, 32 * kTiles[best][0], 64 * kTiles[best][1]);
+  switch (best) {
+    case 0: return launch_as<3, 2, CELL, BFRAG>(a, s);
+    case 1: return launch_as<2, 1, CELL, BFRAG>(a, s);
+    case 2: return launch_as<2, 2, CELL, BFRAG>(a, s);
+    case 3: return launch_as<3, 1, CELL, BFRAG>(a, s);
+    case 4: return launch_as<4, 2, CELL, BFRAG>(a, s);
+    default: return launch_as<1, 1, CELL, BFRAG>(a, s);
+  }
 }
 hipError_t launch(const SkinnyArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.nz <= 0) return hipSuccess;
-  if (a.cell) return launch_as<3, 2, true>(a, s);
-  if (a.M <= kFewRows) return launch_few(a, s);
-  // fewer 96 x 128 tiles than half the device has compute units: 64 x 64 tiles
-  if ((long)cdiv(a.M, 96) * cdiv(a.N, 128) * a.nz < 128) return launch_as<2, 1, false>(a, s);
-  return launch_as<3, 2, false>(a, s);
+  if (a.cell) return launch_tiles<true, false>(a, s);
+  if (a.b_nkc) return launch_tiles<false, true>(a, s);
+  if (few_rows_pay(a.M, a.N, a.K)) return launch_few(a, s);
+  return launch_tiles<false, false>(a, s);
 }
 
 // Wcell[d][128 t + 32 q + u][k] = [W_x^T | 0 | W_h^T | 0] row (q n + 32 t + u), zero for units past n; a 64 x 64 tile of
@@ -389,21 +427,29 @@ __global__ __launch_bounds__(256) void pack_wcell_kernel(const uint16_t* Wx, con
 
 }  // namespace
 
+// only where the 256 x 256 tiles of the throughput kernel would leave most of the device idle (it is the faster one
+// from about half a device's worth of tiles: 768 x 20000 x 1000 takes 49 us there and 72 us here)
+bool gemm_skinny_pays(long M, long N, int nz) { return M <= kSkinnyMaxRows && (long)cdiv(M, 256) * cdiv(N, 256) * nz < 128; }
 bool gemm_skinny_ok(const GemmArgs& g) {
   const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
-  // only where the 256 x 256 tiles of the throughput kernel would leave most of the device idle (it is the faster one
-  // from about half a device's worth of tiles: 768 x 20000 x 1000 takes 49 us there and 72 us here)
-  if ((long)cdiv(g.M, 256) * cdiv(g.N, 256) * g.nz >= 128) return false;
-  return g.in_bf16 && g.a_kcontig && g.b_kcontig && !g.lens && g.M <= kSkinnyMaxRows && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
+  return gemm_skinny_pays(g.M, g.N, g.nz) && g.in_bf16 && g.a_kcontig && g.b_kcontig && !g.lens && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
          !g.k_dev && !g.accumulate && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 &&
          a16(g.A) && a16(g.B) && (long)g.N * g.ldb * 2 <= 0x7fffff00L;
 }
-hipError_t launch_gemm_skinny(const GemmArgs& g, bool relu, hipStream_t s) {
+hipError_t launch_gemm_skinny(const GemmArgs& g, hipStream_t s) {
   SkinnyArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
   a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
-  a.out_bf16 = g.out_bf16; a.relu = relu;
+  a.out_bf16 = g.out_bf16;
+  return launch(a, s);
+}
+hipError_t launch_skinny_readout(const void* A, long lda, const void* Wfrag, const float* bias, void* out, long ldo, int B, int R, int K, hipStream_t s) {
+  SkinnyArgs a = {};
+  a.A = (const char*)A; a.B = (const char*)Wfrag; a.C = out; a.bias = bias;
+  a.b_nkc = cdiv(K, 32);
+  a.M = B; a.N = R; a.K = 32 * a.b_nkc; a.lda = lda; a.ldc = ldo; a.nz = 1;
+  a.out_bf16 = 1; a.relu = 1;
   return launch(a, s);
 }
 hipError_t launch_pack_wcell(const void* W_x, const void* W_h, void* Wcell, int n_in, int n_in_pad, int n, int Kc, int ndir, hipStream_t s) {

@@ -18,7 +18,10 @@ def _bf(rng, *shape, w=1.0):
 
 
 @pytest.mark.parametrize("B,n_in,n", [(1, 37, 50), (16, 300, 104), (17, 300, 104), (32, 1100, 36), (33, 40, 1000), (64, 2620, 130),
-                                      (65, 77, 34), (192, 1200, 66), (193, 1200, 66), (12, 4100, 24), (1025, 300, 104), (1300, 77, 34)])
+                                      (65, 77, 34), (192, 1200, 66), (193, 1200, 66), (12, 4100, 24), (1025, 300, 104), (1300, 77, 34),
+                                      # every tile of gemm_skinny.hip, rows and units that end inside one: 96 x 128 (twice), 128 x 128, 64 x 128, 96 x 64, 64 x 64
+                                      (767, 40, 1000), (765, 64, 1021), (1001, 40, 1000), (500, 40, 700), (333, 100, 901), (640, 300, 512), (257, 64, 330), (1024, 8, 250),
+                                      (64, 40, 1000), (66, 40, 1000), (129, 40, 481), (130, 40, 480), (200, 32, 504)])   # either side of few_cell_pays; 32 x 64
 def test_stepped_cell(B, n_in, n):
     from paper_1805_05225_amd import binding as Bn
     rng = np.random.default_rng(B + n_in)
@@ -37,7 +40,7 @@ def test_stepped_cell(B, n_in, n):
         check("cT", s["cT"], co, TOL)
 
 
-@pytest.mark.parametrize("n,nt,E,R", [(104, 62, 130, 20), (1000, 620, 2000, 1000), (5, 3, 8, 33)])
+@pytest.mark.parametrize("n,nt,E,R", [(104, 62, 130, 20), (1000, 620, 2000, 1000), (5, 3, 8, 33), (104, 62, 130, 4001), (104, 62, 106, 31), (24, 16, 24, 2050)])
 def test_readout_packed_once_for_any_row_count(n, nt, E, R):
     """FLAG_WEIGHTS_PACKED speaks of the weights and the workspace, not of the number of rows."""
     from paper_1805_05225_amd import binding as Bn
@@ -52,7 +55,11 @@ def test_readout_packed_once_for_any_row_count(n, nt, E, R):
         check("readout B=%d" % B, out, D.readout(f64(s), f64(t), f64(a), f64(W).T, br), 5e-3)
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 20001, 1000), (16, 4097, 72), (17, 33, 2048), (32, 1000, 1000), (33, 1000, 1000)])
+@pytest.mark.parametrize("M,N,K", [(1, 20001, 1000), (16, 4097, 72), (17, 33, 2048), (32, 1000, 1000), (33, 1000, 1000),
+                                   # gemm_skinny.hip: 64 x 128, 128 x 128 (one row of tiles, several), 64 x 64, 96 x 128, more work-groups than the device holds at once
+                                   (200, 8000, 4000), (104, 22051, 96), (1000, 3001, 200), (193, 33, 608), (350, 6000, 1000), (130, 16500, 264), (1024, 7169, 8),
+                                   # 32 x 64; either side of few_rows_pay
+                                   (64, 1000, 1000), (130, 2001, 72), (17, 8193, 896), (17, 8200, 904), (32, 8192, 40), (32, 24577, 904)])
 def test_product(M, N, K):
     from paper_1805_05225_amd import binding as Bn
     rng = np.random.default_rng(M + N)
