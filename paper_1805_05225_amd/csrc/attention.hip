@@ -337,8 +337,6 @@ hipError_t linear_rows(const void* A, long lda, const void* W, long ldw, const f
   GemmArgs g = {};
   g.A = A; g.B = W; g.C = C; g.bias = bias; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldw; g.ldc = N;
   g.nz = 1; g.nseg = 1; g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = true; g.out_bf16 = false;
-  const auto vec = [](const void* p, long ld) { int v = 16; while (v > 2 && (((uintptr_t)p % v) || ((ld * 2) % v))) v >>= 1; return v; };
-  g.vecA = vec(A, lda); g.vecB = vec(W, ldw);
   if (gemm_skinny_ok(g)) return launch_gemm_skinny(g, s);       // few rows: one work-group per tile walks the whole K
   g.parts = parts; g.parts_bytes = parts_bytes;
   return launch_gemm(g, s);

@@ -71,7 +71,6 @@ struct GemmArgs {
   long sAz, sBz, sCz, sbiasz;
   int nz;
   int nseg; long sAseg, sBseg;
-  int vecA, vecB;            // widest aligned access (bytes) usable on A / B: 16, 8, 4 or 2
   int accumulate;            // C += result (float C only)
   const int* lens; int Bt; int T;
   bool a_kcontig, b_kcontig;

@@ -15,6 +15,7 @@
 // stored with m / n contiguous are transposed in registers on their way into LDS.  Global loads
 // for tile i+1 are issued before the MFMAs of tile i (register staging, two LDS buffers).
 #include "common.h"
+#include <type_traits>
 
 namespace lstm {
 namespace {
@@ -44,44 +45,49 @@ template <> struct Mma<float> {
 
 // ---- k-contiguous operand: rows of the tile are rows of memory -------------------------------
 // 128 rows x 8 chunks of 16 bytes; thread handles chunks tid + 256*i, i = 0..3
+// Rows lie anywhere: 16 bytes are read from any address that an element may have.  No load is predicated (behind a branch each would be waited for by itself; with
+// element by element where rows are not whole 16 bytes, a stage of 279 x 1853 x 515 took 7 us): rows past the last read another, and what lies past K or
+// the rows is cleared when the stage goes into LDS (settle: any look at what was loaded waits for it).  The chunk that K ends in is read so that it ends with K, and
+// shifted down then (K is at least a chunk: short_kernel).
 template <typename T>
 __device__ __forceinline__ void fetch_kcontig(uint32_t (&st)[16], const char* base, long ld, int rows, int row0,
-                                              int K, int k0, int vec, int tid, const int (&prow)[4]) {
+                                              int K, int k0, int tid, const int (&prow)[4]) {
   constexpr int ES = sizeof(T), EPC = 16 / ES;
+  struct __attribute__((packed, aligned(ES))) Chunk { uint32_t w[4]; };
+  const int kc = k0 / EPC + (tid & 7);                                   // (k0 is a multiple of EPC)
+  const long k = min((long)kc * EPC, (long)K - EPC);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    int c = tid + kThreads * i;
-    int row = row0 + (c >> 3), k = k0 + (c & 7) * EPC;
-    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-    if (row < rows && k < K) {
-      const char* p = base + ((long)prow[i] * ld + k) * ES;                       // prow[i]: where logical row `row` lies in memory
-      if (vec >= 16 && k + EPC <= K) {
-        uint4 v = *(const uint4*)p;
-        w0 = v.x; w1 = v.y; w2 = v.z; w3 = v.w;
-      } else if (vec >= 8 && k + EPC <= K) {
-        uint2 v0 = *(const uint2*)p, v1 = *(const uint2*)(p + 8);
-        w0 = v0.x; w1 = v0.y; w2 = v1.x; w3 = v1.y;
-      } else {
-        uint32_t w[4] = {0, 0, 0, 0};
+    const Chunk c = *(const Chunk*)(base + ((long)prow[i] * ld + k) * ES);   // prow[i]: where the row lies in memory (past the last: the tile's first)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (ES == 4) {
-            if (k + j < K) w[j] = *(const uint32_t*)(p + 4 * j);
-          } else {
-            int ke = k + 2 * j;
-            if (vec >= 4 && ke + 2 <= K) w[j] = *(const uint32_t*)(p + 4 * j);
-            else {
-              uint32_t lo = ke < K ? *(const uint16_t*)(p + 4 * j) : 0u;
-              uint32_t hi = ke + 1 < K ? *(const uint16_t*)(p + 4 * j + 2) : 0u;
-              w[j] = lo | (hi << 16);
-            }
-          }
-        }
-        w0 = w[0]; w1 = w[1]; w2 = w[2]; w3 = w[3];
-      }
-    }
-    st[4 * i] = w0; st[4 * i + 1] = w1; st[4 * i + 2] = w2; st[4 * i + 3] = w3;
+    for (int j = 0; j < 4; ++j) st[4 * i + j] = c.w[j];
   }
+}
+template <typename T>
+__device__ __forceinline__ void settle_kcontig(uint32_t (&st)[16], int rows, int row0, int K, int k0, int tid) {
+  constexpr int ES = sizeof(T), EPC = 16 / ES;
+  const int whole = K / EPC, kc = k0 / EPC + (tid & 7);
+  if (k0 + 8 * EPC > K) {                                     // the stage that K ends in
+    const int gone = EPC - (K - whole * EPC);                             // elements of the cut chunk that are not its own, in front: 1 .. EPC (EPC: there is none)
+    const int d = gone * ES / 4, half = ES == 2 ? gone & 1 : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t w[4] = {st[4 * i], st[4 * i + 1], st[4 * i + 2], st[4 * i + 3]};
+      if (d & 1) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+      if (d & 2) { w[0] = w[2]; w[1] = w[3]; w[2] = 0u; w[3] = 0u; }
+      if (half) {
+        w[0] = (w[0] >> 16) | (w[1] << 16); w[1] = (w[1] >> 16) | (w[2] << 16);
+        w[2] = (w[2] >> 16) | (w[3] << 16); w[3] >>= 16;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) st[4 * i + j] = kc < whole ? st[4 * i + j] : kc == whole && gone < EPC ? w[j] : 0u;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (row0 + ((tid + kThreads * i) >> 3) >= rows)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) st[4 * i + j] = 0u;
 }
 __device__ __forceinline__ void commit_kcontig(const uint32_t (&st)[16], char* lds, int tid) {
 #pragma unroll
@@ -93,10 +99,12 @@ __device__ __forceinline__ void commit_kcontig(const uint32_t (&st)[16], char* l
 
 // ---- m-contiguous operand: rows of memory are k, the tile is transposed in registers ----------
 // frame mask: row k of the K axis is frame (t = k / Bt, b = k % Bt), valid iff t < lens[b]
-// bf16: micro-tile of 8 k x 2 m (eight 4-byte loads), two micro-tiles per thread
+// bf16: micro-tile of 8 k x 2 m (eight 4-byte loads at any address), two micro-tiles per thread; nothing predicated, as above: k past K reads the last
+// row, columns past the last the last two, and both are cleared afterwards
 template <bool MASK>
 __device__ __forceinline__ void fetch_mcontig_bf16(uint32_t (&st)[16], const char* base, long ld, int cols, int col0,
-                                                   int K, int k0, int vec, int tid, const int* lens, int Bt, int T, const int* krows) {
+                                                   int K, int k0, int tid, const int* lens, int Bt, int T, const int* krows, uint32_t (&kept)[4]) {
+  struct __attribute__((packed, aligned(2))) Pair { uint32_t w; };
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     int c = tid + kThreads * i;
@@ -113,19 +121,31 @@ __device__ __forceinline__ void fetch_mcontig_bf16(uint32_t (&st)[16], const cha
         if (++fb == Bt) { fb = 0; ++ft; }
       }
     }
+    if (cols == 1) {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const int k = min(kb + kk, K - 1);
+        st[8 * i + kk] = *(const uint16_t*)(base + (long)(krows ? krows[k] : k) * ld * 2);
+      }
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const int k = min(kb + kk, K - 1);                  // the same in every lane: a scalar look-up
+        st[8 * i + kk] = ((const Pair*)(base + ((long)(krows ? krows[k] : k) * ld + min(m, cols - 2)) * 2))->w;
+      }
+    }
+    kept[i] = keep;
+  }
+}
+__device__ __forceinline__ void settle_mcontig_bf16(uint32_t (&st)[16], int cols, int col0, int K, int k0, int tid, const uint32_t (&kept)[4]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = tid + kThreads * i, m = col0 + 2 * (c & 63), kb = __builtin_amdgcn_readfirstlane(k0 + (c >> 6) * 8);
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      int k = kb + kk;
-      uint32_t w = 0;
-      if (k < K && m < cols) {
-        const char* p = base + ((long)(krows ? krows[k] : k) * ld + m) * 2;   // k is the same in every lane: a scalar look-up
-        if (vec >= 4 && m + 1 < cols) w = *(const uint32_t*)p;
-        else {
-          w = *(const uint16_t*)p;
-          if (m + 1 < cols) w |= ((uint32_t) * (const uint16_t*)(p + 2)) << 16;
-        }
-      }
-      st[8 * i + kk] = ((keep >> kk) & 1u) ? w : 0u;
+      uint32_t w = st[8 * i + kk];
+      if (m + 1 == cols && cols > 1) w >>= 16;              // the last column alone
+      st[8 * i + kk] = m < cols && kb + kk < K && ((kept[i] >> kk) & 1u) ? w : 0u;
     }
   }
 }
@@ -148,7 +168,7 @@ __device__ __forceinline__ void commit_mcontig_bf16(const uint32_t (&st)[16], ch
 // float: micro-tile of 4 k x 1 m, four per thread
 template <bool MASK>
 __device__ __forceinline__ void fetch_mcontig_f32(uint32_t (&st)[16], const char* base, long ld, int cols, int col0,
-                                                  int K, int k0, int tid, const int* lens, int Bt, int T, const int* krows) {
+                                                  int K, int k0, int tid, const int* lens, int Bt, int T, const int* krows, uint32_t (&kept)[4]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     int c = tid + kThreads * i;
@@ -165,10 +185,19 @@ __device__ __forceinline__ void fetch_mcontig_f32(uint32_t (&st)[16], const char
     }
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      int k = kb + kk;
-      uint32_t w = (k < K && m < cols) ? *(const uint32_t*)(base + ((long)(krows ? krows[k] : k) * ld + m) * 4) : 0u;   // scalar look-up
-      st[4 * i + kk] = ((keep >> kk) & 1u) ? w : 0u;
+      const int k = min(kb + kk, K - 1);                                     // (a scalar look-up)
+      st[4 * i + kk] = *(const uint32_t*)(base + ((long)(krows ? krows[k] : k) * ld + min(m, cols - 1)) * 4);
     }
+    kept[i] = keep;
+  }
+}
+__device__ __forceinline__ void settle_mcontig_f32(uint32_t (&st)[16], int cols, int col0, int K, int k0, int tid, const uint32_t (&kept)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int c = tid + kThreads * i, m = col0 + (c & 127), kb = __builtin_amdgcn_readfirstlane(k0 + (c >> 7) * 4);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      if (!(m < cols && kb + kk < K && ((kept[i] >> kk) & 1u))) st[4 * i + kk] = 0u;
   }
 }
 __device__ __forceinline__ void commit_mcontig_f32(const uint32_t (&st)[16], char* lds, int tid) {
@@ -179,37 +208,29 @@ __device__ __forceinline__ void commit_mcontig_f32(const uint32_t (&st)[16], cha
   }
 }
 
-template <typename T, bool AK, bool BK, bool MASK>
+// A stage of one operand: K, rows (columns of a k-major one) in force; `mapped`: its k-rows are those of g.k_rows
+template <typename T, bool KCONTIG, bool MASK>
 struct Stager {
   static constexpr int EPT = kRowBytes / (int)sizeof(T);   // k per tile: 64 bf16 / 32 float
-  // M, K: the extents in force (the arguments', or what the device-side counts cut them down to)
-  __device__ static void fetchA(uint32_t (&st)[16], const GemmArgs& g, const char* A, int M, int K, int m0, int k0, int tid,
-                                const int (&prow)[4]) {
-    if constexpr (AK) fetch_kcontig<T>(st, A, g.lda, M, m0, K, k0, g.vecA, tid, prow);
-    else if constexpr (sizeof(T) == 2) fetch_mcontig_bf16<MASK>(st, A, g.lda, M, m0, K, k0, g.vecA, tid, g.lens, g.Bt, g.T, g.k_rows);
-    else fetch_mcontig_f32<MASK>(st, A, g.lda, M, m0, K, k0, tid, g.lens, g.Bt, g.T, g.k_rows);
+  uint32_t st[16], kept[4];
+  __device__ __forceinline__ void fetch(const GemmArgs& g, const char* base, long ld, int rows, int K, int at, int k0, int tid, const int (&prow)[4], bool mapped) {
+    const int* krows = mapped ? g.k_rows : nullptr;
+    if constexpr (KCONTIG) fetch_kcontig<T>(st, base, ld, rows, at, K, k0, tid, prow);
+    else if constexpr (sizeof(T) == 2) fetch_mcontig_bf16<MASK>(st, base, ld, rows, at, K, k0, tid, g.lens, g.Bt, g.T, krows, kept);
+    else fetch_mcontig_f32<MASK>(st, base, ld, rows, at, K, k0, tid, g.lens, g.Bt, g.T, krows, kept);
   }
-  __device__ static void fetchB(uint32_t (&st)[16], const GemmArgs& g, const char* B, int K, int n0, int k0, int tid,
-                                const int (&prow)[4]) {
-    if constexpr (BK) fetch_kcontig<T>(st, B, g.ldb, g.N, n0, K, k0, g.vecB, tid, prow);
-    else if constexpr (sizeof(T) == 2) fetch_mcontig_bf16<false>(st, B, g.ldb, g.N, n0, K, k0, g.vecB, tid, nullptr, 1, 0, AK ? nullptr : g.k_rows);
-    else fetch_mcontig_f32<false>(st, B, g.ldb, g.N, n0, K, k0, tid, nullptr, 1, 0, AK ? nullptr : g.k_rows);
-  }
-  __device__ static void commitA(const uint32_t (&st)[16], char* lds, int tid) {
-    if constexpr (AK) commit_kcontig(st, lds, tid);
-    else if constexpr (sizeof(T) == 2) commit_mcontig_bf16(st, lds, tid);
-    else commit_mcontig_f32(st, lds, tid);
-  }
-  __device__ static void commitB(const uint32_t (&st)[16], char* lds, int tid) {
-    if constexpr (BK) commit_kcontig(st, lds, tid);
-    else if constexpr (sizeof(T) == 2) commit_mcontig_bf16(st, lds, tid);
-    else commit_mcontig_f32(st, lds, tid);
+  __device__ __forceinline__ void commit(char* lds, int rows, int K, int at, int k0, int tid) {
+    if constexpr (KCONTIG) { settle_kcontig<T>(st, rows, at, K, k0, tid); commit_kcontig(st, lds, tid); }
+    else if constexpr (sizeof(T) == 2) { settle_mcontig_bf16(st, rows, at, K, k0, tid, kept); commit_mcontig_bf16(st, lds, tid); }
+    else { settle_mcontig_f32(st, rows, at, K, k0, tid, kept); commit_mcontig_f32(st, lds, tid); }
   }
 };
 
 template <typename T, typename TC, bool AK, bool BK, bool MASK>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
-  using S = Stager<T, AK, BK, MASK>;
+  using SA = Stager<T, AK, MASK>;
+  using SB = Stager<T, BK, false>;
+  constexpr int EPT = SA::EPT;
   __shared__ __attribute__((aligned(16))) char lds[4 * kTileBytes];   // A0 B0 A1 B1
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
@@ -245,28 +266,30 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int ra = m0 + ((tid + kThreads * i) >> 3);
-    arow[i] = (AK && g.a_rows && ra < M) ? g.a_rows[ra] : ra;
-    brow[i] = n0 + ((tid + kThreads * i) >> 3);
+    arow[i] = ra < M ? ra : m0;
+    if (AK && g.a_rows) arow[i] = g.a_rows[arow[i]];
+    const int rb = n0 + ((tid + kThreads * i) >> 3);
+    brow[i] = rb < g.N ? rb : n0;
   }
-  const int ktiles = (K + S::EPT - 1) / S::EPT;
+  const int ktiles = (K + EPT - 1) / EPT;
   const int total = ktiles * g.nseg;
-  uint32_t sa[16], sb[16];
-  auto fetch = [&](int it) {
+  SA sa[2];                                                 // stages on their way from memory: two, or every stage is a round trip
+  SB sb[2];
+  auto fetch = [&](int it, int set) __attribute__((always_inline)) {
     int seg = it / ktiles, kt = it - seg * ktiles;
     const char* A = (const char*)g.A + (g.sAz * z + g.sAseg * seg) * (long)sizeof(T);
     const char* B = (const char*)g.B + (g.sBz * z + g.sBseg * seg) * (long)sizeof(T);
-    S::fetchA(sa, g, A, M, K, m0, kt * S::EPT, tid, arow);
-    S::fetchB(sb, g, B, K, n0, kt * S::EPT, tid, brow);
+    sa[set].fetch(g, A, g.lda, M, K, m0, kt * EPT, tid, arow, !AK);
+    sb[set].fetch(g, B, g.ldb, g.N, K, n0, kt * EPT, tid, brow, !AK && !BK);
   };
-  if (total > 0) {
-    fetch(0);
-    S::commitA(sa, lds, tid);
-    S::commitB(sb, lds + kTileBytes, tid);
-  }
-  __syncthreads();
-  for (int it = 0; it < total; ++it) {
-    const int cur = it & 1;
-    if (it + 1 < total) fetch(it + 1);
+  auto commit = [&](int it, int set) __attribute__((always_inline)) {        // into LDS buffer `set`
+    const int k0 = it % ktiles * EPT;
+    sa[set].commit(lds + set * 2 * kTileBytes, M, K, m0, k0, tid);
+    sb[set].commit(lds + set * 2 * kTileBytes + kTileBytes, g.N, K, n0, k0, tid);
+  };
+  // stage `it` is in LDS buffer it % 2, stage it + 1 in register set (it + 1) % 2
+  auto stage = [&](int it, int cur) __attribute__((always_inline)) {
+    if (it + 2 < total) fetch(it + 2, cur);
     const char* As = lds + cur * 2 * kTileBytes + (wm * 64 + r) * kLdsStride + gq * 16;
     const char* Bs = lds + cur * 2 * kTileBytes + kTileBytes + (wn * 64 + r) * kLdsStride + gq * 16;
 #pragma unroll
@@ -278,42 +301,82 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
       acc[1][0] = Mma<T>::run(a1, b0, acc[1][0]);
       acc[1][1] = Mma<T>::run(a1, b1, acc[1][1]);
     }
-    if (it + 1 < total) {
-      S::commitA(sa, lds + (cur ^ 1) * 2 * kTileBytes, tid);
-      S::commitB(sb, lds + (cur ^ 1) * 2 * kTileBytes + kTileBytes, tid);
-    }
+    if (it + 1 < total) commit(it + 1, cur ^ 1);
     __syncthreads();
+  };
+  if (total > 0) {
+    fetch(0, 0);
+    if (total > 1) fetch(1, 1);
+    commit(0, 0);
+  }
+  __syncthreads();
+  for (int it = 0; it < total; it += 2) {
+    stage(it, 0);
+    if (it + 1 < total) stage(it + 1, 1);
   }
 
-  // epilogue: lane holds column (lane % 32), rows 8*(v/4) + 4*(lane/32) + v%4 of each 32x32 block
+  // epilogue: lane holds column (lane % 32), rows 8*(v/4) + 4*(lane/32) + v%4 of each 32x32 block.  Row map and, for an accumulating product, C are
+  // read for a whole block before the first store: a read behind a store waits for it (element by element the epilogue alone took 15 us).
   TC* C = (TC*)g.C + g.sCz * z;
   const float* bias = g.bias ? g.bias + g.sbiasz * z : nullptr;
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int col = n0 + wn * 64 + j * 32 + r;
-    if (col >= g.N) continue;
-    const float bv = bias ? bias[col] : 0.f;
+  for (int i = 0; i < 2; ++i) {
+    const int row0 = m0 + wm * 64 + i * 32 + 4 * gq;
+    int crow[16];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int v = 0; v < 16; ++v) crow[v] = min(row0 + 8 * (v >> 2) + (v & 3), M - 1);
+    if (g.c_rows) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int row = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * gq + (v & 3);
-        if (row < M) {
-          float val = acc[i][j][v] + bv;
-          long off = (long)(g.c_rows ? g.c_rows[row] : row) * g.ldc + col;
-          if constexpr (sizeof(TC) == 4) {
-            if (g.accumulate) val += ((float*)C)[off];
-            ((float*)C)[off] = val;
-          } else {
-            ((uint16_t*)C)[off] = f2bf_bits(val);
-          }
+      for (int v = 0; v < 16; ++v) crow[v] = g.c_rows[crow[v]];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + wn * 64 + j * 32 + r, ccol = min(col, g.N - 1);
+      const float bv = bias ? bias[ccol] : 0.f;
+      float val[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) val[v] = acc[i][j][v] + bv;
+      if constexpr (sizeof(TC) == 4) {
+        if (g.accumulate) {
+          float old[16];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) old[v] = ((const float*)C)[(long)crow[v] * g.ldc + ccol];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) val[v] += old[v];
         }
       }
+      if (col >= g.N) continue;
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (row0 + 8 * (v >> 2) + (v & 3) < M) Store<typename std::conditional<sizeof(TC) == 4, float, bf16_t>::type>::store(C, (long)crow[v] * g.ldc + col, val[v]);
+    }
   }
+}
+
+// k-contiguous operands of less than a chunk: a thread per element of C
+template <typename T, typename TC>
+__global__ __launch_bounds__(256) void short_kernel(GemmArgs g) {
+  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  const int m = (int)(idx / g.N), n = (int)(idx - (long)m * g.N), z = blockIdx.y;
+  if (m >= (g.m_dev ? min(g.M, *g.m_dev) : g.M)) return;
+  const int K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
+  float v = g.bias ? g.bias[g.sbiasz * z + n] : 0.f;
+  for (int seg = 0; seg < g.nseg; ++seg)
+    for (int k = 0; k < K; ++k) {
+      const long b_at = g.b_kcontig ? (long)n * g.ldb + k : (long)k * g.ldb + n;
+      v += Store<T>::load(g.A, g.sAz * z + g.sAseg * seg + (long)(g.a_rows ? g.a_rows[m] : m) * g.lda + k) * Store<T>::load(g.B, g.sBz * z + g.sBseg * seg + b_at);
+    }
+  const long off = g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
+  if (g.accumulate) v += Store<TC>::load(g.C, off);
+  Store<TC>::store(g.C, off, v);
 }
 
 template <typename T, typename TC>
 hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
+  if (g.a_kcontig && g.K < 16 / (int)sizeof(T)) {
+    hipLaunchKernelGGL((short_kernel<T, TC>), dim3(cdiv((long)g.M * g.N, 256), g.nz), dim3(256), 0, s, g);
+    return hipGetLastError();
+  }
   const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
   dim3 grid(tiles_m * tiles_n, g.nz), block(kThreads);
   if (g.a_kcontig && !g.b_kcontig) hipLaunchKernelGGL((gemm_kernel<T, TC, true, false, false>), grid, block, 0, s, g);

@@ -2,7 +2,7 @@
 //
 // gemm_dl8_* (operands loaded straight into LDS, eight wavefronts; described where it is defined):
 //     C[M,N] (+)= sum_seg A_seg[M,K] . B_seg[N,K]^T  (+ bias[N]),
-// both operands k-contiguous, rows 16-byte aligned, K a multiple of 8: dX = DZ W_x^T of long batches; gemm_nn8: the same with B k-major, Zx = X W_x + b
+// both operands k-contiguous, rows 8-byte aligned, K a multiple of 4: dX = DZ W_x^T of long batches; gemm_nn8: the same with B k-major, Zx = X W_x + b
 // with W_x as it lies in memory.
 // gemm_tn8_f32: the k-major operand pair of the weight gradients dW_x = X^T DZ, dW_h = Hprev^T DZ.
 // Products with fewer 256 x 256 tiles than fill the device are gemm_tile.hip's.
@@ -20,6 +20,7 @@ constexpr int kSupM = 8, kSupN = 4;   // tiles per XCD-resident block (kSupM * k
 struct NtArgs {
   const char* A; const char* B; void* C; const float* bias;
   int M, N, K;
+  int ktail;                              // both operands k-contiguous: four k behind the K (a multiple of 8) that the stages walk
   long lda, ldb, ldc;                     // elements
   long sAz, sBz, sCz, sbiasz; int nz;
   int nseg; long sAseg, sBseg;
@@ -218,6 +219,28 @@ __device__ __forceinline__ void gemm_dl_body(const NtArgs& g) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  if (!BROWS && g.ktail) {
+    for (int seg = 0; seg < g.nseg; ++seg) {
+      uint2 ta[4], tb[TN];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = m0 + wm * 128 + i * 32 + r;
+        ta[i] = make_uint2(0u, 0u);
+        if (gq == 0 && row < M) ta[i] = *(const uint2*)(g.A + (g.sAz * z + g.sAseg * seg + (long)(g.a_rows ? g.a_rows[row] : row) * g.lda + K) * 2);
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int row = n0 + wn * 64 + j * 32 + r;
+        tb[j] = make_uint2(0u, 0u);
+        if (gq == 0 && row < g.N) tb[j] = *(const uint2*)(g.B + (g.sBz * z + g.sBseg * seg + (long)row * g.ldb + K) * 2);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mma_last4(ta[i], tb[j], acc[i][j]);
+    }
+  }
 
   // K is a multiple of 8 (whole 16-byte chunks).  The last k-tile of a segment may hold fewer than 8 chunks: the lanes
   // that would fetch a chunk past K point outside the buffer descriptor for that tile and their slots arrive as zeros.
@@ -536,33 +559,44 @@ __global__ __launch_bounds__(256) void frame_map_kernel(const int* lens, int T, 
   frame_map_body(blockIdx.x, lens, T, B, fidx, count);
 }
 
-// dst[r][c] = src[r][c] for c < C, zero for C <= c < ldd  (rows made 16-byte aligned)
-__global__ void pad_rows_kernel(const uint16_t* src, uint16_t* dst, long R, int C, int ldd) {
+// dst[r][c] = src[r][c] for c < C, zero for C <= c < ldd (rows made whole 16 bytes; ldd a multiple of 8).  16 bytes a thread, read at any element
+// (9456 rows of 1802 elements: 40 us with an element a thread, 12.8).
+__global__ void pad_rows_kernel(const uint16_t* src, uint4* dst, long R, int C, int ldd8) {
+  struct __attribute__((packed, aligned(2))) Chunk { uint16_t v[8]; };
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= R * ldd) return;
-  const long rr = idx / ldd;
-  const int cc = (int)(idx - rr * ldd);
-  dst[idx] = cc < C ? src[rr * C + cc] : (uint16_t)0;
+  if (idx >= R * ldd8) return;
+  const long rr = idx / ldd8;
+  const int c0 = (int)(idx - rr * ldd8) * 8;
+  const uint16_t* p = src + rr * C + c0;
+  Chunk o = {};
+  if (c0 + 8 <= C) o = *(const Chunk*)p;
+  else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) if (c0 + e < C) o.v[e] = p[e];
+  }
+  dst[idx] = __builtin_bit_cast(uint4, o);
 }
 
 }  // namespace
 
+// Rows need not be whole 16 bytes: a load of 16 bytes into LDS wants an address that is a multiple of 4, and where a row of a k-major operand ends inside
+// one, what it brings of the next row ends in columns that are not stored.  Rows of 8 n bytes (W_x, DZ) are multiples of 8 whatever n is.
 bool gemm_nt_ok(const GemmArgs& g) {
-  const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  const auto a8 = [](const void* p) { return ((uintptr_t)p & 7u) == 0; };
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
   if ((long)g.M * g.lda * 2 > lim || (long)g.N * g.ldb * 2 > lim) return false;
   if (g.k_dev && g.K % 64 != 0) return false;     // a device-resident K counts whole 64-wide stages
-  return g.in_bf16 && g.a_kcontig && g.b_kcontig && !g.lens && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
-         g.sAz % 8 == 0 && g.sBz % 8 == 0 && g.sAseg % 8 == 0 && g.sBseg % 8 == 0 && a16(g.A) && a16(g.B);
+  return g.in_bf16 && g.a_kcontig && g.b_kcontig && !g.lens && g.K >= 8 && g.K % 4 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 &&
+         g.sAz % 4 == 0 && g.sBz % 4 == 0 && g.sAseg % 4 == 0 && g.sBseg % 4 == 0 && a8(g.A) && a8(g.B);
 }
 
 // B k-major, as gemm_nt_ok otherwise (one segment, float C)
 bool gemm_nn_ok(const GemmArgs& g) {
-  const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  const auto a8 = [](const void* p) { return ((uintptr_t)p & 7u) == 0; };
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
   if ((long)g.M * g.lda * 2 > lim || ((long)g.K + kKB) * g.ldb * 2 > lim) return false;
-  return g.in_bf16 && !g.out_bf16 && g.a_kcontig && !g.b_kcontig && !g.lens && !g.k_dev && !g.k_rows && g.nseg == 1 && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
-         g.N % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B) && (!g.k_phys_rows || (g.k_phys_rows <= g.K && g.K - g.k_phys_rows < kKB));
+  return g.in_bf16 && !g.out_bf16 && g.a_kcontig && !g.b_kcontig && !g.lens && !g.k_dev && !g.k_rows && g.nseg == 1 && g.K % 8 == 0 && g.lda % 4 == 0 && g.ldb % 4 == 0 &&
+         g.N % 4 == 0 && g.sAz % 4 == 0 && g.sBz % 4 == 0 && a8(g.A) && a8(g.B) && (!g.k_phys_rows || (g.k_phys_rows <= g.K && g.K - g.k_phys_rows < kKB));
 }
 
 // B k-major: on tiles of 256 x 256 (256 of them at a time) rather than 128 x 128?  us there / here, operands from memory.  Few tiles, gemm_tile_small: there.
@@ -592,12 +626,12 @@ bool gemm_nn_pays(const GemmArgs& g) {
 }
 
 bool gemm_tn_ok(const GemmArgs& g) {
-  const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  const auto a8 = [](const void* p) { return ((uintptr_t)p & 7u) == 0; };
   const long lim = 0x7fffff00L;     // operands are addressed with 32-bit byte offsets
   const long rows = g.k_rows ? g.k_phys_rows : g.K;
   if (rows * g.lda * 2 > lim || rows * g.ldb * 2 > lim) return false;
   return g.in_bf16 && !g.out_bf16 && !g.a_kcontig && !g.b_kcontig && !g.lens && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
-         g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && a16(g.A) && a16(g.B);
+         g.lda % 4 == 0 && g.ldb % 4 == 0 && g.sAz % 4 == 0 && g.sBz % 4 == 0 && a8(g.A) && a8(g.B);
 }
 
 namespace {
@@ -667,7 +701,7 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nz <= 0) return hipSuccess;
   NtArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
-  a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
+  a.M = g.M; a.N = g.N; a.K = g.K / 8 * 8; a.ktail = g.K % 8; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
   a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.m_dev = g.m_dev; a.k_dev = g.k_dev; a.a_phys_rows = g.a_phys_rows; a.k_phys_rows = g.b_kcontig ? 0 : g.k_phys_rows;
@@ -687,7 +721,7 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
   });
   if (ea != hipSuccess) return ea;
   const dim3 grid(tiles, g.nz);
-  const bool ragged = g.K % kKB != 0, bf = g.out_bf16;
+  const bool ragged = a.K % kKB != 0, bf = g.out_bf16;
   if (!g.b_kcontig) {
     if (ragged || a.k_phys_rows % kKB != 0) hipLaunchKernelGGL(gemm_nn8_f32_kernel<true>, grid, dim3(512), kDlLds, s, a);
     else hipLaunchKernelGGL(gemm_nn8_f32_kernel<false>, grid, dim3(512), kDlLds, s, a);
@@ -706,8 +740,8 @@ hipError_t launch_frame_map(const int* lens, int T, int B, int* fidx, int* count
 
 hipError_t launch_pad_rows(const void* src, void* dst, long R, int C, int ld_dst, hipStream_t s) {
   if (R <= 0) return hipSuccess;
-  const long total = R * ld_dst;
-  hipLaunchKernelGGL(pad_rows_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const uint16_t*)src, (uint16_t*)dst, R, C, ld_dst);
+  const long total = R * (ld_dst / 8);
+  hipLaunchKernelGGL(pad_rows_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const uint16_t*)src, (uint4*)dst, R, C, ld_dst / 8);
   return hipGetLastError();
 }
 

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
     }
     step(it, 0);
   }
-  mfmas(1, false, 0);
+  if (nstage > 0) mfmas(1, false, 0);
   __syncthreads();                                 // the stage buffers are free for the epilogue
 
   // Epilogue.  The four k-steps' shares meet in LDS (the stage buffers are free): k-steps 2 and 3 store theirs side by side, 0 and 1

@@ -42,6 +42,7 @@ constexpr int kKB = 64;                 // k per stage
 struct TileArgs {
   const char* A; const char* B; void* C; const float* bias;
   int M, N, K;
+  int ktail;                              // both operands k-contiguous: four k behind the K (a multiple of 8) that the stages walk
   long lda, ldb, ldc;                     // elements
   long sAz, sBz, sCz, sbiasz; int nz;
   int nseg; long sAseg, sBseg;
@@ -241,6 +242,20 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  if (kHalves && g.ktail && ks == 0) {
+    for (int seg = 0; seg < g.nseg; ++seg) {
+      uint2 ta[2], tb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int ra = m0 + (wm * 2 + i) * 32 + r, rb = n0 + (wn * 2 + i) * 32 + r;
+        ta[i] = tb[i] = make_uint2(0u, 0u);
+        if (gq == 0 && ra < M) ta[i] = *(const uint2*)(a_base + (g.sAseg * seg + (long)(g.a_rows ? g.a_rows[ra] : ra) * g.lda + K) * 2);
+        if (gq == 0 && rb < g.N) tb[i] = *(const uint2*)(b_base + (g.sBseg * seg + (long)rb * g.ldb + K) * 2);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q >> 1][q & 1] = mma_last4(ta[q >> 1], tb[q & 1], acc[q >> 1][q & 1]);
+    }
+  }
   // The end of a phase: this wavefront's reads have returned (what they read may be overwritten once all have met), and what the phase
   // after next multiplies has landed (`younger` loads went out behind it).
   auto end_phase = [&](auto younger) __attribute__((always_inline)) {
@@ -506,7 +521,8 @@ size_t bytes_of(long M, long N, int nz, int ks) { return ks > 1 ? (size_t)ks * n
 TileArgs tile_args(const GemmArgs& g, long others, size_t parts_used) {
   TileArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
-  a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
+  const bool halves = g.a_kcontig && g.b_kcontig;
+  a.M = g.M; a.N = g.N; a.K = halves ? g.K / 8 * 8 : g.K; a.ktail = halves ? g.K % 8 : 0; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
   a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
   a.nseg = g.nseg; a.sAseg = g.sAseg; a.sBseg = g.sBseg; a.accumulate = g.accumulate;
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.a_phys_rows = g.a_phys_rows; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
@@ -529,15 +545,15 @@ hipError_t finish(const TileArgs& a, const GemmArgs& g, hipStream_t s) {
 }  // namespace
 
 bool gemm_tile_ok(const GemmArgs& g) {
-  const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
+  const auto a8 = [](const void* p) { return ((uintptr_t)p & 7u) == 0; };       // (see gemm_nt_ok)
   const long lim = 0x7ffffe00L;           // operands are addressed with 32-bit byte offsets
   const long k_rows = g.k_phys_rows > 0 ? g.k_phys_rows : g.K, a_rows = g.a_kcontig ? (g.a_rows ? g.a_phys_rows : g.M) : k_rows;
   if (a_rows * g.lda * 2 > lim || (g.b_kcontig ? (long)g.N : k_rows) * g.ldb * 2 > lim) return false;
-  if (g.a_kcontig && (g.K % 8 != 0 || (g.k_dev && g.K % 64 != 0))) return false;   // whole chunks; a device-resident K counts whole stages there
+  if (g.a_kcontig && (g.K % (g.b_kcontig ? 4 : 8) != 0 || g.K < 8 || (g.k_dev && g.K % 64 != 0))) return false;   // whole chunks, or a half at the end of both; a device-resident K counts whole stages there
   if (!g.a_kcontig && (g.b_kcontig || g.a_rows || g.m_dev || g.nseg > 1)) return false;
   if (g.a_kcontig && !g.b_kcontig && (g.k_rows || g.nseg > 1)) return false;
-  return g.in_bf16 && !g.lens && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 && g.sAseg % 8 == 0 && g.sBseg % 8 == 0 &&
-         a16(g.A) && a16(g.B) && !(g.accumulate && g.out_bf16);
+  return g.in_bf16 && !g.lens && g.lda % 4 == 0 && g.ldb % 4 == 0 && g.sAz % 4 == 0 && g.sBz % 4 == 0 && g.sAseg % 4 == 0 && g.sBseg % 4 == 0 &&
+         a8(g.A) && a8(g.B) && !(g.accumulate && g.out_bf16);
 }
 
 // Fewer 256 x 256 tiles than fill the device's 256 compute units: those of gemm_nt.hip would leave some idle for the whole product.  us there / here, all rows real,

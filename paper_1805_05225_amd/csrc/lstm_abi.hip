@@ -72,7 +72,7 @@ TinyGroup tiny_bwd(const Plan& p, const void* x, const void* W_x, const void* hp
   return g;
 }
 
-int make_plan(const lstm_desc* d, int bidir, Plan* p) {
+int make_plan(const lstm_desc* d, int bidir, Plan* p, bool odd_fast = true) {
   if (!d) return LSTM_ERR_NULL;
   if (d->T < 0 || d->B < 0 || d->n_in < 1 || d->n < 1) return LSTM_ERR_DIM;
   const long TB = (long)d->T * d->B;
@@ -127,7 +127,8 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->Zx_dir_elems = up(TB * 4 * n * 4) / 4;
   // T == 1 inference, bfloat16: few output tiles, so K is cut into ranges that separate work-groups multiply (each at
   // least four 64-wide stages); their partial products lie side by side and the cell kernel adds them
-  p->single_step = p->bf16 && d->n % 2 == 0 && infer && d->T == 1 && !(d->flags & LSTM_FLAG_PER_STEP);
+  const bool fast = p->bf16 && (odd_fast || d->n % 2 == 0);
+  p->single_step = fast && infer && d->T == 1 && !(d->flags & LSTM_FLAG_PER_STEP);
   // k extent of the input projection: a multiple of 8 (16-byte rows), and for narrow inputs a multiple of 64 so that
   // the product runs through the kernel that loads straight into LDS (x is then copied into zero-padded rows)
   p->n_in_pad = d->n_in < 256 ? (d->n_in + 63) / 64 * 64 : (d->n_in + 7) / 8 * 8;
@@ -145,7 +146,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   p->ws_Zx = take(infer && !p->step_fused ? D * p->Zx_dir_elems * 4 * (p->single_step ? p->ksplit : 1) : 0);
   p->ws_colsum = take(infer ? 0 : D * 64 * 4 * n * 4);
   // padded operand copies for the fast bf16 products
-  p->fast_gemm = p->bf16 && d->n % 2 == 0;
+  p->fast_gemm = fast;
   p->TBp = (TB + 63) / 64 * 64;
   const bool fg = p->fast_gemm;
   p->n_in8 = p->bf16 ? (d->n_in + 7) / 8 * 8 : (d->n_in + 3) / 4 * 4;
@@ -195,12 +196,18 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p) {
   return LSTM_OK;
 }
 
+// The plan of a call that brings its buffers.  Workspaces of odd widths were smaller while their products took the generic kernel: such a one still serves, that way.
+int call_plan(const lstm_desc* d, int bidir, Plan* p) {
+  const int rc = make_plan(d, bidir, p);
+  return !rc && p->bf16 && p->n % 2 != 0 && d->workspace_bytes < p->workspace_bytes ? make_plan(d, bidir, p, false) : rc;
+}
+
 bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
 
 // rows one behind the other: the tables' places in the workspace
 PackRows pack_rows(const Plan& p, char* ws, const int* lens, bool backward, const lstm_desc* desc) {
   PackRows r = {};
-  if (!p.fast_gemm || !lens || p.B <= 8 || p.T < 2 || (desc->flags & LSTM_FLAG_PER_STEP)) return r;
+  if (!p.bf16 || p.n % 2 != 0 || !lens || p.B <= 8 || p.T < 2 || (desc->flags & LSTM_FLAG_PER_STEP)) return r;
   r.slots = persist_pack_slots(p.T, p.B, p.n, p.D, backward);
   if (r.slots == 0) return r;
   r.lens = lens; r.T = p.T; r.B = p.B; r.tab_steps = pack_tab_steps(p.T, p.B, r.slots); r.max_steps = pack_max_steps(p.T, backward);
@@ -208,12 +215,6 @@ PackRows pack_rows(const Plan& p, char* ws, const int* lens, bool backward, cons
   r.down = r.up + (size_t)r.slots * r.tab_steps;
   r.steps = (int*)(r.down + (size_t)r.slots * r.tab_steps);
   return r;
-}
-
-int widest(long ld_elems, long s1, long s2, size_t esz, int cap) {
-  int v = cap;
-  while (v > (int)esz && ((ld_elems * (long)esz) % v || (s1 * (long)esz) % v || (s2 * (long)esz) % v)) v >>= 1;
-  return v;
 }
 
 int check_device() {                 // is the current device one this library is built for?  (looked up once per device)
@@ -266,7 +267,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
             const void* h0, const void* c0, const int32_t* seq_lens, void* y, void* c, void* hT, void* cT, void* reserve,
             void* workspace, void* stream) {
   Plan p;
-  int rc = make_plan(desc, bidir, &p);
+  int rc = call_plan(desc, bidir, &p);
   if (rc) return rc;
   if (!bidir && desc->direction != 1 && desc->direction != -1) return LSTM_ERR_DIRECTION;
   const bool infer = desc->flags & LSTM_FLAG_INFERENCE;
@@ -326,7 +327,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         g.A = Acat + d * B * Kc * 2; g.B = Wcat + d * (4 * n) * Kc * 2; g.C = z + d * p.ksplit * part;
         g.M = p.B; g.N = 4 * p.n; g.K = (int)Kr; g.lda = Kc; g.ldb = Kc; g.ldc = 4 * n;
         g.sAz = Kr; g.sBz = Kr; g.sCz = part; g.nz = p.ksplit; g.nseg = 1;
-        g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = true; g.out_bf16 = false; g.vecA = 16; g.vecB = 16;
+        g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = true; g.out_bf16 = false;
         // (ranges planned for that kernel's tiles: the one for few tiles takes 82 instead of 73 us a step at 1500 rows, 131 instead of 119 at 3000)
         HIPCHK(gemm_nt_ok(g) ? launch_gemm_nt(g, s) : launch_gemm(g, s));
       }
@@ -349,8 +350,6 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     g.lda = p.n_in; g.ldb = 4 * n; g.ldc = 4 * n;
     g.sAz = 0; g.sBz = (long)p.n_in * 4 * n; g.sCz = gates_stride; g.sbiasz = 4 * n; g.nz = p.D; g.frames = true;
     g.nseg = 1; g.a_kcontig = true; g.b_kcontig = false; g.in_bf16 = p.bf16; g.out_bf16 = false;
-    g.vecA = widest(g.lda, 0, 0, p.esz, 16);
-    g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
     return g;
   };
   bool projected = false;                // the set-up launch did it
@@ -510,8 +509,6 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.a_kcontig = true; g.in_bf16 = p.bf16; g.accumulate = 1; g.c_rows = rows + d * B; g.k_phys_rows = p.n;
       g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
       if (!(p.bf16 ? gemm_tile_ok(g) : gemm_float_ok(g))) { g.K = p.n; g.k_phys_rows = 0; g.parts = nullptr; }
-      g.vecA = widest(g.lda, 0, 0, p.esz, 16);
-      g.vecB = widest(g.ldb, 0, 0, p.esz, 4);
       HIPCHK(launch_gemm(g, s));
     }
     return LSTM_OK;
@@ -628,7 +625,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
             const void* dhT, const void* dcT, void* dx, void* dW_x, void* dW_h, void* db, void* dh0, void* dc0,
             void* workspace, void* stream) {
   Plan p;
-  int rc = make_plan(desc, bidir, &p);
+  int rc = call_plan(desc, bidir, &p);
   if (rc) return rc;
   if (!bidir && desc->direction != 1 && desc->direction != -1) return LSTM_ERR_DIRECTION;
   if (desc->flags & LSTM_FLAG_INFERENCE) return LSTM_ERR_UNSUPPORTED;
@@ -875,8 +872,6 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.lda = 4 * n; g.ldb = 4 * n; g.ldc = n_in; g.nz = 1;
       g.nseg = p.D; g.sAseg = (long)p.DZ_dir_elems; g.sBseg = (long)(n_in * 4 * n); g.frames = true;
       g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = p.bf16; g.out_bf16 = p.bf16;
-      g.vecA = widest(g.lda, g.sAseg, 0, p.esz, 16);
-      g.vecB = widest(g.ldb, g.sBseg, 0, p.esz, 16);
       Phase ph(LSTM_PHASE_GEMM_DX, 1, s);
       if (compact && (gemm_nt_ok(g) || !p.bf16)) {      // rows of padded frames: zero, and left out of the product
         if (!dx_cleared) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
@@ -893,7 +888,6 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.M = M; g.N = 4 * p.n; g.K = (int)TB; g.lda = lda; g.ldb = 4 * n; g.ldc = 4 * n;
       g.sAz = sAz; g.sBz = (long)p.DZ_dir_elems; g.sCz = (long)M * 4 * n; g.nz = p.D; g.nseg = 1;
       g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
-      g.vecA = 16; g.vecB = 16;
       if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
       if (gemm_tile_small(M, 4L * p.n, p.D)) parts_of(g);
       return g;
@@ -925,8 +919,6 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = p.bf16; g.out_bf16 = false; g.accumulate = acc;
       if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }   // the real frames only
       else { g.lens = seq_lens; g.Bt = p.B; g.T = p.T; }                              // (or every frame, padded ones read as zero)
-      g.vecA = widest(g.lda, 0, 0, p.esz, 4);
-      g.vecB = widest(g.ldb, g.sBz, 0, p.esz, 4);
       if (!p.bf16) {
         parts_of(g);
         if (pad_x) {
@@ -947,7 +939,6 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.sAz = (long)(p.res_dir_stride / p.esz); g.sCz = (long)(n * 4 * n);
       g.lens = nullptr;
       if (!p.bf16) parts_of(g);
-      g.vecA = widest(g.lda, g.sAz, 0, p.esz, 4);
       Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
       HIPCHK(launch_gemm(g, s));
     }
@@ -1035,9 +1026,6 @@ int lstm_gemm(int in_bf16, int out_bf16, int a_kcontig, int b_kcontig, int M, in
   g.A = A; g.B = B; g.C = C; g.bias = bias; g.M = M; g.N = N; g.K = K; g.lda = lda; g.ldb = ldb; g.ldc = ldc;
   g.nz = 1; g.nseg = 1; g.a_kcontig = a_kcontig; g.b_kcontig = b_kcontig; g.in_bf16 = in_bf16; g.out_bf16 = out_bf16;
   g.accumulate = accumulate; g.lens = lens; g.Bt = Bt; g.T = T;
-  auto ptr_vec = [&](const void* p, int cap) { int v = cap; while (v > (int)esz && ((uintptr_t)p % v)) v >>= 1; return v; };
-  g.vecA = std::min(widest(lda, 0, 0, esz, a_kcontig ? 16 : 4), ptr_vec(A, a_kcontig ? 16 : 4));
-  g.vecB = std::min(widest(ldb, 0, 0, esz, b_kcontig ? 16 : 4), ptr_vec(B, b_kcontig ? 16 : 4));
   if (launch_gemm(g, (hipStream_t)stream) != hipSuccess) { (void)hipGetLastError(); return LSTM_ERR_HIP; }
   return LSTM_OK;
 }

@@ -5,6 +5,13 @@
 namespace lstm {
 namespace {
 
+// Four more k for a 32 x 32 block: K of a product of k-contiguous operands that is 4 more than a multiple of 8 (4n for odd n) ends in half a 16-byte chunk,
+// whose other half is the next row's.  The kernels walk the whole chunks and begin their accumulators with these products, operands straight
+// from memory (lanes 0-31 four k of a row; lanes 32-63, which hold the next four, zeros).
+__device__ __forceinline__ f32x16 mma_last4(uint2 a, uint2 b, f32x16 c) {
+  typedef __attribute__((ext_vector_type(4))) short s16x4;
+  return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
+}
 // Block `block` (256 threads) of those that clear the regions.
 __device__ __forceinline__ void fill_zero_body(const ZeroRegions& r, int block, int tid) {
   int k = 0;

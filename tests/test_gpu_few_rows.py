@@ -21,7 +21,8 @@ def _bf(rng, *shape, w=1.0):
                                       (65, 77, 34), (192, 1200, 66), (193, 1200, 66), (12, 4100, 24), (1025, 300, 104), (1300, 77, 34),
                                       # every tile of gemm_skinny.hip, rows and units that end inside one: 96 x 128 (twice), 128 x 128, 64 x 128, 96 x 64, 64 x 64
                                       (767, 40, 1000), (765, 64, 1021), (1001, 40, 1000), (500, 40, 700), (333, 100, 901), (640, 300, 512), (257, 64, 330), (1024, 8, 250),
-                                      (64, 40, 1000), (66, 40, 1000), (129, 40, 481), (130, 40, 480), (200, 32, 504)])   # either side of few_cell_pays; 32 x 64
+                                      (64, 40, 1000), (66, 40, 1000), (129, 40, 481), (130, 40, 480), (200, 32, 504),
+                                      (1, 37, 51), (16, 300, 105), (17, 301, 107), (64, 40, 131), (193, 33, 67), (500, 41, 701), (1030, 45, 203)])   # odd widths; either side of few_cell_pays; 32 x 64
 def test_stepped_cell(B, n_in, n):
     from paper_1805_05225_amd import binding as Bn
     rng = np.random.default_rng(B + n_in)

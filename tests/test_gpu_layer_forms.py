@@ -40,6 +40,48 @@ def test_wider_layer(T, B, n_in, n, bidir):
 
 
 @pytest.mark.parametrize("T,B,n_in,n,bidir", [
+    (60, 7, 333, 263, True), (30, 21, 200, 443, True), (9, 3, 8, 1003, False), (40, 10, 123, 201, False),
+    (52, 64, 60, 1001, True),                                               # the input projection in many tiles
+    (200, 32, 2100, 131, False),                                            # the data gradient
+    (12, 9, 2100, 1001, True),                                              # the weight gradients
+])
+def test_odd_width(T, B, n_in, n, bidir):
+    """Rows of W_x and DZ are whole 8 bytes, not 16, and the data gradient's K ends in half a chunk."""
+    _layer(T, B, n_in, n, bidir, "bf16")
+
+
+@pytest.mark.parametrize("T,B,n_in,n", [(9, 5, 37, 201), (1, 20, 40, 133)])
+def test_odd_width_in_the_smallest_workspace(T, B, n_in, n):
+    """Products at any alignment, for workspaces of the size that sufficed while odd widths had no others."""
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(n)
+    r = lambda *shape: torch.from_numpy(rng.uniform(-0.3, 0.3, shape)).to(torch.bfloat16).cuda()
+    x, Wx, Wh, dy = r(T, B, n_in), r(2, n_in, 4 * n), r(2, n, 4 * n), r(T, B, 2 * n)
+    lens = torch.from_numpy(_lens(rng, T, B).astype(np.int32)).cuda()
+    args = (x, Wx, Wh, None, None, None, lens)
+    flags = Bn.FLAG_INFERENCE if T == 1 else 0
+    want = Bn.forward(*args, bidirectional=True, flags=flags)
+    lo, hi = 0, want["workspace"].numel()                                    # the smallest size that is not refused
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        try:
+            Bn.forward(*args, bidirectional=True, flags=flags, workspace=torch.empty(mid, dtype=torch.uint8, device="cuda"))
+            hi = mid
+        except Bn.LstmError as e:
+            assert e.status == -6
+            lo = mid
+    assert hi < want["workspace"].numel() or T == 1
+    f = Bn.forward(*args, bidirectional=True, flags=flags, workspace=torch.empty(hi, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    check("y", f["y"], want["y"].double().cpu().numpy(), TOL["bf16"])
+    if T > 1:
+        g, h = (Bn.backward(k, x, Wx, Wh, None, None, lens, dy) for k in (f, want))
+        torch.cuda.synchronize()
+        for name in ("dx", "dW_x", "dW_h", "db"):
+            check(name, g[name], h[name].double().cpu().numpy(), TOL["bf16"])
+
+
+@pytest.mark.parametrize("T,B,n_in,n,bidir", [
     (5, 1, 37, 132, False), (6, 17, 30, 256, True), (4, 40, 101, 257, True), (7, 70, 33, 131, True), (3, 300, 8, 130, False),
     (5, 33, 64, 513, True), (4, 64, 41, 1001, True), (90, 12, 30, 140, False),
 ])

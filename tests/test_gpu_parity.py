@@ -79,7 +79,11 @@ def compare(f, g, fo, go, tol):
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("M,N,K", [(130, 140, 70), (257, 129, 620), (5, 7, 3), (256, 256, 256), (300, 520, 136), (1000, 260, 2048),
                                    (300, 520, 160), (513, 300, 4096), (40, 1030, 32), (264, 520, 200), (40, 4096, 333), (1024, 256, 64),
-                                   (300, 520, 1000), (520, 300, 4000), (260, 260, 8), (260, 260, 72)])
+                                   (300, 520, 1000), (520, 300, 4000), (260, 260, 8), (260, 260, 72),
+                                   # rows of whole 8 bytes: K and N that are 4 more than a multiple of 8, many 256 x 256 tiles, K ranges of none or few stages
+                                   (300, 524, 132), (132, 1004, 12), (516, 260, 1028), (4100, 3332, 68), (3900, 3404, 196),
+                                   # rows at any element: K of less than a chunk, whole chunks, one more, one less; one column
+                                   (300, 517, 515), (130, 1, 9), (1, 129, 64), (133, 131, 7), (129, 257, 63), (65, 67, 1), (279, 1853, 519)])
 def test_gemm_layouts(dt, M, N, K):
     rng = np.random.default_rng(M * 1000 + N + K)
     td = tdtype(dt)
