@@ -242,8 +242,8 @@ int persist_fwd_rows(int B, int n, int ndir); // rows per work-group, 8 or 16, w
 bool persist_fwd_w_rows(int B, int n, int ndir);   // with those 8: does it read W_h as it lies in memory?
 int persist_bwd_rows(int B, int n, int ndir);
 bool persist_fwd_fits(const PFwdArgs& a);     // would launch_persist_fwd launch anything on this device?
-// Float storage (an initial hidden state goes into the pre-activations, as for bfloat16): Wf is the per-step kernel's packed W_h (launch_pack_wh_fwd), ring0 / ring1 its
-// fragment-ordered h buffers (initialised here), y / hprev float; nkc = chunks of 16 k.
+// Float storage (an initial hidden state goes into the pre-activations, as for bfloat16): Wf is the per-step kernel's packed W_h, ring0 / ring1 its
+// fragment-ordered h buffers (all by launch_prep_fwd_f32), y / hprev float; nkc = chunks of 16 k.
 hipError_t launch_persist_fwd_f32(const PFwdArgs& a, hipStream_t s);
 bool persist_fwd_f32_fits(const PFwdArgs& a);
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward);      // are the float loops faster than the per-step kernels?
@@ -276,11 +276,10 @@ struct PBwdArgs {
 // bwdp_ring_bytes per direction and slot) fit the device for this problem?
 bool persist_bwd_fits(const PBwdArgs& a);
 hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s);
-// Float storage: the same exchange of partial sums in float.  W_h^T via launch_pack_wh_bwd_f32p (bwd_f32_wh_bytes per
+// Float storage: the same exchange of partial sums in float.  W_h^T via launch_prep_bwd_f32 (bwd_f32_wh_bytes per
 // direction), rings of bwd_f32_ring_bytes per direction and slot, zero-filled; gates, cs, dy, DZ float.
 bool persist_bwd_f32_fits(const PBwdArgs& a);
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s);
-hipError_t launch_pack_wh_bwd_f32p(const void* W_h, void* Wb, int n, int ndir, hipStream_t s);
 inline int bwd_f32_nct(int n) { return n <= 256 ? 4 : n <= 512 ? 8 : 16; }      // output column tiles (of 16) per wavefront
 inline size_t bwd_f32_wh_bytes(int n) { return (size_t)((n + 15) / 16) * 4 * bwd_f32_nct(n) * 16 * 64 * 4; }
 inline size_t bwd_f32_ring_bytes(int B, int n) {
@@ -425,6 +424,9 @@ hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, in
 constexpr int kFewZxRows = 512;
 constexpr long kFewZxWalk = 5120;
 bool few_zx_ok(const GemmArgs& g);
+// The same for the float loops (forward: `p` as launch_persist_fwd_f32 takes it).
+hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, hipStream_t s);
+hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s);
 hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]

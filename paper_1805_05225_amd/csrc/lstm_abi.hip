@@ -390,7 +390,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         if (seq_lens) {
           int* fidx = (int*)(ws + p.ws_fidx);
           int* count = (int*)(ws + p.ws_count);
-          HIPCHK(launch_frame_map(seq_lens, p.T, p.B, fidx, count, s));
+          if (!frames_mapped) HIPCHK(launch_frame_map(seq_lens, p.T, p.B, fidx, count, s));
           g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = g.M; g.m_dev = count;
         }
       }
@@ -462,23 +462,6 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   // (six layers pooled by 8, 200 - 1500 frames: gradients moved by 2.7 %).
   const bool w_rows = infer && p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd && rows.slots == 0 && paired && persist_fwd_w_rows(p.B, p.n, p.D);
   projected = w_rows && few_zx_ok(zx);
-  {
-    Phase ph(projected ? LSTM_PHASE_GEMM_ZX : LSTM_PHASE_PREP, projected ? 1 : 5, s);
-    ZeroRegions z;
-    z.add(ws + p.ws_sync, p.sync_bytes);
-    if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd)
-      z.add(ws + p.ws_Wf + p.Wf_bytes, 1024);              // the chunk of zeros behind the packed W_h (single-launch path)
-    // (on the single-launch path the fills, the packed W_h and the initial ring are one launch)
-    if (p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd) {
-      FrameMapArgs fm = {};
-      if (p.fast_gemm && seq_lens && !projected) {   // the input projection below goes over the real frames
-        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
-        frames_mapped = true;
-      }
-      HIPCHK(launch_prep_fwd_ll(z, W_h, w_rows ? nullptr : (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
-                                p.nrt, fm, rows, projected ? &zx : nullptr, s));
-    } else HIPCHK(launch_fill_zero_many(z, s));
-  }
   // single-launch path: bf16 storage, at least two steps, register budget of the kernel
   bool use_ll = p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.nkc_ll_f <= kLLMaxNkcFwd;
   // what the per-step kernels work on (also what a single-launch path that does not start falls back to)
@@ -549,8 +532,32 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   }
   const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_fwd_f32_fits(pa) &&
                         persist_f32_pays(p.T, p.B, p.n, p.D, seq_lens != nullptr, pa.plain_launch, false);
+  {
+    Phase ph(projected ? LSTM_PHASE_GEMM_ZX : LSTM_PHASE_PREP, projected ? 1 : 5, s);
+    ZeroRegions z;
+    z.add(ws + p.ws_sync, p.sync_bytes);
+    if (use_ll)
+      z.add(ws + p.ws_Wf + p.Wf_bytes, 1024);              // the chunk of zeros behind the packed W_h (single-launch path)
+    // (on the single-launch paths the fills, the packed W_h and the initial ring are one launch)
+    if (use_ll) {
+      FrameMapArgs fm = {};
+      if (p.fast_gemm && seq_lens && !projected) {   // the input projection below goes over the real frames
+        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
+        frames_mapped = true;
+      }
+      HIPCHK(launch_prep_fwd_ll(z, W_h, w_rows ? nullptr : (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
+                                p.nrt, fm, rows, projected ? &zx : nullptr, s));
+    } else if (use_ll32) {
+      FrameMapArgs fm = {};
+      if (seq_lens) {
+        fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
+        frames_mapped = true;
+      }
+      HIPCHK(launch_prep_fwd_f32(z, W_h, ws + p.ws_Wf, pa, fm, s));
+    } else HIPCHK(launch_fill_zero_many(z, s));
+  }
   const bool single = use_ll ? persist_fwd_fits(pa) : use_ll32;
-  if (T > 0 && (!use_ll || !single) && (rc = pack_w())) return rc;
+  if (T > 0 && !single && (rc = pack_w())) return rc;
   if (!single && (rc = state_in())) return rc;
   if (T > 0) {
     if ((rc = project())) return rc;
@@ -715,8 +722,8 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       z.add(ws + p.ws_dzfrag0, p.dzfrag_bytes);
       z.add(ws + p.ws_dzfrag1, p.dzfrag_bytes);
       if (2 * p.nrt <= kColsumSlices) z.add(ws + p.ws_colsum, D * kColsumSlices * 4 * n * 4);   // bias-gradient slices of row groups the grid lacks
-      // (the bfloat16 single-launch path clears and packs W_h^T in one launch)
-      if (use_ll) {
+      // (the single-launch paths clear and pack W_h^T in one launch)
+      if (use_ll || use_ll32) {
         FrameMapArgs fm = {};
         if (compact) {
           fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
@@ -726,13 +733,13 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           z.add(dx, (size_t)TB * n_in * p.esz);
           dx_cleared = true;
         }
-        HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || persist_bwd_rows(p.B, p.n, p.D) == 8, fm, rows, s));
+        if (use_ll32) HIPCHK(launch_prep_bwd_f32(z, W_h, ws + p.ws_Wb, p.n, p.D, fm, s));
+        else HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || persist_bwd_rows(p.B, p.n, p.D) == 8, fm, rows, s));
       } else HIPCHK(launch_fill_zero_many(z, s));
     }
-    if (!use_ll) {
+    if (!use_ll && !use_ll32) {
       Phase ph(LSTM_PHASE_PREP, 1, s);
-      if (use_ll32) HIPCHK(launch_pack_wh_bwd_f32p(W_h, ws + p.ws_Wb, p.n, p.D, s));
-      else HIPCHK(launch_pack_wh_bwd(W_h, (uint4*)(ws + p.ws_Wb), p.n, p.nkc_b, p.D, p.bf16, s));
+      HIPCHK(launch_pack_wh_bwd(W_h, (uint4*)(ws + p.ws_Wb), p.n, p.nkc_b, p.D, p.bf16, s));
     }
 
     const size_t frag_dir = (size_t)p.nrt * p.nkc_b * 1024;

@@ -3219,6 +3219,63 @@ __global__ __launch_bounds__(512) void prep_zx_kernel(PrepArgs a, FewZxArgs f) {
   const int bid = ((int)blockIdx.x - f.blocks) * 2 + (threadIdx.x >> 8);
   if (bid < a.first_map) set_up_body(a, bid, threadIdx.x & 255);
 }
+// Everything a float single-launch loop needs set up, in one launch, as prep_ll_kernel does for bfloat16: as kernels of their own (fills, W_h, the rings of either direction, the
+// frame map) they took 4 to 5 us each, most of it the gap (five layers of 896 units, 4 rows of 9 frames, training 1049 -> 983 us).
+struct PrepF32Args {
+  ZeroRegions z;
+  const float* W; void* Wout; int n, nk, nct; long w_total;     // nk: nkc (forward) / unit tiles (backward)
+  uint4* ring0[2]; uint4* ring1[2]; long ring_total;            // forward: 16-byte units of a direction's ring
+  const int* lens; int T, B; int* fidx; int* count;             // frame map (fidx == NULL: none)
+  int first_pack, first_ring, first_map, per_ring, backward;
+};
+// W_h^T for the float partial-sum backward kernel: float index
+// ((((dir*ntile + J)*4 + wave)*NCT + ci)*16 + s)*64 + lane holds W_h[unit (wave + 4 ci)*16 + lane%16][gate column
+// (kappa/16)*n + J*16 + kappa%16], kappa = 16 (lane/16) + s; stored so that a lane's k-steps 4 s4 .. 4 s4 + 3 are one float4:
+// float4 index ((((dir*ntile + J)*4 + wave)*NCT + ci)*4 + s4)*64 + lane.
+// A wavefront packs one (J, wave, ci): four lanes read the 64 consecutive bytes of a row and gate, and store 256 consecutive bytes with
+// the lanes of the other rows (one value per thread and 64 rows per load: 32 us for config 2's two directions).
+typedef float4 __attribute__((aligned(4))) float4_u;
+__device__ __forceinline__ void pack_wh_bwd_f32p_body(long idx, const float* W, float4* out, int n, int ntile, int nct, long total) {
+  if (idx >= total) return;
+  const int r = (idx & 63) >> 2, s4 = idx & 3;
+  long rest = idx >> 6;
+  const int ci = rest % nct; rest /= nct;
+  const int wave = rest & 3; rest >>= 2;
+  const int J = rest % ntile, dir = rest / ntile;
+  const int unit_in = (wave + 4 * ci) * 16 + r, unit_out = J * 16 + 4 * s4;    // kappa = 16 q + s: gate q of unit J * 16 + s
+  const float* row = W + ((long)dir * n + min(unit_in, n - 1)) * 4 * n;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (unit_in < n && unit_out + 4 <= n) {                     // (at any float)
+      const float4 x = *(const float4_u*)(row + q * n + unit_out);
+      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    } else if (unit_in < n) {
+      for (int e = 0; e < 4; ++e)
+        if (unit_out + e < n) v[e] = row[q * n + unit_out + e];
+    }
+    out[((idx >> 6) * 4 + s4) * 64 + q * 16 + r] = make_float4(v[0], v[1], v[2], v[3]);
+  }
+}
+__global__ __launch_bounds__(256) void prep_f32_kernel(PrepF32Args a) {
+  const int bid = blockIdx.x, tid = threadIdx.x;
+  if (bid < a.first_pack) {
+    fill_zero_body(a.z, bid, tid);
+  } else if (bid < a.first_ring) {
+    const long idx = (long)(bid - a.first_pack) * 256 + tid;
+    if (a.backward) pack_wh_bwd_f32p_body(idx, a.W, (float4*)a.Wout, a.n, a.nk, a.nct, a.w_total);
+    else pack_wh_fwd_body(idx, a.W, (uint4*)a.Wout, a.n, a.nk, a.w_total);
+  } else if (bid < a.first_map) {                               // before the first step: slot 0 holds zeros that carry the tag of step 0 in every unit, slot 1 is cleared
+    const int d = (bid - a.first_ring) / a.per_ring;
+    const long idx = (long)(bid - a.first_ring - d * a.per_ring) * 256 + tid;
+    if (idx >= a.ring_total) return;
+    const unsigned t = ll_fwd_tag(0u) << 30;
+    a.ring0[d][idx] = make_uint4(0u, t, 0u, t);
+    a.ring1[d][idx] = make_uint4(0u, 0u, 0u, 0u);
+  } else {
+    frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.fidx, a.count);
+  }
+}
 // The initial state as the left operand of its product with W_h: rows of `ld` elements, rounded to the storage type as the recurrence
 // would feed it and padded with zeros; rows[dir][b] = the frame and row whose pre-activations it goes into (a row without frames: one that nobody reads).
 template <typename TW>
@@ -3432,14 +3489,6 @@ hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, in
   hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0) + (rows.slots > 0 ? 1 : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-// float ring, before the first step: slot 0 holds zeros that carry the tag of step 0 in every unit, slot 1 is cleared
-__global__ void init_ring_f32_kernel(uint4* ring0, uint4* ring1, long total) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const unsigned t = ll_fwd_tag(0u) << 30;
-  ring0[idx] = make_uint4(0u, t, 0u, t);
-  ring1[idx] = make_uint4(0u, 0u, 0u, 0u);
-}
 // The float kernels' form for n units, as above (50 steps, both directions: n = 500, 64 rows, forward 519 -> 239 us, backward 767 -> 253; n = 256,
 // 16 rows, 332 -> 155 and 329 -> 149, with the exchange inside an XCD).
 FwdKernel fwd_f32_for(int n) { return n <= 256 ? persist_fwd_f32_kernel<4> : n <= 512 ? persist_fwd_f32_kernel<8> : persist_fwd_f32_kernel<16>; }
@@ -3452,7 +3501,9 @@ int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntil
 // 1387 us here, 838 there).  Both sides as they were measured, in us, for n from 130 to 1024, 1 to 512 rows, 2 to 60 steps, one and two
 // directions, plain and cooperative launches (1573 shapes): the choice was within 5 % of the faster side in 99 % of them and never 1.25 times
 // it; always the loops was up to 2.8 times the other.  The loops' side has been measured again since their products are bfloat16 parts (4 and 100 steps of 11
-// shapes): of 396 shapes of 2 to 24 steps the choice is within 5 % of the per-step kernels or faster in 95 %, never 1.16 times them.  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
+// shapes): of 396 shapes of 2 to 24 steps the choice is within 5 % of the per-step kernels or faster in 95 %, never 1.16 times them. Their set-up is one launch since: of 480
+// shapes of 2 to 14 steps and 2 to 64 rows the choice is within 5 % of the faster side in all but 9, at most 1.25 times it (4 steps of 2 rows, n = 700, both directions, ordinary launches: 51 and
+// 92 us, forward and backward, per step 85 and 156).  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward) {
   const int form = n <= 256 ? 0 : n <= 512 ? 1 : 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
   const bool one = (long)ntile * cdiv(B, 16) * ndir <= cap, pair = !one && B > 16;
@@ -3461,11 +3512,11 @@ bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launc
   double here, there;
   if (backward) {
     const double step[2][3] = {{2.8, 4.3, 7.2}, {7.2, 9.3, 17.4}};
-    here = 34.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
+    here = 14.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
     there = 58.3 + 16.0 * w + T * std::max(4.25 + 17.1e-3 * n + 6.6 * nr + 10.4 * nnr, 22.0 * nnr);
   } else {
     const double step[2][3] = {{1.9, 2.65, 4.25}, {4.2, 6.2, 9.2}};
-    here = 19.0 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
+    here = -0.5 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
     there = 27.9 + 7.8 * w + T * std::max(3.8 + 6.15e-3 * n + 4.15 * nr + 4.9 * nnr, 10.9 * nnr);
   }
   return here < there;
@@ -3477,41 +3528,8 @@ bool persist_fwd_f32_fits(const PFwdArgs& a) {
 }
 hipError_t launch_persist_fwd_f32(const PFwdArgs& a, hipStream_t s) {
   if (!persist_fwd_f32_fits(a)) return hipErrorCooperativeLaunchTooLarge;
-  const long total = (long)cdiv(a.B, 16) * a.nkc * 64;
-  for (int d = 0; d < a.ndir; ++d)
-    hipLaunchKernelGGL(init_ring_f32_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, a.d[d].ring0, a.d[d].ring1, total);
-  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   const auto kernel = fwd_f32_for(a.n);
   return coop_slabs(kernel, cdiv(a.n, 16), f32_rows_per_group(kernel, cdiv(a.n, 16), a.B, a.ndir), a, s);
-}
-// W_h^T for the float partial-sum backward kernel: float index
-// ((((dir*ntile + J)*4 + wave)*NCT + ci)*16 + s)*64 + lane holds W_h[unit (wave + 4 ci)*16 + lane%16][gate column
-// (kappa/16)*n + J*16 + kappa%16], kappa = 16 (lane/16) + s; stored so that a lane's k-steps 4 s4 .. 4 s4 + 3 are one float4:
-// float4 index ((((dir*ntile + J)*4 + wave)*NCT + ci)*4 + s4)*64 + lane.
-// A wavefront packs one (J, wave, ci): four lanes read the 64 consecutive bytes of a row and gate, and store 256 consecutive bytes with
-// the lanes of the other rows (one value per thread and 64 rows per load: 32 us for config 2's two directions).
-__global__ void pack_wh_bwd_f32p_kernel(const float* W, float4* out, int n, int ntile, int nct, long total) {
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int r = (idx & 63) >> 2, s4 = idx & 3;
-  long rest = idx >> 6;
-  const int ci = rest % nct; rest /= nct;
-  const int wave = rest & 3; rest >>= 2;
-  const int J = rest % ntile, dir = rest / ntile;
-  const int unit_in = (wave + 4 * ci) * 16 + r, unit_out = J * 16 + 4 * s4;    // kappa = 16 q + s: gate q of unit J * 16 + s
-  const float* row = W + ((long)dir * n + min(unit_in, n - 1)) * 4 * n;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (unit_in < n && n % 4 == 0 && unit_out < n) {
-      const float4 x = *(const float4*)(row + q * n + unit_out);
-      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    } else if (unit_in < n) {
-      for (int e = 0; e < 4; ++e)
-        if (unit_out + e < n) v[e] = row[q * n + unit_out + e];
-    }
-    out[((idx >> 6) * 4 + s4) * 64 + q * 16 + r] = make_float4(v[0], v[1], v[2], v[3]);
-  }
 }
 bool persist_bwd_f32_fits(const PBwdArgs& a) {
   if (a.n > 1024 || a.T < 2) return false;
@@ -3519,11 +3537,29 @@ bool persist_bwd_f32_fits(const PBwdArgs& a) {
   if ((long)cdiv(a.B, 16) * ntile * ntile * 1024 >= 0x7ff00000L) return false;
   return ntile * a.ndir <= capacity(bwd_f32_for(a.n));
 }
-hipError_t launch_pack_wh_bwd_f32p(const void* W, void* Wb, int n, int ndir, hipStream_t s) {
-  const int ntile = cdiv(n, 16), nct = bwd_f32_nct(n);
-  const long total = (long)ndir * ntile * 4 * nct * 64;
-  hipLaunchKernelGGL(pack_wh_bwd_f32p_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, (const float*)W, (float4*)Wb, n, ntile, nct, total);
+static hipError_t prep_f32(PrepF32Args a, const ZeroRegions& z, int ndir, const FrameMapArgs& fm, hipStream_t s) {
+  if (z.overflow) return hipErrorInvalidValue;
+  a.z = z;
+  a.first_pack = z.count ? z.first_block[z.count] : 0;
+  a.first_ring = a.first_pack + cdiv(a.w_total, 256);
+  a.per_ring = cdiv(a.ring_total, 256);
+  a.first_map = a.first_ring + ndir * a.per_ring;
+  a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
+  hipLaunchKernelGGL(prep_f32_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
+}
+hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, hipStream_t s) {
+  PrepF32Args a = {};
+  a.W = (const float*)W; a.Wout = Wf; a.n = p.n; a.nk = p.nkc; a.w_total = (long)p.ndir * cdiv(p.n, 8) * 2 * p.nkc * 64;
+  for (int d = 0; d < p.ndir; ++d) { a.ring0[d] = p.d[d].ring0; a.ring1[d] = p.d[d].ring1; }
+  a.ring_total = (long)cdiv(p.B, 16) * p.nkc * 64;
+  return prep_f32(a, z, p.ndir, fm, s);
+}
+hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s) {
+  PrepF32Args a = {};
+  a.W = (const float*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 16); a.nct = bwd_f32_nct(n); a.w_total = (long)ndir * a.nk * 4 * a.nct * 64;
+  a.backward = 1;
+  return prep_f32(a, z, ndir, fm, s);
 }
 // (the rings must hold zeros)
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s) {

@@ -160,30 +160,9 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(BwdArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // packing
-// forward: chunk index = ((dir*ntiles + tile)*2 + ct)*nkc + kc)*64 + lane ; column ct*16 + (lane%16) of the
-// work-group's 32 columns is gate q = col/8, unit tile*8 + col%8.
 template <typename T>
 __global__ void pack_wh_fwd_kernel(const T* W, uint4* out, int n, int nkc, long total) {
-  constexpr int E = Store<T>::kPerChunk, KC = 4 * E;
-  long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  int lane = idx & 63;
-  long rest = idx >> 6;
-  int kc = rest % nkc; rest /= nkc;
-  int ct = rest & 1; rest >>= 1;
-  int ntiles = (n + 7) / 8;
-  int tile = rest % ntiles;
-  int dir = rest / ntiles;
-  int col = ct * 16 + (lane & 15), g = lane >> 4;
-  int q = col >> 3, unit = tile * 8 + (col & 7);
-  const T* Wd = W + (long)dir * n * 4 * n;
-  T v[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    int k = kc * KC + g * E + e;
-    v[e] = (k < n && unit < n) ? Wd[(long)k * 4 * n + q * n + unit] : (T)0.f;
-  }
-  out[idx] = *(uint4*)v;
+  pack_wh_fwd_body((long)blockIdx.x * blockDim.x + threadIdx.x, W, out, n, nkc, total);
 }
 // backward: chunk index = ((dir*ntiles + tile)*nkc + kc)*64 + lane ; column lane%16 = unit tile*16 + c,
 // k runs over the 4n gate columns: element = W_h[unit][k]

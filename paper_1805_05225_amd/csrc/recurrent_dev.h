@@ -122,5 +122,31 @@ __device__ __forceinline__ void lstm_cell_grad(float gi, float gf, float gg, flo
   dz[3] = dh * tc * go * (1.f - go);
 }
 
+// W_h for the per-step and the float single-launch forward kernels.
+// forward: chunk index = ((dir*ntiles + tile)*2 + ct)*nkc + kc)*64 + lane ; column ct*16 + (lane%16) of the
+// work-group's 32 columns is gate q = col/8, unit tile*8 + col%8.
+template <typename T>
+__device__ __forceinline__ void pack_wh_fwd_body(long idx, const T* W, uint4* out, int n, int nkc, long total) {
+  constexpr int E = Store<T>::kPerChunk, KC = 4 * E;
+  if (idx >= total) return;
+  int lane = idx & 63;
+  long rest = idx >> 6;
+  int kc = rest % nkc; rest /= nkc;
+  int ct = rest & 1; rest >>= 1;
+  int ntiles = (n + 7) / 8;
+  int tile = rest % ntiles;
+  int dir = rest / ntiles;
+  int col = ct * 16 + (lane & 15), g = lane >> 4;
+  int q = col >> 3, unit = tile * 8 + (col & 7);
+  const T* Wd = W + (long)dir * n * 4 * n;
+  T v[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    int k = kc * KC + g * E + e;
+    v[e] = (k < n && unit < n) ? Wd[(long)k * 4 * n + q * n + unit] : (T)0.f;
+  }
+  out[idx] = *(uint4*)v;
+}
+
 }  // namespace
 }  // namespace lstm
