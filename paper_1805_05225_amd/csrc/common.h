@@ -295,10 +295,6 @@ inline size_t bwdp_ring_bytes(int B, int n) {                                   
 }
 // (launch_prep_fwd_ll: W_h in ring order; ring slot 0 = zeros carrying the tag of step 0, ring slot 1 cleared.  The initial state does
 // not travel through the ring: its product with W_h is added to the pre-activations of every row's first frame instead, over operands from here.)
-// out[dir][b][0..ld) = h0[dir][b][0..n) in the storage type, then zeros; rows[dir][b] = t0 * B + b, t0 the row's first frame (reverse: len - 1).
-hipError_t launch_h0_rows(const float* h0, bool bf16, void* out, int ld, int* rows, const int* lens, int T, int B, int n, int ndir, int rev0, int rev1,
-                          hipStream_t s);
-
 // Wide layers, bfloat16 (loop_block.hip): 1024 < n <= 2048, W_h in blocks over the device; one direction per launch.  h0 / c0 / hT / cT / cs / hprev,
 // dhT / dcT / dh0 / dc0 may be NULL.  ring: loop_block_ring_bytes (_bwd) bytes; xcc: a word per block; both cleared by the launch, as is *sync.
 struct BlockFwdArgs {
@@ -411,9 +407,17 @@ struct ZeroRegions {
 hipError_t launch_fill_zero_many(const ZeroRegions& r, hipStream_t s);
 // The set-up of a bfloat16 single-launch loop in one launch: the fills of `z`, W_h in the kernel's order (or fetched), (forward) the initial
 // ring, and the frame map of launch_frame_map if fm.fidx is not NULL.
+// Copies that ride in a set-up launch (each took a launch of its own, 5 us, most of it the gap): x in padded rows, as launch_pad_rows (x NULL: none), and the initial state as the left operand of
+// its product with W_h (h0 NULL: none): out[dir][b][0..ld) = h0[dir][b][0..n) rounded to the storage type, as the recurrence would feed it, then zeros; row[dir][b] = t0 * B + b,
+// t0 the row's first frame (reverse: len - 1; a row without frames: one that nobody reads).
+struct SetUpCopies {
+  const void* x; void* xpad; long x_rows; int x_cols, x_ld;
+  const float* h0; void* out; int* row; int ld, rev0, rev1;
+  const int* lens; int T, B, n, ndir;
+};
 struct FrameMapArgs { const int* lens; int T, B; int* fidx; int* count; };
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
-                              int nrt, const FrameMapArgs& fm, const PackRows& rows, const GemmArgs* zx, hipStream_t s);
+                              int nrt, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, const GemmArgs* zx, hipStream_t s);
 // Wf NULL: W_h is not packed but fetched into the last-level cache (the loop reads it as it lies in memory: PFwdArgs::w_rows).
 // zx (few_zx_ok; neither a frame map nor PackRows): the input projection of all frames in the same launch.  It pays for what the compute units take: a
 // work-group (32 units, 64 frames) walks all of K, so K times the rounds of 256 of them, and a round of its own costs, too.  A layer's forward pass, us, the
@@ -425,9 +429,9 @@ constexpr int kFewZxRows = 512;
 constexpr long kFewZxWalk = 5120;
 bool few_zx_ok(const GemmArgs& g);
 // The same for the float loops (forward: `p` as launch_persist_fwd_f32 takes it).
-hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, hipStream_t s);
-hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s);
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s);
+hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s);
+hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s);
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]
 constexpr int kColsumSlices = 64;

@@ -559,22 +559,8 @@ __global__ __launch_bounds__(256) void frame_map_kernel(const int* lens, int T, 
   frame_map_body(blockIdx.x, lens, T, B, fidx, count);
 }
 
-// dst[r][c] = src[r][c] for c < C, zero for C <= c < ldd (rows made whole 16 bytes; ldd a multiple of 8).  16 bytes a thread, read at any element
-// (9456 rows of 1802 elements: 40 us with an element a thread, 12.8).
 __global__ void pad_rows_kernel(const uint16_t* src, uint4* dst, long R, int C, int ldd8) {
-  struct __attribute__((packed, aligned(2))) Chunk { uint16_t v[8]; };
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= R * ldd8) return;
-  const long rr = idx / ldd8;
-  const int c0 = (int)(idx - rr * ldd8) * 8;
-  const uint16_t* p = src + rr * C + c0;
-  Chunk o = {};
-  if (c0 + 8 <= C) o = *(const Chunk*)p;
-  else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) if (c0 + e < C) o.v[e] = p[e];
-  }
-  dst[idx] = __builtin_bit_cast(uint4, o);
+  pad_rows_body((long)blockIdx.x * blockDim.x + threadIdx.x, src, dst, R, C, ldd8);
 }
 
 }  // namespace

@@ -353,15 +353,21 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     return g;
   };
   bool projected = false;                // the set-up launch did it
+  bool x_padded = false;                 // likewise
+  const int ldx = !p.bf16 ? p.n_in8 : !p.fast_gemm ? p.n_in : p.zx_nn ? p.n_in8 : p.n_in_pad;      // (bfloat16: rows of x are not 16-byte aligned, or narrow: zero-padded copy)
+  // float storage: the product over padded rows, if the float kernel takes it
+  auto padded_float = [&](GemmArgs g) {
+    g.A = ws + p.ws_xpad; g.K = p.n_in8; g.lda = p.n_in8; g.k_phys_rows = p.n_in;
+    return g;
+  };
   auto project = [&]() -> int {
     if (projected) return LSTM_OK;
     GemmArgs g = projection();
     {
       Phase ph(LSTM_PHASE_GEMM_ZX, 1, s);
       if (p.fast_gemm) {
-        const int ldx = p.zx_nn ? p.n_in8 : p.n_in_pad;
-        if (ldx != p.n_in) {             // rows of x are not 16-byte aligned, or narrow: zero-padded copy
-          HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), p.n_in, ldx, s));
+        if (ldx != p.n_in) {
+          if (!x_padded) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), p.n_in, ldx, s));
           g.A = ws + p.ws_xpad;
         }
         g.K = ldx; g.lda = ldx;
@@ -380,10 +386,9 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       } else if (!p.bf16) {              // float storage: the same padding, the same selection of real frames
         g.parts = (float*)(ws + p.ws_parts); g.parts_bytes = p.parts_bytes;
         if (p.n_in8 != p.n_in) {
-          GemmArgs gp = g;
-          gp.A = ws + p.ws_xpad; gp.K = p.n_in8; gp.lda = p.n_in8; gp.k_phys_rows = p.n_in;
+          const GemmArgs gp = padded_float(g);
           if (gemm_float_ok(gp)) {
-            HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), 2 * p.n_in, 2 * p.n_in8, s));
+            if (!x_padded) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)(T * B), 2 * p.n_in, 2 * p.n_in8, s));
             g = gp;
           }
         }
@@ -481,10 +486,9 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   // The initial state does not travel through the exchange rings (what does must keep |h| <= 1): its product with W_h goes into the
   // pre-activations of every row's first frame, and the kernels start from zeros in the ring.  (B rows, but W_h is read once
   // for all of them: a kernel with a thread per column and row took 270 us for 32 rows of 1024 units.)
-  auto h0_term = [&](const PFwdArgs& pa) -> int {
-    Phase ph(LSTM_PHASE_PREP, 1 + p.D, s);
+  auto h0_term = [&]() -> int {            // (its operands by the set-up launch)
+    Phase ph(LSTM_PHASE_PREP, p.D, s);
     int* rows = (int*)(ws + p.ws_h0rows);
-    HIPCHK(launch_h0_rows((const float*)h0, p.bf16, ws + p.ws_h0, (int)p.ldh, rows, seq_lens, p.T, p.B, p.n, p.D, pa.d[0].rev, pa.d[D - 1].rev, s));
     for (size_t d = 0; d < D; ++d) {
       GemmArgs g = {};
       g.A = ws + p.ws_h0 + d * B * p.ldh * p.esz; g.B = (const char*)W_h + d * n * 4 * n * p.esz; g.C = gates + d * gates_stride;
@@ -532,6 +536,17 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   }
   const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && persist_fwd_f32_fits(pa) &&
                         persist_f32_pays(p.T, p.B, p.n, p.D, seq_lens != nullptr, pa.plain_launch, false);
+  const bool single = use_ll ? persist_fwd_fits(pa) : use_ll32;
+  SetUpCopies copies = {};
+  if (T > 0 && !projected && ldx != p.n_in && (p.bf16 || gemm_float_ok(padded_float(zx)))) {
+    const int words = p.bf16 ? 1 : 2;    // (16-bit ones)
+    copies.x = x; copies.xpad = ws + p.ws_xpad; copies.x_rows = (long)(T * B); copies.x_cols = words * p.n_in; copies.x_ld = words * ldx;
+  }
+  if (T > 0 && single && h0) {
+    copies.h0 = (const float*)h0; copies.out = ws + p.ws_h0; copies.row = (int*)(ws + p.ws_h0rows); copies.ld = (int)p.ldh;
+    copies.rev0 = pa.d[0].rev; copies.rev1 = pa.d[D - 1].rev;
+    copies.lens = seq_lens; copies.T = p.T; copies.B = p.B; copies.n = p.n; copies.ndir = p.D;
+  }
   {
     Phase ph(projected ? LSTM_PHASE_GEMM_ZX : LSTM_PHASE_PREP, projected ? 1 : 5, s);
     ZeroRegions z;
@@ -546,23 +561,23 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         frames_mapped = true;
       }
       HIPCHK(launch_prep_fwd_ll(z, W_h, w_rows ? nullptr : (uint4*)(ws + p.ws_Wf), p.n, p.nkc_ll_f, p.D, paired, (uint4*)(ws + p.ws_hfrag0), (uint4*)(ws + p.ws_hfrag1),
-                                p.nrt, fm, rows, projected ? &zx : nullptr, s));
+                                p.nrt, fm, rows, copies, projected ? &zx : nullptr, s));
     } else if (use_ll32) {
       FrameMapArgs fm = {};
       if (seq_lens) {
         fm = {seq_lens, p.T, p.B, (int*)(ws + p.ws_fidx), (int*)(ws + p.ws_count)};
         frames_mapped = true;
       }
-      HIPCHK(launch_prep_fwd_f32(z, W_h, ws + p.ws_Wf, pa, fm, s));
+      HIPCHK(launch_prep_fwd_f32(z, W_h, ws + p.ws_Wf, pa, fm, copies, s));
     } else HIPCHK(launch_fill_zero_many(z, s));
+    x_padded = copies.x && (use_ll || use_ll32);
   }
-  const bool single = use_ll ? persist_fwd_fits(pa) : use_ll32;
   if (T > 0 && !single && (rc = pack_w())) return rc;
   if (!single && (rc = state_in())) return rc;
   if (T > 0) {
     if ((rc = project())) return rc;
     if (single) {
-      if (h0 && (rc = h0_term(pa))) return rc;
+      if (h0 && (rc = h0_term())) return rc;
       // The fill behind rows one behind the other gives padded frames of a reversed direction the state that the call began with, and by then the
       // loop has stored cT: a state in place (cT over c0) is read from a copy.
       const float* c0_fill = (const float*)c0;
@@ -669,7 +684,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   const int TB = (int)(T * B);
   const bool compact = (p.fast_gemm || !p.bf16) && seq_lens && TB > 0;
   char* DZ = ws + p.ws_DZ;
-  bool dx_cleared = false, frames_mapped = false;      // done by a set-up launch of the loop
+  bool dx_cleared = false, frames_mapped = false, x_padded = false;      // done by a set-up launch of the loop
   int db_slices = 0;                                   // slices of the bias gradient that the loop leaves in ws_colsum (0: none)
   TinyGroup tiny = {};
   if (p.dw_tiny) tiny = tiny_bwd(p, x, W_x, rs + p.res_hprev, DZ, seq_lens, dx, dW_x, dW_h, acc);
@@ -733,8 +748,14 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           z.add(dx, (size_t)TB * n_in * p.esz);
           dx_cleared = true;
         }
-        if (use_ll32) HIPCHK(launch_prep_bwd_f32(z, W_h, ws + p.ws_Wb, p.n, p.D, fm, s));
-        else HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || persist_bwd_rows(p.B, p.n, p.D) == 8, fm, rows, s));
+        SetUpCopies copies = {};
+        if (p.n_in8 != p.n_in && (p.fast_gemm || !p.bf16)) {               // x in rows of whole 16 bytes, for dW_x
+          const int words = p.bf16 ? 1 : 2;
+          copies.x = x; copies.xpad = ws + p.ws_xpad; copies.x_rows = TB; copies.x_cols = words * p.n_in; copies.x_ld = words * p.n_in8;
+          x_padded = true;
+        }
+        if (use_ll32) HIPCHK(launch_prep_bwd_f32(z, W_h, ws + p.ws_Wb, p.n, p.D, fm, copies, s));
+        else HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || persist_bwd_rows(p.B, p.n, p.D) == 8, fm, rows, copies, s));
       } else HIPCHK(launch_fill_zero_many(z, s));
     }
     if (!use_ll && !use_ll32) {
@@ -907,7 +928,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       const bool pair = gx.parts && gh.parts && gemm_tn_ranges(gx) == 1 && gemm_tn_ranges(gh) == 1;    // both in few tiles
       {
         Phase ph({{LSTM_PHASE_GEMM_DWX, (double)p.n_in}, {LSTM_PHASE_GEMM_DWH, pair ? (double)n : 0.0}}, 1, s);
-        if (pad_x) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
+        if (pad_x && !x_padded) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
         if (pair) {
           HIPCHK(launch_gemm_tile_pair(gx, gh, s));
           return LSTM_OK;
@@ -932,7 +953,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           GemmArgs gp = g;
           gp.A = ws + p.ws_xpad; gp.lda = p.n_in8;
           if (gemm_float_ok(gp)) {
-            HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, 2 * p.n_in, 2 * p.n_in8, s));
+            if (!x_padded) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, 2 * p.n_in, 2 * p.n_in8, s));
             g = gp;
           }
         }

@@ -3085,8 +3085,28 @@ struct PrepArgs {
   uint4* ring0; uint4* ring1; long ring_total;
   const int* lens; int T, B; int* fidx; int* count;     // frame map (fidx == NULL: none)
   PackRows rows;                                          // rows one behind the other: one more block (slots > 0)
-  int first_pack, first_ring, first_map, backward, paired;
+  SetUpCopies copies;
+  int first_pack, first_ring, first_pad, first_h0, first_map, backward, paired;
 };
+// Blocks of the copies: [first_pad, first_h0) x, [first_h0, first_map) the initial state.
+template <typename TW>
+__device__ __forceinline__ void copies_body(const SetUpCopies& c, int block, int pad_blocks, int tid) {
+  if (block < pad_blocks) {
+    pad_rows_body((long)block * 256 + tid, (const uint16_t*)c.x, (uint4*)c.xpad, c.x_rows, c.x_cols, c.x_ld / 8);
+    return;
+  }
+  const long idx = (long)(block - pad_blocks) * 256 + tid;
+  if (idx >= (long)c.ndir * c.B * c.ld) return;
+  const long r = idx / c.ld;
+  const int k = (int)(idx - r * c.ld), dir = r >= c.B, b = (int)r - dir * c.B;
+  if (k == 0) {
+    const int L = clamp_len(c.lens, b, c.T);
+    c.row[r] = ((dir == 0 ? c.rev0 : c.rev1) && L > 0 ? L - 1 : 0) * c.B + b;
+  }
+  const float v = k < c.n ? c.h0[r * c.n + k] : 0.f;
+  if constexpr (sizeof(TW) == 2) ((uint16_t*)c.out)[idx] = f2bf_bits(v);
+  else ((float*)c.out)[idx] = v;
+}
 constexpr int kTouch = 4;
 __device__ __forceinline__ void set_up_body(const PrepArgs& a, int bid, int tid) {       // (256 threads, no frame map)
   if (bid < a.first_pack) {
@@ -3105,8 +3125,10 @@ __device__ __forceinline__ void set_up_body(const PrepArgs& a, int bid, int tid)
     const int paired = a.rows.slots > 0 ? rows_pay(a.rows) : a.paired;
     if (a.backward) pack_wh_bwdp_body(idx, a.W, a.Wout, a.n, a.nk, a.nct, paired, a.w_total);
     else pack_wh_fwd_ll_body(idx, a.W, a.Wout, a.n, a.nk, paired, a.w_total);
-  } else if (bid < a.first_map) {
+  } else if (bid < a.first_pad) {
     pack_state_ll_body((long)(bid - a.first_ring) * 256 + tid, a.ring0, a.ring1, a.ring_total);
+  } else if (bid < a.first_map) {
+    copies_body<bf16_t>(a.copies, bid - a.first_pad, a.first_h0 - a.first_pad, tid);
   }
 }
 __global__ __launch_bounds__(256) void prep_ll_kernel(PrepArgs a) {
@@ -3226,7 +3248,8 @@ struct PrepF32Args {
   const float* W; void* Wout; int n, nk, nct; long w_total;     // nk: nkc (forward) / unit tiles (backward)
   uint4* ring0[2]; uint4* ring1[2]; long ring_total;            // forward: 16-byte units of a direction's ring
   const int* lens; int T, B; int* fidx; int* count;             // frame map (fidx == NULL: none)
-  int first_pack, first_ring, first_map, per_ring, backward;
+  SetUpCopies copies;
+  int first_pack, first_ring, first_pad, first_h0, first_map, per_ring, backward;
 };
 // W_h^T for the float partial-sum backward kernel: float index
 // ((((dir*ntile + J)*4 + wave)*NCT + ci)*16 + s)*64 + lane holds W_h[unit (wave + 4 ci)*16 + lane%16][gate column
@@ -3265,33 +3288,19 @@ __global__ __launch_bounds__(256) void prep_f32_kernel(PrepF32Args a) {
     const long idx = (long)(bid - a.first_pack) * 256 + tid;
     if (a.backward) pack_wh_bwd_f32p_body(idx, a.W, (float4*)a.Wout, a.n, a.nk, a.nct, a.w_total);
     else pack_wh_fwd_body(idx, a.W, (uint4*)a.Wout, a.n, a.nk, a.w_total);
-  } else if (bid < a.first_map) {                               // before the first step: slot 0 holds zeros that carry the tag of step 0 in every unit, slot 1 is cleared
+  } else if (bid < a.first_pad) {                               // before the first step: slot 0 holds zeros that carry the tag of step 0 in every unit, slot 1 is cleared
     const int d = (bid - a.first_ring) / a.per_ring;
     const long idx = (long)(bid - a.first_ring - d * a.per_ring) * 256 + tid;
     if (idx >= a.ring_total) return;
     const unsigned t = ll_fwd_tag(0u) << 30;
     a.ring0[d][idx] = make_uint4(0u, t, 0u, t);
     a.ring1[d][idx] = make_uint4(0u, 0u, 0u, 0u);
+  } else if (bid < a.first_map) {
+    copies_body<float>(a.copies, bid - a.first_pad, a.first_h0 - a.first_pad, tid);
   } else {
     frame_map_body(bid - a.first_map, a.lens, a.T, a.B, a.fidx, a.count);
   }
 }
-// The initial state as the left operand of its product with W_h: rows of `ld` elements, rounded to the storage type as the recurrence
-// would feed it and padded with zeros; rows[dir][b] = the frame and row whose pre-activations it goes into (a row without frames: one that nobody reads).
-template <typename TW>
-__global__ __launch_bounds__(256) void h0_rows_kernel(const float* h0, TW* out, int ld, int* rows, const int* lens, int T, int B, int n, int rev0, int rev1) {
-  const int k = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y, dir = blockIdx.z;
-  if (k == 0) {
-    const int L = clamp_len(lens, b, T);
-    rows[dir * B + b] = ((dir == 0 ? rev0 : rev1) && L > 0 ? L - 1 : 0) * B + b;
-  }
-  if (k >= ld) return;
-  const float v = k < n ? h0[((long)dir * B + b) * n + k] : 0.f;
-  const long o = ((long)dir * B + b) * ld + k;
-  if constexpr (sizeof(TW) == 2) ((uint16_t*)out)[o] = f2bf_bits(v);
-  else out[o] = v;
-}
-
 std::mutex g_capacity_mu;
 std::map<std::pair<int, const void*>, int> g_capacity;    // (device, kernel) -> work-groups of the kernel that device holds at once
 
@@ -3445,8 +3454,10 @@ hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s) {
   const int rows = persist_bwd_rows(a.B, a.n, a.ndir);
   return coop_slabs(rows == 16 ? bwd16_for(a.n) : bwd8_for(a.n), cdiv(a.n, 32), rows, a, s);
 }
+static int pad_blocks(const SetUpCopies& c) { return c.x ? cdiv(c.x_rows * (c.x_ld / 8), 256) : 0; }
+static int h0_blocks(const SetUpCopies& c) { return c.h0 ? cdiv((long)c.ndir * c.B * c.ld, 256) : 0; }
 hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, int n, int nkc, int ndir, bool paired, uint4* ring0, uint4* ring1,
-                              int nrt, const FrameMapArgs& fm, const PackRows& rows, const GemmArgs* zx, hipStream_t s) {
+                              int nrt, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, const GemmArgs* zx, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
   a.z = z; a.W = (const bf16_t*)W; a.Wout = Wf; a.n = n; a.paired = paired; a.nk = nkc;
@@ -3454,7 +3465,10 @@ hipError_t launch_prep_fwd_ll(const ZeroRegions& z, const void* W, uint4* Wf, in
   a.ring0 = ring0; a.ring1 = ring1; a.ring_total = (long)ndir * nrt * nkc * 64 * 2;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + (int)cdiv(a.w_total, Wf ? 256 : 256 * 16 * kTouch);
-  a.first_map = a.first_ring + cdiv(a.ring_total, 256);
+  a.copies = copies;
+  a.first_pad = a.first_ring + cdiv(a.ring_total, 256);
+  a.first_h0 = a.first_pad + pad_blocks(copies);
+  a.first_map = a.first_h0 + h0_blocks(copies);
   a.backward = 0;
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
   a.rows = rows;
@@ -3476,13 +3490,15 @@ bool few_zx_ok(const GemmArgs& g) {
   return g.in_bf16 && !g.out_bf16 && g.M > 0 && g.M <= kFewZxRows && rounds * g.K <= kFewZxWalk && rounds <= (g.K % 8 == 0 ? 5 : 6) &&
          g.K % 2 == 0 && g.N % 4 == 0 && g.lda == g.K && g.ldb == g.N && g.ldc == g.N && g.sBz == (long)g.K * g.N && g.sCz % 4 == 0 && (long)(g.K + 1024) * g.N * 2 < 0x7ff00000L;
 }
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, hipStream_t s) {
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
   a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.nct = bwdp_nct(n); a.w_total = (long)ndir * a.nk * 4 * 4 * a.nct * 64;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
-  a.first_map = a.first_ring;
+  a.copies = copies;
+  a.first_pad = a.first_ring;
+  a.first_h0 = a.first_map = a.first_pad + pad_blocks(copies);
   a.backward = 1; a.paired = paired;
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
   a.rows = rows;
@@ -3537,29 +3553,32 @@ bool persist_bwd_f32_fits(const PBwdArgs& a) {
   if ((long)cdiv(a.B, 16) * ntile * ntile * 1024 >= 0x7ff00000L) return false;
   return ntile * a.ndir <= capacity(bwd_f32_for(a.n));
 }
-static hipError_t prep_f32(PrepF32Args a, const ZeroRegions& z, int ndir, const FrameMapArgs& fm, hipStream_t s) {
+static hipError_t prep_f32(PrepF32Args a, const ZeroRegions& z, int ndir, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   a.z = z;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.per_ring = cdiv(a.ring_total, 256);
-  a.first_map = a.first_ring + ndir * a.per_ring;
+  a.copies = copies;
+  a.first_pad = a.first_ring + ndir * a.per_ring;
+  a.first_h0 = a.first_pad + pad_blocks(copies);
+  a.first_map = a.first_h0 + h0_blocks(copies);
   a.lens = fm.lens; a.T = fm.T; a.B = fm.B; a.fidx = fm.fidx; a.count = fm.count;
   hipLaunchKernelGGL(prep_f32_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, hipStream_t s) {
+hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s) {
   PrepF32Args a = {};
   a.W = (const float*)W; a.Wout = Wf; a.n = p.n; a.nk = p.nkc; a.w_total = (long)p.ndir * cdiv(p.n, 8) * 2 * p.nkc * 64;
   for (int d = 0; d < p.ndir; ++d) { a.ring0[d] = p.d[d].ring0; a.ring1[d] = p.d[d].ring1; }
   a.ring_total = (long)cdiv(p.B, 16) * p.nkc * 64;
-  return prep_f32(a, z, p.ndir, fm, s);
+  return prep_f32(a, z, p.ndir, fm, copies, s);
 }
-hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, hipStream_t s) {
+hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s) {
   PrepF32Args a = {};
   a.W = (const float*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 16); a.nct = bwd_f32_nct(n); a.w_total = (long)ndir * a.nk * 4 * a.nct * 64;
   a.backward = 1;
-  return prep_f32(a, z, ndir, fm, s);
+  return prep_f32(a, z, ndir, fm, copies, s);
 }
 // (the rings must hold zeros)
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s) {
@@ -3567,12 +3586,4 @@ hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s) {
   const auto kernel = bwd_f32_for(a.n);
   return coop_slabs(kernel, cdiv(a.n, 16), f32_rows_per_group(kernel, cdiv(a.n, 16), a.B, a.ndir), a, s);
 }
-hipError_t launch_h0_rows(const float* h0, bool bf16, void* out, int ld, int* rows, const int* lens, int T, int B, int n, int ndir, int rev0, int rev1,
-                          hipStream_t s) {
-  const dim3 grid(cdiv(ld, 256), B, ndir);
-  if (bf16) hipLaunchKernelGGL(h0_rows_kernel<bf16_t>, grid, dim3(256), 0, s, h0, (bf16_t*)out, ld, rows, lens, T, B, n, rev0, rev1);
-  else hipLaunchKernelGGL(h0_rows_kernel<float>, grid, dim3(256), 0, s, h0, (float*)out, ld, rows, lens, T, B, n, rev0, rev1);
-  return hipGetLastError();
-}
-
 }  // namespace lstm

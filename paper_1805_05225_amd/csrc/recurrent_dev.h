@@ -12,6 +12,22 @@ __device__ __forceinline__ f32x16 mma_last4(uint2 a, uint2 b, f32x16 c) {
   typedef __attribute__((ext_vector_type(4))) short s16x4;
   return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
 }
+// dst[r][c] = src[r][c] for c < C, zero for C <= c < 8 ldd8 (rows made whole 16 bytes).  16 bytes a thread, read at any element
+// (9456 rows of 1802 elements: 40 us with an element a thread, 12.8).
+__device__ __forceinline__ void pad_rows_body(long idx, const uint16_t* src, uint4* dst, long R, int C, int ldd8) {
+  struct __attribute__((packed, aligned(2))) Chunk { uint16_t v[8]; };
+  if (idx >= R * ldd8) return;
+  const long rr = idx / ldd8;
+  const int c0 = (int)(idx - rr * ldd8) * 8;
+  const uint16_t* p = src + rr * C + c0;
+  Chunk o = {};
+  if (c0 + 8 <= C) o = *(const Chunk*)p;
+  else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) if (c0 + e < C) o.v[e] = p[e];
+  }
+  dst[idx] = __builtin_bit_cast(uint4, o);
+}
 // Block `block` (256 threads) of those that clear the regions.
 __device__ __forceinline__ void fill_zero_body(const ZeroRegions& r, int block, int tid) {
   int k = 0;
