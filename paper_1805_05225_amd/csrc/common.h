@@ -280,7 +280,7 @@ hipError_t launch_persist_bwd(const PBwdArgs& a, hipStream_t s);
 // direction), rings of bwd_f32_ring_bytes per direction and slot, zero-filled; gates, cs, dy, DZ float.
 bool persist_bwd_f32_fits(const PBwdArgs& a);
 hipError_t launch_persist_bwd_f32(const PBwdArgs& a, hipStream_t s);
-inline int bwd_f32_nct(int n) { return n <= 256 ? 4 : n <= 512 ? 8 : 16; }      // output column tiles (of 16) per wavefront
+inline int bwd_f32_nct(int n) { return n <= 256 ? 4 : (n + 127) / 128 * 2; }      // output column tiles (of 16) per wavefront
 inline size_t bwd_f32_wh_bytes(int n) { return (size_t)((n + 15) / 16) * 4 * bwd_f32_nct(n) * 16 * 64 * 4; }
 inline size_t bwd_f32_ring_bytes(int B, int n) {
   const size_t tiles = (size_t)((n + 15) / 16), rts = 2 * (size_t)(((B > 0 ? B : 1) + 31) / 32);

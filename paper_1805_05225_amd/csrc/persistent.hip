@@ -3505,10 +3505,31 @@ hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, in
   hipLaunchKernelGGL(prep_ll_kernel, dim3(a.first_map + (fm.fidx ? cdiv(fm.T, 4) : 0) + (rows.slots > 0 ? 1 : 0)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-// The float kernels' form for n units, as above (50 steps, both directions: n = 500, 64 rows, forward 519 -> 239 us, backward 767 -> 253; n = 256,
-// 16 rows, 332 -> 155 and 329 -> 149, with the exchange inside an XCD).
-FwdKernel fwd_f32_for(int n) { return n <= 256 ? persist_fwd_f32_kernel<4> : n <= 512 ? persist_fwd_f32_kernel<8> : persist_fwd_f32_kernel<16>; }
-BwdKernel bwd_f32_for(int n) { return bwd_f32_nct(n) == 4 ? persist_bwd_f32_kernel<4> : bwd_f32_nct(n) == 8 ? persist_bwd_f32_kernel<8> : persist_bwd_f32_kernel<16>; }
+// The float kernels' form for n units: as many chunks of h (forward) and column tiles (backward) to a wavefront as n needs, in twos, since a form's products, ring loads and
+// published blocks are the same whatever n it is used for.  us a step, forward and backward, 27 rows, both directions, in the next power of two's form / its own: n = 300 2.61 3.73 / 2.30
+// 3.22, 563 4.32 5.61 / 3.37 4.37, 700 4.44 5.67 / 3.75 4.97, 850 4.62 6.02 / 4.30 5.93; 64 rows of 563 7.50 8.39 / 5.62 7.65.  (Up to 512 the exchange is inside an XCD.)
+FwdKernel fwd_f32_for(int n) {
+  switch (cdiv(n, 128)) {
+    case 0: case 1: case 2: return persist_fwd_f32_kernel<4>;
+    case 3: return persist_fwd_f32_kernel<6>;
+    case 4: return persist_fwd_f32_kernel<8>;
+    case 5: return persist_fwd_f32_kernel<10>;
+    case 6: return persist_fwd_f32_kernel<12>;
+    case 7: return persist_fwd_f32_kernel<14>;
+    default: return persist_fwd_f32_kernel<16>;
+  }
+}
+BwdKernel bwd_f32_for(int n) {
+  switch (bwd_f32_nct(n)) {
+    case 4: return persist_bwd_f32_kernel<4>;
+    case 6: return persist_bwd_f32_kernel<6>;
+    case 8: return persist_bwd_f32_kernel<8>;
+    case 10: return persist_bwd_f32_kernel<10>;
+    case 12: return persist_bwd_f32_kernel<12>;
+    case 14: return persist_bwd_f32_kernel<14>;
+    default: return persist_bwd_f32_kernel<16>;
+  }
+}
 // A work-group is one row tile where the device holds all of them so, else two.
 template <typename K>
 int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntile * cdiv(B, 16) * ndir <= capacity(kernel) ? 16 : 32; }
@@ -3519,19 +3540,19 @@ int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntil
 // it; always the loops was up to 2.8 times the other.  The loops' side has been measured again since their products are bfloat16 parts (4 and 100 steps of 11
 // shapes): of 396 shapes of 2 to 24 steps the choice is within 5 % of the per-step kernels or faster in 95 %, never 1.16 times them. Their set-up is one launch since: of 480
 // shapes of 2 to 14 steps and 2 to 64 rows the choice is within 5 % of the faster side in all but 9, at most 1.25 times it (4 steps of 2 rows, n = 700, both directions, ordinary launches: 51 and
-// 92 us, forward and backward, per step 85 and 156).  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
+// 92 us, forward and backward, per step 85 and 156).  A step's time goes with the form, cdiv(n, 128).  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward) {
-  const int form = n <= 256 ? 0 : n <= 512 ? 1 : 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
+  const int form = std::min(std::max(cdiv(n, 128), 2), 8) - 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
   const bool one = (long)ntile * cdiv(B, 16) * ndir <= cap, pair = !one && B > 16;
   const int launches = one ? 1 : cdiv(cdiv(B, 32), std::max(1, cap / (ntile * ndir)));
   const double w = (double)n * n / (1024.0 * 1024.0) * ndir, nr = (double)n * ndir * B * 1e-5, nnr = nr * n * 1e-3, part = lens && pair ? 0.8 : 1.0;
   double here, there;
   if (backward) {
-    const double step[2][3] = {{2.8, 4.3, 7.2}, {7.2, 9.3, 17.4}};
+    const double step[2][7] = {{2.8, 3.7, 4.3, 5.7, 6.3, 6.8, 7.2}, {7.2, 8.3, 9.3, 16.2, 16.7, 17.4, 17.4}};
     here = 14.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
     there = 58.3 + 16.0 * w + T * std::max(4.25 + 17.1e-3 * n + 6.6 * nr + 10.4 * nnr, 22.0 * nnr);
   } else {
-    const double step[2][3] = {{1.9, 2.65, 4.25}, {4.2, 6.2, 9.2}};
+    const double step[2][7] = {{1.9, 2.4, 2.65, 3.25, 3.6, 4.0, 4.25}, {4.2, 5.5, 6.2, 7.3, 8.2, 8.8, 9.2}};
     here = -0.5 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
     there = 27.9 + 7.8 * w + T * std::max(3.8 + 6.15e-3 * n + 4.15 * nr + 4.9 * nnr, 10.9 * nnr);
   }

@@ -268,6 +268,15 @@ def test_float_loops_in_parts(T, B, n, what):
         assert err.max() < 5e-5, (name, err.max())
 
 
+@pytest.mark.parametrize("B,n,bidir", [(9, 257, True), (190, 384, True), (12, 640, False), (64, 513, True), (7, 641, True), (70, 768, True), (10, 896, False), (64, 770, True),
+                                       (5, 897, False)])
+def test_float_loop_forms(B, n, bidir):
+    """As many chunks and column tiles as the width needs, in twos: the first and last width of a form, slabs of one and of two row tiles."""
+    _layer(9, B, 24, n, bidir, "f32")
+    for what in ("huge_W", "huge_dy"):
+        test_float_loops_in_parts(24, B, n, what)
+
+
 @pytest.mark.parametrize("dy_exp,w_exp", [(-118, 60), (60, -120)])
 @pytest.mark.parametrize("T,B,n", [(24, 9, 200), (24, 140, 500), (24, 12, 1024)])
 def test_float_backward_loop_small_operands(T, B, n, dy_exp, w_exp):
