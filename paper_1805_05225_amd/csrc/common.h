@@ -288,7 +288,8 @@ inline size_t bwd_f32_ring_bytes(int B, int n) {
 }
 // output column tiles (of 16) per wavefront of the bfloat16 backward kernel: four wavefronts cover n
 inline int bwdp_nct(int n) { return n <= 256 ? 4 : n <= 512 ? 8 : 16; }
-inline size_t bwdp_wh_bytes(int n) { return (size_t)((n + 31) / 32) * 16384 * bwdp_nct(n); }                // per direction
+inline int bwdp8_nct(int n) { return n <= 512 ? bwdp_nct(n) : n <= 640 ? 10 : n <= 768 ? 12 : 16; }      // its 8-row form where every row has a place of its own
+inline size_t bwdp_wh_bytes(int n, int nct) { return (size_t)((n + 31) / 32) * 16384 * nct; }           // per direction
 inline size_t bwdp_ring_bytes(int B, int n) {                                                      // per direction and slot
   const size_t groups = 2 * (size_t)(((B > 0 ? B : 1) + 15) / 16), tiles = (size_t)((n + 31) / 32);
   return groups * tiles * tiles * 512;
@@ -431,7 +432,7 @@ bool few_zx_ok(const GemmArgs& g);
 // The same for the float loops (forward: `p` as launch_persist_fwd_f32 takes it).
 hipError_t launch_prep_fwd_f32(const ZeroRegions& z, const void* W, void* Wf, const PFwdArgs& p, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s);
 hipError_t launch_prep_bwd_f32(const ZeroRegions& z, const void* W, void* Wb, int n, int ndir, const FrameMapArgs& fm, const SetUpCopies& copies, hipStream_t s);
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, hipStream_t s);
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, int nct, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, hipStream_t s);
 // db[c] (+)= sum_rows DZ[row][c]; part = float scratch [nsplit][ncols] per direction
 // db[dir][c] (+)= sum over the first nslices slices of part[dir][kColsumSlices][ncols]
 constexpr int kColsumSlices = 64;

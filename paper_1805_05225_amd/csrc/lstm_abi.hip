@@ -108,7 +108,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p, bool odd_fast = true) {
   const bool part = p->bf16 && d->n <= 1024;          // the partial-sum backward kernel may be chosen
   // float storage: the single-launch backward kernel (batches of up to 256 rows: its rings grow with B n^2 / 16)
   const bool part32 = !p->bf16 && d->n <= 1024 && d->B <= 256;
-  p->ws_Wb = take(infer ? 0 : D * std::max({(size_t)p->ntile_b * p->nkc_b * 1024, part ? bwdp_wh_bytes(d->n) : (size_t)0,
+  p->ws_Wb = take(infer ? 0 : D * std::max({(size_t)p->ntile_b * p->nkc_b * 1024, part ? bwdp_wh_bytes(d->n, bwdp_nct(d->n)) : (size_t)0,
                                             part32 ? bwd_f32_wh_bytes(d->n) : (size_t)0}));
   p->hfrag_bytes = D * p->nrt * (size_t)std::max(p->nkc_f, p->nkc_ll_f) * 1024;
   p->dzfrag_bytes = D * std::max({p->nrt * (size_t)p->nkc_b * 1024, part ? bwdp_ring_bytes(d->B, d->n) : (size_t)0,
@@ -728,6 +728,8 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     PackRows rows = {};
     if (use_ll && compact) rows = pack_rows(p, ws, seq_lens, true, desc);
     pa.slots = rows.slots; pa.tab_steps = rows.tab_steps; pa.steps = rows.steps;
+    const bool eights = persist_bwd_rows(p.B, p.n, p.D) == 8;
+    const int wb_nct = eights && rows.slots == 0 ? bwdp8_nct(p.n) : bwdp_nct(p.n);
     const bool use_ll32 = !p.bf16 && !(desc->flags & LSTM_FLAG_PER_STEP) && T >= 2 && p.n <= 1024 && p.B <= 256 &&
                           persist_bwd_f32_fits(pa) && persist_f32_pays(p.T, p.B, p.n, p.D, seq_lens != nullptr, pa.plain_launch, true);
     {
@@ -755,7 +757,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
           x_padded = true;
         }
         if (use_ll32) HIPCHK(launch_prep_bwd_f32(z, W_h, ws + p.ws_Wb, p.n, p.D, fm, copies, s));
-        else HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || persist_bwd_rows(p.B, p.n, p.D) == 8, fm, rows, copies, s));
+        else HIPCHK(launch_prep_bwd_ll(z, W_h, (uint4*)(ws + p.ws_Wb), p.n, p.D, rows.slots > 0 || eights, wb_nct, fm, rows, copies, s));
       } else HIPCHK(launch_fill_zero_many(z, s));
     }
     if (!use_ll && !use_ll32) {
@@ -768,7 +770,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     const bool db_in_loop = (use_ll || use_ll32) && 2 * p.nrt <= kColsumSlices;   // the single-launch kernels also sum the bias gradient
     if (use_ll || use_ll32) {
       const size_t ring_dir = use_ll ? bwdp_ring_bytes(p.B, p.n) : bwd_f32_ring_bytes(p.B, p.n);
-      const size_t wb_dir = use_ll ? bwdp_wh_bytes(p.n) : bwd_f32_wh_bytes(p.n);
+      const size_t wb_dir = use_ll ? bwdp_wh_bytes(p.n, wb_nct) : bwd_f32_wh_bytes(p.n);
       for (size_t d = 0; d < D; ++d) {
         PBwdDir& bd = pa.d[d];
         bd.Wb = (const uint4*)(ws + p.ws_Wb + d * wb_dir);

@@ -389,7 +389,7 @@ __device__ __forceinline__ u32x2 turned(const char* p) {
 // chunk_of(it): the chunk of the wavefront's it-th operands; use(it, rows): they are at `rows`, [gate][k][64 bytes].
 template <int ITS, typename C, typename U>
 __device__ __forceinline__ void walk_w_rows(const void* W, int n, int tile2, char (&buf)[kWChunks][8192], int lane, C&& chunk_of, U&& use) {
-  static_assert(ITS > kWChunks && kWChunks == 3, "the counted waits below");
+  static_assert(kWChunks == 3, "the counted waits below");
   const unsigned ldw = 8u * n, u0 = tile2 * 32 + (lane & 3) * 8;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, n * ldw, kBufFlags);
   const unsigned off0 = u0 < (unsigned)n ? (lane >> 2) * ldw + u0 * 2u : 0x7ff00000u;
@@ -402,7 +402,7 @@ __device__ __forceinline__ void walk_w_rows(const void* W, int n, int tile2, cha
                    "v"(off0 + ((row0 + (i & 1) * 16u) * ldw + (i >> 1) * 2u * n)), "s"(rs) : "memory", "scc");
   };
 #pragma unroll
-  for (int it = 0; it < kWChunks; ++it) ask(it);
+  for (int it = 0; it < (ITS < kWChunks ? ITS : kWChunks); ++it) ask(it);
 #pragma unroll
   for (int it = 0; it < ITS; ++it) {                       // (loads complete in the order of issue)
     if (it + 2 < ITS) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
@@ -598,15 +598,14 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED, ROW
 #pragma unroll
           for (int q = 0; q < 4; ++q) smfmac_b_agpr(acc[q], av[o], w[2 * p + o][q], sparse);
       };
-      // The stream.  The loads are consumed in pairs: a pair is four chunks, and every accumulator takes its four products in that
+      // The stream.  The loads are consumed in pairs (the last one alone where NL is odd): a pair is four chunks, and every accumulator takes its four products in that
       // order.  A product of this shape issues every 16 cycles (7.05 ns measured, in any order of the
       // accumulators) and occupies the issue slot of the wavefront for 4 of them: independent instructions behind
       // it are free, dependent ones are not (three: 12.4 ns).  What turns the loads
       // into operands (tag test, masking the tags off, chunks into all rows) is cut into single instructions that follow the
       // products of the chunk before.  A pair with a stale tag in any lane is skipped (wave-uniform branch)
       // and both its loads are fetched again by fix_up.
-      static_assert(NL % 2 == 0, "loads are consumed in pairs");
-      constexpr int NP = NL / 2;
+      constexpr int NP = (NL + 1) / 2;
       u32x4 x[NL];
       const unsigned tagw = rd.tag << 16;
       // The poll IS the first pair of loads: they are repeated (bounded) until all their tags have turned, and what
@@ -616,10 +615,11 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED, ROW
       // everything at once without looking was measured slower: the values arrive while the poll is in flight.)
       auto poll_loads = [&]() __attribute__((always_inline)) {
         x[0] = rd.load_it(rd.it_of(0));
-        x[1] = rd.load_it(rd.it_of(1));
+        if constexpr (NL > 1) x[1] = rd.load_it(rd.it_of(1));
       };
       auto polled_stale = [&]() __attribute__((always_inline)) {
-        const unsigned stale = rd.tag_diff(x[0], rd.it_of(0), tagw) | rd.tag_diff(x[1], rd.it_of(1), tagw);
+        unsigned stale = rd.tag_diff(x[0], rd.it_of(0), tagw);
+        if constexpr (NL > 1) stale |= rd.tag_diff(x[1], rd.it_of(1), tagw);
         return __builtin_amdgcn_ballot_w64(stale > 0xffffu) != 0ull;
       };
       poll_loads();
@@ -660,7 +660,8 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED, ROW
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         __builtin_amdgcn_sched_barrier(0);
-        if (p > 0) { prep(2 * p, 0); prep(2 * p + 1, 0); }  // (the poll has looked at the first pair)
+        const bool two = 2 * p + 1 < NL;
+        if (p > 0) { prep(2 * p, 0); if (two) prep(2 * p + 1, 0); }      // (the poll has looked at the first pair)
         if (p == 0 || __builtin_expect(__builtin_amdgcn_ballot_w64(bad[p] > 0xffffu) == 0ull, 1)) {
 #pragma unroll
           for (int kk = 1; kk < 7; ++kk) prep(2 * p, kk);
@@ -670,19 +671,19 @@ __device__ __forceinline__ void fwd8_body(const PFwdArgs& a, Fwd8Lds<PACKED, ROW
           // next step's poll's way.
           if (fetches && p == NP - 1 && redo == 0ull) fetch_next();
 #pragma unroll
-          for (int o = 0; o < 4; ++o)
+          for (int o = 0; o < (two ? 4 : 2); ++o)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               smfmac_b_agpr(acc[q], ops[2 * p + (o >> 1)][o & 1], w[4 * p + o][q], sparse);
               __builtin_amdgcn_sched_barrier(0);
               // the pair's other operands, two products ahead of theirs (the wait states between the two)
               const int i = 2 * p + (o > 0), kk = o == 1 ? 3 : 7;
-              if (o < 3 && q < 2) { prep(i, kk + 2 * q); prep(i, kk + 2 * q + 1); }
-              if (o == 0 && q == 2) { prep(i + 1, 1); prep(i + 1, 2); }
+              if (o < (two ? 3 : 1) && q < 2) { prep(i, kk + 2 * q); prep(i, kk + 2 * q + 1); }
+              if (two && o == 0 && q == 2) { prep(i + 1, 1); prep(i + 1, 2); }
               __builtin_amdgcn_sched_barrier(0);
             }
         } else {                                           // rare once the sample has turned
-          redo |= 3ull << (2 * p);
+          redo |= (two ? 3ull : 1ull) << (2 * p);
         }
       }
       PROF_REDO(__popcll(redo))
@@ -3382,14 +3383,38 @@ template <typename K>
 bool slab_fits(K kernel, int ntile, int rows_per_group, int nrow, int ndir) {
   return capacity(kernel) >= (long)ntile * std::min(16 / rows_per_group, nrow) * ndir;
 }
-// The form of a kernel for n units: half (a quarter) of the registers' worth of weights, MFMAs and ring loads per step
-// for n <= 512 (256).
+// The form of a kernel for n units: as much of the registers' worth of weights, MFMAs and ring loads per step as n needs.  The 8-row kernels in quarters
+// forward (us a step, 16 rows, both directions, with half / all of it and now: n = 144 0.98 / 0.90, 256 1.00 / 0.93, 563 1.33 / 1.26, 768 1.39 / 1.30; inference 0.97 / 0.88, 0.98 / 0.90,
+// 1.30 / 1.20, 1.37 / 1.25); backward a quarter, a half, and from there in eighths up to three quarters (563 1.45 / 1.33, 768 1.51 / 1.41; three eighths for n = 300 1.13 / 1.13,
+// seven for 850 1.55 / 1.52: not worth a form).
 typedef void (*FwdKernel)(PFwdArgs);
 typedef void (*BwdKernel)(PBwdArgs);
-FwdKernel fwd8_for(int n) { return n <= 512 ? persist_fwd8_kernel<2> : persist_fwd8_kernel<4>; }
-FwdKernel fwd8_rows_w_for(int n) { return n <= 512 ? persist_fwd8_rows_w_kernel<2> : persist_fwd8_rows_w_kernel<4>; }
+FwdKernel fwd8_for(int n) {
+  switch (cdiv(n, 256)) {
+    case 0: case 1: return persist_fwd8_kernel<1>;
+    case 2: return persist_fwd8_kernel<2>;
+    case 3: return persist_fwd8_kernel<3>;
+    default: return persist_fwd8_kernel<4>;
+  }
+}
+FwdKernel fwd8_rows_w_for(int n) {
+  switch (cdiv(n, 256)) {
+    case 0: case 1: return persist_fwd8_rows_w_kernel<1>;
+    case 2: return persist_fwd8_rows_w_kernel<2>;
+    case 3: return persist_fwd8_rows_w_kernel<3>;
+    default: return persist_fwd8_rows_w_kernel<4>;
+  }
+}
 FwdKernel fwd16_for(int n) { return n <= 512 ? persist_fwd16r_kernel<4> : persist_fwd16r_kernel<8>; }
-BwdKernel bwd8_for(int n) { return n <= 256 ? persist_bwdp_kernel<4, 4> : n <= 512 ? persist_bwdp_kernel<4, 8> : persist_bwdp_kernel<8, 16>; }
+BwdKernel bwd8_for(int n) {
+  switch (bwdp8_nct(n)) {
+    case 4: return persist_bwdp_kernel<4, 4>;
+    case 8: return persist_bwdp_kernel<4, 8>;
+    case 10: return persist_bwdp_kernel<6, 10>;
+    case 12: return persist_bwdp_kernel<6, 12>;
+    default: return persist_bwdp_kernel<8, 16>;
+  }
+}
 BwdKernel bwd16_for(int n) { return n <= 256 ? persist_bwdp16_kernel<4, 4> : n <= 512 ? persist_bwdp16_kernel<4, 8> : persist_bwdp16_kernel<8, 16>; }
 
 }  // namespace
@@ -3490,10 +3515,10 @@ bool few_zx_ok(const GemmArgs& g) {
   return g.in_bf16 && !g.out_bf16 && g.M > 0 && g.M <= kFewZxRows && rounds * g.K <= kFewZxWalk && rounds <= (g.K % 8 == 0 ? 5 : 6) &&
          g.K % 2 == 0 && g.N % 4 == 0 && g.lda == g.K && g.ldb == g.N && g.ldc == g.N && g.sBz == (long)g.K * g.N && g.sCz % 4 == 0 && (long)(g.K + 1024) * g.N * 2 < 0x7ff00000L;
 }
-hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, hipStream_t s) {
+hipError_t launch_prep_bwd_ll(const ZeroRegions& z, const void* W, uint4* Wb, int n, int ndir, bool paired, int nct, const FrameMapArgs& fm, const PackRows& rows, const SetUpCopies& copies, hipStream_t s) {
   if (z.overflow) return hipErrorInvalidValue;
   PrepArgs a = {};
-  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.nct = bwdp_nct(n); a.w_total = (long)ndir * a.nk * 4 * 4 * a.nct * 64;
+  a.z = z; a.W = (const bf16_t*)W; a.Wout = Wb; a.n = n; a.nk = cdiv(n, 32); a.nct = nct; a.w_total = (long)ndir * a.nk * 4 * 4 * a.nct * 64;
   a.first_pack = z.count ? z.first_block[z.count] : 0;
   a.first_ring = a.first_pack + cdiv(a.w_total, 256);
   a.copies = copies;

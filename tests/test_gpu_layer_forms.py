@@ -97,6 +97,21 @@ def test_eight_row_loops(T, B, n, bidir):
     _layer(T, B, 32, n, bidir, "bf16")
 
 
+@pytest.mark.parametrize("T,B,n,bidir", [(9, 5, 136, True), (8, 17, 256, False), (7, 9, 513, True), (9, 20, 640, True), (8, 3, 641, False), (9, 30, 768, True), (6, 8, 769, False),
+                                         (12, 48, 768, True)])
+def test_eight_row_loop_forms(T, B, n, bidir):
+    """The first and last width of each form, W_h packed and (inference) as it lies in memory; the last batch takes another form's packing."""
+    _layer(T, B, 24, n, bidir, "bf16")
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator(device="cuda").manual_seed(n)
+    r = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * n ** -0.5).bfloat16()
+    D = 2 if bidir else 1
+    x, W_x, W_h = r(T, B, 24), r(*(D, 24, 4 * n)[2 - D:]), r(*(D, n, 4 * n)[2 - D:])
+    lens = torch.linspace(1, T, B, device="cuda").int()
+    got, ref = (Bn.forward(x, W_x, W_h, None, None, None, lens, bidirectional=bidir, flags=f)["y"] for f in (Bn.FLAG_INFERENCE, Bn.FLAG_PER_STEP))
+    check("y", got, host(ref), TOL["bf16"])
+
+
 @pytest.mark.parametrize("T,B,n,bidir", [(7, 40, 1000, True), (3, 70, 1022, False), (9, 100, 514, True), (5, 200, 520, False), (2, 49, 900, True)])
 def test_rows_one_behind_the_other(T, B, n, bidir):
     """More rows than places, lengths from 0 to T, every optional state, against the oracle."""
