@@ -122,6 +122,8 @@ constexpr int kSkinnyMaxRows = 1024;
 bool gemm_skinny_ok(const GemmArgs& g);
 hipError_t launch_gemm_skinny(const GemmArgs& g, hipStream_t s);
 bool gemm_skinny_pays(long M, long N, int nz);
+enum class FewRoute { kHere, kTile, kLarge };          // the kernel for a plain product of few rows: gemm_skinny.hip, gemm_tile.hip, gemm_nt.hip
+FewRoute few_rows_route(int M, int N, int K);
 // out[B][R] = bf16(max(0, A[B][lda] W^T + bias)): W in the fragment order of launch_pack_rows_both, A's rows at least ceil(K / 32) * 32 columns, zeros past K
 hipError_t launch_skinny_readout(const void* A, long lda, const void* Wfrag, const float* bias, void* out, long ldo, int B, int R, int K, hipStream_t s);
 // Numbers the frames (t, b) with t < lens[b] in (t, b) order: fidx[number] -> frame, count[0] = how many, count[1] = that rounded up

@@ -358,21 +358,25 @@ hipError_t launch_as(const SkinnyArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((skinny_kernel<BI, BJ, CELL, BFRAG>), grid, dim3(512), G::kLds, s, a);
   return hipGetLastError();
 }
-template <bool CELL, bool BFRAG>
-hipError_t launch_tiles(SkinnyArgs a, hipStream_t s) {
-  // The tile whose work-groups are done first: rounds times what one reads, which is all of K of its rows and columns; what begins and ends
-  // a work-group counts as 1e5 / K rows more.  Of 46 products and cells measured with every tile the choice is the fastest one or within 6 %, in three
-  // within 12 % (64 x 32000 x 512 12.2 us, 10.9 in 64 x 64).  us, 96 x 128 (or 64 x 64) before and the choice: cells of n = 688, 915 rows, K = 1680 44.9 -> 26.0; n = 1000, 1024 rows,
-  // K = 3620 71.9 -> 49.0; n = 504, 504 rows, K = 2424 31.2 -> 19.8; products 1000 x 4000 x 2000 43.8 -> 30.2, 104 x 22051 x 960 29.8 -> 19.5, 504 x 920 x 2424 14.3 -> 12.5.
-  static constexpr int kTiles[][2] = {{3, 2}, {2, 1}, {2, 2}, {3, 1}, {4, 2}, {1, 1}};
+constexpr int kTiles[][2] = {{3, 2}, {2, 1}, {2, 2}, {3, 1}, {4, 2}, {1, 1}};
+int choose_tile(SkinnyArgs& a, double& least) {
   int best = 0;
-  double least = 0.;
   for (int i = 0; i < 6; ++i) {
     const int tm = 32 * kTiles[i][0], tn = 64 * kTiles[i][1];
     SkinnyArgs b = a;
     const double cost = split_tiles(b, tm, tn) * ((a.M < tm ? a.M : tm) + tn + 1e5 / a.K);
     if (i == 0 || cost < least) { least = cost; best = i; }
   }
+  return best;
+}
+template <bool CELL, bool BFRAG>
+hipError_t launch_tiles(SkinnyArgs a, hipStream_t s) {
+  // The tile whose work-groups are done first: rounds times what one reads, which is all of K of its rows and columns; what begins and ends
+  // a work-group counts as 1e5 / K rows more.  Of 46 products and cells measured with every tile the choice is the fastest one or within 6 %, in three
+  // within 12 % (64 x 32000 x 512 12.2 us, 10.9 in 64 x 64).  us, 96 x 128 (or 64 x 64) before and the choice: cells of n = 688, 915 rows, K = 1680 44.9 -> 26.0; n = 1000, 1024 rows,
+  // K = 3620 71.9 -> 49.0; n = 504, 504 rows, K = 2424 31.2 -> 19.8; products 1000 x 4000 x 2000 43.8 -> 30.2, 104 x 22051 x 960 29.8 -> 19.5, 504 x 920 x 2424 14.3 -> 12.5.
+  double least = 0.;
+  const int best = choose_tile(a, least);
   split_tiles(a, 32 * kTiles[best][0], 64 * kTiles[best][1]);
   switch (best) {
     case 0: return launch_as<3, 2, CELL, BFRAG>(a, s);
@@ -435,6 +439,24 @@ bool gemm_skinny_ok(const GemmArgs& g) {
   return gemm_skinny_pays(g.M, g.N, g.nz) && g.in_bf16 && g.a_kcontig && g.b_kcontig && !g.lens && g.nseg == 1 && !g.a_rows && !g.c_rows && !g.m_dev &&
          !g.k_dev && !g.accumulate && g.K % 8 == 0 && g.lda % 8 == 0 && g.ldb % 8 == 0 && g.sAz % 8 == 0 && g.sBz % 8 == 0 &&
          a16(g.A) && a16(g.B) && (long)g.N * g.ldb * 2 <= 0x7fffff00L;
+}
+// A work-group here begins and ends alone on its compute unit, one of 128 x 128 (gemm_tile.hip) shares it, and one of 256 x 256 (gemm_nt.hip) moves fewest bytes: with many columns the
+// best of the three changes several times.  Each side as measured, in us, operands from memory, 20 to 1024 rows, 300 to 32000 columns, K from 272 to 8000 (691 products): the choice
+// is the fastest or within 5 % in all but 20 of them, at most 1.33 times it; by the number of 256 x 256 tiles alone (here below 128, 128 x 128 up to 200) 134 were not, the
+// worst 1.44.  us, here / 128 x 128 / 256 x 256: 224 x 20000 x 448 17.7 / 14.9 / 19.0, 385 x 14000 x 448 20.2 / 14.0 / 19.0, 480 x 20000 x 800 48.4 / 37.2 / 28.8, 600 x 9000 x 448 17.8 / 14.6 /
+// 19.4, 300 x 5000 x 800 10.3 / 13.8 / 25.2, 900 x 5000 x 800 22.3 / 19.2 / 25.4.
+FewRoute few_rows_route(int M, int N, int K) {
+  SkinnyArgs a = {};
+  a.M = M; a.N = N; a.K = K;
+  double cost = 0.;
+  const int best = choose_tile(a, cost), rounds = split_tiles(a, 32 * kTiles[best][0], 64 * kTiles[best][1]);
+  const double out = 1e-6 * M * N, k = 1e-3 * K, read = rounds ? cost / rounds - 1e5 / K : 0.;      // rows and columns that a work-group reads
+  const int groups = cdiv(M, 128) * cdiv(N, 128), full = (groups - 1) / 512, rest = groups - 512 * full, pairs = full + (rest > 256), alone = rest <= 256;
+  const int large = cdiv((long)cdiv(M, 256) * cdiv(N, 256), 256);
+  const double here = 2.0 + rounds * (1.63 + 0.034 * k * read) + 1.56 * out;
+  const double tile = 2.8 + pairs * (1.63 + 16.6 * k) + alone * (4.1 + 7.1 * k) + 0.89 * out;
+  const double nt = large * (10.2 + 16.4 * k) + 0.55 * out;
+  return here <= tile && here <= nt ? FewRoute::kHere : tile <= nt ? FewRoute::kTile : FewRoute::kLarge;
 }
 hipError_t launch_gemm_skinny(const GemmArgs& g, hipStream_t s) {
   SkinnyArgs a = {};

@@ -70,6 +70,18 @@ def test_product(M, N, K):
     check("C", C, A.double().numpy() @ B.double().numpy().T + bias, 1e-4)
 
 
+@pytest.mark.parametrize("M,N,K", [(65, 31001, 272), (224, 20000, 448), (385, 14002, 268), (480, 20000, 800), (300, 5000, 800), (900, 5001, 104), (1024, 16001, 60), (1024, 3000, 2000)])
+def test_product_on_each_side_of_the_route(M, N, K):
+    """64 rows and up: few-rows tiles, 128 x 128 or 256 x 256, whichever is expected to end first; float and bfloat16 results."""
+    from paper_1805_05225_amd import binding as Bn
+    test_product(M, N, K)
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A, B = (torch.randn(r, K, generator=g, device="cuda").bfloat16() for r in (M, N))
+    C = Bn.gemm(A, B, a_kcontig=True, b_kcontig=True, M=M, N=N, K=K, out_dtype=torch.bfloat16)
+    want = A.double() @ B.double().T
+    assert ((C.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-4 * K ** 0.5).all()
+
+
 @pytest.mark.parametrize("B,n_in,n", [(1, 64, 64), (12, 2620, 1000), (16, 300, 104), (17, 300, 104), (193, 64, 66)])
 def test_stepped_cell_in_place(B, n_in, n):
     """hT = h0 and cT = c0: every work-group needs all of h, so none may store its part before the others have read it."""
