@@ -107,6 +107,7 @@ bool gemm_tile_ok(const GemmArgs& g);
 bool gemm_tile_small(long M, long N, int nz);
 size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg);
 hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_tile_grads(const GemmArgs& dx, const GemmArgs& dwx, const GemmArgs& dwh, hipStream_t s);      // a layer's three gradient products, in one launch
 hipError_t launch_gemm_tile_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s);      // two products of k-major operands, in one launch
 // Float storage (gemm_float.hip): operands as they lie in memory, rows 16-byte aligned, K a multiple of 4 for a k-contiguous
 // operand; row maps, device-resident M / K and segments as above; K ranges of its own if `parts` holds gemm_float_parts_bytes

@@ -54,6 +54,7 @@ struct TileArgs {
 };
 
 struct TileGroup { TileArgs p[2]; int first1; };         // blocks from first1 on are the second product's
+struct TileTrio { TileArgs p[3]; int first1, first2; };
 
 __device__ __forceinline__ void load_to_lds_b128(const u32x4& rsrc, unsigned lds_addr, unsigned voff, unsigned soff) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
@@ -79,15 +80,12 @@ static_assert(2 * kStageBytes >= kEpBytes && 2 * tile_lds(true, false) <= 160 * 
 
 // KROWS: k-major operands whose row k is row k_rows[k] in memory.  PACED (both k-contiguous): half as much on its way (see paced()).
 template <typename TC, bool AK, bool BK, bool KROWS, bool PACED>
-__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
+__device__ __forceinline__ void tile_body(const TileArgs& g, int mine, char* lds) {       // mine: work-group of this product
   constexpr int NW = 4;
   constexpr bool kMixed = AK && !BK;
   constexpr bool kHalves = AK && BK;      // a phase is one row of blocks, half of them, over the stage's 64 k (else: all blocks over 32 k)
   static_assert(!KROWS || (!AK && !BK), "a list of rows: both operands k-major");
-  extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
-  const bool second = (int)blockIdx.x >= grp.first1;
-  const TileArgs g = second ? grp.p[1] : grp.p[0];
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int r = lane & 31, gq = lane >> 5;
@@ -104,7 +102,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
   const int ktiles = (K + kKB - 1) / kKB;
   const int tiles_m = (M + kTM - 1) / kTM, tiles_n = (g.N + kTN - 1) / kTN, per_z = tiles_m * tiles_n, tiles = per_z * g.nz * g.ksplit;
-  const int mine = (int)blockIdx.x - (second ? grp.first1 : 0), each = (tiles + 7) >> 3;
+  const int each = (tiles + 7) >> 3;
   const bool apart = !AK && !BK && g.nz * g.ksplit > 1;
   const bool by_rows = apart || (tiles_m > tiles_n && (g.ksplit == 1 || ktiles * g.nseg > 5 * g.ksplit));
   // B k-major, bands of columns, some units with two work-groups: an eighth of all tiles each as well, where a tile column is not one XCD's.  In whole eights of columns it is, and stays
@@ -478,6 +476,40 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
   }
 }
 
+template <typename TC, bool AK, bool BK, bool KROWS, bool PACED>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(TileGroup grp) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const bool second = (int)blockIdx.x >= grp.first1;
+  const TileArgs g = second ? grp.p[1] : grp.p[0];
+  tile_body<TC, AK, BK, KROWS, PACED>(g, (int)blockIdx.x - (second ? grp.first1 : 0), lds);
+}
+// The three products of a layer's backward pass: dX, both operands k-contiguous, then dW_x and dW_h, both k-major.
+template <typename TC, bool KROWS>
+__global__ __launch_bounds__(256, 2) void gemm_tile_grads_kernel(TileTrio grp) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  if ((int)blockIdx.x < grp.first1) {
+    const TileArgs g = grp.p[0];
+    tile_body<TC, true, true, false, false>(g, blockIdx.x, lds);
+  } else {
+    const bool last = (int)blockIdx.x >= grp.first2;
+    const TileArgs g = last ? grp.p[2] : grp.p[1];
+    tile_body<float, false, false, KROWS, false>(g, (int)blockIdx.x - (last ? grp.first2 : grp.first1), lds);
+  }
+}
+
+int blocks_of(const TileArgs& a) { return (cdiv(a.M, kTM) * cdiv(a.N, kTN) * a.nz * a.ksplit + 7) / 8 * 8; }
+template <typename TC, bool KROWS>
+hipError_t launch_grads_as(TileTrio a, hipStream_t s) {
+  const auto kernel = gemm_tile_grads_kernel<TC, KROWS>;
+  constexpr int lds = std::max(tile_lds(true, true), tile_lds(false, false));
+  static std::atomic<unsigned long long> attr_set{0};
+  const hipError_t ea = once_per_device(attr_set, [&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
+  if (ea != hipSuccess) return ea;
+  a.first1 = blocks_of(a.p[0]);
+  a.first2 = a.first1 + blocks_of(a.p[1]);
+  hipLaunchKernelGGL(kernel, dim3(a.first2 + blocks_of(a.p[2])), dim3(256), lds, s, a);
+  return hipGetLastError();
+}
 template <typename TC, bool AK, bool BK, bool KROWS, bool PACED = false>
 hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
   const auto kernel = gemm_tile_kernel<TC, AK, BK, KROWS, PACED>;
@@ -486,7 +518,7 @@ hipError_t launch_as(const TileGroup& a, int count, hipStream_t s) {
   if (ea != hipSuccess) return ea;
   TileGroup c = a;
   int blocks[2] = {0, 0};
-  for (int i = 0; i < count; ++i) blocks[i] = (cdiv(c.p[i].M, kTM) * cdiv(c.p[i].N, kTN) * c.p[i].nz * c.p[i].ksplit + 7) / 8 * 8;
+  for (int i = 0; i < count; ++i) blocks[i] = blocks_of(c.p[i]);
   c.first1 = count == 2 ? blocks[0] : 0x7fffffff;
   hipLaunchKernelGGL(kernel, dim3(blocks[0] + blocks[1]), dim3(256), tile_lds(AK, BK), s, c);
   return hipGetLastError();
@@ -518,7 +550,7 @@ int ranges(long tiles, long others, long K, int nseg) {
   return (int)std::max(1L, std::min(std::min(512 / std::max(tiles + others, 1L), stages / 4), 16L));
 }
 size_t bytes_of(long M, long N, int nz, int ks) { return ks > 1 ? (size_t)ks * nz * M * ((N + 3) / 4 * 4) * 4 : 0; }
-TileArgs tile_args(const GemmArgs& g, long others, size_t parts_used) {
+TileArgs tile_args(const GemmArgs& g, int ks, size_t parts_used) {
   TileArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
   const bool halves = g.a_kcontig && g.b_kcontig;
@@ -528,7 +560,7 @@ TileArgs tile_args(const GemmArgs& g, long others, size_t parts_used) {
   a.a_rows = g.a_rows; a.c_rows = g.c_rows; a.a_phys_rows = g.a_phys_rows; a.k_rows = g.k_rows; a.k_phys_rows = g.k_phys_rows;
   a.m_dev = g.m_dev; a.k_dev = g.k_dev;
   a.ldp = (g.N + 3) / 4 * 4;
-  a.ksplit = g.parts ? ranges(tiles_of(g), others, g.K, g.nseg) : 1;
+  a.ksplit = g.parts ? ks : 1;
   if (parts_used + bytes_of(g.M, g.N, g.nz, a.ksplit) > g.parts_bytes) a.ksplit = 1;
   a.parts = a.ksplit > 1 ? (float*)((char*)g.parts + parts_used) : nullptr;
   return a;
@@ -568,7 +600,7 @@ size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg) {
 
 hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s) {
   TileGroup a = {};
-  a.p[0] = tile_args(g, 0, 0);
+  a.p[0] = tile_args(g, ranges(tiles_of(g), 0, g.K, g.nseg), 0);
   const bool bf = g.out_bf16 && a.p[0].ksplit == 1;
   const hipError_t e = bf ? launch_layout<uint16_t>(a, 1, g.a_kcontig, g.b_kcontig, s) : launch_layout<float>(a, 1, g.a_kcontig, g.b_kcontig, s);
   return e == hipSuccess ? finish(a.p[0], g, s) : e;
@@ -578,11 +610,54 @@ hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s) {
 hipError_t launch_gemm_tile_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s) {
   if (g.M <= 0 || h.M <= 0 || g.N <= 0 || h.N <= 0 || g.nz <= 0) return hipErrorInvalidValue;
   TileGroup a = {};
-  a.p[0] = tile_args(g, tiles_of(h), 0);
-  a.p[1] = tile_args(h, tiles_of(g), (bytes_of(g.M, g.N, g.nz, a.p[0].ksplit) + 255) / 256 * 256);
+  a.p[0] = tile_args(g, ranges(tiles_of(g), tiles_of(h), g.K, g.nseg), 0);
+  a.p[1] = tile_args(h, ranges(tiles_of(h), tiles_of(g), h.K, h.nseg), (bytes_of(g.M, g.N, g.nz, a.p[0].ksplit) + 255) / 256 * 256);
   hipError_t e = launch_layout<float>(a, 2, false, false, s);
   if (e != hipSuccess || (e = finish(a.p[0], g, s)) != hipSuccess) return e;
   return finish(a.p[1], h, s);
+}
+
+// dX needs dZ and W_x, dW_x and dW_h need dZ, x and h: none waits for another, and each alone ends with most of the device idle (us, dX by itself, the pair, the sums / all
+// three at once, the sums; a training pass' lower layer: 330 units, 21 rows of at most 97 frames, both directions, n_in = 660 19.5 + 18.6 + 13.0 / 31.8 + 5.1, n_in = 123 12.2 + 13.3 + 8.3 / 16.1 + 7.2;
+// 208 units, 6 rows of 65 frames 11.1 + 11.2 + 5.0 / 12.0 + 5.0; 728 units, 14 rows of 113 frames, n_in = 598 19.3 + 26.2 + 13.0 / 37.7 + 4.3;
+// 512 units, 32 rows of 60, both directions, n_in = 1024 23.6 + 34.6 + 6.8 / 48.8 + 4.0; 1000 units, 64 rows of 50, n_in = 1000 39.2 + 52.3 + 8.4 / 96.3 + 4.1).
+// K ranges of about the same number of stages in all three; how many stages by what the launch is expected to take, in stages: a work-group costs 8 more than it has, 512 run at a time, and
+// a megabyte of parts is half a stage.
+hipError_t launch_gemm_tile_grads(const GemmArgs& dx, const GemmArgs& dwx, const GemmArgs& dwh, hipStream_t s) {
+  const GemmArgs* g[3] = {&dx, &dwx, &dwh};
+  long tiles[3], stages[3], most = 4;
+  for (int i = 0; i < 3; ++i) {
+    if (g[i]->M <= 0 || g[i]->N <= 0 || g[i]->nz <= 0) return hipErrorInvalidValue;
+    tiles[i] = tiles_of(*g[i]);
+    stages[i] = (long)cdiv(g[i]->K, kKB) * g[i]->nseg;
+    most = std::max(most, stages[i]);
+  }
+  const auto range_of = [&](int i, long per) { return (int)std::max(1L, std::min({(stages[i] + per - 1) / per, stages[i] / 4, 16L})); };
+  long per = most;
+  double least = 0.;
+  for (long p = most; p >= 4; p -= std::max(1L, p / 32)) {
+    double groups = 0., work = 0., longest = 0., parts = 0.;
+    for (int i = 0; i < 3; ++i) {
+      const int ks = range_of(i, p);
+      const double each = (double)stages[i] / ks + 8.;
+      groups += (double)tiles[i] * ks;
+      work += tiles[i] * ks * each;
+      longest = std::max(longest, each);
+      parts += 5e-7 * bytes_of(g[i]->M, g[i]->N, g[i]->nz, ks);
+    }
+    const double cost = parts + (groups <= 512. ? longest : work / 512. + 0.5 * longest);
+    if (p == most || cost < least) { least = cost; per = p; }
+  }
+  TileTrio a = {};
+  size_t used = 0;
+  for (int i = 0; i < 3; ++i) {
+    a.p[i] = tile_args(*g[i], range_of(i, per), used);
+    if (a.p[i].ksplit > 1) used += (bytes_of(a.p[i].M, a.p[i].N, a.p[i].nz, a.p[i].ksplit) + 255) / 256 * 256;
+  }
+  const bool bf = dx.out_bf16 && a.p[0].ksplit == 1, rows = dwx.k_rows != nullptr;
+  hipError_t e = bf ? (rows ? launch_grads_as<uint16_t, true>(a, s) : launch_grads_as<uint16_t, false>(a, s)) : rows ? launch_grads_as<float, true>(a, s) : launch_grads_as<float, false>(a, s);
+  for (int i = 0; i < 3 && e == hipSuccess; ++i) e = finish(a.p[i], *g[i], s);
+  return e;
 }
 
 }  // namespace lstm

@@ -895,20 +895,20 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
   SumList sums;                        // what the products' K ranges and the loop's bias-gradient slices still have to be added to
   auto parts_of = [&](GemmArgs& g) { g.parts = (float*)(ws + p.ws_parts + sums.used); g.parts_bytes = p.parts_bytes - sums.used; g.sums = &sums; };
   auto products = [&]() -> int {
-    if (dx) {                        // dX = sum over directions of DZ W_x^T
-      GemmArgs g = {};
+    GemmArgs gd = {};                // dX = sum over directions of DZ W_x^T
+    bool fill_dx = false, parts_dx = false;
+    if (dx) {
+      GemmArgs& g = gd;
       g.A = DZ; g.B = W_x; g.C = dx;
       g.M = TB; g.N = p.n_in; g.K = 4 * p.n;
       g.lda = 4 * n; g.ldb = 4 * n; g.ldc = n_in; g.nz = 1;
       g.nseg = p.D; g.sAseg = (long)p.DZ_dir_elems; g.sBseg = (long)(n_in * 4 * n); g.frames = true;
       g.a_kcontig = true; g.b_kcontig = true; g.in_bf16 = p.bf16; g.out_bf16 = p.bf16;
-      Phase ph(LSTM_PHASE_GEMM_DX, 1, s);
       if (compact && (gemm_nt_ok(g) || !p.bf16)) {      // rows of padded frames: zero, and left out of the product
-        if (!dx_cleared) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
+        fill_dx = !dx_cleared;
         g.a_rows = fidx; g.c_rows = fidx; g.a_phys_rows = TB; g.m_dev = count;
       }
-      if (!p.bf16 || (gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz))) parts_of(g);
-      HIPCHK(launch_gemm(g, s));
+      parts_dx = !p.bf16 || (gemm_tile_ok(g) && gemm_tile_small(g.M, g.N, g.nz));
     }
     // Weight gradients straight from the frame-major tensors (a row per frame in X, Hprev and DZ: both operands of
     // X^T DZ are k-major), over the packed list of real frames when lengths are given.
@@ -919,18 +919,38 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       g.sAz = sAz; g.sBz = (long)p.DZ_dir_elems; g.sCz = (long)M * 4 * n; g.nz = p.D; g.nseg = 1;
       g.a_kcontig = false; g.b_kcontig = false; g.in_bf16 = true; g.out_bf16 = false; g.accumulate = acc;
       if (compact) { g.k_rows = fidx; g.k_phys_rows = (int)TB; g.k_dev = count; }
-      if (gemm_tile_small(M, 4L * p.n, p.D)) parts_of(g);
       return g;
     };
     const bool pad_x = p.n_in8 != p.n_in;                          // rows of x are not 16-byte aligned: padded copy
     GemmArgs gx = frame_major(pad_x ? ws + p.ws_xpad : x, p.n_in8, 0, p.n_in, dW_x);
     GemmArgs gh = frame_major(rs + p.res_hprev, p.ldh, (long)(p.res_dir_stride / 2), p.n, dW_h);
     const auto frame_major_ok = [](const GemmArgs& g) { return gemm_tile_small(g.M, g.N, g.nz) ? gemm_tile_ok(g) : gemm_tn_ok(g); };
-    if (p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh)) {
-      const bool pair = gx.parts && gh.parts && gemm_tn_ranges(gx) == 1 && gemm_tn_ranges(gh) == 1;    // both in few tiles
+    const bool all_major = p.fast_gemm && (!seq_lens || compact) && frame_major_ok(gx) && frame_major_ok(gh);
+    const auto in_few_tiles = [&]() {                              // both weight gradients; their parts' room is what is free now
+      if (!all_major || !gemm_tile_small(gx.M, gx.N, gx.nz) || !gemm_tile_small(gh.M, gh.N, gh.nz)) return false;
+      parts_of(gx);
+      parts_of(gh);
+      return gemm_tn_ranges(gx) == 1 && gemm_tn_ranges(gh) == 1;
+    };
+    const auto pad_x_rows = [&]() { return pad_x && !x_padded ? launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s) : hipSuccess; };
+    if (dx) {
+      const bool together = p.bf16 && parts_dx && in_few_tiles();
+      Phase ph({{LSTM_PHASE_GEMM_DX, (double)p.n_in}, {LSTM_PHASE_GEMM_DWX, together ? (double)p.n_in : 0.0}, {LSTM_PHASE_GEMM_DWH, together ? (double)n : 0.0}}, 1, s);
+      if (fill_dx) HIPCHK(launch_fill_zero(dx, (size_t)TB * n_in * p.esz, s));
+      if (parts_dx) parts_of(gd);
+      if (together) {
+        HIPCHK(pad_x_rows());
+        HIPCHK(launch_gemm_tile_grads(gd, gx, gh, s));
+        return LSTM_OK;
+      }
+      HIPCHK(launch_gemm(gd, s));
+    }
+    if (all_major) {
+      const bool pair = in_few_tiles();
+      if (!pair && gemm_tile_small(gx.M, gx.N, gx.nz)) parts_of(gx);
       {
         Phase ph({{LSTM_PHASE_GEMM_DWX, (double)p.n_in}, {LSTM_PHASE_GEMM_DWH, pair ? (double)n : 0.0}}, 1, s);
-        if (pad_x && !x_padded) HIPCHK(launch_pad_rows(x, ws + p.ws_xpad, (long)TB, p.n_in, p.n_in8, s));
+        HIPCHK(pad_x_rows());
         if (pair) {
           HIPCHK(launch_gemm_tile_pair(gx, gh, s));
           return LSTM_OK;
@@ -938,7 +958,7 @@ int run_bwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
         HIPCHK(gemm_tn_ranges(gx) > 1 ? launch_gemm_tn_ranges(gx, s) : launch_gemm(gx, s));
       }
       Phase ph(LSTM_PHASE_GEMM_DWH, 1, s);
-      if (gh.parts) parts_of(gh);
+      if (gemm_tile_small(gh.M, gh.N, gh.nz)) parts_of(gh);
       HIPCHK(gemm_tn_ranges(gh) > 1 ? launch_gemm_tn_ranges(gh, s) : launch_gemm(gh, s));
     } else {                         // dW_x = X^T DZ, padded frames of X masked out
       GemmArgs g = {};

@@ -97,6 +97,12 @@ def test_eight_row_loops(T, B, n, bidir):
     _layer(T, B, 32, n, bidir, "bf16")
 
 
+@pytest.mark.parametrize("T,B,n_in,n,bidir", [(13, 4, 1296, 648, True), (30, 64, 100, 200, True), (25, 9, 130, 203, True), (2, 3, 33, 130, False), (90, 21, 300, 140, False)])
+def test_gradient_products_in_one_launch(T, B, n_in, n, bidir):
+    """More tiles than run at a time and dX in sixteen ranges; dX whole; half a chunk at the end of its K; a stage in all; every product in ranges."""
+    _layer(T, B, n_in, n, bidir, "bf16")
+
+
 @pytest.mark.parametrize("T,B,n,bidir", [(9, 5, 136, True), (8, 17, 256, False), (7, 9, 513, True), (9, 20, 640, True), (8, 3, 641, False), (9, 30, 768, True), (6, 8, 769, False),
                                          (12, 48, 768, True)])
 def test_eight_row_loop_forms(T, B, n, bidir):
