@@ -122,6 +122,9 @@ hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s);
 constexpr int kSkinnyMaxRows = 1024;
 bool gemm_skinny_ok(const GemmArgs& g);
 hipError_t launch_gemm_skinny(const GemmArgs& g, hipStream_t s);
+// the same for rows of any length and alignment (gemm_few.hip)
+bool few_any_ok(const GemmArgs& g);
+hipError_t launch_few_any(const GemmArgs& g, hipStream_t s);
 bool gemm_skinny_pays(long M, long N, int nz);
 enum class FewRoute { kHere, kTile, kLarge };          // the kernel for a plain product of few rows: gemm_skinny.hip, gemm_tile.hip, gemm_nt.hip
 FewRoute few_rows_route(int M, int N, int K);

@@ -391,6 +391,7 @@ hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nz <= 0) return hipSuccess;
+  if (!gemm_skinny_ok(g) && few_any_ok(g)) return launch_few_any(g, s);
   if (g.M > 64 && g.M <= kSkinnyMaxRows && g.a_kcontig && g.b_kcontig && g.nz == 1 && g.nseg == 1 && !g.parts && !g.a_rows && !g.c_rows && !g.m_dev && gemm_tile_ok(g) && gemm_nt_ok(g)) {
     const FewRoute r = few_rows_route(g.M, g.N, g.K);
     if (r != FewRoute::kHere) return r == FewRoute::kTile ? launch_gemm_tile(g, s) : launch_gemm_nt(g, s);

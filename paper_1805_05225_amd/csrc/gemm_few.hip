@@ -16,6 +16,10 @@
 // row-major and k-contiguous, rows 16-byte aligned; neighbouring lanes then sit in different rows, each group of four
 // touches four cache lines, and the load path takes four times as long - which is why the decoder's two large products
 // are packed.  Both bfloat16, K a multiple of 8.
+//
+// ANY: rows of any length that begin at any element (K no multiple of 8, so rows begin anywhere): 16 bytes are read at any element.  The other kernels that take such rows are
+// the 128 x 128 tiles and the generic kernel, a few work-groups that walk K one stage after the other: K = 1003, N = 1000, 4 rows 20.4 us, here 6.0.  A load that begins inside a
+// word costs the load path about three, so odd K pays for fewer rows and columns than even (few_any_ok).
 #include "recurrent_dev.h"
 #include "gemm_skinny.h"
 
@@ -121,7 +125,7 @@ __device__ __forceinline__ void few_epilogue(const SkinnyArgs& g, int ct, const 
 
 // MT row tiles of 16 per work-group, NW wavefronts, U k-chunks (of 32) per wavefront in a batch; with DB the next batch's loads
 // are in flight while a batch is multiplied.
-template <int MT, int NW, int U, bool DB, bool FRAG, bool CELL>
+template <int MT, int NW, int U, bool DB, bool FRAG, bool CELL, bool ANY>
 __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
   static_assert(U % 2 == 0, "chunks come in pairs: 128 bytes of a row");
   __shared__ float red[NW][MT][16][17];                        // [wavefront][row tile][row][column]
@@ -135,6 +139,10 @@ __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
   // the packed rows hold there; both end in output rows that are not stored.
   const int col = r16 & (ct - 1);
   const int nkc = (K + 31) / 32;
+  // ANY: a lane's eight k that K ends in or in front of are K's last eight, and masks leave of them what no other lane has; its lowest half word is element 8 - K % 8.
+  u32x4 tail;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) tail[e] = (2 * e >= 8 - (K & 7) ? 0xffffu : 0u) | (2 * e + 1 >= 8 - (K & 7) ? 0xffff0000u : 0u);
   const long a_bytes = FRAG ? (long)((g.M + 15) / 16) * nkc * 1024 : (long)g.M * g.lda * 2;
   const long b_bytes = FRAG ? (long)((CELL ? (g.n + 3) / 4 : (g.N + 15) / 16)) * nkc * 1024 : (long)g.N * g.ldb * 2;
   const auto rec = [](long bytes) { return (int)(bytes > 0x7fffff00L ? 0x7fffff00L : bytes); };
@@ -147,10 +155,12 @@ __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
 #pragma unroll
     for (int i = 0; i < MT; ++i) ao[i] = (unsigned)((long)min((m0 >> 4) + i, (g.M - 1) >> 4) * nkc * 1024) + (unsigned)lane * 16u;
   } else {
-    bo = (unsigned)((long)min(n0 + col, g.N - 1) * g.ldb * 2) + gk * 16u;
+    bo = (unsigned)((long)min(n0 + col, g.N - 1) * g.ldb * 2) + (ANY ? 0u : gk * 16u);
 #pragma unroll
-    for (int i = 0; i < MT; ++i) ao[i] = (unsigned)((long)min(m0 + 16 * i + r16, g.M - 1) * g.lda * 2) + gk * 16u;
+    for (int i = 0; i < MT; ++i) ao[i] = (unsigned)((long)min(m0 + 16 * i + r16, g.M - 1) * g.lda * 2) + (ANY ? 0u : gk * 16u);
   }
+
+  const char *pa = g.A + g.sAz * z * 2, *pb = g.B + g.sBz * z * 2;
 
   f32x4 acc[MT];
 #pragma unroll
@@ -158,7 +168,7 @@ __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
   // every work-group reads all of A: those of an XCD start at different places, so that they do not ask its L2 for the same
   // lines at the same time
   const int rot = (int)(((long)((blockIdx.x >> 3) & 31) * npair) >> 5);
-  struct Batch { u32x4 a[U][MT], b[U]; };
+  struct Batch { u32x4 a[U][MT], b[U]; int k[ANY ? U : 1]; };
   // Chunk j of a batch that starts at pair p: pair p + NW (j / 2), half j % 2.  A chunk past K arrives as zeros (both operands:
   // the other one may hold anything there).
   auto load = [&](Batch& x, int p) __attribute__((always_inline)) {
@@ -166,6 +176,14 @@ __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
     for (int j = 0; j < U; ++j) {
       const int q = p + NW * (j >> 1), kp = q + rot;
       const int kc = q < npair ? 2 * (kp < npair ? kp : kp - npair) + (j & 1) : 0x1000000;
+      if constexpr (ANY) {
+        x.k[j] = kc * 32 + gk * 8;
+        const unsigned col = (unsigned)min(x.k[j], K - 8) * 2u;
+        x.b[j] = __builtin_bit_cast(u32x4, *(const uint4_u*)(pb + (bo + col)));
+#pragma unroll
+        for (int i = 0; i < MT; ++i) x.a[j][i] = __builtin_bit_cast(u32x4, *(const uint4_u*)(pa + (ao[i] + col)));
+        continue;
+      }
       const bool in = kc * 32 + gk * 8 < K;
       x.b[j] = __builtin_amdgcn_raw_buffer_load_b128(rb, in ? bo + (unsigned)kc * kChunk : kParked, 0, 0);
 #pragma unroll
@@ -174,9 +192,15 @@ __global__ __launch_bounds__(64 * NW) void few_kernel(SkinnyArgs g, int ct) {
   };
   auto multiply = [&](const Batch& x) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < U; ++j)
+    for (int j = 0; j < U; ++j) {
+      u32x4 keep = {~0u, ~0u, ~0u, ~0u};                       // (of both operands: what a row holds twice may be infinite)
+      if constexpr (ANY) {
 #pragma unroll
-      for (int i = 0; i < MT; ++i) acc[i] = mma16(x.a[j][i], x.b[j], acc[i]);
+        for (int e = 0; e < 4; ++e) keep[e] = x.k[j] + 8 <= K ? ~0u : x.k[j] < K ? tail[e] : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[i] = ANY ? mma16(x.a[j][i] & keep, x.b[j] & keep, acc[i]) : mma16(x.a[j][i], x.b[j], acc[i]);
+    }
   };
   constexpr int kAdvance = NW * U / 2;                         // pairs per batch of all wavefronts
   if constexpr (DB) {
@@ -291,18 +315,26 @@ __global__ __launch_bounds__(1024) void few_gather_kernel(SkinnyArgs g, ConcatAr
   few_epilogue<1, NW, CELL>(g, ct, red);
 }
 
-template <int MT, int NW, int U, bool DB, bool FRAG, bool CELL>
+template <int MT, int NW, int U, bool DB, bool FRAG, bool CELL, bool ANY>
 hipError_t launch_as(const SkinnyArgs& a, int ct, int tiles_n, hipStream_t s) {
-  hipLaunchKernelGGL((few_kernel<MT, NW, U, DB, FRAG, CELL>), dim3(tiles_n, cdiv(a.M, 16 * MT), a.nz), dim3(64 * NW), 0, s, a, ct);
+  hipLaunchKernelGGL((few_kernel<MT, NW, U, DB, FRAG, CELL, ANY>), dim3(tiles_n, cdiv(a.M, 16 * MT), a.nz), dim3(64 * NW), 0, s, a, ct);
   return hipGetLastError();
 }
 // Four wavefronts, eight chunks each, hold K = 1024 in one batch; a longer K takes sixteen.
-template <bool FRAG, bool CELL>
+template <bool FRAG, bool CELL, bool ANY = false>
 hipError_t launch_rows(const SkinnyArgs& a, int ct, int tiles_n, hipStream_t s) {
   const bool longk = a.K > 1024;
-  if (a.M <= 16) return longk ? launch_as<1, 16, 8, false, FRAG, CELL>(a, ct, tiles_n, s) : launch_as<1, 4, 8, false, FRAG, CELL>(a, ct, tiles_n, s);
-  if (a.M <= 32) return longk ? launch_as<2, 16, 4, true, FRAG, CELL>(a, ct, tiles_n, s) : launch_as<2, 4, 8, false, FRAG, CELL>(a, ct, tiles_n, s);
-  return longk ? launch_as<4, 16, 2, true, FRAG, CELL>(a, ct, tiles_n, s) : launch_as<4, 4, 8, false, FRAG, CELL>(a, ct, tiles_n, s);
+  if constexpr (ANY) {
+    if (a.K <= 512) {
+      if (a.M <= 16) return launch_as<1, 4, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+      if (a.M <= 32) return launch_as<2, 4, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+      return launch_as<4, 4, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    }
+    if (a.M <= 16 && longk && a.K <= 2048) return launch_as<1, 16, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+  }
+  if (a.M <= 16) return longk ? launch_as<1, 16, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<1, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+  if (a.M <= 32) return longk ? launch_as<2, 16, 4, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<2, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+  return longk ? launch_as<4, 16, 2, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<4, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
 }
 
 // Weights of the stepped cell: tile t holds the gates of units 4 t .. 4 t + 3 (column 4 q + u), k runs over [x | 0 | h | 0].
@@ -393,6 +425,39 @@ int few_columns(int M, int N) {
 hipError_t launch_few(const SkinnyArgs& a, hipStream_t s) {
   const int ct = few_columns(a.M, a.N);
   return a.frag ? launch_rows<true, false>(a, ct, cdiv(a.N, ct), s) : launch_rows<false, false>(a, ct, cdiv(a.N, ct), s);
+}
+
+// columns of a work-group: as few as still give one round of compute units
+static int any_columns(long M, long N, int nz) {
+  const long blocks = (long)cdiv(M, 64) * nz;
+  return blocks * cdiv(N, 4) <= 256 ? 4 : blocks * cdiv(N, 8) <= 256 ? 8 : 16;
+}
+// Both sides estimated from measurements (us; 2 to 1024 rows, 263 to 32000 columns, 24 lengths of K from 60 to 4050, 4060 products).  Here: rounds of work-groups times what
+// a wavefront loads, twice or three times as much if every other row begins inside a word (K odd); the other kernels: hardly anything but K.  It has to look a fifth faster (for
+// K > 1024, whose rounds vary more, two fifths): slower choices are then 26 of those products, by 8 % in the median, and what is left behind is 1.25 times this.
+// us, before / here: K = 334, N = 1000 10.5 / 5.0 for up to 256 rows, 12.1 / 8.1 for 768; K = 1003 20.4 / 6.0 for 4 rows, 22.6 / 13.4 for 64; K = 1012 (rows of whole 8 bytes) 11.7 / 4.9 for 4, 14.6 /
+// 6.3 for 128; K = 505, N = 2787 13.1 / 7 for 16; K = 803, N = 20000 18.4 / 17.7 for 4 and 20.7 / 51 for 64, which stay where they were.
+bool few_any_ok(const GemmArgs& g) {
+  const long lim = 0x7fffff00L;                                // operands are addressed with 32-bit byte offsets
+  if (g.M > kSkinnyMaxRows || !g.in_bf16 || !g.a_kcontig || !g.b_kcontig || g.lens || g.nseg != 1 || g.a_rows || g.c_rows || g.m_dev || g.k_dev || g.accumulate || g.parts || g.K < 8 ||
+      ((long)g.M * g.lda + g.K) * 2 > lim || ((long)g.N * g.ldb + g.K) * 2 > lim)
+    return false;
+  const long M = g.M, groups = (long)cdiv(M, 64) * g.nz * cdiv(g.N, any_columns(M, g.N, g.nz));
+  const int waves = g.K <= 1024 ? 4 : 16, deep = g.K <= 512 ? 4 : g.K <= 1024 ? 8 : M <= 16 ? (g.K <= 2048 ? 4 : 8) : M <= 32 ? 4 : 2;
+  const double loads = (groups > 512 ? groups / 256. : (double)cdiv(groups, 256)) * waves * deep * cdiv(cdiv(g.K, 32), waves * deep), rows = (M < 64 ? M : 64) / 16.;
+  const bool odd = ((g.lda | g.ldb) & 1) || (((uintptr_t)g.A | (uintptr_t)g.B) & 3);
+  const double here = odd ? std::max(5.2, 3.6 + loads * (0.068 + 0.052 * rows)) : std::max(5.2, 4.2 + loads * (0.020 + 0.0155 * rows));
+  const double there = gemm_tile_ok(g) ? 5.8 + 0.006 * g.K + 0.03 * (M < 128 ? M : 128) : (odd ? 5.6 : 6.0) + 0.0145 * g.K;
+  return (g.K > 1024 ? 1.4 : 1.2) * here < there;
+}
+hipError_t launch_few_any(const GemmArgs& g, hipStream_t s) {
+  SkinnyArgs a = {};
+  a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
+  a.M = g.M; a.N = g.N; a.K = g.K; a.lda = g.lda; a.ldb = g.ldb; a.ldc = g.ldc;
+  a.sAz = g.sAz; a.sBz = g.sBz; a.sCz = g.sCz; a.sbiasz = g.sbiasz; a.nz = g.nz;
+  a.out_bf16 = g.out_bf16;
+  const int ct = any_columns(a.M, a.N, a.nz);
+  return launch_rows<false, false, true>(a, ct, cdiv(a.N, ct), s);
 }
 
 hipError_t launch_pack_cell_frag(const void* W_x, const void* W_h, void* out, int n_in, int n_in_pad, int n, int K, int ndir, hipStream_t s) {

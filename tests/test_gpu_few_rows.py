@@ -82,6 +82,30 @@ def test_product_on_each_side_of_the_route(M, N, K):
     assert ((C.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-4 * K ** 0.5).all()
 
 
+@pytest.mark.parametrize("M,N,K,gap,at", [(1, 20, 8, 0, 0), (7, 401, 9, 0, 1), (16, 1000, 334, 0, 0), (17, 401, 333, 2, 3), (32, 2787, 505, 0, 0), (33, 700, 510, 4, 2), (64, 1000, 1003, 1, 1),
+                                          (65, 263, 1012, 0, 0), (192, 700, 31, 0, 0), (4, 8000, 612, 0, 0), (12, 50, 1025, 1, 0), (16, 33, 2046, 3, 1), (16, 33, 2051, 0, 0), (24, 40, 1999, 0, 1),
+                                          (40, 70, 4001, 0, 0), (300, 257, 130, 8, 5), (768, 1000, 334, 0, 0), (1000, 1000, 701, 0, 0)])
+def test_product_of_rows_at_any_element(M, N, K, gap, at):
+    """Rows of any length, distance and first element, either side of few_any_ok; what lies between and around the rows is NaN and takes no part."""
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(M + N + K)
+
+    def rows(count):
+        v, ld = _bf(rng, count, K), K + gap
+        flat = torch.full((at + count * ld + 16,), float("nan"), dtype=torch.bfloat16)
+        flat[at:at + count * ld].view(count, ld)[:, :K] = v
+        return v.double().numpy(), flat.cuda()
+    (a, A), (b, B), bias = rows(M), rows(N), rng.uniform(-1, 1, N)
+    bias_d, want = dev(bias), a @ b.T + bias
+    for out in (torch.float32, torch.bfloat16):
+        C = torch.full((M, N + 1), 7., dtype=out, device="cuda")
+        assert Bn.lib.lstm_gemm(1, out == torch.bfloat16, 1, 1, M, N, K, A.data_ptr() + 2 * at, K + gap, B.data_ptr() + 2 * at, K + gap, C.data_ptr(), N + 1,
+                                bias_d.data_ptr(), 0, None, 1, 0, Bn._stream()) == 0
+        torch.cuda.synchronize()
+        check("C", C[:, :N].contiguous(), want, 1e-4 if out == torch.float32 else 5e-3)
+        assert (C[:, N] == 7.).all()
+
+
 @pytest.mark.parametrize("B,n_in,n", [(1, 64, 64), (12, 2620, 1000), (16, 300, 104), (17, 300, 104), (193, 64, 66)])
 def test_stepped_cell_in_place(B, n_in, n):
     """hT = h0 and cT = c0: every work-group needs all of h, so none may store its part before the others have read it."""
