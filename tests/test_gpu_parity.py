@@ -452,7 +452,8 @@ def test_single_launch_random_shapes_bf16():
 
 # ---- max-pooling in time between encoder layers: exact operation, bit-exact bar ---------------------------------
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
-@pytest.mark.parametrize("T,B,F,pool", [(9, 4, 16, 2), (7, 3, 5, 3), (1, 2, 8, 2), (40, 33, 2048, 2), (13, 5, 264, 4), (6, 2, 24, 1)])
+@pytest.mark.parametrize("T,B,F,pool", [(9, 4, 16, 2), (7, 3, 5, 3), (1, 2, 8, 2), (40, 33, 2048, 2), (13, 5, 264, 4), (6, 2, 24, 1),
+                                        (13, 2, 1114, 2), (97, 21, 660, 2), (40, 33, 1114, 2), (41, 30, 602, 3), (5, 2, 513, 2)])   # rows of whole words; either side of 256 work-groups
 def test_time_pool_matches_oracle_exactly(dt, T, B, F, pool):
     rng = np.random.default_rng(T * 1000 + F + pool)
     lens = rng.integers(0, T + 1, B)
