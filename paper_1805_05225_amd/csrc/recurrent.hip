@@ -9,7 +9,7 @@
 // (forward: 8 units = 32 columns for 32 batch rows; backward: 16 units for 16 batch rows).  So the cell update
 // is local to the work-group and only h_t (forward) or dz_t (backward) crosses work-groups
 // between steps.  The small-M product runs on MFMA 16x16 tiles with the K axis split over the
-// four wavefronts, followed by a reduction through LDS and the pointwise epilogue.
+// wavefronts (four to sixteen), followed by a reduction through LDS and the pointwise epilogue.
 //
 // Operands are kept in "fragment order": the exact register image of an MFMA operand, one
 // 16-byte chunk per lane, so every operand load is one fully coalesced 1 KiB read per wavefront:
@@ -42,9 +42,9 @@ inline int step_grid(int ntile, int nrb, int ndir) { return ndir * ((ntile + 7) 
 
 // ------------------------------------------------------------------------------------------------
 // forward step
-template <typename T>
-__global__ __launch_bounds__(256) void step_fwd_kernel(FwdArgs a) {
-  __shared__ float red[4][32][33];
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void step_fwd_kernel(FwdArgs a) {
+  __shared__ float red[NW][32][33];
   const StepCoord sc = step_coord((a.n + 7) / 8, (a.B + 31) / 32);
   if (!sc.live) return;
   const FwdDir& d = a.d[sc.dir];
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(FwdArgs a) {
   const uint4* wB0 = d.Wf + ((long)(tile * 2 + 0) * nkc) * 64 + lane;
   const uint4* wB1 = d.Wf + ((long)(tile * 2 + 1) * nkc) * 64 + lane;
 #pragma unroll 4
-  for (int kc = wave; kc < nkc; kc += 4) {
+  for (int kc = wave; kc < nkc; kc += NW) {
     uint4 a0 = hA0[(long)kc * 64], a1 = hA1[(long)kc * 64];
     uint4 b0 = wB0[(long)kc * 64], b1 = wB1[(long)kc * 64];
     acc[0][0] = Mma16<T>::run(a0, b0, acc[0][0]);
@@ -80,12 +80,16 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(FwdArgs a) {
       for (int v = 0; v < 4; ++v) red[wave][i * 16 + 4 * (lane >> 4) + v][j * 16 + (lane & 15)] = acc[i][j][v];
   __syncthreads();
 
-  const int r = tid >> 3, u = tid & 7;
+  const int r = tid >> 3, u = tid & 7;                         // (r < 32: the first four wavefronts)
   const int b = rb * 32 + r, j = tile * 8 + u;
-  if (b >= a.B || j >= a.n) return;
+  if (r >= 32 || b >= a.B || j >= a.n) return;
   float z[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) z[q] = red[0][r][q * 8 + u] + red[1][r][q * 8 + u] + red[2][r][q * 8 + u] + red[3][r][q * 8 + u];
+  for (int q = 0; q < 4; ++q) {
+    z[q] = red[0][r][q * 8 + u];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) z[q] += red[w][r][q * 8 + u];
+  }
 
   const int n = a.n;
   const bool valid = d.t < clamp_len(a.lens, b, a.T);
@@ -113,9 +117,9 @@ __global__ __launch_bounds__(256) void step_fwd_kernel(FwdArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // backward step: a work-group owns 16 units for one tile of 16 batch rows
-template <typename T>
-__global__ __launch_bounds__(256) void step_bwd_kernel(BwdArgs a) {
-  __shared__ float red[4][16][17];
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void step_bwd_kernel(BwdArgs a) {
+  __shared__ float red[NW][16][17];
   const StepCoord sc = step_coord((a.n + 15) / 16, (a.B + 15) / 16);
   if (!sc.live) return;
   const BwdDir& d = a.d[sc.dir];
@@ -128,7 +132,7 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(BwdArgs a) {
     const uint4* Ap = d.dzin + ((long)rt * nkc) * 64 + lane;
     const uint4* Bp = d.Wb + ((long)tile * nkc) * 64 + lane;
 #pragma unroll 8
-    for (int kc = wave; kc < nkc; kc += 4) acc = Mma16<T>::run(Ap[(long)kc * 64], Bp[(long)kc * 64], acc);
+    for (int kc = wave; kc < nkc; kc += NW) acc = Mma16<T>::run(Ap[(long)kc * 64], Bp[(long)kc * 64], acc);
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[wave][4 * (lane >> 4) + v][lane & 15] = acc[v];
   }
@@ -136,10 +140,14 @@ __global__ __launch_bounds__(256) void step_bwd_kernel(BwdArgs a) {
 
   const int r = tid >> 4, u = tid & 15;
   const int b = rt * 16 + r, j = tile * 16 + u;
-  if (b >= a.B || j >= n) return;
+  if (r >= 16 || b >= a.B || j >= n) return;
   const int L = clamp_len(a.lens, b, a.T);
   float Dh = d.Dh[(long)b * n + j];
-  if (a.do_matmul && d.t_next < L) Dh = red[0][r][u] + red[1][r][u] + red[2][r][u] + red[3][r][u];
+  if (a.do_matmul && d.t_next < L) {
+    Dh = red[0][r][u];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) Dh += red[w][r][u];
+  }
   d.Dh[(long)b * n + j] = Dh;
   if (!a.do_pointwise) return;
   float dz[4] = {0.f, 0.f, 0.f, 0.f};
@@ -254,16 +262,23 @@ __global__ void colsum_final_kernel(const float* part, float* db, int ncols, int
 
 }  // namespace
 
+// Wavefronts of a work-group: a step reads W_h, whose loads in flight are what a wavefront has, and few work-groups with four of them left most of the path to memory
+// idle.  us for 12 steps with set-up and products, 4 / 8 / 16 wavefronts, float: forward n = 2048, 16 rows, one direction 299 / 253 / 247, n = 1000, 64 rows, both 290 / 271 / 282, n = 512, 300 rows, both
+// (1280 work-groups) 332 / 350 / 378; backward 725 / 496 / 395, 538 / 431 / 407, 508 / 509 / 526.  In bfloat16: forward n = 2304, 16 rows, one direction 183 / 199 / 218; backward
+// 431 / 324 / 263, both directions (288 work-groups) 485 / 379 / 437, 64 rows (1152) 611 / 657 / 662.
 hipError_t launch_step_fwd(const FwdArgs& a, bool bf16, hipStream_t s) {
-  dim3 grid(step_grid(cdiv(a.n, 8), cdiv(a.B, 32), a.ndir)), block(256);
-  if (bf16) hipLaunchKernelGGL(step_fwd_kernel<bf16_t>, grid, block, 0, s, a);
-  else hipLaunchKernelGGL(step_fwd_kernel<float>, grid, block, 0, s, a);
+  const int blocks = step_grid(cdiv(a.n, 8), cdiv(a.B, 32), a.ndir);
+  if (bf16) hipLaunchKernelGGL((step_fwd_kernel<bf16_t, 4>), dim3(blocks), dim3(256), 0, s, a);
+  else if (blocks <= 1024) hipLaunchKernelGGL((step_fwd_kernel<float, 8>), dim3(blocks), dim3(512), 0, s, a);
+  else hipLaunchKernelGGL((step_fwd_kernel<float, 4>), dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_step_bwd(const BwdArgs& a, bool bf16, hipStream_t s) {
-  dim3 grid(step_grid(cdiv(a.n, 16), cdiv(a.B, 16), a.ndir)), block(256);
-  if (bf16) hipLaunchKernelGGL(step_bwd_kernel<bf16_t>, grid, block, 0, s, a);
-  else hipLaunchKernelGGL(step_bwd_kernel<float>, grid, block, 0, s, a);
+  const int blocks = step_grid(cdiv(a.n, 16), cdiv(a.B, 16), a.ndir);
+  const int waves = blocks <= (bf16 ? 256 : 1024) ? 16 : blocks <= 1024 ? 8 : 4;
+  const auto kernel = bf16 ? (waves == 16 ? step_bwd_kernel<bf16_t, 16> : waves == 8 ? step_bwd_kernel<bf16_t, 8> : step_bwd_kernel<bf16_t, 4>)
+                           : waves == 16 ? step_bwd_kernel<float, 16> : step_bwd_kernel<float, 4>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * waves), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_pack_wh_fwd(const void* W, uint4* Wf, int n, int nkc, int ndir, bool bf16, hipStream_t s) {
