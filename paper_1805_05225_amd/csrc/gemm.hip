@@ -15,6 +15,7 @@
 // stored with m / n contiguous are transposed in registers on their way into LDS.  Global loads
 // for tile i+1 are issued before the MFMAs of tile i (register staging, two LDS buffers).
 #include "common.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace lstm {
@@ -353,30 +354,74 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
   }
 }
 
-// k-contiguous operands of less than a chunk: a thread per element of C
-template <typename T, typename TC>
-__global__ __launch_bounds__(256) void short_kernel(GemmArgs g) {
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  const int m = (int)(idx / g.N), n = (int)(idx - (long)m * g.N), z = blockIdx.y;
-  if (m >= (g.m_dev ? min(g.M, *g.m_dev) : g.M)) return;
-  const int K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
-  float v = g.bias ? g.bias[g.sbiasz * z + n] : 0.f;
-  for (int seg = 0; seg < g.nseg; ++seg)
-    for (int k = 0; k < K; ++k) {
-      const long b_at = g.b_kcontig ? (long)n * g.ldb + k : (long)k * g.ldb + n;
-      v += Store<T>::load(g.A, g.sAz * z + g.sAseg * seg + (long)(g.a_rows ? g.a_rows[m] : m) * g.lda + k) * Store<T>::load(g.B, g.sBz * z + g.sBseg * seg + b_at);
+// k-contiguous operands of less than a chunk, K < 16 / sizeof(T): little more than storing C.  A thread owns a column and R rows of a tile of `cols` columns: its column of B in
+// registers, the tile's rows of A in LDS, from where a wavefront's rows are read by all lanes at once.  (A thread per element of C, which read both operands from memory and divided to find its
+// place, took longer than the 128 x 128 tiles of gemm_kernel from a million elements on, and its grid ended at 2^32 of them: what lay behind was not written.)  us, gemm_kernel / a thread per element / so, K = 4 and
+// 7, bfloat16 into float: 4096 x 4096 33.5 / 59.5 / 30.2 and 37.5 / 81 / 31; 768 x 20000 33.8 / 53.9 / 28.1 and 38.3 / 71.6 / 29.0; 64 x 1000 15.0 / 3.8 / 4.1 and 16.5 / 3.9 / 4.2.
+constexpr int kShortGrid = 1 << 16;
+template <typename T, typename TC, int R>
+__global__ __launch_bounds__(256) void short_kernel(GemmArgs g, int cols, long tiles_n, long tiles) {
+  constexpr int E = 16 / (int)sizeof(T);
+  __shared__ __attribute__((aligned(16))) float a[256][E];                     // (at most 16 rows a thread, and at least 16 columns: 256 rows)
+  const int tid = threadIdx.x, z = blockIdx.y, c = tid & (cols - 1), r0 = tid / cols, par = 256 / cols, rows = R * par;
+  const int M = g.m_dev ? min(g.M, *g.m_dev) : g.M, K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
+  for (long t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const long tm = t / tiles_n, m0 = tm * rows, n = (t - tm * tiles_n) * cols + c;
+    if (m0 >= M) return;
+    float acc[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) acc[i] = g.bias && n < g.N ? g.bias[g.sbiasz * z + n] : 0.f;
+    for (int seg = 0; seg < g.nseg; ++seg) {
+      __syncthreads();                                                        // (what is in LDS has been read)
+      for (int i = tid; i < rows * E; i += 256) {
+        const long m = m0 + i / E;
+        const int k = i % E;
+        a[i / E][k] = m < M && k < K ? Store<T>::load(g.A, g.sAz * z + g.sAseg * seg + (g.a_rows ? g.a_rows[m] : m) * g.lda + k) : 0.f;
+      }
+      float b[E];
+#pragma unroll
+      for (int k = 0; k < E; ++k)
+        b[k] = n < g.N && k < K ? Store<T>::load(g.B, g.sBz * z + g.sBseg * seg + (g.b_kcontig ? n * g.ldb + k : k * g.ldb + n)) : 0.f;
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int k = 0; k < E; ++k) acc[i] += a[i * par + r0][k] * b[k];
     }
-  const long off = g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
-  if (g.accumulate) v += Store<TC>::load(g.C, off);
-  Store<TC>::store(g.C, off, v);
+    if (n >= g.N) continue;
+    long off[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const long m = std::min(m0 + i * par + r0, M - 1L);
+      off[i] = g.sCz * z + (g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
+    }
+    if (g.accumulate) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) acc[i] += Store<TC>::load(g.C, off[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      if (m0 + i * par + r0 < M) Store<TC>::store(g.C, off[i], acc[i]);
+  }
+}
+template <typename T, typename TC>
+hipError_t launch_short(const GemmArgs& g, hipStream_t s) {
+  int cols = 16;
+  while (cols < 256 && cols < g.N) cols *= 2;
+  const int par = 256 / cols;
+  const long size = (long)g.M * g.N * g.nz;
+  const int r = g.M >= 16 * par && size >= 1L << 20 ? 16 : g.M >= 4 * par && size >= 1L << 18 ? 4 : 1;      // rows a thread, while there are work-groups for the device
+  const long tiles_n = ((long)g.N + cols - 1) / cols, tiles = tiles_n * (((long)g.M + r * par - 1) / (r * par));
+  const dim3 grid((unsigned)std::min(tiles, (long)kShortGrid), g.nz);
+  if (r == 16) hipLaunchKernelGGL((short_kernel<T, TC, 16>), grid, dim3(256), 0, s, g, cols, tiles_n, tiles);
+  else if (r == 4) hipLaunchKernelGGL((short_kernel<T, TC, 4>), grid, dim3(256), 0, s, g, cols, tiles_n, tiles);
+  else hipLaunchKernelGGL((short_kernel<T, TC, 1>), grid, dim3(256), 0, s, g, cols, tiles_n, tiles);
+  return hipGetLastError();
 }
 
 template <typename T, typename TC>
 hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
-  if (g.a_kcontig && g.K < 16 / (int)sizeof(T)) {
-    hipLaunchKernelGGL((short_kernel<T, TC>), dim3(cdiv((long)g.M * g.N, 256), g.nz), dim3(256), 0, s, g);
-    return hipGetLastError();
-  }
+  if (g.a_kcontig && g.K < 16 / (int)sizeof(T)) return launch_short<T, TC>(g, s);
   const int tiles_m = (g.M + kBM - 1) / kBM, tiles_n = (g.N + kBN - 1) / kBN;
   dim3 grid(tiles_m * tiles_n, g.nz), block(kThreads);
   if (g.a_kcontig && !g.b_kcontig) hipLaunchKernelGGL((gemm_kernel<T, TC, true, false, false>), grid, block, 0, s, g);

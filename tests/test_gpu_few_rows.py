@@ -106,6 +106,37 @@ def test_product_of_rows_at_any_element(M, N, K, gap, at):
         assert (C[:, N] == 7.).all()
 
 
+@pytest.mark.parametrize("dt,bk", [(torch.bfloat16, 1), (torch.bfloat16, 0), (torch.float32, 1), (torch.float32, 0)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 300, 2), (17, 5, 3), (64, 1000, 1), (255, 1025, 3), (2037, 515, 2), (4100, 257, 1), (70001, 17, 3)])
+def test_product_of_less_than_a_chunk(M, N, K, dt, bk):
+    """K below 16 bytes of a k-contiguous A; one, four and sixteen rows a thread, tiles of 16 to 256 columns, remainders of both; what lies behind the rows is NaN."""
+    from paper_1805_05225_amd import binding as Bn
+    K += 4 if dt == torch.bfloat16 and N % 2 else 0
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    rows = lambda r, k: torch.cat([torch.randn(r, k, generator=g, device="cuda"), torch.full((r, 1), float("nan"), device="cuda")], 1).to(dt)
+    A, B, bias = rows(M, K), rows(N, K) if bk else rows(K, N), torch.randn(N, generator=g, device="cuda")
+    a, b = A[:, :K].double(), (B[:, :K].T if bk else B[:, :N]).double()
+    for out, acc in ((torch.float32, 0), (torch.float32, 1)) + (((torch.bfloat16, 0),) if dt == torch.bfloat16 else ()):
+        C = torch.full((M, N + 1), 7., dtype=out, device="cuda")
+        assert Bn.lib.lstm_gemm(dt == torch.bfloat16, out == torch.bfloat16, 1, bk, M, N, K, A.data_ptr(), K + 1, B.data_ptr(), (K if bk else N) + 1, C.data_ptr(), N + 1,
+                                bias.data_ptr(), acc, None, 1, 0, Bn._stream()) == 0
+        want = a @ b + bias + (7. if acc else 0.)
+        # (at most seven products, the bias and what was there: eight sums of float; a result in bfloat16 is rounded once more)
+        bound = 9 * 2.0 ** -24 * (a.abs() @ b.abs() + bias.abs() + (7. if acc else 0.)) + (2.0 ** -8 * want.abs() if out == torch.bfloat16 else 0.)
+        assert ((C[:, :N].double() - want).abs() <= bound).all() and (C[:, N] == 7.).all()
+
+
+def test_product_of_less_than_a_chunk_over_more_than_2_to_32_elements():
+    from paper_1805_05225_amd import binding as Bn
+    M, N, K = 65600, 65552, 4
+    g = torch.Generator(device="cuda").manual_seed(1)
+    A, B = (torch.randn(r, K, generator=g, device="cuda").bfloat16() for r in (M, N))
+    C = Bn.gemm(A, B, a_kcontig=True, b_kcontig=True, M=M, N=N, K=K, out_dtype=torch.bfloat16)
+    for m0 in (0, 32768, M - 64):
+        want = A[m0:m0 + 64].double() @ B.double().T
+        assert ((C[m0:m0 + 64].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-6).all()
+
+
 @pytest.mark.parametrize("B,n_in,n", [(1, 64, 64), (12, 2620, 1000), (16, 300, 104), (17, 300, 104), (193, 64, 66)])
 def test_stepped_cell_in_place(B, n_in, n):
     """hT = h0 and cT = c0: every work-group needs all of h, so none may store its part before the others have read it."""
