@@ -3563,22 +3563,23 @@ int f32_rows_per_group(K kernel, int ntile, int B, int ndir) { return (long)ntil
 // 1387 us here, 838 there).  Both sides as they were measured, in us, for n from 130 to 1024, 1 to 512 rows, 2 to 60 steps, one and two
 // directions, plain and cooperative launches (1573 shapes): the choice was within 5 % of the faster side in 99 % of them and never 1.25 times
 // it; always the loops was up to 2.8 times the other.  The loops' side has been measured again since their products are bfloat16 parts (4 and 100 steps of 11
-// shapes): of 396 shapes of 2 to 24 steps the choice is within 5 % of the per-step kernels or faster in 95 %, never 1.16 times them. Their set-up is one launch since: of 480
-// shapes of 2 to 14 steps and 2 to 64 rows the choice is within 5 % of the faster side in all but 9, at most 1.25 times it (4 steps of 2 rows, n = 700, both directions, ordinary launches: 51 and
-// 92 us, forward and backward, per step 85 and 156).  A step's time goes with the form, cdiv(n, 128).  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
+// shapes): of 396 shapes of 2 to 24 steps the choice is within 5 % of the per-step kernels or faster in 95 %, never 1.16 times them.  With lengths given, a pair of row tiles is taken to have work for 0.8 of its steps.
+// Both sides have become faster since (a form for every 128 units and a set-up of one launch here, more wavefronts there), and the line has not moved with them: the loops carry sums of
+// 2^32 and more with 16 significant bits and add in the order of arrival, the per-step kernels keep 24 bits and repeat theirs, and no call is to lose that for a faster kernel.
+// A line by the present times gives the loops some calls more (us, per step / here: forward and backward of 4 steps of 2 rows, n = 700, both directions, ordinary launches 85 / 51 and 156 / 92).
 bool persist_f32_pays(int T, int B, int n, int ndir, bool lens, bool plain_launch, bool backward) {
-  const int form = std::min(std::max(cdiv(n, 128), 2), 8) - 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
+  const int form = n <= 256 ? 0 : n <= 512 ? 1 : 2, ntile = cdiv(n, 16), cap = backward ? capacity(bwd_f32_for(n)) : capacity(fwd_f32_for(n));
   const bool one = (long)ntile * cdiv(B, 16) * ndir <= cap, pair = !one && B > 16;
   const int launches = one ? 1 : cdiv(cdiv(B, 32), std::max(1, cap / (ntile * ndir)));
   const double w = (double)n * n / (1024.0 * 1024.0) * ndir, nr = (double)n * ndir * B * 1e-5, nnr = nr * n * 1e-3, part = lens && pair ? 0.8 : 1.0;
   double here, there;
   if (backward) {
-    const double step[2][7] = {{2.8, 3.7, 4.3, 5.7, 6.3, 6.8, 7.2}, {7.2, 8.3, 9.3, 16.2, 16.7, 17.4, 17.4}};
-    here = 14.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
+    const double step[2][3] = {{2.8, 4.3, 7.2}, {7.2, 9.3, 17.4}};
+    here = 34.0 + 18.0 * w + launches * (plain_launch ? 30.0 : 51.0) + launches * T * step[pair][form] * part;
     there = 58.3 + 16.0 * w + T * std::max(4.25 + 17.1e-3 * n + 6.6 * nr + 10.4 * nnr, 22.0 * nnr);
   } else {
-    const double step[2][7] = {{1.9, 2.4, 2.65, 3.25, 3.6, 4.0, 4.25}, {4.2, 5.5, 6.2, 7.3, 8.2, 8.8, 9.2}};
-    here = -0.5 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
+    const double step[2][3] = {{1.9, 2.65, 4.25}, {4.2, 6.2, 9.2}};
+    here = 19.0 + 11.7 * w + launches * (plain_launch ? 15.0 : 36.0) + launches * T * step[pair][form] * part;
     there = 27.9 + 7.8 * w + T * std::max(3.8 + 6.15e-3 * n + 4.15 * nr + 4.9 * nnr, 10.9 * nnr);
   }
   return here < there;

@@ -39,6 +39,25 @@ def test_wider_layer(T, B, n_in, n, bidir):
     _layer(T, B, n_in, n, bidir, "bf16")
 
 
+@pytest.mark.parametrize("T,B,n,bidir", [(3, 1, 500, True), (4, 4, 330, False), (6, 29, 134, True), (3, 40, 200, False), (2, 2, 330, True)])
+def test_float_calls_of_few_steps_keep_their_bits(T, B, n, bidir):
+    """Where few steps go to the per-step kernels, sums of gradients past 2^32 have all 24 bits and every result repeats: bit for bit as with FLAG_PER_STEP."""
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator(device="cuda").manual_seed(n)
+    D = 2 if bidir else 1
+    r = lambda w, *s: (torch.rand(*s, generator=g, device="cuda") * 2 - 1) * w
+    sq = lambda t: t if bidir else t[0]
+    x, Wx, Wh, b = r(1., T, B, 24), sq(r(.3, D, 24, 4 * n)), sq(r(.3, D, n, 4 * n)), sq(r(.1, D, 4 * n))
+    dy = r(2. ** 40, T, B, D * n)
+
+    def run(flags):
+        f = Bn.forward(x, Wx, Wh, b, bidirectional=bidir, flags=flags)
+        return dict(Bn.backward(f, x, Wx, Wh, None, None, None, dy), **{k: f[k].clone() for k in ("y", "c", "hT", "cT")})
+    got, want = run(0), run(Bn.FLAG_PER_STEP)
+    for k in want:
+        assert torch.isfinite(want[k]).all() and torch.equal(got[k], want[k]), k
+
+
 @pytest.mark.parametrize("T,B,n_in,n,bidir", [
     (60, 7, 333, 263, True), (30, 21, 200, 443, True), (9, 3, 8, 1003, False), (40, 10, 123, 201, False),
     (52, 64, 60, 1001, True),                                               # the input projection in many tiles
