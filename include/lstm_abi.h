@@ -296,7 +296,7 @@ int lstm_embed(int B, int n, int V, const int32_t* label, const void* W_trg, con
  * other between time steps with BOUNDED waits.  If a wait ever expired, the kernel drained early, the
  * results of that call are invalid and a word in the workspace says so.  This call copies that word
  * to the host (it SYNCHRONISES the device) and stores 1 in *timed_out if it is set, else 0.  It refers
- * to the last *_fwd / *_bwd call that used `workspace` (every call clears the word first). */
+ * to the last *_fwd / *_bwd call of B > 0 that used `workspace` (every such call clears the word first). */
 int lstm_sync_status(const void* workspace, int32_t* timed_out);
 
 /* Phase timing for benchmarks.  While enabled, every *_fwd / *_bwd call brackets its phases with

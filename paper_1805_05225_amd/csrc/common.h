@@ -461,12 +461,12 @@ hipError_t launch_concat_xh(const void* x, const float* h, void* Acat, int B, in
 inline size_t wcell_rows(int n) { return (size_t)128 * ((n + 31) / 32); }
 hipError_t launch_pack_wcell(const void* W_x, const void* W_h, void* Wcell, int n_in, int n_in_pad, int n, int Kc, int ndir, hipStream_t s);
 hipError_t launch_step_cell(const void* Acat, const void* Wcell, const float* bias, const float* h_in, const float* c_in, float* h_out,
-                            float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n, int Kc, int ndir, hipStream_t s);
+                            float* c_out, void* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n, int Kc, int ndir, hipStream_t s);
 // The same step for a handful of rows (gemm_few.hip, few_cell_pays): weights packed in MFMA fragment order (at most wcell_rows(n) x Kc
 // elements per direction), K = n_in_pad + n; A is scratch for the concatenated rows in the same order.
 hipError_t launch_pack_cell_frag(const void* W_x, const void* W_h, void* out, int n_in, int n_in_pad, int n, int K, int ndir, hipStream_t s);
 hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void* Wfrag, const float* bias, const float* c_in, float* h_out,
-                           float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n_in, int n_in_pad, int n, int ndir, hipStream_t s);
+                           float* c_out, void* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n_in, int n_in_pad, int n, int ndir, hipStream_t s);
 // out[B][R] = bf16(max(0, [x0 | x1 | x2] W^T + bias)), W in the fragment order of launch_pack_rows_both, A scratch of frag_bytes(B, K)
 hipError_t launch_pack_rows_both(const void* W, void* rows, void* frag, int R, int K, int Kp, hipStream_t s);
 hipError_t launch_few_readout(const void* x0, long ld0, int k0, const void* x1, long ld1, int k1, const void* x2, long ld2, int k2, void* A,
@@ -477,7 +477,7 @@ inline size_t frag_bytes(long rows, long K) { return (size_t)((rows + 15) / 16) 
 // leaving it (NULL = not wanted); y[B][ldy] (direction d at column d*n); cs[ndir][B][n] or NULL; rows with lens[b] < 1
 // keep their state and output zero
 hipError_t launch_cell_step(const float* z, long part, int nparts, const float* bias, const float* h_in, const float* c_in, float* h_out,
-                            float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n, int ndir, hipStream_t s);
+                            float* c_out, void* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n, int ndir, hipStream_t s);
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 

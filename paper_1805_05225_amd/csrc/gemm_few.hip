@@ -83,6 +83,7 @@ template <int MT, int NW, bool CELL>
 __device__ __forceinline__ void few_epilogue(const SkinnyArgs& g, int ct, const float (&red)[NW][MT][16][17]) {
   const int tid = threadIdx.x, z = blockIdx.z, m0 = blockIdx.y * (16 * MT), n0 = blockIdx.x * ct;
   if constexpr (CELL) {
+    if (tid == 0 && (blockIdx.x | blockIdx.y | blockIdx.z) == 0) *g.status = 0u;
     // thread -> (row, unit of four)
     for (int idx = tid; idx < MT * 64; idx += 64 * NW) {
       const int u = idx & 3, row = idx >> 2, b = m0 + row, j = blockIdx.x * 4 + u, n = g.n;
@@ -474,7 +475,7 @@ hipError_t launch_pack_rows_both(const void* W, void* rows, void* frag, int R, i
 }
 
 hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void* Wfrag, const float* bias, const float* c_in, float* h_out,
-                           float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n_in, int n_in_pad, int n, int ndir, hipStream_t s) {
+                           float* c_out, void* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n_in, int n_in_pad, int n, int ndir, hipStream_t s) {
   const int K = n_in_pad + n, nkc = cdiv(K, 32);
   ConcatArgs c = {};
   c.x0 = (const uint16_t*)x; c.ld0 = n_in; c.k0 = 0; c.len0 = n_in;
@@ -485,7 +486,7 @@ hipError_t launch_few_cell(const void* x, const float* h_in, void* A, const void
   SkinnyArgs a = {};
   a.A = (const char*)A; a.B = (const char*)Wfrag; a.bias = bias; a.M = B; a.N = 4 * n; a.K = K; a.frag = 1;
   a.sAz = (long)cdiv(B, 16) * nkc * 512; a.sBz = (long)cdiv(n, 4) * nkc * 512; a.nz = ndir;
-  a.n = n; a.h_in = h_in; a.c_in = c_in; a.h_out = h_out; a.c_out = c_out; a.y = (uint16_t*)y; a.ldy = ldy; a.cs = cs; a.lens = lens;
+  a.n = n; a.h_in = h_in; a.c_in = c_in; a.h_out = h_out; a.c_out = c_out; a.y = (uint16_t*)y; a.ldy = ldy; a.cs = cs; a.lens = lens; a.status = status;
   const size_t state = (size_t)ndir * B * n * 4;
   bool in_place = false;
   for (const void* o : {(const void*)h_out, (const void*)c_out, (const void*)cs})

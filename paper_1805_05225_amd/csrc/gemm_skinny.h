@@ -16,6 +16,7 @@ struct SkinnyArgs {
   // cell epilogue (cell != 0): N = 128 * ceil(n / 32), column 128 * tile + 32 * gate + unit; bias is [4n] gate-major
   int cell, n;
   const float* h_in; const float* c_in; float* h_out; float* c_out; uint16_t* y; long ldy; float* cs; const int* lens;
+  unsigned* status;                      // cleared: nothing in a step waits for another work-group (lstm_sync_status)
 };
 // gemm_few.hip: C = A B^T for a handful of rows.  The limits lie where it stops being the faster kernel (us here / in gemm_skinny.hip,
 // concatenation included).  Cell: a work-group is 4 units of 64 rows, and more than 360 of them (a second round, in part) cost more than the other

@@ -317,6 +317,7 @@ __global__ __launch_bounds__(512) void skinny_kernel(SkinnyArgs g) {
   } else {
     // thread -> (unit of the tile, row): a thread per unit and row, 512 / kUnits rows per pass; staged columns kUnits q + unit
     const int uu = tid % kUnits, j = tl.tn * kUnits + uu, n = g.n;
+    if (tid == 0 && (blockIdx.x | blockIdx.z) == 0) *g.status = 0u;
     if (j < n) {
       float bv[4] = {0.f, 0.f, 0.f, 0.f};
       if (g.bias) {
@@ -481,13 +482,13 @@ hipError_t launch_pack_wcell(const void* W_x, const void* W_h, void* Wcell, int 
   return hipGetLastError();
 }
 hipError_t launch_step_cell(const void* Acat, const void* Wcell, const float* bias, const float* h_in, const float* c_in, float* h_out,
-                            float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n, int Kc, int ndir, hipStream_t s) {
+                            float* c_out, void* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n, int Kc, int ndir, hipStream_t s) {
   SkinnyArgs a = {};
   const int Np = 128 * cdiv(n, 32);
   a.A = (const char*)Acat; a.B = (const char*)Wcell; a.bias = bias;
   a.M = B; a.N = Np; a.K = Kc; a.lda = Kc; a.ldb = Kc;
   a.sAz = (long)B * Kc; a.sBz = (long)Np * Kc; a.nz = ndir;
-  a.cell = 1; a.n = n; a.h_in = h_in; a.c_in = c_in; a.h_out = h_out; a.c_out = c_out; a.y = (uint16_t*)y; a.ldy = ldy; a.cs = cs; a.lens = lens;
+  a.cell = 1; a.n = n; a.h_in = h_in; a.c_in = c_in; a.h_out = h_out; a.c_out = c_out; a.y = (uint16_t*)y; a.ldy = ldy; a.cs = cs; a.lens = lens; a.status = status;
   return launch(a, s);
 }
 

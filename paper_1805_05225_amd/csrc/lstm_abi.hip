@@ -293,6 +293,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     const long Kc = p.Kc;
     char* Wcat = ws + p.ws_Wcat;
     char* Acat = ws + p.ws_Acat;
+    unsigned* status = (unsigned*)(ws + p.ws_sync);
     float* z = (float*)(ws + p.ws_Zx);
     if (p.step_few) {                  // a handful of rows: operands in fragment order
       if (!(desc->flags & LSTM_FLAG_WEIGHTS_PACKED)) {
@@ -301,7 +302,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
       }
       Phase ph(LSTM_PHASE_LOOP_FWD, 2, s);
       HIPCHK(launch_few_cell(x, (const float*)h0, Acat, Wcat, (const float*)b, (const float*)c0, (float*)hT, (float*)cT, y, (long)(D * n), (float*)c,
-                             seq_lens, p.B, p.n_in, p.n_in_pad, p.n, p.D, s));
+                             seq_lens, status, p.B, p.n_in, p.n_in_pad, p.n, p.D, s));
       return LSTM_OK;
     }
     {
@@ -315,7 +316,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     if (p.step_fused) {                // product, bias, cell update and outputs in one kernel
       Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
       HIPCHK(launch_step_cell(Acat, Wcat, (const float*)b, (const float*)h0, (const float*)c0, (float*)hT, (float*)cT, y, (long)(D * n),
-                              (float*)c, seq_lens, p.B, p.n, p.Kc, p.D, s));
+                              (float*)c, seq_lens, status, p.B, p.n, p.Kc, p.D, s));
       return LSTM_OK;
     }
     // batch index of the product = K range: A and B advance by Kr columns, C by one partial result
@@ -335,7 +336,7 @@ int run_fwd(const lstm_desc* desc, int bidir, const void* x, const void* W_x, co
     {
       Phase ph(LSTM_PHASE_LOOP_FWD, 1, s);
       HIPCHK(launch_cell_step(z, part, p.ksplit, (const float*)b, (const float*)h0, (const float*)c0, (float*)hT, (float*)cT, y,
-                              (long)(D * n), (float*)c, seq_lens, p.B, p.n, p.D, s));
+                              (long)(D * n), (float*)c, seq_lens, status, p.B, p.n, p.D, s));
     }
     return LSTM_OK;
   }

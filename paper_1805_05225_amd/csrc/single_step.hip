@@ -81,8 +81,9 @@ __global__ void concat_kernel(const uint16_t* x, const float* h, uint16_t* Acat,
 // outputs zero.  One thread per (row, unit): four units per thread with 16-byte accesses measured slower (too few
 // wavefronts left to cover the latency of the partial-product reads).
 __global__ void cell_step_kernel(const float* z, long part, int nparts, const float* bias, const float* h_in, const float* c_in,
-                                 float* h_out, float* c_out, uint16_t* y, long ldy, float* cs, const int* lens, int B, int n, long total) {
+                                 float* h_out, float* c_out, uint16_t* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n, long total) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx == 0) *status = 0u;                              // nothing in a step waits for another work-group (lstm_sync_status)
   if (idx >= total) return;
   const int j = (int)(idx % n);
   const long rest = idx / n;
@@ -126,11 +127,11 @@ hipError_t launch_concat_xh(const void* x, const float* h, void* Acat, int B, in
   return hipGetLastError();
 }
 hipError_t launch_cell_step(const float* z, long part, int nparts, const float* bias, const float* h_in, const float* c_in, float* h_out,
-                            float* c_out, void* y, long ldy, float* cs, const int* lens, int B, int n, int ndir, hipStream_t s) {
+                            float* c_out, void* y, long ldy, float* cs, const int* lens, unsigned* status, int B, int n, int ndir, hipStream_t s) {
   const long total = (long)ndir * B * n;
   if (total <= 0) return hipSuccess;
   hipLaunchKernelGGL(cell_step_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, z, part, nparts, bias, h_in, c_in, h_out, c_out, (uint16_t*)y,
-                     ldy, cs, lens, B, n, total);
+                     ldy, cs, lens, status, B, n, total);
   return hipGetLastError();
 }
 

@@ -41,6 +41,23 @@ def test_stepped_cell(B, n_in, n):
         check("cT", s["cT"], co, TOL)
 
 
+@pytest.mark.parametrize("B,n,bidir", [(12, 40, False), (12, 41, True), (64, 40, True), (64, 41, False), (300, 200, False), (300, 201, True), (1300, 34, True), (1300, 35, False)])
+def test_stepped_cell_clears_the_status(B, n, bidir):
+    """A workspace on record for a wait that expired: one step, in every kernel that takes one, clears the record, weights kept or not."""
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator(device="cuda").manual_seed(n)
+    r = lambda *s: (torch.randn(*s, generator=g, device="cuda") * 0.1).bfloat16()
+    D = 2 if bidir else 1
+    x, Wx, Wh = r(1, B, 24), r(*(D, 24, 4 * n)[2 - D:]), r(*(D, n, 4 * n)[2 - D:])
+    ws = None
+    for flags in (Bn.FLAG_INFERENCE, Bn.FLAG_INFERENCE, Bn.FLAG_INFERENCE | Bn.FLAG_WEIGHTS_PACKED):
+        if ws is not None:
+            ws[:512].fill_(1)                                # (the word, at the first 256 bytes' boundary)
+            assert Bn.sync_status(ws)
+        ws = Bn.forward(x, Wx, Wh, bidirectional=bidir, flags=flags, want_c=False, workspace=ws)["workspace"]
+        assert not Bn.sync_status(ws)
+
+
 @pytest.mark.parametrize("n,nt,E,R", [(104, 62, 130, 20), (1000, 620, 2000, 1000), (5, 3, 8, 33), (104, 62, 130, 4001), (104, 62, 106, 31), (24, 16, 24, 2050)])
 def test_readout_packed_once_for_any_row_count(n, nt, E, R):
     """FLAG_WEIGHTS_PACKED speaks of the weights and the workspace, not of the number of rows."""
