@@ -26,6 +26,7 @@
 // is the path from L2 to LDS: of 138 us without the products 120 remain, without the loads 108 (1270 TFLOP/s).  Tried without gain: a phase
 // a quarter of a stage (130, 137 and 74 us of the first three), ten quarters of a stage in 80 KiB of LDS (128, 143, 80), three or four whole stages with one
 // work-group per compute unit.
+#include "gemm_plan.h"
 #include "recurrent_dev.h"
 #include <algorithm>
 #include <type_traits>
@@ -37,7 +38,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 constexpr int kBufFlags = 0x00020000;   // raw buffer descriptor word 3 for gfx9-family devices
 constexpr unsigned kParked = 0x7ffffff0u;
-constexpr int kKB = 64;                 // k per stage
+constexpr int kKB = kTileK;             // k per stage
 
 struct TileArgs {
   const char* A; const char* B; void* C; const float* bias;
@@ -72,7 +73,7 @@ __device__ __forceinline__ f32x16 mma(uint4 a, uint4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-constexpr int kTM = 128, kTN = 128;     // tile
+constexpr int kTM = kTileEdge, kTN = kTileEdge;
 constexpr int kOpBytes = 128 * kKB * 2, kStageBytes = 2 * kOpBytes;                  // one operand of a stage, both
 constexpr int kEpStride = kTN + 4, kEpBytes = 64 * kEpStride * 4;                    // the epilogue stages 64 rows at a time
 constexpr int tile_lds(bool ak, bool bk) { return 2 * kStageBytes + (ak && !bk ? kOpBytes : 0); }      // (k-contiguous A, k-major B: a third stage of B)
@@ -543,13 +544,9 @@ hipError_t launch_layout(const TileGroup& a, int count, bool ak, bool bk, hipStr
   return launch_as<TC, false, false, false>(a, count, s);
 }
 
-long tiles_of(const GemmArgs& g) { return (long)cdiv(g.M, 128) * cdiv(g.N, 128) * g.nz; }
-// `others`: tiles of the product that shares the launch
-int ranges(long tiles, long others, long K, int nseg) {
-  const long stages = (long)cdiv(K, kKB) * nseg;
-  return (int)std::max(1L, std::min(std::min(512 / std::max(tiles + others, 1L), stages / 4), 16L));
-}
-size_t bytes_of(long M, long N, int nz, int ks) { return ks > 1 ? (size_t)ks * nz * M * ((N + 3) / 4 * 4) * 4 : 0; }
+TileProduct sizes_of(const GemmArgs& g) { return {g.M, g.N, g.K, g.nz, g.nseg}; }
+long tiles_of(const GemmArgs& g) { return tile_count(g.M, g.N, g.nz); }
+int ranges_of(const GemmArgs& g, long others) { return tile_ranges(tiles_of(g), others, tile_stages(g.K, g.nseg)); }
 TileArgs tile_args(const GemmArgs& g, int ks, size_t parts_used) {
   TileArgs a = {};
   a.A = (const char*)g.A; a.B = (const char*)g.B; a.C = g.C; a.bias = g.bias;
@@ -561,7 +558,7 @@ TileArgs tile_args(const GemmArgs& g, int ks, size_t parts_used) {
   a.m_dev = g.m_dev; a.k_dev = g.k_dev;
   a.ldp = (g.N + 3) / 4 * 4;
   a.ksplit = g.parts ? ks : 1;
-  if (parts_used + bytes_of(g.M, g.N, g.nz, a.ksplit) > g.parts_bytes) a.ksplit = 1;
+  if (parts_used + tile_part_bytes(g.M, g.N, g.nz, a.ksplit) > g.parts_bytes) a.ksplit = 1;
   a.parts = a.ksplit > 1 ? (float*)((char*)g.parts + parts_used) : nullptr;
   return a;
 }
@@ -571,7 +568,7 @@ hipError_t finish(const TileArgs& a, const GemmArgs& g, hipStream_t s) {
   j.parts = a.parts; j.C = a.C; j.bias = a.bias; j.M = a.M; j.N = a.N; j.ksplit = a.ksplit; j.nz = a.nz;
   j.ldp = a.ldp; j.sPz = (long)a.ksplit * a.M * a.ldp; j.ldc = a.ldc; j.sCz = a.sCz; j.sbiasz = a.sbiasz;
   j.c_rows = a.c_rows; j.m_dev = a.m_dev; j.accumulate = a.accumulate; j.out_bf16 = g.out_bf16;
-  return finish_parts(j, bytes_of(a.M, a.N, a.nz, a.ksplit), g.sums, s);
+  return finish_parts(j, tile_part_bytes(a.M, a.N, a.nz, a.ksplit), g.sums, s);
 }
 
 }  // namespace
@@ -595,12 +592,12 @@ bool gemm_tile_ok(const GemmArgs& g) {
 bool gemm_tile_small(long M, long N, int nz) { return (long)cdiv(M, 256) * cdiv(N, 256) * nz <= 200; }
 
 size_t gemm_tile_parts_bytes(long M, long N, long K, int nz, int nseg) {
-  return bytes_of(M, N, nz, ranges((long)cdiv(M, 128) * cdiv(N, 128) * nz, 0, K, nseg));
+  return tile_part_bytes(M, N, nz, tile_ranges(tile_count(M, N, nz), 0, tile_stages(K, nseg)));
 }
 
 hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s) {
   TileGroup a = {};
-  a.p[0] = tile_args(g, ranges(tiles_of(g), 0, g.K, g.nseg), 0);
+  a.p[0] = tile_args(g, ranges_of(g, 0), 0);
   const bool bf = g.out_bf16 && a.p[0].ksplit == 1;
   const hipError_t e = bf ? launch_layout<uint16_t>(a, 1, g.a_kcontig, g.b_kcontig, s) : launch_layout<float>(a, 1, g.a_kcontig, g.b_kcontig, s);
   return e == hipSuccess ? finish(a.p[0], g, s) : e;
@@ -610,8 +607,8 @@ hipError_t launch_gemm_tile(const GemmArgs& g, hipStream_t s) {
 hipError_t launch_gemm_tile_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s) {
   if (g.M <= 0 || h.M <= 0 || g.N <= 0 || h.N <= 0 || g.nz <= 0) return hipErrorInvalidValue;
   TileGroup a = {};
-  a.p[0] = tile_args(g, ranges(tiles_of(g), tiles_of(h), g.K, g.nseg), 0);
-  a.p[1] = tile_args(h, ranges(tiles_of(h), tiles_of(g), h.K, h.nseg), (bytes_of(g.M, g.N, g.nz, a.p[0].ksplit) + 255) / 256 * 256);
+  a.p[0] = tile_args(g, ranges_of(g, tiles_of(h)), 0);
+  a.p[1] = tile_args(h, ranges_of(h, tiles_of(g)), tile_part_room(g.M, g.N, g.nz, a.p[0].ksplit));
   hipError_t e = launch_layout<float>(a, 2, false, false, s);
   if (e != hipSuccess || (e = finish(a.p[0], g, s)) != hipSuccess) return e;
   return finish(a.p[1], h, s);
@@ -621,38 +618,18 @@ hipError_t launch_gemm_tile_pair(const GemmArgs& g, const GemmArgs& h, hipStream
 // three at once, the sums; a training pass' lower layer: 330 units, 21 rows of at most 97 frames, both directions, n_in = 660 19.5 + 18.6 + 13.0 / 31.8 + 5.1, n_in = 123 12.2 + 13.3 + 8.3 / 16.1 + 7.2;
 // 208 units, 6 rows of 65 frames 11.1 + 11.2 + 5.0 / 12.0 + 5.0; 728 units, 14 rows of 113 frames, n_in = 598 19.3 + 26.2 + 13.0 / 37.7 + 4.3;
 // 512 units, 32 rows of 60, both directions, n_in = 1024 23.6 + 34.6 + 6.8 / 48.8 + 4.0; 1000 units, 64 rows of 50, n_in = 1000 39.2 + 52.3 + 8.4 / 96.3 + 4.1).
-// K ranges of about the same number of stages in all three; how many stages by what the launch is expected to take, in stages: a work-group costs 8 more than it has, 512 run at a time, and
-// a megabyte of parts is half a stage.
 hipError_t launch_gemm_tile_grads(const GemmArgs& dx, const GemmArgs& dwx, const GemmArgs& dwh, hipStream_t s) {
   const GemmArgs* g[3] = {&dx, &dwx, &dwh};
-  long tiles[3], stages[3], most = 4;
-  for (int i = 0; i < 3; ++i) {
+  for (int i = 0; i < 3; ++i)
     if (g[i]->M <= 0 || g[i]->N <= 0 || g[i]->nz <= 0) return hipErrorInvalidValue;
-    tiles[i] = tiles_of(*g[i]);
-    stages[i] = (long)cdiv(g[i]->K, kKB) * g[i]->nseg;
-    most = std::max(most, stages[i]);
-  }
-  const auto range_of = [&](int i, long per) { return (int)std::max(1L, std::min({(stages[i] + per - 1) / per, stages[i] / 4, 16L})); };
-  long per = most;
-  double least = 0.;
-  for (long p = most; p >= 4; p -= std::max(1L, p / 32)) {
-    double groups = 0., work = 0., longest = 0., parts = 0.;
-    for (int i = 0; i < 3; ++i) {
-      const int ks = range_of(i, p);
-      const double each = (double)stages[i] / ks + 8.;
-      groups += (double)tiles[i] * ks;
-      work += tiles[i] * ks * each;
-      longest = std::max(longest, each);
-      parts += 5e-7 * bytes_of(g[i]->M, g[i]->N, g[i]->nz, ks);
-    }
-    const double cost = parts + (groups <= 512. ? longest : work / 512. + 0.5 * longest);
-    if (p == most || cost < least) { least = cost; per = p; }
-  }
+  const TileProduct p[3] = {sizes_of(dx), sizes_of(dwx), sizes_of(dwh)};
+  int ks[3];
+  tile_ranges3(p, dx.parts_bytes, ks);
   TileTrio a = {};
   size_t used = 0;
   for (int i = 0; i < 3; ++i) {
-    a.p[i] = tile_args(*g[i], range_of(i, per), used);
-    if (a.p[i].ksplit > 1) used += (bytes_of(a.p[i].M, a.p[i].N, a.p[i].nz, a.p[i].ksplit) + 255) / 256 * 256;
+    a.p[i] = tile_args(*g[i], ks[i], used);
+    used += tile_part_room(a.p[i].M, a.p[i].N, a.p[i].nz, a.p[i].ksplit);
   }
   const bool bf = dx.out_bf16 && a.p[0].ksplit == 1, rows = dwx.k_rows != nullptr;
   hipError_t e = bf ? (rows ? launch_grads_as<uint16_t, true>(a, s) : launch_grads_as<uint16_t, false>(a, s)) : rows ? launch_grads_as<float, true>(a, s) : launch_grads_as<float, false>(a, s);
