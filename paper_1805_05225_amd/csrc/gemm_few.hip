@@ -331,11 +331,18 @@ hipError_t launch_rows(const SkinnyArgs& a, int ct, int tiles_n, hipStream_t s) 
       if (a.M <= 32) return launch_as<2, 4, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
       return launch_as<4, 4, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
     }
-    if (a.M <= 16 && longk && a.K <= 2048) return launch_as<1, 16, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    // (Two batches of four chunks of two row tiles, or of two of four, do not fit 128 registers beside the masks.  us, those with what spilled / these, the mean of 60 to 2400 columns: 20 and 32
+    // rows, K = 1067 14.2 / 8.5, 1801 15.0 / 13.9, 2801 27.2 / 20.7, 4094 13.5 / 11.9; 50 to 200 rows, K = 1419 20.1 / 19.8, 2377 34.4 / 33.3, 4094 22.8 / 21.6.)
+    if (a.M > 16 && longk) return a.M <= 32 ? launch_as<2, 16, 2, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<4, 16, 2, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    if (longk) return a.K <= 2048 ? launch_as<1, 16, 4, false, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<1, 16, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    if (a.M <= 16) return launch_as<1, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    if (a.M <= 32) return launch_as<2, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    return launch_as<4, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+  } else {
+    if (a.M <= 16) return longk ? launch_as<1, 16, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<1, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    if (a.M <= 32) return longk ? launch_as<2, 16, 4, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<2, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
+    return longk ? launch_as<4, 16, 2, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<4, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
   }
-  if (a.M <= 16) return longk ? launch_as<1, 16, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<1, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
-  if (a.M <= 32) return longk ? launch_as<2, 16, 4, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<2, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
-  return longk ? launch_as<4, 16, 2, true, FRAG, CELL, ANY>(a, ct, tiles_n, s) : launch_as<4, 4, 8, false, FRAG, CELL, ANY>(a, ct, tiles_n, s);
 }
 
 // Weights of the stepped cell: tile t holds the gates of units 4 t .. 4 t + 3 (column 4 q + u), k runs over [x | 0 | h | 0].
@@ -444,7 +451,7 @@ bool few_any_ok(const GemmArgs& g) {
       ((long)g.M * g.lda + g.K) * 2 > lim || ((long)g.N * g.ldb + g.K) * 2 > lim)
     return false;
   const long M = g.M, groups = (long)cdiv(M, 64) * g.nz * cdiv(g.N, any_columns(M, g.N, g.nz));
-  const int waves = g.K <= 1024 ? 4 : 16, deep = g.K <= 512 ? 4 : g.K <= 1024 ? 8 : M <= 16 ? (g.K <= 2048 ? 4 : 8) : M <= 32 ? 4 : 2;
+  const int waves = g.K <= 1024 ? 4 : 16, deep = g.K <= 512 ? 4 : g.K <= 1024 ? 8 : M <= 16 ? (g.K <= 2048 ? 4 : 8) : 2;
   const double loads = (groups > 512 ? groups / 256. : (double)cdiv(groups, 256)) * waves * deep * cdiv(cdiv(g.K, 32), waves * deep), rows = (M < 64 ? M : 64) / 16.;
   const bool odd = ((g.lda | g.ldb) & 1) || (((uintptr_t)g.A | (uintptr_t)g.B) & 3);
   const double here = odd ? std::max(5.2, 3.6 + loads * (0.068 + 0.052 * rows)) : std::max(5.2, 4.2 + loads * (0.020 + 0.0155 * rows));

@@ -101,7 +101,7 @@ def test_product_on_each_side_of_the_route(M, N, K):
 
 @pytest.mark.parametrize("M,N,K,gap,at", [(1, 20, 8, 0, 0), (7, 401, 9, 0, 1), (16, 1000, 334, 0, 0), (17, 401, 333, 2, 3), (32, 2787, 505, 0, 0), (33, 700, 510, 4, 2), (64, 1000, 1003, 1, 1),
                                           (65, 263, 1012, 0, 0), (192, 700, 31, 0, 0), (4, 8000, 612, 0, 0), (12, 50, 1025, 1, 0), (16, 33, 2046, 3, 1), (16, 33, 2051, 0, 0), (24, 40, 1999, 0, 1),
-                                          (40, 70, 4001, 0, 0), (300, 257, 130, 8, 5), (768, 1000, 334, 0, 0), (1000, 1000, 701, 0, 0)])
+                                          (40, 70, 4001, 0, 0), (17, 300, 1027, 0, 0), (32, 61, 4099, 2, 1), (33, 300, 1050, 0, 1), (64, 60, 2049, 1, 0), (300, 257, 130, 8, 5), (768, 1000, 334, 0, 0), (1000, 1000, 701, 0, 0)])
 def test_product_of_rows_at_any_element(M, N, K, gap, at):
     """Rows of any length, distance and first element, either side of few_any_ok; what lies between and around the rows is NaN and takes no part."""
     from paper_1805_05225_amd import binding as Bn
