@@ -76,13 +76,13 @@ __device__ __forceinline__ Tile tile_of(const SkinnyArgs& g, int tiles_m, int ti
   t.live = t.tm < tiles_m && t.tn < tiles_n;
   return t;
 }
-// xr, pr, pc for tiles of tm x tn; the rounds
+// xr, pr, pc for tiles of tm x tn; the rounds, of all nz problems
 int split_tiles(SkinnyArgs& a, int tm, int tn) {
   const int tiles_m = cdiv(a.M, tm), tiles_n = cdiv(a.N, tn);
   long best = 0;
   int rounds = 0;
   for (int xr = 1; xr <= 8; xr *= 2) {
-    const int pr = cdiv(tiles_m, xr), pc = cdiv(tiles_n, 8 / xr), r = cdiv((long)pr * pc, 32);
+    const int pr = cdiv(tiles_m, xr), pc = cdiv(tiles_n, 8 / xr), r = cdiv((long)pr * pc * a.nz, 32);
     const long cost = ((long)r << 32) + (long)pr * tm + (long)pc * tn;
     if (xr == 1 || cost < best) { best = cost; rounds = r; a.xr = xr; a.pr = pr; a.pc = pc; }
   }
@@ -375,7 +375,8 @@ hipError_t launch_tiles(SkinnyArgs a, hipStream_t s) {
   // The tile whose work-groups are done first: rounds times what one reads, which is all of K of its rows and columns; what begins and ends
   // a work-group counts as 1e5 / K rows more.  Of 46 products and cells measured with every tile the choice is the fastest one or within 6 %, in three
   // within 12 % (64 x 32000 x 512 12.2 us, 10.9 in 64 x 64).  us, 96 x 128 (or 64 x 64) before and the choice: cells of n = 688, 915 rows, K = 1680 44.9 -> 26.0; n = 1000, 1024 rows,
-  // K = 3620 71.9 -> 49.0; n = 504, 504 rows, K = 2424 31.2 -> 19.8; products 1000 x 4000 x 2000 43.8 -> 30.2, 104 x 22051 x 960 29.8 -> 19.5, 504 x 920 x 2424 14.3 -> 12.5.
+  // K = 3620 71.9 -> 49.0; n = 504, 504 rows, K = 2424 31.2 -> 19.8; both directions of a cell are one launch and share its rounds (over 237 such cells of more than 192 rows the choice is
+  // 1.02 times the fastest tile in the mean, 1.09 with the rounds of one direction: 930 rows, n = 276, K = 2240 43.6 -> 34.6, 898 rows, n = 384, K = 2880 51.9 -> 42.0); products 1000 x 4000 x 2000 43.8 -> 30.2, 104 x 22051 x 960 29.8 -> 19.5, 504 x 920 x 2424 14.3 -> 12.5.
   double least = 0.;
   const int best = choose_tile(a, least);
   split_tiles(a, 32 * kTiles[best][0], 64 * kTiles[best][1]);
@@ -448,7 +449,7 @@ bool gemm_skinny_ok(const GemmArgs& g) {
 // 19.4, 300 x 5000 x 800 10.3 / 13.8 / 25.2, 900 x 5000 x 800 22.3 / 19.2 / 25.4.
 FewRoute few_rows_route(int M, int N, int K) {
   SkinnyArgs a = {};
-  a.M = M; a.N = N; a.K = K;
+  a.M = M; a.N = N; a.K = K; a.nz = 1;
   double cost = 0.;
   const int best = choose_tile(a, cost), rounds = split_tiles(a, 32 * kTiles[best][0], 64 * kTiles[best][1]);
   const double out = 1e-6 * M * N, k = 1e-3 * K, read = rounds ? cost / rounds - 1e5 / K : 0.;      // rows and columns that a work-group reads

@@ -136,7 +136,7 @@ int make_plan(const lstm_desc* d, int bidir, Plan* p, bool odd_fast = true) {
   // epilogue (B <= kSkinnyMaxRows); larger batches go through the throughput kernel, K cut into ranges whose partial
   // products lie side by side for the cell kernel to add.
   p->step_fused = p->single_step && d->B <= kSkinnyMaxRows;
-  p->step_few = p->step_fused && few_cell_pays(d->B, d->n, p->D);
+  p->step_few = p->step_fused && few_cell_pays(d->B, d->n, p->D, (long)p->n_in_pad + d->n);
   {
     const long tiles = (long)cdiv(B > 0 ? B : 1, 256) * cdiv(4L * d->n, 256) * p->D;
     const long stages = cdiv((long)p->n_in_pad + d->n, 64);

@@ -41,6 +41,27 @@ def test_stepped_cell(B, n_in, n):
         check("cT", s["cT"], co, TOL)
 
 
+@pytest.mark.parametrize("B,n_in,n", [(1, 30, 1021), (16, 300, 1024), (16, 40, 1028), (17, 40, 720), (64, 77, 724), (193, 40, 201), (368, 64, 560), (361, 150, 552), (835, 58, 520), (1024, 9, 333)])
+def test_stepped_cell_of_both_directions(B, n_in, n):
+    """One launch steps both directions: either side of few_cell_pays for 16 rows and more, and tiles chosen for the rounds of both."""
+    from paper_1805_05225_amd import binding as Bn
+    rng = np.random.default_rng(B + n)
+    Wx, Wh = _bf(rng, 2, n_in, 4 * n, w=0.1), _bf(rng, 2, n, 4 * n, w=0.1)
+    b, h, c = rng.uniform(-.1, .1, (2, 4 * n)), rng.uniform(-1, 1, (2, B, n)), rng.standard_normal((2, B, n))
+    x = _bf(rng, 1, B, n_in)
+    lens = (np.arange(B) % 7 > 0).astype(np.int32)           # (a row without a frame keeps its state)
+    f64 = lambda t: t.float().numpy().astype(np.float64)
+    y, _, ho, co = O.blstm_fwd(f64(x), f64(Wx), f64(Wh), b, h, c, lens)
+    ws = None
+    for flags in (Bn.FLAG_INFERENCE, Bn.FLAG_INFERENCE | Bn.FLAG_WEIGHTS_PACKED):
+        s = Bn.forward(x.cuda(), Wx.cuda(), Wh.cuda(), dev(b), dev(h), dev(c), dev(lens), bidirectional=True, flags=flags, workspace=ws)
+        ws = s["workspace"]
+        torch.cuda.synchronize()
+        check("y", s["y"], y, TOL)
+        check("hT", s["hT"], ho, TOL)
+        check("cT", s["cT"], co, TOL)
+
+
 @pytest.mark.parametrize("B,n,bidir", [(12, 40, False), (12, 41, True), (64, 40, True), (64, 41, False), (300, 200, False), (300, 201, True), (1300, 34, True), (1300, 35, False)])
 def test_stepped_cell_clears_the_status(B, n, bidir):
     """A workspace on record for a wait that expired: one step, in every kernel that takes one, clears the record, weights kept or not."""
