@@ -68,67 +68,88 @@ __device__ __forceinline__ Cand wave_best(Cand c) {
   w.i = __builtin_amdgcn_readlane(c.i, 63);
   return w;
 }
-// The choice of a work-group's best `need` candidates, best first, out of what its 256 threads hold in registers.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ unsigned dpp_max(unsigned c) { return max(c, (unsigned)__builtin_amdgcn_update_dpp((int)c, (int)c, CTRL, ROW_MASK, 0xf, false)); }
+__device__ __forceinline__ unsigned wave_max(unsigned c) {        // (the same steps)
+  c = dpp_max<0x142, 0xa>(dpp_max<0x140, 0xf>(dpp_max<0x141, 0xf>(dpp_max<0x4E, 0xf>(dpp_max<0xB1, 0xf>(c)))));
+  return (unsigned)__builtin_amdgcn_readlane((int)dpp_max<0x143, 0xc>(c), 63);
+}
+// The choice of a work-group's best `need` candidates, best first, out of what its NW wavefronts hold in registers.
+template <int NW>
 struct Chooser {
-  static constexpr int kSeg = 128;                               // finalists a wavefront may contribute
-  unsigned key[256];
-  float v[4][kSeg], out_v[kBeamMax], win_v[4];
-  int i[4][kSeg], out_i[kBeamMax], win_i[4], count[4];
+  static constexpr int kSeg = NW == 1 ? 64 : 128;                // finalists a wavefront may contribute
+  unsigned key[64 * NW];
+  float v[NW][kSeg], out_v[kBeamMax], win_v[NW];
+  int i[NW][kSeg], out_i[kBeamMax], win_i[NW], count[NW];
 };
 // `top` is the largest value this thread has seen (its own entries or earlier ones that the list so far holds), each(f) calls
 // f(value, index) for every entry and scan(bound, f) for every entry that is not surely below the bound; both are wavefront-wide.  -inf and NaN are no candidates.  Results in s.out_v / out_i[0 .. need), (-inf, 0x7fffffff) where there are
 // fewer; the caller synchronises before the next use of s.
-// An entry strictly below the need-th largest of the 256 `top`s has `need` entries in front of it.  That bound is found by bisection over
-// the ordered bit patterns (20 bits of them, rounded down) with ballots; what reaches it - little more than `need` entries unless values
+// An entry strictly below the need-th largest of 64 values seen (a lane's `top`s, the largest of all wavefronts') has `need` entries in front of it.  That bound is found by bisection over
+// the ordered bit patterns (20 bits of them, rounded down) between the least and the largest of the 64, a ballot a step, ended where exactly `need` are above (over 256 values with four ballots a step, and
+// always 20 of them, it took 0.6 us more); what reaches it - little more than `need` entries unless values
 // repeat - goes to a list in LDS, a stretch per wavefront, and the place of a finalist is the number of better ones.  Lists that do not
 // fit (plateaus) are left: `need` rounds of "every thread offers its best behind the last winner" over the registers take their place.
-template <typename Each, typename Scan>
-__device__ __forceinline__ void choose_best(Chooser& s, float top, int need, Each each, Scan scan) {
+template <int NW, typename Each, typename Scan>
+__device__ __forceinline__ void choose_best(Chooser<NW>& s, float top, int need, Each each, Scan scan) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float kNegInf = -__builtin_inff();
   const unsigned f = __float_as_uint(top);
-  s.key[threadIdx.x] = ((f & 0x80000000u) ? ~f : (f | 0x80000000u)) >> 12;     // larger float => key not smaller
-  __syncthreads();
-  const unsigned k0 = s.key[lane], k1 = s.key[64 + lane], k2 = s.key[128 + lane], k3 = s.key[192 + lane];
-  unsigned lo = 0u, hi = 0xfffffu;
-  while (lo < hi) {
-    const unsigned mid = lo + ((hi - lo) >> 1) + 1u;
-    const int n = __popcll(__ballot(k0 >= mid)) + __popcll(__ballot(k1 >= mid)) + __popcll(__ballot(k2 >= mid)) + __popcll(__ballot(k3 >= mid));
-    if (n >= need) lo = mid; else hi = mid - 1u;
+  unsigned key = ((f & 0x80000000u) ? ~f : (f | 0x80000000u)) >> 12;           // larger float => key not smaller
+  if constexpr (NW > 1) {
+    s.key[threadIdx.x] = key;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) key = max(key, s.key[64 * w + lane]);
   }
-  // Keys at or below that of -inf: fewer than `need` threads hold anything.
-  const unsigned full = lo << 12;                                 // the smallest ordered pattern with this key
-  const float bound = lo <= (0x007fffffu >> 12) ? kNegInf : __uint_as_float((full & 0x80000000u) ? (full & 0x7fffffffu) : ~full);
+  constexpr unsigned kNone = 0x007fffffu >> 12;                   // the key of -inf: nothing seen
+  float bound = kNegInf;
+  if (__popcll(__ballot(key > kNone)) >= need) {
+    unsigned hi = wave_max(key), lo = ~wave_max(key > kNone ? ~key : 0u);
+    while (lo < hi) {
+      const unsigned mid = lo + ((hi - lo) >> 1) + 1u;
+      const int n = __popcll(__ballot(key >= mid));
+      if (n >= need) lo = mid; else hi = mid - 1u;
+      if (n == need) break;
+    }
+    const unsigned full = lo << 12;                               // the smallest ordered pattern with this key
+    bound = __uint_as_float((full & 0x80000000u) ? (full & 0x7fffffffu) : ~full);
+  }
   int count = 0;                                                 // of this wavefront (the same in every lane)
   scan(bound, [&](float x, int idx) {
     const bool keep = x > kNegInf && x >= bound;
     const unsigned long long mask = __ballot(keep);
     if (mask == 0ull) return;
     const int pos = count + (int)__popcll(mask & ((1ull << lane) - 1ull));
-    if (keep && pos < Chooser::kSeg) { s.v[wave][pos] = x; s.i[wave][pos] = idx; }
+    if (keep && pos < Chooser<NW>::kSeg) { s.v[wave][pos] = x; s.i[wave][pos] = idx; }
     count += (int)__popcll(mask);
   });
   if (lane == 0) s.count[wave] = count;
   if (threadIdx.x < kBeamMax) { s.out_v[threadIdx.x] = kNegInf; s.out_i[threadIdx.x] = 0x7fffffff; }
   __syncthreads();
-  const int c0 = s.count[0], c1 = s.count[1], c2 = s.count[2], c3 = s.count[3];
-  if (max(max(c0, c1), max(c2, c3)) <= Chooser::kSeg && c0 + c1 + c2 + c3 <= 256) {
-    // thread t has finalist t of the four stretches
-    const int t1 = c0, t2 = c0 + c1, t3 = t2 + c2, total = t3 + c3, t = threadIdx.x;
+  int most = 0, total = 0, w = 0, at = threadIdx.x;                // thread t has finalist t of the stretches, number `at` of wavefront w's
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    const int c = s.count[q];
+    total += c;
+    most = max(most, c);
+    if (q + 1 < NW && (int)threadIdx.x >= total) { w = q + 1; at = threadIdx.x - total; }
+  }
+  if (most <= Chooser<NW>::kSeg && total <= 64 * NW) {
+    const int t = threadIdx.x;
     if (wave * 64 >= total) return;
-    const int w = (t >= t1) + (t >= t2) + (t >= t3), at = t - (w == 0 ? 0 : w == 1 ? t1 : w == 2 ? t2 : t3);
     Cand mine = {kNegInf, 0x7fffffff};
     if (t < total) { mine.v = s.v[w][at]; mine.i = s.i[w][at]; }
     int place = 0;
-    if (total <= 64) {
+    if (NW == 1 || total <= 64) {
       for (int j = 0; j < total; ++j) {
         const Cand other = {__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine.v), j)), __builtin_amdgcn_readlane(mine.i, j)};
         place += better(other, mine) ? 1 : 0;
       }
     } else {
 #pragma unroll
-      for (int seg = 0; seg < 4; ++seg) {
-        const int n = seg == 0 ? c0 : seg == 1 ? c1 : seg == 2 ? c2 : c3;
+      for (int seg = 0; seg < NW; ++seg) {
+        const int n = s.count[seg];
         for (int j = 0; j < n; ++j) {
           const Cand other = {s.v[seg][j], s.i[seg][j]};
           place += better(other, mine) ? 1 : 0;
@@ -146,37 +167,39 @@ __device__ __forceinline__ void choose_best(Chooser& s, float top, int need, Eac
       if (better(last, c) && better(c, mine)) { mine.v = x; mine.i = idx; }
     });
     const Cand win = wave_best(mine);
-    if (lane == 0) { s.win_v[wave] = win.v; s.win_i[wave] = win.i; }
-    __syncthreads();
-    Cand best = {s.win_v[0], s.win_i[0]};
+    Cand best = win;
+    if constexpr (NW > 1) {
+      if (lane == 0) { s.win_v[wave] = win.v; s.win_i[wave] = win.i; }
+      __syncthreads();
 #pragma unroll
-    for (int w = 1; w < 4; ++w) best = pick(best, Cand{s.win_v[w], s.win_i[w]});
+      for (int q = 0; q < NW; ++q) best = pick(best, Cand{s.win_v[q], s.win_i[q]});
+    }
     if (threadIdx.x == 0 && best.v > kNegInf) { s.out_v[k] = best.v; s.out_i[k] = best.i; }
     last = best;
     __syncthreads();
   }
 }
 
-// Row r of the logits in `parts` stretches, a work-group of four wavefronts each (parts > 1: few rows, which would leave compute units
-// idle).  A stretch is read once, up to U loads of 16 bytes a thread in flight, and stays in registers: the logsumexp is
+// Row r of the logits in `parts` stretches, a work-group each (parts > 1: few rows, which would leave compute units
+// idle): four wavefronts, or one for a row of at most 64 pieces, which four would have to meet over.  A stretch is read once, up to U loads of 16 bytes a thread in flight, and stays in registers: the logsumexp is
 // folded four pieces at a time as they arrive, one bound for the whole work-group tells the few entries that can be among the best
-// apart, and these are ranked (choose_best).  A stretch of more than 256 U pieces (of 16 bytes) takes several rounds, each with the best so far among its candidates.
+// apart, and these are ranked (choose_best).  A stretch of more than 64 NW U pieces (of 16 bytes) takes several rounds, each with the best so far among its candidates.
 // Rows start and end anywhere: 16-byte pieces between the first and the last 16-byte boundary, the up to three entries on
 // either side one by one.
 // What bounds it: the reading of the logits, and for few rows a round trip to memory, the bisection and the ranking behind each other.
-// 768 rows x 20000: 21.8 -> 16.5 us (3.7 TB/s); 600 x 20787 (rows that are not whole 16 bytes) 73.6 -> 16.3; 104 x 22051 54.3 -> 9.7;
-// 8 x 14274 35.8 -> 6.2; 279 x 1853 9.6 -> 7.0.
-// (The form before kept a buffer of candidates in LDS and renewed its bound in every round of 4 loads, each a
-// round trip to memory and a bisection one after the other; rows that are not whole 16 bytes were read 4 bytes at a time.)
+// us a step, merge included, calls in a graph (a buffer of candidates in LDS with a bound renewed every four loads / four wavefronts for any row and a bisection over 256 values / now): 64 sentences of 12,
+// V = 20000 26.4 / 20.3 / 19.2; 50 of 12, V = 20787 (rows that are not whole 16 bytes) 64.8 / 20.7 / 19.8; 8 of 13, V = 22051 48.8 / 16.7 / 14.7; 1 of 8, V = 14274 31.6 / 11.2 / 9.9; 31 of 9, V = 1853
+// 12.7 / 10.8 / 9.1; 32 of 8, V = 1000 9.6 / 9.5 / 7.9; 16 of 4, V = 100 8.1 / 8.9 / 6.7; 77 of 5, V = 19 7.8 / 11.3 / 7.4.
 // clean: a NaN counts as no entry (rows that are not whole 16 bytes); otherwise it makes the row's scores NaN, which never win.
 // One stretch: cand_val[r][k] = score[r] + logits[r][label] - logsumexp and cand_lab[r][k].  Several: the logit itself in
 // cand_val[r][part][k], and the stretch's (maximum, sum of exponentials, score) in part_sums[r][part].
-template <int U>
-__global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__ logits, long ld, const float* __restrict__ score, bool clean,
+template <int U, int NW>
+__global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restrict__ logits, long ld, const float* __restrict__ score, bool clean,
                                                        float* __restrict__ cand_val, int* __restrict__ cand_lab, float4* __restrict__ part_sums,
                                                        int V, int beam, int parts, int per, int step) {
-  __shared__ Chooser s;
-  __shared__ float part_m[4], part_z[4];
+  constexpr int NT = 64 * NW, G = U < 4 ? U : 4;
+  __shared__ Chooser<NW> s;
+  __shared__ float part_m[NW], part_z[NW];
   const int r = (int)blockIdx.x / parts, part = (int)blockIdx.x - r * parts, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* row = logits + (long)r * ld;
   const int head = min(V, (int)((4u - ((unsigned)((uintptr_t)row >> 2) & 3u)) & 3u)), n4 = (V - head) >> 2, tail = V - head - 4 * n4;
@@ -197,37 +220,37 @@ __global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__
     const int stop = min(end, base + step);
     u32x4 x4[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) x4[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)(base + u * 256 + tid) * 16u, 0, 0);
+    for (int u = 0; u < U; ++u) x4[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, (unsigned)(base + u * NT + tid) * 16u, 0, 0);
     float x[U][4];
 #pragma unroll
-    for (int u0 = 0; u0 < U; u0 += 4) {
-      float pm[4], mn = m;
+    for (int u0 = 0; u0 < U; u0 += G) {
+      float pm[G], mn = m;
 #pragma unroll
-      for (int u = u0; u < u0 + 4; ++u)
+      for (int u = u0; u < u0 + G; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[u][e] = __uint_as_float(x4[u][e]);
-      if (base + (u0 + 4) * 256 > stop) {
+      if (base + (u0 + G) * NT > stop) {
         const int left = stop - base - tid;
 #pragma unroll
-        for (int u = u0; u < u0 + 4; ++u)
+        for (int u = u0; u < u0 + G; ++u)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[u][e] = u * 256 < left ? x[u][e] : kNegInf;
+          for (int e = 0; e < 4; ++e) x[u][e] = u * NT < left ? x[u][e] : kNegInf;
       }
       if (clean) {
 #pragma unroll
-        for (int u = u0; u < u0 + 4; ++u)
+        for (int u = u0; u < u0 + G; ++u)
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[u][e] = x[u][e] > kNegInf ? x[u][e] : kNegInf;
       }
 #pragma unroll
-      for (int u = u0; u < u0 + 4; ++u) {
+      for (int u = u0; u < u0 + G; ++u) {
         pm[u - u0] = fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3]));
         mn = fmaxf(mn, pm[u - u0]);
       }
       if (mn > kNegInf) {
         z *= __expf(m - mn);
 #pragma unroll
-        for (int u = u0; u < u0 + 4; ++u) {
+        for (int u = u0; u < u0 + G; ++u) {
           const float pz = (__expf(x[u][0] - mn) + __expf(x[u][1] - mn)) + (__expf(x[u][2] - mn) + __expf(x[u][3] - mn));
           z += pm[u - u0] > kNegInf ? pz : 0.f;
         }
@@ -241,7 +264,7 @@ __global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f(x[u][e], i + 1024 * u + e);
+        for (int e = 0; e < 4; ++e) f(x[u][e], i + 4 * NT * u + e);
       f(ex, ei);
     };
     const auto scan = [&](float bound, auto f) {
@@ -249,7 +272,7 @@ __global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__
       for (int u = 0; u < U; ++u) {
         if (__ballot(fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3])) >= bound) == 0ull) continue;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f(x[u][e], first + 1024 * u + e);
+        for (int e = 0; e < 4; ++e) f(x[u][e], first + 4 * NT * u + e);
       }
       f(ex, ei);
     };
@@ -271,10 +294,11 @@ __global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__
   if (lane == 0) { part_m[wave] = mw; part_z[wave] = zw; }
   __syncthreads();
   if (tid >= 64) return;
-  const float mr = fmaxf(fmaxf(part_m[0], part_m[1]), fmaxf(part_m[2], part_m[3]));
-  float zr = 0.f;
+  float mr = kNegInf, zr = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) zr += part_m[w] > kNegInf ? part_z[w] * __expf(part_m[w] - mr) : 0.f;
+  for (int w = 0; w < NW; ++w) mr = fmaxf(mr, part_m[w]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) zr += part_m[w] > kNegInf ? part_z[w] * __expf(part_m[w] - mr) : 0.f;
   const float sc = score[r];
   if (parts > 1 && tid == 0) part_sums[blockIdx.x] = make_float4(mr, zr, sc, 0.f);
   if (tid < beam) {
@@ -286,12 +310,12 @@ __global__ __launch_bounds__(256) void beam_row_kernel(const float* __restrict__
 }
 
 // The beam * parts * beam survivors of sentence q = blockIdx.x: the best `beam`, by value and then by flat index b * V + label.
-// 256 N >= that many.
-template <int N>
-__global__ __launch_bounds__(256) void beam_merge_kernel(const float* __restrict__ cand_val, const int* __restrict__ cand_lab,
+// 64 NW N >= that many.  One wavefront up to 256 of them: nothing to meet over.
+template <int N, int NW>
+__global__ __launch_bounds__(64 * NW) void beam_merge_kernel(const float* __restrict__ cand_val, const int* __restrict__ cand_lab,
                                                          const float4* __restrict__ part_sums, float* __restrict__ score_out,
                                                          int* __restrict__ src_out, int* __restrict__ label_out, int V, int beam, int parts) {
-  __shared__ Chooser s;
+  __shared__ Chooser<NW> s;
   __shared__ float row_sc[kBeamMax], row_lse[kBeamMax];
   const int q = blockIdx.x, tid = threadIdx.x, per_row = parts * beam, total = beam * per_row;
   const float kNegInf = -__builtin_inff();
@@ -299,7 +323,7 @@ __global__ __launch_bounds__(256) void beam_merge_kernel(const float* __restrict
   int flat[N], b[N];
 #pragma unroll
   for (int k = 0; k < N; ++k) {
-    const int c = tid + 256 * k;
+    const int c = tid + 64 * NW * k;
     b[k] = c / per_row;
     v[k] = c < total ? cand_val[(long)q * total + c] : kNegInf;
     flat[k] = c < total ? b[k] * V + cand_lab[(long)q * total + c] : 0x7fffffff;
@@ -415,25 +439,29 @@ static int beam_launch(int Q, int beam, int V, const float* logits, int64_t ld, 
                        int32_t* label, int parts, float* cand_val, int* cand_lab, float4* part_sums, hipStream_t st) {
   const bool clean = (ld & 3) != 0 || ((uintptr_t)logits & 15) != 0;
   const int per = cdiv(cdiv(V, 4), parts), step = cdiv(per, cdiv(per, 256 * kRowPieces));       // pieces of a stretch, of a round
-  const auto row = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(Q * beam * parts)), dim3(256), 0, st, logits, (long)ld, score_in, clean, cand_val, cand_lab, part_sums, V,
+  const auto row = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(Q * beam * parts)), dim3(64 * waves), 0, st, logits, (long)ld, score_in, clean, cand_val, cand_lab, part_sums, V,
                        beam, parts, per, step);
   };
   const int u = cdiv(step, 256);
-  if (u <= 4) row(beam_row_kernel<4>);
-  else if (u <= 8) row(beam_row_kernel<8>);
-  else if (u <= 12) row(beam_row_kernel<12>);
-  else if (u <= 16) row(beam_row_kernel<16>);
-  else if (u <= 20) row(beam_row_kernel<20>);
-  else row(beam_row_kernel<kRowPieces>);
-  const auto merge = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(Q), dim3(256), 0, st, cand_val, cand_lab, part_sums, score_out, src, label, V, beam, parts);
+  if (step <= 64) row(beam_row_kernel<1, 1>, 1);
+  else if (u <= 1) row(beam_row_kernel<1, 4>, 4);
+  else if (u <= 2) row(beam_row_kernel<2, 4>, 4);
+  else if (u <= 4) row(beam_row_kernel<4, 4>, 4);
+  else if (u <= 8) row(beam_row_kernel<8, 4>, 4);
+  else if (u <= 12) row(beam_row_kernel<12, 4>, 4);
+  else if (u <= 16) row(beam_row_kernel<16, 4>, 4);
+  else if (u <= 20) row(beam_row_kernel<20, 4>, 4);
+  else row(beam_row_kernel<kRowPieces, 4>, 4);
+  const auto merge = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3(Q), dim3(64 * waves), 0, st, cand_val, cand_lab, part_sums, score_out, src, label, V, beam, parts);
   };
-  const int c = cdiv((long)beam * parts * beam, 256);
-  if (c <= 1) merge(beam_merge_kernel<1>);
-  else if (c <= 2) merge(beam_merge_kernel<2>);
-  else if (c <= 4) merge(beam_merge_kernel<4>);
-  else merge(beam_merge_kernel<kRowParts * kBeamMax * kBeamMax / 256>);
+  const int c = beam * parts * beam;
+  if (c <= 64) merge(beam_merge_kernel<1, 1>, 1);
+  else if (c <= 256) merge(beam_merge_kernel<4, 1>, 1);
+  else if (c <= 512) merge(beam_merge_kernel<2, 4>, 4);
+  else if (c <= 1024) merge(beam_merge_kernel<4, 4>, 4);
+  else merge(beam_merge_kernel<kRowParts * kBeamMax * kBeamMax / 256, 4>, 4);
   if (hipGetLastError() != hipSuccess) return LSTM_ERR_HIP;
   return LSTM_OK;
 }

@@ -150,7 +150,10 @@ def test_beam_step_strided_logits():
 # end between pieces, rows cut into stretches (up to eight, of at least 2048 entries), stretches of more than one round of 24 * 256 pieces
 @pytest.mark.parametrize("Q,beam,V,ld,shift", [(1, 1, 1, 1, 0), (2, 3, 2, 5, 1), (1, 16, 7, 7, 3), (3, 4, 2047, 2047, 0), (3, 4, 4096, 4099, 2),
                                                (2, 16, 14274, 14274, 0), (1, 4, 22051, 22051, 1), (13, 8, 22051, 22051, 0), (24, 16, 4999, 5001, 3),
-                                               (48, 16, 1025, 1025, 0), (49, 16, 24579, 24579, 0), (49, 16, 24576, 24576, 0), (48, 16, 32771, 32771, 2), (1, 2, 250007, 250007, 1)])
+                                               (48, 16, 1025, 1025, 0), (49, 16, 24579, 24579, 0), (49, 16, 24576, 24576, 0), (48, 16, 32771, 32771, 2), (1, 2, 250007, 250007, 1),
+                                               # short rows: one wavefront for a row, for a merge (64 and 256 survivors), and one more
+                                               (5, 8, 256, 256, 0), (5, 9, 259, 259, 1), (3, 16, 257, 260, 0), (2, 8, 1024, 1024, 0), (2, 9, 1028, 1031, 3), (1, 16, 2049, 2049, 2), (3, 4, 66, 66, 1),
+                                               (1, 8, 9000, 9000, 0), (1, 12, 9001, 9001, 0)])
 def test_beam_step_stretches_rounds_and_alignment(Q, beam, V, ld, shift):
     rng = np.random.default_rng(Q * 1000 + V)
     rows = Q * beam
