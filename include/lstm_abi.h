@@ -251,6 +251,8 @@ int lstm_readout(int flags, int B, int R, const void* s, int64_t ld_s, int n, co
  *     the `beam` largest cand[q, :, :] become the new hypotheses of sentence q, best first: score_out[q, k], the
  *     hypothesis it extends src[q, k] in [0, beam) and its label[q, k] in [0, V); equal candidates are ordered by the
  *     smaller b * V + v.  A hypothesis with score -inf (the unused slots of the first step) never beats a finite one.
+ *     A logit of -inf is a label that cannot be chosen; a NaN or +inf anywhere among a hypothesis' logits makes all its
+ *     candidates NaN, and a NaN never wins.  Places that nothing is left for get score -inf, hypothesis 0, label 0.
  * Finished hypotheses and length normalisation are not part of this step.  All arithmetic is float.
  *   logits float [Q*beam][ld >= V] (e.g. lstm_gemm of the readout with the output weights), score_in, score_out float
  *   [Q][beam], src, label int32 [Q][beam]; beam <= 16, V <= 2^26; workspace of lstm_beam_query() bytes.

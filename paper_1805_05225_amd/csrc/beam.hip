@@ -180,6 +180,9 @@ __device__ __forceinline__ void choose_best(Chooser<NW>& s, float top, int need,
   }
 }
 
+// What exponentials are taken relative to where the maximum may be -inf (nothing but -inf and NaN so far): exp(-inf - base) is 0 then, and a NaN stays one.
+__device__ __forceinline__ float lse_base(float m) { return fmaxf(m, -__FLT_MAX__); }
+
 // Row r of the logits in `parts` stretches, a work-group each (parts > 1: few rows, which would leave compute units
 // idle): four wavefronts, or one for a row of at most 64 pieces, which four would have to meet over.  A stretch is read once, up to U loads of 16 bytes a thread in flight, and stays in registers: the logsumexp is
 // folded four pieces at a time as they arrive, one bound for the whole work-group tells the few entries that can be among the best
@@ -190,11 +193,11 @@ __device__ __forceinline__ void choose_best(Chooser<NW>& s, float top, int need,
 // us a step, merge included, calls in a graph (a buffer of candidates in LDS with a bound renewed every four loads / four wavefronts for any row and a bisection over 256 values / now): 64 sentences of 12,
 // V = 20000 26.4 / 20.3 / 19.2; 50 of 12, V = 20787 (rows that are not whole 16 bytes) 64.8 / 20.7 / 19.8; 8 of 13, V = 22051 48.8 / 16.7 / 14.7; 1 of 8, V = 14274 31.6 / 11.2 / 9.9; 31 of 9, V = 1853
 // 12.7 / 10.8 / 9.1; 32 of 8, V = 1000 9.6 / 9.5 / 7.9; 16 of 4, V = 100 8.1 / 8.9 / 6.7; 77 of 5, V = 19 7.8 / 11.3 / 7.4.
-// clean: a NaN counts as no entry (rows that are not whole 16 bytes); otherwise it makes the row's scores NaN, which never win.
+// A NaN (or +inf) anywhere in a row makes its logsumexp and so all its scores NaN, and these never win.
 // One stretch: cand_val[r][k] = score[r] + logits[r][label] - logsumexp and cand_lab[r][k].  Several: the logit itself in
 // cand_val[r][part][k], and the stretch's (maximum, sum of exponentials, score) in part_sums[r][part].
 template <int U, int NW>
-__global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restrict__ logits, long ld, const float* __restrict__ score, bool clean,
+__global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restrict__ logits, long ld, const float* __restrict__ score,
                                                        float* __restrict__ cand_val, int* __restrict__ cand_lab, float4* __restrict__ part_sums,
                                                        int V, int beam, int parts, int per, int step) {
   constexpr int NT = 64 * NW, G = U < 4 ? U : 4;
@@ -213,7 +216,8 @@ __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restri
   if (part == 0 && tid < head + tail) {
     ei = tid < head ? tid : head + 4 * n4 + tid - head;
     ex = row[ei];
-    if (ex > kNegInf) { m = ex; z = __expf(ex - ex); }
+    m = fmaxf(ex, kNegInf);
+    z = __expf(ex - lse_base(ex));
   }
   int base = begin;
   for (;;) {
@@ -224,7 +228,7 @@ __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restri
     float x[U][4];
 #pragma unroll
     for (int u0 = 0; u0 < U; u0 += G) {
-      float pm[G], mn = m;
+      float mn = m;
 #pragma unroll
       for (int u = u0; u < u0 + G; ++u)
 #pragma unroll
@@ -236,24 +240,17 @@ __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restri
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[u][e] = u * NT < left ? x[u][e] : kNegInf;
       }
-      if (clean) {
 #pragma unroll
-        for (int u = u0; u < u0 + G; ++u)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[u][e] = x[u][e] > kNegInf ? x[u][e] : kNegInf;
-      }
-#pragma unroll
-      for (int u = u0; u < u0 + G; ++u) {
-        pm[u - u0] = fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3]));
-        mn = fmaxf(mn, pm[u - u0]);
-      }
+      for (int u = u0; u < u0 + G; ++u) mn = fmaxf(mn, fmaxf(fmaxf(x[u][0], x[u][1]), fmaxf(x[u][2], x[u][3])));
       if (mn > kNegInf) {
         z *= __expf(m - mn);
 #pragma unroll
-        for (int u = u0; u < u0 + G; ++u) {
-          const float pz = (__expf(x[u][0] - mn) + __expf(x[u][1] - mn)) + (__expf(x[u][2] - mn) + __expf(x[u][3] - mn));
-          z += pm[u - u0] > kNegInf ? pz : 0.f;
-        }
+        for (int u = u0; u < u0 + G; ++u) z += (__expf(x[u][0] - mn) + __expf(x[u][1] - mn)) + (__expf(x[u][2] - mn) + __expf(x[u][3] - mn));
+      } else {                                                   // nothing but -inf and NaN so far
+#pragma unroll
+        for (int u = u0; u < u0 + G; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) z = x[u][e] == kNegInf ? z : __builtin_nanf("");
       }
       m = mn;
     }
@@ -288,7 +285,7 @@ __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restri
   float mw = m;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
-  float zw = mw > kNegInf ? z * __expf(m - mw) : 0.f;
+  float zw = z * __expf(lse_base(m) - lse_base(mw));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) zw += __shfl_xor(zw, o);
   if (lane == 0) { part_m[wave] = mw; part_z[wave] = zw; }
@@ -298,7 +295,7 @@ __global__ __launch_bounds__(64 * NW) void beam_row_kernel(const float* __restri
 #pragma unroll
   for (int w = 0; w < NW; ++w) mr = fmaxf(mr, part_m[w]);
 #pragma unroll
-  for (int w = 0; w < NW; ++w) zr += part_m[w] > kNegInf ? part_z[w] * __expf(part_m[w] - mr) : 0.f;
+  for (int w = 0; w < NW; ++w) zr += part_z[w] * __expf(lse_base(part_m[w]) - lse_base(mr));
   const float sc = score[r];
   if (parts > 1 && tid == 0) part_sums[blockIdx.x] = make_float4(mr, zr, sc, 0.f);
   if (tid < beam) {
@@ -333,7 +330,7 @@ __global__ __launch_bounds__(64 * NW) void beam_merge_kernel(const float* __rest
       const float4* ps = part_sums + ((long)q * beam + tid) * parts;
       float mr = kNegInf, zr = 0.f;
       for (int p = 0; p < parts; ++p) mr = fmaxf(mr, ps[p].x);
-      for (int p = 0; p < parts; ++p) zr += ps[p].x > kNegInf ? ps[p].y * __expf(ps[p].x - mr) : 0.f;
+      for (int p = 0; p < parts; ++p) zr += ps[p].y * __expf(lse_base(ps[p].x) - lse_base(mr));
       row_sc[tid] = ps[0].z;
       row_lse[tid] = mr + __logf(zr);
     }
@@ -437,10 +434,9 @@ int lstm_beam_query(int Q, int beam, int V, uint64_t* workspace_bytes) {
 // both kernels of a step; cand_val / cand_lab hold Q * beam * parts * beam entries each, part_sums Q * beam * parts
 static int beam_launch(int Q, int beam, int V, const float* logits, int64_t ld, const float* score_in, float* score_out, int32_t* src,
                        int32_t* label, int parts, float* cand_val, int* cand_lab, float4* part_sums, hipStream_t st) {
-  const bool clean = (ld & 3) != 0 || ((uintptr_t)logits & 15) != 0;
   const int per = cdiv(cdiv(V, 4), parts), step = cdiv(per, cdiv(per, 256 * kRowPieces));       // pieces of a stretch, of a round
   const auto row = [&](auto kernel, int waves) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(Q * beam * parts)), dim3(64 * waves), 0, st, logits, (long)ld, score_in, clean, cand_val, cand_lab, part_sums, V,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(Q * beam * parts)), dim3(64 * waves), 0, st, logits, (long)ld, score_in, cand_val, cand_lab, part_sums, V,
                        beam, parts, per, step);
   };
   const int u = cdiv(step, 256);

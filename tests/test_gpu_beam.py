@@ -183,6 +183,31 @@ def test_beam_step_stretches_rounds_and_alignment(Q, beam, V, ld, shift):
     _validate(logits, score, beam, (out.cpu().numpy(), src.cpu().numpy().astype(np.int64), lab.cpu().numpy().astype(np.int64)))
 
 
+@pytest.mark.parametrize("Q,beam,V,ld,shift", [(2, 6, 103, 104, 0), (2, 6, 103, 105, 1), (2, 6, 1503, 1503, 2), (1, 6, 22051, 22052, 0), (1, 6, 22051, 22051, 3), (1, 6, 60003, 60004, 0)])
+def test_beam_step_hypothesis_with_a_nan_never_wins(Q, beam, V, ld, shift):
+    """A NaN in front of the first 16-byte boundary, behind the last, among finite logits and among nothing but -inf: the rows' alignment makes no difference."""
+    rng = np.random.default_rng(V + shift)
+    rows = Q * beam
+    logits = (rng.standard_normal((rows, V)) * 3).astype(np.float32)
+    logits[0, V // 2] = np.nan                               # inside
+    logits[1, 0] = np.nan                                    # first
+    logits[2, V - 1] = np.nan                                # last
+    logits[3, :] = -np.inf
+    logits[3, [V // 3, 1]] = np.nan, 2.0                     # alone in its 16 bytes, and in what a thread holds
+    logits[4, V // 4] = np.inf
+    score = (-rng.uniform(0, 1, (Q, beam))).astype(np.float32)
+    score[0, :5] += 20.0                                     # (they would win)
+    buf = torch.zeros(rows * ld + shift, dtype=torch.float32, device="cuda")
+    x = buf[shift:].as_strided((rows, V), (ld, 1))
+    x.copy_(torch.from_numpy(logits))
+    r = Bn.beam_step(x, torch.from_numpy(score).cuda())
+    torch.cuda.synchronize()
+    logits[:5], score[0, :5] = 0.0, -np.inf
+    got = (r["score"].cpu().numpy(), r["src"].cpu().numpy().astype(np.int64), r["label"].cpu().numpy().astype(np.int64))
+    with np.errstate(all="ignore"):
+        _validate(logits, score, beam, got)
+
+
 def test_gather_and_embed_are_exact():
     rng = np.random.default_rng(10)
     Q, beam = 6, 12
