@@ -36,6 +36,13 @@ def test_static_scratch_matches_workspace_two_calls():
     _case(Bn, 256, 16, 40, 4)                       # exactly at the limit Q * beam * beam = 65536
 
 
+def test_static_scratch_holds_rows_in_stretches():
+    """Rows of many labels cut into up to eight stretches: their sums lie at the array's end, behind the survivors of at most 768 stretches; whole rows before and behind."""
+    from paper_1805_05225_amd import binding as Bn
+    for k, (Q, beam, V) in enumerate([(256, 16, 40), (1, 4, 22051), (2, 16, 14274), (6, 16, 20000), (24, 16, 5003), (32, 12, 4096), (256, 3, 4100), (64, 12, 20000), (1, 1, 20000)]):
+        _case(Bn, Q, beam, V, 10 + k)
+
+
 def test_static_scratch_rejects_sizes_beyond_the_array():
     from paper_1805_05225_amd import binding as Bn
     Q, beam, V = 257, 16, 8
