@@ -264,12 +264,13 @@ __global__ void colsum_final_kernel(const float* part, float* db, int ncols, int
 
 // Wavefronts of a work-group: a step reads W_h, whose loads in flight are what a wavefront has, and few work-groups with four of them left most of the path to memory
 // idle.  us for 12 steps with set-up and products, 4 / 8 / 16 wavefronts, float: forward n = 2048, 16 rows, one direction 299 / 253 / 247, n = 1000, 64 rows, both 290 / 271 / 282, n = 512, 300 rows, both
-// (1280 work-groups) 332 / 350 / 378; backward 725 / 496 / 395, 538 / 431 / 407, 508 / 509 / 526.  In bfloat16: forward n = 2304, 16 rows, one direction 183 / 199 / 218; backward
+// (1280 work-groups) 332 / 350 / 378 (of 45 shapes of 200 to 1024 work-groups eight are 0.87 to 1.00 times four up to 256, and 0.93 to 0.99 up to 512 from n = 700 on; 1.01 to 1.05 up to 512 below that, 0.99 to
+// 1.04 beyond); backward 725 / 496 / 395, 538 / 431 / 407, 508 / 509 / 526.  In bfloat16: forward n = 2304, 16 rows, one direction 183 / 199 / 218; backward
 // 431 / 324 / 263, both directions (288 work-groups) 485 / 379 / 437, 64 rows (1152) 611 / 657 / 662.
 hipError_t launch_step_fwd(const FwdArgs& a, bool bf16, hipStream_t s) {
   const int blocks = step_grid(cdiv(a.n, 8), cdiv(a.B, 32), a.ndir);
   if (bf16) hipLaunchKernelGGL((step_fwd_kernel<bf16_t, 4>), dim3(blocks), dim3(256), 0, s, a);
-  else if (blocks <= 1024) hipLaunchKernelGGL((step_fwd_kernel<float, 8>), dim3(blocks), dim3(512), 0, s, a);
+  else if (blocks <= 256 || (blocks <= 512 && a.n >= 700)) hipLaunchKernelGGL((step_fwd_kernel<float, 8>), dim3(blocks), dim3(512), 0, s, a);
   else hipLaunchKernelGGL((step_fwd_kernel<float, 4>), dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
