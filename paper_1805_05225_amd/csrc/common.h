@@ -87,13 +87,13 @@ struct GemmArgs {
   bool frames;                            // rows of A and C are frames, padded ones included (gemm_float_ranges)
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-// Fast bfloat16 kernel for problems with both operands k-contiguous, 16-byte aligned rows and K % 8 == 0
+// Fast bfloat16 kernel for problems with both operands k-contiguous, rows of whole 8 bytes at 8-byte addresses, K >= 8 and K % 4 == 0
 // (launch_gemm routes such problems to it by itself).
 bool gemm_nt_ok(const GemmArgs& g);
 bool gemm_nn_ok(const GemmArgs& g);                   // (launch_gemm_nt takes these too)
 bool gemm_nn_pays(const GemmArgs& g);                 // (the others that are gemm_nn_ok are for launch_gemm_tile)
 hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s);
-// Fast bfloat16 kernel for the opposite storage: both operands k-major (A[K][lda], B[K][ldb], 16-byte aligned rows),
+// Fast bfloat16 kernel for the opposite storage: both operands k-major (A[K][lda], B[K][ldb], rows of whole 8 bytes),
 // float C.  Row k of both operands is row k_rows[k] in memory if k_rows is given (launch_gemm routes to it by itself).
 bool gemm_tn_ok(const GemmArgs& g);
 hipError_t launch_gemm_tn(const GemmArgs& g, hipStream_t s);
@@ -117,7 +117,7 @@ size_t gemm_float_parts_bytes(long M, long N, long K, int nz, int nseg, bool fra
 bool gemm_float_ok(const GemmArgs& g);
 hipError_t launch_gemm_float(const GemmArgs& g, hipStream_t s);
 // Products with few rows (gemm_skinny.hip): both operands k-contiguous bfloat16 with 16-byte aligned rows, K % 8 == 0,
-// M <= kSkinnyMaxRows, one segment, no row maps, no K ranges: a work-group owns 96 x 128 of C for the whole K, so bias,
+// M <= kSkinnyMaxRows, one segment, no row maps, no K ranges: a work-group owns a tile of C, of 32 x 64 to 128 x 128, for the whole K, so bias,
 // max(0, .) and the rounding to bfloat16 happen in its epilogue (launch_gemm routes such problems to it by itself).
 constexpr int kSkinnyMaxRows = 1024;
 bool gemm_skinny_ok(const GemmArgs& g);

@@ -2502,7 +2502,7 @@ __global__ __launch_bounds__(256) void persist_bwd_f32_kernel(PBwdArgs a) {
   unsigned* err = a.sync;
   bool dead = false;
 
-  // W_h^T slice: column tile wave + 4 ci of the outputs, k-step s (launch_pack_wh_bwd_f32p)
+  // W_h^T slice: column tile wave + 4 ci of the outputs, k-step s (pack_wh_bwd_f32p_body)
   // In three bfloat16 parts, as forward: two fill the 256 accumulation registers of every lane, the smallest lies in LDS.
   u32x4 wh[NCT][2], wm[NCT][2];
   float w_bound = 0.f;                                     // 64 times the slice's largest weight, over all lanes: a sum of products, scaled by 2^-32, is no larger
