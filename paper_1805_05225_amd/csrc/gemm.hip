@@ -354,10 +354,28 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs g) {
   }
 }
 
-// k-contiguous operands of less than a chunk, K < 16 / sizeof(T): little more than storing C.  A thread owns a column and R rows of a tile of `cols` columns: its column of B in
-// registers, the tile's rows of A in LDS, from where a wavefront's rows are read by all lanes at once.  (A thread per element of C, which read both operands from memory and divided to find its
-// place, took longer than the 128 x 128 tiles of gemm_kernel from a million elements on, and its grid ended at 2^32 of them: what lay behind was not written.)  us, gemm_kernel / a thread per element / so, K = 4 and
-// 7, bfloat16 into float: 4096 x 4096 33.5 / 59.5 / 30.2 and 37.5 / 81 / 31; 768 x 20000 33.8 / 53.9 / 28.1 and 38.3 / 71.6 / 29.0; 64 x 1000 15.0 / 3.8 / 4.1 and 16.5 / 3.9 / 4.2.
+// k-contiguous operands of less than a chunk, K < 16 / sizeof(T): little more than storing C.  Small results are bound by the chain from the loads to the store: a thread per element of C, with
+// its operands from memory.
+template <typename T, typename TC>
+__global__ __launch_bounds__(256) void short_element_kernel(GemmArgs g) {
+  const int idx = blockIdx.x * 256 + threadIdx.x, m = idx / g.N, n = idx - m * g.N, z = blockIdx.y;      // (at most 2^21 of them)
+  if (m >= (g.m_dev ? min(g.M, *g.m_dev) : g.M)) return;
+  const int K = g.k_dev ? min(g.K, *g.k_dev) : g.K;
+  float v = g.bias ? g.bias[g.sbiasz * z + n] : 0.f;
+  for (int seg = 0; seg < g.nseg; ++seg)
+    for (int k = 0; k < K; ++k) {
+      const long b_at = g.b_kcontig ? (long)n * g.ldb + k : (long)k * g.ldb + n;
+      v += Store<T>::load(g.A, g.sAz * z + g.sAseg * seg + (long)(g.a_rows ? g.a_rows[m] : m) * g.lda + k) * Store<T>::load(g.B, g.sBz * z + g.sBseg * seg + b_at);
+    }
+  const long off = g.sCz * z + (long)(g.c_rows ? g.c_rows[m] : m) * g.ldc + n;
+  if (g.accumulate) v += Store<TC>::load(g.C, off);
+  Store<TC>::store(g.C, off, v);
+}
+// Larger ones: a thread owns a column and R rows of a tile of `cols` columns: its column of B in registers, the tile's rows of A in LDS, from where a wavefront's rows are read by all lanes at
+// once.  us, gemm_kernel / a thread per element / so: 4096 x 4096 into float, K = 4 33.5 / 59.5 / 30.2, K = 7 37.5 / 81 / 31; 768 x 20000 33.8 / 53.9 / 28.1 and 38.3 / 71.6 / 29.0.
+// The line lies where the two take the same: a million elements (310 x 2983 x 3 5.4 / 4.8, 1803 x 516 x 7 7.3 / 6.6, 13986 x 76 x 2 5.4 / 7.9, 106199 x 5 x 4 4.6 / 7.2), twice that with at most
+// three k (90551 x 23 x 1 8.0 / 8.2, 1057 x 1405 x 3 7.4 / 6.9) or less than sixteen columns, the narrowest tile (280032 x 5 x 7 11.6 / 16.6).
+bool short_by_element(const GemmArgs& g) { return (long)g.M * g.N * g.nz <= 1L << (g.K <= 3 || g.N < 16 ? 21 : 20); }
 constexpr int kShortGrid = 1 << 16;
 template <typename T, typename TC, int R>
 __global__ __launch_bounds__(256) void short_kernel(GemmArgs g, int cols, long tiles_n, long tiles) {
@@ -406,11 +424,14 @@ __global__ __launch_bounds__(256) void short_kernel(GemmArgs g, int cols, long t
 }
 template <typename T, typename TC>
 hipError_t launch_short(const GemmArgs& g, hipStream_t s) {
+  if (short_by_element(g)) {
+    hipLaunchKernelGGL((short_element_kernel<T, TC>), dim3(cdiv((long)g.M * g.N, 256), g.nz), dim3(256), 0, s, g);
+    return hipGetLastError();
+  }
   int cols = 16;
   while (cols < 256 && cols < g.N) cols *= 2;
   const int par = 256 / cols;
-  const long size = (long)g.M * g.N * g.nz;
-  const int r = g.M >= 16 * par && size >= 1L << 20 ? 16 : g.M >= 4 * par && size >= 1L << 18 ? 4 : 1;      // rows a thread, while there are work-groups for the device
+  const int r = g.M >= 16 * par ? 16 : g.M >= 4 * par ? 4 : 1;                                                // rows a thread
   const long tiles_n = ((long)g.N + cols - 1) / cols, tiles = tiles_n * (((long)g.M + r * par - 1) / (r * par));
   const dim3 grid((unsigned)std::min(tiles, (long)kShortGrid), g.nz);
   if (r == 16) hipLaunchKernelGGL((short_kernel<T, TC, 16>), grid, dim3(256), 0, s, g, cols, tiles_n, tiles);

@@ -145,9 +145,10 @@ def test_product_of_rows_at_any_element(M, N, K, gap, at):
 
 
 @pytest.mark.parametrize("dt,bk", [(torch.bfloat16, 1), (torch.bfloat16, 0), (torch.float32, 1), (torch.float32, 0)])
-@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 300, 2), (17, 5, 3), (64, 1000, 1), (255, 1025, 3), (2037, 515, 2), (4100, 257, 1), (70001, 17, 3)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 300, 2), (17, 5, 3), (64, 1000, 1), (255, 1025, 3), (2037, 515, 2), (4100, 257, 1), (70001, 17, 3),
+                                   (3, 1000001, 1), (9, 300001, 3), (2113, 1025, 3), (250001, 9, 1)])
 def test_product_of_less_than_a_chunk(M, N, K, dt, bk):
-    """K below 16 bytes of a k-contiguous A; one, four and sixteen rows a thread, tiles of 16 to 256 columns, remainders of both; what lies behind the rows is NaN."""
+    """K below 16 bytes of a k-contiguous A; an element a thread, then tiles of 16 to 256 columns with one, four and sixteen rows a thread, remainders of both; what lies behind the rows is NaN."""
     from paper_1805_05225_amd import binding as Bn
     K += 4 if dt == torch.bfloat16 and N % 2 else 0
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
