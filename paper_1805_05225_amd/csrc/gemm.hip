@@ -453,6 +453,14 @@ hipError_t dispatch(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// A handful of columns in bfloat16 and little K, rows or K of whole 8 bytes but not 16: the 128 x 128 tiles of gemm_tile.hip store a row's few bytes at a time and take as long as the
+// kernel here takes for two stages (us, there / here: 6604 x 4 x 16 11.9 / 8.8, 1684 x 16 x 12 12.1 / 9.1, 2004 x 8 x 80 12.4 / 10.2; in float 8 / 9, and from 36 columns or 100 k on there).
+// Less than a tile of rows is faster there (m-contiguous 28 x 12 x 20 5.7 / 7.0, 80 x 4 x 20 7.8 / 9.5).  The kernel here knows no padding of K and no ranges.
+bool narrow_result(const GemmArgs& g) {
+  const bool whole = ((g.lda | g.ldb | (g.a_kcontig ? g.K : 0)) & 7) == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 15) == 0;
+  return g.in_bf16 && g.out_bf16 && !whole && !g.k_phys_rows && !g.parts && g.M > kBM && g.N <= 32 && g.K < (g.b_kcontig ? 100 : 72);
+}
+
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
@@ -463,6 +471,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     if (r != FewRoute::kHere) return r == FewRoute::kTile ? launch_gemm_tile(g, s) : launch_gemm_nt(g, s);
   }
   if (gemm_skinny_ok(g)) return launch_gemm_skinny(g, s);
+  if (narrow_result(g)) return dispatch<bf16_t, bf16_t>(g, s);
   if (gemm_nn_ok(g) && (gemm_nn_pays(g) || !gemm_tile_ok(g))) return launch_gemm_nt(g, s);
   if (gemm_tile_ok(g) && (gemm_tile_small(g.M, g.N, g.nz) || (g.a_kcontig && !g.b_kcontig))) return launch_gemm_tile(g, s);
   if (gemm_nt_ok(g)) return launch_gemm_nt(g, s);

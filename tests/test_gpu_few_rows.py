@@ -144,6 +144,25 @@ def test_product_of_rows_at_any_element(M, N, K, gap, at):
         assert (C[:, N] == 7.).all()
 
 
+@pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 0)])
+@pytest.mark.parametrize("M,N,K", [(129, 4, 12), (260, 8, 68), (1684, 16, 76), (2004, 32, 96), (3000, 12, 100), (129, 36, 20), (128, 4, 20), (8104, 24, 20)])
+def test_product_of_a_handful_of_columns(M, N, K, ak, bk):
+    """Results in bfloat16, rows of whole 8 bytes but not 16, either side of narrow_result; what lies between the rows is NaN."""
+    from paper_1805_05225_amd import binding as Bn
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+
+    def rows(r, k):
+        ld = k + (4 if k % 8 == 0 else 8)
+        return torch.cat([torch.randn(r, k, generator=g, device="cuda"), torch.full((r, ld - k), float("nan"), device="cuda")], 1).bfloat16()
+    A, B = rows(M, K) if ak else rows(K, M), rows(N, K) if bk else rows(K, N)
+    a, b = (A[:, :K] if ak else A[:, :M].T).double(), (B[:, :K].T if bk else B[:, :N]).double()
+    C = torch.full((M, N + 1), 7., dtype=torch.bfloat16, device="cuda")
+    assert Bn.lib.lstm_gemm(1, 1, ak, bk, M, N, K, A.data_ptr(), A.shape[1], B.data_ptr(), B.shape[1], C.data_ptr(), N + 1, None, 0, None, 1, 0, Bn._stream()) == 0
+    want = a @ b
+    # (K sums of float, then rounded once)
+    assert ((C[:, :N].double() - want).abs() <= K * 2.0 ** -24 * (a.abs() @ b.abs()) + 2.0 ** -8 * want.abs()).all() and (C[:, N] == 7.).all()
+
+
 @pytest.mark.parametrize("dt,bk", [(torch.bfloat16, 1), (torch.bfloat16, 0), (torch.float32, 1), (torch.float32, 0)])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 300, 2), (17, 5, 3), (64, 1000, 1), (255, 1025, 3), (2037, 515, 2), (4100, 257, 1), (70001, 17, 3),
                                    (3, 1000001, 1), (9, 300001, 3), (2113, 1025, 3), (250001, 9, 1)])
